@@ -337,6 +337,15 @@ int semicrf_entropies(const float *pos_marg, const float *bdy_post, const int32_
                       int C, float *h_pos, float *h_bdy, void *stream);
 
 /*
+ * The same values with a workspace, spread over the whole chip (semicrf_entropies has one workgroup per sequence,
+ * which long sequences wait for).  semicrf_entropies_workspace_bytes is host only and pure; its `bytes` is a host
+ * pointer.  Sizes beyond B = 65535 return SEMICRF_EUNSUPPORTED.
+ */
+int semicrf_entropies_workspace_bytes(int B, int T, size_t *bytes);
+int semicrf_entropies_ws(const float *pos_marg, const float *bdy_post, const int32_t *lengths, int B, int T,
+                         int C, void *workspace, size_t workspace_bytes, float *h_pos, float *h_bdy, void *stream);
+
+/*
  * Measurement aid: semicrf_fwd_bwd with five caller-owned HIP events recorded on
  * `stream`: stage_events[0] before the first kernel and stage_events[1..4] after
  * each of the four stages

@@ -21,7 +21,7 @@ EXPORTS = ("semicrf_version", "semicrf_strerror", "semicrf_workspace_bytes",
            "semicrf_fwd_bwd_boundary", "semicrf_entropies", "semicrf_viterbi_workspace_bytes",
            "semicrf_viterbi", "semicrf_durtrans_workspace_bytes", "semicrf_durtrans_ckpt_interval", "semicrf_logz_fwd_durtrans",
            "semicrf_fwd_bwd_durtrans", "semicrf_fwd_bwd_static", "semicrf_seq_report",
-           "semicrf_ckpt_interval_low_memory")
+           "semicrf_ckpt_interval_low_memory", "semicrf_entropies_workspace_bytes", "semicrf_entropies_ws")
 SEMICRF_STATIC_WORKSPACE_BYTES = 64 << 20
 SEMICRF_CENTER = 1
 SEMICRF_SEQUENTIAL_SCAN = 2
@@ -101,6 +101,10 @@ def load():
     lib.semicrf_viterbi.argtypes = [vp] * 8 + [ci, ci, ci, ci, cu, vp, sz] + [vp] * 5
     lib.semicrf_entropies.restype = ci
     lib.semicrf_entropies.argtypes = [vp, vp, vp, ci, ci, ci, vp, vp, vp]
+    lib.semicrf_entropies_workspace_bytes.restype = ci
+    lib.semicrf_entropies_workspace_bytes.argtypes = [ci, ci, ctypes.POINTER(sz)]
+    lib.semicrf_entropies_ws.restype = ci
+    lib.semicrf_entropies_ws.argtypes = [vp, vp, vp, ci, ci, ci, vp, sz, vp, vp, vp]
     lib.semicrf_durtrans_workspace_bytes.restype = ci
     lib.semicrf_durtrans_workspace_bytes.argtypes = [ci, ci, ci, ci, ci, ci, ctypes.POINTER(sz)]
     lib.semicrf_durtrans_ckpt_interval.restype = ci
@@ -392,9 +396,17 @@ def semicrf_entropies(pos_marg, bdy_post, lengths):
     B, T, C = pos_marg.shape
     h_pos = torch.empty(B, dtype=torch.float32, device=pos_marg.device)
     h_bdy = torch.empty(B, dtype=torch.float32, device=pos_marg.device)
-    _check(load().semicrf_entropies(_ptr(pos_marg, torch.float32), _ptr(bdy_post, torch.float32),
-                                    _ptr(lengths, torch.int32), B, T, C, h_pos.data_ptr(), h_bdy.data_ptr(),
-                                    _stream()))
+    if B > 65535:  # more sequences than the form with a workspace takes
+        _check(load().semicrf_entropies(_ptr(pos_marg, torch.float32), _ptr(bdy_post, torch.float32),
+                                        _ptr(lengths, torch.int32), B, T, C, h_pos.data_ptr(), h_bdy.data_ptr(),
+                                        _stream()))
+        return h_pos, h_bdy
+    n = ctypes.c_size_t(0)
+    _check(load().semicrf_entropies_workspace_bytes(B, T, ctypes.byref(n)))
+    workspace = torch.empty(n.value, dtype=torch.uint8, device=pos_marg.device)  # torch aligns to 512 bytes
+    _check(load().semicrf_entropies_ws(_ptr(pos_marg, torch.float32), _ptr(bdy_post, torch.float32),
+                                       _ptr(lengths, torch.int32), B, T, C, workspace.data_ptr(), n.value,
+                                       h_pos.data_ptr(), h_bdy.data_ptr(), _stream()))
     return h_pos, h_bdy
 
 

@@ -988,6 +988,30 @@ int semicrf_viterbi_workspace_bytes(int B, int T, int K, int C, size_t *bytes)
 int semicrf_viterbi(const float *emis, const int32_t *lengths, const float *trans, const float *dur,
                     const float *proj_start, const float *proj_end, const float *pi_start,
                     const float *pi_end, int B, int T, int K, int C, unsigned flags, void *workspace,
+    return check_launch();
+}
+
+int semicrf_entropies_workspace_bytes(int B, int T, size_t *bytes)
+{
+    if (B < 1 || T < 1 || !bytes) return SEMICRF_EINVAL;
+    *bytes = (size_t)B * (((size_t)T + ENT_TOK - 1) / ENT_TOK) * 3 * sizeof(double);
+    return SEMICRF_OK;
+}
+
+int semicrf_entropies_ws(const float *pos_marg, const float *bdy_post, const int32_t *lengths, int B, int T, int C,
+                         void *workspace, size_t workspace_bytes, float *h_pos, float *h_bdy, void *stream)
+{
+    if (B < 1 || T < 1 || C < 1) return SEMICRF_EINVAL;
+    if ((!h_pos && !h_bdy) || (h_pos && !pos_marg) || (h_bdy && !bdy_post)) return SEMICRF_EINVAL;
+    if (B > 65535 || C > (1 << 20)) return SEMICRF_EUNSUPPORTED;  // grid y; elements of a workgroup in 32 bits
+    size_t need = 0;
+    (void)semicrf_entropies_workspace_bytes(B, T, &need);
+    if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < need) return SEMICRF_EWORKSPACE;
+    const int npart = (int)(((long long)T + ENT_TOK - 1) / ENT_TOK);
+    hipLaunchKernelGGL(k_ent_part, dim3(npart, B), dim3(NT), 0, (hipStream_t)stream, pos_marg, bdy_post, lengths, T, C,
+                       h_pos ? 1 : 0, h_bdy ? 1 : 0, (double *)workspace);
+    hipLaunchKernelGGL(k_ent_fin, dim3(B), dim3(NT), 0, (hipStream_t)stream, (const double *)workspace, lengths, T, npart,
+                       h_pos, h_bdy);
                     size_t workspace_bytes, float *score, int32_t *labels, int32_t *starts, int32_t *nseg,
                     void *stream)
 {
