@@ -55,7 +55,9 @@ struct Params {
     double *nu;         // [B][C]
     double *chsum;      // [B][NCH][C] chunk sums, then exclusive chunk offsets
     double *chmax;      // [B][NCH]
-    double *tabmax;     // [2]: max dur, max trans
+    double *tabmax;     // [ntab][2]: max dur, max trans of each table workgroup's share
+    double logKC;       // log(K * C)
+    int ntab;           // workgroups that build the tables
     double *W;          // [K][C]
     double *Etr;        // [C][C]
     double2 *EI;        // [B][T+1][C]  .x = ES = exp(S - n ln2), .y = 1/ES

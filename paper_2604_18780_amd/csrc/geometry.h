@@ -11,6 +11,7 @@ namespace semicrf_impl {
 constexpr int NT = 256;          // threads per workgroup in the scan kernels
 constexpr int PREP_CH = 256;     // positions per prefix-sum chunk (multiple of JMAX)
 constexpr int JMAX = 32;         // largest scaling block
+constexpr int TAB_BLOCKS_MAX = 64;  // most workgroups the exp tables (and their maxima) are spread over
 constexpr int NSLOT_MAX = 1024;  // resident tasks of the interval kernel (one wave per SIMD)
 constexpr int LOWMEM_SLOTS_PER_SEQ = 8;  // row slots per sequence in the low-memory plan
 constexpr int GRAD_CMAX = 64;    // most labels the gradient path holds transition accumulators for

@@ -123,7 +123,7 @@ int make_plan(int B, int T, int K, int C, int ckpt_interval, int want_grad, Plan
     sz[PL_NU] = b * c * 8;
     sz[PL_CHSUM] = b * pl->NCH * c * 8;
     sz[PL_CHMAX] = b * pl->NCH * 8;
-    sz[PL_TABMAX] = 2 * 8;
+    sz[PL_TABMAX] = 2 * TAB_BLOCKS_MAX * 8;
     sz[PL_W] = k * c * 8;
     sz[PL_ETR] = c * c * 8;
     sz[PL_EI] = b * t1 * c * 16;

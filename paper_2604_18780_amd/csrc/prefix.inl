@@ -2,9 +2,19 @@
 // Included by semicrf.hip inside its anonymous namespace (after common.h); not a translation unit of its own.
 
 // ---------------------------------------------------------------------------
-// exp(dur), exp(trans) in fp64 and the maxima that bound per-step growth.
+// exp(dur), exp(trans) in fp64 and the maxima that bound per-step growth.  The table entries are spread over
+// p.ntab workgroups (TAB_ITEMS entries each); every one leaves the two maxima of its share.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void tables_body(const Params &p)
+constexpr int TAB_ITEMS = 8 * NT;
+inline int tables_blocks(const Params &p)
+{
+    if (!p.dur || (!p.trans && !p.trans3)) return 1;
+    const size_t n = (size_t)p.K * p.C + (size_t)p.C * p.C * (p.trans3 ? (size_t)p.K : 1);
+    const size_t w = (n + TAB_ITEMS - 1) / TAB_ITEMS;
+    return (int)(w < (size_t)TAB_BLOCKS_MAX ? w : (size_t)TAB_BLOCKS_MAX);
+}
+
+__device__ __forceinline__ void tables_body(const Params &p, const int blk)
 {
     __shared__ double red[2 * (NT / 64)];
     const int tid = threadIdx.x;
@@ -14,19 +24,19 @@ __device__ __forceinline__ void tables_body(const Params &p)
         return;
     }
     double mxd = -DBL_MAX, mxt = -DBL_MAX;
+    const int first = blk * NT + tid, step = p.ntab * NT;
     if (p.trans3) {  // one transition matrix per duration: only the maxima are needed here
-        for (int i = tid; i < KC; i += NT) mxd = fmax(mxd, (double)p.dur[i]);
-        for (int i = tid; i < p.K * CC; i += NT) mxt = fmax(mxt, (double)p.trans3[i]);
+        for (int i = first; i < KC; i += step) mxd = fmax(mxd, (double)p.dur[i]);
+#pragma unroll 8
+        for (int i = first; i < p.K * CC; i += step) mxt = fmax(mxt, (double)p.trans3[i]);
     } else {
-        for (int i = tid; i < KC; i += NT) {
-            double v = (double)p.dur[i];
-            p.W[i] = exp(v);
-            mxd = fmax(mxd, v);
-        }
-        for (int i = tid; i < CC; i += NT) {
-            double v = (double)p.trans[i];
-            p.Etr[i] = exp(v);
-            mxt = fmax(mxt, v);
+#pragma unroll 4
+        for (int i = first; i < KC + CC; i += step) {
+            const bool isd = i < KC;
+            const double v = (double)(isd ? p.dur[i] : p.trans[i - KC]);
+            (isd ? p.W : p.Etr - KC)[i] = exp(v);
+            mxd = fmax(mxd, isd ? v : -DBL_MAX);
+            mxt = fmax(mxt, isd ? -DBL_MAX : v);
         }
     }
     // maxima: inside each wave by shuffles, then over the waves (any order)
@@ -43,7 +53,7 @@ __device__ __forceinline__ void tables_body(const Params &p)
     if (tid < 2) {
         double m = red[tid * (NT / 64)];
         for (int i = 1; i < NT / 64; ++i) m = fmax(m, red[tid * (NT / 64) + i]);
-        p.tabmax[tid] = m;
+        p.tabmax[2 * blk + tid] = m;
     }
 }
 
@@ -72,16 +82,20 @@ __device__ __forceinline__ void colsum_body(const Params &p, const int b, const 
         }
     }
     // the boundary projections move a message like an emission does: their maxima are added
-    double mps = 0.0, mpe = 0.0;
-    if (r < R && (p.proj_start || p.proj_end)) {
-        const size_t o = ((size_t)b * p.T) * C;
-        for (int u = u0 + r; u < u1; u += R) {
-            if (p.proj_start) mps = fmax(mps, fabs((double)p.proj_start[o + (size_t)u * C + c]));
-            if (p.proj_end) mpe = fmax(mpe, fabs((double)p.proj_end[o + (size_t)u * C + c]));
+    float mps = 0.f, mpe = 0.f;
+    auto absmax = [&](const float *a) {
+        float m = 0.f;
+        if (a && r < R) {
+            a += ((size_t)b * p.T) * C + c;
+#pragma unroll 8
+            for (int u = u0 + r; u < u1; u += R) m = fmaxf(m, fabsf(a[(size_t)u * C]));
         }
-    }
+        return m;
+    };
+    mps = absmax(p.proj_start);
+    mpe = absmax(p.proj_end);
     // the maxima first inside each wave (threads that took no row hold zeros; a maximum does not care for order)
-    double mp = mps + mpe;
+    double mp = (double)mps + (double)mpe;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         mx = fmax(mx, __shfl_xor(mx, off));
@@ -108,20 +122,40 @@ __device__ __forceinline__ void colsum_body(const Params &p, const int b, const 
     }
 }
 
-// One launch for both: workgroup 0 builds the tables, workgroup 1 + b*NCH + ch sums a chunk.
+// One launch for both: the first p.ntab workgroups build the tables, workgroup p.ntab + b*NCH + ch sums a chunk.
 template <int ET>
 __global__ __launch_bounds__(NT) void k_colsum(Params p)
 {
-    if (blockIdx.x == 0) {
-        tables_body(p);
+    if ((int)blockIdx.x < p.ntab) {
+        tables_body(p, blockIdx.x);
         return;
     }
-    const int id = blockIdx.x - 1;
+    const int id = blockIdx.x - p.ntab;
     colsum_body<ET>(p, id / p.NCH, id % p.NCH);
 }
 
+// Scaling block length J and the range flag of a sequence: fm = max |f - nu| over its positions and labels, boundary
+// terms included.  tabmax: the maxima of the p.ntab table workgroups.
+__device__ __forceinline__ SeqHdr seq_header(const Params &p, const int L, const double fm)
+{
+    double dmax = p.tabmax[0], tmax = p.tabmax[1];
+    for (int i = 1; i < p.ntab; ++i) {
+        dmax = fmax(dmax, p.tabmax[2 * i]);
+        tmax = fmax(tmax, p.tabmax[2 * i + 1]);
+    }
+    double grow = fm + fmax(dmax, 0.0) + fmax(tmax, 0.0) + p.logKC;
+    double shrink = fm + fmax(-dmax, 0.0) + fmax(-tmax, 0.0);
+    double r = fmax(fmax(grow, shrink), 1e-9);
+    int J = 1, flags = 0;
+    if (!(r <= RANGE_NATS)) flags = 1;  // also catches NaN
+    while (J < JMAX && (double)(2 * J) * r <= RANGE_NATS) J *= 2;
+    SeqHdr h;
+    h.L = L; h.J = J; h.flags = flags; h.pad = 0; h.logZ = 0.0; h.logZb = 0.0;
+    return h;
+}
+
 // ---------------------------------------------------------------------------
-// Eq. 1, stage 2: nu = mean over valid positions; chunk sums -> exclusive
+// Eq. 1, stage 2, for sequences of many chunks: nu = mean over valid positions; chunk sums -> exclusive
 // offsets of the centred prefix sum; scaling block length J.  grid B.
 // ---------------------------------------------------------------------------
 constexpr int PREP_NT = 1024;  // one workgroup per sequence: as many threads as a workgroup may have
@@ -184,91 +218,250 @@ __global__ __launch_bounds__(PREP_NT) void k_prep_seq(Params p)
             if (p.pi_start) npi = fmax(npi, fabs((double)p.pi_start[i]));
             if (p.pi_end) npi = fmax(npi, fabs((double)p.pi_end[i]));
         }
-        fm += nm + 2.0 * npi;
-        double dmax = p.tabmax[0], tmax = p.tabmax[1];
-        double grow = fm + fmax(dmax, 0.0) + fmax(tmax, 0.0) + log((double)p.K * (double)C);
-        double shrink = fm + fmax(-dmax, 0.0) + fmax(-tmax, 0.0);
-        double r = fmax(fmax(grow, shrink), 1e-9);
-        int J = 1, flags = 0;
-        if (!(r <= RANGE_NATS)) flags = 1;  // also catches NaN
-        while (J < JMAX && (double)(2 * J) * r <= RANGE_NATS) J *= 2;
-        SeqHdr h;
-        h.L = L; h.J = J; h.flags = flags; h.pad = 0; h.logZ = 0.0; h.logZb = 0.0;
-        p.hdr[b] = h;
+        p.hdr[b] = seq_header(p, L, fm + nm + 2.0 * npi);
     }
 }
 
 // ---------------------------------------------------------------------------
 // Eq. 2: centred prefix sums S[t,c] (fp64), the per-block exponents n_j(c) and the pair
-// (ES, 1/ES), ES = exp(S - n ln2).  grid (NCH,B), 256 threads: a chunk of PREP_CH
-// positions is cut into 8 segments of 32 (a multiple of every scaling block length), thread
-// (segment, label) first sums its segment, the segment sums are combined in segment order,
-// then the thread walks its segment again and writes.  Labels beyond 32 take further turns.
+// (ES, 1/ES), ES = exp(S - n ln2).  grid (NCH, B), 256 threads; a workgroup takes one chunk of PREP_CH positions.
+//
+// INLINE: the workgroup also does what k_prep_seq does, for its own chunk: it reads ALL chunk sums of its sequence
+// (label totals -> nu, the part before its chunk -> offset) and the chunk maxima (-> J); the first chunk's workgroup
+// leaves nu and the header for the later kernels.  That is NCH*C doubles per workgroup from L2 instead of a launch of
+// one workgroup per sequence (9 us at 391 chunks, 6 us at 2), and it grows like NCH^2: up to PREP_INLINE chunks.
+//
+// A chunk is cut into 32 segments of PREP_SEG = 8 positions; an item is (segment, label), labels fastest, so that a
+// wave reads and writes whole cache lines.  An item loads its 8 emissions at once and adds them up, the segment sums
+// of a label are scanned by one thread, then every item walks its 8 positions from its exact start.  (Segments of 32
+// positions walked with one dependent load each took 25 us for a single chunk, all of it latency.)
 // ---------------------------------------------------------------------------
-constexpr int PREP_SEG = 32;
-static_assert(PREP_CH == 8 * PREP_SEG && JMAX <= PREP_SEG && NT == 256, "k_prefix geometry");
+constexpr int PREP_SEG = 8;
+constexpr int PREP_NSEG = PREP_CH / PREP_SEG;
+constexpr int PREP_INLINE = 512;
+static_assert(PREP_CH % JMAX == 0 && JMAX % PREP_SEG == 0 && NT == 256 && PREP_NSEG == 32, "k_prefix geometry");
 
-template <bool BTERMS, int ET>  // any boundary term of Eq. 4 present; emission storage type
+// 1/x to the last bit or two: hardware estimate and two Newton steps (x is a finite positive exp)
+__device__ __forceinline__ double recip(const double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
+// exp by the reduction x = n ln2 + r, |r| <= ln2 / 2, and the Taylor polynomial of degree 13 (remainder below 5e-18);
+// without the library's special cases: arguments beyond +-708 overflow to inf or 0 in the scaling, NaN stays NaN.
+__device__ __forceinline__ double exp_inner(const double x)
+{
+    constexpr double LN2_HI = 0x1.62e42fefa39efp-1, LN2_LO = 0x1.abc9e3b39803fp-56;  // ln 2 in two parts
+    const double n = rint(x * LOG2E);
+    const double r = fma(n, -LN2_LO, fma(n, -LN2_HI, x));
+    double q = 1.0 / 6227020800.0;
+    q = fma(q, r, 1.0 / 479001600.0);
+    q = fma(q, r, 1.0 / 39916800.0);
+    q = fma(q, r, 1.0 / 3628800.0);
+    q = fma(q, r, 1.0 / 362880.0);
+    q = fma(q, r, 1.0 / 40320.0);
+    q = fma(q, r, 1.0 / 5040.0);
+    q = fma(q, r, 1.0 / 720.0);
+    q = fma(q, r, 1.0 / 120.0);
+    q = fma(q, r, 1.0 / 24.0);
+    q = fma(q, r, 1.0 / 6.0);
+    q = fma(q, r, 0.5);
+    q = fma(q, r, 1.0);
+    q = fma(q, r, 1.0);
+    return ldexp(q, (int)n);
+}
+
+// BTERMS: any boundary term of Eq. 4 present, or the log-domain pair of the max semiring; ET: emission storage type
+template <bool BTERMS, int ET, bool INLINE>
 __global__ __launch_bounds__(NT) void k_prefix(Params p)
 {
-    __shared__ double segsum[8][PREP_SEG + 1];
-    const int b = blockIdx.y, ch = blockIdx.x;
-    const int seg = threadIdx.x >> 5, cl = threadIdx.x & 31;
-    const int C = p.C;
-    const SeqHdr h = p.hdr[b];
-    const int L = h.L, J = h.J;
-    const int t0 = ch * PREP_CH + seg * PREP_SEG;
-    const int tend = min(t0 + PREP_SEG, p.T + 1);
+    extern __shared__ double lds_raw[];  // [PREP_NSEG][C] segment sums, then starts; INLINE: + [C] nu
+    __shared__ double red2[2 * NT];
+    __shared__ double redm[NT / 64];
+    __shared__ SeqHdr hs;
+    const int b = blockIdx.y, ch = blockIdx.x, tid = threadIdx.x;
+    const int C = p.C, NCH = p.NCH;
+    double *seg = lds_raw, *nus = lds_raw + PREP_NSEG * C;
+    int L, J;
+    double off = 0.0;  // threads tid < C: centred prefix sum at the chunk's first position
+    if (INLINE) {
+        L = seq_len(p, b);
+        const int G = NT / C, g = tid / C, c = tid % C;
+        const double *cs = p.chsum + (size_t)b * NCH * C + c;
+        double tot = 0.0, pre = 0.0;
+        if (g < G) {
+#pragma unroll 8
+            for (int i = g; i < NCH; i += G) {
+                const double v = cs[(size_t)i * C];
+                tot += v;
+                pre += i < ch ? v : 0.0;
+            }
+        }
+        double fm = 0.0;
+        for (int i = tid; i < NCH; i += NT) fm = fmax(fm, p.chmax[(size_t)b * NCH + i]);
+        red2[tid] = tot;
+        red2[NT + tid] = pre;
+        __syncthreads();
+        double nm = 0.0;
+        if (tid < C) {
+            tot = 0.0;
+            for (int gg = 0; gg < G; ++gg) {
+                tot += red2[gg * C + tid];
+                off += red2[NT + gg * C + tid];
+            }
+            const double nu = (p.center && L > 0) ? tot / (double)L : 0.0;
+            off -= (double)min(ch * PREP_CH, L) * nu;
+            nus[tid] = nu;
+            if (ch == 0) p.nu[(size_t)b * C + tid] = nu;
+            nm = fabs(nu);
+        }
+        // maxima of |f|, of |nu| and of the scalar boundaries: inside each wave by shuffles, then over the waves
+        double npi = 0.0;
+        if (BTERMS && tid < C) {
+            if (p.pi_start) npi = fabs((double)p.pi_start[tid]);
+            if (p.pi_end) npi = fmax(npi, fabs((double)p.pi_end[tid]));
+        }
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            fm = fmax(fm, __shfl_xor(fm, o));
+            nm = fmax(nm, __shfl_xor(nm, o));
+            if (BTERMS) npi = fmax(npi, __shfl_xor(npi, o));
+        }
+        __syncthreads();
+        if ((tid & 63) == 0) {
+            redm[tid >> 6] = fm;
+            red2[tid >> 6] = nm;
+            red2[NT + (tid >> 6)] = npi;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            for (int i = 0; i < NT / 64; ++i) {
+                fm = fmax(fm, redm[i]);
+                nm = fmax(nm, red2[i]);
+                npi = fmax(npi, red2[NT + i]);
+            }
+            hs = seq_header(p, L, fm + nm + 2.0 * npi);
+            if (ch == 0) p.hdr[b] = hs;
+        }
+    } else {
+        const SeqHdr h = p.hdr[b];
+        L = h.L;
+        J = h.J;
+        if (tid < C) {
+            nus[tid] = p.nu[(size_t)b * C + tid];
+            off = p.chsum[((size_t)b * NCH + ch) * C + tid];
+        }
+    }
+    __syncthreads();
+    if (INLINE) J = hs.J;
+    const int Jm = J - 1;
+    const int tc = ch * PREP_CH;
     const size_t row0 = (size_t)b * (p.T + 1);
-    for (int cb = 0; cb < C; cb += 32) {
-        const int c = cb + cl;
-        const bool valid = c < C;
-        const size_t f0 = ((size_t)b * p.T) * C + (valid ? c : 0);
-        const double nu = valid ? p.nu[(size_t)b * C + c] : 0.0;
-        double sum = 0.0;
-        if (valid)
-            for (int t = t0; t < min(tend, L); ++t) sum += emis_at<ET>(p, f0 + (size_t)t * C) - nu;
-        segsum[seg][cl] = sum;
-        __syncthreads();
-        double S = valid ? p.chsum[((size_t)b * p.NCH + ch) * C + c] : 0.0;
-        for (int s2 = 0; s2 < seg; ++s2) S += segsum[s2][cl];
-        __syncthreads();
-        if (!valid) continue;
-        double base = 0.0;
-        for (int t = t0; t < tend; ++t) {
+    const size_t f0 = (size_t)b * p.T * C;
+    const int items = PREP_NSEG * C;
+    auto load = [&](const int t0, const int c, double (&f)[PREP_SEG]) {
+        const size_t o = f0 + (size_t)t0 * C + c;
+        if (t0 + PREP_SEG <= L) {
+#pragma unroll
+            for (int i = 0; i < PREP_SEG; ++i) f[i] = emis_at<ET>(p, o + (unsigned)(i * C));
+        } else {
+#pragma unroll
+            for (int i = 0; i < PREP_SEG; ++i) f[i] = t0 + i < L ? emis_at<ET>(p, o + (unsigned)(i * C)) : 0.0;
+        }
+    };
+    for (int it = tid; it < items; it += NT) {
+        const int s = it / C, c = it - s * C;
+        const int t0 = tc + s * PREP_SEG;
+        double f[PREP_SEG];
+        load(t0, c, f);
+        const double sum = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
+        seg[it] = fma(-(double)max(0, min(PREP_SEG, L - t0)), nus[c], sum);
+    }
+    __syncthreads();
+    if (tid < C) {
+        double v[PREP_NSEG];
+#pragma unroll
+        for (int s = 0; s < PREP_NSEG; ++s) v[s] = seg[s * C + tid];
+        double S = off;
+#pragma unroll
+        for (int s = 0; s < PREP_NSEG; ++s) {
+            seg[s * C + tid] = S;
+            S += v[s];
+        }
+    }
+    __syncthreads();
+    const int bmask = ~((J < PREP_SEG ? 1 : J / PREP_SEG) - 1), logJ = 31 - __clz(J);
+    for (int it = tid; it < items; it += NT) {
+        const int s = it / C, c = it - s * C;
+        const int t0 = tc + s * PREP_SEG;
+        if (t0 > p.T) break;
+        double f[PREP_SEG];
+        load(t0, c, f);
+        const double nu = nus[c];
+        double S = seg[it];
+        // exponent of the scaling block that position t0 lies in: from the sum at the block's first position, which
+        // is the start of a segment of this chunk (blocks longer than a segment), or t0 itself (shorter ones)
+        double n = rint(seg[(s & bmask) * C + c] * LOG2E);
+        double base = n * LN2;
+        double2 *E = p.EI + (row0 + t0) * C + c;
+        if (!BTERMS && J >= PREP_SEG && t0 + PREP_SEG <= L && !p.cum) {
+            if ((t0 & Jm) == 0) p.nbase[(row0 + (size_t)(t0 >> logJ)) * C + c] = (int)n;
+#pragma unroll
+            for (int i = 0; i < PREP_SEG; ++i) {
+                const double es = exp_inner(S - base);
+                E[(unsigned)(i * C)] = make_double2(es, recip(es));
+                S += f[i] - nu;
+            }
+            continue;
+        }
+        // boundary terms: start score of token t, end score of token t-1
+        double xs[PREP_SEG], xe[PREP_SEG];
+        if (BTERMS) {
+            const size_t o = f0 + (size_t)t0 * C + c;
+#pragma unroll
+            for (int i = 0; i < PREP_SEG; ++i) {
+                xs[i] = (p.proj_start && t0 + i < L) ? (double)p.proj_start[o + (unsigned)(i * C)] : 0.0;
+                xe[i] = (p.proj_end && t0 + i >= 1 && t0 + i <= L) ? (double)p.proj_end[o + (unsigned)(i * C) - C] : 0.0;
+            }
+            if (t0 == 0 && L > 0 && p.pi_start) xs[0] += (double)p.pi_start[c];
+            if (p.pi_end) {
+#pragma unroll
+                for (int i = 0; i < PREP_SEG; ++i)
+                    if (t0 + i == L && L >= 1) xe[i] += (double)p.pi_end[c];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < PREP_SEG; ++i) {
+            const int t = t0 + i;
             if (t <= L) {
-                if ((t % J) == 0) {
-                    const double n = rint(S * LOG2E);
-                    p.nbase[(row0 + (size_t)(t / J)) * C + c] = (int)n;
+                if ((t & Jm) == 0) {
+                    n = rint(S * LOG2E);
+                    p.nbase[(row0 + (size_t)(t >> logJ)) * C + c] = (int)n;
                     base = n * LN2;
                 }
                 const double x = S - base;
                 double2 pr;
                 if (!BTERMS) {
-                    const double es = exp(x);
-                    pr = make_double2(es, 1.0 / es);
+                    const double es = exp_inner(x);
+                    pr = make_double2(es, recip(es));
                 } else {
                     // (ES * exp(end score of token t-1), exp(start score of token t) / ES): every message
-                    // that arrives at position t is multiplied by the first, every one that leaves by the second
-                    double xs = 0.0, xe = 0.0;
-                    if (t < L) {
-                        if (p.proj_start) xs = (double)p.proj_start[((size_t)b * p.T + t) * C + c];
-                        if (t == 0 && p.pi_start) xs += (double)p.pi_start[c];
-                    }
-                    if (t >= 1) {
-                        if (p.proj_end) xe = (double)p.proj_end[((size_t)b * p.T + t - 1) * C + c];
-                        if (t == L && p.pi_end) xe += (double)p.pi_end[c];
-                    }
+                    // that arrives at position t is multiplied by the first, every one that leaves by the second;
                     // max semiring: the same pair in the log domain, (S + end score, start score - S)
-                    pr = p.logpair ? make_double2(S + xe, xs - S) : make_double2(exp(x + xe), exp(xs - x));
+                    pr = p.logpair ? make_double2(S + xe[i], xs[i] - S)
+                                   : make_double2(exp_inner(x + xe[i]), exp_inner(xs[i] - x));
                 }
-                p.EI[(row0 + t) * C + c] = pr;
+                E[(unsigned)(i * C)] = pr;
                 if (p.cum) p.cum[(row0 + t) * C + c] = S;
-                if (t < L) S += emis_at<ET>(p, f0 + (size_t)t * C) - nu;
-            } else if (p.cum) {
+                if (t < L) S += f[i] - nu;
+            } else if (p.cum && t <= p.T) {
                 p.cum[(row0 + t) * C + c] = 0.0;
             }
         }
     }
 }
 
+// Dynamic LDS of k_prefix.
+inline size_t prefix_lds(const int C) { return ((size_t)PREP_NSEG * C + C) * sizeof(double); }

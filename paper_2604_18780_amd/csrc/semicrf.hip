@@ -119,19 +119,36 @@ int check_launch()
 }
 
 // prefix stage shared by all entry points
-template <int ET>
-int launch_prep_et(const Params &p, hipStream_t st)
+template <bool BTERMS, int ET, bool INLINE>
+void launch_prefix(const Params &p, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_colsum<ET>, dim3(1 + p.NCH * p.B), dim3(NT), 0, st, p);
-    hipLaunchKernelGGL(k_prep_seq, dim3(p.B), dim3(PREP_NT), 0, st, p);
-    if (p.logpair || p.proj_start || p.proj_end || p.pi_start || p.pi_end)
-        hipLaunchKernelGGL((k_prefix<true, ET>), dim3(p.NCH, p.B), dim3(NT), 0, st, p);
-    else
-        hipLaunchKernelGGL((k_prefix<false, ET>), dim3(p.NCH, p.B), dim3(NT), 0, st, p);
+    // at most 66 KB (C = 256): C <= 64 stays within the default dynamic LDS
+    const size_t lds = prefix_lds(p.C);
+    if (lds > 64 * 1024)
+        (void)hipFuncSetAttribute((const void *)k_prefix<BTERMS, ET, INLINE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)lds);
+    hipLaunchKernelGGL((k_prefix<BTERMS, ET, INLINE>), dim3(p.NCH, p.B), dim3(NT), lds, st, p);
+}
+
+template <int ET>
+int launch_prep_et(Params &p, hipStream_t st)
+{
+    p.ntab = tables_blocks(p);
+    p.logKC = log((double)p.K * (double)p.C);
+    hipLaunchKernelGGL(k_colsum<ET>, dim3(p.ntab + p.NCH * p.B), dim3(NT), 0, st, p);
+    const bool bterms = p.logpair || p.proj_start || p.proj_end || p.pi_start || p.pi_end;
+    if (p.NCH <= PREP_INLINE) {
+        if (bterms) launch_prefix<true, ET, true>(p, st);
+        else launch_prefix<false, ET, true>(p, st);
+    } else {
+        hipLaunchKernelGGL(k_prep_seq, dim3(p.B), dim3(PREP_NT), 0, st, p);
+        if (bterms) launch_prefix<true, ET, false>(p, st);
+        else launch_prefix<false, ET, false>(p, st);
+    }
     return check_launch();
 }
 
-int launch_prep(const Params &p, hipStream_t st)
+int launch_prep(Params &p, hipStream_t st)
 {
     if (p.emis_type == 1) return launch_prep_et<1>(p, st);
     if (p.emis_type == 2) return launch_prep_et<2>(p, st);
