@@ -19,7 +19,12 @@ namespace semicrf_impl {
 
 constexpr double LN2 = 0.6931471805599453094;
 constexpr double LOG2E = 1.4426950408889634074;
-constexpr double RANGE_NATS = 300.0;  // growth allowed inside one scaling block (2x this < ln DBL_MAX)
+constexpr double RANGE_NATS = 300.0;  // per-position growth that is supported (2x this < ln DBL_MAX)
+// Growth allowed inside one scaling block, the pair of a message and the prefix factor together: what is kept stays
+// below e^600 < DBL_MAX = e^709, and a product of two such values always has the tiny factor exp((Y + Y') ln2 - logZ)
+// multiplied in first.  Longer blocks mean fewer rescalings of the window (at 300 the genomic shape had blocks of 8
+// positions, and its window was read and written once per 8 positions only to be scaled).
+constexpr double BLOCK_NATS = 600.0;
 
 struct SeqHdr {
     int L;          // clamped length

@@ -148,7 +148,7 @@ __device__ __forceinline__ SeqHdr seq_header(const Params &p, const int L, const
     double r = fmax(fmax(grow, shrink), 1e-9);
     int J = 1, flags = 0;
     if (!(r <= RANGE_NATS)) flags = 1;  // also catches NaN
-    while (J < JMAX && (double)(2 * J) * r <= RANGE_NATS) J *= 2;
+    while (J < JMAX && (double)(2 * J) * r <= BLOCK_NATS) J *= 2;
     SeqHdr h;
     h.L = L; h.J = J; h.flags = flags; h.pad = 0; h.logZ = 0.0; h.logZb = 0.0;
     return h;
