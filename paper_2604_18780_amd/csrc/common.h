@@ -241,6 +241,138 @@ __device__ __forceinline__ double group_sum(double v)
     return v;
 }
 
+// ---- products of a message vector with the transition matrix inside one wave, without LDS.
+// v_fmac_f64 with the DPP control row_newbcast:n multiplies by the value lane n of the own row of 16 lanes holds, so
+// a vector that lies one entry per lane along a row is contracted by one instruction per entry.  (Through LDS, a
+// store, six 16-byte broadcast reads and their waits: 250 clocks of a position's chain against 160, and half of the
+// scan kernels' LDS traffic.)  The leading s_nop covers the two wait states a DPP read needs after a vector write.
+#define SEMICRF_FD(acc, n, op) "v_fmac_f64_dpp %" #acc ", %2, %" #op " row_newbcast:" #n " row_mask:0xf bank_mask:0xf\n\t"
+__device__ __forceinline__ void row_dot4(const double y, const double *e, double &z0, double &z1)
+{
+    asm("s_nop 1\n\t" SEMICRF_FD(0, 0, 3) SEMICRF_FD(1, 1, 4) SEMICRF_FD(0, 2, 5) SEMICRF_FD(1, 3, 6)
+        : "+&v"(z0), "+&v"(z1) : "v"(y), "v"(e[0]), "v"(e[1]), "v"(e[2]), "v"(e[3]));
+}
+
+__device__ __forceinline__ void row_dot8(const double y, const double *e, double &z0, double &z1)
+{
+    asm("s_nop 1\n\t" SEMICRF_FD(0, 0, 3) SEMICRF_FD(1, 1, 4) SEMICRF_FD(0, 2, 5) SEMICRF_FD(1, 3, 6)
+        SEMICRF_FD(0, 4, 7) SEMICRF_FD(1, 5, 8) SEMICRF_FD(0, 6, 9) SEMICRF_FD(1, 7, 10)
+        : "+&v"(z0), "+&v"(z1)
+        : "v"(y), "v"(e[0]), "v"(e[1]), "v"(e[2]), "v"(e[3]), "v"(e[4]), "v"(e[5]), "v"(e[6]), "v"(e[7]));
+}
+
+__device__ __forceinline__ void row_dot12(const double y, const double *e, double &z0, double &z1)
+{
+    asm("s_nop 1\n\t" SEMICRF_FD(0, 0, 3) SEMICRF_FD(1, 1, 4) SEMICRF_FD(0, 2, 5) SEMICRF_FD(1, 3, 6)
+        SEMICRF_FD(0, 4, 7) SEMICRF_FD(1, 5, 8) SEMICRF_FD(0, 6, 9) SEMICRF_FD(1, 7, 10)
+        SEMICRF_FD(0, 8, 11) SEMICRF_FD(1, 9, 12) SEMICRF_FD(0, 10, 13) SEMICRF_FD(1, 11, 14)
+        : "+&v"(z0), "+&v"(z1)
+        : "v"(y), "v"(e[0]), "v"(e[1]), "v"(e[2]), "v"(e[3]), "v"(e[4]), "v"(e[5]), "v"(e[6]), "v"(e[7]), "v"(e[8]),
+          "v"(e[9]), "v"(e[10]), "v"(e[11]));
+}
+
+__device__ __forceinline__ void row_dot16(const double y, const double *e, double &z0, double &z1)
+{
+    asm("s_nop 1\n\t" SEMICRF_FD(0, 0, 3) SEMICRF_FD(1, 1, 4) SEMICRF_FD(0, 2, 5) SEMICRF_FD(1, 3, 6)
+        SEMICRF_FD(0, 4, 7) SEMICRF_FD(1, 5, 8) SEMICRF_FD(0, 6, 9) SEMICRF_FD(1, 7, 10)
+        SEMICRF_FD(0, 8, 11) SEMICRF_FD(1, 9, 12) SEMICRF_FD(0, 10, 13) SEMICRF_FD(1, 11, 14)
+        SEMICRF_FD(0, 12, 15) SEMICRF_FD(1, 13, 16) SEMICRF_FD(0, 14, 17) SEMICRF_FD(1, 15, 18)
+        : "+&v"(z0), "+&v"(z1)
+        : "v"(y), "v"(e[0]), "v"(e[1]), "v"(e[2]), "v"(e[3]), "v"(e[4]), "v"(e[5]), "v"(e[6]), "v"(e[7]), "v"(e[8]),
+          "v"(e[9]), "v"(e[10]), "v"(e[11]), "v"(e[12]), "v"(e[13]), "v"(e[14]), "v"(e[15]));
+}
+#undef SEMICRF_FD
+
+// rows 0,2 of v in rows 0,1,2,3 as 0,0,2,2 (-> even) and rows 1,3 as 1,1,3,3 (-> odd)
+__device__ __forceinline__ void both_row_parities(const double v, double &even, double &odd)
+{
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    even = __hiloint2double((int)b[0], (int)a[0]);
+    odd = __hiloint2double((int)b[1], (int)a[1]);
+}
+
+// Lane organisation of a wave for CT labels and the transition product in it.  Lane -> (label, group): 64 lanes hold
+// every label GW times.  Labels lie along rows of 16 lanes: one row holds 16 labels (CT = 16, 32, 64), 12 (CT = 24,
+// four lanes idle), or 8 twice (CT = 8).  The matrix column of a lane is split over the two halves of the wave
+// (CT <= 32): half h takes the inputs h*HC .. h*HC+HC-1, which must then lie at lanes 0 .. HC-1 of its rows.
+template <int CT>
+struct RowMap {
+    static constexpr int CTP = CT <= 8 ? 8 : (CT <= 16 ? 16 : (CT <= 32 ? 32 : 64));
+    static constexpr int H = CT <= 32 ? 2 : 1;
+    static constexpr int HC = CT / H;  // inputs per lane
+    static __device__ __forceinline__ int label(const int lane)  // labels >= C and idle lanes: not used
+    {
+        if (CT == 24) {
+            const int i = lane & 15;
+            return i < 12 ? ((lane >> 4) & 1) * 12 + i : 24 + (i - 12);  // idle lanes: numbers beyond every label
+        }
+        return lane % CTP;
+    }
+    static __device__ __forceinline__ int group(const int lane) { return lane / CTP; }
+
+    // y: entry of the vector at the lane's own label, the same in every group.  Returns sum_o y(o) e[o] with e the
+    // lane's part of its column: e[i] belongs to input (lane >> 5) * HC + i (CT <= 32), i (CT = 64).
+    static __device__ __forceinline__ double product(const double y, const double *e)
+    {
+        double z0 = 0.0, z1 = 0.0;
+        if (CT == 64) {
+            double lo, hi, y0, y1, y2, y3;
+            both_halves(y, lo, hi);
+            both_row_parities(lo, y0, y1);
+            both_row_parities(hi, y2, y3);
+            row_dot16(y0, e, z0, z1);
+            row_dot16(y1, e + 16, z0, z1);
+            row_dot16(y2, e + 32, z0, z1);
+            row_dot16(y3, e + 48, z0, z1);
+            return z0 + z1;
+        }
+        const double in = half_inputs(y);
+        if (CT == 8) row_dot4(in, e, z0, z1);
+        else if (CT == 16) row_dot8(in, e, z0, z1);
+        else if (CT == 24) row_dot12(in, e, z0, z1);
+        else row_dot16(in, e, z0, z1);
+        return add_across_32(z0 + z1);
+    }
+
+    // sum of the vector, the same value in every lane (labels >= C must hold zeros)
+    static __device__ __forceinline__ double total(const double y)
+    {
+        double one[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) one[i] = 1.0;
+        double z0 = 0.0, z1 = 0.0;
+        if (CT == 64) {
+            row_dot16(y, one, z0, z1);
+            return add_across_16(add_across_32(z0 + z1));
+        }
+        const double in = half_inputs(y);
+        if (CT == 8) row_dot4(in, one, z0, z1);
+        else if (CT == 16) row_dot8(in, one, z0, z1);
+        else if (CT == 24) row_dot12(in, one, z0, z1);
+        else row_dot16(in, one, z0, z1);
+        return add_across_32(z0 + z1);
+    }
+
+private:
+    // the inputs of the lane's half at lanes 0 .. HC-1 of its row
+    static __device__ __forceinline__ double half_inputs(const double y)
+    {
+        if (CT == 24 || CT == 32) {  // rows hold labels A, B, A, B; the lower half needs A, the upper B
+            double even, odd;
+            both_row_parities(y, even, odd);
+            return (__lane_id() & 32) ? odd : even;
+        }
+        // every row holds all labels: the upper half's rows are rotated by HC lanes
+        constexpr int ROR = 0x120 + (16 - HC);  // row_ror: lane i gets lane (i - n) mod 16, n = 16 - HC
+        const int lo = __double2loint(y), hi = __double2hiint(y);
+        const int lo2 = __builtin_amdgcn_update_dpp(lo, lo, ROR, 0xc, 0xf, false);
+        const int hi2 = __builtin_amdgcn_update_dpp(hi, hi, ROR, 0xc, 0xf, false);
+        return __hiloint2double(hi2, lo2);
+    }
+};
+
 // ---- the lock-step scan on the matrix cores (mscan.hip)
 constexpr int MS_JMIN = 16;  // shortest scaling block that kernel handles; shorter ones are left to the one-wave scan
 bool mscan_applies(int K, int C, int Delta);

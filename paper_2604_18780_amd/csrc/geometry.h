@@ -76,6 +76,47 @@ constexpr size_t wave_lds_doubles(int CT, int NKW)
     return (size_t)(KW + lin_slack(KW)) * CT + (size_t)(CTP - CT) + (size_t)MB * YS;
 }
 
+// Tasks of the scan kernel a SIMD holds by registers: one where the transition column or the duration strip is long.
+constexpr int spec_waves_per_simd(int CT, int NKW) { return (CT == 64 || (CT == 32 && NKW == 64)) ? 1 : 2; }
+
+// Rows of slack of the scan kernels' windows: the window is moved back once per that many positions, which costs a
+// read and a write of every window entry, so the slack takes what LDS the resident tasks of a compute unit leave
+// (up to a whole window), never less than lin_slack.
+// two: the tasks of two waves, which keep more than the window in LDS and are half as many.
+constexpr int spec2_waves_per_simd(int CT, int NKW) { return (CT <= 32 && NKW <= 32) ? 4 : 2; }
+constexpr int scan_slack(int CT, int NKW, bool two)
+{
+    const int CTP = pow2_ge8(CT);
+    const int KW = wave_nk(CT, NKW) * (64 / CTP);
+    const size_t extra = (CTP - CT) + (two ? (size_t)2 * MB * CT + (size_t)2 * MB * CTP + 2 : 0);
+    const size_t least = (size_t)(KW + lin_slack(KW)) * CT + extra;
+    const size_t limit = LDS_LIMIT / sizeof(double);
+    size_t tasks = limit / least;
+    const size_t most = two ? 2 * (size_t)spec2_waves_per_simd(CT, NKW) : 4 * (size_t)spec_waves_per_simd(CT, NKW);
+    if (tasks < 1) tasks = 1;
+    if (tasks > most) tasks = most;
+    const size_t rows = limit / tasks > extra ? (limit / tasks - extra) / CT : 0;
+    int m = rows > (size_t)KW ? (int)(rows - KW) : 0;
+    if (m > KW) m = KW;
+    m &= ~3;
+    return m > lin_slack(KW) ? m : lin_slack(KW);
+}
+
+// LDS of a one-wave scan task: the window.
+constexpr size_t scan_lds_doubles(int CT, int NKW)
+{
+    const int CTP = pow2_ge8(CT);
+    const int KW = wave_nk(CT, NKW) * (64 / CTP);
+    return (size_t)(KW + scan_slack(CT, NKW, false)) * CT + (size_t)(CTP - CT);
+}
+
+// Single-wave tasks of one workgroup of the scan kernel: one per SIMD where their LDS fits.
+constexpr int spec_waves(int CT, int NKW)
+{
+    const size_t lds = scan_lds_doubles(CT, NKW) * sizeof(double);
+    return 4 * lds <= LDS_LIMIT ? 4 : (2 * lds <= LDS_LIMIT ? 2 : 1);
+}
+
 // Single-wave tasks of one workgroup of the interval kernel.
 constexpr int interval_waves(int CT, int NKW) { return CT == 64 ? 4 : (NKW == 64 ? 3 : 1); }
 

@@ -201,15 +201,16 @@ __global__ __launch_bounds__(NT) void k_interval(Params p)
 // ---------------------------------------------------------------------------
 // MB positions per time block; wave_nk, lin_slack and wave_lds_doubles give the window's size (geometry.h).
 
-// Geometry and the window operations shared by the one-wave kernels.
-template <int CT, int NKW>
+// Geometry and the window operations shared by the one-wave kernels.  SLACK: 0 lin_slack, 1 that of the one-wave
+// scan tasks, 2 that of the two-wave ones.
+template <int CT, int NKW, int SLACK = 0>
 struct WaveWin {
     static constexpr int CTP = pow2_ge8(CT);
     static constexpr int RS = CT;
     static constexpr int GW = 64 / CTP;
     static constexpr int NK = wave_nk(CT, NKW);
     static constexpr int KW = NK * GW;
-    static constexpr int M = lin_slack(KW);
+    static constexpr int M = SLACK ? scan_slack(CT, NKW, SLACK == 2) : lin_slack(KW);
     static constexpr int ROWS = KW + M;
     static constexpr int RTOT = ROWS * RS + (CTP - CT);  // lanes c >= C read (and ignore) past a row's end
     static constexpr int H = CT <= 32 ? 2 : 1;
@@ -242,19 +243,28 @@ struct WaveWin {
     }
 
     // Move the live window (newest row r) back to the start of the buffer; returns the new r.
-    // Chunk order keeps the sources ahead of the stores.
+    // Chunk order keeps the sources ahead of the stores; chunks are taken MVB at a time, all of them read before
+    // the first is written (one at a time, a chunk cost an LDS round trip: 24 of them per 16 positions at C = 24).
     template <bool BWD>
     static __device__ __forceinline__ int move(double *ring, int lane, int r)
     {
         constexpr int NCP = (KW * RS + 63) / 64;
+        constexpr int MVB = NCP < 8 ? NCP : 8;
         const int shift = (BWD ? M - r : r - (KW - 1)) * RS;  // doubles, > 0
         const int first = (BWD ? r : r - (KW - 1)) * RS;      // lowest double of the live window
-        for (int u = 0; u < NCP; ++u) {
-            const int i = (BWD ? NCP - 1 - u : u) * 64 + lane;
-            double v = 0.0;
-            if (i < KW * RS) v = ring[first + i];
+        for (int u0 = 0; u0 < NCP; u0 += MVB) {
+            double v[MVB];
+#pragma unroll
+            for (int u = 0; u < MVB; ++u) {
+                const int i = (BWD ? NCP - 1 - u0 - u : u0 + u) * 64 + lane;
+                v[u] = (i >= 0 && i < KW * RS) ? ring[first + i] : 0.0;
+            }
             lds_wave_fence();
-            if (i < KW * RS) ring[first + i + (BWD ? shift : -shift)] = v;
+#pragma unroll
+            for (int u = 0; u < MVB; ++u) {
+                const int i = (BWD ? NCP - 1 - u0 - u : u0 + u) * 64 + lane;
+                if (i >= 0 && i < KW * RS) ring[first + i + (BWD ? shift : -shift)] = v[u];
+            }
             lds_wave_fence();
         }
         return BWD ? M : KW - 1;

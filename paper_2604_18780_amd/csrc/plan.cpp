@@ -15,10 +15,11 @@ bool wave_tasks_per_cu(int K, int C, int *scan, int *interval)
     const int per_lane = (K + GW - 1) / GW;
     if (per_lane > 64) return false;
     const int NKW = per_lane <= 16 ? 16 : (per_lane <= 32 ? 32 : 64);
-    const size_t lds = wave_lds_doubles(CT, NKW) * sizeof(double);
+    const size_t lds = scan_lds_doubles(CT, NKW) * sizeof(double);
     if (lds > LDS_LIMIT) return false;
-    const int fit = (int)(LDS_LIMIT / lds);
-    const int scan_regs = (CT == 64 || (CT == 32 && NKW == 64)) ? 4 : 8;
+    const int sw = spec_waves(CT, NKW);  // tasks come by whole workgroups
+    const int fit = (int)(LDS_LIMIT / (sw * lds)) * sw;
+    const int scan_regs = 4 * spec_waves_per_simd(CT, NKW);
     *scan = fit < scan_regs ? fit : scan_regs;
     const size_t ilds = interval_lds_doubles(CT, NKW) * sizeof(double);
     int iw = ilds <= LDS_LIMIT ? (int)(LDS_LIMIT / ilds) * interval_waves(CT, NKW) : 1;  // else the generic kernel

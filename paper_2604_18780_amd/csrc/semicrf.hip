@@ -246,10 +246,11 @@ int launch_interval(const Params &p, const Plan &pl, hipStream_t st)
 template <int CT, int NKW>
 int launch_spec_k(const Params &p, hipStream_t st, bool both, int warm, int tier)
 {
-    const size_t lds = wave_lds_doubles(CT, NKW) * sizeof(double);
+    const size_t lds = scan_lds_doubles(CT, NKW) * sizeof(double);
+    constexpr int SW = spec_waves(CT, NKW);
     if (lds > LDS_LIMIT) return 1;
     if (hipFuncSetAttribute((const void *)k_spec<CT, NKW>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds) != hipSuccess ||
+                            (int)(SW * lds)) != hipSuccess ||
         hipFuncSetAttribute((const void *)k_spec_repair<CT, NKW>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds) != hipSuccess)
         return SEMICRF_ELAUNCH;
@@ -271,8 +272,8 @@ int launch_spec_k(const Params &p, hipStream_t st, bool both, int warm, int tier
         hipLaunchKernelGGL((k_spec2<CT, NKW>), dim3(p.B * p.N * ndir), dim3(128), lds2, st, p, both ? 1 : 0,
                            warm, tier, rest);
     } else if (warm > 0)
-        hipLaunchKernelGGL((k_spec<CT, NKW>), dim3(p.B * p.N * ndir), dim3(64), lds, st, p, both ? 1 : 0,
-                           warm, tier, rest);
+        hipLaunchKernelGGL((k_spec<CT, NKW>), dim3((p.B * p.N + SW - 1) / SW * ndir), dim3(64 * SW), SW * lds, st, p,
+                           both ? 1 : 0, warm, tier, rest);
     else
         hipLaunchKernelGGL((k_spec_repair<CT, NKW>), dim3(p.B * p.N * ndir), dim3(64), lds, st, p, both ? 1 : 0);
     hipLaunchKernelGGL(k_spec_cmp, dim3(p.N, p.B, ndir), dim3(NT), 0, st, p, tier);
@@ -990,24 +991,6 @@ int semicrf_entropies(const float *pos_marg, const float *bdy_post, const int32_
     return check_launch();
 }
 
-int semicrf_viterbi_workspace_bytes(int B, int T, int K, int C, size_t *bytes)
-{
-    if (!bytes) return SEMICRF_EINVAL;
-    Plan pl;
-    int rc = make_plan(B, T, K, C, 0, 0, &pl);
-    if (rc != SEMICRF_OK) return rc;
-    if (C > 64 || !spec_applies(K, C)) return SEMICRF_EUNSUPPORTED;
-    if (((size_t)T + 1) * C >= ((size_t)1 << 31)) return SEMICRF_EUNSUPPORTED;
-    *bytes = pl.total + viterbi_layout(B, T, C).total;
-    return SEMICRF_OK;
-}
-
-int semicrf_viterbi(const float *emis, const int32_t *lengths, const float *trans, const float *dur,
-                    const float *proj_start, const float *proj_end, const float *pi_start,
-                    const float *pi_end, int B, int T, int K, int C, unsigned flags, void *workspace,
-    return check_launch();
-}
-
 int semicrf_entropies_workspace_bytes(int B, int T, size_t *bytes)
 {
     if (B < 1 || T < 1 || !bytes) return SEMICRF_EINVAL;
@@ -1029,6 +1012,24 @@ int semicrf_entropies_ws(const float *pos_marg, const float *bdy_post, const int
                        h_pos ? 1 : 0, h_bdy ? 1 : 0, (double *)workspace);
     hipLaunchKernelGGL(k_ent_fin, dim3(B), dim3(NT), 0, (hipStream_t)stream, (const double *)workspace, lengths, T, npart,
                        h_pos, h_bdy);
+    return check_launch();
+}
+
+int semicrf_viterbi_workspace_bytes(int B, int T, int K, int C, size_t *bytes)
+{
+    if (!bytes) return SEMICRF_EINVAL;
+    Plan pl;
+    int rc = make_plan(B, T, K, C, 0, 0, &pl);
+    if (rc != SEMICRF_OK) return rc;
+    if (C > 64 || !spec_applies(K, C)) return SEMICRF_EUNSUPPORTED;
+    if (((size_t)T + 1) * C >= ((size_t)1 << 31)) return SEMICRF_EUNSUPPORTED;
+    *bytes = pl.total + viterbi_layout(B, T, C).total;
+    return SEMICRF_OK;
+}
+
+int semicrf_viterbi(const float *emis, const int32_t *lengths, const float *trans, const float *dur,
+                    const float *proj_start, const float *proj_end, const float *pi_start,
+                    const float *pi_end, int B, int T, int K, int C, unsigned flags, void *workspace,
                     size_t workspace_bytes, float *score, int32_t *labels, int32_t *starts, int32_t *nseg,
                     void *stream)
 {

@@ -32,16 +32,16 @@ template <int CT, int NKW, bool BWD, bool repair>
 __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, const int b, const int j,
                                           const int warm)
 {
-    using G = WaveWin<CT, NKW>;
+    using G = WaveWin<CT, NKW, 1>;
+    using R = RowMap<CT>;
     constexpr int CTP = G::CTP, RS = G::RS, NK = G::NK, KW = G::KW, M = G::M, ROWS = G::ROWS;
     constexpr int RTOT = G::RTOT, H = G::H, HC = G::HC;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     const int K = p.K, C = p.C, KC = K * C;
     double *ring = lds_raw;          // [ROWS][RS] (+ pad)
-    double *yv = ring + RTOT;        // [CTP]
     const int Delta = p.Delta, N = p.N;
     const size_t ckstride = (size_t)KC + C;
-    const int c = lane % CTP, g = lane / CTP;
+    const int c = R::label(lane), g = R::group(lane);
     const int hh = H == 2 ? (lane >> 5) : 0;
     const bool cval = c < C;
     const int cc = cval ? c : 0;
@@ -70,14 +70,12 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
         const bool ok = cval && o < C;
         Ereg[i] = ok ? (BWD ? p.Etr[(size_t)c * C + o] : p.Etr[(size_t)o * C + c]) : 0.0;
     }
-    const double2 *ys = (const double2 *)__builtin_assume_aligned(yv + hh * HC, 16);
-
     // ---- start: the state of a sequence that begins (forward) / ends (backward) at s0
     const int s0 = repair ? (BWD ? hi : lo) : (BWD ? min(hi + warm, L) : max(lo - warm, 0));
     for (int i = lane; i < RTOT; i += 64) ring[i] = 0.0;
-    if (lane < CTP) yv[lane] = 0.0;
     lds_wave_fence();
     int r = BWD ? M : KW - 1;  // row of the newest message
+    double ylast = 0.0;        // newest message vector, entry c (the same in every group; 0 beyond C)
     double Y = 0.0;
     if (repair) {
         // the reached state at the boundary: K-deep window in slot order, message vector, scale
@@ -89,7 +87,7 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
             const int d = G::template slot_dist<BWD>(sl, tm, K);
             ring[(BWD ? r + d : r - d) * RS + col] = src[i];
         }
-        if (lane < C) yv[lane] = src[KC + lane];
+        if (cval) ylast = src[KC + c];
         Y = ((BWD ? p.ckYB2 : p.ckYA2) + (size_t)b * (N + 1))[bs];
     } else {
         double q;
@@ -99,10 +97,10 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
             for (int i = 0; i < HC; ++i) z += Ereg[i];
             if (H == 2) z = add_across_32(z);
             q = z * EIc[(size_t)s0 * C].y;
-            if (lane < C) yv[lane] = 1.0;
+            ylast = cval ? 1.0 : 0.0;
         } else {
             q = EIc[(size_t)s0 * C].x;
-            if (lane == 0) yv[0] = 1.0;
+            ylast = c == 0 ? 1.0 : 0.0;
         }
         if (cval && g == 0) ring[r * RS + c] = q;
     }
@@ -118,7 +116,7 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
                 ck[(size_t)sl * C + c] = ring[(BWD ? r + d : r - d) * RS + c];
             }
         }
-        if (lane < C) ck[KC + lane] = yv[lane];
+        if (cval && g == 0) ck[KC + c] = ylast;
         if (lane == 0) *ckY = Y;
     };
     double *ck1 = (BWD ? p.ckB : p.ckA) + ((size_t)b * (N + 1)) * ckstride;
@@ -141,7 +139,7 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
     auto start_rows = [&]() {
         Yrec = Y;
         if (BWD) return;
-        if (keep && writer) aloc[c] = make_double2(yv[c], ring[r * RS + c]);
+        if (keep && writer) aloc[c] = make_double2(ylast, ring[r * RS + c]);
         if (keep && lane == 0) alocY[0] = 0.0;
     };
     if (s0 == tstart && !(BWD && tstart == L)) {
@@ -188,17 +186,9 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
         const bool inchunk = keep && (BWD ? t <= tstart : t >= tstart);  // blocks end at tstart: holds for the whole block
         const bool boundary = BWD ? (t & Jm) == 0 : (t1 & Jm) == 0;
         if (__builtin_expect(boundary, 0)) {
-            // sum of the newest message vector (each half of the wave its half of the labels, as in the
-            // transition product); only its exponent is used, and any power of two would do: scaling is exact
-            double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-            for (int o = 0; o < HC; o += 2) {
-                const double2 vv = ys[o >> 1];
-                s0 += vv.x;
-                s1 += vv.y;
-            }
-            double prevsum = s0 + s1;
-            if (H == 2) prevsum = add_across_32(prevsum);
+            // sum of the newest message vector; only its exponent is used, and any power of two would do: scaling
+            // is exact
+            const double prevsum = R::total(ylast);
             const int ex = safe_exponent(prevsum);
             Y += (double)ex;
             G::template rescale_live<BWD>(ring, g, c, cval, r, dnx - ex);
@@ -242,23 +232,13 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
 #pragma unroll
                 for (int jn = 0; jn < i; ++jn) x = fma(wn[i - 1 - jn], qn[jn], x);
                 const double y = x * (BWD ? e[i].y : e[i].x);
-                yv[c] = y;  // both lane groups the same value; entries beyond C are zero and nobody reads them
-                lds_wave_fence();
-                double z0 = 0.0, z1 = 0.0;
-#pragma unroll
-                for (int o = 0; o < HC; o += 2) {
-                    const double2 vv = ys[o >> 1];
-                    z0 = fma(vv.x, Ereg[o], z0);
-                    z1 = fma(vv.y, Ereg[o + 1], z1);
-                }
-                double z = z0 + z1;
-                if (H == 2) z = add_across_32(z);
+                ylast = y;
+                const double z = R::product(y, Ereg);
                 const double q = z * (BWD ? e[i].x : e[i].y);
                 qn[i] = q;
                 r += BWD ? -1 : 1;
                 if (writer) ring[r * RS + c] = q;
                 if (keep) store_row(rowp + i * rstep, y, q);
-                lds_wave_fence();
             }
         } else {
     #pragma unroll
@@ -268,17 +248,8 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
     #pragma unroll
                     for (int jn = 0; jn < i; ++jn) x = fma(wn[i - 1 - jn], qn[jn], x);
                     const double y = x * (BWD ? e[i].y : e[i].x);
-                    if (cval) yv[c] = y;
-                    lds_wave_fence();
-                    double z0 = 0.0, z1 = 0.0;
-    #pragma unroll
-                    for (int o = 0; o < HC; o += 2) {
-                        const double2 vv = ys[o >> 1];
-                        z0 = fma(vv.x, Ereg[o], z0);
-                        z1 = fma(vv.y, Ereg[o + 1], z1);
-                    }
-                    double z = z0 + z1;
-                    if (H == 2) z = add_across_32(z);
+                    ylast = y;
+                    const double z = R::product(y, Ereg);
                     const double q = z * (BWD ? e[i].x : e[i].y);
                     qn[i] = q;
                     r += BWD ? -1 : 1;
@@ -291,13 +262,13 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
                         if (writer) aloc[(size_t)(t - 1 - i - lo) * C + c] = make_double2(y, q);
                         if (lane == 0) alocY[t - 1 - i - lo] = Y - Yrec;
                     }
-                    lds_wave_fence();
                 } else {
                     qn[i] = 0.0;
                 }
             }
 
         }
+        lds_wave_fence();  // the block's new rows are read by other lanes from here on
         t = tn;
 #pragma unroll
         for (int i = 0; i < MB; ++i) e[i] = en[i];
@@ -309,19 +280,27 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
     record(tend, ck2 + (size_t)iend * ckstride, ckY2 + iend);
 }
 
+// spec_waves(CT, NKW) independent tasks per workgroup, one per wave, no barrier between them.  A workgroup of four
+// waves puts one on each SIMD; single-wave workgroups are placed as the launches before left the dispatcher, and two
+// tasks on one SIMD with another SIMD idle decide how long the launch takes (forward-only genomic scan, 1024 tasks:
+// 227 or 264 us depending on the shape of the kernel before).  The directions fill one half of the grid each, so that
+// a SIMD with two tasks has one of each.
 // rest: only the sequences the lock-step kernel (k_mscan, launched before) leaves out
 template <int CT, int NKW>
-__global__ __launch_bounds__(64) void k_spec(Params p, int both, int warm, int tier, int rest)
+__global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, NKW)) void k_spec(Params p, int both, int warm, int tier, int rest)
 {
+    constexpr int SW = spec_waves(CT, NKW);
     extern __shared__ double lds_raw[];
-    const int ndir = both ? 2 : 1;
-    const int dir = blockIdx.x % ndir;
-    const int task = blockIdx.x / ndir;
+    const int per = both ? gridDim.x / 2 : gridDim.x;
+    const int dir = (int)blockIdx.x >= per ? 1 : 0;
+    const int task = ((int)blockIdx.x - dir * per) * SW + (threadIdx.x >> 6);
     const int b = task / p.N, j = task % p.N;
+    if (b >= p.B) return;
     if (tier > 0 && p.spec_ok[b * 2 + dir]) return;  // accepted by an earlier attempt
     if (rest && p.hdr[b].J >= MS_JMIN) return;
-    if (dir == 0) spec_task<CT, NKW, false, false>(p, lds_raw, b, j, warm);
-    else spec_task<CT, NKW, true, false>(p, lds_raw, b, j, warm);
+    double *lds = lds_raw + (size_t)(threadIdx.x >> 6) * scan_lds_doubles(CT, NKW);
+    if (dir == 0) spec_task<CT, NKW, false, false>(p, lds, b, j, warm);
+    else spec_task<CT, NKW, true, false>(p, lds, b, j, warm);
 }
 
 // The repair attempt of the chunk-parallel scans, for the (sequence, direction) pairs that are still open.

@@ -25,15 +25,16 @@ __host__ __device__ constexpr size_t spec2_lds_doubles()
     const int CTP = pow2_ge8(CT);
     const int KW = wave_nk(CT, NKW) * (64 / CTP);
     // window rows + MB spare rows at both ends (the helper's window starts MB rows behind the newest row),
-    // the message vector, two sets of MB far sums per label, the published exponent
-    return (size_t)(KW + lin_slack(KW) + 2 * MB) * CT + (size_t)(CTP - CT) + (size_t)CTP + (size_t)2 * MB * CTP + 2;
+    // two sets of MB far sums per label, the published exponent
+    return (size_t)(KW + scan_slack(CT, NKW, true) + 2 * MB) * CT + (size_t)(CTP - CT) + (size_t)2 * MB * CTP + 2;
 }
 
 template <int CT, int NKW, bool BWD>
 __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, const int b, const int j,
                                            const int warm)
 {
-    using G = WaveWin<CT, NKW>;
+    using G = WaveWin<CT, NKW, 2>;
+    using R = RowMap<CT>;
     constexpr int CTP = G::CTP, RS = G::RS, NK = G::NK, KW = G::KW, M = G::M, ROWS = G::ROWS, GW = G::GW;
     constexpr int H = G::H, HC = G::HC;
     constexpr int RTOT2 = (ROWS + 2 * MB) * RS + (CTP - CT);
@@ -41,12 +42,11 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
     const bool tip = threadIdx.x < 64;
     const int K = p.K, C = p.C, KC = K * C;
     double *ring = lds_raw + MB * RS;   // logical row 0 (MB spare rows below, MB above)
-    double *yv = lds_raw + RTOT2;       // [CTP]
-    double *farb = yv + CTP;            // [2][MB][CTP] what the older window entries add to the next block
+    double *farb = lds_raw + RTOT2;     // [2][MB][CTP] what the older window entries add to the next block
     int *exv = (int *)(farb + 2 * MB * CTP);
     const int Delta = p.Delta, N = p.N;
     const size_t ckstride = (size_t)KC + C;
-    const int c = lane % CTP, g = lane / CTP;
+    const int c = R::label(lane), g = R::group(lane);
     const int hh = H == 2 ? (lane >> 5) : 0;
     const bool cval = c < C;
     const int cc = cval ? c : 0;
@@ -81,7 +81,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
 
     // ---- start: the state of a sequence that begins (forward) / ends (backward) at s0
     for (int i = threadIdx.x; i < RTOT2; i += 128) lds_raw[i] = 0.0;
-    for (int i = threadIdx.x; i < CTP + 2 * MB * CTP; i += 128) yv[i] = 0.0;
+    for (int i = threadIdx.x; i < 2 * MB * CTP; i += 128) farb[i] = 0.0;
     lds_barrier();
     int r = BWD ? M : KW - 1;  // row of the newest message
     int t = s0;
@@ -102,7 +102,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
             const bool ok = cval && o < C;
             Ereg[i] = ok ? (BWD ? p.Etr[(size_t)c * C + o] : p.Etr[(size_t)o * C + c]) : 0.0;
         }
-        const double2 *ys = (const double2 *)__builtin_assume_aligned(yv + hh * HC, 16);
+        double ylast = 0.0;      // newest message vector, entry c (the same in every group; 0 beyond C)
         double Y = 0.0;
         {
             double q;
@@ -112,10 +112,10 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
                 for (int i = 0; i < HC; ++i) z += Ereg[i];
                 if (H == 2) z = add_across_32(z);
                 q = z * EIc[(size_t)s0 * C].y;
-                if (lane < C) yv[lane] = 1.0;
+                ylast = cval ? 1.0 : 0.0;
             } else {
                 q = EIc[(size_t)s0 * C].x;
-                if (lane == 0) yv[0] = 1.0;
+                ylast = c == 0 ? 1.0 : 0.0;
             }
             if (cval && g == 0) ring[r * RS + c] = q;
         }
@@ -131,7 +131,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
                     ck[(size_t)sl * C + c] = ring[(BWD ? r + d : r - d) * RS + c];
                 }
             }
-            if (lane < C) ck[KC + lane] = yv[lane];
+            if (cval && g == 0) ck[KC + c] = ylast;
             if (lane == 0) *ckY = Y;
         };
         double *ck1 = (BWD ? p.ckB : p.ckA) + ((size_t)b * (N + 1)) * ckstride;
@@ -148,7 +148,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
         auto start_rows = [&]() {
             Yrec = Y;
             if (BWD) return;
-            if (keep && writer) aloc[c] = make_double2(yv[c], ring[r * RS + c]);
+            if (keep && writer) aloc[c] = make_double2(ylast, ring[r * RS + c]);
             if (keep && lane == 0) alocY[0] = 0.0;
         };
         if (s0 == tstart && !(BWD && tstart == L)) {
@@ -185,17 +185,9 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
                 qp[i] = ring[(BWD ? r + i : r - i) * RS + c];   // message of the position i before this block
             }
             if (__builtin_expect(at_boundary(t), 0)) {
-                // sum of the newest message vector, one entry per lane, added up across the wave (the same value in
-                // every lane; only its exponent is used, and any power of two would do: scaling is exact)
-                // (a short vector is summed faster entry by entry)
-                double prevsum = 0.0;
-                if (CT >= 32) {
-                    prevsum = lane < CT ? yv[lane] : 0.0;
-#pragma unroll
-                    for (int off = 1; off < 64; off <<= 1) prevsum += __shfl_xor(prevsum, off);
-                } else {
-                    for (int i = 0; i < CT; ++i) prevsum += yv[i];
-                }
+                // sum of the newest message vector (the same value in every lane; only its exponent is used, and any
+                // power of two would do: scaling is exact)
+                const double prevsum = R::total(ylast);
                 const int ex = safe_exponent(prevsum);
                 Y += (double)ex;
                 if (lane == 0) exv[0] = ex;
@@ -219,17 +211,8 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
 #pragma unroll
                     for (int jn = 0; jn < i; ++jn) x = fma(wn[i - 1 - jn], qn[jn], x);  // inside the block
                     const double y = x * (BWD ? e[i].y : e[i].x);
-                    if (cval) yv[c] = y;
-                    lds_wave_fence();
-                    double z0 = 0.0, z1 = 0.0;
-#pragma unroll
-                    for (int o = 0; o < HC; o += 2) {
-                        const double2 vv = ys[o >> 1];
-                        z0 = fma(vv.x, Ereg[o], z0);
-                        z1 = fma(vv.y, Ereg[o + 1], z1);
-                    }
-                    double z = z0 + z1;
-                    if (H == 2) z = add_across_32(z);
+                    ylast = y;
+                    const double z = R::product(y, Ereg);
                     const double q = z * (BWD ? e[i].x : e[i].y);
                     qn[i] = q;
                     if (writer) ring[(BWD ? r - 1 - i : r + 1 + i) * RS + c] = q;
@@ -241,7 +224,6 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
                         if (writer) store_row(aloc + (size_t)(t - 1 - i - lo) * C + c, y, q);
                         if (lane == 0) alocY[t - 1 - i - lo] = Y - Yrec;
                     }
-                    lds_wave_fence();
                 } else {
                     qn[i] = 0.0;
                 }
@@ -320,9 +302,6 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
         }
     }
 }
-
-// Waves per SIMD the register allocation aims at: four (two tasks) where both roles fit 128 registers.
-constexpr int spec2_waves_per_simd(int CT, int NKW) { return (CT <= 32 && NKW <= 32) ? 4 : 2; }
 
 template <int CT, int NKW>
 __global__ __launch_bounds__(128, spec2_waves_per_simd(CT, NKW)) void k_spec2(Params p, int both, int warm, int tier, int rest)
