@@ -270,6 +270,39 @@ struct WaveWin {
         return BWD ? M : KW - 1;
     }
 
+    // acc[i] += sum over the lane's strip of w[jj + i] * (entry at distance jj from `base`), every entry read once.
+    // The reads go out WRD at a time, one group ahead of the multiply-adds that use them (left to itself the compiler
+    // waits for every pair of reads before its eight multiply-adds: an LDS round trip of ~100 clocks for each 32).
+    static constexpr int WRD = 8;
+    template <bool BWD, int NI>
+    static __device__ __forceinline__ void window_sums(const double *base, const double *w, double (&acc)[NI])
+    {
+        constexpr int NG = (NK + WRD - 1) / WRD;
+        double v[2][WRD];
+        auto read = [&](const int grp, double (&d)[WRD]) {  // furthest entries first
+#pragma unroll
+            for (int u = 0; u < WRD; ++u) {
+                const int jj = NK - 1 - (grp * WRD + u);
+                if (jj >= 0) d[u] = base[(BWD ? jj : NK - 1 - jj) * RS];
+            }
+        };
+        read(0, v[0]);
+#pragma unroll
+        for (int grp = 0; grp < NG; ++grp) {
+            if (grp + 1 < NG) read(grp + 1, v[(grp + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < WRD; ++u) {
+                const int jj = NK - 1 - (grp * WRD + u);
+                if (jj >= 0) {
+#pragma unroll
+                    for (int i = 0; i < NI; ++i) acc[i] = fma(w[jj + i], v[grp & 1][u], acc[i]);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
     // Checkpoint layout: message of position t' at slot t' mod K.  d = distance of slot sl
     // from the newest position t.
     template <bool BWD>

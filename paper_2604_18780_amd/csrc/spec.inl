@@ -201,12 +201,7 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
         double acc[MB];
 #pragma unroll
         for (int i = 0; i < MB; ++i) acc[i] = 0.0;
-#pragma unroll
-        for (int jj = 0; jj < NK; ++jj) {
-            const double v = base[(BWD ? jj : NK - 1 - jj) * RS];  // distance g*NK + jj from the newest
-#pragma unroll
-            for (int i = 0; i < MB; ++i) acc[i] = fma(wx[jj + i], v, acc[i]);
-        }
+        G::template window_sums<BWD, MB>(base, wx, acc);
 #pragma unroll
         for (int i = 0; i < MB; ++i) acc[i] = group_sum<CTP>(acc[i]);
         // ---- the positions one after the other
@@ -293,12 +288,13 @@ __global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, N
     extern __shared__ double lds_raw[];
     const int per = both ? gridDim.x / 2 : gridDim.x;
     const int dir = (int)blockIdx.x >= per ? 1 : 0;
-    const int task = ((int)blockIdx.x - dir * per) * SW + (threadIdx.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // the same in every lane: scalar registers
+    const int task = ((int)blockIdx.x - dir * per) * SW + wave;
     const int b = task / p.N, j = task % p.N;
     if (b >= p.B) return;
     if (tier > 0 && p.spec_ok[b * 2 + dir]) return;  // accepted by an earlier attempt
     if (rest && p.hdr[b].J >= MS_JMIN) return;
-    double *lds = lds_raw + (size_t)(threadIdx.x >> 6) * scan_lds_doubles(CT, NKW);
+    double *lds = lds_raw + (size_t)wave * scan_lds_doubles(CT, NKW);
     if (dir == 0) spec_task<CT, NKW, false, false>(p, lds, b, j, warm);
     else spec_task<CT, NKW, true, false>(p, lds, b, j, warm);
 }

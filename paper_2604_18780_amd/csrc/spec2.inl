@@ -281,12 +281,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
                 double acc[MB];
 #pragma unroll
                 for (int i = 0; i < MB; ++i) acc[i] = 0.0;
-#pragma unroll
-                for (int jj = 0; jj < NK; ++jj) {
-                    const double v = base[(BWD ? jj : NK - 1 - jj) * RS];  // distance g*NK + jj behind rb
-#pragma unroll
-                    for (int i = 0; i < MB; ++i) acc[i] = fma(wx[jj + i], v, acc[i]);
-                }
+                G::template window_sums<BWD, MB>(base, wx, acc);
 #pragma unroll
                 for (int i = 0; i < MB; ++i) acc[i] = group_sum<CTP>(acc[i]);
                 double *fb = farb + ((nblk + 1) & 1) * MB * CTP + c;
