@@ -79,6 +79,7 @@ struct Params {
     double *ckYB2;      // [B][N+1]
     double *spec_lr;    // [B][2][N+1]
     double *spec_err;   // [B][2][N+1]
+    double *spec_rep;   // [B][2] largest mismatch of the last verification (-1: not attempted), for the report
     int *spec_ok;       // [B][2]  1: the chunk-parallel scan of (sequence, direction) was accepted
     int logpair;        // k_prefix stores the log-domain pair (S + end score, start score - S): Viterbi
     double2 *vr;        // [B][T+1][C] Viterbi: (V_t(c), r_t(c)) = best score arriving at / leaving position t
@@ -129,6 +130,7 @@ struct Params {
     // duration-dependent transitions (null / unused otherwise)
     const float *trans3;  // [K][C][C] trans3[k-1][c'][c] in place of trans[c'][c]
     double *G3;           // [K][C][C] exp(dur[k-1,c] + trans3[k-1,c',c])
+    double *GF, *GB;      // the same in the operand order of the matrix-core scans (forward, backward)
     double *dtA;          // [B][T+1][C] forward messages a_t(c), scaled
     double *dtY;          // [B][T+1]    log2 scale of that row relative to its interval's first position
     double *dtV;          // [B][T+1][C] backward messages v_t(c) = b_t(c) ES_t(c), scaled

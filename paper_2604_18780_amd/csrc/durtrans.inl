@@ -499,60 +499,6 @@ __device__ __forceinline__ double dt_ytop(const Params &p, int b, int j, int L)
     return hi == L ? 0.0 : p.ckYB[(size_t)b * (p.N + 1) + j + 1];
 }
 
-// Running emission-gradient sums per interval, in the form k_fin_seq / k_fin_emis expect from the
-// interval kernels: grad_emis[t] = sum of (out - in) over the interval's positions above t, tot and
-// sumR per interval.  One wave per (sequence, interval), lane = label; rows are fetched eight
-// positions at a time.
-__global__ __launch_bounds__(64) void k_dt_emis(Params p)
-{
-    const int b = blockIdx.x / p.N, j = blockIdx.x % p.N, lane = threadIdx.x;
-    const int C = p.C, Delta = p.Delta, N = p.N;
-    const int L = p.hdr[b].L;
-    const int lo = j * Delta;
-    if (lo >= L) return;
-    const int hi = min(lo + Delta, L);
-    const size_t row0 = (size_t)b * (p.T + 1);
-    const double *rowD = p.dtD + row0 * C;
-    const double *rowY = p.dtY + row0, *rowYb = p.dtYb + row0;
-    const double *ckYA = p.ckYA + (size_t)b * (N + 1);
-    const double logZ = p.hdr[b].logZ;
-    const double ytop = dt_ytop(p, b, j, L);
-    const bool act = lane < C;
-    double R = 0.0, sR = 0.0, kappa = 0.0, kY = -1.0e300;
-    for (int t1 = hi; t1 > lo; t1 -= 8) {
-        double d[8], y[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int tt = t1 - 1 - i;
-            d[i] = 0.0;
-            y[i] = 0.0;
-            if (tt >= lo) {
-                if (act) d[i] = rowD[(size_t)tt * C + lane];
-                y[i] = ckYA[tt == 0 ? 0 : (tt - 1) / Delta] + rowY[tt] + ytop + rowYb[tt];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int tt = t1 - 1 - i;
-            if (tt >= lo) {
-                if (y[i] != kY) {  // uniform
-                    kY = y[i];
-                    kappa = exp(kY * LN2 - logZ);
-                }
-                if (act) {
-                    p.grad_emis[((size_t)b * p.T + tt) * C + lane] = (float)R;
-                    sR += R;
-                    R = fma(d[i], kappa, R);
-                }
-            }
-        }
-    }
-    if (act) {
-        p.tot[((size_t)b * p.NP + j) * C + lane] = R;
-        p.sumR[((size_t)b * p.NP + j) * C + lane] = sR;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Marginals: sum_t w_b mu_b(t -> t+k, c', c) for every (k, c', c), from the stored rows.
 //   mu = a_t(c') IE_t(c) G[k][c'][c] v_{t+k}(c) 2^(n_blk(t+k)(c) - n_blk(t)(c)) exp((YA(t) + YB(t+k)) ln2 - logZ)
@@ -664,18 +610,31 @@ __global__ __launch_bounds__(1024) void k_dt_acc(Params p)
 }
 
 // Finalisation: FIN_FS workgroups per sequence (interval carries and means, as for the
-// factorised path), the others sum the per-workgroup marginal sums in workgroup order.
+// factorised path), the others sum the per-workgroup marginal sums: DT_FO outputs each, eight thread groups over the
+// partial tables (fixed order; one thread per output walked 256 tables one load at a time: 63 to 108 us).
+constexpr int DT_FO = 32;
 __global__ __launch_bounds__(NT) void k_dt_fin(Params p)
 {
     if ((int)blockIdx.x < p.B * FIN_FS) {
         fin_seq_body(p, blockIdx.x / FIN_FS, blockIdx.x % FIN_FS);
         return;
     }
+    __shared__ double red[NT];
+    constexpr int NG = NT / DT_FO;
     const size_t n = (size_t)p.K * p.C * p.C;
-    const size_t i = (size_t)(blockIdx.x - p.B * FIN_FS) * NT + threadIdx.x;
-    if (i >= n) return;
+    const int o = threadIdx.x % DT_FO, g = threadIdx.x / DT_FO;
+    const size_t i = (size_t)(blockIdx.x - p.B * FIN_FS) * DT_FO + o;
     double s = 0.0;
-    for (int w = 0; w < p.dt_nwg; ++w) s += p.partG[(size_t)w * n + i];
+    if (i < n) {
+#pragma unroll 8
+        for (int w = g; w < p.dt_nwg; w += NG) s += p.partG[(size_t)w * n + i];
+    }
+    red[threadIdx.x] = s;
+    __syncthreads();
+    if (g != 0 || i >= n) return;
+    s = 0.0;
+#pragma unroll
+    for (int q = 0; q < NG; ++q) s += red[q * DT_FO + o];
     p.sumG[i] = s;
     p.grad_trans3[i] = (float)s;
 }

@@ -128,7 +128,7 @@ int make_plan(int B, int T, int K, int C, int ckpt_interval, int want_grad, Plan
     sz[PL_W] = k * c * 8;
     sz[PL_ETR] = c * c * 8;
     sz[PL_EI] = b * t1 * c * 16;
-    sz[PL_SPEC] = 2 * b * 2 * (n + 1) * 8 + b * 2 * 4 + 256;  // spec_lr, spec_err, spec_ok
+    sz[PL_SPEC] = align_up(b * 2 * (8 + 4)) + 2 * b * 2 * (n + 1) * 8;  // spec_rep, spec_ok; spec_lr, spec_err
     sz[PL_NBASE] = b * t1 * c * 4;
     sz[PL_CKA] = b * (n + 1) * (k * c + c) * 8;
     sz[PL_CKB] = g * b * (n + 1) * (k * c + c) * 8;

@@ -67,6 +67,7 @@ using namespace semicrf_impl;
 #include "viterbi.inl"    // max-semiring decode and trace-back
 #include "finalise.inl"   // fixed-order reductions of the gradient formulas
 #include "durtrans.inl"   // duration-dependent transitions
+#include "durtrans_mx.inl"  // their scans and marginals on the matrix cores
 #include "marg.inl"       // marginals from the stored rows of both scans
 
 // ---------------------------------------------------------------------------
@@ -108,9 +109,11 @@ void bind_workspace(Params &p, const Plan &pl, void *ws)
     p.bloc = (double *)(w + pl.off[28]);
     p.blocY = (double *)(w + pl.off[29]);
     p.sink = (double *)(w + pl.off[30]);
-    p.spec_lr = (double *)(w + pl.off[8]);
+    // what the report reads comes first: its place does not depend on how many tasks the scans were cut into
+    p.spec_rep = (double *)(w + pl.off[8]);
+    p.spec_ok = (int *)(p.spec_rep + (size_t)p.B * 2);
+    p.spec_lr = (double *)(w + pl.off[8] + align_up((size_t)p.B * 2 * (sizeof(double) + sizeof(int))));
     p.spec_err = p.spec_lr + (size_t)p.B * 2 * (pl.N + 1);
-    p.spec_ok = (int *)(p.spec_err + (size_t)p.B * 2 * (pl.N + 1));
 }
 
 int check_launch()
@@ -640,20 +643,60 @@ int dt_auto_interval(int B, int T, int K, const DtGeom &g)
 }
 
 constexpr int DT_NWG = 256;  // most persistent workgroups (per group of 16 durations) of the marginal kernel
+constexpr int DXA_WGS = 512;  // workgroups of the matrix-core marginals: two per compute unit
+
+// Scan tasks per reported interval.  The matrix-core scans take four tasks per workgroup and one workgroup per compute
+// unit: an interval is cut into 2, 4 or 8 equal parts where that lowers rounds * (warm-up + positions); the automatic
+// interval stays what it is for the caller.  Explicit intervals are not cut.
+int dt_parts(int B, int T, int K, int C, int interval)
+{
+    if (!dx_geometry(K, C).ok) return 1;
+    int best = 1;
+    double best_cost = 0.0;
+    for (int parts = 1; parts <= 8; parts *= 2) {
+        if (interval % parts || (parts > 1 && interval / parts < 8)) break;
+        const int d = interval / parts;
+        const double tasks = (double)B * (double)(((long long)T + d - 1) / d);
+        const double cost = ceil(tasks / (256.0 * DX_TASKS)) * ((double)sum_warmup(K) + d);
+        if (parts == 1 || cost < best_cost) {
+            best = parts;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+// The interval the scans run with: the caller's, or the automatic one over dt_parts.
+int dt_scan_interval(int B, int T, int K, int C, int ckpt_interval, const DtGeom &g)
+{
+    if (ckpt_interval > 0) return ckpt_interval > T ? T : ckpt_interval;
+    const int d = dt_auto_interval(B, T, K, g);
+    return d / dt_parts(B, T, K, C, d);
+}
 
 struct DtLayout {
-    size_t g3, dta, dty, dtv, dtd, dtyb, partg, sumg, total;
+    size_t g3, gf, gb, dta, dty, dtv, dtd, dtyb, partg, sumg, total;
     int nwg;
 };
 
 DtLayout dt_layout(int B, int T, int K, int C, int N, int want_grad)
 {
     DtLayout l;
+    const DxGeom g = dx_geometry(K, C);
     const size_t kcc = (size_t)K * C * C, t1 = (size_t)T + 1;
     const size_t ntask = (size_t)B * N;
-    l.nwg = (int)(ntask < (size_t)DT_NWG ? ntask : (size_t)DT_NWG);
+    // workgroups with partial tables of their own: enough to fill the chip, whole rounds of tasks
+    size_t most = DT_NWG;
+    if (g.ok) {
+        const size_t ny = ((size_t)C * ((K + DXA_K - 1) / DXA_K) + DXA_W - 1) / DXA_W;
+        const size_t rounds = (ntask * ny + DXA_WGS - 1) / DXA_WGS;
+        most = (ntask + rounds - 1) / rounds;
+    }
+    l.nwg = (int)(ntask < most ? ntask : most);
     size_t off = 0;
     l.g3 = off; off += align_up(kcc * 8);
+    l.gf = off; off += g.ok ? align_up(g.gf * 8) : 0;
+    l.gb = off; off += g.ok ? align_up(g.gb * 8) : 0;
     l.dta = off; off += align_up((size_t)B * t1 * C * 8);
     l.dty = off; off += align_up((size_t)B * t1 * 8);
     l.dtv = off; off += want_grad ? align_up((size_t)B * t1 * C * 8) : 0;
@@ -663,6 +706,43 @@ DtLayout dt_layout(int B, int T, int K, int C, int N, int want_grad)
     l.sumg = off; off += want_grad ? align_up(kcc * 8) : 0;
     l.total = off;
     return l;
+}
+
+template <int SF2>
+int launch_dx_fwd(const Params &p, const DxGeom &g, hipStream_t st, int warm, int tier)
+{
+    if (hipFuncSetAttribute((const void *)k_dx_fwd<SF2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g.lds_f) != hipSuccess)
+        return SEMICRF_ELAUNCH;
+    hipLaunchKernelGGL((k_dx_fwd<SF2>), dim3((p.B * p.N + DX_TASKS - 1) / DX_TASKS), dim3(DX_NT), g.lds_f, st, p, warm, tier);
+    return SEMICRF_OK;
+}
+
+int launch_dx_fwd_any(const Params &p, const DxGeom &g, hipStream_t st, int warm, int tier)
+{
+    switch (g.sf2) {
+    case 1: return launch_dx_fwd<1>(p, g, st, warm, tier);
+    case 2: return launch_dx_fwd<2>(p, g, st, warm, tier);
+    case 3: return launch_dx_fwd<3>(p, g, st, warm, tier);
+    default: return launch_dx_fwd<4>(p, g, st, warm, tier);
+    }
+}
+
+template <int MT>
+int launch_dx_bwd(const Params &p, const DxGeom &g, hipStream_t st, int warm, int tier)
+{
+    if (hipFuncSetAttribute((const void *)k_dx_bwd<MT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g.lds_b) != hipSuccess)
+        return SEMICRF_ELAUNCH;
+    hipLaunchKernelGGL((k_dx_bwd<MT>), dim3((p.B * p.N + DX_TASKS - 1) / DX_TASKS), dim3(DX_NT), g.lds_b, st, p, warm, tier);
+    return SEMICRF_OK;
+}
+
+template <int MT>
+int launch_dx_acc(const Params &p, hipStream_t st)
+{
+    const size_t lds = dxa_lds_doubles(MT) * sizeof(double);
+    const int items = p.C * ((p.K + DXA_K - 1) / DXA_K);
+    hipLaunchKernelGGL((k_dx_acc<MT>), dim3(p.dt_nwg, (items + DXA_W - 1) / DXA_W), dim3(64 * DXA_W), lds, st, p);
+    return SEMICRF_OK;
 }
 
 template <int KPTF>
@@ -710,7 +790,7 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
     if (p.B < 1 || p.T < 1 || p.K < 1 || p.C < 1 || ckpt_interval < 0) return SEMICRF_EINVAL;
     DtGeom g;
     if (!dt_geometry(p.K, p.C, &g)) return SEMICRF_EUNSUPPORTED;
-    if (ckpt_interval == 0) ckpt_interval = dt_auto_interval(p.B, p.T, p.K, g);
+    ckpt_interval = dt_scan_interval(p.B, p.T, p.K, p.C, ckpt_interval, g);
     Plan pl;
     int rc = make_plan(p.B, p.T, p.K, p.C, ckpt_interval, grad ? 2 : 0, &pl);
     if (rc != SEMICRF_OK) return rc;
@@ -725,6 +805,8 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
     bind_workspace(p, pl, workspace);
     char *dw = (char *)workspace + pl.total;
     p.G3 = (double *)(dw + dl.g3);
+    p.GF = (double *)(dw + dl.gf);
+    p.GB = (double *)(dw + dl.gb);
     p.dtA = (double *)(dw + dl.dta);
     p.dtY = (double *)(dw + dl.dty);
     p.dtV = (double *)(dw + dl.dtv);
@@ -736,15 +818,22 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
     rc = launch_prep(p, st);
     if (rc != SEMICRF_OK) return rc;
     const size_t kcc = (size_t)p.K * p.C * p.C;
-    hipLaunchKernelGGL(k_dt_tables, dim3((unsigned)((kcc + NT - 1) / NT)), dim3(NT), 0, st, p);
+    const DxGeom dx = dx_geometry(p.K, p.C);
+    const size_t ntable = kcc + (dx.ok ? dx.gf + dx.gb : 0);
+    if (dx.ok)
+        hipLaunchKernelGGL(k_dx_tables, dim3((unsigned)((ntable + NT - 1) / NT)), dim3(NT), 0, st, p);
+    else
+        hipLaunchKernelGGL(k_dt_tables, dim3((unsigned)((ntable + NT - 1) / NT)), dim3(NT), 0, st, p);
     const int ndir = grad ? 2 : 1;
     if (p.spec) {
         const int warm[2] = {sum_warmup(p.K), 8 * p.K < 64 ? 64 : 8 * p.K};
         for (int tier = 0; tier < 2; ++tier) {
-            rc = launch_dt_fwd_any(p, g, st, p.B * p.N, warm[tier], tier, 0);
+            rc = dx.ok ? launch_dx_fwd_any(p, dx, st, warm[tier], tier)
+                       : launch_dt_fwd_any(p, g, st, p.B * p.N, warm[tier], tier, 0);
             if (rc != SEMICRF_OK) return rc;
             if (grad) {
-                rc = launch_dt_bwd_any(p, g, st, p.B * p.N, warm[tier], tier, 0);
+                if (dx.ok) rc = dx.mt == 1 ? launch_dx_bwd<1>(p, dx, st, warm[tier], tier) : launch_dx_bwd<2>(p, dx, st, warm[tier], tier);
+                else rc = launch_dt_bwd_any(p, g, st, p.B * p.N, warm[tier], tier, 0);
                 if (rc != SEMICRF_OK) return rc;
             }
             hipLaunchKernelGGL(k_spec_cmp, dim3(p.N, p.B, ndir), dim3(NT), 0, st, p, tier);
@@ -759,9 +848,11 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
     if (!grad) return check_launch();
     rc = launch_dt_bwd_any(p, g, st, p.B, 0, 0, 1);
     if (rc != SEMICRF_OK) return rc;
-    hipLaunchKernelGGL(k_dt_emis, dim3(p.B * p.N), dim3(64), 0, st, p);
-    hipLaunchKernelGGL((k_dt_acc<16>), dim3(dl.nwg, (p.K + 15) / 16), dim3(g.nta), g.lds_a, st, p);
-    hipLaunchKernelGGL(k_dt_fin, dim3(p.B * FIN_FS + (unsigned)((kcc + NT - 1) / NT)), dim3(NT), 0, st, p);
+    hipLaunchKernelGGL(k_dx_emis, dim3(p.B * p.N), dim3(NT), 0, st, p);
+    if (dx.ok) rc = dx.mt == 1 ? launch_dx_acc<1>(p, st) : launch_dx_acc<2>(p, st);
+    else hipLaunchKernelGGL((k_dt_acc<16>), dim3(dl.nwg, (p.K + 15) / 16), dim3(g.nta), g.lds_a, st, p);
+    if (rc != SEMICRF_OK) return rc;
+    hipLaunchKernelGGL(k_dt_fin, dim3(p.B * FIN_FS + (unsigned)((kcc + DT_FO - 1) / DT_FO)), dim3(NT), 0, st, p);
     hipLaunchKernelGGL(k_dt_fin_dur, dim3((p.K * p.C + NT - 1) / NT), dim3(NT), 0, st, p);
     launch_fin_emis(p, st);
     return check_launch();
@@ -1050,7 +1141,7 @@ int semicrf_durtrans_workspace_bytes(int B, int T, int K, int C, int ckpt_interv
     if (B < 1 || T < 1 || K < 1 || C < 1 || ckpt_interval < 0) return SEMICRF_EINVAL;
     DtGeom g;
     if (!dt_geometry(K, C, &g)) return SEMICRF_EUNSUPPORTED;
-    if (ckpt_interval == 0) ckpt_interval = dt_auto_interval(B, T, K, g);
+    ckpt_interval = dt_scan_interval(B, T, K, C, ckpt_interval, g);
     Plan pl;
     int rc = make_plan(B, T, K, C, ckpt_interval, want_grad ? 2 : 0, &pl);
     if (rc != SEMICRF_OK) return rc;

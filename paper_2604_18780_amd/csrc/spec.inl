@@ -394,7 +394,7 @@ __global__ __launch_bounds__(64) void k_spec_fix(Params p, int ndir, int tier, i
     if (dir >= ndir) {  // direction not run in this call
         if (lane == 0) {
             p.spec_ok[b * 2 + dir] = 0;
-            p.spec_err[so] = -1.0;
+            p.spec_rep[b * 2 + dir] = -1.0;
         }
         return;
     }
@@ -452,8 +452,8 @@ __global__ __launch_bounds__(64) void k_spec_fix(Params p, int ndir, int tier, i
         if (dir == 0 && nint > 0 && lane < C) p.inL[(size_t)b * C + lane] = vL / sumL;
     }
     if (lane != 0) return;
-    p.spec_err[so] = worst;  // entry 0 is no boundary: it carries the report value,
-    p.spec_lr[so] = (double)nbad;  // and this one the number of boundaries that disagreed (read by the repair attempt)
+    p.spec_rep[b * 2 + dir] = worst;
+    p.spec_lr[so] = (double)nbad;  // entry 0 is no boundary: it carries the number of boundaries that disagreed (read by the repair attempt)
     if (dir == 0 && ok) {
         p.hdr[b].logZ = lz;
         p.logz[b] = (float)lz;
@@ -467,7 +467,7 @@ __global__ void k_spec_clear(Params p)
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= 2 * p.B) return;
     p.spec_ok[i] = 0;
-    p.spec_err[(size_t)i * (p.N + 1)] = -1.0;
+    p.spec_rep[i] = -1.0;
 }
 
 __global__ void k_spec_report(Params p, int32_t *accepted, double *mismatch)
@@ -475,7 +475,7 @@ __global__ void k_spec_report(Params p, int32_t *accepted, double *mismatch)
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= 2 * p.B) return;
     if (accepted) accepted[i] = p.spec_ok[i];
-    if (mismatch) mismatch[i] = p.spec_err[(size_t)i * (p.N + 1)];
+    if (mismatch) mismatch[i] = p.spec_rep[i];
 }
 
 __global__ void k_seq_report(Params p, int32_t *range_exceeded, double *logz64)

@@ -356,7 +356,7 @@ __global__ __launch_bounds__(64) void k_vit_fix(Params p, int tier)
     }
     if (lane == 0) {
         p.spec_ok[b * 2] = ok ? 1 : 0;
-        p.spec_err[so] = worst;
+        p.spec_rep[b * 2] = worst;
     }
 }
 
