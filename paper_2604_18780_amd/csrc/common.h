@@ -130,7 +130,7 @@ struct Params {
     // duration-dependent transitions (null / unused otherwise)
     const float *trans3;  // [K][C][C] trans3[k-1][c'][c] in place of trans[c'][c]
     double *G3;           // [K][C][C] exp(dur[k-1,c] + trans3[k-1,c',c])
-    double *GF, *GB;      // the same in the operand order of the matrix-core scans (forward, backward)
+    double *GF, *GB, *GS; // the same in the operand order of the matrix-core scans (forward, backward, durations 1 .. 3)
     double *dtA;          // [B][T+1][C] forward messages a_t(c), scaled
     double *dtY;          // [B][T+1]    log2 scale of that row relative to its interval's first position
     double *dtV;          // [B][T+1][C] backward messages v_t(c) = b_t(c) ES_t(c), scaled

@@ -23,37 +23,40 @@ typedef double dx_d4 __attribute__((ext_vector_type(4)));
 
 struct DxGeom {
     int khp;          // half of the durations, rounded up to a multiple of four (forward tiles hold two halves)
-    int ncg;          // label groups of eight (forward tiles)
-    int sf2;          // pairs of inner steps of the forward product (source labels, eight per pair)
+    int ncg;          // label groups of eight (forward tiles), and pairs of inner steps of the forward product
     int mt;           // tiles of sixteen source labels (backward, marginals)
-    int ks;           // inner steps of the backward product (four durations each), even
-    int kr;           // ring slots: K + 4, so that all targets of a block are different slots, and at least 8, so that
-                      // the next block's four slots are not those of this one
-    int xs, ts;       // doubles per task of the forward / backward ring
-    int cp, cpb;      // row length of the small per-position arrays
-    size_t gf, gb;    // doubles of the two tables in operand order
+    int ks;           // inner steps of the backward product (four durations each), a multiple of four
+    int kr;           // forward ring slots: K + 4, so that all targets of a block are different slots
+    int w, m;         // rows of the backward window per label (positions upwards), and its slack
+    int xs, ts;       // doubles per task of the forward ring / backward window
+    size_t gf, gb, gs; // doubles of the tables in operand order (gs: durations 1 .. 3, forward order by label tiles)
     size_t lds_f, lds_b;
     bool ok;
 };
+constexpr int DX_CTL = 4 * 4 + 4 * 32;  // ints: block length, first slot / row, rescale and record flags, shifts per label
 
 __host__ __device__ inline DxGeom dx_geometry(const int K, const int C)
 {
     DxGeom g;
     g.khp = ((K + 1) / 2 + 3) & ~3;
     g.ncg = (C + 7) / 8;
-    g.sf2 = (C + 7) / 8;
     g.mt = (C + 15) / 16;
-    g.ks = ((K + 3) / 4 + 1) & ~1;
-    g.kr = K + DX_MB < 2 * DX_MB ? 2 * DX_MB : K + DX_MB;
+    g.ks = ((K + 3) / 4 + 3) & ~3;
+    g.kr = K + DX_MB;
+    g.gf = (size_t)g.ncg * g.khp * g.ncg * 128;
+    g.gb = (size_t)C * g.ks * g.mt * 64;
+    g.gs = (size_t)(DX_MB - 1) * g.mt * g.ncg * 128;
     // tasks 8 doubles (16 LDS banks) apart modulo the banks: the four tasks of an access do not collide
     g.xs = ((g.kr * C + 31) & ~31) + 8;
-    g.ts = ((g.kr * C + 31) & ~31) + 8;
-    g.cp = 8 * g.sf2;
-    g.cpb = 16 * g.mt;
-    g.gf = (size_t)g.ncg * g.khp * g.sf2 * 128;
-    g.gb = (size_t)C * g.ks * g.mt * 64;
-    g.lds_f = ((size_t)DX_TASKS * g.xs + 2 * (size_t)16 * g.cp) * sizeof(double) + 64;
-    g.lds_b = ((size_t)DX_TASKS * g.ts + 5 * (size_t)16 * g.cpb + (size_t)8 * C * 16 + (size_t)(DX_MB - 1) * C * C) * sizeof(double) + 64;
+    // (the rows of the small per-position arrays are an odd number of doubles long: a wave reads them across)
+    g.lds_f = ((size_t)DX_TASKS * g.xs + 2 * (size_t)16 * (8 * g.ncg + 1)) * sizeof(double) + DX_CTL * sizeof(int);
+    g.m = 32;
+    for (;; g.m -= 8) {
+        g.w = 4 * g.ks + DX_MB + g.m;
+        g.ts = ((g.w * C + 31) & ~31) + 8;
+        g.lds_b = ((size_t)DX_TASKS * g.ts + (size_t)(4 + DX_MB - 1) * 16 * (16 * g.mt + 1) + 16 * (size_t)4 * (16 * g.mt + 1) + (size_t)8 * C * 16) * sizeof(double) + DX_CTL * sizeof(int);
+        if (g.m == 8 || g.lds_b <= LDS_LIMIT) break;
+    }
     g.ok = C <= 32 && g.lds_f <= LDS_LIMIT && g.lds_b <= LDS_LIMIT;
     return g;
 }
@@ -63,13 +66,15 @@ __host__ __device__ inline DxGeom dx_geometry(const int K, const int C)
 //             8 group + j % 8; inner index: source label 8 pair + 4 (0, 1) + lane / 16
 //   backward  [label][step][lane][mt] (two label tiles) or [label][step pair][lane][2] (one): row: source label
 //             16 mt + lane % 16, inner index: duration 4 step + lane / 16 + 1
+//   short     [duration - 1][label tile][step pair][lane][2]: durations 1 .. 3, column: label 16 tile + lane % 16, inner
+//             index as forward
 __global__ __launch_bounds__(NT) void k_dx_tables(Params p)
 {
     const int K = p.K, C = p.C, CC = C * C;
     const DxGeom g = dx_geometry(K, C);
-    const size_t n0 = (size_t)K * CC, n1 = n0 + g.gf, n2 = n1 + g.gb;
+    const size_t n0 = (size_t)K * CC, n1 = n0 + g.gf, n2 = n1 + g.gb, n3 = n2 + g.gs;
     const size_t i = (size_t)blockIdx.x * NT + threadIdx.x;
-    if (i >= n2) return;
+    if (i >= n3) return;
     int k, o, c;  // duration (from 1), source label, label
     double *dst;
     if (i < n0) {
@@ -80,12 +85,20 @@ __global__ __launch_bounds__(NT) void k_dx_tables(Params p)
     } else if (i < n1) {
         const size_t q = i - n0;
         const int u = (int)(q & 1), lane = (int)(q >> 1) & 63, j = lane & 15;
-        const size_t tile = (q >> 7) / g.sf2;
-        const int s = (int)((q >> 7) % g.sf2);
+        const size_t tile = (q >> 7) / g.ncg;
+        const int s = (int)((q >> 7) % g.ncg);
         k = (int)(tile % g.khp) + 1 + (j >> 3) * g.khp;
         c = (int)(tile / g.khp) * 8 + (j & 7);
         o = 8 * s + 4 * u + (lane >> 4);
         dst = p.GF + q;
+    } else if (i >= n2) {
+        const size_t q = i - n2;
+        const int u = (int)(q & 1), lane = (int)(q >> 1) & 63, s = (int)((q >> 7) % g.ncg);
+        const int tile = (int)((q >> 7) / g.ncg);
+        k = tile / g.mt + 1;
+        c = (tile % g.mt) * 16 + (lane & 15);
+        o = 8 * s + 4 * u + (lane >> 4);
+        dst = p.GS + q;
     } else {
         const size_t q = i - n1;
         const int u = (int)(q & 1), lane = (int)(q >> 1) & 63;
@@ -129,28 +142,35 @@ __device__ __forceinline__ int dx_wrap(int i, const int kr) { return i >= kr ? i
 // Forward ("push"): the product of a block's sixteen message rows with the whole table; column (k, c) of row (task, t)
 // goes, times IE_t(c), into the ring entry of position t + k.  A lane holds the four positions of one task for its
 // column and walks consecutive durations of one label, so the four positions' terms for one target are added up in
-// registers and the ring is touched once per duration.  Waves own whole runs of durations (multiples of four); the last three
-// targets of a run belong to the next run too and are added after a barrier: every entry has one writer at a time and
-// the order of additions is fixed.
+// registers and the ring is touched once per duration.  Waves own whole runs of durations (multiples of four); the last
+// three targets of a run belong to the next run too and are added after a barrier: every entry has one writer at a time
+// and the order of additions is fixed.
+// The block's own four positions are finished by one wave per task (waves 0 .. 3), in registers: its transition
+// products are row broadcasts (RowMap), and durations 1 .. 3 inside the block never touch the ring.  fp64 matrix and
+// vector instructions share one pipe, so the loop over the tiles carries as few of the latter as possible: the ring entry
+// is read before the product it is added to, indices run instead of being computed.
 // ---------------------------------------------------------------------------
 template <int SF2>
 __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tier)
 {
     extern __shared__ double lds_raw[];
+    constexpr int CT = 8 * SF2, CS = CT + 1;
+    using R = RowMap<CT>;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g4 = lane >> 4, j = lane & 15;
     const int K = p.K, C = p.C, CC = C * C, KC = K * C, N = p.N;
     const DxGeom g = dx_geometry(K, C);
     const int KR = g.kr, KHP = g.khp, XS = g.xs;
-    constexpr int CP = 8 * SF2;
     double *X = lds_raw;                       // [task][slot][C] partial sums of the positions to come
-    double *av = X + DX_TASKS * XS;            // [task][pos][CP] message vectors of the block (zero beyond it)
-    double *ieL = av + 16 * CP;                // [task][pos][CP] 1/ES
-    int *ctl = (int *)(ieL + 16 * CP);         // [task] block length, [task] slot of its first position, [task] rebase
-    const int q = wave >> 1;                   // the thread's own task, its position in a block and label
-    const int pos = (tid >> 5) & 3, c = tid & 31;
-    const bool cv = c < C;
+    double *av = X + DX_TASKS * XS;            // [task][pos][CS] message vectors of the block (zero beyond it)
+    double *ieL = av + 16 * CS;                // [task][pos][CS] 1/ES
+    int *ctl = (int *)(ieL + 16 * CS);         // per task: block length, slot of its first position, rescale, record
+    int *sftL = ctl + 16;                      // [task][32] shift per label at a scaling-block boundary
+    const int q = wave & 3;                    // the wave's task; waves 0 .. 3 run the chains
+    const bool chain = wave < 4;
+    const int c = R::label(lane), gr = R::group(lane);
+    const bool cv = c < C, owner = cv && gr == 0;
     const DxTask tk = dx_task(p, blockIdx.x * DX_TASKS + q, 0, tier);
     const int L = tk.L, J = tk.J, lo = tk.lo, hi = tk.hi;
     const int s0 = max(lo - warm, 0);
@@ -159,324 +179,395 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tie
     const int *nb = p.nbase + row0 * C + (cv ? c : 0);
     double *rowA = p.dtA + row0 * C, *rowY = p.dtY + row0;
     const size_t ckstride = (size_t)KC + C;
-    double *Xq = X + q * XS, *avq = av + q * 4 * CP, *ieq = ieL + q * 4 * CP;
+    double *Xq = X + q * XS, *avq = av + q * 4 * CS, *ieq = ieL + q * 4 * CS;
 
-    // column c of the tables of the durations inside a block (thread's duration pos + 1)
-    double gcol[CP];
+    // the lane's part of the tables of durations 1 .. 3
+    double Ek[DX_MB - 1][R::HC];
 #pragma unroll
-    for (int o = 0; o < CP; ++o)
-        gcol[o] = (pos < DX_MB - 1 && pos < K && cv && o < C) ? p.G3[(size_t)pos * CC + (size_t)o * C + c] : 0.0;
+    for (int k = 0; k < DX_MB - 1; ++k)
+#pragma unroll
+        for (int i = 0; i < R::HC; ++i) {
+            const int o = (lane >> 5) * R::HC + i;
+            const bool ok = chain && k < K && cv && o < C;
+            const double v = p.G3[ok ? (size_t)k * CC + (size_t)o * C + c : 0];
+            Ek[k][i] = ok ? v : 0.0;
+        }
 
-    for (int i = tid; i < DX_TASKS * XS + 2 * 16 * CP; i += DX_NT) lds_raw[i] = 0.0;
-    double Y = 0.0, Ybase = 0.0;
-    int t0 = s0, rb = 0, last = 0;  // rb: ring slot of t0; last: position of the newest message vector in av
+    for (int i = tid; i < DX_TASKS * XS + 2 * 16 * CS; i += DX_NT) lds_raw[i] = 0.0;
+    double Y = 0.0, Ybase = 0.0, ylast = 0.0;
+    int t0 = s0, rb = 0;  // rb: ring slot of t0
     bool done = !tk.active;
+    double2 e[DX_MB];
     auto load_ei = [&](const int tb) {
-        double2 e = make_double2(0.0, 0.0);
-        if (!done && cv && tb + pos <= hi) e = EI[(size_t)(tb + pos) * C];
-        return e;
+#pragma unroll
+        for (int i = 0; i < DX_MB; ++i) {
+            e[i] = make_double2(0.0, 0.0);
+            if (chain && !done) e[i] = EI[(size_t)min(tb + i, hi) * C];
+        }
     };
-    double2 e = load_ei(t0);
+    load_ei(t0);
+    auto nbdelta = [&](const int jb) {  // exponent step of the lane's label at the scaling-block boundary jb
+        return (chain && !done && jb >= 1 && (long)jb * J <= (long)L) ? nb[(size_t)jb * C] - nb[(size_t)(jb - 1) * C] : 0;
+    };
+    int jnx = s0 / J + 1, dnx = nbdelta(jnx);
     lds_barrier();
 
-    // runs of durations: units of four tiles, a contiguous share per wave
+    // runs of durations: units of four tiles, a contiguous share per wave (at most two label groups)
     const int units = g.ncg * (KHP / 4), per = (units + 7) / 8;
     const int u0 = wave * per, u1 = min(u0 + per, units);
 
+    double2 B0[SF2];  // the first tile's entries: the same in every block
+#pragma unroll
+    for (int s = 0; s < SF2; ++s) B0[s] = ((const double2 *)p.GF + (size_t)(min(u0, units - 1) * 4) * (SF2 * 64) + lane)[s * 64];
+
     for (;;) {
         int nbk = 0;
-        bool bd = false;
+        bool rec = false;
         if (!done) {
             nbk = min(DX_MB, hi - t0 + 1);
             if (t0 <= lo) nbk = min(nbk, lo - t0 + 1);  // the interval's first position ends its block
             nbk = min(nbk, J - (t0 & (J - 1)));         // no scaling-block boundary inside a block
-            bd = t0 > s0 && (t0 & (J - 1)) == 0;
+            rec = t0 + nbk - 1 == lo || t0 + nbk > hi;
         }
-        if ((tid & 127) == 0) {
-            ctl[q] = nbk;
-            ctl[4 + q] = rb;
-            ctl[8 + q] = bd;
+        if (chain) {
+            const bool bd = !done && t0 > s0 && (t0 & (J - 1)) == 0;
+            if (bd) {
+                const int ex = safe_exponent(R::total(ylast));
+                Y += (double)ex;
+                if (owner) sftL[q * 32 + c] = dnx - ex;
+                ++jnx;
+                dnx = nbdelta(jnx);
+            }
+            if (lane == 0) {
+                ctl[q] = nbk;
+                ctl[4 + q] = rb;
+                ctl[8 + q] = bd;
+                ctl[12 + q] = rec;
+            }
         }
         lds_barrier();
         if ((ctl[0] | ctl[1] | ctl[2] | ctl[3]) == 0) break;
+        const bool anyrec = (ctl[12] | ctl[13] | ctl[14] | ctl[15]) != 0;  // (read here: the next block's are written early)
         if (ctl[8] | ctl[9] | ctl[10] | ctl[11]) {
-            if (bd) {
-                double pm = 0.0;
-                for (int i = 0; i < C; ++i) pm += avq[last * CP + i];
-                const int ex = safe_exponent(pm);
-                Y += (double)ex;
-                if (cv) {
-                    const int sft = nb[(size_t)(t0 / J) * C] - nb[(size_t)(t0 / J - 1) * C] - ex;
-                    for (int r = pos; r < KR; r += 4) Xq[r * C + c] = fmin(ldexp(Xq[r * C + c], sft), DBL_MAX);
+            if (ctl[8 + q] && (lane & 31) < C) {
+                const int sft = sftL[q * 32 + (lane & 31)];
+#pragma unroll 4
+                for (int r = (wave >> 2) * 2 + (lane >> 5); r < KR; r += 4) {
+                    double *x = Xq + r * C + (lane & 31);
+                    *x = fmin(ldexp(*x, sft), DBL_MAX);
                 }
             }
             lds_barrier();
         }
         // ---- the block's positions, one after the other
-        if (cv) ieq[pos * CP + c] = pos < nbk ? e.y : 0.0;
+        if (chain) {
+            double x[DX_MB];
 #pragma unroll
-        for (int i = 0; i < DX_MB; ++i) {
-            if (pos == i && cv) {
+            for (int i = 0; i < DX_MB; ++i) x[i] = Xq[dx_wrap(rb + i, KR) * C + (cv ? c : 0)];
+#pragma unroll
+            for (int i = 0; i < DX_MB; ++i) {
                 double a = 0.0;
-                const int tt = t0 + i;
-                if (i < nbk) {
-                    a = tt == s0 ? 1.0 : e.x * Xq[dx_wrap(rb + i, KR) * C + c];
-                    if (tt > lo || tt == 0) rowA[(size_t)tt * C + c] = a;
-                    if (c == 0 && (tt > lo || tt == 0)) rowY[tt] = Y - Ybase;
-                }
-                avq[i * CP + c] = a;
-            }
-            lds_barrier();
-            if (i < DX_MB - 1) {
-                // durations that stay inside the block: duration pos + 1
-                if (pos < DX_MB - 1 && pos < K && cv && i + pos + 1 < nbk) {
-                    double m0 = 0.0, m1 = 0.0;
-                    const double2 *a2 = (const double2 *)(avq + i * CP);
+                if (i < nbk) {  // uniform
+                    const int tt = t0 + i;
+                    a = cv ? (tt == s0 ? 1.0 : e[i].x * x[i]) : 0.0;
+                    ylast = a;
 #pragma unroll
-                    for (int o = 0; o < CP / 2; ++o) {
-                        const double2 v = a2[o];
-                        m0 = fma(v.x, gcol[2 * o], m0);
-                        m1 = fma(v.y, gcol[2 * o + 1], m1);
+                    for (int k = 1; i + k < DX_MB; ++k)
+                        if (i + k < nbk) x[i + k] = fma(e[i].y, R::product(a, Ek[k - 1]), x[i + k]);
+                    if (tt > lo || tt == 0) {
+                        if (owner) rowA[(size_t)tt * C + c] = a;
+                        if (lane == 0) rowY[tt] = Y - Ybase;
                     }
-                    double *x = Xq + dx_wrap(rb + i + pos + 1, KR) * C + c;
-                    *x = fma(ieq[i * CP + c], m0 + m1, *x);
+                    if (owner) Xq[dx_wrap(rb + i, KR) * C + c] = 0.0;  // consumed: free for a later target
                 }
-                lds_barrier();
+                if (owner) {
+                    avq[i * CS + c] = a;
+                    ieq[i * CS + c] = e[i].y;
+                }
             }
+            load_ei(t0 + nbk);  // the next block's factors, requested before the long part
         }
-        if (nbk) last = nbk - 1;
-        const double2 en = load_ei(t0 + nbk);  // the next block's factors, requested before the long part
+        lds_barrier();
         // ---- durations that leave the block
         {
             double A[2 * SF2];
 #pragma unroll
-            for (int s = 0; s < 2 * SF2; ++s) A[s] = av[((j & 3) * 4 + (j >> 2)) * CP + 4 * s + g4];
+            for (int s = 0; s < 2 * SF2; ++s) A[s] = av[((j & 3) * 4 + (j >> 2)) * CS + 4 * s + g4];
             const int nbD = ctl[g4], rbD = ctl[4 + g4];
             double *XD = X + g4 * XS;
-            const double2 *GF = (const double2 *)p.GF + lane;
-            double2 Bn[SF2];
-            auto fetch = [&](const int tile, double2 (&B)[SF2]) {
-#pragma unroll
-                for (int s = 0; s < SF2; ++s) B[s] = GF[((size_t)tile * SF2 + s) * 64];
-            };
-            // sums whose targets the next run writes too, per run (a wave's share meets at most two label groups)
-            double pend[2][3];
+            double pend[2][3];  // sums whose targets the next run writes too
             int pslot[2] = {0, 0}, pk[2] = {0, 0};
-            bool first = true;
-            double w1 = 0.0, w2 = 0.0, w3 = 0.0, ier[DX_MB];
 #pragma unroll
-            for (int a = 0; a < 2; ++a)
+            for (int a = 0; a < 2; ++a) pend[a][0] = pend[a][1] = pend[a][2] = 0.0;
+            int u = u0;
 #pragma unroll
-                for (int i = 0; i < 3; ++i) pend[a][i] = 0.0;
+            for (int sgm = 0; sgm < 2; ++sgm) {
+                if (u >= u1) break;  // uniform
+                const int cg = u * 4 / KHP, ka = u * 4 - cg * KHP, kb = min(KHP, ka + (u1 - u) * 4);
+                const int cl = cg * 8 + (j & 7);
+                const double2 *GF = (const double2 *)p.GF + (size_t)(u * 4) * (SF2 * 64) + lane;
+                double ier[DX_MB];
 #pragma unroll
-            for (int i = 0; i < DX_MB; ++i) ier[i] = 0.0;
-            if (u0 < u1) fetch(u0 * 4, Bn);
-            int cg = -1, cl = 0;
-            for (int tile = u0 * 4; tile < u1 * 4; ++tile) {
-                double2 B[SF2];
+                for (int i = 0; i < DX_MB; ++i) ier[i] = ieL[(g4 * 4 + i) * CS + cl];
+                double w1 = 0.0, w2 = 0.0, w3 = 0.0;
+                int k1 = ka + 1 + (j >> 3) * KHP;         // the lane's duration
+                int slot = dx_wrap(rbD + k1, KR);
+                if (slot >= KR) slot = 0;                  // beyond K + 3: not used
+                const int kmax = cl < C ? K + DX_MB - 1 : 0;
+                double2 B[2][SF2];
 #pragma unroll
-                for (int s = 0; s < SF2; ++s) B[s] = Bn[s];
-                if (tile + 1 < u1 * 4) fetch(tile + 1, Bn);
-                const int ncg = tile / KHP, kk = tile - ncg * KHP;
-                if (ncg != cg) {  // uniform: a new label group (the first one included)
-                    cg = ncg;
-                    cl = cg * 8 + (j & 7);
+                for (int s = 0; s < SF2; ++s) B[0][s] = sgm == 0 ? B0[s] : GF[s * 64];
+                for (int kk = ka; kk < kb; kk += 2) {
 #pragma unroll
-                    for (int i = 0; i < DX_MB; ++i) ier[i] = ieL[(g4 * 4 + i) * CP + cl];
-                    w1 = w2 = w3 = 0.0;
-                }
-                dx_d4 D = {0.0, 0.0, 0.0, 0.0};
+                    for (int h = 0; h < 2; ++h) {
+                        const bool use = k1 <= kmax;
+                        double *xp = XD + slot * C + cl;
+                        double xo = 0.0;
+                        if (use) xo = *xp;
+                        if (h == 0 || kk + 2 < kb) {  // the next tile's entries
+                            GF += SF2 * 64;
 #pragma unroll
-                for (int s = 0; s < SF2; ++s) {
-                    D = __builtin_amdgcn_mfma_f64_16x16x4f64(A[2 * s], B[s].x, D, 0, 0, 0);
-                    D = __builtin_amdgcn_mfma_f64_16x16x4f64(A[2 * s + 1], B[s].y, D, 0, 0, 0);
-                }
-                const int k1 = kk + 1 + (j >> 3) * KHP;  // the lane's duration
-                double d0 = ier[0] * D[0], d1 = ier[1] * D[1], d2 = ier[2] * D[2], d3 = ier[3] * D[3];
-                if (kk < DX_MB - 1 && k1 < DX_MB) {  // targets inside the block were served above
-                    d0 = k1 >= nbD ? d0 : 0.0;
-                    d1 = k1 + 1 >= nbD ? d1 : 0.0;
-                    d2 = k1 + 2 >= nbD ? d2 : 0.0;
-                    d3 = k1 + 3 >= nbD ? d3 : 0.0;
-                }
-                const double w0 = w1 + d0;
-                w1 = w2 + d1;
-                w2 = w3 + d2;
-                w3 = d3;
-                if (cl < C && k1 <= K + DX_MB - 1) {
-                    double *x = XD + dx_wrap(rbD + k1, KR) * C + cl;
-                    *x += w0;
-                }
-                if (tile + 1 == u1 * 4 || kk + 1 == KHP) {  // uniform: the run ends
-                    if (first) {
-                        pend[0][0] = w1; pend[0][1] = w2; pend[0][2] = w3;
-                        pk[0] = k1;
-                        pslot[0] = cl;
-                    } else {
-                        pend[1][0] = w1; pend[1][1] = w2; pend[1][2] = w3;
-                        pk[1] = k1;
-                        pslot[1] = cl;
+                            for (int s = 0; s < SF2; ++s) B[1 - h][s] = GF[s * 64];
+                        }
+                        dx_d4 D = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                        for (int s = 0; s < SF2; ++s) {
+                            D = __builtin_amdgcn_mfma_f64_16x16x4f64(A[2 * s], B[h][s].x, D, 0, 0, 0);
+                            D = __builtin_amdgcn_mfma_f64_16x16x4f64(A[2 * s + 1], B[h][s].y, D, 0, 0, 0);
+                        }
+                        if (kk < DX_MB - 1) {  // uniform: targets inside the block were served above
+                            D[0] = k1 >= nbD ? D[0] : 0.0;
+                            D[1] = k1 + 1 >= nbD ? D[1] : 0.0;
+                            D[2] = k1 + 2 >= nbD ? D[2] : 0.0;
+                        }
+                        const double w0 = fma(ier[0], D[0], w1);
+                        w1 = fma(ier[1], D[1], w2);
+                        w2 = fma(ier[2], D[2], w3);
+                        w3 = ier[3] * D[3];
+                        if (use) *xp = xo + w0;
+                        ++k1;
+                        ++slot;
+                        slot = slot == KR ? 0 : slot;
                     }
-                    first = false;
                 }
+                pend[sgm][0] = w1;
+                pend[sgm][1] = w2;
+                pend[sgm][2] = w3;
+                pk[sgm] = k1;      // duration of the first pending target
+                pslot[sgm] = cl;
+                u += (kb - ka) / 4;
             }
             lds_barrier();
 #pragma unroll
             for (int a = 0; a < 2; ++a)
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
-                    const int k1 = pk[a] + 1 + i;
+                    const int k1 = pk[a] + i;
                     if (pk[a] > 0 && pslot[a] < C && k1 <= K + DX_MB - 1) XD[dx_wrap(rbD + k1, KR) * C + pslot[a]] += pend[a][i];
                 }
-            if (cv && pos < nbk) Xq[dx_wrap(rb + pos, KR) * C + c] = 0.0;  // consumed: free for a later target
         }
-        lds_barrier();
-        // ---- checkpoints
         const int tlast = t0 + nbk - 1;
         t0 += nbk;
         rb = dx_wrap(rb + nbk, KR);
-        e = en;
-        if (!done) {
-            auto record = [&](double *ck, double *ckY) {
-                if (cv) {
-                    for (int d = pos; d < K; d += 4) {  // position t0 + d
-                        ck[(size_t)((t0 + d) % K) * C + c] = Xq[dx_wrap(rb + d, KR) * C + c];
+        // ---- checkpoints
+        if (anyrec) {
+            lds_barrier();
+            if (rec) {
+                auto record = [&](double *ck, double *ckY) {
+                    if ((lane & 31) < C) {
+                        for (int d = (wave >> 2) * 2 + (lane >> 5); d < K; d += 4)  // position t0 + d
+                            ck[(size_t)((t0 + d) % K) * C + (lane & 31)] = Xq[dx_wrap(rb + d, KR) * C + (lane & 31)];
                     }
-                    if (pos == 0) ck[KC + c] = avq[last * CP + c];
+                    if (chain && owner) ck[KC + c] = ylast;
+                    if (chain && lane == 0) *ckY = Y;
+                };
+                const size_t at = (size_t)tk.b * (N + 1) + tk.chunk;
+                if (tlast == lo) {
+                    record(p.ckA + at * ckstride, p.ckYA + at);
+                    Ybase = Y;
                 }
-                if ((tid & 127) == 0) *ckY = Y;
-            };
-            const size_t at = (size_t)tk.b * (N + 1) + tk.chunk;
-            if (tlast == lo) {
-                record(p.ckA + at * ckstride, p.ckYA + at);
-                Ybase = Y;
+                if (t0 > hi) {
+                    record(p.ckA2 + (at + 1) * ckstride, p.ckYA2 + at + 1);
+                    done = true;
+                }
             }
-            if (t0 > hi) {
-                record(p.ckA2 + (at + 1) * ckstride, p.ckYA2 + at + 1);
-                done = true;
-            }
+            lds_barrier();  // the ring is read by both waves of a task before either goes on
         }
     }
 }
 
 // ---------------------------------------------------------------------------
 // Backward ("pull"): for every label c a product [source labels] x [durations] . [durations] x [sixteen (task,
-// position) columns] of the table with the ring of v; IE_t(c) is applied to its result, which is then added up over
+// position) columns] of the table with the window of v; IE_t(c) is applied to its result, which is then added up over
 // the labels (b_t) and, weighted with a_t, over the source labels (mass of the segments that start at t).  A wave takes the
-// labels wave, wave + 8, ...; the waves' sums for b meet in LDS.
+// labels wave, wave + 8, ...; the waves' sums for b meet in LDS.  The window lies label by label along the positions, so
+// that the product's operand comes with immediate offsets; it slides downwards and is moved back every m positions.
+// Inside the block, one wave per task (0 .. 3) finishes the positions by row broadcasts, the other (4 .. 7) forms what
+// durations 1 .. 3 add to the mass that starts at a position, and writes the block's rows.
 // ---------------------------------------------------------------------------
-template <int MT>
+template <int MT, int SF2>
 __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tier)
 {
     extern __shared__ double lds_raw[];
+    constexpr int CT = 8 * SF2;
+    using R = RowMap<CT>;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g4 = lane >> 4, j = lane & 15;
     const int K = p.K, C = p.C, CC = C * C, KC = K * C, N = p.N;
     const DxGeom g = dx_geometry(K, C);
-    const int KR = g.kr, TS = g.ts, KS = g.ks;
-    constexpr int CPB = 16 * MT;
-    double *V = lds_raw;                       // [task][C][slot] v of the positions above
+    const int W = g.w, M = g.m, TS = g.ts, KS = g.ks;
+    constexpr int CPB = 16 * MT + 1;
+    double *V = lds_raw;                       // [task][C][W] v of the positions from the block upwards
     double *avL = V + DX_TASKS * TS;           // [task][pos][CPB] a_t
     double *ieL = avL + 16 * CPB;              // [task][pos][CPB] 1/ES
     double *esL = ieL + 16 * CPB;              // [task][pos][CPB] ES
     double *bL = esL + 16 * CPB;               // [task][pos][CPB] b_t
-    double *oL = bL + 16 * CPB;                // [task][pos][CPB] segments that start at t and leave the block
-    double *bp = oL + 16 * CPB;                // [wave][C][16] the waves' shares of b
-    double *Gs = bp + 8 * C * 16;              // [DX_MB-1][C][C] the durations inside a block
-    int *ctl = (int *)(Gs + (DX_MB - 1) * CC);
-    const int q = wave >> 1;
-    const int pos = (tid >> 5) & 3, c = tid & 31;    // own (task, position, label)
-    const int cs = (tid >> 2) & 31, sl = tid & 3;    // own (source label, slice of the labels) in the serial part
-    const bool cv = c < C;
+    double *wL = bL + 16 * CPB;                 // [k][task][pos][CPB] sum over the source labels of a_t G[k], k = 1 .. 3
+    double *oL = wL + 3 * 16 * CPB;            // [g4][task][pos][CPB] segments that start at t and leave the block, in four parts
+    double *bp = oL + 4 * 16 * CPB;            // [wave][C][16] the waves' shares of b
+    int *ctl = (int *)(bp + 8 * C * 16);       // per task: block length, row of its first position, rescale, record
+    int *sftL = ctl + 16;                      // [task][32] shift per label at a scaling-block boundary
+    const int q = wave & 3;
+    const bool chain = wave < 4;
+    const int c = R::label(lane), gr = R::group(lane);
+    const bool cv = c < C, owner = cv && gr == 0;
+    const int cc0 = cv ? c : 0;
     const DxTask tk = dx_task(p, blockIdx.x * DX_TASKS + q, 1, tier);
     const int L = tk.L, J = tk.J, lo = tk.lo, hi = tk.hi;
     const int s1 = min(hi + warm, L);
     const size_t row0 = (size_t)tk.b * (p.T + 1);
-    const double2 *EI = p.EI + row0 * C + (cv ? c : 0);
-    const int *nb = p.nbase + row0 * C + (cv ? c : 0);
-    const double *rowA = p.dtA + row0 * C + (cv ? c : 0);
+    const double2 *EI = p.EI + row0 * C + cc0;
+    const int *nb = p.nbase + row0 * C + cc0;
+    const double *rowA = p.dtA + row0 * C + cc0;
     double *rowV = p.dtV + row0 * C, *rowD = p.dtD + row0 * C, *rowYb = p.dtYb + row0;
     const size_t ckstride = (size_t)KC + C;
     double *Vq = V + q * TS;
     const int qo = q * 4 * CPB;
 
-    for (int i = tid; i < DX_TASKS * TS + 5 * 16 * CPB; i += DX_NT) lds_raw[i] = 0.0;
-    for (int i = tid; i < (DX_MB - 1) * CC; i += DX_NT) Gs[i] = i < K * CC ? p.G3[i] : 0.0;
-    lds_barrier();
-    // table entries of the serial part: durations 1 .. 3, source label cs, labels sl, sl + 4, ...
-    double gr[DX_MB - 1][8];
+    for (int i = tid; i < DX_TASKS * TS + 4 * 16 * CPB; i += DX_NT) lds_raw[i] = 0.0;
+    // the lane's part of the tables of durations 1 .. 3 (chain waves: contraction over the label)
+    double Ek[DX_MB - 1][R::HC];
 #pragma unroll
     for (int k = 0; k < DX_MB - 1; ++k)
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            const int cc = sl + 4 * m;
-            gr[k][m] = (cs < C && cc < C) ? Gs[(k * C + cs) * C + cc] : 0.0;
+        for (int i = 0; i < R::HC; ++i) {
+            const int o = (lane >> 5) * R::HC + i;
+            const bool ok = chain && k < K && cv && o < C;
+            const double v = p.G3[ok ? (size_t)k * CC + (size_t)c * C + o : 0];
+            Ek[k][i] = ok ? v : 0.0;
         }
+    lds_barrier();
     bool done = !tk.active;
-    double Yb = 0.0, Ytop = 0.0;
-    int t0 = s1 - 1, rb = KR - 1;  // slot of s1 is 0, of s1 - 1 is KR - 1, ...
+    double Yb = 0.0, Ytop = 0.0, blast = 0.0;
+    int t0 = s1 - 1, r0 = M + DX_MB - 1;  // window row of t0
     // a sequence that ends at s1 (exactly so when s1 = L): b = 1, v = ES; scale reference: a single 1
-    if (!done && cv && pos == 0) {
+    if (!done && chain) {
+        blast = c == 0 ? 1.0 : 0.0;
         const double v = EI[(size_t)s1 * C].x;
-        Vq[c * KR] = v;
-        bL[qo + c] = c == 0 ? 1.0 : 0.0;
-        if (s1 == L) rowV[(size_t)L * C + c] = v;
-        if (s1 == L && c == 0) rowYb[L] = 0.0;
+        if (owner) {
+            Vq[c * W + r0 + 1] = v;
+            if (s1 == L) rowV[(size_t)L * C + c] = v;
+        }
+        if (s1 == L && lane == 0) rowYb[L] = 0.0;
     }
-    int last = 0;  // position of the newest b in bL
-    double2 e = make_double2(0.0, 0.0);
-    double a = 0.0;
+    double2 e[DX_MB];
+    double a[DX_MB];
     auto load_rows = [&](const int tb) {
-        e = make_double2(0.0, 0.0);
-        a = 0.0;
-        if (!done && cv && tb - pos >= lo) {
-            e = EI[(size_t)(tb - pos) * C];
-            a = rowA[(size_t)(tb - pos) * C];
+#pragma unroll
+        for (int i = 0; i < DX_MB; ++i) {
+            e[i] = make_double2(0.0, 0.0);
+            a[i] = 0.0;
+            if (!done) {
+                const size_t o = (size_t)max(tb - i, lo) * C;
+                e[i] = EI[o];
+                if (!chain) a[i] = rowA[o];
+            }
         }
     };
     load_rows(t0);
+    auto nbdelta = [&](const int jb) {
+        return (chain && !done && jb >= 1 && (long)jb * J <= (long)L) ? nb[(size_t)jb * C] - nb[(size_t)(jb - 1) * C] : 0;
+    };
+    int jnx = s1 / J, dnx = nbdelta(jnx);
 
     for (;;) {
         int nbk = 0;
-        bool bd = false;
+        bool rec = false;
         if (!done) {
             nbk = min(DX_MB, t0 - lo + 1);
             if (t0 >= hi) nbk = min(nbk, t0 - hi + 1);     // the interval's upper end ends its block
             nbk = min(nbk, (t0 & (J - 1)) + 1);             // no scaling-block boundary inside a block
-            bd = ((t0 + 1) & (J - 1)) == 0;
+            rec = t0 - nbk + 1 == hi || t0 - nbk + 1 == lo;
         }
-        if ((tid & 127) == 0) {
-            ctl[q] = nbk;
-            ctl[4 + q] = rb;
-            ctl[8 + q] = bd;
+        const bool bd = !done && ((t0 + 1) & (J - 1)) == 0;
+        if (chain) {
+            if (bd) {
+                const int ex = safe_exponent(R::total(blast));
+                Yb += (double)ex;
+                if (owner) sftL[q * 32 + c] = dnx - ex;
+                --jnx;
+                dnx = nbdelta(jnx);
+            }
+            if (lane == 0) {
+                ctl[q] = nbk;
+                ctl[4 + q] = r0 < DX_MB - 1 ? M + DX_MB - 1 : r0;
+                ctl[8 + q] = bd || r0 < DX_MB - 1;
+                ctl[12 + q] = rec;
+            }
         }
         lds_barrier();
         if ((ctl[0] | ctl[1] | ctl[2] | ctl[3]) == 0) break;
+        // window rows: each wave of a task looks after its half of the labels
+        const int lh = (C + 1) / 2, c0 = chain ? 0 : lh, c1 = chain ? lh : C;
         if (ctl[8] | ctl[9] | ctl[10] | ctl[11]) {
+            if (r0 < DX_MB - 1) {
+                // move the K live rows back up, four labels by sixteen rows at a time
+                const int sh = M + DX_MB - 1 - r0;
+                for (int d0 = (K - 1) & ~15; d0 >= 0; d0 -= 16) {
+                    double v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int cl = c0 + 4 * u + g4, d = d0 + j;
+                        v[u] = (cl < c1 && d < K) ? Vq[cl * W + r0 + 1 + d] : 0.0;
+                    }
+                    lds_wave_fence();
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int cl = c0 + 4 * u + g4, d = d0 + j;
+                        if (cl < c1 && d < K) Vq[cl * W + r0 + 1 + d + sh] = v[u];
+                    }
+                    lds_wave_fence();
+                }
+                r0 += sh;
+            }
             if (bd) {
-                double pm = 0.0;
-                for (int i = 0; i < C; ++i) pm += bL[qo + last * CPB + i];
-                const int ex = safe_exponent(pm);
-                Yb += (double)ex;
-                if (cv) {
-                    const int sft = nb[(size_t)(t0 / J + 1) * C] - nb[(size_t)(t0 / J) * C] - ex;
-                    for (int r = pos; r < KR; r += 4) Vq[c * KR + r] = fmin(ldexp(Vq[c * KR + r], sft), DBL_MAX);
+                for (int cl = c0 + g4; cl < c1; cl += 4) {
+                    const int sft = sftL[q * 32 + cl];
+#pragma unroll 4
+                    for (int d = j; d < K; d += 16) {
+                        double *x = Vq + cl * W + r0 + 1 + d;
+                        *x = fmin(ldexp(*x, sft), DBL_MAX);
+                    }
                 }
             }
-            lds_barrier();
         }
-        // rows of the block (zeros beyond it), then the next block's requested
-        if (cv) {
-            const bool in = pos < nbk;
-            avL[qo + pos * CPB + c] = in ? a : 0.0;
-            ieL[qo + pos * CPB + c] = in ? e.y : 0.0;
-            esL[qo + pos * CPB + c] = in ? e.x : 0.0;
+        // rows of the block (zeros beyond it) and its window rows (zeros until they are known); the next rows requested
+        for (int cl = c0 + g4; cl < c1; cl += 4)
+            if (j < DX_MB && !done) Vq[cl * W + r0 - j] = 0.0;
+        if (owner) {
+#pragma unroll
+            for (int i = 0; i < DX_MB; ++i) {
+                if (chain) {
+                    esL[qo + i * CPB + c] = i < nbk ? e[i].x : 0.0;
+                    ieL[qo + i * CPB + c] = i < nbk ? e[i].y : 0.0;
+                } else {
+                    avL[qo + i * CPB + c] = i < nbk ? a[i] : 0.0;
+                }
+            }
         }
-        const double a_own = a, ie_own = e.y;
-        load_rows(t0 - nbk);
         lds_barrier();
-        // ---- durations that reach beyond the block (entries of its own positions are zeros in the ring)
+        // ---- durations that reach beyond the block
         {
             const int tn = j & 3, pn = j >> 2;  // column: task, position
             double An[4 * MT], bacc[MT][4];
@@ -487,45 +578,33 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
                     An[4 * m + v] = avL[(tn * 4 + pn) * CPB + 16 * m + 4 * v + g4];
                     bacc[m][v] = 0.0;
                 }
-            const int ib = dx_wrap(ctl[4 + tn] - pn, KR);
-            const int i0 = dx_wrap(ib + g4 + 1, KR);
-            for (int cc = wave; cc < C; cc += 8) {
-                const double *Vc = V + tn * TS + cc * KR;
-                const double2 *GB = (const double2 *)p.GB + (size_t)cc * KS * MT * 32 + lane;
-                dx_d4 D[MT];
+            const double *Vn = V + tn * TS + (ctl[4 + tn] - pn + g4 + 1);
+            // table entries: one double2 per lane and step (two label tiles) or pair of steps (one), four steps at a
+            // time, a group ahead (the first group of a label during the last of the label before)
+            constexpr int LG = 2 * MT;
+            double2 Gg[2][LG];
+            double bg[2][4];
+            auto fetch = [&](const int cc, const int s, double2 (&G)[LG], double (&b)[4]) {
+                const double2 *GB = (const double2 *)p.GB + ((size_t)cc * KS + s) * (MT * 32) + lane;
+                const double *Vc = Vn + cc * W + 4 * s;
 #pragma unroll
-                for (int m = 0; m < MT; ++m) D[m] = dx_d4{0.0, 0.0, 0.0, 0.0};
-                // steps in pairs; the table entries of a pair are requested two pairs ahead
-                constexpr int LP = MT;  // double2 loads per pair of steps
-                double2 G0[LP], G1[LP];
-                const int np = KS / 2;
+                for (int u = 0; u < LG; ++u) G[u] = GB[u * 64];
 #pragma unroll
-                for (int u = 0; u < LP; ++u) {
-                    G0[u] = GB[(size_t)u * 64];
-                    G1[u] = GB[(size_t)(min(1, np - 1) * LP + u) * 64];
-                }
-                int idx = i0;
-                for (int s = 0; s < np; ++s) {
-                    const int idx2 = dx_wrap(idx + 4, KR);
-                    const double b0 = Vc[idx], b1 = Vc[idx2];
-                    idx = dx_wrap(idx2 + 4, KR);
-                    double2 Gc[LP];
+                for (int u = 0; u < 4; ++u) b[u] = Vc[4 * u];
+            };
+            dx_d4 D[MT];
+            auto group = [&](const double2 (&G)[LG], const double (&b)[4]) {
 #pragma unroll
-                    for (int u = 0; u < LP; ++u) {
-                        Gc[u] = G0[u];
-                        G0[u] = G1[u];
-                        G1[u] = GB[(size_t)(min(s + 2, np - 1) * LP + u) * 64];
-                    }
-                    if (MT == 2) {  // .x, .y: the two label tiles of one step
-                        D[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(Gc[0].x, b0, D[0], 0, 0, 0);
-                        D[MT - 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(Gc[0].y, b0, D[MT - 1], 0, 0, 0);
-                        D[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(Gc[LP - 1].x, b1, D[0], 0, 0, 0);
-                        D[MT - 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(Gc[LP - 1].y, b1, D[MT - 1], 0, 0, 0);
-                    } else {        // .x, .y: the two steps
-                        D[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(Gc[0].x, b0, D[0], 0, 0, 0);
-                        D[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(Gc[0].y, b1, D[0], 0, 0, 0);
+                for (int u = 0; u < 4; ++u) {
+                    if (MT == 2) {
+                        D[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(G[u % LG].x, b[u], D[0], 0, 0, 0);
+                        D[MT - 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(G[u % LG].y, b[u], D[MT - 1], 0, 0, 0);
+                    } else {
+                        D[0] = __builtin_amdgcn_mfma_f64_16x16x4f64((u & 1) ? G[u / 2].y : G[u / 2].x, b[u], D[0], 0, 0, 0);
                     }
                 }
+            };
+            auto finish = [&](const int cc) {
                 const double ie = ieL[(tn * 4 + pn) * CPB + cc];
                 double o = 0.0;
 #pragma unroll
@@ -535,8 +614,54 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
                         bacc[m][v] = fma(ie, D[m][v], bacc[m][v]);
                         o = fma(An[4 * m + v], D[m][v], o);
                     }
-                o = add_across_32(add_across_16(o));
-                if (g4 == 0) oL[(tn * 4 + pn) * CPB + cc] = ie * o;
+                oL[((g4 * 4 + tn) * 4 + pn) * CPB + cc] = o;
+            };
+            if (wave < C) {
+                // groups of all the wave's labels in one sequence, two per turn (even and odd buffers)
+                const int ng = KS / 4, total = ((C - wave + 7) / 8) * ng;
+                int cc = wave, gq = 0;        // group being multiplied
+                int ccn = wave, gn = 0;       // group being fetched
+                auto next = [&](int &cx, int &gx) {
+                    if (++gx == ng) {
+                        gx = 0;
+                        cx += 8;
+                    }
+                };
+                fetch(ccn, 0, Gg[0], bg[0]);
+                next(ccn, gn);
+                for (int i = 0; i < total; i += 2) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        if (i + h < total) {  // uniform
+                            if (i + h + 1 < total) fetch(ccn, 4 * gn, Gg[1 - h], bg[1 - h]);
+                            next(ccn, gn);
+                            if (gq == 0) {
+#pragma unroll
+                                for (int m = 0; m < MT; ++m) D[m] = dx_d4{0.0, 0.0, 0.0, 0.0};
+                            }
+                            group(Gg[h], bg[h]);
+                            if (gq == ng - 1) finish(cc);
+                            next(cc, gq);
+                        }
+                    }
+                }
+            }
+            // sums over the source labels of a_t G[k], k = 1 .. 3, for what durations inside the block add to the mass
+            // that starts at a position: one product of the sixteen rows per (duration, label tile), waves 7, 6, ...
+            for (int tile = 7 - wave; tile < (DX_MB - 1) * MT; tile += 8) {
+                dx_d4 w = {0.0, 0.0, 0.0, 0.0};
+                const double2 *GS = (const double2 *)p.GS + (size_t)tile * (SF2 * 64) + lane;
+#pragma unroll
+                for (int s = 0; s < SF2; ++s) {
+                    const double2 gs = GS[s * 64];
+                    const double *ar = avL + (tn * 4 + pn) * CPB + 8 * s + g4;
+                    w = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[0], gs.x, w, 0, 0, 0);
+                    w = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[4], gs.y, w, 0, 0, 0);
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {  // row 4 v + g4: task g4, position v
+                    wL[(((tile / MT) * 4 + g4) * 4 + v) * CPB + (tile % MT) * 16 + j] = w[v];
+                }
             }
 #pragma unroll
             for (int m = 0; m < MT; ++m)
@@ -546,82 +671,72 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
                     if (r < C) bp[(wave * C + r) * 16 + j] = bacc[m][v];
                 }
         }
-        // what a segment of duration k <= pos inside the block adds to the mass that starts at the thread's position:
-        // sum over the source labels of a G[k] (the factor v follows when it is known)
-        double wk[DX_MB - 1];
-#pragma unroll
-        for (int k = 0; k < DX_MB - 1; ++k) {
-            wk[k] = 0.0;
-            if (cv && k < pos && pos < nbk) {
-                double m = 0.0;
-#pragma unroll 8
-                for (int o = 0; o < C; ++o) m = fma(avL[qo + pos * CPB + o], Gs[(k * C + o) * C + c], m);
-                wk[k] = m;
-            }
-        }
+        load_rows(t0 - nbk);  // the next block's, with the serial part to arrive
         lds_barrier();
-        if (cs < C) {
+        if ((tid >> 4) < C) {  // 512 threads: source label, column
             double b = 0.0;
 #pragma unroll
-            for (int w = 0; w < 8; ++w) b += bp[(w * C + cs) * 16 + q + 4 * sl];
-            bL[qo + sl * CPB + cs] = b;
+            for (int w = 0; w < 8; ++w) b += bp[(w * C + (tid >> 4)) * 16 + j];
+            bL[((j & 3) * 4 + (j >> 2)) * CPB + (tid >> 4)] = b;
         }
         lds_barrier();
-        // ---- finish the positions one after the other
+        if (chain) {
+            // ---- finish the positions one after the other
+            double bf[DX_MB], ie[DX_MB], es[DX_MB], v[DX_MB];
 #pragma unroll
-        for (int i = 0; i < DX_MB; ++i) {
-            if (i < nbk && cs < C) {
-                double s = 0.0;
+            for (int i = 0; i < DX_MB; ++i) {
+                bf[i] = bL[qo + i * CPB + cc0];
+                ie[i] = ieL[qo + i * CPB + cc0];
+                es[i] = esL[qo + i * CPB + cc0];
+            }
 #pragma unroll
-                for (int k = 1; k <= i; ++k) {
-                    const int slot = dx_wrap(rb - i + k, KR);  // position t0 - i + k, finished just before
+            for (int i = 0; i < DX_MB; ++i) {
+                v[i] = 0.0;
+                if (i < nbk) {  // uniform
+                    double b = bf[i];
 #pragma unroll
-                    for (int m = 0; m < 8; ++m) {
-                        const int cc = sl + 4 * m;
-                        if (cc < C) s = fma(gr[k - 1][m], ieL[qo + i * CPB + cc] * Vq[cc * KR + slot], s);
+                    for (int k = 1; k <= i; ++k)  // ends at position i - k of the block, finished before
+                        b += R::product(cv ? ie[i] * v[i - k] : 0.0, Ek[k - 1]);
+                    b = cv ? b : 0.0;
+                    v[i] = b * es[i];
+                    blast = b;
+                    if (owner) {
+                        bL[qo + i * CPB + c] = b;
+                        Vq[c * W + r0 - i] = v[i];
                     }
                 }
-                if (i > 0) {  // over the four slices: lanes of a quad
-                    s += __shfl_xor(s, 1);
-                    s += __shfl_xor(s, 2);
-                }
-                if (sl == 0) {
-                    const double b = bL[qo + i * CPB + cs] + s;
-                    bL[qo + i * CPB + cs] = b;
-                    Vq[cs * KR + dx_wrap(rb - i, KR)] = b * esL[qo + i * CPB + cs];
-                }
             }
-            lds_barrier();
         }
-        if (nbk) last = nbk - 1;
-        if (cv && pos < nbk) {
-            const int tt = t0 - pos;
-            if (tt < hi) {
-                const double b = bL[qo + pos * CPB + c];
-                double o = oL[qo + pos * CPB + c];
+        lds_barrier();
+        if (!chain && owner) {
+            double v[DX_MB];
 #pragma unroll
-                for (int k = 1; k < DX_MB; ++k)
-                    if (k <= pos) o = fma(wk[k - 1] * ie_own, Vq[c * KR + dx_wrap(rb - pos + k, KR)], o);
-                rowV[(size_t)tt * C + c] = Vq[c * KR + dx_wrap(rb - pos, KR)];
-                rowD[(size_t)tt * C + c] = o - (tt >= 1 ? a_own * b : 0.0);
-                if (c == 0) rowYb[tt] = Yb - Ytop;
+            for (int i = 0; i < DX_MB; ++i) v[i] = Vq[c * W + r0 - i];
+#pragma unroll
+            for (int i = 0; i < DX_MB; ++i) {
+                const int tt = t0 - i;
+                if (i < nbk && tt < hi) {
+                    const int o = qo + i * CPB + c;
+                    double out = (oL[o] + oL[o + 16 * CPB]) + (oL[o + 32 * CPB] + oL[o + 48 * CPB]);
+#pragma unroll
+                    for (int k = 1; k <= i; ++k) out = fma(wL[(k - 1) * 16 * CPB + o], v[i - k], out);
+                    rowV[(size_t)tt * C + c] = v[i];
+                    rowD[(size_t)tt * C + c] = out * ieL[o] - (tt >= 1 ? avL[o] * bL[o] : 0.0);
+                }
             }
         }
-        const int tlast = t0 - nbk + 1;
-        const int rlast = dx_wrap(rb - nbk + 1, KR);  // slot of tlast
+        if (chain && lane < nbk && t0 - lane < hi) rowYb[t0 - lane] = Yb - Ytop;
+        const int tlast = t0 - nbk + 1, rlast = r0 - nbk + 1;
         t0 -= nbk;
-        rb = dx_wrap(rb - nbk, KR);
-        // slots of the next block's positions: free (their old contents lie more than K above)
-        if (!done && cv) Vq[c * KR + dx_wrap(rb - pos, KR)] = 0.0;
-        if (!done) {
+        r0 -= nbk;
+        if (rec) {
+            // (window rows are not written again before the next block's first barrier)
             auto record = [&](double *ck, double *ckY) {
-                if (cv) {
-                    for (int d = pos; d < K; d += 4) {  // position tlast + d
-                        ck[(size_t)((tlast + d) % K) * C + c] = Vq[c * KR + dx_wrap(rlast + d, KR)];
-                    }
-                    if (pos == 0) ck[KC + c] = bL[qo + last * CPB + c];
-                }
-                if ((tid & 127) == 0) *ckY = Yb;
+                for (int cl = wave >> 2; cl < C; cl += 2)
+                    for (int d = lane; d < K; d += 64)  // position tlast + d
+                        ck[(size_t)((tlast + d) % K) * C + cl] = Vq[cl * W + rlast + d];
+                if (chain && owner) ck[KC + c] = blast;
+                if (chain && lane == 0) *ckY = Yb;
             };
             const size_t at = (size_t)tk.b * (N + 1);
             if (tlast == hi && hi < L) {
@@ -711,9 +826,14 @@ __global__ __launch_bounds__(NT) void k_dx_emis(Params p)
 constexpr int DXA_K = 64;
 constexpr int DXA_VR = DT_TG + DXA_K + 4;   // rows of v a group of positions can reach
 constexpr int DXA_W = 8;                     // waves per workgroup
-__host__ __device__ constexpr size_t dxa_lds_doubles(int mt) { return (size_t)DT_TG * (16 * mt + 1) + (size_t)DXA_W * (DT_TG + DXA_VR); }
+// LDS doubles: a rows, the row factors, per wave the label's 1/ES and v rows
+__host__ __device__ inline size_t dxa_lds_doubles(int mt, int K)
+{
+    return (size_t)DT_TG * (16 * mt + 1) + DT_TG + 2 * (size_t)(K + DT_TG + DXA_K + 4) + (size_t)DXA_W * (DT_TG + DXA_VR);
+}
+
 template <int MT>
-__global__ __launch_bounds__(64 * DXA_W, 2) void k_dx_acc(Params p)
+__global__ __launch_bounds__(64 * DXA_W, 4) void k_dx_acc(Params p)
 {
     extern __shared__ double lds_raw[];
     constexpr int AS = 16 * MT + 1;
@@ -725,8 +845,12 @@ __global__ __launch_bounds__(64 * DXA_W, 2) void k_dx_acc(Params p)
     const int item = blockIdx.y * DXA_W + wave;
     const bool mine = item < C * kgs;
     const int c = mine ? item / kgs : 0, kA = mine ? (item % kgs) * DXA_K : 0;  // durations kA + 1 .. kA + 64
+    const int nfac = K + DT_TG + DXA_K + 4;
     double *Arow = lds_raw;                            // [DT_TG][AS]  a_t(c') w_b 2^(YA(t) - YA(group)), zero beyond C
-    double *IEw = Arow + DT_TG * AS + wave * (DT_TG + DXA_VR);  // [DT_TG] 1/ES of the wave's label
+    double *fA = Arow + DT_TG * AS;                    // [DT_TG] w_b 2^(YA(t) - YA(group))
+    double *fV = fA + DT_TG;                           // [nfac] mantissa of 2^(YA(group) + YB(s)) / Z, s = group + 1 + r
+    int *eV = (int *)(fV + nfac);                      // [nfac] its exponent
+    double *IEw = fV + 2 * nfac + wave * (DT_TG + DXA_VR);  // [DT_TG] 1/ES of the wave's label
     double *Vw = IEw + DT_TG;                          // [DXA_VR] v of the wave's label from position group + kA + 1 on
     dx_d4 acc[MT][4];
 #pragma unroll
@@ -738,49 +862,62 @@ __global__ __launch_bounds__(64 * DXA_W, 2) void k_dx_acc(Params p)
     for (int task = blockIdx.x; task < ntask; task += gridDim.x) {
         const int b = task / N, chunk = task % N;
         const SeqHdr h = p.hdr[b];
-        const int L = h.L, J = h.J;
+        const int L = h.L, J = h.J, Jl = 31 - __clz(h.J);
         const int lo = chunk * Delta;
         if (lo >= L) continue;
         const int hi = min(lo + Delta, L);
         const size_t row0 = (size_t)b * (p.T + 1);
         const double2 *EI = p.EI + row0 * C;
-        const int *nb = p.nbase + row0 * C;
-        const double *rowA = p.dtA + row0 * C, *rowV = p.dtV + row0 * C;
+        const int *nb = p.nbase + row0 * C + c;
+        const double *rowA = p.dtA + row0 * C, *rowV = p.dtV + row0 * C + c;
         const double *rowY = p.dtY + row0, *rowYb = p.dtYb + row0;
         const double *ckYA = p.ckYA + (size_t)b * (N + 1);
         const double lz2 = h.logZ * LOG2E;
         const double wb = p.grad_logz ? (double)p.grad_logz[b] : 1.0;
         for (int tg0 = lo; tg0 < hi;) {
-            const int tg1 = min(min(hi, (tg0 / J + 1) * J), tg0 + DT_TG);
-            const int ng = tg1 - tg0, jt = tg0 / J;
+            const int tg1 = min(min(hi, ((tg0 >> Jl) + 1) << Jl), tg0 + DT_TG);
+            const int ng = tg1 - tg0, jt = tg0 >> Jl;
             const double yA0 = ckYA[tg0 == 0 ? 0 : (tg0 - 1) / Delta] + rowY[tg0];
-            __syncthreads();  // the previous group is done with the staged rows
-            for (int i = tid; i < ((ng + 3) & ~3) * 16 * MT; i += 64 * DXA_W) {
-                const int r = i / (16 * MT), o = i % (16 * MT), tt = tg0 + r;
-                double a = 0.0;
-                if (r < ng && o < C) {
-                    const double yA = ckYA[tt == 0 ? 0 : (tt - 1) / Delta] + rowY[tt];
-                    a = rowA[(size_t)tt * C + o] * wb * exp2(yA - yA0);
-                }
-                Arow[r * AS + o] = a;
+            // the wave's raw rows, requested before the barriers
+            double vr[2];
+            int nr[2];
+            const int nbt = nb[(size_t)jt * C];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int s = min(tg0 + kA + 1 + lane + 64 * u, L);
+                vr[u] = rowV[(size_t)s * C];
+                nr[u] = nb[(size_t)(s >> Jl) * C];
             }
-            if (lane < DT_TG) IEw[lane] = (mine && lane < ng) ? EI[(size_t)(tg0 + lane) * C + c].y : 0.0;
-            const int nbt = nb[(size_t)jt * C + c];
-            for (int r = lane; r < ng + DXA_K + 3; r += 64) {
-                const int s = tg0 + kA + 1 + r;
-                double v = 0.0;
-                if (mine && s <= L && r < ng + DXA_K) {
-                    const int js = s / J;
+            const double iel = EI[(size_t)min(tg0 + (lane & 31), L) * C + c].y;
+            __syncthreads();  // the previous group is done with the staged rows
+            // scale factors of the group's a rows and of the v rows any of its durations reaches; all exponents are
+            // combined before anything is formed, so that an empty row stays zero and nothing passes through infinity
+            for (int i = tid; i < DT_TG + ng + K; i += 64 * DXA_W) {
+                if (i < DT_TG) {
+                    const int tt = tg0 + i;
+                    fA[i] = i < ng ? wb * exp2(ckYA[tt == 0 ? 0 : (tt - 1) / Delta] + rowY[tt] - yA0) : 0.0;
+                } else {
+                    const int r = i - DT_TG, s = min(tg0 + 1 + r, L);
                     const double yB = s == L ? 0.0 : dt_ytop(p, b, s / Delta, L) + rowYb[s];
-                    // all exponents are combined before anything is formed, so that an empty row
-                    // stays zero and nothing passes through infinity
                     const double lf = (yA0 + yB) - lz2;
                     const double fl = floor(lf);
-                    const int sh = nb[(size_t)js * C + c] - nbt;
-                    const double ef = fmin(fmax(fl, -100000.0), 100000.0);
-                    v = fmin(ldexp(rowV[(size_t)s * C + c] * exp2(lf - fl), sh + (int)ef), DBL_MAX);
+                    fV[r] = exp2(lf - fl);
+                    eV[r] = (int)fmin(fmax(fl, -100000.0), 100000.0);
                 }
-                Vw[r] = v;
+            }
+            __syncthreads();
+            for (int i = tid; i < ((ng + 3) & ~3) * 16 * MT; i += 64 * DXA_W) {
+                const int r = i / (16 * MT), o = i % (16 * MT);
+                Arow[r * AS + o] = (r < ng && o < C) ? rowA[(size_t)(tg0 + r) * C + o] * fA[r] : 0.0;
+            }
+            if (lane < DT_TG) IEw[lane] = (mine && lane < ng) ? iel : 0.0;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int r = lane + 64 * u, s = tg0 + kA + 1 + r;
+                double v = 0.0;
+                if (mine && s <= L && r < ng + DXA_K && kA + r < ng + K)
+                    v = fmin(ldexp(vr[u] * fV[kA + r], nr[u] - nbt + eV[kA + r]), DBL_MAX);
+                if (r < DXA_VR) Vw[r] = v;
             }
             __syncthreads();
             for (int i0 = 0; i0 < ng; i0 += 4) {  // positions i0 .. i0+3 (zero rows beyond the group)
@@ -788,12 +925,13 @@ __global__ __launch_bounds__(64 * DXA_W, 2) void k_dx_acc(Params p)
 #pragma unroll
                 for (int m = 0; m < MT; ++m) A[m] = Arow[(i0 + g4) * AS + 16 * m + j];
                 const double ie = IEw[i0 + g4];
+                double bv[4];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const double bv = ie * Vw[i0 + g4 + 16 * k + j];
+                for (int k = 0; k < 4; ++k) bv[k] = ie * Vw[i0 + g4 + 16 * k + j];
 #pragma unroll
-                    for (int m = 0; m < MT; ++m) acc[m][k] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[m], bv, acc[m][k], 0, 0, 0);
-                }
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) acc[m][k] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[m], bv[k], acc[m][k], 0, 0, 0);
             }
             tg0 = tg1;
         }

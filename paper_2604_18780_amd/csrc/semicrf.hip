@@ -675,7 +675,7 @@ int dt_scan_interval(int B, int T, int K, int C, int ckpt_interval, const DtGeom
 }
 
 struct DtLayout {
-    size_t g3, gf, gb, dta, dty, dtv, dtd, dtyb, partg, sumg, total;
+    size_t g3, gf, gb, gs, dta, dty, dtv, dtd, dtyb, partg, sumg, total;
     int nwg;
 };
 
@@ -697,6 +697,7 @@ DtLayout dt_layout(int B, int T, int K, int C, int N, int want_grad)
     l.g3 = off; off += align_up(kcc * 8);
     l.gf = off; off += g.ok ? align_up(g.gf * 8) : 0;
     l.gb = off; off += g.ok ? align_up(g.gb * 8) : 0;
+    l.gs = off; off += g.ok ? align_up(g.gs * 8) : 0;
     l.dta = off; off += align_up((size_t)B * t1 * C * 8);
     l.dty = off; off += align_up((size_t)B * t1 * 8);
     l.dtv = off; off += want_grad ? align_up((size_t)B * t1 * C * 8) : 0;
@@ -719,7 +720,7 @@ int launch_dx_fwd(const Params &p, const DxGeom &g, hipStream_t st, int warm, in
 
 int launch_dx_fwd_any(const Params &p, const DxGeom &g, hipStream_t st, int warm, int tier)
 {
-    switch (g.sf2) {
+    switch (g.ncg) {
     case 1: return launch_dx_fwd<1>(p, g, st, warm, tier);
     case 2: return launch_dx_fwd<2>(p, g, st, warm, tier);
     case 3: return launch_dx_fwd<3>(p, g, st, warm, tier);
@@ -727,19 +728,29 @@ int launch_dx_fwd_any(const Params &p, const DxGeom &g, hipStream_t st, int warm
     }
 }
 
-template <int MT>
+template <int MT, int SF2>
 int launch_dx_bwd(const Params &p, const DxGeom &g, hipStream_t st, int warm, int tier)
 {
-    if (hipFuncSetAttribute((const void *)k_dx_bwd<MT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g.lds_b) != hipSuccess)
+    if (hipFuncSetAttribute((const void *)k_dx_bwd<MT, SF2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g.lds_b) != hipSuccess)
         return SEMICRF_ELAUNCH;
-    hipLaunchKernelGGL((k_dx_bwd<MT>), dim3((p.B * p.N + DX_TASKS - 1) / DX_TASKS), dim3(DX_NT), g.lds_b, st, p, warm, tier);
+    hipLaunchKernelGGL((k_dx_bwd<MT, SF2>), dim3((p.B * p.N + DX_TASKS - 1) / DX_TASKS), dim3(DX_NT), g.lds_b, st, p, warm, tier);
     return SEMICRF_OK;
+}
+
+int launch_dx_bwd_any(const Params &p, const DxGeom &g, hipStream_t st, int warm, int tier)
+{
+    switch (g.ncg) {
+    case 1: return launch_dx_bwd<1, 1>(p, g, st, warm, tier);
+    case 2: return launch_dx_bwd<1, 2>(p, g, st, warm, tier);
+    case 3: return launch_dx_bwd<2, 3>(p, g, st, warm, tier);
+    default: return launch_dx_bwd<2, 4>(p, g, st, warm, tier);
+    }
 }
 
 template <int MT>
 int launch_dx_acc(const Params &p, hipStream_t st)
 {
-    const size_t lds = dxa_lds_doubles(MT) * sizeof(double);
+    const size_t lds = dxa_lds_doubles(MT, p.K) * sizeof(double);  // at most 36 KB (K <= 1024)
     const int items = p.C * ((p.K + DXA_K - 1) / DXA_K);
     hipLaunchKernelGGL((k_dx_acc<MT>), dim3(p.dt_nwg, (items + DXA_W - 1) / DXA_W), dim3(64 * DXA_W), lds, st, p);
     return SEMICRF_OK;
@@ -807,6 +818,7 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
     p.G3 = (double *)(dw + dl.g3);
     p.GF = (double *)(dw + dl.gf);
     p.GB = (double *)(dw + dl.gb);
+    p.GS = (double *)(dw + dl.gs);
     p.dtA = (double *)(dw + dl.dta);
     p.dtY = (double *)(dw + dl.dty);
     p.dtV = (double *)(dw + dl.dtv);
@@ -819,7 +831,7 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
     if (rc != SEMICRF_OK) return rc;
     const size_t kcc = (size_t)p.K * p.C * p.C;
     const DxGeom dx = dx_geometry(p.K, p.C);
-    const size_t ntable = kcc + (dx.ok ? dx.gf + dx.gb : 0);
+    const size_t ntable = kcc + (dx.ok ? dx.gf + dx.gb + dx.gs : 0);
     if (dx.ok)
         hipLaunchKernelGGL(k_dx_tables, dim3((unsigned)((ntable + NT - 1) / NT)), dim3(NT), 0, st, p);
     else
@@ -832,7 +844,7 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
                        : launch_dt_fwd_any(p, g, st, p.B * p.N, warm[tier], tier, 0);
             if (rc != SEMICRF_OK) return rc;
             if (grad) {
-                if (dx.ok) rc = dx.mt == 1 ? launch_dx_bwd<1>(p, dx, st, warm[tier], tier) : launch_dx_bwd<2>(p, dx, st, warm[tier], tier);
+                if (dx.ok) rc = launch_dx_bwd_any(p, dx, st, warm[tier], tier);
                 else rc = launch_dt_bwd_any(p, g, st, p.B * p.N, warm[tier], tier, 0);
                 if (rc != SEMICRF_OK) return rc;
             }
