@@ -136,6 +136,8 @@ struct Params {
     double *dtV;          // [B][T+1][C] backward messages v_t(c) = b_t(c) ES_t(c), scaled
     double *dtD;          // [B][T+1][C] (mass of the segments that start at t) - (that end at t), scaled
     double *dtYb;         // [B][T+1]    log2 scale of those two rows relative to the interval's upper end
+    double *dtMA, *dtMB;  // [B][T+1] factors in [1, 2) of 2^YA / Z and 2^YB (matrix-core marginals; dtMA null otherwise)
+    int2 *dtE;            // [B][T+1] their exponents
     double *partG;        // [dt_nwg][K][C][C] per-workgroup sums of the weighted segment marginals
     double *sumG;         // [K][C][C] their fixed-order total
     int dt_nwg;

@@ -648,6 +648,7 @@ __global__ __launch_bounds__(NT) void k_dt_fin_dur(Params p)
     if (i >= p.K * C) return;
     const int k = i / C, c = i % C;
     double s = 0.0;
+#pragma unroll 8
     for (int o = 0; o < C; ++o) s += p.sumG[(size_t)k * CC + (size_t)o * C + c];
     p.grad_dur[i] = (float)s;
 }

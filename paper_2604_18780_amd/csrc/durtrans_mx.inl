@@ -772,6 +772,18 @@ __global__ __launch_bounds__(NT) void k_dx_emis(Params p)
     const double *ckYA = p.ckYA + (size_t)b * (N + 1);
     const double logZ = p.hdr[b].logZ;
     const double ytop = dt_ytop(p, b, jv, L);
+    // absolute scales of the stored rows for k_dx_acc, split into a factor in [1, 2) and an exponent:
+    // 2^YA(t) / Z and 2^YB(t)
+    if (p.dtMA) {
+        for (int tt = lo + (int)threadIdx.x; tt < hi || (tt == L && hi == L); tt += NT) {
+            const double yb = tt == L ? 0.0 : ytop + rowYb[tt];
+            const double ya = tt == L ? 0.0 : ckYA[tt == 0 ? 0 : (tt - 1) / Delta] + rowY[tt] - logZ * LOG2E;
+            const double fa = floor(ya), fb = floor(yb);
+            p.dtMA[row0 + tt] = exp2(ya - fa);
+            p.dtMB[row0 + tt] = exp2(yb - fb);
+            p.dtE[row0 + tt] = make_int2((int)fmin(fmax(fa, -1.0e8), 1.0e8), (int)fmin(fmax(fb, -1.0e8), 1.0e8));
+        }
+    }
     const int per = (hi - lo + 7) / 8;
     const int th = hi - sg * per, tl = max(lo, th - per);  // positions tl .. th-1, walked downwards
     const bool act = c < C;
@@ -826,17 +838,22 @@ __global__ __launch_bounds__(NT) void k_dx_emis(Params p)
 constexpr int DXA_K = 64;
 constexpr int DXA_VR = DT_TG + DXA_K + 4;   // rows of v a group of positions can reach
 constexpr int DXA_W = 8;                     // waves per workgroup
-// LDS doubles: a rows, the row factors, per wave the label's 1/ES and v rows
-__host__ __device__ inline size_t dxa_lds_doubles(int mt, int K)
-{
-    return (size_t)DT_TG * (16 * mt + 1) + DT_TG + 2 * (size_t)(K + DT_TG + DXA_K + 4) + (size_t)DXA_W * (DT_TG + DXA_VR);
-}
+// Work is handed out in pieces of at most this many positions of an interval: whole intervals would leave the
+// persistent workgroups with unequal shares.
+constexpr int DXA_PIECE = 64;
+__host__ __device__ constexpr int dxa_pieces(int Delta) { return (Delta + DXA_PIECE - 1) / DXA_PIECE; }
+// LDS doubles: a rows, per wave the label's 1/ES and v rows
+__host__ __device__ constexpr size_t dxa_lds_doubles(int mt) { return (size_t)DT_TG * (16 * mt + 1) + (size_t)DXA_W * (DT_TG + DXA_VR); }
 
-template <int MT>
+// A group of positions (at most DT_TG, inside one scaling block) goes through LDS; the rows of the next group are
+// requested before the products of this one.  Scales: k_dx_emis has left them as factor and exponent, all exponents
+// are combined before anything is formed, so that an empty row stays zero and nothing passes through infinity.
+template <int MT, int KT>  // KT: duration tiles of sixteen with anything in them (four where K > 64)
 __global__ __launch_bounds__(64 * DXA_W, 4) void k_dx_acc(Params p)
 {
     extern __shared__ double lds_raw[];
     constexpr int AS = 16 * MT + 1;
+    constexpr int AE = DT_TG * 16 * MT / (64 * DXA_W);  // a elements per thread
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g4 = lane >> 4, j = lane & 15;
@@ -845,95 +862,94 @@ __global__ __launch_bounds__(64 * DXA_W, 4) void k_dx_acc(Params p)
     const int item = blockIdx.y * DXA_W + wave;
     const bool mine = item < C * kgs;
     const int c = mine ? item / kgs : 0, kA = mine ? (item % kgs) * DXA_K : 0;  // durations kA + 1 .. kA + 64
-    const int nfac = K + DT_TG + DXA_K + 4;
-    double *Arow = lds_raw;                            // [DT_TG][AS]  a_t(c') w_b 2^(YA(t) - YA(group)), zero beyond C
-    double *fA = Arow + DT_TG * AS;                    // [DT_TG] w_b 2^(YA(t) - YA(group))
-    double *fV = fA + DT_TG;                           // [nfac] mantissa of 2^(YA(group) + YB(s)) / Z, s = group + 1 + r
-    int *eV = (int *)(fV + nfac);                      // [nfac] its exponent
-    double *IEw = fV + 2 * nfac + wave * (DT_TG + DXA_VR);  // [DT_TG] 1/ES of the wave's label
+    double *Arow = lds_raw;                            // [DT_TG][AS]  a_t(c') w_b 2^YA(t) / Z in the group's scale
+    double *IEw = Arow + DT_TG * AS + wave * (DT_TG + DXA_VR);  // [DT_TG] 1/ES of the wave's label
     double *Vw = IEw + DT_TG;                          // [DXA_VR] v of the wave's label from position group + kA + 1 on
-    dx_d4 acc[MT][4];
+    dx_d4 acc[MT][KT];
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) acc[m][k] = dx_d4{0.0, 0.0, 0.0, 0.0};
+        for (int k = 0; k < KT; ++k) acc[m][k] = dx_d4{0.0, 0.0, 0.0, 0.0};
 
-    const int ntask = p.B * N;
-    for (int task = blockIdx.x; task < ntask; task += gridDim.x) {
-        const int b = task / N, chunk = task % N;
-        const SeqHdr h = p.hdr[b];
-        const int L = h.L, J = h.J, Jl = 31 - __clz(h.J);
-        const int lo = chunk * Delta;
-        if (lo >= L) continue;
-        const int hi = min(lo + Delta, L);
-        const size_t row0 = (size_t)b * (p.T + 1);
-        const double2 *EI = p.EI + row0 * C;
+    const int pieces = dxa_pieces(Delta), nitem = p.B * N * pieces;
+    int it = blockIdx.x, tg0 = 0, tg1 = 0, hi = 0, L = 0, Jl = 0;
+    size_t row0 = 0;
+    double wb = 1.0;
+    // the next group: false when there is none
+    auto advance = [&]() {
+        tg0 = tg1;
+        while (tg0 >= hi) {
+            if (it >= nitem) return false;
+            const int task = it / pieces, b = task / N, chunk = task % N;
+            const int lo = chunk * Delta + (it % pieces) * DXA_PIECE;
+            const SeqHdr h = p.hdr[b];
+            L = h.L;
+            Jl = 31 - __clz(h.J);
+            hi = min(min(lo + DXA_PIECE, (chunk + 1) * Delta), L);
+            tg0 = lo;
+            row0 = (size_t)b * (p.T + 1);
+            wb = p.grad_logz ? (double)p.grad_logz[b] : 1.0;
+            it += gridDim.x;
+        }
+        tg1 = min(min(hi, ((tg0 >> Jl) + 1) << Jl), tg0 + DT_TG);
+        return true;
+    };
+    double ar[AE], am[AE], vr[2], vm[2], ie = 0.0;
+    int ae[AE], vs[2], nbt = 0, eA0 = 0;
+    auto request = [&]() {
         const int *nb = p.nbase + row0 * C + c;
-        const double *rowA = p.dtA + row0 * C, *rowV = p.dtV + row0 * C + c;
-        const double *rowY = p.dtY + row0, *rowYb = p.dtYb + row0;
-        const double *ckYA = p.ckYA + (size_t)b * (N + 1);
-        const double lz2 = h.logZ * LOG2E;
-        const double wb = p.grad_logz ? (double)p.grad_logz[b] : 1.0;
-        for (int tg0 = lo; tg0 < hi;) {
-            const int tg1 = min(min(hi, ((tg0 >> Jl) + 1) << Jl), tg0 + DT_TG);
-            const int ng = tg1 - tg0, jt = tg0 >> Jl;
-            const double yA0 = ckYA[tg0 == 0 ? 0 : (tg0 - 1) / Delta] + rowY[tg0];
-            // the wave's raw rows, requested before the barriers
-            double vr[2];
-            int nr[2];
-            const int nbt = nb[(size_t)jt * C];
+        nbt = nb[(size_t)(tg0 >> Jl) * C];
+        eA0 = p.dtE[row0 + tg0].x;
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int s = min(tg0 + kA + 1 + lane + 64 * u, L);
-                vr[u] = rowV[(size_t)s * C];
-                nr[u] = nb[(size_t)(s >> Jl) * C];
-            }
-            const double iel = EI[(size_t)min(tg0 + (lane & 31), L) * C + c].y;
-            __syncthreads();  // the previous group is done with the staged rows
-            // scale factors of the group's a rows and of the v rows any of its durations reaches; all exponents are
-            // combined before anything is formed, so that an empty row stays zero and nothing passes through infinity
-            for (int i = tid; i < DT_TG + ng + K; i += 64 * DXA_W) {
-                if (i < DT_TG) {
-                    const int tt = tg0 + i;
-                    fA[i] = i < ng ? wb * exp2(ckYA[tt == 0 ? 0 : (tt - 1) / Delta] + rowY[tt] - yA0) : 0.0;
-                } else {
-                    const int r = i - DT_TG, s = min(tg0 + 1 + r, L);
-                    const double yB = s == L ? 0.0 : dt_ytop(p, b, s / Delta, L) + rowYb[s];
-                    const double lf = (yA0 + yB) - lz2;
-                    const double fl = floor(lf);
-                    fV[r] = exp2(lf - fl);
-                    eV[r] = (int)fmin(fmax(fl, -100000.0), 100000.0);
-                }
-            }
-            __syncthreads();
-            for (int i = tid; i < ((ng + 3) & ~3) * 16 * MT; i += 64 * DXA_W) {
-                const int r = i / (16 * MT), o = i % (16 * MT);
-                Arow[r * AS + o] = (r < ng && o < C) ? rowA[(size_t)(tg0 + r) * C + o] * fA[r] : 0.0;
-            }
-            if (lane < DT_TG) IEw[lane] = (mine && lane < ng) ? iel : 0.0;
+        for (int u = 0; u < AE; ++u) {
+            const int i = tid + u * 64 * DXA_W, r = i / (16 * MT), o = i % (16 * MT);
+            const size_t t = row0 + min(tg0 + r, tg1 - 1);
+            ar[u] = p.dtA[t * C + min(o, C - 1)];
+            am[u] = p.dtMA[t];
+            ae[u] = p.dtE[t].x;
+        }
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int r = lane + 64 * u, s = tg0 + kA + 1 + r;
-                double v = 0.0;
-                if (mine && s <= L && r < ng + DXA_K && kA + r < ng + K)
-                    v = fmin(ldexp(vr[u] * fV[kA + r], nr[u] - nbt + eV[kA + r]), DBL_MAX);
-                if (r < DXA_VR) Vw[r] = v;
-            }
-            __syncthreads();
-            for (int i0 = 0; i0 < ng; i0 += 4) {  // positions i0 .. i0+3 (zero rows beyond the group)
-                double A[MT];
+        for (int u = 0; u < 2; ++u) {
+            const int s = min(tg0 + kA + 1 + lane + 64 * u, L);
+            vr[u] = p.dtV[(row0 + s) * C + c];
+            vm[u] = p.dtMB[row0 + s];
+            vs[u] = p.dtE[row0 + s].y + nb[(size_t)(s >> Jl) * C];
+        }
+        ie = p.EI[(row0 + min(tg0 + (lane & 31), L)) * C + c].y;
+    };
+    bool more = advance();
+    if (more) request();
+    while (more) {  // uniform
+        const int ng = tg1 - tg0;
+        __syncthreads();  // the previous group is done with the staged rows
 #pragma unroll
-                for (int m = 0; m < MT; ++m) A[m] = Arow[(i0 + g4) * AS + 16 * m + j];
-                const double ie = IEw[i0 + g4];
-                double bv[4];
+        for (int u = 0; u < AE; ++u) {
+            const int i = tid + u * 64 * DXA_W, r = i / (16 * MT), o = i % (16 * MT);
+            Arow[r * AS + o] = (r < ng && o < C) ? ldexp(ar[u] * wb * am[u], ae[u] - eA0) : 0.0;
+        }
+        if (lane < DT_TG) IEw[lane] = (mine && lane < ng) ? ie : 0.0;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) bv[k] = ie * Vw[i0 + g4 + 16 * k + j];
+        for (int u = 0; u < 2; ++u) {
+            const int r = lane + 64 * u, s = tg0 + kA + 1 + r;
+            double v = 0.0;
+            if (mine && s <= L && r < ng + DXA_K && kA + r < ng + K) v = fmin(ldexp(vr[u] * vm[u], vs[u] + eA0 - nbt), DBL_MAX);
+            if (r < DXA_VR) Vw[r] = v;
+        }
+        __syncthreads();
+        more = advance();
+        if (more) request();
+        for (int i0 = 0; i0 < ng; i0 += 4) {  // positions i0 .. i0+3 (zero rows beyond the group)
+            double A[MT];
 #pragma unroll
-                for (int k = 0; k < 4; ++k)
+            for (int m = 0; m < MT; ++m) A[m] = Arow[(i0 + g4) * AS + 16 * m + j];
+            const double iet = IEw[i0 + g4];
+            double bv[KT];
 #pragma unroll
-                    for (int m = 0; m < MT; ++m) acc[m][k] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[m], bv[k], acc[m][k], 0, 0, 0);
-            }
-            tg0 = tg1;
+            for (int k = 0; k < KT; ++k) bv[k] = iet * Vw[i0 + g4 + 16 * k + j];
+#pragma unroll
+            for (int k = 0; k < KT; ++k)
+#pragma unroll
+                for (int m = 0; m < MT; ++m) acc[m][k] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[m], bv[k], acc[m][k], 0, 0, 0);
         }
     }
     if (!mine) return;
@@ -941,7 +957,7 @@ __global__ __launch_bounds__(64 * DXA_W, 4) void k_dx_acc(Params p)
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int k = 0; k < KT; ++k)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int o = 16 * m + 4 * v + g4, kd = kA + 16 * k + j;

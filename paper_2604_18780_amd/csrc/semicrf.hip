@@ -675,24 +675,24 @@ int dt_scan_interval(int B, int T, int K, int C, int ckpt_interval, const DtGeom
 }
 
 struct DtLayout {
-    size_t g3, gf, gb, gs, dta, dty, dtv, dtd, dtyb, partg, sumg, total;
+    size_t g3, gf, gb, gs, dta, dty, dtv, dtd, dtyb, partg, sumg, ma, mb, eab, total;
     int nwg;
 };
 
-DtLayout dt_layout(int B, int T, int K, int C, int N, int want_grad)
+DtLayout dt_layout(int B, int T, int K, int C, int Delta, int N, int want_grad)
 {
     DtLayout l;
     const DxGeom g = dx_geometry(K, C);
     const size_t kcc = (size_t)K * C * C, t1 = (size_t)T + 1;
     const size_t ntask = (size_t)B * N;
-    // workgroups with partial tables of their own: enough to fill the chip, whole rounds of tasks
-    size_t most = DT_NWG;
+    // workgroups with partial tables of their own: as many as the chip holds at once, with equal shares
+    l.nwg = (int)(ntask < (size_t)DT_NWG ? ntask : (size_t)DT_NWG);
     if (g.ok) {
         const size_t ny = ((size_t)C * ((K + DXA_K - 1) / DXA_K) + DXA_W - 1) / DXA_W;
-        const size_t rounds = (ntask * ny + DXA_WGS - 1) / DXA_WGS;
-        most = (ntask + rounds - 1) / rounds;
+        const size_t most = ny < (size_t)DXA_WGS ? DXA_WGS / ny : 1, items = ntask * dxa_pieces(Delta);
+        const size_t rounds = (items + most - 1) / most;
+        l.nwg = (int)((items + rounds - 1) / rounds);
     }
-    l.nwg = (int)(ntask < most ? ntask : most);
     size_t off = 0;
     l.g3 = off; off += align_up(kcc * 8);
     l.gf = off; off += g.ok ? align_up(g.gf * 8) : 0;
@@ -705,6 +705,10 @@ DtLayout dt_layout(int B, int T, int K, int C, int N, int want_grad)
     l.dtyb = off; off += want_grad ? align_up((size_t)B * t1 * 8) : 0;
     l.partg = off; off += want_grad ? align_up((size_t)l.nwg * kcc * 8) : 0;
     l.sumg = off; off += want_grad ? align_up(kcc * 8) : 0;
+    const size_t nf = want_grad && g.ok ? (size_t)B * t1 : 0;
+    l.ma = off; off += align_up(nf * 8);
+    l.mb = off; off += align_up(nf * 8);
+    l.eab = off; off += align_up(nf * 8);
     l.total = off;
     return l;
 }
@@ -747,13 +751,21 @@ int launch_dx_bwd_any(const Params &p, const DxGeom &g, hipStream_t st, int warm
     }
 }
 
-template <int MT>
-int launch_dx_acc(const Params &p, hipStream_t st)
+template <int MT, int KT>
+void launch_dx_acc_k(const Params &p, hipStream_t st)
 {
-    const size_t lds = dxa_lds_doubles(MT, p.K) * sizeof(double);  // at most 36 KB (K <= 1024)
     const int items = p.C * ((p.K + DXA_K - 1) / DXA_K);
-    hipLaunchKernelGGL((k_dx_acc<MT>), dim3(p.dt_nwg, (items + DXA_W - 1) / DXA_W), dim3(64 * DXA_W), lds, st, p);
-    return SEMICRF_OK;
+    hipLaunchKernelGGL((k_dx_acc<MT, KT>), dim3(p.dt_nwg, (items + DXA_W - 1) / DXA_W), dim3(64 * DXA_W),
+                       dxa_lds_doubles(MT) * sizeof(double), st, p);
+}
+
+template <int MT>
+void launch_dx_acc(const Params &p, hipStream_t st)
+{
+    if (p.K <= 16) launch_dx_acc_k<MT, 1>(p, st);
+    else if (p.K <= 32) launch_dx_acc_k<MT, 2>(p, st);
+    else if (p.K <= 48) launch_dx_acc_k<MT, 3>(p, st);
+    else launch_dx_acc_k<MT, 4>(p, st);
 }
 
 template <int KPTF>
@@ -805,7 +817,7 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
     Plan pl;
     int rc = make_plan(p.B, p.T, p.K, p.C, ckpt_interval, grad ? 2 : 0, &pl);
     if (rc != SEMICRF_OK) return rc;
-    const DtLayout dl = dt_layout(p.B, p.T, p.K, p.C, pl.N, grad ? 1 : 0);
+    const DtLayout dl = dt_layout(p.B, p.T, p.K, p.C, pl.Delta, pl.N, grad ? 1 : 0);
     if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < pl.total + dl.total)
         return SEMICRF_EWORKSPACE;
     p.Delta = pl.Delta;
@@ -827,10 +839,13 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
     p.partG = (double *)(dw + dl.partg);
     p.sumG = (double *)(dw + dl.sumg);
     p.dt_nwg = dl.nwg;
+    const DxGeom dx = dx_geometry(p.K, p.C);
+    p.dtMA = dx.ok ? (double *)(dw + dl.ma) : nullptr;
+    p.dtMB = (double *)(dw + dl.mb);
+    p.dtE = (int2 *)(dw + dl.eab);
     rc = launch_prep(p, st);
     if (rc != SEMICRF_OK) return rc;
     const size_t kcc = (size_t)p.K * p.C * p.C;
-    const DxGeom dx = dx_geometry(p.K, p.C);
     const size_t ntable = kcc + (dx.ok ? dx.gf + dx.gb + dx.gs : 0);
     if (dx.ok)
         hipLaunchKernelGGL(k_dx_tables, dim3((unsigned)((ntable + NT - 1) / NT)), dim3(NT), 0, st, p);
@@ -861,9 +876,8 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
     rc = launch_dt_bwd_any(p, g, st, p.B, 0, 0, 1);
     if (rc != SEMICRF_OK) return rc;
     hipLaunchKernelGGL(k_dx_emis, dim3(p.B * p.N), dim3(NT), 0, st, p);
-    if (dx.ok) rc = dx.mt == 1 ? launch_dx_acc<1>(p, st) : launch_dx_acc<2>(p, st);
+    if (dx.ok) dx.mt == 1 ? launch_dx_acc<1>(p, st) : launch_dx_acc<2>(p, st);
     else hipLaunchKernelGGL((k_dt_acc<16>), dim3(dl.nwg, (p.K + 15) / 16), dim3(g.nta), g.lds_a, st, p);
-    if (rc != SEMICRF_OK) return rc;
     hipLaunchKernelGGL(k_dt_fin, dim3(p.B * FIN_FS + (unsigned)((kcc + DT_FO - 1) / DT_FO)), dim3(NT), 0, st, p);
     hipLaunchKernelGGL(k_dt_fin_dur, dim3((p.K * p.C + NT - 1) / NT), dim3(NT), 0, st, p);
     launch_fin_emis(p, st);
@@ -1157,7 +1171,7 @@ int semicrf_durtrans_workspace_bytes(int B, int T, int K, int C, int ckpt_interv
     Plan pl;
     int rc = make_plan(B, T, K, C, ckpt_interval, want_grad ? 2 : 0, &pl);
     if (rc != SEMICRF_OK) return rc;
-    *bytes = pl.total + dt_layout(B, T, K, C, pl.N, want_grad ? 1 : 0).total;
+    *bytes = pl.total + dt_layout(B, T, K, C, pl.Delta, pl.N, want_grad ? 1 : 0).total;
     return SEMICRF_OK;
 }
 
