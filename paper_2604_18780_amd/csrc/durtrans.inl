@@ -17,7 +17,7 @@
 //   marginal  mu(t -> t+k, c', c) = a_t(c') G[k][c'][c] IE_t(c) v_{t+k}(c) / Z
 //
 // Both recurrences run chunk-parallel with warm-up and are verified and chained by the same
-// k_spec_cmp / k_spec_fix as the factorised scans (the checkpoint format is theirs: K*C ring
+// k_spec_cmp as the factorised scans (the checkpoint format is theirs: K*C ring
 // entries in slot order, then the C-vector whose sum is the scale reference); what is rejected
 // is rescanned by the same kernels in whole-sequence mode.
 //

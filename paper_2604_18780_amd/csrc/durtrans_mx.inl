@@ -171,6 +171,9 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tie
     const bool chain = wave < 4;
     const int c = R::label(lane), gr = R::group(lane);
     const bool cv = c < C, owner = cv && gr == 0;
+    bool any = false;  // nothing to do for any of the four tasks: the whole workgroup leaves
+    for (int i = 0; i < DX_TASKS; ++i) any = any || dx_task(p, blockIdx.x * DX_TASKS + i, 0, tier).active;
+    if (!any) return;
     const DxTask tk = dx_task(p, blockIdx.x * DX_TASKS + q, 0, tier);
     const int L = tk.L, J = tk.J, lo = tk.lo, hi = tk.hi;
     const int s0 = max(lo - warm, 0);
@@ -433,6 +436,9 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
     const int c = R::label(lane), gr = R::group(lane);
     const bool cv = c < C, owner = cv && gr == 0;
     const int cc0 = cv ? c : 0;
+    bool any = false;  // nothing to do for any of the four tasks: the whole workgroup leaves
+    for (int i = 0; i < DX_TASKS; ++i) any = any || dx_task(p, blockIdx.x * DX_TASKS + i, 1, tier).active;
+    if (!any) return;
     const DxTask tk = dx_task(p, blockIdx.x * DX_TASKS + q, 1, tier);
     const int L = tk.L, J = tk.J, lo = tk.lo, hi = tk.hi;
     const int s1 = min(hi + warm, L);

@@ -112,7 +112,7 @@ __global__ __launch_bounds__(NT) void k_scan(Params p, int both)
     const int tid = threadIdx.x;
     const int b = both ? (int)(blockIdx.x >> 1) : (int)blockIdx.x;
     const int dir = both ? (int)(blockIdx.x & 1) : 0;
-    if (p.spec && p.spec_ok[b * 2 + dir]) return;  // the chunk-parallel scan was accepted
+    if (spec_settled(p, b, dir, both ? 2 : 1, SPEC_ATTEMPTS - 1)) return;  // the chunk-parallel scan was accepted
     const int K = p.K, C = p.C, KC = K * C, CP1 = C | 1;
     const int G = min(NT / C, K);
     const Lds l = carve(lds_raw, K, C, G, false);
@@ -601,7 +601,7 @@ __global__ __launch_bounds__(CT == 64 ? 64 * (NHR + 1) : 320) void k_scan_fast(P
     extern __shared__ double lds_raw[];
     const int b = both ? (int)(blockIdx.x >> 1) : (int)blockIdx.x;
     const int dir = both ? (int)(blockIdx.x & 1) : 0;
-    if (p.spec && p.spec_ok[b * 2 + dir]) return;  // the chunk-parallel scan was accepted
+    if (spec_settled(p, b, dir, both ? 2 : 1, SPEC_ATTEMPTS - 1)) return;  // the chunk-parallel scan was accepted
     if (dir == 0) scan_fast_body<CT, NHR, false>(p, lds_raw, b);
     else scan_fast_body<CT, NHR, true>(p, lds_raw, b);
 }

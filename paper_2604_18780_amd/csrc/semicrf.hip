@@ -26,7 +26,7 @@
 // log(sum_c a_L(c)).
 //
 // Kernels (each group in its own include file, see below): k_colsum (+ the exp tables), k_prep_seq,
-// k_prefix (Eq. 1-2); k_spec, k_spec_repair, k_spec_cmp, k_spec_fix (Algorithm 1 and the beta
+// k_prefix (Eq. 1-2); k_spec, k_spec2, k_spec_cmp (Algorithm 1 and the beta
 // recurrence of Algorithm 3 as chunk-parallel scans that are verified at every chunk boundary and
 // write ring checkpoints every Delta positions; k_mscan in mscan.hip runs the same tasks sixteen at
 // a time on the matrix cores); k_scan_fast / k_scan (the same scans sequentially, for what the
@@ -60,6 +60,7 @@ using namespace semicrf_impl;
 
 // The kernels, stage by stage (each file is included here, inside this namespace):
 #include "prefix.inl"     // Eq. 1-2: baseline, centred prefix sums, block exponents, (ES, 1/ES)
+#include "verify.inl"     // verification of the chunk-parallel scans
 #include "scan_seq.inl"   // sequential scans (fallback of the chunk-parallel ones)
 #include "interval.inl"   // Algorithm 3 body: per-interval recompute + marginals; one-wave window geometry
 #include "spec.inl"       // chunk-parallel scans with warm-up, repair and verification
@@ -246,41 +247,48 @@ int launch_interval(const Params &p, const Plan &pl, hipStream_t st)
 }
 
 // Chunk-parallel scan: returns 1 when it does not apply to these sizes.
+// two: the form with two waves per task.
+template <int CT, int NKW, bool RETRY>
+int launch_spec_tasks(const Params &p, hipStream_t st, bool both, int warm, int tier, int rest, bool two)
+{
+    const int ndir = both ? 2 : 1;
+    if (two) {
+        const size_t lds = spec2_lds_doubles<CT, NKW>() * sizeof(double);
+        if (hipFuncSetAttribute((const void *)k_spec2<CT, NKW, RETRY>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds) != hipSuccess)
+            return SEMICRF_ELAUNCH;
+        hipLaunchKernelGGL((k_spec2<CT, NKW, RETRY>), dim3(p.B * p.N * ndir), dim3(128), lds, st, p, both ? 1 : 0,
+                           warm, tier, rest);
+        return SEMICRF_OK;
+    }
+    constexpr int SW = spec_waves(CT, NKW);
+    const size_t lds = SW * scan_lds_doubles(CT, NKW) * sizeof(double);
+    if (hipFuncSetAttribute((const void *)k_spec<CT, NKW, RETRY>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds) != hipSuccess)
+        return SEMICRF_ELAUNCH;
+    hipLaunchKernelGGL((k_spec<CT, NKW, RETRY>), dim3((p.B * p.N + SW - 1) / SW * ndir), dim3(64 * SW), lds, st, p,
+                       both ? 1 : 0, warm, tier, rest);
+    return SEMICRF_OK;
+}
+
 template <int CT, int NKW>
 int launch_spec_k(const Params &p, hipStream_t st, bool both, int warm, int tier)
 {
-    const size_t lds = scan_lds_doubles(CT, NKW) * sizeof(double);
-    constexpr int SW = spec_waves(CT, NKW);
-    if (lds > LDS_LIMIT) return 1;
-    if (hipFuncSetAttribute((const void *)k_spec<CT, NKW>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)(SW * lds)) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_spec_repair<CT, NKW>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds) != hipSuccess)
-        return SEMICRF_ELAUNCH;
-    const int ndir = both ? 2 : 1;
-    int rest = 0;
-    if (warm > 0 && p.mscan && mscan_applies(p.K, p.C, p.Delta) && (double)p.B * ((double)p.T + 1.0) * (double)p.C < 134217728.0) {
-        const int rc = launch_mscan(p, st, both, warm, tier);
+    if (scan_lds_doubles(CT, NKW) * sizeof(double) > LDS_LIMIT) return 1;
+    int rest = 0, rc;
+    if (tier == 0 && p.mscan && mscan_applies(p.K, p.C, p.Delta) && (double)p.B * ((double)p.T + 1.0) * (double)p.C < 134217728.0) {
+        rc = launch_mscan(p, st, both, warm, tier);
         if (rc != SEMICRF_OK) return rc;
         rest = 1;
     }
-    const size_t lds2 = spec2_lds_doubles<CT, NKW>() * sizeof(double);
     // two waves per task where the window or the transition product is long next to a position's dependent chain
     // (measured: longgen scans 1.27 -> 0.85 ms, speech 0.30 -> 0.25 ms; genomic 0.37 -> 0.41 ms, so not there)
-    const bool two = p.spec2 == 1 || (p.spec2 == 0 && (NKW == 64 || CT == 64));
-    if (warm > 0 && two && lds2 <= LDS_LIMIT) {
-        if (hipFuncSetAttribute((const void *)k_spec2<CT, NKW>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds2) != hipSuccess)
-            return SEMICRF_ELAUNCH;
-        hipLaunchKernelGGL((k_spec2<CT, NKW>), dim3(p.B * p.N * ndir), dim3(128), lds2, st, p, both ? 1 : 0,
-                           warm, tier, rest);
-    } else if (warm > 0)
-        hipLaunchKernelGGL((k_spec<CT, NKW>), dim3((p.B * p.N + SW - 1) / SW * ndir), dim3(64 * SW), SW * lds, st, p,
-                           both ? 1 : 0, warm, tier, rest);
-    else
-        hipLaunchKernelGGL((k_spec_repair<CT, NKW>), dim3(p.B * p.N * ndir), dim3(64), lds, st, p, both ? 1 : 0);
-    hipLaunchKernelGGL(k_spec_cmp, dim3(p.N, p.B, ndir), dim3(NT), 0, st, p, tier);
-    hipLaunchKernelGGL(k_spec_fix, dim3(p.B, 2), dim3(64), 0, st, p, ndir, tier, tier == 0 ? 1 : (warm == 0 ? 2 : 3));
+    const bool two = (p.spec2 == 1 || (p.spec2 == 0 && (NKW == 64 || CT == 64))) &&
+                     spec2_lds_doubles<CT, NKW>() * sizeof(double) <= LDS_LIMIT;
+    if (tier == 0) rc = launch_spec_tasks<CT, NKW, false>(p, st, both, warm, tier, rest, two);
+    else rc = launch_spec_tasks<CT, NKW, true>(p, st, both, warm, tier, rest, two);
+    if (rc != SEMICRF_OK) return rc;
+    hipLaunchKernelGGL(k_spec_cmp, dim3(p.N, p.B, both ? 2 : 1), dim3(NT), 0, st, p, tier);
     return check_launch();
 }
 
@@ -375,6 +383,7 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
     // eight for the (sequence, direction) pairs that fails for, the sequential scan for the rest
     int warm[2] = {sum_warmup(p.K), 8 * p.K < 64 ? 64 : 8 * p.K};
     if (p.warm0 > 0) warm[0] = p.warm0, warm[1] = 4 * p.warm0;  // the caller's first warm-up length (flags bits 16..31)
+    p.warm_long = warm[1];
     p.spec = p.spec && mode != 0 && spec_applies(p.K, p.C);
     p.mscan = p.mscan && p.spec;
     p.fuse = p.spec && mode == 2 && (size_t)p.B * pl.N <= (size_t)pl.nslot;  // one slot per task
@@ -394,11 +403,11 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
     T.mark();
     if (rc != SEMICRF_OK || mode == 0) return rc;
     if (p.spec) {
-        // Every interval after a short warm-up; then, for what did not verify, the intervals whose start disagreed
-        // restart from the state their neighbour reached (warm-up 0 selects that); then everything that is still
-        // open once more after a long warm-up.  The sequential scan takes the rest.
-        const int attempt[3] = {warm[0], 0, warm[1]};
-        for (int tier = 0; tier < 3; ++tier) {
+        // Every interval after a short warm-up; then, for what did not verify, mending of isolated boundaries or a
+        // warm-up as long as the mismatch asks for; then the same once more with the longest warm-up.  The sequential
+        // scan takes the rest.
+        const int attempt[SPEC_ATTEMPTS] = {warm[0], warm[0], warm[1]};
+        for (int tier = 0; tier < SPEC_ATTEMPTS; ++tier) {
             rc = launch_spec(p, st, mode == 2, attempt[tier], tier);
             if (rc != SEMICRF_OK) return rc;
         }
@@ -854,6 +863,7 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
     const int ndir = grad ? 2 : 1;
     if (p.spec) {
         const int warm[2] = {sum_warmup(p.K), 8 * p.K < 64 ? 64 : 8 * p.K};
+        p.warm_long = warm[1];
         for (int tier = 0; tier < 2; ++tier) {
             rc = dx.ok ? launch_dx_fwd_any(p, dx, st, warm[tier], tier)
                        : launch_dt_fwd_any(p, g, st, p.B * p.N, warm[tier], tier, 0);
@@ -864,7 +874,7 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
                 if (rc != SEMICRF_OK) return rc;
             }
             hipLaunchKernelGGL(k_spec_cmp, dim3(p.N, p.B, ndir), dim3(NT), 0, st, p, tier);
-            hipLaunchKernelGGL(k_spec_fix, dim3(p.B, 2), dim3(64), 0, st, p, ndir, tier, tier == 0 ? 1 : 3);
+            hipLaunchKernelGGL(k_spec_fix, dim3(p.B, ndir), dim3(64), 0, st, p, ndir, tier);
         }
     } else {
         hipLaunchKernelGGL(k_spec_clear, dim3((2 * p.B + 63) / 64), dim3(64), 0, st, p);

@@ -16,21 +16,66 @@
 // from, entry by entry, after removing their common scale factor.  If all boundaries of
 // a (sequence, direction) agree to SPEC_TOL the warm-up states ARE the sequential
 // states to that relative accuracy (perturbations of the start do not grow: the maps
-// are non-expansive in the projective metric); k_spec_fix then chains the scale
+// are non-expansive in the projective metric); spec_fix then chains the scale
 // factors into the checkpoint scales and logZ.  Otherwise the flag stays 0 and the
 // sequential scan kernel, which is launched afterwards and returns at once for
 // accepted (sequence, direction) pairs, recomputes that pair from scratch.
 // One wave per task, no barriers, same register/LDS organisation as k_interval_wave.
 // ---------------------------------------------------------------------------
-constexpr double SPEC_TOL = 1e-10;
 constexpr int SPEC_RUN_MAX = 2;  // intervals one wave mends in a row in the repair attempt
+
+// What an attempt does for one (sequence, direction) pair.
+//   tier 0: every task after `warm` positions of warm-up.
+//   tier 1, 2 (pairs that are still open): where a few isolated boundaries disagreed, mending: it is sequential work,
+//   one task per run of disagreeing boundaries, and pays for a stretch of uninformative input, not for a model that
+//   forgets slowly everywhere.  Otherwise every task again after a longer warm-up: at tier 1 what the mismatch of the
+//   attempt before asks for, at tier 2 the longest.
+// Whether the attempt before was accepted is worked out here, by every wave for its own pair (spec_verdict reads a few
+// hundred numbers): the first task of an accepted pair also settles it.  A launch in between for the verdicts alone would
+// cost every call as much as a comparison.
+struct SpecJob {
+    bool idle, mend;
+    int warm, nint;
+    const double *err;
+};
+__device__ __forceinline__ SpecJob spec_job(const Params &p, const int b, const int dir, const int j, const int ndir,
+                                            const int warm, const int tier)
+{
+    SpecJob s;
+    s.idle = s.mend = false;
+    s.warm = warm;
+    s.nint = 0;
+    s.err = p.spec_err + ((size_t)b * 2 + dir) * (p.N + 1);
+    if (tier == 0) return s;
+    const int lane = threadIdx.x & 63;
+    if (tier > 1 && p.spec_ok[b * 2 + dir]) {
+        s.idle = true;
+        return s;
+    }
+    const SpecVerdict v = spec_verdict(p, b, dir, lane);
+    if (j == 0 && (blockDim.x != 128 || threadIdx.x < 64)) spec_settle(p, b, dir, ndir, tier - 1, v, lane);
+    s.idle = v.ok;
+    s.nint = v.nint;
+    s.mend = v.nbad <= max(2, v.nint / 16);
+    if (tier == 1) {
+        // The mismatch falls geometrically with the warm-up, so the length that brings the worst boundary to 1e-12
+        // follows from the one just measured; a quarter and half a segment length on top for stretches that forget
+        // more slowly.  Hopeless cases take the longest.
+        double w = (double)p.warm_long;
+        if (v.worst > 0.0 && v.worst < 0.1) w = fmin(w, 1.25 * (double)warm * (-27.7 / log(v.worst)) + 0.5 * (double)p.K);
+        s.warm = ((int)w + 3) & ~3;
+    }
+    return s;
+}
+// Boundary m disagreed in the attempt before.
+__device__ __forceinline__ bool spec_bad(const SpecJob &s, const int m) { return m >= 1 && m <= s.nint - 1 && !(s.err[m] <= SPEC_TOL); }
 
 // One scan task of the chunk-parallel scan, one wave (window and time blocking as above).
 // repair: the task restarts from the state its neighbour in scan order REACHED at their common boundary (no
-// warm-up: exact if the neighbour's own start was); k_spec decides which tasks do that.
-template <int CT, int NKW, bool BWD, bool repair>
+// warm-up: exact if the neighbour's own start was).
+template <int CT, int NKW, bool BWD>
 __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, const int b, const int j,
-                                          const int warm)
+                                          const int warm, const bool repair)
 {
     using G = WaveWin<CT, NKW, 1>;
     using R = RowMap<CT>;
@@ -281,7 +326,9 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
 // 227 or 264 us depending on the shape of the kernel before).  The directions fill one half of the grid each, so that
 // a SIMD with two tasks has one of each.
 // rest: only the sequences the lock-step kernel (k_mscan, launched before) leaves out
-template <int CT, int NKW>
+// RETRY: the later attempts; a kernel of its own, so that the first attempt is not compiled around their cases
+// (one kernel for both: 304 -> 338 us at the genomic shape).
+template <int CT, int NKW, bool RETRY>
 __global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, NKW)) void k_spec(Params p, int both, int warm, int tier, int rest)
 {
     constexpr int SW = spec_waves(CT, NKW);
@@ -292,173 +339,34 @@ __global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, N
     const int task = ((int)blockIdx.x - dir * per) * SW + wave;
     const int b = task / p.N, j = task % p.N;
     if (b >= p.B) return;
-    if (tier > 0 && p.spec_ok[b * 2 + dir]) return;  // accepted by an earlier attempt
-    if (rest && p.hdr[b].J >= MS_JMIN) return;
     double *lds = lds_raw + (size_t)wave * scan_lds_doubles(CT, NKW);
-    if (dir == 0) spec_task<CT, NKW, false, false>(p, lds, b, j, warm);
-    else spec_task<CT, NKW, true, false>(p, lds, b, j, warm);
-}
-
-// The repair attempt of the chunk-parallel scans, for the (sequence, direction) pairs that are still open.
-template <int CT, int NKW>
-__global__ __launch_bounds__(64) void k_spec_repair(Params p, int both)
-{
-    extern __shared__ double lds_raw[];
-    const int ndir = both ? 2 : 1;
-    const int dir = blockIdx.x % ndir;
-    const int task = blockIdx.x / ndir;
-    const int b = task / p.N, j = task % p.N;
-    if (p.spec_ok[b * 2 + dir]) return;
+    SpecJob job = {};
+    if (RETRY) {
+        job = spec_job(p, b, dir, j, both ? 2 : 1, warm, tier);
+        if (job.idle) return;  // accepted by an earlier attempt
+    } else if (rest && p.hdr[b].J >= MS_JMIN) {
+        return;
+    }
+    if (!RETRY || !job.mend) {
+        if (dir == 0) spec_task<CT, NKW, false>(p, lds, b, j, RETRY ? job.warm : warm, false);
+        else spec_task<CT, NKW, true>(p, lds, b, j, RETRY ? job.warm : warm, false);
+        return;
+    }
     // A run of adjacent boundaries that disagreed is taken by ONE wave, the task that starts at the first of them
     // in scan order (its neighbour started from a verified or exact state, so what that neighbour reached is
     // right): it restarts from the reached state and goes on through the run's intervals one after the other,
     // at most SPEC_RUN_MAX of them; a longer run stays open for the next attempt.  Every other task returns at
     // once and keeps what it has.  Nothing in this kernel writes spec_err.
-    const int L = p.hdr[b].L;
-    const int nint = (L + p.Delta - 1) / p.Delta;
-    const double *err = p.spec_err + ((size_t)b * 2 + dir) * (p.N + 1);
-    // Mending is sequential work, one wave per run: it pays for a few isolated disagreements (a stretch of
-    // uninformative input), not for a model that forgets slowly everywhere; that goes to the long warm-up.
-    if (p.spec_lr[((size_t)b * 2 + dir) * (p.N + 1)] > (double)max(2, nint / 16)) return;
-    auto bad = [&](const int m) { return m >= 1 && m <= nint - 1 && !(err[m] <= SPEC_TOL); };
-    if (!bad(dir ? j + 1 : j) || bad(dir ? j + 2 : j - 1)) return;
+    if (!spec_bad(job, dir ? j + 1 : j) || spec_bad(job, dir ? j + 2 : j - 1)) return;
     int jj = j;
     for (int n = 0; n < SPEC_RUN_MAX; ++n) {
-        if (dir == 0) spec_task<CT, NKW, false, true>(p, lds_raw, b, jj, 0);
-        else spec_task<CT, NKW, true, true>(p, lds_raw, b, jj, 0);
+        if (dir == 0) spec_task<CT, NKW, false>(p, lds, b, jj, 0, true);
+        else spec_task<CT, NKW, true>(p, lds, b, jj, 0, true);
         const int nx = dir ? jj - 1 : jj + 1;              // the next task in scan order ...
-        if (nx < 0 || nx >= nint || !bad(dir ? nx + 1 : nx)) break;  // ... starts where this one ended
+        if (nx < 0 || nx >= job.nint || !spec_bad(job, dir ? nx + 1 : nx)) break;  // ... starts where this one ended
         __threadfence();  // the reached state this wave has just written is what it restarts from
         jj = nx;
     }
-}
-
-// One workgroup per (chunk boundary j, sequence, direction): compare the state chunk j-1
-// (forward) / chunk j (backward) reached at position j*Delta with the warm-up state the
-// neighbouring chunk started from.
-__global__ __launch_bounds__(NT) void k_spec_cmp(Params p, int tier)
-{
-    __shared__ double part[NT / 64];
-    const int j = blockIdx.x, b = blockIdx.y, dir = blockIdx.z, tid = threadIdx.x;
-    const int lane = tid & 63, wv = tid >> 6;
-    if (tier > 0 && p.spec_ok[b * 2 + dir]) return;
-    const int L = p.hdr[b].L;
-    const int nint = (L + p.Delta - 1) / p.Delta;
-    if (j < 1 || j >= nint) return;
-    const int KC = p.K * p.C, C = p.C, N = p.N;
-    const size_t ckstride = (size_t)KC + C;
-    const double *A = (dir ? p.ckB : p.ckA) + ((size_t)b * (N + 1) + j) * ckstride;    // warm-up state
-    const double *A2 = (dir ? p.ckB2 : p.ckA2) + ((size_t)b * (N + 1) + j) * ckstride;  // reached state
-    const double Y = (dir ? p.ckYB : p.ckYA)[(size_t)b * (N + 1) + j];
-    const double Y2 = (dir ? p.ckYB2 : p.ckYA2)[(size_t)b * (N + 1) + j];
-    // sums of the two message vectors (their ratio is the common scale factor); C <= 64 here:
-    // every wave forms them, in lane order
-    double s1 = lane < C ? A[KC + lane] : 0.0, s2 = lane < C ? A2[KC + lane] : 0.0;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        s1 += __shfl_xor(s1, off);
-        s2 += __shfl_xor(s2, off);
-    }
-    const double f = s2 / s1;  // reached = f * 2^(Y2-Y) * warm-up, entry by entry, if they agree
-    double err = 0.0;
-    if (!(s1 > 0.0) || !(s2 > 0.0) || !(f > 0.0) || !(f < DBL_MAX)) err = DBL_MAX;
-#pragma unroll 8
-    for (int i = tid; i < KC + C; i += NT) {
-        const double x = A2[i], y = A[i] * f;
-        const double m = fmax(fabs(x), fabs(y));
-        if (m > 1e-290) err = fmax(err, fabs(x - y) / m);
-        if (!(m < DBL_MAX)) err = DBL_MAX;
-    }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) err = fmax(err, __shfl_xor(err, off));
-    if (lane == 0) part[wv] = err;
-    __syncthreads();
-    if (tid == 0) {
-        for (int i = 1; i < NT / 64; ++i) err = fmax(err, part[i]);
-        const size_t o = ((size_t)b * 2 + dir) * (N + 1) + j;
-        p.spec_err[o] = err;
-        p.spec_lr[o] = (Y2 - Y) + log2(f);
-    }
-}
-
-// Accept or reject each (sequence, direction); chain the scale factors.  grid (B, 2), one
-// wave: lane l owns a contiguous run of boundaries in scan order, the running log2 factor
-// is a fixed-order prefix sum (per lane, then across lanes).
-__global__ __launch_bounds__(64) void k_spec_fix(Params p, int ndir, int tier, int code)
-{
-    const int b = blockIdx.x, dir = blockIdx.y, lane = threadIdx.x;
-    if (tier > 0 && p.spec_ok[b * 2 + dir]) return;
-    const int L = p.hdr[b].L, N = p.N, C = p.C, KC = p.K * C;
-    const int nint = (L + p.Delta - 1) / p.Delta;
-    const size_t so = ((size_t)b * 2 + dir) * (N + 1);
-    if (dir >= ndir) {  // direction not run in this call
-        if (lane == 0) {
-            p.spec_ok[b * 2 + dir] = 0;
-            p.spec_rep[b * 2 + dir] = -1.0;
-        }
-        return;
-    }
-    const int nb = nint > 1 ? nint - 1 : 0;  // boundaries 1 .. nint-1
-    const int per = (nb + 63) / 64;
-    const int i0 = min(lane * per, nb), i1 = min(i0 + per, nb);
-    // i-th boundary in scan order: ascending for the forward scan, descending for the backward one
-    auto jof = [&](int i) { return dir == 0 ? 1 + i : nint - 1 - i; };
-    double s = 0.0, worst = 0.0;
-    int nbad = 0;  // boundaries that disagreed
-    for (int i = i0; i < i1; ++i) {
-        s += p.spec_lr[so + jof(i)];
-        const double e = p.spec_err[so + jof(i)];
-        worst = fmax(worst, e);
-        nbad += !(e <= SPEC_TOL);
-    }
-    double inc = s;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const double v = __shfl_up(inc, off);
-        if (lane >= off) inc += v;
-    }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        worst = fmax(worst, __shfl_xor(worst, off));
-        nbad += __shfl_xor(nbad, off);
-    }
-    const double total = __shfl(inc, 63);
-    // accepted or not (the same in every lane): every boundary within the bound, and a finite logZ
-    bool ok = worst <= SPEC_TOL;
-    double lz = 0.0, sumL = 1.0, vL = 0.0;
-    if (dir == 0) {
-        if (nint == 0) {
-            lz = log((double)C);
-        } else {
-            // a_L(c) / Z: mass of the segments that end at L with label c
-            const double *e = p.ckA2 + ((size_t)b * (N + 1) + nint) * ((size_t)KC + C);
-            vL = lane < C ? e[KC + lane] : 0.0;
-            sumL = vL;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) sumL += __shfl_xor(sumL, off);
-            lz = (p.ckYA2[(size_t)b * (N + 1) + nint] + total) * LN2 + log(sumL);
-            ok = ok && sumL > 0.0 && lz == lz;
-        }
-    }
-    if (ok) {
-        // Chain the scale factors into the checkpoint scales.  Only on acceptance: a later attempt that rewrites
-        // some of the checkpoints must find the others as their tasks left them.
-        double *ckY = (dir ? p.ckYB : p.ckYA) + (size_t)b * (N + 1);
-        double acc = inc - s;  // log2 of the factor between the true state and the warm-up state
-        for (int i = i0; i < i1; ++i) {
-            acc += p.spec_lr[so + jof(i)];
-            ckY[jof(i)] += acc;
-        }
-        if (dir == 0 && nint > 0 && lane < C) p.inL[(size_t)b * C + lane] = vL / sumL;
-    }
-    if (lane != 0) return;
-    p.spec_rep[b * 2 + dir] = worst;
-    p.spec_lr[so] = (double)nbad;  // entry 0 is no boundary: it carries the number of boundaries that disagreed (read by the repair attempt)
-    if (dir == 0 && ok) {
-        p.hdr[b].logZ = lz;
-        p.logz[b] = (float)lz;
-    }
-    p.spec_ok[b * 2 + dir] = ok ? code : 0;  // which attempt verified it (1 first, 2 after repairs, 3 long warm-up)
 }
 
 // The chunk-parallel scan was not attempted: say so in the report fields.

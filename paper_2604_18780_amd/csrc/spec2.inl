@@ -31,7 +31,7 @@ __host__ __device__ constexpr size_t spec2_lds_doubles()
 
 template <int CT, int NKW, bool BWD>
 __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, const int b, const int j,
-                                           const int warm)
+                                           const int warm, const bool repair)
 {
     using G = WaveWin<CT, NKW, 2>;
     using R = RowMap<CT>;
@@ -57,7 +57,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
     const int hi = min(lo + Delta, L);
     const size_t row0 = (size_t)b * (p.T + 1);
     const int *nbc = p.nbase + row0 * C + cc;
-    const int s0 = BWD ? min(hi + warm, L) : max(lo - warm, 0);
+    const int s0 = repair ? (BWD ? hi : lo) : (BWD ? min(hi + warm, L) : max(lo - warm, 0));
     const int tstart = BWD ? hi : lo;   // where the chunk proper begins (state -> ck1)
     const int tend = BWD ? lo : hi;
 
@@ -84,6 +84,15 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
     for (int i = threadIdx.x; i < 2 * MB * CTP; i += 128) farb[i] = 0.0;
     lds_barrier();
     int r = BWD ? M : KW - 1;  // row of the newest message
+    const int bs = BWD ? j + 1 : j;  // repair: the reached state at this boundary is the start (window by both waves)
+    const double *reached = (BWD ? p.ckB2 : p.ckA2) + ((size_t)b * (N + 1) + bs) * ((size_t)KC + C);
+    if (repair) {
+        const int tm = s0 % K;
+        for (int i = threadIdx.x; i < KC; i += 128) {
+            const int sl = i / C, d = G::template slot_dist<BWD>(sl, tm, K);
+            ring[(BWD ? r + d : r - d) * RS + (i - sl * C)] = reached[i];
+        }
+    }
     int t = s0;
     int jnx = BWD ? s0 / J : s0 / J + 1;
     int dnx = nbdelta(jnx);
@@ -104,7 +113,10 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
         }
         double ylast = 0.0;      // newest message vector, entry c (the same in every group; 0 beyond C)
         double Y = 0.0;
-        {
+        if (repair) {
+            if (cval) ylast = reached[KC + c];
+            Y = ((BWD ? p.ckYB2 : p.ckYA2) + (size_t)b * (N + 1))[bs];
+        } else {
             double q;
             if (!BWD) {
                 double z = 0.0;
@@ -298,7 +310,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
     }
 }
 
-template <int CT, int NKW>
+template <int CT, int NKW, bool RETRY>
 __global__ __launch_bounds__(128, spec2_waves_per_simd(CT, NKW)) void k_spec2(Params p, int both, int warm, int tier, int rest)
 {
     extern __shared__ double lds_raw[];
@@ -306,8 +318,27 @@ __global__ __launch_bounds__(128, spec2_waves_per_simd(CT, NKW)) void k_spec2(Pa
     const int dir = blockIdx.x % ndir;
     const int task = blockIdx.x / ndir;
     const int b = task / p.N, j = task % p.N;
-    if (tier > 0 && p.spec_ok[b * 2 + dir]) return;  // accepted by an earlier attempt
-    if (rest && p.hdr[b].J >= MS_JMIN) return;
-    if (dir == 0) spec2_task<CT, NKW, false>(p, lds_raw, b, j, warm);
-    else spec2_task<CT, NKW, true>(p, lds_raw, b, j, warm);
+    SpecJob job = {};
+    if (RETRY) {
+        job = spec_job(p, b, dir, j, ndir, warm, tier);
+        if (job.idle) return;  // accepted by an earlier attempt
+    } else if (rest && p.hdr[b].J >= MS_JMIN) {
+        return;
+    }
+    if (!RETRY || !job.mend) {
+        if (dir == 0) spec2_task<CT, NKW, false>(p, lds_raw, b, j, RETRY ? job.warm : warm, false);
+        else spec2_task<CT, NKW, true>(p, lds_raw, b, j, RETRY ? job.warm : warm, false);
+        return;
+    }
+    if (!spec_bad(job, dir ? j + 1 : j) || spec_bad(job, dir ? j + 2 : j - 1)) return;
+    int jj = j;
+    for (int n = 0; n < SPEC_RUN_MAX; ++n) {  // a run of boundaries is mended as in k_spec
+        if (dir == 0) spec2_task<CT, NKW, false>(p, lds_raw, b, jj, 0, true);
+        else spec2_task<CT, NKW, true>(p, lds_raw, b, jj, 0, true);
+        const int nx = dir ? jj - 1 : jj + 1;
+        if (nx < 0 || nx >= job.nint || !spec_bad(job, dir ? nx + 1 : nx)) break;
+        __threadfence();
+        __syncthreads();
+        jj = nx;
+    }
 }

@@ -1,0 +1,180 @@
+// Verification of the chunk-parallel scans: comparison of the states at the interval boundaries, the verdict over a
+// (sequence, direction), and what an accepted one leaves for the later kernels.
+// Included by semicrf.hip inside its anonymous namespace (after common.h); not a translation unit of its own.
+
+constexpr double SPEC_TOL = 1e-10;
+constexpr int SPEC_ATTEMPTS = 3;
+
+// One workgroup per (chunk boundary j, sequence, direction): compare the state chunk j-1
+// (forward) / chunk j (backward) reached at position j*Delta with the warm-up state the
+// neighbouring chunk started from.  Number 0 is no boundary: its workgroup checks that the forward scan's final
+// message vector can be summed (entry nint of the mismatches).
+__global__ __launch_bounds__(NT) void k_spec_cmp(Params p, int tier)
+{
+    __shared__ double part[NT / 64];
+    const int j = blockIdx.x, b = blockIdx.y, dir = blockIdx.z, tid = threadIdx.x;
+    const int lane = tid & 63, wv = tid >> 6;
+    if (tier > 0 && p.spec_ok[b * 2 + dir]) return;
+    const int L = p.hdr[b].L;
+    const int nint = (L + p.Delta - 1) / p.Delta;
+    if (j >= nint) return;
+    const int KC = p.K * p.C, C = p.C, N = p.N;
+    const size_t ckstride = (size_t)KC + C;
+    const size_t so = ((size_t)b * 2 + dir) * (N + 1);
+    if (j == 0) {
+        if (dir == 0 && wv == 0) {
+            const double *e = p.ckA2 + ((size_t)b * (N + 1) + nint) * ckstride;
+            double s = lane < C ? e[KC + lane] : 0.0;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) s += __shfl_xor(s, off);
+            const double Y = p.ckYA2[(size_t)b * (N + 1) + nint];
+            if (lane == 0) p.spec_err[so + nint] = (s > 0.0 && s < DBL_MAX && Y == Y) ? 0.0 : DBL_MAX;
+        }
+        return;
+    }
+    const double *A = (dir ? p.ckB : p.ckA) + ((size_t)b * (N + 1) + j) * ckstride;    // warm-up state
+    const double *A2 = (dir ? p.ckB2 : p.ckA2) + ((size_t)b * (N + 1) + j) * ckstride;  // reached state
+    const double Y = (dir ? p.ckYB : p.ckYA)[(size_t)b * (N + 1) + j];
+    const double Y2 = (dir ? p.ckYB2 : p.ckYA2)[(size_t)b * (N + 1) + j];
+    // sums of the two message vectors (their ratio is the common scale factor); C <= 64 here:
+    // every wave forms them, in lane order
+    double s1 = lane < C ? A[KC + lane] : 0.0, s2 = lane < C ? A2[KC + lane] : 0.0;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        s1 += __shfl_xor(s1, off);
+        s2 += __shfl_xor(s2, off);
+    }
+    const double f = s2 / s1;  // reached = f * 2^(Y2-Y) * warm-up, entry by entry, if they agree
+    double err = 0.0;
+    if (!(s1 > 0.0) || !(s2 > 0.0) || !(f > 0.0) || !(f < DBL_MAX)) err = DBL_MAX;
+#pragma unroll 8
+    for (int i = tid; i < KC + C; i += NT) {
+        const double x = A2[i], y = A[i] * f;
+        const double m = fmax(fabs(x), fabs(y));
+        if (m > 1e-290) err = fmax(err, fabs(x - y) / m);
+        if (!(m < DBL_MAX)) err = DBL_MAX;
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) err = fmax(err, __shfl_xor(err, off));
+    if (lane == 0) part[wv] = err;
+    __syncthreads();
+    if (tid == 0) {
+        for (int i = 1; i < NT / 64; ++i) err = fmax(err, part[i]);
+        p.spec_err[so + j] = err;
+        p.spec_lr[so + j] = (Y2 - Y) + log2(f);
+    }
+}
+
+// Verdict over the boundaries of a (sequence, direction), worked out by one wave, the same in every lane: accepted if
+// every boundary is within the bound (and the forward scan's final vector is sound).
+struct SpecVerdict {
+    bool ok;
+    int nint, nbad;  // intervals; boundaries that disagreed
+    double worst;
+};
+__device__ __forceinline__ SpecVerdict spec_verdict(const Params &p, const int b, const int dir, const int lane)
+{
+    SpecVerdict v;
+    const double *err = p.spec_err + ((size_t)b * 2 + dir) * (p.N + 1);
+    v.nint = (p.hdr[b].L + p.Delta - 1) / p.Delta;
+    v.worst = 0.0;
+    v.nbad = 0;
+#pragma unroll 4
+    for (int i = 1 + lane; i < v.nint; i += 64) {
+        const double e = err[i];
+        v.worst = fmax(v.worst, e);
+        v.nbad += !(e <= SPEC_TOL);
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        v.worst = fmax(v.worst, __shfl_xor(v.worst, off));
+        v.nbad += __shfl_xor(v.nbad, off);
+    }
+    v.ok = v.nbad == 0 && v.worst <= SPEC_TOL && (dir == 1 || v.nint == 0 || err[v.nint] == 0.0);
+    return v;
+}
+
+// Leaves the verdict on attempt `tier` for the later kernels and, on acceptance, chains the scale factors into the
+// checkpoint scales (only then: a later attempt that rewrites some of the checkpoints must find the others as their tasks
+// left them) and logZ.  One wave: lane l owns a contiguous run of boundaries in scan order, the running log2 factor is a
+// fixed-order prefix sum (per lane, then across lanes).
+__device__ __forceinline__ void spec_settle(const Params &p, const int b, const int dir, const int ndir, const int tier,
+                                            const SpecVerdict &v, const int lane)
+{
+    const int N = p.N, C = p.C, KC = p.K * C, nint = v.nint;
+    double *lr = p.spec_lr + ((size_t)b * 2 + dir) * (N + 1);  // entry 0 is no boundary: it carries the number that disagreed
+    if (dir == 0 && ndir == 1 && lane == 0) {  // the other direction is not run in this call
+        p.spec_ok[b * 2 + 1] = 0;
+        p.spec_rep[b * 2 + 1] = -1.0;
+    }
+    if (v.ok) {
+        const int nb = nint > 1 ? nint - 1 : 0;  // boundaries 1 .. nint-1
+        const int per = (nb + 63) / 64;
+        const int i0 = min(lane * per, nb), i1 = min(i0 + per, nb);
+        // i-th boundary in scan order: ascending for the forward scan, descending for the backward one
+        auto jof = [&](int i) { return dir == 0 ? 1 + i : nint - 1 - i; };
+        double s = 0.0;
+#pragma unroll 4
+        for (int i = i0; i < i1; ++i) s += lr[jof(i)];
+        double inc = s;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const double x = __shfl_up(inc, off);
+            if (lane >= off) inc += x;
+        }
+        const double total = __shfl(inc, 63);
+        double *ckY = (dir ? p.ckYB : p.ckYA) + (size_t)b * (N + 1);
+        double acc = inc - s;  // log2 of the factor between the true state and the warm-up state
+        for (int i = i0; i < i1; ++i) {
+            acc += lr[jof(i)];
+            ckY[jof(i)] += acc;
+        }
+        if (dir == 0) {
+            double lz;
+            if (nint == 0) {
+                lz = log((double)C);
+            } else {
+                // a_L(c) / Z: mass of the segments that end at L with label c
+                const double *e = p.ckA2 + ((size_t)b * (N + 1) + nint) * ((size_t)KC + C);
+                const double vL = lane < C ? e[KC + lane] : 0.0;
+                double sumL = vL;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) sumL += __shfl_xor(sumL, off);
+                lz = (p.ckYA2[(size_t)b * (N + 1) + nint] + total) * LN2 + log(sumL);
+                if (lane < C) p.inL[(size_t)b * C + lane] = vL / sumL;
+            }
+            if (lane == 0) {
+                p.hdr[b].logZ = lz;
+                p.logz[b] = (float)lz;
+            }
+        }
+    }
+    if (lane != 0) return;
+    // which attempt verified it: 1 the first, 2 after repairs, 3 after a longer warm-up (what the later attempts did
+    // was decided by the number of boundaries that had disagreed before)
+    const int code = tier == 0 ? 1 : (lr[0] <= (double)max(2, nint / 16) ? 2 : 3);
+    p.spec_rep[b * 2 + dir] = v.worst;
+    p.spec_ok[b * 2 + dir] = v.ok ? code : 0;
+    lr[0] = (double)v.nbad;
+}
+
+// Verdicts in a launch of their own, for scans whose kernels do not work them out.  grid (B, directions), one wave.
+__global__ __launch_bounds__(64) void k_spec_fix(Params p, int ndir, int tier)
+{
+    const int b = blockIdx.x, dir = blockIdx.y, lane = threadIdx.x;
+    if (tier > 0 && p.spec_ok[b * 2 + dir]) return;
+    spec_settle(p, b, dir, ndir, tier, spec_verdict(p, b, dir, lane), lane);
+}
+
+// Sequential scans: true if the pair needs none.  They follow the last attempt (number `tier`), whose verdict they
+// work out themselves.
+__device__ __forceinline__ bool spec_settled(const Params &p, const int b, const int dir, const int ndir, const int tier)
+{
+    if (!p.spec) return false;
+    if (p.spec_ok[b * 2 + dir]) return true;
+    const int lane = threadIdx.x & 63;
+    const SpecVerdict v = spec_verdict(p, b, dir, lane);
+    if (threadIdx.x < 64) spec_settle(p, b, dir, ndir, tier, v, lane);
+    return v.ok;
+}
+
