@@ -82,11 +82,12 @@ struct Params {
     double *spec_rep;   // [B][2] largest mismatch of the last verification (-1: not attempted), for the report
     int *spec_ok;       // [B][2]  1: the chunk-parallel scan of (sequence, direction) was accepted
     int logpair;        // k_prefix stores the log-domain pair (S + end score, start score - S): Viterbi
-    double2 *vr;        // [B][T+1][C] Viterbi: (V_t(c), r_t(c)) = best score arriving at / leaving position t
+    double *vv;         // [B][T+1][C] Viterbi: V_t(c) = best score arriving at position t
+    double *vrt;        // [B][C][T+1] Viterbi: r_t(c) = best score leaving position t
     int *vbest;         // [B] Viterbi: label of the last segment
     int *vbp;           // [B][T+1][C] Viterbi back-pointers: (duration << 8) | predecessor label
     int *vpar[2];       // [B][T+1][C] parent node (position * C + label) and its doublings (ping-pong)
-    int *vexit;         // [B][T+1][C] second buffer of the interval-exit pointers (the first is vpar[1])
+    int2 *vpiece;       // [B][pieces] nodes by which the path enters a piece of the trace-back and leaves it
     unsigned char *vmark;  // [B][T+1][C] 1: the node lies on the best path
     float *vscore;      // Viterbi outputs
     int32_t *vlabels, *vstarts, *vnseg;
@@ -288,6 +289,68 @@ __device__ __forceinline__ void row_dot16(const double y, const double *e, doubl
 }
 #undef SEMICRF_FD
 
+// the value lane N of the own row of 16 lanes holds
+template <int N>
+__device__ __forceinline__ double row_bcast(const double v)
+{
+    return __builtin_amdgcn_update_dpp(v, v, 0x150 + N, 0xf, 0xf, true);
+}
+
+// z0, z1 = running maxima of y(n) + e[n] over the even and the odd lanes n of the own row
+template <int... I>
+__device__ __forceinline__ void row_max(const double y, const double *e, double &z0, double &z1,
+                                        std::integer_sequence<int, I...>)
+{
+    (((I & 1 ? z1 : z0) = fmax(I & 1 ? z1 : z0, row_bcast<I>(y) + e[I])), ...);
+}
+
+// the larger of v and the v of the lane 32, 16 or (inside a row of 16) 8 away
+__device__ __forceinline__ double max_across_32(double v)
+{
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return fmax(__hiloint2double((int)b[0], (int)a[0]), __hiloint2double((int)b[1], (int)a[1]));
+}
+
+__device__ __forceinline__ double max_across_16(double v)
+{
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return fmax(__hiloint2double((int)b[0], (int)a[0]), __hiloint2double((int)b[1], (int)a[1]));
+}
+
+// the larger of v and the v of the lane N places on in the own row of 16 (cyclically)
+template <int N>
+__device__ __forceinline__ double max_row_ror(double v)
+{
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    const int lo2 = __builtin_amdgcn_update_dpp(0, lo, 0x120 + N, 0xf, 0xf, false);
+    const int hi2 = __builtin_amdgcn_update_dpp(0, hi, 0x120 + N, 0xf, 0xf, false);
+    return fmax(v, __hiloint2double(hi2, lo2));
+}
+
+// max over the 64/CTP lanes of a wave that share lane % CTP; every lane gets the result
+template <int CTP>
+__device__ __forceinline__ double group_max(double v)
+{
+    if (CTP <= 8) v = max_row_ror<8>(v);
+    if (CTP <= 16) v = max_across_16(v);
+    if (CTP <= 32) v = max_across_32(v);
+    return v;
+}
+
+// max over the wave, in every lane
+__device__ __forceinline__ double wave_max(double v)
+{
+    v = max_row_ror<8>(v);
+    v = max_row_ror<4>(v);
+    v = max_row_ror<2>(v);
+    v = max_row_ror<1>(v);
+    return max_across_32(max_across_16(v));
+}
+
 // rows 0,2 of v in rows 0,1,2,3 as 0,0,2,2 (-> even) and rows 1,3 as 1,1,3,3 (-> odd)
 __device__ __forceinline__ void both_row_parities(const double v, double &even, double &odd)
 {
@@ -339,6 +402,26 @@ struct RowMap {
         else if (CT == 24) row_dot12(in, e, z0, z1);
         else row_dot16(in, e, z0, z1);
         return add_across_32(z0 + z1);
+    }
+
+    // max_o (y(o) + e[o]), as product() (lanes and labels alike; an e of -infinity leaves an input out).
+    static __device__ __forceinline__ double max_product(const double y, const double *e)
+    {
+        double z0 = -INFINITY, z1 = -INFINITY;
+        if (CT == 64) {
+            constexpr std::make_integer_sequence<int, 16> seq;
+            double lo, hi, y0, y1, y2, y3;
+            both_halves(y, lo, hi);
+            both_row_parities(lo, y0, y1);
+            both_row_parities(hi, y2, y3);
+            row_max(y0, e, z0, z1, seq);
+            row_max(y1, e + 16, z0, z1, seq);
+            row_max(y2, e + 32, z0, z1, seq);
+            row_max(y3, e + 48, z0, z1, seq);
+            return fmax(z0, z1);
+        }
+        row_max(half_inputs(y), e, z0, z1, std::make_integer_sequence<int, HC <= 16 ? HC : 16>());
+        return max_across_32(fmax(z0, z1));
     }
 
     // sum of the vector, the same value in every lane (labels >= C must hold zeros)

@@ -270,12 +270,12 @@ struct WaveWin {
         return BWD ? M : KW - 1;
     }
 
-    // acc[i] += sum over the lane's strip of w[jj + i] * (entry at distance jj from `base`), every entry read once.
-    // The reads go out WRD at a time, one group ahead of the multiply-adds that use them (left to itself the compiler
+    // acc[i] = f(acc[i], w[jj + i], entry at distance jj from `base`) over the lane's strip, every entry read once.
+    // The reads go out WRD at a time, one group ahead of the arithmetic that uses them (left to itself the compiler
     // waits for every pair of reads before its eight multiply-adds: an LDS round trip of ~100 clocks for each 32).
     static constexpr int WRD = 8;
-    template <bool BWD, int NI>
-    static __device__ __forceinline__ void window_sums(const double *base, const double *w, double (&acc)[NI])
+    template <bool BWD, int NI, class F>
+    static __device__ __forceinline__ void window_fold(const double *base, const double *w, double (&acc)[NI], const F f)
     {
         constexpr int NG = (NK + WRD - 1) / WRD;
         double v[2][WRD];
@@ -296,11 +296,25 @@ struct WaveWin {
                 const int jj = NK - 1 - (grp * WRD + u);
                 if (jj >= 0) {
 #pragma unroll
-                    for (int i = 0; i < NI; ++i) acc[i] = fma(w[jj + i], v[grp & 1][u], acc[i]);
+                    for (int i = 0; i < NI; ++i) acc[i] = f(acc[i], w[jj + i], v[grp & 1][u]);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+    }
+
+    // sums of weight * entry
+    template <bool BWD, int NI>
+    static __device__ __forceinline__ void window_sums(const double *base, const double *w, double (&acc)[NI])
+    {
+        window_fold<BWD, NI>(base, w, acc, [](const double a, const double wt, const double x) { return fma(wt, x, a); });
+    }
+
+    // maxima of weight + entry
+    template <bool BWD, int NI>
+    static __device__ __forceinline__ void window_maxima(const double *base, const double *w, double (&acc)[NI])
+    {
+        window_fold<BWD, NI>(base, w, acc, [](const double a, const double wt, const double x) { return fmax(a, wt + x); });
     }
 
     // Checkpoint layout: message of position t' at slot t' mod K.  d = distance of slot sl

@@ -451,9 +451,9 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
 }
 
 // Viterbi workspace beyond the prefix-stage plan: (V, r) pairs, best final labels, back-pointers,
-// two pointer arrays and the path marks.
+// two pointer arrays, the trace-back's pieces and the path marks.
 struct VitLayout {
-    size_t vr, vbest, vbp, vpar0, vpar1, vexit, vmark, total;
+    size_t vr, vbest, vbp, vpar0, vpar1, vpiece, vmark, total;
 };
 
 VitLayout viterbi_layout(int B, int T, int C)
@@ -466,7 +466,7 @@ VitLayout viterbi_layout(int B, int T, int C)
     l.vbp = off; off += align_up(nodes * sizeof(int));
     l.vpar0 = off; off += align_up(nodes * sizeof(int));
     l.vpar1 = off; off += align_up(nodes * sizeof(int));
-    l.vexit = off; off += align_up(nodes * sizeof(int));
+    l.vpiece = off; off += align_up(nodes * sizeof(int));
     l.vmark = off; off += align_up(nodes);
     l.total = off;
     return l;
@@ -475,26 +475,29 @@ VitLayout viterbi_layout(int B, int T, int C)
 template <int CT, int NKW>
 int launch_viterbi_k(const Params &p, hipStream_t st)
 {
-    const size_t lds = wave_lds_doubles(CT, NKW) * sizeof(double);
+    constexpr int SW = spec_waves(CT, NKW);
+    const size_t lds = scan_lds_doubles(CT, NKW) * sizeof(double);
     if (lds > LDS_LIMIT) return SEMICRF_EUNSUPPORTED;
     if (hipFuncSetAttribute((const void *)k_viterbi<CT, NKW>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_vit_spec<CT, NKW>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds) != hipSuccess)
         return SEMICRF_ELAUNCH;
     if (p.spec) {
         // chunk-parallel scan with two warm-up lengths, as for the sum recurrences
         int warm[2] = {2 * p.K < 32 ? 32 : 2 * p.K, 8 * p.K < 64 ? 64 : 8 * p.K};
         if (p.warm0 > 0) warm[0] = p.warm0, warm[1] = 4 * p.warm0;  // the caller's first warm-up length
-        for (int tier = 0; tier < 2; ++tier) {
-            hipLaunchKernelGGL((k_vit_spec<CT, NKW>), dim3(p.B * p.N), dim3(64), lds, st, p, warm[tier], tier);
-            hipLaunchKernelGGL(k_vit_cmp, dim3(p.N, p.B), dim3(64), 0, st, p, tier);
-            hipLaunchKernelGGL(k_vit_fix, dim3(p.B), dim3(64), 0, st, p, tier);
-        }
+        if (hipFuncSetAttribute((const void *)k_vit_spec<CT, NKW, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)(SW * lds)) != hipSuccess ||
+            hipFuncSetAttribute((const void *)k_vit_spec<CT, NKW, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)(SW * lds)) != hipSuccess)
+            return SEMICRF_ELAUNCH;
+        const dim3 grid((p.B * p.N + SW - 1) / SW), block(64 * SW);
+        hipLaunchKernelGGL((k_vit_spec<CT, NKW, false>), grid, block, SW * lds, st, p, warm[0]);
+        hipLaunchKernelGGL(k_vit_cmp, dim3(p.N, p.B), dim3(NT), 0, st, p, 0);
+        hipLaunchKernelGGL((k_vit_spec<CT, NKW, true>), grid, block, SW * lds, st, p, warm[1]);
+        hipLaunchKernelGGL(k_vit_cmp, dim3(p.N, p.B), dim3(NT), 0, st, p, 1);
     } else {
         hipLaunchKernelGGL(k_spec_clear, dim3((2 * p.B + 63) / 64), dim3(64), 0, st, p);
     }
-    // sequential scan for what the verification rejected (returns at once otherwise)
     hipLaunchKernelGGL((k_viterbi<CT, NKW>), dim3(p.B), dim3(64), lds, st, p);
     return check_launch();
 }
@@ -528,12 +531,13 @@ int run_viterbi(Params p, void *workspace, size_t workspace_bytes, hipStream_t s
     p.nslot = pl.nslot;
     bind_workspace(p, pl, workspace);
     char *vw = (char *)workspace + pl.total;
-    p.vr = (double2 *)(vw + vl.vr);
+    p.vv = (double *)(vw + vl.vr);
+    p.vrt = p.vv + (size_t)p.B * ((size_t)p.T + 1) * p.C;
     p.vbest = (int *)(vw + vl.vbest);
     p.vbp = (int *)(vw + vl.vbp);
     p.vpar[0] = (int *)(vw + vl.vpar0);
     p.vpar[1] = (int *)(vw + vl.vpar1);
-    p.vexit = (int *)(vw + vl.vexit);
+    p.vpiece = (int2 *)(vw + vl.vpiece);
     p.vmark = (unsigned char *)(vw + vl.vmark);
     p.logpair = 1;
     p.spec = p.spec ? 1 : 0;
@@ -546,29 +550,29 @@ int run_viterbi(Params p, void *workspace, size_t workspace_bytes, hipStream_t s
     else if (C <= 32) rc = launch_viterbi_ct<32>(p, st);
     else rc = launch_viterbi_ct<64>(p, st);
     if (rc != SEMICRF_OK) return rc;
+    if (!p.vit_global) {
+        const int n = vit_piece_tokens(p.K, p.C), nt = n * VT_PIECES;
+        const size_t lds = vit_tile_lds(n, p.K, p.C);
+        if (lds + 1024 > LDS_LIMIT ||
+            hipFuncSetAttribute((const void *)k_vit_trace<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+                hipSuccess ||
+            hipFuncSetAttribute((const void *)k_vit_trace<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+                hipSuccess ||
+            hipFuncSetAttribute((const void *)k_vit_settle, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+                hipSuccess)
+            return SEMICRF_ELAUNCH;
+        const dim3 grid((p.T + nt - 1) / nt, p.B);
+        hipLaunchKernelGGL(k_vit_trace<false>, grid, dim3(VT_THREADS), lds, st, p, n);
+        hipLaunchKernelGGL(k_vit_trace<true>, grid, dim3(VT_THREADS), lds, st, p, n);
+        hipLaunchKernelGGL(k_vit_settle, dim3(p.B), dim3(VT_THREADS), lds, st, p, n);
+        return check_launch();
+    }
     {
         const size_t lds = 2 * (size_t)(p.K + VBP_TILE) * p.C * sizeof(double);  // checked before the first launch
         if (hipFuncSetAttribute((const void *)k_vit_bp, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
             hipSuccess)
             return SEMICRF_ELAUNCH;
         hipLaunchKernelGGL(k_vit_bp, dim3(p.T / VBP_TILE + 1, p.B), dim3(NT), lds, st, p);
-    }
-    const size_t lds_iv = (size_t)p.Delta * p.C * 5 + 16;  // parents (int) and path marks (byte) of one interval
-    if (lds_iv <= LDS_LIMIT && !p.vit_global) {
-        // trace-back by interval: local pointer jumping in LDS, doubling over the window nodes only
-        if (hipFuncSetAttribute((const void *)k_vit_local, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds_iv) != hipSuccess ||
-            hipFuncSetAttribute((const void *)k_vit_walk, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds_iv) != hipSuccess)
-            return SEMICRF_ELAUNCH;
-        hipLaunchKernelGGL(k_vit_local, dim3(p.N, p.B), dim3(NT), lds_iv, st, p);
-        int hops = 1;  // after round i the marks reach the exit nodes fewer than 2^(i+1) intervals down
-        while ((1 << hops) < p.N + 1) ++hops;
-        const unsigned wblk = (unsigned)(((size_t)p.N * p.K * p.C + NT - 1) / NT);
-        for (int i = 0; i < hops; ++i)
-            hipLaunchKernelGGL(k_vit_hop, dim3(wblk, p.B), dim3(NT), 0, st, p, i & 1, i == 0 ? 1 : 0);
-        hipLaunchKernelGGL(k_vit_walk, dim3(p.N, p.B), dim3(NT), lds_iv, st, p);
-        return check_launch();
     }
     const size_t nn = ((size_t)p.T + 1) * p.C;
     const unsigned nblk = (unsigned)((nn + NT - 1) / NT);

@@ -6,78 +6,63 @@
 // kernels, in the log domain (fp64 additions and maxima only; nothing needs rescaling):
 //     r_s(c) = max_c' (V_s(c') + trans[c',c]) + (start score of token s) - S[s,c]        (leaves s)
 //     V_t(c) = S[t,c] + (end score of token t-1) + max_k (dur[k,c] + r_{t-k}(c))          (arrives at t)
-// V_0 = 0 for every label.  One wave per sequence walks the positions in order and stores
-// (V_t, r_t) for every position and label; no back-pointers are kept.  The trace-back
-// (k_vit_trace) finds each segment's duration and predecessor label by recomputing the
-// candidates from the stored values: the same additions as in the scan, so the maxima are
-// bit-identical.  Ties go to the smallest duration, then the smallest label.
+// V_0 = 0 for every label.  The scan stores V_t by position and r_t by label for every position and label; no
+// back-pointers are kept.  The trace-back (k_vit_trace) finds each segment's duration and
+// predecessor label by recomputing the candidates from the stored values.  Ties go to the
+// smallest duration, then the smallest label.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double max_across_32(double v)
+// Best final label (smallest on ties) and score: lane holds V_L of label c in v, in the lanes `own` (one per label).
+__device__ __forceinline__ void vit_best(const Params &p, const int b, const double v, const int c, const bool own,
+                                         const double unit)
 {
-    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
-    const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-    const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-    return fmax(__hiloint2double((int)b[0], (int)a[0]), __hiloint2double((int)b[1], (int)a[1]));
+    const double best = wave_max(own ? v : -INFINITY);
+    int bl = own && v == best ? c : 0x7fffffff;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) bl = min(bl, __shfl_xor(bl, off));
+    if ((threadIdx.x & 63) == 0) {
+        p.vscore[b] = p.hdr[b].L > 0 ? (float)(best + unit) : 0.f;
+        p.vbest[b] = bl < 0x7fffffff ? bl : 0;
+    }
 }
 
-__device__ __forceinline__ double max_across_16(double v)
-{
-    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
-    const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-    const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    return fmax(__hiloint2double((int)b[0], (int)a[0]), __hiloint2double((int)b[1], (int)a[1]));
-}
-
-__device__ __forceinline__ double max_across_8(double v)
-{
-    const int lo = __double2loint(v), hi = __double2hiint(v);
-    const int lo2 = __builtin_amdgcn_update_dpp(0, lo, 0x128, 0xf, 0xf, false);
-    const int hi2 = __builtin_amdgcn_update_dpp(0, hi, 0x128, 0xf, 0xf, false);
-    return fmax(v, __hiloint2double(hi2, lo2));
-}
-
-// max over the 64/CTP lanes of a wave that share lane % CTP; every lane gets the result
-template <int CTP>
-__device__ __forceinline__ double group_max(double v)
-{
-    if (CTP <= 8) v = max_across_8(v);
-    if (CTP <= 16) v = max_across_16(v);
-    if (CTP <= 32) v = max_across_32(v);
-    return v;
-}
-
-// One scan task: the whole sequence (chunk < 0: the sequential scan) or one checkpoint interval
+// One scan task: the whole sequence (WHOLE: the sequential scan) or one checkpoint interval
 // (lo, hi] after a warm-up over the `warm` positions before it, started as a sequence that
 // begins there.  A chunk task records its window and V vector at lo (-> ckA[chunk]) and at hi
-// (-> ckA2[chunk+1]) for the verification, and stores (V_t, r_t) for lo < t <= hi (and for
+// (-> ckA2[chunk+1]) for the verification, and stores V_t and r_t for lo < t <= hi (and for
 // position 0 if lo = 0) in ITS OWN additive unit: max-plus recurrences are invariant under adding
 // a constant to every message, and a warmed-up chunk differs from the true values by exactly such
 // a constant once all best paths through the warm-up have merged.
-template <int CT, int NKW>
+// Lanes, window and time blocks as in the sum scans (spec_task): a maximum of sums is two
+// instructions where they have one, and the transition maximum three per entry (row broadcast, add,
+// max), still less than the way through LDS.  Genomic shape, 1024 tasks of 520 positions: 366 us with the
+// V vector in LDS and the window read where it is used, 205 us so.
+// V goes out by position, as it is made.  The trace-back looks at r along the positions of one label, so r is stored
+// by label, FT positions at a time out of the window (a row of FT * 8 bytes per label).
+template <int CT, int NKW, bool WHOLE>
 __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const int b, const int chunk,
                                          const int warm)
 {
-    using G = WaveWin<CT, NKW>;
-    constexpr int CTP = G::CTP, RS = G::RS, NK = G::NK, KW = G::KW, ROWS = G::ROWS;
-    constexpr int RTOT = G::RTOT, H = G::H, HC = G::HC;
-    const int lane = threadIdx.x;
+    using G = WaveWin<CT, NKW, 1>;
+    using R = RowMap<CT>;
+    constexpr int RS = G::RS, NK = G::NK, KW = G::KW, ROWS = G::ROWS;
+    constexpr int RTOT = G::RTOT, HC = G::HC;
+    const int lane = threadIdx.x & 63;
     const int K = p.K, C = p.C, KC = K * C;
     double *ring = lds_raw;          // [ROWS][RS] (+ pad): r of the last KW positions
-    double *yv = ring + RTOT;        // [CTP]: V of the current position
-    const int c = lane % CTP, g = lane / CTP;
-    const int hh = H == 2 ? (lane >> 5) : 0;
+    const int c = R::label(lane), g = R::group(lane);
+    const int hh = G::H == 2 ? (lane >> 5) : 0;
     const bool cval = c < C;
     const int cc = cval ? c : 0;
     const bool writer = cval && g == 0;
     const int L = p.hdr[b].L;
-    const bool whole = chunk < 0;
-    const int lo = whole ? 0 : chunk * p.Delta;
-    if (!whole && lo >= L && !(lo == 0 && L == 0)) return;
-    const int hi = whole ? L : min(lo + p.Delta, L);
-    const int s0 = whole ? 0 : max(lo - warm, 0);
+    const int lo = WHOLE ? 0 : chunk * p.Delta;
+    if (!WHOLE && lo >= L && !(lo == 0 && L == 0)) return;
+    const int hi = WHOLE ? L : min(lo + p.Delta, L);
+    const int s0 = WHOLE ? 0 : max(lo - warm, 0);
     const size_t row0 = (size_t)b * (p.T + 1);
     const double2 *LPc = p.EI + row0 * C + cc;  // (S + end score, start score - S)
-    double2 *VR = p.vr + row0 * C;
+    double *VV = p.vv + row0 * C, *RT = p.vrt + row0 * C;
+    const size_t ts = (size_t)p.T + 1;  // positions of a label in RT
     const double NINF = -INFINITY;
 
     double wd[NK + MB - 1];  // dur[g*NK + jj, c] (duration g*NK + jj + 1)
@@ -95,41 +80,43 @@ __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const
         const int o = hh * HC + i;
         Treg[i] = (cval && o < C) ? (double)p.trans[(size_t)o * C + c] : NINF;
     }
-    const double2 *ys = (const double2 *)__builtin_assume_aligned(yv + hh * HC, 16);
 
     for (int i = lane; i < RTOT; i += 64) ring[i] = NINF;
-    if (lane < CTP) yv[lane] = lane < C ? 0.0 : NINF;  // V = 0 for every label where the (sub)sequence begins
     lds_wave_fence();
     int r = KW - 1;
-    auto leave = [&]() {  // max_o (V(o) + trans[o,c]) from the V vector in yv
-        double m0 = NINF, m1 = NINF;
-#pragma unroll
-        for (int o = 0; o < HC; o += 2) {
-            const double2 vv = ys[o >> 1];
-            m0 = fmax(m0, vv.x + Treg[o]);
-            m1 = fmax(m1, vv.y + Treg[o + 1]);
-        }
-        double m = fmax(m0, m1);
-        if (H == 2) m = max_across_32(m);
-        return m;
-    };
+    double ylast = cval ? 0.0 : NINF;  // V of the newest position: 0 for every label where the (sub)sequence begins
     // state for the verification: r of the K positions up to t (by distance), then V_t
     const size_t ckstride = (size_t)KC + C;
     auto record = [&](double *ck) {
-        for (int i = lane; i < KC; i += 64) ck[i] = ring[(r - i / C) * RS + i % C];
-        if (lane < C) ck[KC + lane] = yv[lane];
+        if (cval) {
+#pragma unroll 4
+            for (int d = g; d < K; d += G::GW) ck[(size_t)d * C + c] = ring[(r - d) * RS + c];
+        }
+        if (writer) ck[KC + c] = ylast;
     };
     {
-        const double q = leave() + LPc[(size_t)s0 * C].y;
+        const double q = R::max_product(ylast, Treg) + LPc[(size_t)s0 * C].y;
         if (writer) {
             ring[r * RS + c] = q;
-            if (s0 == lo) VR[(size_t)s0 * C + c] = make_double2(0.0, q);
+            if (s0 == lo) VV[c] = 0.0;  // position 0
         }
     }
     lds_wave_fence();
-    if (!whole && s0 == lo) record(p.ckA + ((size_t)b * (p.N + 1) + chunk) * ckstride);
-    const int rdoff = -(g * NK + NK - 1) * RS + c;
+    constexpr int FT = KW >= 32 ? 16 : 8;  // the window must hold FT + MB - 1 positions
+    int tf = s0 == lo ? 0 : lo + 1;        // first position whose r has not been stored
     int t = s0;
+    auto flush = [&]() {
+        const int tp = tf + (lane & (FT - 1));
+        const double *src = ring + (r - (t - tp)) * RS;
+        double *dst = RT + tp;
+#pragma unroll
+        for (int i = 0; i < CT * FT / 64; ++i) {
+            const int cl = i * (64 / FT) + lane / FT;
+            if (tp <= t && cl < C) dst[cl * ts] = src[cl];
+        }
+        tf += FT;
+    };
+    const int rdoff = -(g * NK + NK - 1) * RS + c;
     auto load_rows = [&](double2 (&e)[MB], const int tfrom) {
 #pragma unroll
         for (int i = 0; i < MB; ++i) e[i] = LPc[(size_t)min(tfrom + 1 + i, hi) * C];
@@ -143,124 +130,111 @@ __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const
         double2 en[MB];
         load_rows(en, t + nb);
         if (__builtin_expect(r + MB > ROWS - 1, 0)) r = G::template move<false>(ring, lane, r);
-        const double *base = ring + r * RS + rdoff;
         double acc[MB];
 #pragma unroll
         for (int i = 0; i < MB; ++i) acc[i] = NINF;
+        G::template window_maxima<false, MB>(ring + r * RS + rdoff, wd, acc);
 #pragma unroll
-        for (int jj = 0; jj < NK; ++jj) {
-            const double v = base[(NK - 1 - jj) * RS];  // r of the position g*NK + jj before the newest
-#pragma unroll
-            for (int i = 0; i < MB; ++i) acc[i] = fmax(acc[i], wd[jj + i] + v);
+        for (int i = 0; i < MB; ++i) acc[i] = group_max<G::CTP>(acc[i]);
+        double *rowp = p.sink + lane;  // where there is no row to keep (or a lane owns no label)
+        int rstep = 0;
+        if (keep && writer) {
+            rowp = VV + (size_t)(t + 1) * C + c;
+            rstep = C;
         }
-#pragma unroll
-        for (int i = 0; i < MB; ++i) acc[i] = group_max<CTP>(acc[i]);
         double qn[MB];
+        auto position = [&](const int i) {
+            double x = acc[i];
 #pragma unroll
-        for (int i = 0; i < MB; ++i) {
-            if (i < nb) {
-                double x = acc[i];
+            for (int jn = 0; jn < i; ++jn) x = fmax(x, wn[i - 1 - jn] + qn[jn]);
+            const double y = x + e[i].x;  // V_t(c)
+            ylast = y;
+            const double q = R::max_product(y, Treg) + e[i].y;
+            qn[i] = q;
+            ++r;
+            if (writer) ring[r * RS + c] = q;
+            __builtin_nontemporal_store(y, rowp + i * rstep);
+        };
+        if (__builtin_expect(nb == MB, 1)) {  // a whole block: nothing is decided per position
 #pragma unroll
-                for (int jn = 0; jn < i; ++jn) x = fmax(x, wn[i - 1 - jn] + qn[jn]);
-                const double y = x + e[i].x;  // V_t(c)
-                if (cval) yv[c] = y;
-                lds_wave_fence();
-                const double q = leave() + e[i].y;
-                qn[i] = q;
-                ++r;
-                if (writer) {
-                    ring[r * RS + c] = q;
-                    if (keep) VR[(size_t)(t + 1 + i) * C + c] = make_double2(y, q);
-                }
-                lds_wave_fence();
-            } else {
-                qn[i] = NINF;
+            for (int i = 0; i < MB; ++i) position(i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < MB; ++i) {
+                if (i < nb) position(i);
+                else qn[i] = NINF;
             }
         }
+        lds_wave_fence();
         t += nb;
+        if (t - tf >= FT - 1) flush();
 #pragma unroll
         for (int i = 0; i < MB; ++i) e[i] = en[i];
-        if (!whole && t == lo) record(p.ckA + ((size_t)b * (p.N + 1) + chunk) * ckstride);
+        if (!WHOLE && __builtin_expect(t == lo, 0)) record(p.ckA + ((size_t)b * (p.N + 1) + chunk) * ckstride);
     }
-    if (!whole) {
+    if (tf <= t) flush();
+    if (!WHOLE) {
         record(p.ckA2 + ((size_t)b * (p.N + 1) + chunk + 1) * ckstride);
         return;
     }
-    // best final label (smallest on ties) and score
-    double best = cval ? yv[c] : NINF;
-    int bl = cval ? c : 0x7fffffff;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const double ov = __shfl_xor(best, off);
-        const int ol = __shfl_xor(bl, off);
-        if (ov > best || (ov == best && ol < bl)) {
-            best = ov;
-            bl = ol;
-        }
-    }
-    if (lane == 0) {
-        p.vscore[b] = L > 0 ? (float)best : 0.f;
-        p.vbest[b] = bl;
-    }
-}
-
-// The sequential scan: one wave per sequence (skips sequences whose chunk-parallel scan was accepted).
-template <int CT, int NKW>
-__global__ __launch_bounds__(64) void k_viterbi(Params p)
-{
-    extern __shared__ double lds_raw[];
-    if (p.spec && p.spec_ok[blockIdx.x * 2]) return;
-    vit_task<CT, NKW>(p, lds_raw, blockIdx.x, -1, 0);
+    vit_best(p, b, ylast, c, writer, 0.0);
 }
 
 // Largest disagreement at a chunk boundary that is accepted, relative to the larger of the entry
 // and the prefix sums at the boundary.
 constexpr double VIT_TOL = 1e-12;
 
-// The chunk-parallel scan: one wave per (sequence, checkpoint interval).
-template <int CT, int NKW>
-__global__ __launch_bounds__(64) void k_vit_spec(Params p, int warm, int tier)
+// The chunk-parallel scan: spec_waves(CT, NKW) tasks per workgroup, one per wave, as k_spec.  RETRY: only the chunks
+// whose warmed-up start disagreed with what the chunk before reached (chunk 0 starts exactly; by induction over the
+// boundaries a chunk whose left boundary agrees is right up to its constant, so only these can be wrong).
+template <int CT, int NKW, bool RETRY>
+__global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, NKW)) void k_vit_spec(Params p, int warm)
 {
     extern __shared__ double lds_raw[];
-    const int b = blockIdx.x / p.N, chunk = blockIdx.x % p.N;
-    if (tier > 0) {
-        // second pass: only the chunks whose warmed-up start disagreed with what the chunk before
-        // reached (chunk 0 starts exactly; by induction over the boundaries a chunk whose left
-        // boundary agrees is right up to its constant, so only these can be wrong)
-        if (p.spec_ok[b * 2] || chunk == 0) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int task = (int)blockIdx.x * spec_waves(CT, NKW) + wave;
+    const int b = task / p.N, chunk = task % p.N;
+    if (b >= p.B) return;
+    if (RETRY) {
+        if (chunk == 0 || chunk * p.Delta >= p.hdr[b].L) return;
         if (p.spec_err[((size_t)b * 2) * (p.N + 1) + chunk] <= VIT_TOL) return;
     }
-    vit_task<CT, NKW>(p, lds_raw, b, chunk, warm);
+    vit_task<CT, NKW, false>(p, lds_raw + (size_t)wave * scan_lds_doubles(CT, NKW), b, chunk, warm);
 }
 
 // Per chunk boundary j (position j*Delta): the state chunk j-1 reached against the warmed-up
 // state chunk j started from.  They must agree entry by entry up to ONE additive constant
-// (taken from the largest V entry); -inf entries must coincide.
-__global__ __launch_bounds__(64) void k_vit_cmp(Params p, int tier)
+// (taken from the largest V entry); -inf entries must coincide.  The results of the first attempt and of the second lie
+// in the two halves of spec_err and spec_lr; the second compares again what its scans have rewritten.
+__global__ __launch_bounds__(NT) void k_vit_cmp(Params p, int tier)
 {
-    const int j = blockIdx.x, b = blockIdx.y, lane = threadIdx.x;
-    if (tier > 0 && p.spec_ok[b * 2]) return;
+    __shared__ double part[NT / 64], spart[NT / 64];
+    const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int L = p.hdr[b].L;
     const int nint = (L + p.Delta - 1) / p.Delta;
     if (j < 1 || j >= nint) return;
     const int KC = p.K * p.C, C = p.C, N = p.N;
+    const size_t o = ((size_t)b * 2) * (N + 1) + j, o2 = o + (tier ? N + 1 : 0);
+    if (tier) {
+        const double e0 = p.spec_err[o], em = j > 1 ? p.spec_err[o - 1] : 0.0;
+        if (e0 <= VIT_TOL && em <= VIT_TOL) {
+            if (tid == 0) {
+                p.spec_err[o2] = e0;
+                p.spec_lr[o2] = p.spec_lr[o];
+            }
+            return;
+        }
+    }
     const size_t ckstride = (size_t)KC + C;
     const double *A = p.ckA + ((size_t)b * (N + 1) + j) * ckstride;    // warm-up state
     const double *A2 = p.ckA2 + ((size_t)b * (N + 1) + j) * ckstride;  // reached state
-    // additive constant: at the largest reached V entry (smallest label on ties)
-    double v = lane < C ? A2[KC + lane] : -INFINITY;
-    int idx = lane < C ? lane : 0x7fffffff;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const double ov = __shfl_xor(v, off);
-        const int oi = __shfl_xor(idx, off);
-        if (ov > v || (ov == v && oi < idx)) {
-            v = ov;
-            idx = oi;
-        }
-    }
-    const double delta = v - A[KC + idx];
-    double err = (v > -INFINITY && delta == delta && fabs(delta) < DBL_MAX) ? 0.0 : DBL_MAX;
+    // additive constant: at the largest reached V entry (smallest label on ties); every wave finds it
+    const double v = lane < C ? A2[KC + lane] : -INFINITY;
+    const double va = lane < C ? A[KC + lane] : -INFINITY;
+    const double vm = wave_max(v);
+    const unsigned long long at = __ballot(v == vm);
+    const double delta = vm - __shfl(va, at ? __ffsll(at) - 1 : 0);
+    double err = (vm > -INFINITY && delta == delta && fabs(delta) < DBL_MAX) ? 0.0 : DBL_MAX;
     // Every entry is a difference of prefix sums (r carries -S, V carries +S), so its rounding
     // error scales with |S| here, not with the entry: measure relative to the larger of the two.
     double smag = 1.0;
@@ -269,10 +243,9 @@ __global__ __launch_bounds__(64) void k_vit_cmp(Params p, int tier)
         if (fabs(lp.x) < DBL_MAX) smag = fmax(smag, fabs(lp.x));
         if (fabs(lp.y) < DBL_MAX) smag = fmax(smag, fabs(lp.y));
     }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) smag = fmax(smag, __shfl_xor(smag, off));
-#pragma unroll 4
-    for (int i = lane; i < KC + C; i += 64) {
+    smag = wave_max(smag);
+#pragma unroll 8
+    for (int i = tid; i < KC + C; i += NT) {
         const double x = A2[i], y = A[i];
         if (x == -INFINITY || y == -INFINITY) {
             if (x != y) err = DBL_MAX;
@@ -280,91 +253,382 @@ __global__ __launch_bounds__(64) void k_vit_cmp(Params p, int tier)
             err = fmax(err, fabs(x - (y + delta)) / fmax(smag, fmax(fabs(x), fabs(y + delta))));
         }
     }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) err = fmax(err, __shfl_xor(err, off));
-    if (lane == 0) {
-        const size_t o = ((size_t)b * 2) * (N + 1) + j;
-        p.spec_err[o] = err;
-        p.spec_lr[o] = delta;
+    err = wave_max(err);
+    if (lane == 0) part[wv] = err;
+    __syncthreads();
+    if (tid == 0) {
+        for (int i = 1; i < NT / 64; ++i) err = fmax(err, part[i]);
+        p.spec_err[o2] = err;
+        p.spec_lr[o2] = delta;
     }
 }
 
-// Accept or reject each sequence; chain the additive constants (ckYA[b][j] = what must be added
-// to the values stored by chunk j to get the true ones); best final label and score.
-
-__global__ __launch_bounds__(64) void k_vit_fix(Params p, int tier)
+// Accepts or rejects a sequence after the second attempt; chains the additive constants (ckYA[b][j] = what must be added
+// to the values stored by chunk j to get the true ones); best final label and score.  One wave; true if accepted.
+__device__ __forceinline__ bool vit_settle_scan(const Params &p, const int b, const int lane)
 {
-    const int b = blockIdx.x, lane = threadIdx.x;
-    if (tier > 0 && p.spec_ok[b * 2]) return;
     const int L = p.hdr[b].L, N = p.N, C = p.C, KC = p.K * C;
     const int nint = (L + p.Delta - 1) / p.Delta;
-    const size_t so = ((size_t)b * 2) * (N + 1);
+    const size_t so = ((size_t)b * 2) * (N + 1) + N + 1;
     double *off = p.ckYA + (size_t)b * (N + 1);
-    double worst = 0.0;
-    for (int j = 1 + lane; j < nint; j += 64) worst = fmax(worst, p.spec_err[so + j]);
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) worst = fmax(worst, __shfl_xor(worst, o));
     // prefix sums of the constants in a fixed order: lane l owns boundaries 1 + l*per .. l*per + per,
     // sums them in order, the lane totals are scanned across the wave, then every lane walks its own
-    double total = 0.0;
-    {
-        const int per = (max(nint - 1, 0) + 63) / 64;
-        const int j0 = 1 + lane * per, j1 = min(j0 + per, nint);
-        double mine = 0.0;
-        for (int j = j0; j < j1; ++j) mine += p.spec_lr[so + j];
-        double incl = mine;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const double up = __shfl_up(incl, o);
-            if (lane >= o) incl += up;
-        }
-        double run = incl - mine;
-        for (int j = j0; j < j1; ++j) {
-            run += p.spec_lr[so + j];
-            off[j] = run;
-        }
-        if (lane == 0) off[0] = 0.0;
-        total = __shfl(incl, 63);
+    const int per = (max(nint - 1, 0) + 63) / 64;
+    const int j0 = 1 + lane * per, j1 = min(j0 + per, nint);
+    double mine = 0.0, worst = 0.0;
+#pragma unroll 4
+    for (int j = j0; j < j1; ++j) {
+        mine += p.spec_lr[so + j];
+        worst = fmax(worst, p.spec_err[so + j]);
     }
+    worst = wave_max(worst);
+    double incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const double up = __shfl_up(incl, o);
+        if (lane >= o) incl += up;
+    }
+    double run = incl - mine;
+    for (int j = j0; j < j1; ++j) {
+        run += p.spec_lr[so + j];
+        off[j] = run;
+    }
+    const double total = __shfl(incl, 63);
     const bool ok = worst <= VIT_TOL;
     if (ok) {
-        double best = -INFINITY;
-        int bl = 0x7fffffff;
-        if (nint > 0) {
-            const double *e = p.ckA2 + ((size_t)b * (N + 1) + nint) * ((size_t)KC + C);
-            if (lane < C) {
-                best = e[KC + lane];
-                bl = lane;
-            }
-        } else if (lane == 0) {
-            best = 0.0;
-            bl = 0;
-        }
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const double ov = __shfl_xor(best, o);
-            const int ol = __shfl_xor(bl, o);
-            if (ov > best || (ov == best && ol < bl)) {
-                best = ov;
-                bl = ol;
-            }
-        }
-        if (lane == 0) {
-            p.vscore[b] = L > 0 ? (float)(best + total) : 0.f;
-            p.vbest[b] = bl;
-        }
+        const double *e = p.ckA2 + ((size_t)b * (N + 1) + nint) * ((size_t)KC + C);
+        const double v = lane < C ? (nint > 0 ? e[KC + lane] : 0.0) : -INFINITY;
+        vit_best(p, b, v, lane, lane < C, total);
     }
     if (lane == 0) {
+        off[0] = 0.0;
         p.spec_ok[b * 2] = ok ? 1 : 0;
         p.spec_rep[b * 2] = worst;
+        p.spec_ok[b * 2 + 1] = 0;  // there is no scan in the other direction
+        p.spec_rep[b * 2 + 1] = -1.0;
+    }
+    return ok;
+}
+
+// The verdict on the chunk-parallel scan of a sequence, and the sequential scan where there is none or it was rejected:
+// one wave per sequence.
+template <int CT, int NKW>
+__global__ __launch_bounds__(64) void k_viterbi(Params p)
+{
+    extern __shared__ double lds_raw[];
+    if (p.spec && vit_settle_scan(p, blockIdx.x, threadIdx.x)) return;
+    vit_task<CT, NKW, true>(p, lds_raw, blockIdx.x, 0, 0);
+}
+
+// ---------------------------------------------------------------------------
+// Trace-back.  Node (t, c) = "a segment with label c ends at position t"; its duration is the smallest k that
+// maximises dur[k,c] + r_{t-k}(c), the label of the node before it (at t - k) the smallest c' that maximises
+// V_{t-k}(c') + trans[c',c].  Only nodes that a path runs through are looked at.
+// Paths merge going back just as the scan's states do going forward, so a path is followed in pieces that are traced side
+// by side and verified against each other.  A piece of n tokens [lo, hi) follows a path from the best node a few positions
+// above hi down to lo; it came in by the lowest node at a position >= hi and leaves by the lowest at a position >= lo.
+// Where the piece above leaves by another node than the one by which this piece came in, it is traced again from there, until
+// every boundary agrees.  What starts at the root is right, so by induction all of it is THE path.
+//   k_vit_trace   one workgroup per tile of VT_PIECES pieces, with the rows of V and r that they can reach in LDS and 16
+//                 lanes per piece; tiles among each other are pieces again.  RETRY: the tiles that did not agree with the
+//                 tile above, from the node by which that one left.
+//   k_vit_settle  one workgroup per sequence: the tiles that do not even then, from the top down.
+// A tile writes its own tokens only, so a wrong path is overwritten where it was written.
+// What bounds it: the instructions of the chain of a path's nodes (from global memory instead of LDS, two loads of ~1000
+// clocks per node: 208 us at the genomic shape), then the reading of V and r.  A row of 16 lanes has one path because maxima
+// along a row are cheap, and 24 labels or a few dozen durations do not fill a wave.
+// ---------------------------------------------------------------------------
+constexpr int VT_THREADS = 512;
+constexpr int VT_PIECES = VT_THREADS / 16;
+constexpr int VT_WARM = 4;  // warm-up of a piece inside its tile
+
+// Tokens per piece n (tile: VT_PIECES n tokens): the most with which a compute unit holds two tiles, so that one loads while
+// the other follows its paths.  A tile's own warm-up is 4 n positions.
+inline __host__ __device__ int vit_tile_rows(const int n) { return VT_PIECES * n + 4 * n; }
+inline __host__ __device__ int vit_row_floats(const int n) { return ((n + 15) & ~15) + 1; }
+inline __host__ __device__ int vit_r_stride(const int n, const int K) { return (vit_tile_rows(n) + K) | 1; }
+inline size_t vit_tile_lds(const int n, const int K, const int C)
+{
+    return ((size_t)C * vit_r_stride(n, K) + (size_t)(vit_tile_rows(n) + 1) * C + vit_tile_rows(n) + K + 1) * sizeof(double) +
+           ((size_t)C * vit_row_floats(K) + (size_t)(C + 1) * vit_row_floats(C)) * sizeof(float);
+}
+inline int vit_piece_tokens(const int K, const int C)
+{
+    int n = 8;
+    while (n > 2 && vit_tile_lds(n, K, C) > LDS_LIMIT / 2 - 1024) n >>= 1;
+    return n;
+}
+
+// max and min along a row of 16 lanes, in each of its lanes
+__device__ __forceinline__ double row16_max(double v)
+{
+    v = max_row_ror<8>(v);
+    v = max_row_ror<4>(v);
+    v = max_row_ror<2>(v);
+    return max_row_ror<1>(v);
+}
+__device__ __forceinline__ int row16_min(int v)
+{
+    v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, true));
+    v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x124, 0xf, 0xf, true));
+    v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x122, 0xf, 0xf, true));
+    return min(v, __builtin_amdgcn_update_dpp(0, v, 0x121, 0xf, 0xf, true));
+}
+
+// Smallest index with the largest value along a row of 16 lanes; lane l holds its best so far.  `none` if all are -infinity.
+__device__ __forceinline__ int row16_first(const double best, const int at, const int none)
+{
+    const double m = row16_max(best);
+    const int i = row16_min(best == m ? at : 0x7fffffff);
+    return m > -INFINITY ? i : none;
+}
+
+// A tile's share of V and r, and the tables: dur by label, then trans by the label it leads to and a row of zeros (rows
+// padded with -infinity to whole turns of 16 lanes, and by one so that they start in different banks).
+struct VitTile {
+    double *r;     // [C][rs]: r_s(c) at [c][s - rbase]
+    double *v;     // [..][C]: V_s(c) at [s - vbase][c]
+    double *unit;  // [..]: additive constant of position rbase + i
+    float *dur, *tr;
+    int K, C, ks, cs, rs, rbase, vbase;
+
+    __device__ __forceinline__ VitTile(const Params &p, double *lds, const int n)
+    {
+        K = p.K;
+        C = p.C;
+        ks = vit_row_floats(K);
+        cs = vit_row_floats(C);
+        rs = vit_r_stride(n, K);
+        rbase = vbase = 0;
+        r = lds;
+        v = r + C * rs;
+        unit = v + (vit_tile_rows(n) + 1) * C;
+        dur = (float *)(unit + vit_tile_rows(n) + K + 1);
+        tr = dur + C * ks;
+    }
+    __device__ __forceinline__ void load_tables(const Params &p) const
+    {
+        const int tid = threadIdx.x;
+        // 16 lanes to a row, rows in turn
+        for (int c = tid >> 4; c < C; c += VT_PIECES) {
+#pragma unroll 4
+            for (int k = tid & 15; k < ks - 1; k += 16) dur[c * ks + k] = k < K ? p.dur[(size_t)k * C + c] : -INFINITY;
+        }
+        for (int c = tid >> 4; c <= C; c += VT_PIECES) {
+#pragma unroll 4
+            for (int o = tid & 15; o < cs - 1; o += 16)
+                tr[c * cs + o] = o < C ? (c < C ? p.trans[(size_t)o * C + c] : 0.f) : -INFINITY;
+        }
+    }
+    // V of positions lo .. top and r of positions max(lo - K, 0) .. top - 1, in the unit of the whole sequence
+    __device__ __forceinline__ void load_rows(const Params &p, const int b, const int lo, const int top)
+    {
+        const int tid = threadIdx.x;
+        const size_t ts = (size_t)p.T + 1;
+        rbase = max(lo - K, 0);
+        vbase = lo;
+        const int nr = top - rbase + 1;
+        const bool chunked = p.spec && p.spec_ok[b * 2];
+        const double *u = p.ckYA + (size_t)b * (p.N + 1);
+        // r: 256 threads along the positions, in two groups that take the labels in turn
+        const double *R = p.vrt + (size_t)b * ts * C + rbase;
+        for (int i = tid & 255; i < nr; i += 256) {
+            const int s = rbase + i;
+            const double x = chunked ? u[s == 0 ? 0 : (unsigned)(s - 1) / (unsigned)p.Delta] : 0.0;
+            if (tid < 256) unit[i] = x;
+            if (i == nr - 1) break;  // r at `top` itself is not needed
+#pragma unroll 8
+            for (int c = tid >> 8; c < C; c += VT_THREADS / 256) r[c * rs + i] = R[c * ts + i] + x;
+        }
+        __syncthreads();
+        const double *V = p.vv + ((size_t)b * ts + lo) * C;
+        const double *uv = unit + (lo - rbase);
+        const unsigned nv = (unsigned)(top - lo + 1) * C;
+#pragma unroll 8
+        for (unsigned i = tid; i < nv; i += VT_THREADS) {
+            const double x = V[i];
+            v[i] = x + uv[i / (unsigned)C];
+        }
+        __syncthreads();
+    }
+    // duration of the segment that ends at (t, c); l: lane of the row
+    __device__ __forceinline__ int duration(const int t, const int c, const int l) const
+    {
+        const double *rc = r + c * rs + (t - 1 - rbase);
+        const float *dc = dur + c * ks;
+        double best = -INFINITY;
+        int at = 0;
+#pragma unroll 4
+        for (int i = l; i < min(K, t); i += 16) {
+            const double x = rc[-i] + (double)dc[i];
+            if (x > best) {
+                best = x;
+                at = i;
+            }
+        }
+        return row16_first(best, at, 0) + 1;
+    }
+    // label of the node at s before one with label c (c = C: the best label at s)
+    __device__ __forceinline__ int label(const int s, const int c, const int l) const
+    {
+        const double *vs = v + (s - vbase) * C;
+        const float *tc = tr + c * cs;
+        double best = -INFINITY;
+        int at = 0;
+#pragma unroll 4
+        for (int o = l; o < C; o += 16) {
+            const double x = vs[o] + (double)tc[o];
+            if (x > best) {
+                best = x;
+                at = o;
+            }
+        }
+        return row16_first(best, at, 0);
+    }
+};
+
+// Traces tile j of sequence b (at least one token of it lies in the sequence).  from: the node (t C + c) by which the tile
+// above left, and the position where its segment starts (-1: not known); from.x < 0: start at the warm-up's best node.
+__device__ __forceinline__ void vit_tile(const Params &p, VitTile &tile, const int b, const int j, const int n, const int2 from)
+{
+    __shared__ int in[VT_PIECES];
+    __shared__ int2 out[VT_PIECES];
+    __shared__ int starts;
+    const int C = p.C, T = p.T, L = p.hdr[b].L, tid = threadIdx.x, i = tid >> 4, l = tid & 15;
+    const int tlo = j * n * VT_PIECES, thi = min(tlo + n * VT_PIECES, L);
+    const int top = from.x < 0 ? min(thi + 4 * n, L) : thi;
+    const int last = (thi - tlo - 1) / n;  // piece that ends at the tile's upper end
+    const int lo = tlo + i * n, hi = min(lo + n, L);
+    const int u = lo + l;  // the lane's token (l < n)
+    if (tid == 0) starts = 0;
+    tile.load_rows(p, b, tlo, top);
+    int lab = -1, st = 0;
+    auto trace = [&](int t, int c, int s) {  // s: start of the segment that ends at (t, c), -1: not known
+        lab = -1;
+        st = 0;
+        int entry = t * C + c;
+        bool inside = false;
+        int2 leave = make_int2(0, -1);
+        for (;;) {
+            if (t == lo) {
+                leave = make_int2(t * C + c, -1);
+                break;
+            }
+            if (s < 0) s = t - tile.duration(t, c, l);
+            if (s < hi) {
+                if (!inside) entry = t * C + c;
+                inside = true;
+                if (u >= s && u < t) {
+                    lab = c;
+                    st = u == s;
+                }
+            }
+            if (s < lo) {
+                leave = make_int2(t * C + c, s);
+                break;
+            }
+            c = tile.label(s, c, l);
+            t = s;
+            s = -1;
+        }
+        if (l == 0) {
+            in[i] = entry;
+            out[i] = leave;
+        }
+    };
+    if (i <= last) {
+        if (i == last && from.x >= 0) {
+            trace(from.x / C, from.x % C, from.y);
+        } else {
+            const int t = i == last ? top : min(hi + VT_WARM, top);
+            trace(t, t == L ? p.vbest[b] : tile.label(t, C, l), -1);
+        }
+    }
+    for (;;) {
+        __syncthreads();
+        const int2 above = i < last ? out[i + 1] : make_int2(0, 0);
+        const bool wrong = i < last && in[i] != above.x;
+        if (!__syncthreads_or(wrong)) break;
+        if (wrong) trace(above.x / C, above.x % C, above.y);
+    }
+    if (l < n && u < min(tlo + n * VT_PIECES, T)) {
+        p.vlabels[(size_t)b * T + u] = u < L ? lab : -1;
+        p.vstarts[(size_t)b * T + u] = u < L ? st : 0;
+    }
+    const int count = __popcll(__ballot(l < n && u < thi && st));
+    if ((tid & 63) == 0 && count) atomicAdd(&starts, count);
+    __syncthreads();
+    if (tid == 0) {
+        const size_t o = (size_t)b * ((T + n * VT_PIECES - 1) / (n * VT_PIECES)) + j;
+        p.vpiece[o] = make_int2(in[last], out[0].x);
+        p.vpar[0][o] = out[0].y;
+        p.vbp[o] = starts;
     }
 }
 
-// Trace-back, in parallel.  Node (t, c) = "a segment with label c ends at position t".
-// 1. k_vit_bp: for every node the duration is the smallest k that maximises
-//    dur[k,c] + r_{t-k}(c), then the predecessor label the smallest c' that maximises
-//    V_{t-k}(c') + trans[c',c]: the same additions as in the scan, so the maxima are the scan's,
-//    bit for bit.  A tile of 32 positions per workgroup with the K + 32 rows of (V, r) it can
+template <bool RETRY>
+__global__ __launch_bounds__(VT_THREADS) void k_vit_trace(Params p, int n)
+{
+    extern __shared__ double lds_raw[];
+    const int b = blockIdx.y, j = blockIdx.x, T = p.T, L = p.hdr[b].L, nt = n * VT_PIECES, lo = j * nt;
+    if (lo >= L) {
+        if (!RETRY) {  // tokens beyond the sequence
+            for (int u = lo + threadIdx.x; u < min(lo + nt, T); u += VT_THREADS) {
+                p.vlabels[(size_t)b * T + u] = -1;
+                p.vstarts[(size_t)b * T + u] = 0;
+            }
+        }
+        return;
+    }
+    int2 from = make_int2(-1, -1);
+    if (RETRY) {
+        if (lo + nt >= L) return;
+        const size_t o = (size_t)b * gridDim.x + j;
+        from = make_int2(p.vpiece[o + 1].y, p.vpar[0][o + 1]);
+        if (p.vpiece[o].x == from.x) return;
+    }
+    VitTile tile(p, lds_raw, n);
+    tile.load_tables(p);
+    vit_tile(p, tile, b, j, n, from);
+}
+
+__global__ __launch_bounds__(VT_THREADS) void k_vit_settle(Params p, int n)
+{
+    extern __shared__ double lds_raw[];
+    __shared__ int total[VT_THREADS / 64];
+    const int b = blockIdx.x, tid = threadIdx.x, nt = n * VT_PIECES;
+    const int npl = (p.hdr[b].L + nt - 1) / nt;
+    const size_t o = (size_t)b * ((p.T + nt - 1) / nt);
+    const int2 *piece = p.vpiece + o;  // (enters, leaves)
+    int again = 0;
+    for (int j = tid; j < npl - 1; j += VT_THREADS) again |= piece[j].x != piece[j + 1].y;
+    if (__syncthreads_or(again)) {  // rarely
+        VitTile tile(p, lds_raw, n);
+        tile.load_tables(p);
+        for (int j = npl - 2; j >= 0; --j) {
+            const int2 from = make_int2(piece[j + 1].y, p.vpar[0][o + j + 1]);
+            if (piece[j].x != from.x) vit_tile(p, tile, b, j, n, from);
+            __threadfence_block();
+            __syncthreads();
+        }
+    }
+    int cnt = 0;
+    for (int j = tid; j < npl; j += VT_THREADS) cnt += p.vbp[o + j];
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) cnt += __shfl_xor(cnt, off);
+    if ((tid & 63) == 0) total[tid >> 6] = cnt;
+    __syncthreads();
+    if (tid == 0) {
+        for (int i = 1; i < VT_THREADS / 64; ++i) cnt += total[i];
+        p.vnseg[b] = cnt;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The same path by pointer doubling over all nodes (SEMICRF_VITERBI_GLOBAL_TRACE): looks at every node, at a cost that
+// does not depend on the data; kept as the other side of the comparison.
+// 1. k_vit_bp: duration and predecessor label of every node.
+//    A tile of 32 positions per workgroup with the K + 32 rows of (V, r) it can
 //    reach staged in LDS.  parent(t, c) = (t - k, c'); nodes at position 0 are their own parent.
 // 2. k_vit_round, ceil(log2(T+1)) times: every marked node marks the node its current
 //    pointer leads to, then every pointer is replaced by the pointer's pointer.  After round i
@@ -383,7 +647,7 @@ __global__ __launch_bounds__(NT) void k_vit_bp(Params p)
     double *vv = lds_raw;                            // [rows][C]  V
     double *rr = lds_raw + (size_t)rows * C;         // [rows][C]  r
     const size_t nn = (size_t)(T + 1) * C;
-    const double2 *VR = p.vr + (size_t)b * nn;
+    const double *VV = p.vv + (size_t)b * nn, *RT = p.vrt + (size_t)b * nn;
     // values stored by an accepted chunk-parallel scan are in their chunk's additive unit
     const bool chunked = p.spec && p.spec_ok[b * 2];
     const double *unit = p.ckYA + (size_t)b * (p.N + 1);
@@ -391,7 +655,7 @@ __global__ __launch_bounds__(NT) void k_vit_bp(Params p)
         const int sp = sbase + i / C;
         double2 x = make_double2(-INFINITY, -INFINITY);
         if (sp >= 0 && sp <= L) {
-            x = VR[(size_t)sp * C + i % C];
+            x = make_double2(VV[(size_t)sp * C + i % C], RT[(size_t)(i % C) * (T + 1) + sp]);
             if (chunked) {
                 const double u = unit[sp == 0 ? 0 : (sp - 1) / p.Delta];
                 x.x += u;
@@ -495,143 +759,3 @@ __global__ __launch_bounds__(NT) void k_vit_count(Params p)
     for (int off = 32; off; off >>= 1) cnt += __shfl_xor(cnt, off);
     if ((threadIdx.x & 63) == 0 && cnt) atomicAdd(&p.vnseg[b], cnt);
 }
-
-// ---------------------------------------------------------------------------
-// Trace-back by checkpoint interval (used when an interval's nodes fit in LDS): pointer doubling
-// over all nodes touches every node ceil(log2 T) times in HBM; here
-//   k_vit_local  one workgroup per (sequence, interval): the parents of the interval's nodes
-//                (positions lo < t <= hi) are loaded into LDS and jumped until every node points
-//                at its EXIT node, the first node of its path at a position <= lo;
-//   k_vit_hop    ceil(log2 N) + 1 launches over the window nodes only (the at most K positions
-//                below each interval's upper end, where exit nodes lie): marks the path's exit
-//                nodes by pointer doubling over the exit pointers, as k_vit_round does over all;
-//   k_vit_walk   one workgroup per (sequence, interval): from the interval's marked entry node
-//                one thread follows the parents in LDS and marks the path; all threads then
-//                write the marked nodes' segments and count them.
-// ---------------------------------------------------------------------------
-// local parent of the interval's node i (global id n): index inside the interval, or -(id) - 1 of
-// a parent at a position <= lo
-__device__ __forceinline__ int vit_local_parent(const int *par, const size_t n, const int lo, const int C)
-{
-    const int gp = par[n];
-    const int tp = gp / C;
-    return tp > lo ? (tp - lo - 1) * C + (gp - tp * C) : -gp - 1;
-}
-
-__global__ __launch_bounds__(NT) void k_vit_local(Params p)
-{
-    extern __shared__ int lds_int[];
-    const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-    const int C = p.C, L = p.hdr[b].L;
-    const size_t nn = (size_t)(p.T + 1) * C;
-    const int *par = p.vpar[0] + (size_t)b * nn;
-    int *e0 = p.vpar[1] + (size_t)b * nn, *e1 = p.vexit + (size_t)b * nn;
-    if (j == 0 && tid < C) {  // the nodes at position 0 are where every path ends
-        e0[tid] = tid;
-        e1[tid] = tid;
-    }
-    const int lo = j * p.Delta;
-    if (lo >= L) return;
-    const int hi = min(lo + p.Delta, L);
-    const int nloc = (hi - lo) * C;
-    int *lp = lds_int;
-    for (int i = tid; i < nloc; i += NT) lp[i] = vit_local_parent(par, (size_t)(lo + 1) * C + i, lo, C);
-    __syncthreads();
-    for (;;) {  // jump until every pointer has left the interval (at most ceil(log2(hi - lo)) + 1 rounds)
-        int pending = 0;
-        for (int i = tid; i < nloc; i += NT) {
-            const int v = lp[i];
-            if (v >= 0) {
-                const int w = lp[v];  // an older or a newer pointer of v: both lie on i's path
-                lp[i] = w;
-                pending |= w >= 0;
-            }
-        }
-        if (!__syncthreads_or(pending)) break;
-    }
-    for (int i = tid; i < nloc; i += NT) {
-        const int e = -lp[i] - 1;
-        e0[(size_t)(lo + 1) * C + i] = e;
-        e1[(size_t)(lo + 1) * C + i] = e;
-    }
-}
-
-// One doubling round over the window nodes (interval j, distance d below its upper end, label c).
-__global__ __launch_bounds__(NT) void k_vit_hop(Params p, int src, int first)
-{
-    const int b = blockIdx.y, C = p.C, K = p.K;
-    const int L = p.hdr[b].L;
-    const size_t nn = (size_t)(p.T + 1) * C;
-    const unsigned idx = blockIdx.x * NT + threadIdx.x;
-    const unsigned kc = (unsigned)K * C;
-    const int j = (int)(idx / kc);
-    if (j >= p.N) return;
-    const int lo = j * p.Delta;
-    if (lo >= L) return;
-    const int hi = min(lo + p.Delta, L);
-    const int r = (int)(idx - (unsigned)j * kc);
-    const int t = hi - r / C;
-    if (t <= lo) return;  // that position belongs to an earlier interval's window
-    const size_t n = (size_t)t * C + r % C;
-    const int *ein = (src ? p.vexit : p.vpar[1]) + (size_t)b * nn;
-    int *eout = (src ? p.vpar[1] : p.vexit) + (size_t)b * nn;
-    unsigned char *mark = p.vmark + (size_t)b * nn;
-    const int e = ein[n];
-    const bool root = first && n == (size_t)L * C + p.vbest[b];
-    if (root) mark[n] = 1;
-    if (root || mark[n]) mark[e] = 1;  // a mark set earlier in this launch only arrives sooner
-    eout[n] = ein[e];
-}
-
-__global__ __launch_bounds__(NT) void k_vit_walk(Params p)
-{
-    extern __shared__ int lds_int[];
-    __shared__ int entry, cnt;
-    const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-    const int C = p.C, T = p.T, L = p.hdr[b].L;
-    const size_t nn = (size_t)(T + 1) * C;
-    int32_t *lab = p.vlabels + (size_t)b * T, *st = p.vstarts + (size_t)b * T;
-    const int lo = j * p.Delta;
-    // tokens beyond the sequence
-    for (int u = max(lo, L) + tid; u < min(lo + p.Delta, T); u += NT) {
-        lab[u] = -1;
-        st[u] = 0;
-    }
-    if (lo >= L) return;
-    const int hi = min(lo + p.Delta, L);
-    const int nloc = (hi - lo) * C;
-    const int *par = p.vpar[0] + (size_t)b * nn;
-    const unsigned char *mark = p.vmark + (size_t)b * nn;
-    int *lp = lds_int;
-    unsigned char *lm = (unsigned char *)(lds_int + nloc);
-    if (tid == 0) {
-        entry = -1;
-        cnt = 0;
-    }
-    __syncthreads();
-    for (int i = tid; i < nloc; i += NT) {
-        lp[i] = vit_local_parent(par, (size_t)(lo + 1) * C + i, lo, C);
-        lm[i] = 0;
-        if (mark[(size_t)(lo + 1) * C + i]) entry = i;  // at most one: where the best path enters the interval
-    }
-    __syncthreads();
-    if (tid == 0) {
-        for (int cur = entry; cur >= 0; cur = lp[cur]) lm[cur] = 1;
-    }
-    __syncthreads();
-    int mine = 0;
-    for (int i = tid; i < nloc; i += NT) {
-        if (!lm[i]) continue;
-        const int t = lo + 1 + i / C, c = i % C;
-        const int k = p.vbp[(size_t)b * nn + (size_t)t * C + c] >> 8;
-        for (int u = t - k; u < t; ++u) {
-            lab[u] = c;
-            st[u] = u == t - k ? 1 : 0;
-        }
-        ++mine;
-    }
-    if (mine) atomicAdd(&cnt, mine);
-    __syncthreads();
-    if (tid == 0 && cnt) atomicAdd(&p.vnseg[b], cnt);
-}
-
