@@ -184,63 +184,57 @@ inline void launch_fin_emis(const Params &p, hipStream_t st)
 }
 
 // grad_trans[c',c] = Etr[c',c] * sum_b w_b sum_i partTr;  grad_dur[k,c] = sum_b w_b sum_i partD.
-// One workgroup per FIN_PO outputs; NT / FIN_PO thread groups take the partial sums i = g, g + groups, ... and
-// their sums are combined in group order (fixed order for a given problem).
+// One workgroup per FIN_PO outputs; its NT / FIN_PO thread groups take the partial sums of all sequences in turn and
+// their sums are combined in group order (fixed order for a given problem).  Eight of a group's partial sums are
+// requested before the first is added: taken sequence by sequence, a batch of short ones (16 partial sums for 32 groups
+// each) cost a memory latency per four sequences with half of the groups idle, 30 us for B = 64, T = 256.
+// Outputs are dealt so that neighbouring ones, which share lines, fall to workgroups of one chiplet (blocks go round the
+// eight of them).
 constexpr int FIN_PO = 8;  // small: the partial sums of a long sequence are many, the outputs few
+inline __host__ __device__ int fin_param_blocks(const int K, const int C)
+{
+    return ((C * C + K * C + FIN_PO - 1) / FIN_PO + 7) & ~7;
+}
 __device__ __forceinline__ void fin_params_body(const Params &p, const int blk)
 {
     __shared__ double red[NT];
-    constexpr int NG = NT / FIN_PO;
+    constexpr int NG = NT / FIN_PO, UB = 8;
     const int C = p.C, CC = C * C, KC = p.K * C, N = p.NP, tid = threadIdx.x;
     const int o = tid % FIN_PO, g = tid / FIN_PO;
-    const int idx = blk * FIN_PO + o;
+    const int idx = ((blk & 7) * (fin_param_blocks(p.K, C) >> 3) + (blk >> 3)) * FIN_PO + o;
     const bool ok = idx < CC + KC;
-    // The number of partial sums of a sequence is fetched once per sequence by the first threads, and the
-    // sequences are taken four at a time: the first partial sum each thread group takes of each of them is loaded
-    // before any is added (many short sequences would otherwise cost one memory latency each), the rest, for
-    // sequences with more partial sums than thread groups, in four chains as before.  Fixed order throughout.
-    constexpr int UB = 4;
-    __shared__ int npart[NT];
-    if (tid < p.B) {
-        const int Ds = stat_delta(p, tid);
-        npart[tid] = (p.hdr[tid].L + Ds - 1) / Ds;
-    }
-    __syncthreads();
+    __shared__ int npart[NT];  // partial sums of the first NT sequences, and their weights
+    __shared__ double weight[NT];
     auto count = [&](const int b) {
-        if (b < NT) return npart[b];
         const int Ds = stat_delta(p, b);
         return (p.hdr[b].L + Ds - 1) / Ds;
     };
+    auto factor = [&](const int b) { return p.grad_logz ? (double)p.grad_logz[b] : 1.0; };
+    if (tid < p.B) {
+        npart[tid] = count(tid);
+        weight[tid] = factor(tid);
+    }
+    __syncthreads();
     const size_t stride = idx < CC ? (size_t)CC : (size_t)KC;
     const double *q0 = idx < CC ? p.partTr + idx : p.partD + (idx - CC);  // partial sum i of sequence b at (b*N + i)*stride
     double acc = 0.0;
     if (ok) {
-        for (int b0 = 0; b0 < p.B; b0 += UB) {
+        int b = g / N, i = g % N;  // the group's next partial sum
+        const int db = NG / N, di = NG % N;
+        while (b < p.B) {
             double v[UB], w[UB];
-            int nint[UB];
-            bool more = false;
 #pragma unroll
             for (int u = 0; u < UB; ++u) {
-                const int b = b0 + u;
-                nint[u] = b < p.B ? count(b) : 0;
-                w[u] = (b < p.B && p.grad_logz) ? (double)p.grad_logz[b] : 1.0;
-                v[u] = g < nint[u] ? q0[((size_t)b * N + g) * stride] : 0.0;
-                more = more || nint[u] > NG;
-            }
-            if (more) {
-#pragma unroll
-                for (int u = 0; u < UB; ++u) {
-                    const double *q = q0 + ((size_t)(b0 + u) * N) * stride;
-                    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-                    int i = g + NG;
-                    for (; i + 3 * NG < nint[u]; i += 4 * NG) {
-                        s0 += q[(size_t)i * stride];
-                        s1 += q[(size_t)(i + NG) * stride];
-                        s2 += q[(size_t)(i + 2 * NG) * stride];
-                        s3 += q[(size_t)(i + 3 * NG) * stride];
-                    }
-                    for (; i < nint[u]; i += NG) s0 += q[(size_t)i * stride];
-                    v[u] += (s0 + s1) + (s2 + s3);
+                v[u] = w[u] = 0.0;
+                if (b < p.B && i < (b < NT ? npart[b] : count(b))) {
+                    v[u] = q0[((size_t)b * N + i) * stride];
+                    w[u] = b < NT ? weight[b] : factor(b);
+                }
+                b += db;
+                i += di;
+                if (i >= N) {
+                    i -= N;
+                    ++b;
                 }
             }
 #pragma unroll
@@ -261,7 +255,7 @@ __device__ __forceinline__ void fin_params_body(const Params &p, const int blk)
 // per FIN_PO parameter gradients.
 __global__ __launch_bounds__(NT) void k_fin_seq(Params p)
 {
-    const int nparam = (p.C * p.C + p.K * p.C + FIN_PO - 1) / FIN_PO;
+    const int nparam = fin_param_blocks(p.K, p.C);
     const int nseq = p.B * FIN_FS;
     if ((int)blockIdx.x < nseq) fin_seq_body(p, blockIdx.x / FIN_FS, blockIdx.x % FIN_FS);
     else if ((int)blockIdx.x < nseq + nparam) fin_params_body(p, blockIdx.x - nseq);

@@ -114,7 +114,7 @@ void bind_workspace(Params &p, const Plan &pl, void *ws)
     p.spec_rep = (double *)(w + pl.off[8]);
     p.spec_ok = (int *)(p.spec_rep + (size_t)p.B * 2);
     p.spec_lr = (double *)(w + pl.off[8] + align_up((size_t)p.B * 2 * (sizeof(double) + sizeof(int))));
-    p.spec_err = p.spec_lr + (size_t)p.B * 2 * (pl.N + 1);
+    p.spec_err = p.spec_lr + (size_t)p.B * 2 * (pl.Ns + 1);
 }
 
 int check_launch()
@@ -373,8 +373,8 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
     if (rc != SEMICRF_OK) return rc;
     if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < pl.total)
         return SEMICRF_EWORKSPACE;
-    p.Delta = pl.Delta;
-    p.N = pl.N;
+    p.Delta = pl.Ds;  // = Delta with gradients
+    p.N = pl.Ns;
     p.NCH = pl.NCH;
     p.nslot = pl.nslot;
     p.want_grad = mode == 2;
@@ -443,7 +443,7 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
     rc = launch_interval(p, pl, st);
     if (rc != SEMICRF_OK) return rc;
     T.mark();
-    hipLaunchKernelGGL(k_fin_seq, dim3(p.B * FIN_FS + (p.C * p.C + p.K * p.C + FIN_PO - 1) / FIN_PO + ((p.g_pi_start || p.g_pi_end) ? 1 : 0)),
+    hipLaunchKernelGGL(k_fin_seq, dim3(p.B * FIN_FS + fin_param_blocks(p.K, p.C) + ((p.g_pi_start || p.g_pi_end) ? 1 : 0)),
                        dim3(NT), 0, st, p);
     launch_fin_emis(p, st);
     T.mark();
