@@ -82,6 +82,22 @@ int auto_interval(int B, int T, int K, int C)
     return best;
 }
 
+// A forward-only call has one scan where the interval was chosen for two: where that leaves half of the chip's places for
+// scan tasks empty, its intervals are half as long.  Two waves on a SIMD take about 1.25 times the time of one per position
+// (a lone one waits for 40 % of its time), so with a warm-up of W positions halving D gains while D + W > 1.25 (D/2 + W),
+// D > W / 1.5.  Measured at K = 64, C = 24, D = 392, whole call: 238 -> 224 us.  (The best-score scan is bound by the issue
+// of its maxima, two waves take twice the time of one, and keeps D: 245 us either way.)
+int forward_interval(int B, int T, int K, int C, int Delta)
+{
+    int per_scan = 0, per_int = 0;
+    if (!spec_applies(K, C) || !wave_tasks_per_cu(K, C, &per_scan, &per_int)) return Delta;
+    const int unit = Delta % 32 == 0 ? 32 : 8;
+    const int half = (Delta / 2 + unit - 1) / unit * unit;
+    if (half >= Delta || half < sum_warmup(K)) return Delta;
+    const double tasks = (double)B * (double)(((long long)T + half - 1) / half);
+    return tasks <= 256.0 * per_scan ? half : Delta;
+}
+
 int low_memory_interval(int T, int K)
 {
     const double d = ceil(sqrt((double)T * (double)K));
@@ -103,6 +119,8 @@ int make_plan(int B, int T, int K, int C, int ckpt_interval, int want_grad, Plan
     pl->Delta = ckpt_interval > 0 ? (ckpt_interval > T ? T : ckpt_interval)
                                   : (lowmem ? low_memory_interval(T, K) : auto_interval(B, T, K, C));
     pl->N = (int)(((long long)T + pl->Delta - 1) / pl->Delta);
+    pl->Ds = kind == 0 && !lowmem && ckpt_interval == 0 ? forward_interval(B, T, K, C, pl->Delta) : pl->Delta;
+    pl->Ns = (int)(((long long)T + pl->Ds - 1) / pl->Ds);
     pl->NCH = T / PREP_CH + 1;
     pl->G = (NT / C) < K ? (NT / C) : K;
     pl->lds_scan = lds_doubles(K, C, pl->G, false) * sizeof(double);
@@ -116,7 +134,8 @@ int make_plan(int B, int T, int K, int C, int ckpt_interval, int want_grad, Plan
     const size_t capped = cap < (size_t)NSLOT_MAX ? cap : (size_t)NSLOT_MAX;
     pl->nslot = (int)(ntask < capped ? ntask : capped);
     pl->nslot = (pl->nslot + 11) / 12 * 12;  // whole workgroups of three or four single-wave tasks
-    const size_t b = (size_t)B, t1 = (size_t)T + 1, c = (size_t)C, k = (size_t)K, n = (size_t)pl->N;
+    const size_t b = (size_t)B, t1 = (size_t)T + 1, c = (size_t)C, k = (size_t)K, n = (size_t)pl->N,
+                 ns = (size_t)pl->Ns;
     size_t *sz = pl->size;
     for (int j = 0; j < 32; ++j) sz[j] = 0, pl->off[j] = 0;
     const size_t g = kind ? 1 : 0;
@@ -128,18 +147,18 @@ int make_plan(int B, int T, int K, int C, int ckpt_interval, int want_grad, Plan
     sz[PL_W] = k * c * 8;
     sz[PL_ETR] = c * c * 8;
     sz[PL_EI] = b * t1 * c * 16;
-    sz[PL_SPEC] = align_up(b * 2 * (8 + 4)) + 2 * b * 2 * (n + 1) * 8;  // spec_rep, spec_ok; spec_lr, spec_err
+    sz[PL_SPEC] = align_up(b * 2 * (8 + 4)) + 2 * b * 2 * (ns + 1) * 8;  // spec_rep, spec_ok; spec_lr, spec_err
     sz[PL_NBASE] = b * t1 * c * 4;
-    sz[PL_CKA] = b * (n + 1) * (k * c + c) * 8;
+    sz[PL_CKA] = b * (ns + 1) * (k * c + c) * 8;
     sz[PL_CKB] = g * b * (n + 1) * (k * c + c) * 8;
-    sz[PL_CKYA] = b * (n + 1) * 8;
+    sz[PL_CKYA] = b * (ns + 1) * 8;
     sz[PL_CKYB] = g * b * (n + 1) * 8;
     sz[PL_ALOC] = g * (size_t)pl->nslot * pl->Delta * 2 * c * 8;
     sz[PL_ALOCY] = g * (size_t)pl->nslot * pl->Delta * 8;
     sz[PL_MEAN] = g * b * FIN_SLICES * c * 8;
-    sz[PL_CKA2] = b * (n + 1) * (k * c + c) * 8;
+    sz[PL_CKA2] = b * (ns + 1) * (k * c + c) * 8;
     sz[PL_CKB2] = g * b * (n + 1) * (k * c + c) * 8;
-    sz[PL_CKYA2] = b * (n + 1) * 8;
+    sz[PL_CKYA2] = b * (ns + 1) * 8;
     sz[PL_CKYB2] = g * b * (n + 1) * 8;
     sz[PL_OUT0] = b * c * 8;
     sz[PL_INL] = b * c * 8;

@@ -12,6 +12,7 @@ namespace semicrf_impl {
 
 struct Plan {
     int Delta, N, NCH, nslot, G;
+    int Ds, Ns;  // interval and number of intervals of the scans of a forward-only call
     int rows;  // the backward scan tasks have row storage (stored-row marginals possible)
     int msplit;  // parts an interval is cut into by the one-wave stored-row marginals (per-part partial sums)
     size_t lds_mg_dur, lds_mg_te;
@@ -48,6 +49,9 @@ bool spec_applies(int K, int C);
 
 // Automatic checkpoint interval of the default plan (one task per SIMD where the sizes allow it).
 int auto_interval(int B, int T, int K, int C);
+
+// Interval of the scans of a forward-only call whose automatic interval is Delta.
+int forward_interval(int B, int T, int K, int C, int Delta);
 
 // Checkpoint interval of the low-memory plan: the spacing of Algorithm 1, ceil(sqrt(T*K)), as a multiple of 8.
 int low_memory_interval(int T, int K);
