@@ -105,6 +105,7 @@ struct Params {
     double *alocY;      // [nslot][Delta]
     double *bloc;       // [nslot][Delta][2C] backward rows (p_t, v_t) of the chunk-parallel backward tasks
     double *blocY;      // [nslot][Delta]     their scale relative to the interval's upper end
+    int bterms;         // the call has boundary terms among its inputs or outputs
     int marg;           // marginals from the stored rows of both scans (no recurrence in the interval stage)
     int msplit;         // parts per interval of the one-wave stored-row marginals; a sequence they handle has its partial
                         // sums per part (index interval*msplit + part), any other per interval (index interval)

@@ -359,6 +359,19 @@ __global__ __launch_bounds__(64 * interval_waves(CT, NKW)) void k_interval_wave(
     extern __shared__ double lds_raw[];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int K = p.K, C = p.C, KC = K * C, CC = C * C;
+    const int slot = blockIdx.x * IW + wave;
+    if (p.marg) {  // nearly always the stored-row marginals have done everything: no tables then
+        bool work = false;
+        for (int task = slot; task < p.B * p.N; task += gridDim.x * IW) {
+            const int b = task / p.N;
+            work = work || !(p.spec_ok[b * 2] && p.spec_ok[b * 2 + 1]);
+        }
+        if (ELDS || WLDS) {
+            if (!__syncthreads_or(work)) return;
+        } else if (!work) {
+            return;
+        }
+    }
     double *EtF = lds_raw;                        // [o][c] = Etr[o,c]   (forward:  z(c) = sum_o a(o) Etr[o,c])
     double *EtB = lds_raw + (ELDS ? CT * CT : 0);  // [o][c] = Etr[c,o]   (backward: b(c) = sum_o Etr[c,o] p(o))
     if (ELDS) {
@@ -387,7 +400,6 @@ __global__ __launch_bounds__(64 * interval_waves(CT, NKW)) void k_interval_wave(
     const bool cval = c < C;
     const int cc = cval ? c : 0;
     const bool writer = cval && g == 0;  // one lane per label
-    const int slot = blockIdx.x * IW + wave;
     double2 *aloc = (double2 *)p.aloc + (size_t)slot * Delta * C;
     double *alocY = p.alocY + (size_t)slot * Delta;
 

@@ -287,7 +287,20 @@ __global__ __launch_bounds__(NT) void k_mg_te(Params p)
 // positions; the transition statistics run on the matrix cores, four positions per v_mfma_f64_16x16x4; the
 // emission sums are running sums.  The rows of the next block are requested as soon as the current block's have
 // been turned into the few values the multiply-adds need.
-template <int CT, int NKW>
+// BT: calls with boundary terms.  The pair of a position is then no longer (E, 1/E), so the masses of the segments that
+// start and end there are formed with the reciprocals of its two factors, and go out as the gradients of the boundary
+// projections and, summed over the labels, as the boundary posterior.  (Genomic shape with all of them: 193 us, the interval
+// kernel's own recurrence 550 us.)
+template <int N>
+__device__ __forceinline__ double add_row_ror(const double v)  // v + the v of the lane N places on in its row of 16
+{
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    const int lo2 = __builtin_amdgcn_update_dpp(0, lo, 0x120 + N, 0xf, 0xf, true);
+    const int hi2 = __builtin_amdgcn_update_dpp(0, hi, 0x120 + N, 0xf, 0xf, true);
+    return v + __hiloint2double(hi2, lo2);
+}
+
+template <int CT, int NKW, bool BT>
 __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Params p)
 {
     using G = WaveWin<CT, NKW>;
@@ -446,6 +459,29 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
     const int rdoff = g * NK * RS + c;
     request(t);
     double kappa = kappa_of();
+    // mass (less kappa) of the segments of a label that start / end at a position: z p with z = q ES, and a b with b = v IE
+    auto recip0 = [](const double x) { return x > 1e-300 ? recip(x) : 0.0; };  // a forbidden start or end has mass 0
+    auto start_mass = [&](const double2 &a, const double2 &ev, const double2 &v) {
+        return BT ? a.y * recip0(ev.y) * v.x : a.y * ev.x * v.x;
+    };
+    auto end_mass = [&](const double2 &a, const double2 &ev, const double2 &v) {
+        return BT ? a.x * recip0(ev.x) * v.y : a.x * v.y * ev.y;
+    };
+    const double wb = BT && p.grad_logz ? (double)p.grad_logz[b] : 1.0;
+    // what a position gives the boundary outputs; on: it belongs to the block and the lane to a label
+    auto boundary = [&](const int tt, const double out, const double in, const bool on) {
+        if (!BT) return;
+        if (p.g_proj_start && on) p.g_proj_start[((size_t)b * p.T + tt) * C + c] = (float)(wb * out);
+        if (p.g_proj_end && on && tt >= 1) p.g_proj_end[((size_t)b * p.T + tt - 1) * C + c] = (float)(wb * in);
+        if (p.bdy_post) {  // posterior of a boundary: total mass of the segments that end there
+            double s = on && (SPLIT ? (lane & 31) : lane) < CTP ? in : 0.0;
+            s = add_row_ror<1>(add_row_ror<2>(add_row_ror<4>(add_row_ror<8>(s))));
+            s = add_across_16(s);
+            if (!SPLIT) s = add_across_32(s);
+            if (on && tt >= 1 && (SPLIT ? (lane & 31) : lane) == 0) p.bdy_post[(size_t)b * (p.T + 1) + tt] = (float)s;
+        }
+        if (tt == 0 && on) p.out0[(size_t)b * C + c] = out;
+    };
     float *const gseq = p.grad_emis + ((size_t)b * p.T) * C;
     while (t > ta) {
         const int nb = min(min(t - ta, MB), ((t - 1) & Jm) + 1);
@@ -469,7 +505,13 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
             for (int l = 0; l < NPL; ++l) {
                 both_halves(aq[l].y * kappa, coef[l], coef[NPL + l]);  // q_t(c) kappa of positions l and NPL + l
                 // a segment of this label starts at the position (z p, z = q ES) / ends at it (a b, b = v IE)
-                dl[l] = (aq[l].y * e[l].x * pv[l].x - aq[l].x * pv[l].y * e[l].y) * kappa;
+                if (BT) {
+                    const double out = start_mass(aq[l], e[l], pv[l]) * kappa, in = end_mass(aq[l], e[l], pv[l]) * kappa;
+                    boundary(t - 1 - pofs - l, out, in, cval);
+                    dl[l] = out - in;
+                } else {
+                    dl[l] = (start_mass(aq[l], e[l], pv[l]) - end_mass(aq[l], e[l], pv[l])) * kappa;
+                }
             }
             // durations 1..3 inside the block: this lane's v rows with the coefficients of the later positions
             // (lower half: positions 0, 1; upper half: 2, 3; the two halves are added up at the end)
@@ -504,7 +546,10 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
                 act[l] = pofs + l < nb;
                 both_halves((act[l] && cval) ? aq[l].y * kappa : 0.0, coef[l], coef[NPL + l]);
                 // none ends at position 0
-                dl[l] = act[l] ? (aq[l].y * e[l].x * pv[l].x - (tt >= 1 ? aq[l].x * pv[l].y * e[l].y : 0.0)) * kappa : 0.0;
+                const double out = act[l] ? start_mass(aq[l], e[l], pv[l]) * kappa : 0.0;
+                const double in = act[l] && tt >= 1 ? end_mass(aq[l], e[l], pv[l]) * kappa : 0.0;
+                boundary(tt, out, in, act[l] && cval);
+                dl[l] = out - in;
             }
             const bool lowh = pofs == 0;
             const double k13 = lowh ? coef[1] : coef[3], k2 = lowh ? coef[2] : 0.0, k3 = lowh ? coef[3] : 0.0;
@@ -537,7 +582,9 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
 #pragma unroll
                 for (int jn = 0; jn < i; ++jn) dn[i - 1 - jn] = fma(coef[i], pv[jn].y, dn[i - 1 - jn]);
                 rw[-i * RS] = pv[i].y;
-                const double d = (aq[i].y * e[i].x * pv[i].x - aq[i].x * pv[i].y * e[i].y) * kappa;
+                const double out = start_mass(aq[i], e[i], pv[i]) * kappa, in = end_mass(aq[i], e[i], pv[i]) * kappa;
+                boundary(t - 1 - i, out, in, cval);
+                const double d = out - in;
                 gp[-i * C] = (float)R;
                 sR += R;
                 R += d;
@@ -553,7 +600,10 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
                 for (int jn = 0; jn < i; ++jn) dn[i - 1 - jn] = fma(cg, pv[jn].y, dn[i - 1 - jn]);
                 double *rdst = (on && writer) ? ring + (r - 1 - i) * RS + c : ring + RTOT + lane;
                 *rdst = pv[i].y;
-                const double d = on ? (aq[i].y * e[i].x * pv[i].x - (tt >= 1 ? aq[i].x * pv[i].y * e[i].y : 0.0)) * kappa : 0.0;
+                const double out = on ? start_mass(aq[i], e[i], pv[i]) * kappa : 0.0;
+                const double in = on && tt >= 1 ? end_mass(aq[i], e[i], pv[i]) * kappa : 0.0;
+                boundary(tt, out, in, on && cval);
+                const double d = out - in;
                 float *dst = (on && writer) ? gout + (unsigned)tt * (unsigned)C : sink;
                 *dst = (float)R;
                 sR += on ? R : 0.0;

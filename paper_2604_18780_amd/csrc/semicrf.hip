@@ -333,10 +333,18 @@ int launch_mg_k(const Params &p, hipStream_t st)
 {
     const size_t lds = (wave_lds_doubles(CT, NKW) + 64) * sizeof(double);
     if (lds > LDS_LIMIT) return SEMICRF_EUNSUPPORTED;
-    if (hipFuncSetAttribute((const void *)k_mg_wave<CT, NKW>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    const dim3 grid(p.B * p.N * p.msplit);
+    if (p.bterms) {
+        if (hipFuncSetAttribute((const void *)k_mg_wave<CT, NKW, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)lds) != hipSuccess)
+            return SEMICRF_ELAUNCH;
+        hipLaunchKernelGGL((k_mg_wave<CT, NKW, true>), grid, dim3(64), lds, st, p);
+        return SEMICRF_OK;
+    }
+    if (hipFuncSetAttribute((const void *)k_mg_wave<CT, NKW, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds) != hipSuccess)
         return SEMICRF_ELAUNCH;
-    hipLaunchKernelGGL((k_mg_wave<CT, NKW>), dim3(p.B * p.N * p.msplit), dim3(64), lds, st, p);
+    hipLaunchKernelGGL((k_mg_wave<CT, NKW, false>), grid, dim3(64), lds, st, p);
     return SEMICRF_OK;
 }
 
@@ -387,13 +395,12 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
     p.spec = p.spec && mode != 0 && spec_applies(p.K, p.C);
     p.mscan = p.mscan && p.spec;
     p.fuse = p.spec && mode == 2 && (size_t)p.B * pl.N <= (size_t)pl.nslot;  // one slot per task
-    // Marginals from the stored rows of both scans: where the plan has the row slots and no
-    // boundary-term output is asked for (those come from the interval kernels).
-    // Their emission sums are formed from the stored pairs with ES * (1/ES) = 1, which start / end projections
-    // break; calls with boundary inputs or outputs go through the one-wave interval kernel.
-    const bool bterms = p.proj_start || p.proj_end || p.pi_start || p.pi_end || p.g_proj_start || p.g_proj_end ||
-                        p.g_pi_start || p.g_pi_end || p.bdy_post;
-    p.marg = pl.rows && p.fuse && !bterms;
+    // Marginals from the stored rows of both scans: where the plan has the row slots.  For K >= 128 their emission sums
+    // are formed from the stored pairs with ES * (1/ES) = 1, which start / end projections break, and no kernel has the
+    // boundary outputs: calls with boundary inputs or outputs go through the one-wave interval kernel there.
+    p.bterms = p.proj_start || p.proj_end || p.pi_start || p.pi_end || p.g_proj_start || p.g_proj_end ||
+               p.g_pi_start || p.g_pi_end || p.bdy_post;
+    p.marg = pl.rows && p.fuse && (!p.bterms || p.K < 128);
     if (p.K < 128 && ((double)p.T + 1.0) * (double)p.C >= 2147483648.0)
         p.marg = 0;  // the one-wave kernel indexes a sequence's rows with 32 bits
     // (the partial-sum arrays are planned for N * pl.msplit either way; a part holds at least K positions)
