@@ -80,8 +80,8 @@ __device__ __forceinline__ void fin_seq_body(const Params &p, const int b, const
     // kernels wrote positions 1 .. L-1)
     if (p.bdy_post && s == 0) {
         float *bd = p.bdy_post + (size_t)b * (p.T + 1);
-        for (int t = tid; t <= p.T; t += NT)
-            if (t == 0 || t >= L) bd[t] = (t == 0 || t == L) ? 1.f : 0.f;
+        if (tid == 0) bd[0] = 1.f;
+        for (int t = max(L, 1) + tid; t <= p.T; t += NT) bd[t] = t == L ? 1.f : 0.f;
     }
 }
 
@@ -104,7 +104,7 @@ __device__ __forceinline__ void fin_pi_body(const Params &p)
 
 // grad_emis / pos_marg, elementwise over (u,c) of one sequence.  grid (blocks, B).
 // V = 4: four labels of one position per thread as 16-byte accesses (C a multiple of 4, outputs 16-byte aligned,
-// fewer than 2^31 elements per sequence, no boundary projections among the outputs); V = 1: the general form.
+// fewer than 2^31 elements per sequence); V = 1: the general form.
 template <int V>
 __global__ __launch_bounds__(NT) void k_fin_emis(Params p)
 {
@@ -140,6 +140,18 @@ __global__ __launch_bounds__(NT) void k_fin_emis(Params p)
             }
             ge4[q] = ge;
             if (pm4) pm4[q] = pmv;
+            if ((int)u >= L - 1) {  // boundary projections, as below
+                const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (p.g_proj_start && (int)u >= L) ((float4 *)(p.g_proj_start + base))[q] = zero;
+                if (p.g_proj_end) {
+                    float4 x = zero;
+                    if ((int)u == L - 1) {
+                        const double *in = p.inL + (size_t)b * C + c;
+                        x = make_float4((float)(w * in[0]), (float)(w * in[1]), (float)(w * in[2]), (float)(w * in[3]));
+                    }
+                    ((float4 *)(p.g_proj_end + base))[q] = x;
+                }
+            }
         }
         return;
     }
@@ -175,8 +187,9 @@ __global__ __launch_bounds__(NT) void k_fin_emis(Params p)
 inline void launch_fin_emis(const Params &p, hipStream_t st)
 {
     const size_t n = (size_t)p.T * p.C;
-    const bool vec = p.C % 4 == 0 && n < ((size_t)1 << 31) && !p.g_proj_start && !p.g_proj_end &&
-                     ((uintptr_t)p.grad_emis & 15) == 0 && ((uintptr_t)p.pos_marg & 15) == 0;
+    const bool vec = p.C % 4 == 0 && n < ((size_t)1 << 31) &&
+                     (((uintptr_t)p.grad_emis | (uintptr_t)p.pos_marg | (uintptr_t)p.g_proj_start |
+                       (uintptr_t)p.g_proj_end) & 15) == 0;
     size_t blocks = ((vec ? n / 4 : n) + NT - 1) / NT;
     if (blocks > 16384) blocks = 16384;
     if (vec) hipLaunchKernelGGL(k_fin_emis<4>, dim3((unsigned)blocks, p.B), dim3(NT), 0, st, p);
@@ -185,12 +198,12 @@ inline void launch_fin_emis(const Params &p, hipStream_t st)
 
 // grad_trans[c',c] = Etr[c',c] * sum_b w_b sum_i partTr;  grad_dur[k,c] = sum_b w_b sum_i partD.
 // One workgroup per FIN_PO outputs; its NT / FIN_PO thread groups take the partial sums of all sequences in turn and
-// their sums are combined in group order (fixed order for a given problem).  Eight of a group's partial sums are
-// requested before the first is added: taken sequence by sequence, a batch of short ones (16 partial sums for 32 groups
+// their sums are combined in group order (fixed order for a given problem).  Sixteen of a group's partial sums are
+// requested before the first is added: taken sequence by sequence, a batch of short ones (16 partial sums for 64 groups
 // each) cost a memory latency per four sequences with half of the groups idle, 30 us for B = 64, T = 256.
 // Outputs are dealt so that neighbouring ones, which share lines, fall to workgroups of one chiplet (blocks go round the
 // eight of them).
-constexpr int FIN_PO = 8;  // small: the partial sums of a long sequence are many, the outputs few
+constexpr int FIN_PO = 4;  // small: the partial sums of a long sequence are many, the outputs few
 inline __host__ __device__ int fin_param_blocks(const int K, const int C)
 {
     return ((C * C + K * C + FIN_PO - 1) / FIN_PO + 7) & ~7;
@@ -198,7 +211,7 @@ inline __host__ __device__ int fin_param_blocks(const int K, const int C)
 __device__ __forceinline__ void fin_params_body(const Params &p, const int blk)
 {
     __shared__ double red[NT];
-    constexpr int NG = NT / FIN_PO, UB = 8;
+    constexpr int NG = NT / FIN_PO, UB = 16;
     const int C = p.C, CC = C * C, KC = p.K * C, N = p.NP, tid = threadIdx.x;
     const int o = tid % FIN_PO, g = tid / FIN_PO;
     const int idx = ((blk & 7) * (fin_param_blocks(p.K, C) >> 3) + (blk >> 3)) * FIN_PO + o;
