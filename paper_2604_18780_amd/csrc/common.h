@@ -20,11 +20,15 @@ namespace semicrf_impl {
 constexpr double LN2 = 0.6931471805599453094;
 constexpr double LOG2E = 1.4426950408889634074;
 constexpr double RANGE_NATS = 300.0;  // per-position growth that is supported (2x this < ln DBL_MAX)
-// Growth allowed inside one scaling block, the pair of a message and the prefix factor together: what is kept stays
-// below e^600 < DBL_MAX = e^709, and a product of two such values always has the tiny factor exp((Y + Y') ln2 - logZ)
-// multiplied in first.  Longer blocks mean fewer rescalings of the window (at 300 the genomic shape had blocks of 8
-// positions, and its window was read and written once per 8 positions only to be scaled).
-constexpr double BLOCK_NATS = 600.0;
+// What a scaling block of J positions may reach, as a logarithm.  With r the most a position changes a message by and E the
+// furthest the centred prefix sum of a label gets from its value at the block's first position:
+//   a message of one scan, or the product of a forward and a backward one    e^((J + 1) r)   (each is 1 in sum at its end
+//                                                                             of the block; both together cross it once)
+//   the same times a prefix factor ES or 1/ES (q, v, a v, q exp(Y + Y'))      e^((J + 1) r + E)
+// and no kernel forms anything larger, so that stays below ln DBL_MAX = 709.8 (and above ln DBL_MIN = -708.4).
+// E is at most (J - 1) max|f - nu|, but with noisy scores far less: k_colsum measures it (genomic shape, J = 32: 96 nats
+// measured, 212 by the bound, next to 33 r = 488; the window is read and written once per block only to be scaled).
+constexpr double BLOCK_NATS = 690.0;
 
 struct SeqHdr {
     int L;          // clamped length
@@ -59,7 +63,7 @@ struct Params {
     SeqHdr *hdr;        // [B]
     double *nu;         // [B][C]
     double *chsum;      // [B][NCH][C] chunk sums, then exclusive chunk offsets
-    double *chmax;      // [B][NCH]
+    float2 *chmax;      // [B][NCH] .x = largest |f| (boundary terms added), .y = largest excursion (see k_colsum)
     double *tabmax;     // [ntab][2]: max dur, max trans of each table workgroup's share
     double logKC;       // log(K * C)
     int ntab;           // workgroups that build the tables

@@ -227,7 +227,7 @@ __global__ __launch_bounds__(NT) void k_mg_te(Params p)
                         ak = fa.x * kap;
                         pp = fb.x;
                         // a segment of label o starts at t (z_t p_t, z = q ES) / ends at t (a_t b_t, b = v IE; none ends at 0)
-                        d = (fa.y * e.x * fb.x - (t >= 1 ? fa.x * fb.y * e.y : 0.0)) * kap;
+                        d = fa.y * kap * e.x * fb.x - (t >= 1 ? ak * fb.y * e.y : 0.0);
                     }
                     AK[r * C + o] = ak;
                     P[r * C + o] = pp;
@@ -459,13 +459,14 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
     const int rdoff = g * NK * RS + c;
     request(t);
     double kappa = kappa_of();
-    // mass (less kappa) of the segments of a label that start / end at a position: z p with z = q ES, and a b with b = v IE
+    // mass of the segments of a label that start / end at a position: z p kappa with z = q ES, and a b kappa with b = v IE
+    // (no factor in these orders exceeds what BLOCK_NATS allows)
     auto recip0 = [](const double x) { return x > 1e-300 ? recip(x) : 0.0; };  // a forbidden start or end has mass 0
     auto start_mass = [&](const double2 &a, const double2 &ev, const double2 &v) {
-        return BT ? a.y * recip0(ev.y) * v.x : a.y * ev.x * v.x;
+        return BT ? a.y * recip0(ev.y) * v.x * kappa : a.y * kappa * ev.x * v.x;
     };
     auto end_mass = [&](const double2 &a, const double2 &ev, const double2 &v) {
-        return BT ? a.x * recip0(ev.x) * v.y : a.x * v.y * ev.y;
+        return BT ? a.x * recip0(ev.x) * v.y * kappa : a.x * kappa * v.y * ev.y;
     };
     const double wb = BT && p.grad_logz ? (double)p.grad_logz[b] : 1.0;
     // what a position gives the boundary outputs; on: it belongs to the block and the lane to a label
@@ -506,11 +507,11 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
                 both_halves(aq[l].y * kappa, coef[l], coef[NPL + l]);  // q_t(c) kappa of positions l and NPL + l
                 // a segment of this label starts at the position (z p, z = q ES) / ends at it (a b, b = v IE)
                 if (BT) {
-                    const double out = start_mass(aq[l], e[l], pv[l]) * kappa, in = end_mass(aq[l], e[l], pv[l]) * kappa;
+                    const double out = start_mass(aq[l], e[l], pv[l]), in = end_mass(aq[l], e[l], pv[l]);
                     boundary(t - 1 - pofs - l, out, in, cval);
                     dl[l] = out - in;
                 } else {
-                    dl[l] = (start_mass(aq[l], e[l], pv[l]) - end_mass(aq[l], e[l], pv[l])) * kappa;
+                    dl[l] = start_mass(aq[l], e[l], pv[l]) - end_mass(aq[l], e[l], pv[l]);
                 }
             }
             // durations 1..3 inside the block: this lane's v rows with the coefficients of the later positions
@@ -546,8 +547,8 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
                 act[l] = pofs + l < nb;
                 both_halves((act[l] && cval) ? aq[l].y * kappa : 0.0, coef[l], coef[NPL + l]);
                 // none ends at position 0
-                const double out = act[l] ? start_mass(aq[l], e[l], pv[l]) * kappa : 0.0;
-                const double in = act[l] && tt >= 1 ? end_mass(aq[l], e[l], pv[l]) * kappa : 0.0;
+                const double out = act[l] ? start_mass(aq[l], e[l], pv[l]) : 0.0;
+                const double in = act[l] && tt >= 1 ? end_mass(aq[l], e[l], pv[l]) : 0.0;
                 boundary(tt, out, in, act[l] && cval);
                 dl[l] = out - in;
             }
@@ -582,7 +583,7 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
 #pragma unroll
                 for (int jn = 0; jn < i; ++jn) dn[i - 1 - jn] = fma(coef[i], pv[jn].y, dn[i - 1 - jn]);
                 rw[-i * RS] = pv[i].y;
-                const double out = start_mass(aq[i], e[i], pv[i]) * kappa, in = end_mass(aq[i], e[i], pv[i]) * kappa;
+                const double out = start_mass(aq[i], e[i], pv[i]), in = end_mass(aq[i], e[i], pv[i]);
                 boundary(t - 1 - i, out, in, cval);
                 const double d = out - in;
                 gp[-i * C] = (float)R;
@@ -600,8 +601,8 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
                 for (int jn = 0; jn < i; ++jn) dn[i - 1 - jn] = fma(cg, pv[jn].y, dn[i - 1 - jn]);
                 double *rdst = (on && writer) ? ring + (r - 1 - i) * RS + c : ring + RTOT + lane;
                 *rdst = pv[i].y;
-                const double out = on ? start_mass(aq[i], e[i], pv[i]) * kappa : 0.0;
-                const double in = on && tt >= 1 ? end_mass(aq[i], e[i], pv[i]) * kappa : 0.0;
+                const double out = on ? start_mass(aq[i], e[i], pv[i]) : 0.0;
+                const double in = on && tt >= 1 ? end_mass(aq[i], e[i], pv[i]) : 0.0;
                 boundary(tt, out, in, on && cval);
                 const double d = out - in;
                 float *dst = (on && writer) ? gout + (unsigned)tt * (unsigned)C : sink;

@@ -58,33 +58,64 @@ __device__ __forceinline__ void tables_body(const Params &p, const int blk)
 }
 
 // ---------------------------------------------------------------------------
-// Eq. 1, stage 1: per-chunk column sums (fp64) and |f| maxima.  grid (NCH, B).
+// Eq. 1, stage 1: per-chunk column sums (fp64) and what bounds the growth inside a scaling block.  grid (NCH, B).
+// An item is (32 positions, label), labels fastest: 32 loads in flight, and the running sum along the positions gives the
+// furthest that the prefix sum of a label gets from its value at the first of them (JMAX = 32 is the longest block; a
+// shorter one lies inside such a group).  The baseline nu is not known yet: it moves that by at most 31 |nu|.
+// Bound by the latency of its loads: 9.3 us with rows dealt out over the threads (eight loads in flight, no excursions),
+// 7.0 us so (B = 32, T = 2000, C = 64, bfloat16); C = 24 leaves 64 of 256 threads idle, 26.8 -> 30.2 us at 4 x 100 000 with
+// projections.
 // ---------------------------------------------------------------------------
+constexpr int COL_NG = PREP_CH / JMAX;
+
+// the smallest float that is not below x >= 0 (two bounds of a chunk in the place of one double)
+__device__ __forceinline__ float float_above(const double x)
+{
+    const float q = (float)x;
+    return (double)q < x ? nextafterf(q, INFINITY) : q;
+}
+
 template <int ET>
 __device__ __forceinline__ void colsum_body(const Params &p, const int b, const int ch)
 {
-    __shared__ double red[NT];
-    __shared__ double redm[2 * (NT / 64)];
+    __shared__ double red[COL_NG * 256];  // C <= 256
+    __shared__ double redm[NT / 64], redx[NT / 64];
+    __shared__ float reds[NT / 64], rede[NT / 64];
     const int tid = threadIdx.x;
     const int C = p.C, L = seq_len(p, b);
     const int u0 = ch * PREP_CH;
     const int u1 = min(u0 + PREP_CH, L);
-    const int R = NT / C;  // rows handled per pass
-    const int r = tid / C, c = tid % C;
-    double acc = 0.0, mx = 0.0;
-    if (r < R) {
-        const size_t f0 = ((size_t)b * p.T) * C;
-#pragma unroll 8
-        for (int u = u0 + r; u < u1; u += R) {
-            double v = emis_at<ET>(p, f0 + (size_t)u * C + c);
-            acc += v;
-            mx = fmax(mx, fabs(v));
+    double mx = 0.0, ex = 0.0;
+    for (int it = tid; it < COL_NG * C; it += NT) {
+        const int t0 = u0 + it / C * JMAX, n = min(L - t0, JMAX);
+        const size_t o = ((size_t)b * p.T + t0) * C + it % C;
+        double f[JMAX];
+        if (n == JMAX) {
+#pragma unroll
+            for (int i = 0; i < JMAX; ++i) f[i] = emis_at<ET>(p, o + (unsigned)(i * C));
+        } else if (n > 0) {  // the sequence's last: rows beyond its end are replaced by its last one, so that nothing waits in a branch
+#pragma unroll
+            for (int i = 0; i < JMAX; ++i) {
+                const double v = emis_at<ET>(p, o + (unsigned)(min(i, n - 1) * C));
+                f[i] = i < n ? v : 0.0;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < JMAX; ++i) f[i] = 0.0;
         }
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < JMAX; ++i) {
+            mx = fmax(mx, fabs(f[i]));
+            s += f[i];
+            if (i < JMAX - 1) ex = fmax(ex, fabs(s));
+        }
+        red[it] = s;
     }
     // the boundary projections move a message like an emission does: their maxima are added
-    float mps = 0.f, mpe = 0.f;
     auto absmax = [&](const float *a) {
         float m = 0.f;
+        const int R = NT / C, r = tid / C, c = tid % C;  // rows handled per pass
         if (a && r < R) {
             a += ((size_t)b * p.T) * C + c;
 #pragma unroll 8
@@ -92,33 +123,36 @@ __device__ __forceinline__ void colsum_body(const Params &p, const int b, const 
         }
         return m;
     };
-    mps = absmax(p.proj_start);
-    mpe = absmax(p.proj_end);
-    // the maxima first inside each wave (threads that took no row hold zeros; a maximum does not care for order)
-    double mp = (double)mps + (double)mpe;
+    float mps = absmax(p.proj_start), mpe = absmax(p.proj_end);
+    // the maxima first inside each wave (a maximum does not care for order)
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         mx = fmax(mx, __shfl_xor(mx, off));
-        mp = fmax(mp, __shfl_xor(mp, off));
+        ex = fmax(ex, __shfl_xor(ex, off));
+        mps = fmaxf(mps, __shfl_xor(mps, off));
+        mpe = fmaxf(mpe, __shfl_xor(mpe, off));
     }
-    red[tid] = acc;
     if ((tid & 63) == 0) {
         redm[tid >> 6] = mx;
-        redm[NT / 64 + (tid >> 6)] = mp;
+        redx[tid >> 6] = ex;
+        reds[tid >> 6] = mps;
+        rede[tid >> 6] = mpe;
     }
     __syncthreads();
     if (tid < C) {
         double s = 0.0;
-        for (int i = 0; i < R; ++i) s += red[i * C + tid];
+#pragma unroll
+        for (int i = 0; i < COL_NG; ++i) s += red[i * C + tid];
         p.chsum[((size_t)b * p.NCH + ch) * C + tid] = s;
     }
     if (tid == 0) {
-        double m = 0.0, q = 0.0;
-        for (int i = 0; i < NT / 64; ++i) {
-            m = fmax(m, redm[i]);
-            q = fmax(q, redm[NT / 64 + i]);
+        for (int i = 1; i < NT / 64; ++i) {
+            mx = fmax(mx, redm[i]);
+            ex = fmax(ex, redx[i]);
+            mps = fmaxf(mps, reds[i]);
+            mpe = fmaxf(mpe, rede[i]);
         }
-        p.chmax[(size_t)b * p.NCH + ch] = m + 2.0 * q;  // |start| + |end| bounded by twice the larger sum
+        p.chmax[(size_t)b * p.NCH + ch] = make_float2(float_above(mx + (double)mps + (double)mpe), float_above(ex));
     }
 }
 
@@ -135,8 +169,9 @@ __global__ __launch_bounds__(NT) void k_colsum(Params p)
 }
 
 // Scaling block length J and the range flag of a sequence: fm = max |f - nu| over its positions and labels, boundary
-// terms included.  tabmax: the maxima of the p.ntab table workgroups.
-__device__ __forceinline__ SeqHdr seq_header(const Params &p, const int L, const double fm)
+// terms included; ex = largest excursion of the sums of f inside JMAX aligned positions, nm = max |nu|.  tabmax: the maxima of the
+// p.ntab table workgroups.
+__device__ __forceinline__ SeqHdr seq_header(const Params &p, const int L, const double fm, const double ex, const double nm)
 {
     double dmax = p.tabmax[0], tmax = p.tabmax[1];
     for (int i = 1; i < p.ntab; ++i) {
@@ -148,7 +183,15 @@ __device__ __forceinline__ SeqHdr seq_header(const Params &p, const int L, const
     double r = fmax(fmax(grow, shrink), 1e-9);
     int J = 1, flags = 0;
     if (!(r <= RANGE_NATS)) flags = 1;  // also catches NaN
-    while (J < JMAX && (double)(2 * J) * r <= BLOCK_NATS) J *= 2;
+    // excursion of the centred sums inside JMAX aligned positions; between two positions of a shorter block it can be
+    // twice that.  A boundary term is part of the pair of its position.
+    const double exc = ex + (double)(JMAX - 1) * nm;
+    const double term = (p.proj_start || p.proj_end || p.pi_start || p.pi_end) ? fm : 0.0;
+    for (int n = 2; n <= JMAX; n *= 2) {
+        const double E = fmin((double)(n - 1) * fm, n == JMAX ? exc : 2.0 * exc) + term;
+        if (!((double)(n + 1) * r + E <= BLOCK_NATS)) break;
+        J = n;
+    }
     SeqHdr h;
     h.L = L; h.J = J; h.flags = flags; h.pad = 0; h.logZ = 0.0; h.logZb = 0.0;
     return h;
@@ -164,7 +207,7 @@ __global__ __launch_bounds__(PREP_NT) void k_prep_seq(Params p)
     // The chunks are split into G = PREP_NT/C contiguous ranges, one per thread group; range sums
     // are combined in range order (a fixed order for a given problem).
     __shared__ double gsum[PREP_NT];
-    __shared__ double red[PREP_NT / 64];
+    __shared__ double red[PREP_NT / 64], redx[PREP_NT / 64];
     __shared__ double nu_s[256];  // C <= 256
     const int b = blockIdx.x, tid = threadIdx.x;
     const int C = p.C, L = seq_len(p, b), NCH = p.NCH;
@@ -201,24 +244,36 @@ __global__ __launch_bounds__(PREP_NT) void k_prep_seq(Params p)
             pref += sum;
         }
     }
-    // bound on |f - nu|
-    double fm = 0.0;
+    // bounds on |f - nu| and on the excursions
+    double fm = 0.0, ex = 0.0;
 #pragma unroll 4
-    for (int ch = tid; ch < NCH; ch += PREP_NT) fm = fmax(fm, p.chmax[(size_t)b * NCH + ch]);
+    for (int ch = tid; ch < NCH; ch += PREP_NT) {
+        const float2 m = p.chmax[(size_t)b * NCH + ch];
+        fm = fmax(fm, (double)m.x);
+        ex = fmax(ex, (double)m.y);
+    }
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) fm = fmax(fm, __shfl_xor(fm, off));  // a maximum: any order
-    if ((tid & 63) == 0) red[tid >> 6] = fm;
+    for (int off = 1; off < 64; off <<= 1) {  // maxima: any order
+        fm = fmax(fm, __shfl_xor(fm, off));
+        ex = fmax(ex, __shfl_xor(ex, off));
+    }
+    if ((tid & 63) == 0) {
+        red[tid >> 6] = fm;
+        redx[tid >> 6] = ex;
+    }
     __syncthreads();
     if (tid == 0) {
-        fm = 0.0;
-        for (int i = 0; i < PREP_NT / 64; ++i) fm = fmax(fm, red[i]);
+        for (int i = 0; i < PREP_NT / 64; ++i) {
+            fm = fmax(fm, red[i]);
+            ex = fmax(ex, redx[i]);
+        }
         double nm = 0.0, npi = 0.0;
         for (int i = 0; i < C; ++i) {
             nm = fmax(nm, fabs(nu_s[i]));
             if (p.pi_start) npi = fmax(npi, fabs((double)p.pi_start[i]));
             if (p.pi_end) npi = fmax(npi, fabs((double)p.pi_end[i]));
         }
-        p.hdr[b] = seq_header(p, L, fm + nm + 2.0 * npi);
+        p.hdr[b] = seq_header(p, L, fm + nm + 2.0 * npi, ex, nm);
     }
 }
 
@@ -279,7 +334,7 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
 {
     extern __shared__ double lds_raw[];  // [PREP_NSEG][C] segment sums, then starts; INLINE: + [C] nu
     __shared__ double red2[2 * NT];
-    __shared__ double redm[NT / 64];
+    __shared__ double redm[NT / 64], redx[NT / 64];
     __shared__ SeqHdr hs;
     const int b = blockIdx.y, ch = blockIdx.x, tid = threadIdx.x;
     const int C = p.C, NCH = p.NCH;
@@ -299,8 +354,12 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
                 pre += i < ch ? v : 0.0;
             }
         }
-        double fm = 0.0;
-        for (int i = tid; i < NCH; i += NT) fm = fmax(fm, p.chmax[(size_t)b * NCH + i]);
+        double fm = 0.0, ex = 0.0;
+        for (int i = tid; i < NCH; i += NT) {
+            const float2 m = p.chmax[(size_t)b * NCH + i];
+            fm = fmax(fm, (double)m.x);
+            ex = fmax(ex, (double)m.y);
+        }
         red2[tid] = tot;
         red2[NT + tid] = pre;
         __syncthreads();
@@ -317,7 +376,7 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
             if (ch == 0) p.nu[(size_t)b * C + tid] = nu;
             nm = fabs(nu);
         }
-        // maxima of |f|, of |nu| and of the scalar boundaries: inside each wave by shuffles, then over the waves
+        // maxima of |f|, of the excursions, of |nu| and of the scalar boundaries: inside each wave by shuffles, then over the waves
         double npi = 0.0;
         if (BTERMS && tid < C) {
             if (p.pi_start) npi = fabs((double)p.pi_start[tid]);
@@ -326,12 +385,14 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
             fm = fmax(fm, __shfl_xor(fm, o));
+            ex = fmax(ex, __shfl_xor(ex, o));
             nm = fmax(nm, __shfl_xor(nm, o));
             if (BTERMS) npi = fmax(npi, __shfl_xor(npi, o));
         }
         __syncthreads();
         if ((tid & 63) == 0) {
             redm[tid >> 6] = fm;
+            redx[tid >> 6] = ex;
             red2[tid >> 6] = nm;
             red2[NT + (tid >> 6)] = npi;
         }
@@ -339,10 +400,11 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
         if (tid == 0) {
             for (int i = 0; i < NT / 64; ++i) {
                 fm = fmax(fm, redm[i]);
+                ex = fmax(ex, redx[i]);
                 nm = fmax(nm, red2[i]);
                 npi = fmax(npi, red2[NT + i]);
             }
-            hs = seq_header(p, L, fm + nm + 2.0 * npi);
+            hs = seq_header(p, L, fm + nm + 2.0 * npi, ex, nm);
             if (ch == 0) p.hdr[b] = hs;
         }
     } else {

@@ -81,7 +81,7 @@ void bind_workspace(Params &p, const Plan &pl, void *ws)
     p.hdr = (SeqHdr *)(w + pl.off[0]);
     p.nu = (double *)(w + pl.off[1]);
     p.chsum = (double *)(w + pl.off[2]);
-    p.chmax = (double *)(w + pl.off[3]);
+    p.chmax = (float2 *)(w + pl.off[3]);
     p.tabmax = (double *)(w + pl.off[4]);
     p.W = (double *)(w + pl.off[5]);
     p.Etr = (double *)(w + pl.off[6]);
