@@ -91,7 +91,8 @@ struct Params {
     int *vbest;         // [B] Viterbi: label of the last segment
     int *vbp;           // [B][T+1][C] Viterbi back-pointers: (duration << 8) | predecessor label
     int *vpar[2];       // [B][T+1][C] parent node (position * C + label) and its doublings (ping-pong)
-    int2 *vpiece;       // [B][pieces] nodes by which the path enters a piece of the trace-back and leaves it
+    int4 *vtile[2];     // [B][tiles] what the first pass and the retry of the trace-back left of a tile: nodes by which the
+                        // path enters and leaves it, start of the segment it leaves by, segments that start in it
     unsigned char *vmark;  // [B][T+1][C] 1: the node lies on the best path
     float *vscore;      // Viterbi outputs
     int32_t *vlabels, *vstarts, *vnseg;

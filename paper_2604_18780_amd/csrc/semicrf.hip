@@ -457,10 +457,10 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
     return check_launch();
 }
 
-// Viterbi workspace beyond the prefix-stage plan: (V, r) pairs, best final labels, back-pointers,
-// two pointer arrays, the trace-back's pieces and the path marks.
+// Viterbi workspace beyond the prefix-stage plan: V and r, best final labels, then what the trace-back needs: the records
+// of its tiles, or (SEMICRF_VITERBI_GLOBAL_TRACE) back-pointers, two pointer arrays and the path marks in the same place.
 struct VitLayout {
-    size_t vr, vbest, vbp, vpar0, vpar1, vpiece, vmark, total;
+    size_t vr, vbest, tile0, tile1, vbp, vpar0, vpar1, vmark, total;
 };
 
 VitLayout viterbi_layout(int B, int T, int C)
@@ -470,12 +470,15 @@ VitLayout viterbi_layout(int B, int T, int C)
     size_t off = 0;
     l.vr = off; off += align_up(nodes * sizeof(double2));
     l.vbest = off; off += align_up((size_t)B * sizeof(int));
+    const size_t tiles = (size_t)B * (((size_t)T + VT_TILE_MIN - 1) / VT_TILE_MIN);
+    l.tile0 = off;
+    l.tile1 = off + align_up(tiles * sizeof(int4));
+    const size_t end = l.tile1 + align_up(tiles * sizeof(int4));
     l.vbp = off; off += align_up(nodes * sizeof(int));
     l.vpar0 = off; off += align_up(nodes * sizeof(int));
     l.vpar1 = off; off += align_up(nodes * sizeof(int));
-    l.vpiece = off; off += align_up(nodes * sizeof(int));
     l.vmark = off; off += align_up(nodes);
-    l.total = off;
+    l.total = off > end ? off : end;
     return l;
 }
 
@@ -544,7 +547,8 @@ int run_viterbi(Params p, void *workspace, size_t workspace_bytes, hipStream_t s
     p.vbp = (int *)(vw + vl.vbp);
     p.vpar[0] = (int *)(vw + vl.vpar0);
     p.vpar[1] = (int *)(vw + vl.vpar1);
-    p.vpiece = (int2 *)(vw + vl.vpiece);
+    p.vtile[0] = (int4 *)(vw + vl.tile0);
+    p.vtile[1] = (int4 *)(vw + vl.tile1);
     p.vmark = (unsigned char *)(vw + vl.vmark);
     p.logpair = 1;
     p.spec = p.spec ? 1 : 0;

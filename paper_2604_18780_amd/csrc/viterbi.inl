@@ -333,7 +333,10 @@ __global__ __launch_bounds__(64) void k_viterbi(Params p)
 //                 lanes per piece; tiles among each other are pieces again.  RETRY: the tiles that did not agree with the
 //                 tile above, from the node by which that one left.
 //   k_vit_settle  one workgroup per sequence: the tiles that do not even then, from the top down.
-// A tile writes its own tokens only, so a wrong path is overwritten where it was written.
+// A tile writes its own tokens only, so a wrong path is overwritten where it was written.  The retry reads the records of
+// the first pass and writes others (which the first pass has filled too, for the tiles with nothing to do): no workgroup
+// reads what another of its launch writes.  Where two records name the same node, they name the same path below it: the start of its segment
+// is a function of the node.
 // What bounds it: the instructions of the chain of a path's nodes (from global memory instead of LDS, two loads of ~1000
 // clocks per node: 208 us at the genomic shape), then the reading of V and r.  A row of 16 lanes has one path because maxima
 // along a row are cheap, and 24 labels or a few dozen durations do not fill a wave.
@@ -352,10 +355,11 @@ inline size_t vit_tile_lds(const int n, const int K, const int C)
     return ((size_t)C * vit_r_stride(n, K) + (size_t)(vit_tile_rows(n) + 1) * C + vit_tile_rows(n) + K + 1) * sizeof(double) +
            ((size_t)C * vit_row_floats(K) + (size_t)(C + 1) * vit_row_floats(C)) * sizeof(float);
 }
+constexpr int VT_TILE_MIN = 2 * VT_PIECES;  // fewest tokens of a tile
 inline int vit_piece_tokens(const int K, const int C)
 {
     int n = 8;
-    while (n > 2 && vit_tile_lds(n, K, C) > LDS_LIMIT / 2 - 1024) n >>= 1;
+    while (n > VT_TILE_MIN / VT_PIECES && vit_tile_lds(n, K, C) > LDS_LIMIT / 2 - 1024) n >>= 1;
     return n;
 }
 
@@ -489,7 +493,9 @@ struct VitTile {
 
 // Traces tile j of sequence b (at least one token of it lies in the sequence).  from: the node (t C + c) by which the tile
 // above left, and the position where its segment starts (-1: not known); from.x < 0: start at the warm-up's best node.
-__device__ __forceinline__ void vit_tile(const Params &p, VitTile &tile, const int b, const int j, const int n, const int2 from)
+// rec, also: where the tile's record goes.
+__device__ __forceinline__ void vit_tile(const Params &p, VitTile &tile, const int b, const int j, const int n, const int2 from,
+                                         int4 *rec, int4 *also)
 {
     __shared__ int in[VT_PIECES];
     __shared__ int2 out[VT_PIECES];
@@ -558,12 +564,7 @@ __device__ __forceinline__ void vit_tile(const Params &p, VitTile &tile, const i
     const int count = __popcll(__ballot(l < n && u < thi && st));
     if ((tid & 63) == 0 && count) atomicAdd(&starts, count);
     __syncthreads();
-    if (tid == 0) {
-        const size_t o = (size_t)b * ((T + n * VT_PIECES - 1) / (n * VT_PIECES)) + j;
-        p.vpiece[o] = make_int2(in[last], out[0].x);
-        p.vpar[0][o] = out[0].y;
-        p.vbp[o] = starts;
-    }
+    if (tid == 0) *rec = *also = make_int4(in[last], out[0].x, out[0].y, starts);
 }
 
 template <bool RETRY>
@@ -580,16 +581,17 @@ __global__ __launch_bounds__(VT_THREADS) void k_vit_trace(Params p, int n)
         }
         return;
     }
+    const size_t o = (size_t)b * gridDim.x + j;
     int2 from = make_int2(-1, -1);
     if (RETRY) {
         if (lo + nt >= L) return;
-        const size_t o = (size_t)b * gridDim.x + j;
-        from = make_int2(p.vpiece[o + 1].y, p.vpar[0][o + 1]);
-        if (p.vpiece[o].x == from.x) return;
+        const int4 mine = p.vtile[0][o], above = p.vtile[0][o + 1];
+        from = make_int2(above.y, above.z);
+        if (mine.x == from.x) return;
     }
     VitTile tile(p, lds_raw, n);
     tile.load_tables(p);
-    vit_tile(p, tile, b, j, n, from);
+    vit_tile(p, tile, b, j, n, from, p.vtile[1] + o, p.vtile[RETRY ? 1 : 0] + o);
 }
 
 __global__ __launch_bounds__(VT_THREADS) void k_vit_settle(Params p, int n)
@@ -598,22 +600,21 @@ __global__ __launch_bounds__(VT_THREADS) void k_vit_settle(Params p, int n)
     __shared__ int total[VT_THREADS / 64];
     const int b = blockIdx.x, tid = threadIdx.x, nt = n * VT_PIECES;
     const int npl = (p.hdr[b].L + nt - 1) / nt;
-    const size_t o = (size_t)b * ((p.T + nt - 1) / nt);
-    const int2 *piece = p.vpiece + o;  // (enters, leaves)
+    int4 *rec = p.vtile[1] + (size_t)b * ((p.T + nt - 1) / nt);
     int again = 0;
-    for (int j = tid; j < npl - 1; j += VT_THREADS) again |= piece[j].x != piece[j + 1].y;
+    for (int j = tid; j < npl - 1; j += VT_THREADS) again |= rec[j].x != rec[j + 1].y;
     if (__syncthreads_or(again)) {  // rarely
         VitTile tile(p, lds_raw, n);
         tile.load_tables(p);
         for (int j = npl - 2; j >= 0; --j) {
-            const int2 from = make_int2(piece[j + 1].y, p.vpar[0][o + j + 1]);
-            if (piece[j].x != from.x) vit_tile(p, tile, b, j, n, from);
+            const int2 from = make_int2(rec[j + 1].y, rec[j + 1].z);
+            if (rec[j].x != from.x) vit_tile(p, tile, b, j, n, from, rec + j, rec + j);
             __threadfence_block();
             __syncthreads();
         }
     }
     int cnt = 0;
-    for (int j = tid; j < npl; j += VT_THREADS) cnt += p.vbp[o + j];
+    for (int j = tid; j < npl; j += VT_THREADS) cnt += rec[j].w;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) cnt += __shfl_xor(cnt, off);
     if ((tid & 63) == 0) total[tid >> 6] = cnt;
