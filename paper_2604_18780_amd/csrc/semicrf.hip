@@ -523,6 +523,43 @@ int launch_viterbi_ct(const Params &p, hipStream_t st)
     return SEMICRF_EUNSUPPORTED;
 }
 
+// The trace-back in tiles.
+template <class SH>
+int launch_vit_trace_sh(const Params &p, hipStream_t st)
+{
+    const int n = vit_piece_tokens(p.K, p.C), nt = n * VT_PIECES;
+    const size_t lds = vit_tile_lds(n, p.K, p.C);
+    if (lds + 1024 > LDS_LIMIT ||
+        hipFuncSetAttribute((const void *)k_vit_trace<false, SH>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+            hipSuccess ||
+        hipFuncSetAttribute((const void *)k_vit_trace<true, SH>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+            hipSuccess ||
+        hipFuncSetAttribute((const void *)k_vit_settle<SH>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
+            hipSuccess)
+        return SEMICRF_ELAUNCH;
+    const dim3 grid((p.T + nt - 1) / nt, p.B);
+    hipLaunchKernelGGL((k_vit_trace<false, SH>), grid, dim3(VT_THREADS), lds, st, p, n);
+    hipLaunchKernelGGL((k_vit_trace<true, SH>), grid, dim3(VT_THREADS), lds, st, p, n);
+    hipLaunchKernelGGL((k_vit_settle<SH>), dim3(p.B), dim3(VT_THREADS), lds, st, p, n);
+    return check_launch();
+}
+
+template <int CU>
+int launch_vit_trace_cu(const Params &p, hipStream_t st)
+{
+    if (p.K <= 16) return launch_vit_trace_sh<VitShape<1, CU, false>>(p, st);
+    if (p.K <= 32) return launch_vit_trace_sh<VitShape<2, CU, false>>(p, st);
+    if (p.K <= 64) return launch_vit_trace_sh<VitShape<4, CU, false>>(p, st);
+    return launch_vit_trace_sh<VitShape<4, CU, true>>(p, st);
+}
+
+int launch_vit_trace(const Params &p, hipStream_t st)
+{
+    if (p.C <= 16) return launch_vit_trace_cu<1>(p, st);
+    if (p.C <= 32) return launch_vit_trace_cu<2>(p, st);
+    return launch_vit_trace_cu<4>(p, st);
+}
+
 // Viterbi: prefix stage with the log-domain pair, one scan wave per sequence, trace-back.
 int run_viterbi(Params p, void *workspace, size_t workspace_bytes, hipStream_t st)
 {
@@ -561,23 +598,7 @@ int run_viterbi(Params p, void *workspace, size_t workspace_bytes, hipStream_t s
     else if (C <= 32) rc = launch_viterbi_ct<32>(p, st);
     else rc = launch_viterbi_ct<64>(p, st);
     if (rc != SEMICRF_OK) return rc;
-    if (!p.vit_global) {
-        const int n = vit_piece_tokens(p.K, p.C), nt = n * VT_PIECES;
-        const size_t lds = vit_tile_lds(n, p.K, p.C);
-        if (lds + 1024 > LDS_LIMIT ||
-            hipFuncSetAttribute((const void *)k_vit_trace<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
-                hipSuccess ||
-            hipFuncSetAttribute((const void *)k_vit_trace<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
-                hipSuccess ||
-            hipFuncSetAttribute((const void *)k_vit_settle, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
-                hipSuccess)
-            return SEMICRF_ELAUNCH;
-        const dim3 grid((p.T + nt - 1) / nt, p.B);
-        hipLaunchKernelGGL(k_vit_trace<false>, grid, dim3(VT_THREADS), lds, st, p, n);
-        hipLaunchKernelGGL(k_vit_trace<true>, grid, dim3(VT_THREADS), lds, st, p, n);
-        hipLaunchKernelGGL(k_vit_settle, dim3(p.B), dim3(VT_THREADS), lds, st, p, n);
-        return check_launch();
-    }
+    if (!p.vit_global) return launch_vit_trace(p, st);
     {
         const size_t lds = 2 * (size_t)(p.K + VBP_TILE) * p.C * sizeof(double);  // checked before the first launch
         if (hipFuncSetAttribute((const void *)k_vit_bp, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=

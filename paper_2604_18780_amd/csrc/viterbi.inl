@@ -10,13 +10,36 @@
 // back-pointers are kept.  The trace-back (k_vit_trace) finds each segment's duration and
 // predecessor label by recomputing the candidates from the stored values.  Ties go to the
 // smallest duration, then the smallest label.
+//
+// Ties are structural (a run of one label longer than K can be cut into the same durations in any order), and equal sums
+// come out different in their last bits, so candidates within rounding of the best one are ties.  A stored value is a
+// sum with the prefix sum in it and off by a few units in the last place of the larger of the two, more where the scores
+// of two paths were added up over many segments before they meet; 2^-42 (1024 units) of |candidate| + |prefix sum| is
+// well above that and far below what single-precision scores differ by.  With an exact comparison 1 % of the
+// start flags depended on the order of additions (C = 3, K = 57), and so on how the scan was cut into intervals.
 // ---------------------------------------------------------------------------
+constexpr double VIT_TIE = 0x1p-42;
+
+// Candidate x ties with the best one where x + vit_slack(scale) >= vit_floor(best); scale: a value of about the size of the
+// prefix sums in x (ignored if infinite).  In two parts, so that only the second has to wait for the best one.
+__device__ __forceinline__ double vit_slack(const double scale)
+{
+    const double a = fabs(scale);
+    return VIT_TIE * (1.0 + (a < DBL_MAX ? a : 0.0));
+}
+__device__ __forceinline__ double vit_floor(const double best)
+{
+    const double m = fabs(best);
+    return m < DBL_MAX ? fma(-VIT_TIE, m, best) : best;
+}
+
 // Best final label (smallest on ties) and score: lane holds V_L of label c in v, in the lanes `own` (one per label).
 __device__ __forceinline__ void vit_best(const Params &p, const int b, const double v, const int c, const bool own,
                                          const double unit)
 {
     const double best = wave_max(own ? v : -INFINITY);
-    int bl = own && v == best ? c : 0x7fffffff;
+    const double sum = own ? p.EI[((size_t)b * (p.T + 1) + p.hdr[b].L) * p.C + c].x : 0.0;
+    int bl = own && (v + unit) + vit_slack(sum) >= vit_floor(best + unit) ? c : 0x7fffffff;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) bl = min(bl, __shfl_xor(bl, off));
     if ((threadIdx.x & 63) == 0) {
@@ -323,7 +346,7 @@ __global__ __launch_bounds__(64) void k_viterbi(Params p)
 // ---------------------------------------------------------------------------
 // Trace-back.  Node (t, c) = "a segment with label c ends at position t"; its duration is the smallest k that
 // maximises dur[k,c] + r_{t-k}(c), the label of the node before it (at t - k) the smallest c' that maximises
-// V_{t-k}(c') + trans[c',c].  Only nodes that a path runs through are looked at.
+// V_{t-k}(c') + trans[c',c] (both up to ties as above; V_t(c) and r_{t-k}(c') show how large the prefix sums are).  Only nodes that a path runs through are looked at.
 // Paths merge going back just as the scan's states do going forward, so a path is followed in pieces that are traced side
 // by side and verified against each other.  A piece of n tokens [lo, hi) follows a path from the best node a few positions
 // above hi down to lo; it came in by the lowest node at a position >= hi and leaves by the lowest at a position >= lo.
@@ -349,7 +372,7 @@ constexpr int VT_WARM = 4;  // warm-up of a piece inside its tile
 // the other follows its paths.  A tile's own warm-up is 4 n positions.
 inline __host__ __device__ int vit_tile_rows(const int n) { return VT_PIECES * n + 4 * n; }
 inline __host__ __device__ int vit_row_floats(const int n) { return ((n + 15) & ~15) + 1; }
-inline __host__ __device__ int vit_r_stride(const int n, const int K) { return (vit_tile_rows(n) + K) | 1; }
+inline __host__ __device__ int vit_r_stride(const int n, const int K) { return (vit_tile_rows(n) + K + 1) | 1; }  // max(lo - K, 0) .. top
 inline size_t vit_tile_lds(const int n, const int K, const int C)
 {
     return ((size_t)C * vit_r_stride(n, K) + (size_t)(vit_tile_rows(n) + 1) * C + vit_tile_rows(n) + K + 1) * sizeof(double) +
@@ -377,14 +400,6 @@ __device__ __forceinline__ int row16_min(int v)
     v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x124, 0xf, 0xf, true));
     v = min(v, __builtin_amdgcn_update_dpp(0, v, 0x122, 0xf, 0xf, true));
     return min(v, __builtin_amdgcn_update_dpp(0, v, 0x121, 0xf, 0xf, true));
-}
-
-// Smallest index with the largest value along a row of 16 lanes; lane l holds its best so far.  `none` if all are -infinity.
-__device__ __forceinline__ int row16_first(const double best, const int at, const int none)
-{
-    const double m = row16_max(best);
-    const int i = row16_min(best == m ? at : 0x7fffffff);
-    return m > -INFINITY ? i : none;
 }
 
 // A tile's share of V and r, and the tables: dur by label, then trans by the label it leads to and a row of zeros (rows
@@ -424,7 +439,7 @@ struct VitTile {
                 tr[c * cs + o] = o < C ? (c < C ? p.trans[(size_t)o * C + c] : 0.f) : -INFINITY;
         }
     }
-    // V of positions lo .. top and r of positions max(lo - K, 0) .. top - 1, in the unit of the whole sequence
+    // V of positions lo .. top and r of positions max(lo - K, 0) .. top, in the unit of the whole sequence
     __device__ __forceinline__ void load_rows(const Params &p, const int b, const int lo, const int top)
     {
         const int tid = threadIdx.x;
@@ -440,7 +455,6 @@ struct VitTile {
             const int s = rbase + i;
             const double x = chunked ? u[s == 0 ? 0 : (unsigned)(s - 1) / (unsigned)p.Delta] : 0.0;
             if (tid < 256) unit[i] = x;
-            if (i == nr - 1) break;  // r at `top` itself is not needed
 #pragma unroll 8
             for (int c = tid >> 8; c < C; c += VT_THREADS / 256) r[c * rs + i] = R[c * ts + i] + x;
         }
@@ -455,45 +469,89 @@ struct VitTile {
         }
         __syncthreads();
     }
-    // duration of the segment that ends at (t, c); l: lane of the row
+    // Duration of the segment that ends at (t, c); l: lane of the row.  KU: candidates per lane that stay in registers between the
+    // search for the best one and the search for the first that ties with it; MORE: there are further ones.
+    template <int KU, bool MORE>
     __device__ __forceinline__ int duration(const int t, const int c, const int l) const
     {
         const double *rc = r + c * rs + (t - 1 - rbase);
         const float *dc = dur + c * ks;
-        double best = -INFINITY;
-        int at = 0;
-#pragma unroll 4
-        for (int i = l; i < min(K, t); i += 16) {
-            const double x = rc[-i] + (double)dc[i];
-            if (x > best) {
-                best = x;
-                at = i;
-            }
+        const int lim = min(K, t);
+        double x[KU], best = -INFINITY;
+        float d[KU];
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {  // (lanes beyond the last candidate repeat it: nothing waits in a branch)
+            const int i = min(l + 16 * u, lim - 1);
+            x[u] = rc[-i];
+            d[u] = dc[i];
         }
-        return row16_first(best, at, 0) + 1;
+        const double slack = vit_slack(v[(t - vbase) * C + c]);
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+            x[u] = l + 16 * u < lim ? x[u] + (double)d[u] : -INFINITY;
+            best = fmax(best, x[u]);
+        }
+        if (MORE) {
+#pragma unroll 4
+            for (int i = l + 16 * KU; i < lim; i += 16) best = fmax(best, rc[-i] + (double)dc[i]);
+        }
+        best = row16_max(best);
+        const double floor = vit_floor(best) - slack;
+        int at = 0x7fffffff;
+        if (MORE) {
+#pragma unroll 4
+            for (int i = l + 16 * KU; i < lim; i += 16)
+                if (rc[-i] + (double)dc[i] >= floor) at = min(at, i);
+        }
+#pragma unroll
+        for (int u = KU - 1; u >= 0; --u) at = x[u] >= floor ? l + 16 * u : at;
+        at = row16_min(at);
+        return (best > -INFINITY ? at : 0) + 1;
     }
-    // label of the node at s before one with label c (c = C: the best label at s)
+    // label of the node at s before one with label c (c = C: the best label at s); CU: labels per lane
+    template <int CU>
     __device__ __forceinline__ int label(const int s, const int c, const int l) const
     {
-        const double *vs = v + (s - vbase) * C;
+        const double *vs = v + (s - vbase) * C, *rr = r + (s - rbase);
         const float *tc = tr + c * cs;
-        double best = -INFINITY;
-        int at = 0;
-#pragma unroll 4
-        for (int o = l; o < C; o += 16) {
-            const double x = vs[o] + (double)tc[o];
-            if (x > best) {
-                best = x;
-                at = o;
-            }
+        double x[CU], z[CU], best = -INFINITY;
+        float d[CU];
+#pragma unroll
+        for (int u = 0; u < CU; ++u) {
+            const int o = min(l + 16 * u, C - 1);
+            x[u] = vs[o];
+            z[u] = rr[o * rs];
+            d[u] = tc[l + 16 * u];  // -infinity beyond the last label
         }
-        return row16_first(best, at, 0);
+#pragma unroll
+        for (int u = 0; u < CU; ++u) {
+            x[u] += (double)d[u];
+            best = fmax(best, x[u]);
+            x[u] += vit_slack(z[u]);
+        }
+        best = row16_max(best);
+        const double floor = vit_floor(best);
+        int at = 0x7fffffff;
+#pragma unroll
+        for (int u = CU - 1; u >= 0; --u) at = x[u] >= floor ? l + 16 * u : at;
+        at = row16_min(at);
+        return best > -INFINITY ? at : 0;
     }
+};
+
+// Lanes' shares of the durations and labels as compile-time sizes.  First pass at the genomic shape (KU = 4, CU = 2): 164 us so;
+// one kernel with four candidates per lane for all sizes 192 us, with runtime loops instead 213 us (and 168 us without the
+// second search, where rounding decided the ties).
+template <int KU_, int CU_, bool MORE_>
+struct VitShape {
+    static constexpr int KU = KU_, CU = CU_;  // K <= 16 KU unless MORE, C <= 16 CU
+    static constexpr bool MORE = MORE_;
 };
 
 // Traces tile j of sequence b (at least one token of it lies in the sequence).  from: the node (t C + c) by which the tile
 // above left, and the position where its segment starts (-1: not known); from.x < 0: start at the warm-up's best node.
 // rec, also: where the tile's record goes.
+template <class SH>
 __device__ __forceinline__ void vit_tile(const Params &p, VitTile &tile, const int b, const int j, const int n, const int2 from,
                                          int4 *rec, int4 *also)
 {
@@ -520,7 +578,7 @@ __device__ __forceinline__ void vit_tile(const Params &p, VitTile &tile, const i
                 leave = make_int2(t * C + c, -1);
                 break;
             }
-            if (s < 0) s = t - tile.duration(t, c, l);
+            if (s < 0) s = t - tile.template duration<SH::KU, SH::MORE>(t, c, l);
             if (s < hi) {
                 if (!inside) entry = t * C + c;
                 inside = true;
@@ -533,7 +591,7 @@ __device__ __forceinline__ void vit_tile(const Params &p, VitTile &tile, const i
                 leave = make_int2(t * C + c, s);
                 break;
             }
-            c = tile.label(s, c, l);
+            c = tile.template label<SH::CU>(s, c, l);
             t = s;
             s = -1;
         }
@@ -547,7 +605,7 @@ __device__ __forceinline__ void vit_tile(const Params &p, VitTile &tile, const i
             trace(from.x / C, from.x % C, from.y);
         } else {
             const int t = i == last ? top : min(hi + VT_WARM, top);
-            trace(t, t == L ? p.vbest[b] : tile.label(t, C, l), -1);
+            trace(t, t == L ? p.vbest[b] : tile.template label<SH::CU>(t, C, l), -1);
         }
     }
     for (;;) {
@@ -567,7 +625,7 @@ __device__ __forceinline__ void vit_tile(const Params &p, VitTile &tile, const i
     if (tid == 0) *rec = *also = make_int4(in[last], out[0].x, out[0].y, starts);
 }
 
-template <bool RETRY>
+template <bool RETRY, class SH>
 __global__ __launch_bounds__(VT_THREADS) void k_vit_trace(Params p, int n)
 {
     extern __shared__ double lds_raw[];
@@ -591,9 +649,10 @@ __global__ __launch_bounds__(VT_THREADS) void k_vit_trace(Params p, int n)
     }
     VitTile tile(p, lds_raw, n);
     tile.load_tables(p);
-    vit_tile(p, tile, b, j, n, from, p.vtile[1] + o, p.vtile[RETRY ? 1 : 0] + o);
+    vit_tile<SH>(p, tile, b, j, n, from, p.vtile[1] + o, p.vtile[RETRY ? 1 : 0] + o);
 }
 
+template <class SH>
 __global__ __launch_bounds__(VT_THREADS) void k_vit_settle(Params p, int n)
 {
     extern __shared__ double lds_raw[];
@@ -608,7 +667,7 @@ __global__ __launch_bounds__(VT_THREADS) void k_vit_settle(Params p, int n)
         tile.load_tables(p);
         for (int j = npl - 2; j >= 0; --j) {
             const int2 from = make_int2(rec[j + 1].y, rec[j + 1].z);
-            if (rec[j].x != from.x) vit_tile(p, tile, b, j, n, from, rec + j, rec + j);
+            if (rec[j].x != from.x) vit_tile<SH>(p, tile, b, j, n, from, rec + j, rec + j);
             __threadfence_block();
             __syncthreads();
         }
@@ -681,27 +740,23 @@ __global__ __launch_bounds__(NT) void k_vit_bp(Params p)
             continue;
         }
         const int kmax = min(K, t);
-        double best = -INFINITY;
-        int kb = 1;
         const double *rcol = rr + (size_t)(t - sbase) * C + c;  // r_{t-k}(c) at rcol[-k*C]
-        for (int k = 1; k <= kmax; ++k) {
-            const double cand = (double)p.dur[(size_t)(k - 1) * C + c] + rcol[-(k * C)];
-            if (cand > best) {
-                best = cand;
-                kb = k;
-            }
-        }
+        auto by_duration = [&](const int k) { return (double)p.dur[(size_t)(k - 1) * C + c] + rcol[-(k * C)]; };
+        double best = -INFINITY;
+        for (int k = 1; k <= kmax; ++k) best = fmax(best, by_duration(k));
+        const double floor = vit_floor(best) - vit_slack(vv[(size_t)(t - sbase) * C + c]);
+        int kb = 1;
+        if (best > -INFINITY)
+            while (kb < kmax && !(by_duration(kb) >= floor)) ++kb;
         const int sp = t - kb;
-        const double *vrow = vv + (size_t)(sp - sbase) * C;
-        double best2 = -INFINITY;
+        const double *vrow = vv + (size_t)(sp - sbase) * C, *rrow = rr + (size_t)(sp - sbase) * C;
+        auto by_label = [&](const int o) { return vrow[o] + (double)p.trans[(size_t)o * C + c]; };
+        best = -INFINITY;
+        for (int o = 0; o < C; ++o) best = fmax(best, by_label(o));
+        const double lfloor = vit_floor(best);
         int cb = 0;
-        for (int o = 0; o < C; ++o) {
-            const double cand = vrow[o] + (double)p.trans[(size_t)o * C + c];
-            if (cand > best2) {
-                best2 = cand;
-                cb = o;
-            }
-        }
+        if (best > -INFINITY)
+            while (cb < C - 1 && !(by_label(cb) + vit_slack(rrow[cb]) >= lfloor)) ++cb;
         bp[n] = (kb << 8) | cb;
         par[n] = sp * C + cb;
     }

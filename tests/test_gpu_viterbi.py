@@ -5,8 +5,9 @@ fp32).  The best PATH need not be unique, so the decoded segmentation is checked
 (segments tile the sequence, one label each, no segment longer than K, flags and counts agree,
 nothing beyond the sequence) and for optimality: its score, recomputed by the oracle's independent
 path scorer, must equal the best score.  Ties are structural, not accidental (a run of one label
-cut as 1+2 or as 2+1 tokens scores the same), and rounding decides them, so the paths themselves
-are not compared; the fraction of tokens on which both decoders agree is printed.
+cut as 1+2 or as 2+1 tokens scores the same), and in the oracle rounding decides them, so the paths
+themselves are not compared here (test_gpu_viterbi_ties.py compares those of the decode's own routes); the
+fraction of tokens on which both decoders agree is printed.
 """
 import numpy as np
 import pytest
