@@ -305,7 +305,8 @@ __device__ __forceinline__ double recip(const double x)
 }
 
 // exp by the reduction x = n ln2 + r, |r| <= ln2 / 2, and the Taylor polynomial of degree 13 (remainder below 5e-18);
-// without the library's special cases: arguments beyond +-708 overflow to inf or 0 in the scaling, NaN stays NaN.
+// without the library's special cases: finite arguments beyond +-708 overflow to inf or 0 in the scaling, infinite ones are not
+// for it, NaN stays NaN.
 __device__ __forceinline__ double exp_inner(const double x)
 {
     constexpr double LN2_HI = 0x1.62e42fefa39efp-1, LN2_LO = 0x1.abc9e3b39803fp-56;  // ln 2 in two parts
@@ -326,6 +327,13 @@ __device__ __forceinline__ double exp_inner(const double x)
     q = fma(q, r, 1.0);
     q = fma(q, r, 1.0);
     return ldexp(q, (int)n);
+}
+
+// The same for any argument: 0 for -infinity and what is too small, infinity for what is too large, NaN for NaN.  (Boundary
+// terms are added to the prefix sum, and -infinity is how a caller forbids a start or an end.)
+__device__ __forceinline__ double exp_any(const double x)
+{
+    return exp_inner(x < -746.0 ? -746.0 : (x > 710.0 ? 710.0 : x));
 }
 
 // BTERMS: any boundary term of Eq. 4 present, or the log-domain pair of the max semiring; ET: emission storage type
@@ -513,7 +521,7 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
                     // that arrives at position t is multiplied by the first, every one that leaves by the second;
                     // max semiring: the same pair in the log domain, (S + end score, start score - S)
                     pr = p.logpair ? make_double2(S + xe[i], xs[i] - S)
-                                   : make_double2(exp_inner(x + xe[i]), exp_inner(xs[i] - x));
+                                   : make_double2(exp_any(x + xe[i]), exp_any(xs[i] - x));
                 }
                 E[(unsigned)(i * C)] = pr;
                 if (p.cum) p.cum[(row0 + t) * C + c] = S;
