@@ -395,5 +395,6 @@ __global__ __launch_bounds__(NT) void k_ent_fin(const double *part, const int32_
     for (int j = 0; j < 3; ++j) v[j] = ent_block_sum(v[j], red);
     if (threadIdx.x != 0) return;
     if (h_pos) h_pos[b] = L > 0 ? (float)(v[0] / (double)L) : 0.f;
-    if (h_bdy) h_bdy[b] = L > 0 ? (float)(log(v[1]) - v[2] / v[1]) : 0.f;
+    // (no mass: no distribution, entropy 0, as k_entropies gives it)
+    if (h_bdy) h_bdy[b] = L > 0 && v[1] > 0.0 && v[1] < DBL_MAX ? (float)(log(v[1]) - v[2] / v[1]) : 0.f;
 }

@@ -52,3 +52,14 @@ def test_prefix_sums_either_side_of_the_inline_limit(T):
     cum = sb.semicrf_cum_scores(dev(emis), None).cpu().numpy()
     f = emis[0].astype(np.float64)
     np.testing.assert_allclose(cum[0, 1:], np.cumsum(f - f.mean(axis=0), axis=0), rtol=0, atol=1e-8)
+
+
+@pytest.mark.parametrize("T", [5, 700, 3000])
+def test_entropies_of_an_empty_boundary_posterior(T):
+    """No mass at all (a caller's own weights, or a sequence without a valid path): an entropy of 0, as for length 0."""
+    pm = np.full((3, T, 4), 0.25, dtype=np.float32)
+    bd = np.zeros((3, T + 1), dtype=np.float32)
+    bd[1, :T] = 1.0
+    h_pos, h_bdy = sb.semicrf_entropies(dev(pm), dev(bd), dev(np.array([T, T, 0], dtype=np.int32)))
+    np.testing.assert_allclose(h_pos.cpu().numpy(), [np.log(4.0), np.log(4.0), 0.0], rtol=1e-6)
+    np.testing.assert_allclose(h_bdy.cpu().numpy(), [0.0, np.log(T), 0.0], rtol=1e-6)
