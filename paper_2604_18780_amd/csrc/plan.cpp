@@ -83,17 +83,19 @@ int auto_interval(int B, int T, int K, int C)
 }
 
 // A forward-only call has one scan where the interval was chosen for two: where that leaves half of the chip's places for
-// scan tasks empty, its intervals are half as long.  Two waves on a SIMD take about 1.25 times the time of one per position
-// (a lone one waits for 40 % of its time), so with a warm-up of W positions halving D gains while D + W > 1.25 (D/2 + W),
-// D > W / 1.5.  Measured at K = 64, C = 24, D = 392, whole call: 238 -> 224 us.  (The best-score scan is bound by the issue
-// of its maxima, two waves take twice the time of one, and keeps D: 245 us either way.)
+// scan tasks empty, its intervals are half as long, if they are at least four warm-ups W long.  Two waves on a SIMD take
+// longer per position than one, and shorter intervals make more boundaries to compare, so halving pays only where the
+// positions saved outweigh that.  Whole call, D against D/2: K = 64, C = 24 (W = 96): D = 400 226 -> 212 us, 288 185 -> 187,
+// 240 162 -> 161, 208 152 -> 154, 192 146 -> 150, 160 132 -> 143, 96 108 -> 123; K = 16, C = 24 (W = 32): D = 128
+// 87.3 -> 85.8, 96 76.9 -> 80.1, 64 69.3 -> 72.0.  (The best-score scan is bound by the issue of its maxima, two waves take
+// twice the time of one, and keeps D: 245 us either way at D = 392.)
 int forward_interval(int B, int T, int K, int C, int Delta)
 {
     int per_scan = 0, per_int = 0;
     if (!spec_applies(K, C) || !wave_tasks_per_cu(K, C, &per_scan, &per_int)) return Delta;
     const int unit = Delta % 32 == 0 ? 32 : 8;
     const int half = (Delta / 2 + unit - 1) / unit * unit;
-    if (half >= Delta || half < sum_warmup(K)) return Delta;
+    if (half >= Delta || Delta < 4 * sum_warmup(K)) return Delta;
     const double tasks = (double)B * (double)(((long long)T + half - 1) / half);
     return tasks <= 256.0 * per_scan ? half : Delta;
 }
