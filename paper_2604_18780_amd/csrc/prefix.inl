@@ -63,8 +63,8 @@ __device__ __forceinline__ void tables_body(const Params &p, const int blk)
 // furthest that the prefix sum of a label gets from its value at the first of them (JMAX = 32 is the longest block; a
 // shorter one lies inside such a group).  The baseline nu is not known yet: it moves that by at most 31 |nu|.
 // Bound by the latency of its loads: 9.3 us with rows dealt out over the threads (eight loads in flight, no excursions),
-// 7.0 us so (B = 32, T = 2000, C = 64, bfloat16); C = 24 leaves 64 of 256 threads idle, 26.8 -> 30.2 us at 4 x 100 000 with
-// projections.
+// 7.0 us so (B = 32, T = 2000, C = 64, bfloat16); 11.8 us both ways at 4 x 100 000 x 24, 27.0 and 26.8 us with projections,
+// which are read 16 bytes at a time where they are aligned (30.2 us one by one).
 // ---------------------------------------------------------------------------
 constexpr int COL_NG = PREP_CH / JMAX;
 
@@ -115,12 +115,16 @@ __device__ __forceinline__ void colsum_body(const Params &p, const int b, const 
     // the boundary projections move a message like an emission does: their maxima are added
     auto absmax = [&](const float *a) {
         float m = 0.f;
-        const int R = NT / C, r = tid / C, c = tid % C;  // rows handled per pass
-        if (a && r < R) {
-            a += ((size_t)b * p.T) * C + c;
-#pragma unroll 8
-            for (int u = u0 + r; u < u1; u += R) m = fmaxf(m, fabsf(a[(size_t)u * C]));
+        if (!a || u1 <= u0) return m;
+        a += ((size_t)b * p.T + u0) * C;  // the chunk's rows, one after the other
+        const int n = (u1 - u0) * C, n4 = ((uintptr_t)a & 15) == 0 ? n / 4 : 0;
+#pragma unroll 4
+        for (int i = tid; i < n4; i += NT) {
+            const float4 v = ((const float4 *)a)[i];
+            m = fmaxf(fmaxf(fmaxf(m, fabsf(v.x)), fmaxf(fabsf(v.y), fabsf(v.z))), fabsf(v.w));
         }
+#pragma unroll 4
+        for (int i = 4 * n4 + tid; i < n; i += NT) m = fmaxf(m, fabsf(a[i]));
         return m;
     };
     float mps = absmax(p.proj_start), mpe = absmax(p.proj_end);
