@@ -109,8 +109,8 @@ typedef enum {
  * that is the faster form.  Same results up to rounding; both at once are refused. */
 #define SEMICRF_TWO_WAVE_SCAN 512u
 #define SEMICRF_ONE_WAVE_SCAN 1024u
-/* flags bit 7 (semicrf_viterbi only): trace back by pointer doubling over all nodes, the route otherwise taken
- * only when an interval's nodes do not fit in LDS.  Same back-pointers, same path; for tests of that route. */
+/* flags bit 7 (semicrf_viterbi only): trace back by pointer doubling over all nodes, at a cost that does not depend on the
+ * data.  Same path as the default route; the other side of the comparison in tests. */
 #define SEMICRF_VITERBI_GLOBAL_TRACE 128u
 /* flags bits 16..31: first warm-up length of the chunk-parallel scans, in positions (0 = the default, max(1.5K, 32);
  * the long second warm-up is four times this).  A length too short for the input costs time, never accuracy:
@@ -221,7 +221,9 @@ int semicrf_fwd_bwd_static(const float *emis, const int32_t *lengths, const floa
  *     proj_start[b, s, c] + proj_end[b, s+k-1, c]
  * (first and last TOKEN of the segment), plus pi_start[c] if s = 0 and pi_end[c] if
  * s+k = L_b (the scalars are added to the projections at token 0 / token L_b-1).
- *   proj_start, proj_end [B,T,C] float or NULL (= zeros); rows u >= L_b are never read
+ *   proj_start, proj_end [B,T,C] float or NULL (= zeros); rows u >= L_b are never read.  -INFINITY (here or in the
+ *                        scalars) forbids the start or end; semicrf_seq_report then counts the sequence as out of
+ *                        range, since it goes by magnitudes, but the results are right
  *   pi_start, pi_end     [C]     float or NULL (= zeros)
  * With all four NULL these calls are semicrf_logz_fwd / semicrf_fwd_bwd.  Additional
  * outputs of the gradient call, each optional (NULL = not wanted), fully overwritten:
@@ -260,10 +262,11 @@ int semicrf_fwd_bwd_boundary(const float *emis, const int32_t *lengths, const fl
  *   nseg   [B]   int32  number of segments
  * Among equally good segmentations the last segment's label is the smallest, and going
  * backwards each segment takes the smallest duration, then the smallest predecessor label,
- * among the maximisers; since sums are rounded, "equally good" means equal in fp64.
+ * among the maximisers; since sums are rounded, "equally good" means within 2^-42 of the larger of the candidates
+ * and the prefix sums in them, and the path does not depend on how the scan was cut into intervals.
  * Supported sizes: C <= 64 and K <= 64 * (64 / (C rounded up to 8/16/32/64)).  Workspace:
- * semicrf_viterbi_workspace_bytes (O(T*C): prefix arrays plus two doubles and four
- * integers per position and label).
+ * semicrf_viterbi_workspace_bytes (O(T*C): prefix arrays plus two doubles and 13 bytes
+ * per position and label; the latter are what the flag's trace-back needs).
  * The forward recurrence runs chunk-parallel like the sums: every checkpoint interval is
  * scanned on its own after a warm-up from the state of a sequence that begins there.  Best
  * paths that have merged give states equal up to one additive constant, so each interval
@@ -274,9 +277,8 @@ int semicrf_fwd_bwd_boundary(const float *emis, const int32_t *lengths, const fl
  * once more after a longer warm-up; a sequence with a boundary that still does not agree
  * is rescanned sequentially inside the same call, and SEMICRF_SEQUENTIAL_SCAN forces that.
  * semicrf_scan_report with ckpt_interval = 0 and want_grad = 0 on this workspace reports
- * the outcome in column 0.  The trace-back (back-pointers of every node, pointer jumping
- * inside each interval, pointer doubling across intervals, one store per token) is parallel
- * either way.
+ * the outcome in column 0.  The trace-back follows the path in pieces side by side, which
+ * are verified against each other and traced again where they disagree.
  */
 int semicrf_viterbi_workspace_bytes(int B, int T, int K, int C, size_t *bytes);
 

@@ -330,7 +330,7 @@ __global__ __launch_bounds__(NT) void k_entropies(const float *pos_marg, const f
 // The same with a workspace: any number of workgroups per sequence, ENT_TOK tokens each, and one more launch that adds
 // their sums up in token order.  Three sums suffice in one pass over the data: with n = sum bdy,
 // h_bdy = log n - (sum bdy log bdy) / n.  Bound by the fp64 log per element; genomic shape (4 x 100 000 x 24):
-// 4.53 ms for k_entropies (four workgroups on the whole chip) -> 0.03 ms.
+// 4.53 ms for k_entropies (four workgroups on the whole chip) -> 0.05 ms.
 constexpr int ENT_TOK = 512;
 __device__ __forceinline__ double ent_block_sum(double v, double *red)  // every thread of NT; sum in thread 0
 {

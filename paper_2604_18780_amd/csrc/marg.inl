@@ -289,8 +289,8 @@ __global__ __launch_bounds__(NT) void k_mg_te(Params p)
 // been turned into the few values the multiply-adds need.
 // BT: calls with boundary terms.  The pair of a position is then no longer (E, 1/E), so the masses of the segments that
 // start and end there are formed with the reciprocals of its two factors, and go out as the gradients of the boundary
-// projections and, summed over the labels, as the boundary posterior.  (Genomic shape with all of them: 193 us, the interval
-// kernel's own recurrence 550 us.)
+// projections and, summed over the labels, as the boundary posterior.  (Genomic shape with all of them: 196 us, 665 us
+// for the call; with the interval kernel's own recurrence the call takes 1025 us.)
 template <int N>
 __device__ __forceinline__ double add_row_ror(const double v)  // v + the v of the lane N places on in its row of 16
 {
@@ -461,7 +461,8 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
     double kappa = kappa_of();
     // mass of the segments of a label that start / end at a position: z p kappa with z = q ES, and a b kappa with b = v IE
     // (no factor in these orders exceeds what BLOCK_NATS allows)
-    auto recip0 = [](const double x) { return x > 1e-300 ? recip(x) : 0.0; };  // a forbidden start or end has mass 0
+    // (a forbidden start or end has mass 0; so has one whose factor is below 1e-300, which is a score of -690)
+    auto recip0 = [](const double x) { return x > 1e-300 ? recip(x) : 0.0; };
     auto start_mass = [&](const double2 &a, const double2 &ev, const double2 &v) {
         return BT ? a.y * recip0(ev.y) * v.x * kappa : a.y * kappa * ev.x * v.x;
     };

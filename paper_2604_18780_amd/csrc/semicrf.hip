@@ -281,8 +281,9 @@ int launch_spec_k(const Params &p, hipStream_t st, bool both, int warm, int tier
         if (rc != SEMICRF_OK) return rc;
         rest = 1;
     }
-    // two waves per task where the window or the transition product is long next to a position's dependent chain
-    // (measured: longgen scans 1.27 -> 0.85 ms, speech 0.30 -> 0.25 ms; genomic 0.37 -> 0.41 ms, so not there)
+    // two waves per task where the window or the transition product is long next to a position's dependent chain.  Whole
+    // gradient call, one wave against two: K = 32, C = 64 296 -> 269 us; K = 512, C = 8 1023 -> 1039; K = 64, C = 24
+    // 557 -> 545; K = 37, C = 19 302 -> 314; K = 16, C = 24 99 -> 98: apart from 64 labels the two are close.
     const bool two = (p.spec2 == 1 || (p.spec2 == 0 && (NKW == 64 || CT == 64))) &&
                      spec2_lds_doubles<CT, NKW>() * sizeof(double) <= LDS_LIMIT;
     if (tier == 0) rc = launch_spec_tasks<CT, NKW, false>(p, st, both, warm, tier, rest, two);

@@ -16,9 +16,9 @@
 // from, entry by entry, after removing their common scale factor.  If all boundaries of
 // a (sequence, direction) agree to SPEC_TOL the warm-up states ARE the sequential
 // states to that relative accuracy (perturbations of the start do not grow: the maps
-// are non-expansive in the projective metric); spec_fix then chains the scale
+// are non-expansive in the projective metric); spec_settle then chains the scale
 // factors into the checkpoint scales and logZ.  Otherwise the flag stays 0 and the
-// sequential scan kernel, which is launched afterwards and returns at once for
+// sequential scan kernel, launched after the later attempts, which returns at once for
 // accepted (sequence, direction) pairs, recomputes that pair from scratch.
 // One wave per task, no barriers, same register/LDS organisation as k_interval_wave.
 // ---------------------------------------------------------------------------

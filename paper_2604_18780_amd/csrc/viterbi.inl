@@ -57,8 +57,8 @@ __device__ __forceinline__ void vit_best(const Params &p, const int b, const dou
 // a constant once all best paths through the warm-up have merged.
 // Lanes, window and time blocks as in the sum scans (spec_task): a maximum of sums is two
 // instructions where they have one, and the transition maximum three per entry (row broadcast, add,
-// max), still less than the way through LDS.  Genomic shape, 1024 tasks of 520 positions: 366 us with the
-// V vector in LDS and the window read where it is used, 205 us so.
+// max), still less than the way through LDS.  Genomic shape, 1024 tasks of 520 positions: 395 us with the
+// V vector in LDS and the window read where it is used, 252 us so (an instruction issues in 69 % of a wave's cycles).
 // V goes out by position, as it is made.  The trace-back looks at r along the positions of one label, so r is stored
 // by label, FT positions at a time out of the window (a row of FT * 8 bytes per label).
 template <int CT, int NKW, bool WHOLE>

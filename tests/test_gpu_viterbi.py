@@ -152,8 +152,8 @@ def test_paths_that_do_not_merge_fall_back_to_the_sequential_scan():
 
 
 def test_both_trace_back_routes_write_the_same_path():
-    """Intervals too large for LDS fall back to pointer doubling over all nodes; the test knob forces
-    that route on a shape that normally takes the interval route.  Same back-pointers, same path."""
+    """The trace-back in tiles, and the one by pointer doubling over all nodes that a flag asks for: same candidates, same
+    rule for ties, same path."""
     w = synth.small_random(77, 3, 3000, 12, 6, ragged=True)
     dev = [torch.from_numpy(a).to(DEV) for a in (w.emis, w.lengths, w.trans, w.dur)]
     a = [o.cpu().numpy() for o in sb.semicrf_viterbi(*dev)]
