@@ -403,7 +403,7 @@ __device__ __forceinline__ int row16_min(int v)
 }
 
 // A tile's share of V and r, and the tables: dur by label, then trans by the label it leads to and a row of zeros (rows
-// padded with -infinity to whole turns of 16 lanes, and by one so that they start in different banks).
+// padded with -infinity to whole turns of 16 lanes, and by one, of trans also filled, so that they start in different banks).
 struct VitTile {
     double *r;     // [C][rs]: r_s(c) at [c][s - rbase]
     double *v;     // [..][C]: V_s(c) at [s - vbase][c]
@@ -435,7 +435,7 @@ struct VitTile {
         }
         for (int c = tid >> 4; c <= C; c += VT_PIECES) {
 #pragma unroll 4
-            for (int o = tid & 15; o < cs - 1; o += 16)
+            for (int o = tid & 15; o < cs; o += 16)
                 tr[c * cs + o] = o < C ? (c < C ? p.trans[(size_t)o * C + c] : 0.f) : -INFINITY;
         }
     }
@@ -521,7 +521,7 @@ struct VitTile {
             const int o = min(l + 16 * u, C - 1);
             x[u] = vs[o];
             z[u] = rr[o * rs];
-            d[u] = tc[l + 16 * u];  // -infinity beyond the last label
+            d[u] = tc[CU == 4 ? min(l + 16 * u, cs - 1) : l + 16 * u];  // -infinity beyond the last label, up to the row's last entry
         }
 #pragma unroll
         for (int u = 0; u < CU; ++u) {
@@ -608,7 +608,7 @@ __device__ __forceinline__ void vit_tile(const Params &p, VitTile &tile, const i
             trace(t, t == L ? p.vbest[b] : tile.template label<SH::CU>(t, C, l), -1);
         }
     }
-    for (;;) {
+    for (int round = 0; round < VT_PIECES; ++round) {  // the last piece is right; each round makes one more right
         __syncthreads();
         const int2 above = i < last ? out[i + 1] : make_int2(0, 0);
         const bool wrong = i < last && in[i] != above.x;

@@ -50,7 +50,7 @@ def test_many_adjacent_tiles_are_traced_again(K, C):
 
 
 @pytest.mark.parametrize("T", [1, 2, 7, 8, 9, 63, 64, 65, 127, 128, 129, 255, 256, 257, 511, 513, 769])
-@pytest.mark.parametrize("K,C", [(5, 3), (40, 24), (300, 8), (30, 64)])
+@pytest.mark.parametrize("K,C", [(5, 3), (40, 24), (300, 8), (30, 64), (25, 47), (48, 33)])
 def test_lengths_at_the_edges_of_pieces_and_tiles(T, K, C):
     """Pieces of 8, 4 (40 x 24) and 2 tokens (30 x 64), tiles of 32 of them, K longer than a tile; lengths
     that end one token into a tile or fill it."""
