@@ -548,10 +548,13 @@ int launch_vit_trace_sh(const Params &p, hipStream_t st)
 template <int CU>
 int launch_vit_trace_cu(const Params &p, hipStream_t st)
 {
-    if (p.K <= 16) return launch_vit_trace_sh<VitShape<1, CU, false>>(p, st);
-    if (p.K <= 32) return launch_vit_trace_sh<VitShape<2, CU, false>>(p, st);
-    if (p.K <= 64) return launch_vit_trace_sh<VitShape<4, CU, false>>(p, st);
-    return launch_vit_trace_sh<VitShape<4, CU, true>>(p, st);
+    constexpr int KUMAX = CU == 1 ? 32 : (CU == 2 ? 8 : 4);  // spec_applies: K <= 512, 128 and 64 at most
+    if (p.K <= 16) return launch_vit_trace_sh<VitShape<1, CU>>(p, st);
+    if (p.K <= 32) return launch_vit_trace_sh<VitShape<2, CU>>(p, st);
+    if (p.K <= 64) return launch_vit_trace_sh<VitShape<4, CU>>(p, st);
+    if (p.K <= 128) return launch_vit_trace_sh<VitShape<(KUMAX < 8 ? KUMAX : 8), CU>>(p, st);
+    if (p.K <= 256) return launch_vit_trace_sh<VitShape<(KUMAX < 16 ? KUMAX : 16), CU>>(p, st);
+    return launch_vit_trace_sh<VitShape<KUMAX, CU>>(p, st);
 }
 
 int launch_vit_trace(const Params &p, hipStream_t st)

@@ -369,10 +369,10 @@ constexpr int VT_PIECES = VT_THREADS / 16;
 constexpr int VT_WARM = 4;  // warm-up of a piece inside its tile
 
 // Tokens per piece n (tile: VT_PIECES n tokens): the most with which a compute unit holds two tiles, so that one loads while
-// the other follows its paths.  A tile's own warm-up is 4 n positions.
+// the other follows its paths.  A tile's own warm-up is 4 n - 1 positions, so that it reads vit_tile_rows positions.
 inline __host__ __device__ int vit_tile_rows(const int n) { return VT_PIECES * n + 4 * n; }
 inline __host__ __device__ int vit_row_floats(const int n) { return ((n + 15) & ~15) + 1; }
-inline __host__ __device__ int vit_r_stride(const int n, const int K) { return (vit_tile_rows(n) + K + 1) | 1; }  // max(lo - K, 0) .. top
+inline __host__ __device__ int vit_r_stride(const int n, const int K) { return (vit_tile_rows(n) + K) | 1; }  // max(lo - K, 0) .. top
 inline size_t vit_tile_lds(const int n, const int K, const int C)
 {
     return ((size_t)C * vit_r_stride(n, K) + (size_t)(vit_tile_rows(n) + 1) * C + vit_tile_rows(n) + K + 1) * sizeof(double) +
@@ -469,42 +469,67 @@ struct VitTile {
         }
         __syncthreads();
     }
-    // Duration of the segment that ends at (t, c); l: lane of the row.  KU: candidates per lane that stay in registers between the
-    // search for the best one and the search for the first that ties with it; MORE: there are further ones.
-    template <int KU, bool MORE>
+    // Duration of the segment that ends at (t, c); l: lane of the row.  KU: candidates per lane.  Up to 16 stay in registers
+    // between the search for the best one and the search for the first that ties with it; of more, the largest of every
+    // four does, and the first four with one that ties are looked at again (32 in registers leave a compute unit one tile
+    // fewer: whole call at 5 x 84 374, K = 388, C = 4 1188 us, all looked at again 1056, so 1044).
+    template <int KU>
     __device__ __forceinline__ int duration(const int t, const int c, const int l) const
     {
         const double *rc = r + c * rs + (t - 1 - rbase);
         const float *dc = dur + c * ks;
         const int lim = min(K, t);
-        double x[KU], best = -INFINITY;
-        float d[KU];
+        constexpr int NX = KU <= 16 ? KU : 4;
+        double x[NX], best = -INFINITY;
+        float d[NX];
+        auto load = [&](const int i0) {  // (lanes beyond the last candidate repeat it: nothing waits in a branch)
 #pragma unroll
-        for (int u = 0; u < KU; ++u) {  // (lanes beyond the last candidate repeat it: nothing waits in a branch)
-            const int i = min(l + 16 * u, lim - 1);
-            x[u] = rc[-i];
-            d[u] = dc[i];
-        }
-        const double slack = vit_slack(v[(t - vbase) * C + c]);
+            for (int u = 0; u < NX; ++u) {
+                const int i = min(i0 + 16 * u, lim - 1);
+                x[u] = rc[-i];
+                d[u] = dc[i];
+            }
+        };
+        auto add = [&](const int i0) {
 #pragma unroll
-        for (int u = 0; u < KU; ++u) {
-            x[u] = l + 16 * u < lim ? x[u] + (double)d[u] : -INFINITY;
-            best = fmax(best, x[u]);
-        }
-        if (MORE) {
-#pragma unroll 4
-            for (int i = l + 16 * KU; i < lim; i += 16) best = fmax(best, rc[-i] + (double)dc[i]);
-        }
-        best = row16_max(best);
-        const double floor = vit_floor(best) - slack;
+            for (int u = 0; u < NX; ++u) x[u] = i0 + 16 * u < lim ? x[u] + (double)d[u] : -INFINITY;
+        };
         int at = 0x7fffffff;
-        if (MORE) {
-#pragma unroll 4
-            for (int i = l + 16 * KU; i < lim; i += 16)
-                if (rc[-i] + (double)dc[i] >= floor) at = min(at, i);
-        }
+        if constexpr (KU <= 16) {
+            load(l);
+            const double slack = vit_slack(v[(t - vbase) * C + c]);
+            add(l);
 #pragma unroll
-        for (int u = KU - 1; u >= 0; --u) at = x[u] >= floor ? l + 16 * u : at;
+            for (int u = 0; u < NX; ++u) best = fmax(best, x[u]);
+            best = row16_max(best);
+            const double floor = vit_floor(best) - slack;
+#pragma unroll
+            for (int u = NX - 1; u >= 0; --u) at = x[u] >= floor ? l + 16 * u : at;
+        } else {
+            double top[KU / 4];
+            const double slack = vit_slack(v[(t - vbase) * C + c]);
+#pragma unroll
+            for (int q = 0; q < KU / 4; ++q) {
+                top[q] = -INFINITY;
+                if (K > 64 * q) {  // uniform
+                    load(l + 64 * q);
+                    add(l + 64 * q);
+                    top[q] = fmax(fmax(x[0], x[1]), fmax(x[2], x[3]));
+                }
+                best = fmax(best, top[q]);
+            }
+            best = row16_max(best);
+            const double floor = vit_floor(best) - slack;
+            int i0 = -1;
+#pragma unroll
+            for (int q = KU / 4 - 1; q >= 0; --q) i0 = top[q] >= floor ? l + 64 * q : i0;
+            if (i0 >= 0) {
+                load(i0);
+                add(i0);
+#pragma unroll
+                for (int u = NX - 1; u >= 0; --u) at = x[u] >= floor ? i0 + 16 * u : at;
+            }
+        }
         at = row16_min(at);
         return (best > -INFINITY ? at : 0) + 1;
     }
@@ -542,10 +567,9 @@ struct VitTile {
 // Lanes' shares of the durations and labels as compile-time sizes.  First pass at the genomic shape (KU = 4, CU = 2): 164 us so;
 // one kernel with four candidates per lane for all sizes 192 us, with runtime loops instead 213 us (and 168 us without the
 // second search, where rounding decided the ties).
-template <int KU_, int CU_, bool MORE_>
+template <int KU_, int CU_>
 struct VitShape {
-    static constexpr int KU = KU_, CU = CU_;  // K <= 16 KU unless MORE, C <= 16 CU
-    static constexpr bool MORE = MORE_;
+    static constexpr int KU = KU_, CU = CU_;  // K <= 16 KU, C <= 16 CU
 };
 
 // Traces tile j of sequence b (at least one token of it lies in the sequence).  from: the node (t C + c) by which the tile
@@ -560,7 +584,7 @@ __device__ __forceinline__ void vit_tile(const Params &p, VitTile &tile, const i
     __shared__ int starts;
     const int C = p.C, T = p.T, L = p.hdr[b].L, tid = threadIdx.x, i = tid >> 4, l = tid & 15;
     const int tlo = j * n * VT_PIECES, thi = min(tlo + n * VT_PIECES, L);
-    const int top = from.x < 0 ? min(thi + 4 * n, L) : thi;
+    const int top = from.x < 0 ? min(thi + 4 * n - 1, L) : thi;
     const int last = (thi - tlo - 1) / n;  // piece that ends at the tile's upper end
     const int lo = tlo + i * n, hi = min(lo + n, L);
     const int u = lo + l;  // the lane's token (l < n)
@@ -578,7 +602,7 @@ __device__ __forceinline__ void vit_tile(const Params &p, VitTile &tile, const i
                 leave = make_int2(t * C + c, -1);
                 break;
             }
-            if (s < 0) s = t - tile.template duration<SH::KU, SH::MORE>(t, c, l);
+            if (s < 0) s = t - tile.template duration<SH::KU>(t, c, l);
             if (s < hi) {
                 if (!inside) entry = t * C + c;
                 inside = true;

@@ -37,7 +37,8 @@ def decode(w, flags):
     (3000, 8, 4, 40, 2.0), (3000, 8, 4, 40, 12.0), (6000, 57, 3, 150, 2.0), (6000, 57, 3, 400, 8.0), (4000, 16, 8, 60, 3.0),
     (20000, 5, 3, 100, 30.0), (3000, 90, 5, 300, 4.0), (2000, 12, 24, 80, 6.0), (1500, 20, 64, 90, 8.0),
     (1200, 9, 15, 60, 4.0), (1200, 9, 16, 60, 4.0), (1200, 9, 17, 60, 4.0), (1200, 33, 32, 60, 4.0), (1200, 33, 33, 60, 4.0),
-    (1200, 25, 47, 60, 4.0), (1200, 16, 48, 60, 4.0), (1200, 17, 49, 60, 4.0),
+    (3000, 128, 8, 500, 4.0), (3000, 129, 8, 500, 4.0), (3000, 256, 16, 700, 4.0), (3000, 257, 5, 700, 4.0), (3000, 388, 4, 900, 4.0),
+    (3000, 512, 8, 900, 4.0), (1200, 128, 24, 400, 4.0), (1200, 25, 47, 60, 4.0), (1200, 16, 48, 60, 4.0), (1200, 17, 49, 60, 4.0),
 ])
 @pytest.mark.parametrize("center", [True, False])
 def test_the_path_does_not_depend_on_how_the_scan_was_cut(T, K, C, length, level, center):
