@@ -545,23 +545,24 @@ int launch_vit_trace_sh(const Params &p, hipStream_t st)
     return check_launch();
 }
 
-template <int CU>
-int launch_vit_trace_cu(const Params &p, hipStream_t st)
+// The smallest of KU, KUS ... that covers the durations (empty shares cost what full ones do: K = 160 in 16 instead of 12 of
+// them 4 % of a call).
+template <int CU, int KU, int... KUS>
+int launch_vit_trace_k(const Params &p, hipStream_t st)
 {
-    constexpr int KUMAX = CU == 1 ? 32 : (CU == 2 ? 8 : 4);  // spec_applies: K <= 512, 128 and 64 at most
-    if (p.K <= 16) return launch_vit_trace_sh<VitShape<1, CU>>(p, st);
-    if (p.K <= 32) return launch_vit_trace_sh<VitShape<2, CU>>(p, st);
-    if (p.K <= 64) return launch_vit_trace_sh<VitShape<4, CU>>(p, st);
-    if (p.K <= 128) return launch_vit_trace_sh<VitShape<(KUMAX < 8 ? KUMAX : 8), CU>>(p, st);
-    if (p.K <= 256) return launch_vit_trace_sh<VitShape<(KUMAX < 16 ? KUMAX : 16), CU>>(p, st);
-    return launch_vit_trace_sh<VitShape<KUMAX, CU>>(p, st);
+    if constexpr (sizeof...(KUS) > 0) {
+        if (p.K > 16 * KU) return launch_vit_trace_k<CU, KUS...>(p, st);
+    }
+    return launch_vit_trace_sh<VitShape<KU, CU>>(p, st);
 }
 
 int launch_vit_trace(const Params &p, hipStream_t st)
 {
-    if (p.C <= 16) return launch_vit_trace_cu<1>(p, st);
-    if (p.C <= 32) return launch_vit_trace_cu<2>(p, st);
-    return launch_vit_trace_cu<4>(p, st);
+    // (spec_applies: K <= 512 for 8 labels, 256 for 16, 128 for 32, 64 for 64)
+    if (p.C <= 16) return launch_vit_trace_k<1, 1, 2, 4, 6, 8, 12, 16, 24, 32>(p, st);
+    if (p.C <= 32) return launch_vit_trace_k<2, 1, 2, 4, 6, 8>(p, st);
+    if (p.C <= 48) return launch_vit_trace_k<3, 1, 2, 4>(p, st);
+    return launch_vit_trace_k<4, 1, 2, 4>(p, st);
 }
 
 // Viterbi: prefix stage with the log-domain pair, one scan wave per sequence, trace-back.

@@ -403,7 +403,7 @@ __device__ __forceinline__ int row16_min(int v)
 }
 
 // A tile's share of V and r, and the tables: dur by label, then trans by the label it leads to and a row of zeros (rows
-// padded with -infinity to whole turns of 16 lanes, and by one, of trans also filled, so that they start in different banks).
+// padded with -infinity to whole turns of 16 lanes, and by one so that they start in different banks).
 struct VitTile {
     double *r;     // [C][rs]: r_s(c) at [c][s - rbase]
     double *v;     // [..][C]: V_s(c) at [s - vbase][c]
@@ -435,7 +435,7 @@ struct VitTile {
         }
         for (int c = tid >> 4; c <= C; c += VT_PIECES) {
 #pragma unroll 4
-            for (int o = tid & 15; o < cs; o += 16)
+            for (int o = tid & 15; o < cs - 1; o += 16)
                 tr[c * cs + o] = o < C ? (c < C ? p.trans[(size_t)o * C + c] : 0.f) : -INFINITY;
         }
     }
@@ -546,7 +546,7 @@ struct VitTile {
             const int o = min(l + 16 * u, C - 1);
             x[u] = vs[o];
             z[u] = rr[o * rs];
-            d[u] = tc[CU == 4 ? min(l + 16 * u, cs - 1) : l + 16 * u];  // -infinity beyond the last label, up to the row's last entry
+            d[u] = tc[l + 16 * u];  // -infinity beyond the last label: CU is the fewest shares, so rows are padded to 16 CU
         }
 #pragma unroll
         for (int u = 0; u < CU; ++u) {
@@ -569,7 +569,7 @@ struct VitTile {
 // second search, where rounding decided the ties).
 template <int KU_, int CU_>
 struct VitShape {
-    static constexpr int KU = KU_, CU = CU_;  // K <= 16 KU, C <= 16 CU
+    static constexpr int KU = KU_, CU = CU_;  // K <= 16 KU, 16 (CU - 1) < C <= 16 CU
 };
 
 // Traces tile j of sequence b (at least one token of it lies in the sequence).  from: the node (t C + c) by which the tile
