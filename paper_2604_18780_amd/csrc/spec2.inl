@@ -177,6 +177,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
         double2 e[MB];
         load_rows(e, t);
         lds_barrier();  // start: the helper may read the window
+        if (repair) lds_barrier();  // ... and has added up what its older entries add to the first block
         while (t != tend) {
             const int nb = block_len(t);
             const int tn = BWD ? t - nb : t + nb;
@@ -260,7 +261,28 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
             const int k = g * NK + jj + MB + 1;
             wx[jj] = (cval && k <= K) ? p.W[(size_t)(k - 1) * C + c] : 0.0;
         }
+        // what the entries from row rb on (MB positions behind a block's base, and older) add to its MB positions
+        auto far_sums = [&](const int rb, const int buf) {
+            const double *base = ring + rb * RS + (BWD ? g * NK * RS + c : -(g * NK + NK - 1) * RS + c);
+            double acc[MB];
+#pragma unroll
+            for (int i = 0; i < MB; ++i) acc[i] = 0.0;
+            G::template window_sums<BWD, MB>(base, wx, acc);
+#pragma unroll
+            for (int i = 0; i < MB; ++i) acc[i] = group_sum<CTP>(acc[i]);
+            double *fb = farb + buf * MB * CTP + c;
+            if (g == 0) {
+#pragma unroll
+                for (int i = 0; i < MB; ++i) fb[i * CTP] = acc[i];
+            }
+        };
         lds_barrier();  // start
+        if (repair) {
+            // a mended task starts with a whole window: the first block has older entries, too (after a warm-up's start
+            // there is only the newest one)
+            far_sums(BWD ? r + MB : r - MB, 0);
+            lds_barrier();
+        }
         while (t != tend) {
             const int nb = block_len(t);
             const int tn = BWD ? t - nb : t + nb;
@@ -287,21 +309,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
             }
             // what the entries at least MB positions before the NEXT block's base add to its MB positions
             // (the base is the last position of this block; its newest MB predecessors are the tip's)
-            {
-                const int rb = BWD ? r - nb + MB : r + nb - MB;   // row of the newest entry that is the helper's
-                const double *base = ring + rb * RS + (BWD ? g * NK * RS + c : -(g * NK + NK - 1) * RS + c);
-                double acc[MB];
-#pragma unroll
-                for (int i = 0; i < MB; ++i) acc[i] = 0.0;
-                G::template window_sums<BWD, MB>(base, wx, acc);
-#pragma unroll
-                for (int i = 0; i < MB; ++i) acc[i] = group_sum<CTP>(acc[i]);
-                double *fb = farb + ((nblk + 1) & 1) * MB * CTP + c;
-                if (g == 0) {
-#pragma unroll
-                    for (int i = 0; i < MB; ++i) fb[i * CTP] = acc[i];
-                }
-            }
+            far_sums(BWD ? r - nb + MB : r + nb - MB, (nblk + 1) & 1);
             lds_barrier();   // end of the block
             r += BWD ? -nb : nb;
             t = tn;
