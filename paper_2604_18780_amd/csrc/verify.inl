@@ -158,12 +158,16 @@ __device__ __forceinline__ void spec_settle(const Params &p, const int b, const 
     lr[0] = (double)v.nbad;
 }
 
-// Verdicts in a launch of their own, for scans whose kernels do not work them out.  grid (B, directions), one wave.
+// Verdicts in a launch of their own, for scans whose kernels do not work them out (duration-dependent transitions).
+// grid (B, directions), one wave.  The backward scans there have used the forward rows of the same attempt, so a backward
+// scan is accepted only where the forward one is.
 __global__ __launch_bounds__(64) void k_spec_fix(Params p, int ndir, int tier)
 {
     const int b = blockIdx.x, dir = blockIdx.y, lane = threadIdx.x;
     if (tier > 0 && p.spec_ok[b * 2 + dir]) return;
-    spec_settle(p, b, dir, ndir, tier, spec_verdict(p, b, dir, lane), lane);
+    SpecVerdict v = spec_verdict(p, b, dir, lane);
+    if (dir == 1) v.ok = v.ok && spec_verdict(p, b, 0, lane).ok;
+    spec_settle(p, b, dir, ndir, tier, v, lane);
 }
 
 // Sequential scans: true if the pair needs none.  They follow the last attempt (number `tier`), whose verdict they

@@ -24,3 +24,14 @@ def test_several_groups_of_durations(K, C):
     w = synth.small_random(K + C, 2, 2 * K + 37, K, C, ragged=False)
     w.lengths[:] = [w.T, K + 5]
     check(w, trans3_of(w, K))
+
+
+@pytest.mark.parametrize("seed", [0, 1, 2, 3, 4, 5, 1073057435])
+@pytest.mark.parametrize("K,C,delta", [(5, 17, 64), (4, 6, 40), (12, 20, 48), (400, 8, 0)])
+def test_backward_scans_whose_forward_rows_were_scanned_again(seed, K, C, delta):
+    """The backward scan weights what starts and ends at a position with the forward rows.  Weak emissions and banded transitions
+    are forgotten so slowly that one direction can be verified at an attempt at which the other is not."""
+    w = synth.small_random(seed, 3, 113 if delta else 1500, K, C, ragged=True, scale=0.05)
+    w.lengths[0] = w.T
+    w.trans[:] = synth.reshape_transitions(w.trans, sd=0.1, band=2)
+    check(w, trans3_of(w, seed % 1000), ckpt_interval=delta)
