@@ -31,15 +31,15 @@ constexpr int SPEC_RUN_MAX = 2;  // intervals one wave mends in a row in the rep
 //   forgets slowly everywhere.  Otherwise every task again after a longer warm-up: at tier 1 what the mismatch of the
 //   attempt before asks for, at tier 2 the longest.
 // Whether the attempt before was accepted is worked out here, by every wave for its own pair (spec_verdict reads a few
-// hundred numbers): the first task of an accepted pair also settles it.  A launch in between for the verdicts alone would
-// cost every call as much as a comparison.
+// hundred numbers): the first task of the pair also settles it (settles: this wave is the one of its task to do so).  A launch
+// in between for the verdicts alone would cost every call as much as a comparison.
 struct SpecJob {
     bool idle, mend;
     int warm, nint;
     const double *err;
 };
 __device__ __forceinline__ SpecJob spec_job(const Params &p, const int b, const int dir, const int j, const int ndir,
-                                            const int warm, const int tier)
+                                            const int warm, const int tier, const bool settles)
 {
     SpecJob s;
     s.idle = s.mend = false;
@@ -53,7 +53,7 @@ __device__ __forceinline__ SpecJob spec_job(const Params &p, const int b, const 
         return s;
     }
     const SpecVerdict v = spec_verdict(p, b, dir, lane);
-    if (j == 0 && (blockDim.x != 128 || threadIdx.x < 64)) spec_settle(p, b, dir, ndir, tier - 1, v, lane);
+    if (j == 0 && settles) spec_settle(p, b, dir, ndir, tier - 1, v, lane);
     s.idle = v.ok;
     s.nint = v.nint;
     s.mend = v.nbad <= max(2, v.nint / 16);
@@ -342,7 +342,7 @@ __global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, N
     double *lds = lds_raw + (size_t)wave * scan_lds_doubles(CT, NKW);
     SpecJob job = {};
     if (RETRY) {
-        job = spec_job(p, b, dir, j, both ? 2 : 1, warm, tier);
+        job = spec_job(p, b, dir, j, both ? 2 : 1, warm, tier, true);
         if (job.idle) return;  // accepted by an earlier attempt
     } else if (rest && p.hdr[b].J >= MS_JMIN) {
         return;

@@ -328,7 +328,7 @@ __global__ __launch_bounds__(128, spec2_waves_per_simd(CT, NKW)) void k_spec2(Pa
     const int b = task / p.N, j = task % p.N;
     SpecJob job = {};
     if (RETRY) {
-        job = spec_job(p, b, dir, j, ndir, warm, tier);
+        job = spec_job(p, b, dir, j, ndir, warm, tier, threadIdx.x < 64);
         if (job.idle) return;  // accepted by an earlier attempt
     } else if (rest && p.hdr[b].J >= MS_JMIN) {
         return;
