@@ -11,7 +11,7 @@ SOURCES = [os.path.join(HERE, "csrc", n) for n in ("semicrf.hip", "mscan.hip", "
 OBJDIR = os.path.join(HERE, "_build")
 FLAGS = [
     "-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17",
-    # packed fp32 VALU forms are not to be generated on the test machines
+    # packed fp32 VALU forms are not to be generated: some have given wrong results on this hardware
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I" + os.path.join(ROOT, "include"),
 ]
