@@ -112,8 +112,8 @@ typedef enum {
 /* flags bit 7 (semicrf_viterbi only): trace back by pointer doubling over all nodes, at a cost that does not depend on the
  * data.  Same path as the default route; the other side of the comparison in tests. */
 #define SEMICRF_VITERBI_GLOBAL_TRACE 128u
-/* flags bits 16..31: first warm-up length of the chunk-parallel scans, in positions (0 = the default, max(1.5K, 32);
- * the long second warm-up is four times this).  A length too short for the input costs time, never accuracy:
+/* flags bits 16..31: first warm-up length of the chunk-parallel scans, in positions (0 = chosen from the model and the
+ * scores, max(1.5K, 32) where that does not apply; the long second warm-up is four times this).  A length too short for the input costs time, never accuracy:
  * what does not verify is repaired or rescanned.  Tests use it to force those routes. */
 #define SEMICRF_WARMUP(n) ((unsigned)(n) << 16)
 
@@ -375,7 +375,7 @@ int semicrf_fwd_bwd_profiled(const float *emis, const int32_t *lengths, const fl
  *   accepted [B,2] int32 device, or NULL: [b,0] forward scan (Algorithm 1), [b,1] backward
  *             scan (Algorithm 3): > 0 = the chunk-parallel result was verified and used:
  *             1 at the first attempt, 2 after the intervals whose start had disagreed were
- *             rerun from the state their neighbour reached, 3 after the long warm-up;
+ *             rerun from the state their neighbour reached, 3 after a warm-up longer than max(1.5K, 32);
  *             0 = the sequential scan computed it (flag SEMICRF_SEQUENTIAL_SCAN, sizes the
  *             chunk-parallel kernels do not cover, a direction that call did not run, or
  *             a boundary that did not agree).

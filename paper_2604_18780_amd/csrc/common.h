@@ -30,6 +30,8 @@ constexpr double RANGE_NATS = 300.0;  // per-position growth that is supported (
 // measured, 212 by the bound, next to 33 r = 488; the window is read and written once per block only to be scaled).
 constexpr double BLOCK_NATS = 690.0;
 
+constexpr int WARM_LONGER = 1, WARM_SHORTER = 2;  // Params::warm_model
+
 struct SeqHdr {
     int L;          // clamped length
     int J;          // scaling block length (power of two <= JMAX)
@@ -102,6 +104,12 @@ struct Params {
     int spec2;          // chunk-parallel scan tasks with two waves each (tip + helper): 0 where it pays, 1 always, 2 never
     int lowmem;         // low-memory plan: interval at the spacing of Algorithm 1, a few row slots per sequence
     int warm_long;      // longest warm-up length
+    int warm_model;     // the first warm-up of a sequence comes from its model and scores (warm_plan): WARM_LONGER if that is
+                        // longer than the default, WARM_SHORTER also if it is shorter (windows are then compared by what
+                        // their entries can still contribute, and may be incomplete otherwise); 0: always the default
+    double *negl;       // [B][C] see warm_plan
+    int4 *wlen;         // [B] first warm-up; duration-dependent transitions: warm-ups of the second attempt (forward, backward)
+    float *contrast;    // [B][NCH] sum over the sampled positions of a chunk of log sum_c exp(score - largest score)
     int warm0;          // first warm-up length of the chunk-parallel scans asked for by the caller (0 = default)
     int marg_route;     // 0 automatic, 1 marginals from the stored rows of both scans, 2 per-interval recurrence
     int vit_global;     // Viterbi trace-back by pointer doubling over all nodes (test of the fallback route)
@@ -345,6 +353,21 @@ __device__ __forceinline__ double group_max(double v)
     if (CTP <= 16) v = max_across_16(v);
     if (CTP <= 32) v = max_across_32(v);
     return v;
+}
+
+template <int N>
+__device__ __forceinline__ double add_row_ror(const double v)  // v + the v of the lane N places on in its row of 16
+{
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    const int lo2 = __builtin_amdgcn_update_dpp(0, lo, 0x120 + N, 0xf, 0xf, true);
+    const int hi2 = __builtin_amdgcn_update_dpp(0, hi, 0x120 + N, 0xf, 0xf, true);
+    return v + __hiloint2double(hi2, lo2);
+}
+
+// sum over the wave, in every lane
+__device__ __forceinline__ double wave_sum(const double v)
+{
+    return add_across_32(add_across_16(add_row_ror<1>(add_row_ror<2>(add_row_ror<4>(add_row_ror<8>(v))))));
 }
 
 // max over the wave, in every lane

@@ -105,7 +105,7 @@ __global__ __launch_bounds__(1024) void k_dt_fwd(Params p, int warm, int tier, i
     const int lo = whole ? 0 : chunk * Delta;
     if (!whole && lo >= L) return;
     const int hi = whole ? L : min(lo + Delta, L);
-    const int s0 = whole ? 0 : max(lo - warm, 0);
+    const int s0 = whole ? 0 : max(lo - dt_warm(p, b, 0, tier, warm), 0);
     const size_t row0 = (size_t)b * (p.T + 1);
     const double2 *EI = p.EI + row0 * C;
     const int *nb = p.nbase + row0 * C;
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(1024) void k_dt_bwd(Params p, int warm, int tier, i
     const int lo = mode == 1 ? 0 : chunk * Delta;
     if (mode != 1 && lo >= L) return;
     const int hi = mode == 1 ? L : min(lo + Delta, L);
-    const int s1 = mode == 0 ? min(hi + warm, L) : hi;  // where this task's recurrence starts
+    const int s1 = mode == 0 ? min(hi + dt_warm(p, b, 1, tier, warm), L) : hi;  // where this task's recurrence starts
     const size_t row0 = (size_t)b * (p.T + 1);
     const double2 *EI = p.EI + row0 * C;
     const int *nb = p.nbase + row0 * C;

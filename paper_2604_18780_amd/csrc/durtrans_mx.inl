@@ -177,7 +177,7 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tie
     if (!any) return;
     const DxTask tk = dx_task(p, blockIdx.x * DX_TASKS + q, 0, tier);
     const int L = tk.L, J = tk.J, lo = tk.lo, hi = tk.hi;
-    const int s0 = max(lo - warm, 0);
+    const int s0 = max(lo - dt_warm(p, tk.b, 0, tier, warm), 0);
     const size_t row0 = (size_t)tk.b * (p.T + 1);
     const double2 *EI = p.EI + row0 * C + (cv ? c : 0);
     const int *nb = p.nbase + row0 * C + (cv ? c : 0);
@@ -442,7 +442,7 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
     if (!any) return;
     const DxTask tk = dx_task(p, blockIdx.x * DX_TASKS + q, 1, tier);
     const int L = tk.L, J = tk.J, lo = tk.lo, hi = tk.hi;
-    const int s1 = min(hi + warm, L);
+    const int s1 = min(hi + dt_warm(p, tk.b, 1, tier, warm), L);
     const size_t row0 = (size_t)tk.b * (p.T + 1);
     const double2 *EI = p.EI + row0 * C + cc0;
     const int *nb = p.nbase + row0 * C + cc0;

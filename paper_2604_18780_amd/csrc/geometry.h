@@ -32,6 +32,21 @@ constexpr int mg_waves_per_simd(int CT, int NKW) { return (CT <= 32 && NKW <= 32
 
 constexpr size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// What the choice of the first warm-up reads and leaves (one array of the workspace): per sequence and label what the
+// comparison of two windows takes for negligible, per sequence the warm-up lengths, per chunk the sampled contrast.
+struct WarmLayout {
+    size_t negl, len, contrast, total;
+};
+constexpr WarmLayout warm_layout(int B, int C, int NCH)
+{
+    WarmLayout l{};
+    l.negl = 0;
+    l.len = align_up((size_t)B * C * 8);
+    l.contrast = l.len + align_up((size_t)B * 4 * 4);
+    l.total = l.contrast + align_up((size_t)B * NCH * 4);
+    return l;
+}
+
 constexpr int pow2_ge8(int x)
 {
     int r = 8;

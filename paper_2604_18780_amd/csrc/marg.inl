@@ -291,15 +291,6 @@ __global__ __launch_bounds__(NT) void k_mg_te(Params p)
 // start and end there are formed with the reciprocals of its two factors, and go out as the gradients of the boundary
 // projections and, summed over the labels, as the boundary posterior.  (Genomic shape with all of them: 196 us, 665 us
 // for the call; with the interval kernel's own recurrence the call takes 1025 us.)
-template <int N>
-__device__ __forceinline__ double add_row_ror(const double v)  // v + the v of the lane N places on in its row of 16
-{
-    const int lo = __double2loint(v), hi = __double2hiint(v);
-    const int lo2 = __builtin_amdgcn_update_dpp(0, lo, 0x120 + N, 0xf, 0xf, true);
-    const int hi2 = __builtin_amdgcn_update_dpp(0, hi, 0x120 + N, 0xf, 0xf, true);
-    return v + __hiloint2double(hi2, lo2);
-}
-
 template <int CT, int NKW, bool BT>
 __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Params p)
 {
@@ -346,14 +337,27 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
     if (tb == L) {  // v_L = E_L
         if (writer) ring[r * RS + c] = EIc[(size_t)L * C].x;
     } else if (tb == t1) {  // the state the backward task started from
-        const double *ck = p.ckB + ((size_t)b * (N + 1) + iv + 1) * ((size_t)KC + C);
+        // (or, where that may be incomplete in what no longer matters to the scan, the one the task above reached there,
+        // divided by the common factor of the two)
+        const size_t at = ((size_t)b * (N + 1) + iv + 1) * ((size_t)KC + C);
+        const double *ck = ((p.warm_model & WARM_SHORTER) ? p.ckB2 : p.ckB) + at;
+        double fi = 1.0;
+        if (p.warm_model & WARM_SHORTER) {
+            double s1 = lane < C ? p.ckB[at + KC + lane] : 0.0, s2 = lane < C ? ck[KC + lane] : 0.0;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                s1 += __shfl_xor(s1, off);
+                s2 += __shfl_xor(s2, off);
+            }
+            fi = s1 / s2;
+        }
         const int tm = t1 % K;
         if (cval) {  // lane (g, c): the window rows at distances g, g + GW, ... of its label (no index divisions)
 #pragma unroll 8
             for (int d = g; d < K; d += G::GW) {
                 int sl = tm + d;  // checkpoint slot of the position at that distance
                 sl -= sl >= K ? K : 0;
-                ring[(r + d) * RS + c] = ck[(size_t)sl * C + c];
+                ring[(r + d) * RS + c] = fi * ck[(size_t)sl * C + c];
             }
         }
     } else {

@@ -194,6 +194,7 @@ int make_plan(int B, int T, int K, int C, int ckpt_interval, int want_grad, Plan
     sz[PL_SUMR] = g * b * np * c * 8;
     sz[PL_CARRY] = g * b * np * c * 8;
     sz[PL_SINK] = (size_t)SINK_DOUBLES * 8;
+    sz[PL_WARM] = warm_layout(B, C, pl->NCH).total;
     pl->narrays = PL_COUNT;
     size_t off = 0;
     for (int j = 0; j < PL_COUNT; ++j) {

@@ -27,7 +27,7 @@ struct Plan {
 enum PlanArray {
     PL_HDR = 0, PL_NU, PL_CHSUM, PL_CHMAX, PL_TABMAX, PL_W, PL_ETR, PL_EI, PL_SPEC, PL_NBASE, PL_CKA, PL_CKB,
     PL_CKYA, PL_CKYB, PL_ALOC, PL_ALOCY, PL_PARTD, PL_PARTTR, PL_TOT, PL_SUMR, PL_CARRY, PL_MEAN, PL_CKA2,
-    PL_CKB2, PL_CKYA2, PL_CKYB2, PL_OUT0, PL_INL, PL_BLOC, PL_BLOCY, PL_SINK, PL_COUNT
+    PL_CKB2, PL_CKYA2, PL_CKYB2, PL_OUT0, PL_INL, PL_BLOC, PL_BLOCY, PL_SINK, PL_WARM, PL_COUNT
 };
 
 // Kinds of plan (the want_grad argument of semicrf_workspace_bytes): 0 forward only, 1 gradients (with the row
@@ -35,10 +35,18 @@ enum PlanArray {
 // stored-row marginals, 3 the same plan as 1 (a caller that asks for that route by flag); plus PLAN_LOW_MEMORY.
 constexpr int PLAN_LOW_MEMORY = 8;
 
-// First warm-up length of the chunk-parallel sum scans: one and a half maximal segment lengths.
-// The products of positive maps forget their start fast enough that the boundary mismatch is at the
-// rounding floor there on all workloads (it reaches 1e-11 at 1.25 K; the acceptance bound is 1e-10).
-inline int sum_warmup(int K) { return 3 * K / 2 < 32 ? 32 : (3 * K + 1) / 2; }
+// First warm-up length of the chunk-parallel sum scans where it does not come from the model (warm_plan in warm.inl): one
+// and a half maximal segment lengths, so that the K-deep windows agree entry by entry.  The products of positive maps
+// forget their start fast enough that the boundary mismatch is at the rounding floor there on all workloads (it reaches
+// 1e-11 at 1.25 K; the acceptance bound is 1e-10).
+constexpr int sum_warmup(int K) { return 3 * K / 2 < 32 ? 32 : (3 * K + 1) / 2; }
+
+// Longest warm-up.  Where the choice takes the model into account it is at least WARM_LONG_LEAST: labels that reach each
+// other only over several steps take as long for short segments as for long ones (160 .. 700 positions at K = 6 .. 48 and
+// bands of 2 in 19 .. 60 labels), and what is rejected here is scanned sequentially (K = 6, C = 42, band 2, T = 2801:
+// 1687 us after 64 positions).
+constexpr int long_warmup(int K) { return 8 * K < 64 ? 64 : 8 * K; }
+constexpr int WARM_LONG_LEAST = 768;
 
 // Single-wave tasks a compute unit holds at once for these sizes (scan kernel, interval kernel); false when
 // the one-wave kernels do not apply.

@@ -80,11 +80,12 @@ __device__ __forceinline__ void colsum_body(const Params &p, const int b, const 
 {
     __shared__ double red[COL_NG * 256];  // C <= 256
     __shared__ double redm[NT / 64], redx[NT / 64];
-    __shared__ float reds[NT / 64], rede[NT / 64];
+    __shared__ float reds[NT / 64], rede[NT / 64], redc[NT / 64];
     const int tid = threadIdx.x;
     const int C = p.C, L = seq_len(p, b);
     const int u0 = ch * PREP_CH;
     const int u1 = min(u0 + PREP_CH, L);
+    const double smp = p.warm_model ? warm_load<ET>(p, b, ch, L) : 0.0;
     double mx = 0.0, ex = 0.0;
     for (int it = tid; it < COL_NG * C; it += NT) {
         const int t0 = u0 + it / C * JMAX, n = min(L - t0, JMAX);
@@ -136,7 +137,9 @@ __device__ __forceinline__ void colsum_body(const Params &p, const int b, const 
         mps = fmaxf(mps, __shfl_xor(mps, off));
         mpe = fmaxf(mpe, __shfl_xor(mpe, off));
     }
+    const float con = p.warm_model ? warm_sample(p, ch, L, smp) : 0.f;
     if ((tid & 63) == 0) {
+        redc[tid >> 6] = con;
         redm[tid >> 6] = mx;
         redx[tid >> 6] = ex;
         reds[tid >> 6] = mps;
@@ -157,6 +160,7 @@ __device__ __forceinline__ void colsum_body(const Params &p, const int b, const 
             mpe = fmaxf(mpe, rede[i]);
         }
         p.chmax[(size_t)b * p.NCH + ch] = make_float2(float_above(mx + (double)mps + (double)mpe), float_above(ex));
+        if (p.warm_model) p.contrast[(size_t)b * p.NCH + ch] = ((redc[0] + redc[1]) + redc[2]) + redc[3];
     }
 }
 
@@ -348,8 +352,13 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
     __shared__ double red2[2 * NT];
     __shared__ double redm[NT / 64], redx[NT / 64];
     __shared__ SeqHdr hs;
-    const int b = blockIdx.y, ch = blockIdx.x, tid = threadIdx.x;
+    // the first workgroup of a sequence chooses its first warm-up, where that comes from the model
+    const int b = blockIdx.y, ch = (int)blockIdx.x - (p.warm_model ? 1 : 0), tid = threadIdx.x;
     const int C = p.C, NCH = p.NCH;
+    if (ch < 0) {
+        warm_plan(p, b, lds_raw, red2);
+        return;
+    }
     double *seg = lds_raw, *nus = lds_raw + PREP_NSEG * C;
     int L, J;
     double off = 0.0;  // threads tid < C: centred prefix sum at the chunk's first position

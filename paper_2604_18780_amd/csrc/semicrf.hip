@@ -59,6 +59,7 @@ namespace {
 using namespace semicrf_impl;
 
 // The kernels, stage by stage (each file is included here, inside this namespace):
+#include "warm.inl"         // first warm-up of the scans from the model and the scores
 #include "prefix.inl"     // Eq. 1-2: baseline, centred prefix sums, block exponents, (ES, 1/ES)
 #include "verify.inl"     // verification of the chunk-parallel scans
 #include "scan_seq.inl"   // sequential scans (fallback of the chunk-parallel ones)
@@ -110,6 +111,10 @@ void bind_workspace(Params &p, const Plan &pl, void *ws)
     p.bloc = (double *)(w + pl.off[28]);
     p.blocY = (double *)(w + pl.off[29]);
     p.sink = (double *)(w + pl.off[30]);
+    const WarmLayout wl = warm_layout(p.B, p.C, pl.NCH);
+    p.negl = (double *)(w + pl.off[31] + wl.negl);
+    p.wlen = (int4 *)(w + pl.off[31] + wl.len);
+    p.contrast = (float *)(w + pl.off[31] + wl.contrast);
     // what the report reads comes first: its place does not depend on how many tasks the scans were cut into
     p.spec_rep = (double *)(w + pl.off[8]);
     p.spec_ok = (int *)(p.spec_rep + (size_t)p.B * 2);
@@ -131,7 +136,7 @@ void launch_prefix(const Params &p, hipStream_t st)
     if (lds > 64 * 1024)
         (void)hipFuncSetAttribute((const void *)k_prefix<BTERMS, ET, INLINE>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)lds);
-    hipLaunchKernelGGL((k_prefix<BTERMS, ET, INLINE>), dim3(p.NCH, p.B), dim3(NT), lds, st, p);
+    hipLaunchKernelGGL((k_prefix<BTERMS, ET, INLINE>), dim3(p.NCH + (p.warm_model ? 1 : 0), p.B), dim3(NT), lds, st, p);
 }
 
 template <int ET>
@@ -246,6 +251,18 @@ int launch_interval(const Params &p, const Plan &pl, hipStream_t st)
     return check_launch();
 }
 
+// negl: directions whose windows may be compared by what their entries can still contribute.  The template argument is the
+// most entries a thread takes.
+void launch_spec_cmp(const Params &p, hipStream_t st, int ndir, int tier, int negl)
+{
+    const dim3 grid(p.N, p.B, ndir);
+    const int G = NT / p.C, per = (p.warm_model & WARM_SHORTER) ? (p.K + G - 1) / G : 0;
+    if (per == 0) hipLaunchKernelGGL(k_spec_cmp<0>, grid, dim3(NT), 0, st, p, tier, 0, 0, 0);
+    else if (per <= 2) hipLaunchKernelGGL(k_spec_cmp<2>, grid, dim3(NT), 0, st, p, tier, negl, G, per);
+    else if (per <= 8) hipLaunchKernelGGL(k_spec_cmp<8>, grid, dim3(NT), 0, st, p, tier, negl, G, per);
+    else hipLaunchKernelGGL(k_spec_cmp<WARM_PER>, grid, dim3(NT), 0, st, p, tier, negl, G, per);
+}
+
 // Chunk-parallel scan: returns 1 when it does not apply to these sizes.
 // two: the form with two waves per task.
 template <int CT, int NKW, bool RETRY>
@@ -289,7 +306,7 @@ int launch_spec_k(const Params &p, hipStream_t st, bool both, int warm, int tier
     if (tier == 0) rc = launch_spec_tasks<CT, NKW, false>(p, st, both, warm, tier, rest, two);
     else rc = launch_spec_tasks<CT, NKW, true>(p, st, both, warm, tier, rest, two);
     if (rc != SEMICRF_OK) return rc;
-    hipLaunchKernelGGL(k_spec_cmp, dim3(p.N, p.B, both ? 2 : 1), dim3(NT), 0, st, p, tier);
+    launch_spec_cmp(p, st, both ? 2 : 1, tier, 3);
     return check_launch();
 }
 
@@ -371,6 +388,12 @@ int launch_mg(const Params &p, hipStream_t st)
     return SEMICRF_EUNSUPPORTED;
 }
 
+// Sizes for which the first warm-up comes from the model, unless the caller has named one.
+bool warm_from_model(const Params &p)
+{
+    return p.spec && p.warm0 == 0 && !p.mscan && p.C >= 2 && p.C <= 64 && p.K <= WARM_PER * (NT / p.C);
+}
+
 int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hipStream_t st,
         int mode /*0 cum, 1 logz, 2 fwd_bwd*/, StageTimer *tm = nullptr)
 {
@@ -390,7 +413,7 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
     bind_workspace(p, pl, workspace);
     // warm-up lengths of the chunk-parallel scan: one and a half maximal segment lengths first,
     // eight for the (sequence, direction) pairs that fails for, the sequential scan for the rest
-    int warm[2] = {sum_warmup(p.K), 8 * p.K < 64 ? 64 : 8 * p.K};
+    int warm[2] = {sum_warmup(p.K), long_warmup(p.K)};
     if (p.warm0 > 0) warm[0] = p.warm0, warm[1] = 4 * p.warm0;  // the caller's first warm-up length (flags bits 16..31)
     p.warm_long = warm[1];
     p.spec = p.spec && mode != 0 && spec_applies(p.K, p.C);
@@ -406,6 +429,10 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
         p.marg = 0;  // the one-wave kernel indexes a sequence's rows with 32 bits
     // (the partial-sum arrays are planned for N * pl.msplit either way; a part holds at least K positions)
     if (p.marg && p.K < 128 && pl.Delta / pl.msplit >= p.K) p.msplit = pl.msplit;
+    // Windows that agree only in what they still contribute serve the scans and, where they come complete from the neighbour
+    // (intervals of at least K positions), the stored-row marginals; the interval kernels count every entry.
+    if (warm_from_model(p)) p.warm_model = WARM_LONGER | ((mode == 1 || (p.marg && p.Delta >= p.K)) ? WARM_SHORTER : 0);
+    if (p.warm_model) p.warm_long = warm[1] = warm[1] < WARM_LONG_LEAST ? WARM_LONG_LEAST : warm[1];
     T.mark();
     rc = launch_prep(p, st);
     T.mark();
@@ -893,6 +920,9 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
     p.dtMA = dx.ok ? (double *)(dw + dl.ma) : nullptr;
     p.dtMB = (double *)(dw + dl.mb);
     p.dtE = (int2 *)(dw + dl.eab);
+    p.warm_model = warm_from_model(p) ? WARM_LONGER | WARM_SHORTER : 0;
+    p.warm_long = long_warmup(p.K);
+    if (p.warm_model && p.warm_long < WARM_LONG_LEAST) p.warm_long = WARM_LONG_LEAST;
     rc = launch_prep(p, st);
     if (rc != SEMICRF_OK) return rc;
     const size_t kcc = (size_t)p.K * p.C * p.C;
@@ -903,8 +933,7 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
         hipLaunchKernelGGL(k_dt_tables, dim3((unsigned)((ntable + NT - 1) / NT)), dim3(NT), 0, st, p);
     const int ndir = grad ? 2 : 1;
     if (p.spec) {
-        const int warm[2] = {sum_warmup(p.K), 8 * p.K < 64 ? 64 : 8 * p.K};
-        p.warm_long = warm[1];
+        const int warm[2] = {sum_warmup(p.K), p.warm_long};
         for (int tier = 0; tier < 2; ++tier) {
             rc = dx.ok ? launch_dx_fwd_any(p, dx, st, warm[tier], tier)
                        : launch_dt_fwd_any(p, g, st, p.B * p.N, warm[tier], tier, 0);
@@ -914,7 +943,8 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
                 else rc = launch_dt_bwd_any(p, g, st, p.B * p.N, warm[tier], tier, 0);
                 if (rc != SEMICRF_OK) return rc;
             }
-            hipLaunchKernelGGL(k_spec_cmp, dim3(p.N, p.B, ndir), dim3(NT), 0, st, p, tier);
+            // (the forward windows hold what is still to arrive at each position: those are compared as they are)
+            launch_spec_cmp(p, st, ndir, tier, 2);
             hipLaunchKernelGGL(k_spec_fix, dim3(p.B, ndir), dim3(64), 0, st, p, ndir, tier);
         }
     } else {

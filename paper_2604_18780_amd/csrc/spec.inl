@@ -13,10 +13,12 @@
 //   backward task j: the mirror image from above (-> ckB[j+1], ckB2[j]).
 // Nothing is taken on trust: k_spec_cmp compares, for every chunk boundary, the state
 // the previous chunk actually reached with the warm-up state the next chunk started
-// from, entry by entry, after removing their common scale factor.  If all boundaries of
-// a (sequence, direction) agree to SPEC_TOL the warm-up states ARE the sequential
-// states to that relative accuracy (perturbations of the start do not grow: the maps
-// are non-expansive in the projective metric); spec_settle then chains the scale
+// from, entry by entry or by what an entry can still contribute, after removing their common scale
+// factor.  If all boundaries of a (sequence, direction) agree to SPEC_TOL the warm-up states do what the
+// sequential states do, to that relative accuracy (perturbations of the start do not grow: the maps
+// are non-expansive in the projective metric).  The warm-up is 1.5 K positions, or what the model asks
+// for (warm_plan): genomic shape 96 -> 40, scans 310 -> 278 us; K = 512, C = 8 768 -> 56, 684 -> 388 us;
+// band 2 in 19 labels, K = 37 56 -> 204, so that the first attempt is accepted (225 -> 120 us).  spec_settle then chains the scale
 // factors into the checkpoint scales and logZ.  Otherwise the flag stays 0 and the
 // sequential scan kernel, launched after the later attempts, which returns at once for
 // accepted (sequence, direction) pairs, recomputes that pair from scratch.
@@ -39,8 +41,9 @@ struct SpecJob {
     const double *err;
 };
 __device__ __forceinline__ SpecJob spec_job(const Params &p, const int b, const int dir, const int j, const int ndir,
-                                            const int warm, const int tier, const bool settles)
+                                            const int deflt, const int tier, const bool settles)
 {
+    const int warm = tier < 2 ? first_warm(p, b, deflt) : deflt;
     SpecJob s;
     s.idle = s.mend = false;
     s.warm = warm;
@@ -58,12 +61,7 @@ __device__ __forceinline__ SpecJob spec_job(const Params &p, const int b, const 
     s.nint = v.nint;
     s.mend = v.nbad <= max(2, v.nint / 16);
     if (tier == 1) {
-        // The mismatch falls geometrically with the warm-up, so the length that brings the worst boundary to 1e-12
-        // follows from the one just measured; a quarter and half a segment length on top for stretches that forget
-        // more slowly.  Hopeless cases take the longest.
-        double w = (double)p.warm_long;
-        if (v.worst > 0.0 && v.worst < 0.1) w = fmin(w, 1.25 * (double)warm * (-27.7 / log(v.worst)) + 0.5 * (double)p.K);
-        s.warm = ((int)w + 3) & ~3;
+        s.warm = second_warm(p, warm, v.worst);
     }
     return s;
 }
@@ -348,8 +346,9 @@ __global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, N
         return;
     }
     if (!RETRY || !job.mend) {
-        if (dir == 0) spec_task<CT, NKW, false>(p, lds, b, j, RETRY ? job.warm : warm, false);
-        else spec_task<CT, NKW, true>(p, lds, b, j, RETRY ? job.warm : warm, false);
+        const int w = RETRY ? job.warm : first_warm(p, b, warm);
+        if (dir == 0) spec_task<CT, NKW, false>(p, lds, b, j, w, false);
+        else spec_task<CT, NKW, true>(p, lds, b, j, w, false);
         return;
     }
     // A run of adjacent boundaries that disagreed is taken by ONE wave, the task that starts at the first of them

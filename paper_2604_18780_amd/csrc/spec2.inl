@@ -334,8 +334,9 @@ __global__ __launch_bounds__(128, spec2_waves_per_simd(CT, NKW)) void k_spec2(Pa
         return;
     }
     if (!RETRY || !job.mend) {
-        if (dir == 0) spec2_task<CT, NKW, false>(p, lds_raw, b, j, RETRY ? job.warm : warm, false);
-        else spec2_task<CT, NKW, true>(p, lds_raw, b, j, RETRY ? job.warm : warm, false);
+        const int w = RETRY ? job.warm : first_warm(p, b, warm);
+        if (dir == 0) spec2_task<CT, NKW, false>(p, lds_raw, b, j, w, false);
+        else spec2_task<CT, NKW, true>(p, lds_raw, b, j, w, false);
         return;
     }
     if (!spec_bad(job, dir ? j + 1 : j) || spec_bad(job, dir ? j + 2 : j - 1)) return;

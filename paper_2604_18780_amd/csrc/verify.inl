@@ -9,17 +9,52 @@ constexpr int SPEC_ATTEMPTS = 3;
 // (forward) / chunk j (backward) reached at position j*Delta with the warm-up state the
 // neighbouring chunk started from.  Number 0 is no boundary: its workgroup checks that the forward scan's final
 // message vector can be summed (entry nint of the mismatches).
-__global__ __launch_bounds__(NT) void k_spec_cmp(Params p, int tier)
+//
+// negl: directions (bit 0 forward, bit 1 backward) whose windows are compared by what their entries can still contribute (p.negl,
+// see warm_plan): the difference of two entries counts against the larger of the two, or against negl[c] times the largest
+// newer entry of the label, whichever is more.  At every later position an entry's difference then adds at most 1e-10 / K of
+// what the newer entry adds there, so the states agree to 2e-10 in all they do, as with the plain comparison: everything a
+// state does later is a sum of positive multiples of these direct contributions.
+template <int PER>
+__global__ __launch_bounds__(NT) void k_spec_cmp(Params p, int tier, int negl, int G, int per)
 {
-    __shared__ double part[NT / 64];
+    __shared__ double part[NT / 64], newer[NT];
     const int j = blockIdx.x, b = blockIdx.y, dir = blockIdx.z, tid = threadIdx.x;
     const int lane = tid & 63, wv = tid >> 6;
     if (tier > 0 && p.spec_ok[b * 2 + dir]) return;
+    const int K = p.K, KC = p.K * p.C, C = p.C, N = p.N;
+    const size_t ckstride = (size_t)KC + C;
+    const size_t at = (size_t)b * (N + 1) + j;
+    const double *A = (dir ? p.ckB : p.ckA) + at * ckstride;    // warm-up state
+    const double *A2 = (dir ? p.ckB2 : p.ckA2) + at * ckstride;  // reached state
+    // thread (range of per <= PER distances, label), G ranges: all its entries are requested before anything is waited for
+    const int g = tid / C, c = tid - g * C, d0 = g * per;
+    const int nu = g < G ? min(per, K - d0) : 0;  // entries of this thread (none where that is negative)
+    double x[PER > 0 ? PER : 1], y[PER > 0 ? PER : 1];
+    const bool contrib = PER > 0 && ((negl >> dir) & 1);
+    bool shorter = false;
+    if (PER > 0) {
+        shorter = p.wlen[b].x < sum_warmup(K);
+        const int tm = j * p.Delta % K;
+        int sl = dir ? tm + d0 : tm - d0;  // slot of the position at that distance
+        sl += dir ? (sl >= K ? -K : 0) : (sl < 0 ? K : 0);
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int o = u < nu ? sl * C + c : 0;
+            x[u] = A2[o];
+            y[u] = A[o];
+            sl += dir ? 1 : -1;
+            sl = dir ? (sl == K ? 0 : sl) : (sl < 0 ? K - 1 : sl);
+        }
+    }
+    const double Y = (dir ? p.ckYB : p.ckYA)[at], Y2 = (dir ? p.ckYB2 : p.ckYA2)[at];
+    // sums of the two message vectors (their ratio is the common scale factor); C <= 64 here:
+    // every wave forms them, in lane order
+    double s1 = lane < C ? A[KC + lane] : 0.0, s2 = lane < C ? A2[KC + lane] : 0.0;
+    const double m1 = s1, m2 = s2, ng = contrib ? p.negl[(size_t)b * C + c] : 0.0;
     const int L = p.hdr[b].L;
     const int nint = (L + p.Delta - 1) / p.Delta;
     if (j >= nint) return;
-    const int KC = p.K * p.C, C = p.C, N = p.N;
-    const size_t ckstride = (size_t)KC + C;
     const size_t so = ((size_t)b * 2 + dir) * (N + 1);
     if (j == 0) {
         if (dir == 0 && wv == 0) {
@@ -27,18 +62,11 @@ __global__ __launch_bounds__(NT) void k_spec_cmp(Params p, int tier)
             double s = lane < C ? e[KC + lane] : 0.0;
 #pragma unroll
             for (int off = 1; off < 64; off <<= 1) s += __shfl_xor(s, off);
-            const double Y = p.ckYA2[(size_t)b * (N + 1) + nint];
-            if (lane == 0) p.spec_err[so + nint] = (s > 0.0 && s < DBL_MAX && Y == Y) ? 0.0 : DBL_MAX;
+            const double Yl = p.ckYA2[(size_t)b * (N + 1) + nint];
+            if (lane == 0) p.spec_err[so + nint] = (s > 0.0 && s < DBL_MAX && Yl == Yl) ? 0.0 : DBL_MAX;
         }
         return;
     }
-    const double *A = (dir ? p.ckB : p.ckA) + ((size_t)b * (N + 1) + j) * ckstride;    // warm-up state
-    const double *A2 = (dir ? p.ckB2 : p.ckA2) + ((size_t)b * (N + 1) + j) * ckstride;  // reached state
-    const double Y = (dir ? p.ckYB : p.ckYA)[(size_t)b * (N + 1) + j];
-    const double Y2 = (dir ? p.ckYB2 : p.ckYA2)[(size_t)b * (N + 1) + j];
-    // sums of the two message vectors (their ratio is the common scale factor); C <= 64 here:
-    // every wave forms them, in lane order
-    double s1 = lane < C ? A[KC + lane] : 0.0, s2 = lane < C ? A2[KC + lane] : 0.0;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         s1 += __shfl_xor(s1, off);
@@ -47,19 +75,57 @@ __global__ __launch_bounds__(NT) void k_spec_cmp(Params p, int tier)
     const double f = s2 / s1;  // reached = f * 2^(Y2-Y) * warm-up, entry by entry, if they agree
     double err = 0.0;
     if (!(s1 > 0.0) || !(s2 > 0.0) || !(f > 0.0) || !(f < DBL_MAX)) err = DBL_MAX;
-#pragma unroll 8
-    for (int i = tid; i < KC + C; i += NT) {
-        const double x = A2[i], y = A[i] * f;
+    auto differ = [&](const double x, const double y, const double least) {
         const double m = fmax(fabs(x), fabs(y));
-        if (m > 1e-290) err = fmax(err, fabs(x - y) / m);
-        if (!(m < DBL_MAX)) err = DBL_MAX;
-    }
+        // (an estimate of the reciprocal, good to eight digits, decides as well as a division; 1e307: no message is larger)
+        if (m > 1e-290) err = fmax(err, fabs(x - y) * __builtin_amdgcn_rcp(fmax(m, least)));
+        if (!(m < 1e307)) err = DBL_MAX;
+    };
+    auto over_waves = [&]() {  // the largest over the workgroup, in every thread
+        err = wave_max(err);
+        if (lane == 0) part[wv] = err;
+        __syncthreads();
+        for (int i = 0; i < NT / 64; ++i) err = fmax(err, part[i]);
+    };
+    if (wv == 0 && lane < C) differ(m2, m1 * f, 0.0);
+    const double err0 = err;
+    if (PER == 0) {
+#pragma unroll 8
+        for (int i = tid; i < KC; i += NT) differ(A2[i], A[i] * f, 0.0);
+        over_waves();
+    } else {
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) err = fmax(err, __shfl_xor(err, off));
-    if (lane == 0) part[wv] = err;
-    __syncthreads();
+        for (int u = 0; u < PER; ++u) {
+            x[u] = u < nu ? x[u] : 0.0;
+            y[u] = u < nu ? y[u] * f : 0.0;
+        }
+        // entry by entry first, where the warm-up was long enough for that
+        if (!contrib || !shorter) {
+#pragma unroll
+            for (int u = 0; u < PER; ++u) differ(x[u], y[u], 0.0);
+            over_waves();
+        }
+        if (contrib && (shorter || err > SPEC_TOL)) {
+            double big = 0.0;
+#pragma unroll
+            for (int u = 0; u < PER; ++u) big = fmax(big, fmin(x[u], y[u]));
+            newer[tid] = big;
+            __syncthreads();
+            err = err0;
+            big = 0.0;
+            for (int g0 = 0; g0 < min(g, G); g0 += 8) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) big = fmax(big, newer[min(g0 + i, g - 1) * C + c]);
+            }
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                differ(x[u], y[u], ng * big);
+                big = fmax(big, fmin(x[u], y[u]));
+            }
+            over_waves();
+        }
+    }
     if (tid == 0) {
-        for (int i = 1; i < NT / 64; ++i) err = fmax(err, part[i]);
         p.spec_err[so + j] = err;
         p.spec_lr[so + j] = (Y2 - Y) + log2(f);
     }
@@ -150,9 +216,9 @@ __device__ __forceinline__ void spec_settle(const Params &p, const int b, const 
         }
     }
     if (lane != 0) return;
-    // which attempt verified it: 1 the first, 2 after repairs, 3 after a longer warm-up (what the later attempts did
-    // was decided by the number of boundaries that had disagreed before)
-    const int code = tier == 0 ? 1 : (lr[0] <= (double)max(2, nint / 16) ? 2 : 3);
+    // how it was verified: 1 after the default warm-up or a shorter one, 2 after repairs, 3 after a longer warm-up: chosen
+    // from the model, or by a later attempt (what those did was decided by the number of boundaries that had disagreed before)
+    const int code = tier == 0 ? (first_warm(p, b, 0) > sum_warmup(p.K) + 3 ? 3 : 1) : (lr[0] <= (double)max(2, nint / 16) ? 2 : 3);
     p.spec_rep[b * 2 + dir] = v.worst;
     p.spec_ok[b * 2 + dir] = v.ok ? code : 0;
     lr[0] = (double)v.nbad;
@@ -166,6 +232,11 @@ __global__ __launch_bounds__(64) void k_spec_fix(Params p, int ndir, int tier)
     const int b = blockIdx.x, dir = blockIdx.y, lane = threadIdx.x;
     if (tier > 0 && p.spec_ok[b * 2 + dir]) return;
     SpecVerdict v = spec_verdict(p, b, dir, lane);
+    if (p.warm_model && tier == 0 && lane == 0) {
+        // the next attempt's warm-up, as spec_job works it out
+        const int w0 = p.wlen[b].x;
+        (&p.wlen[b].y)[dir] = v.ok ? w0 : max(w0, second_warm(p, w0, v.worst));
+    }
     if (dir == 1) v.ok = v.ok && spec_verdict(p, b, 0, lane).ok;
     spec_settle(p, b, dir, ndir, tier, v, lane);
 }

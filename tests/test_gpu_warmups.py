@@ -1,0 +1,82 @@
+"""Warm-ups from the model: windows that agree only in what they still contribute.  Durations so long that the warm-up is a fraction
+of the window (with the gradients of durations that hardly occur, which come from the neighbouring interval's window), label counts
+at the edges of the comparison's shares, models that the choice misjudges (long durations favoured, forbidden transitions), one
+transition matrix per duration, and a workspace full of NaN."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2604_18780_amd import binding as sb
+from paper_2604_18780_amd import synth
+from test_gpu_parity import assert_outputs_match_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def case(T, K, C, kind, B=2):
+    w = synth.small_random(T + 7 * K + C, B, T, K, C, ragged=True)
+    w.lengths[:] = ([T, T - K // 2 - 1, 0] * B)[:B]
+    if kind == "band":
+        i = np.arange(C)
+        d = np.abs(i[:, None] - i[None, :])
+        w.trans[np.minimum(d, C - d) > 1] = -1e4
+    elif kind == "long":  # what a warm-up of the predicted length leaves out decides
+        w.dur += (0.25 * np.arange(K, dtype=np.float32))[:, None]
+    elif kind == "forbidden durations":
+        w.dur[: K // 2] = -1e4
+    elif kind == "confident":
+        w.emis[:, :, 0] += 9.0
+    return w
+
+
+def train(w, delta):
+    ws = sb.alloc_workspace(w.B, w.T, w.K, w.C, delta, 1, "cuda:0").fill_(255)
+    out = sb.semicrf_fwd_bwd(dev(w.emis), dev(w.lengths), dev(w.trans), dev(w.dur), None, delta, workspace=ws)
+    acc = sb.semicrf_scan_report(ws, w.B, w.T, w.K, w.C, delta, 1)[0].cpu().numpy()
+    return [o.double().cpu().numpy() for o in out], acc
+
+
+@pytest.mark.parametrize("T,K,C,delta", [(900, 64, 24, 96), (905, 65, 24, 72), (700, 37, 19, 40), (600, 32, 64, 64), (603, 40, 33, 40),
+                                         (1500, 130, 8, 136), (2100, 512, 8, 512), (1300, 256, 16, 256), (900, 128, 32, 128),
+                                         (500, 17, 3, 24), (400, 8, 2, 8), (330, 60, 15, 64)])
+def test_rare_durations(T, K, C, delta):
+    w = case(T, K, C, "plain")
+    out, acc = train(w, delta)
+    r = oracle.fwd_bwd(w.emis, w.lengths, w.trans, w.dur)
+    assert (acc[w.lengths > 0] >= 1).all()
+    assert_outputs_match_oracle(out, r)
+    # every duration, however rare: the scans agree to 2e-10 a boundary, the rest is the rounding of the float (6e-8)
+    some = r.grad_dur > 1e-30
+    rel = np.abs(out[3] - r.grad_dur)[some] / r.grad_dur[some]
+    print(f"[case] T={T} K={K} C={C} relative error of grad_dur {rel.max():.1e} down to {r.grad_dur[some].min():.1e}", flush=True)
+    assert rel.max() <= 1e-6
+    lz = sb.semicrf_logz_fwd(dev(w.emis), dev(w.lengths), dev(w.trans), dev(w.dur)).double().cpu().numpy()
+    assert np.abs(lz - r.logz).max() <= 1e-5 * np.abs(r.logz).max()
+
+
+@pytest.mark.parametrize("T,K,C", [(800, 60, 10), (1200, 6, 20), (700, 130, 7), (500, 20, 40)])
+@pytest.mark.parametrize("kind", ["band", "long", "forbidden durations", "confident"])
+def test_models_the_choice_may_misjudge(T, K, C, kind):
+    w = case(T, K, C, kind, B=3)
+    r = oracle.fwd_bwd(w.emis, w.lengths, w.trans, w.dur)
+    for delta in (0, max(K, 40)):
+        out, acc = train(w, delta)
+        print(f"[case] {kind} T={T} K={K} C={C} interval {delta} verified at {acc.tolist()}", flush=True)
+        assert_outputs_match_oracle(out, r)
+
+
+@pytest.mark.parametrize("T,K,C", [(700, 64, 8), (500, 40, 24), (600, 200, 3), (300, 18, 32), (400, 512, 8)])
+@pytest.mark.parametrize("kind", ["plain", "band", "long"])
+def test_duration_dependent_transitions(T, K, C, kind):
+    w = case(T, K, C, kind)
+    t3 = synth.duration_transitions(w, 5, 0.2)
+    r = oracle.fwd_bwd_durtrans(w.emis, w.lengths, t3, w.dur)
+    for delta in (0, 64):
+        ws = sb.alloc_durtrans_workspace(w.B, T, K, C, delta, True, "cuda:0").fill_(255)
+        out = sb.semicrf_fwd_bwd_durtrans(dev(w.emis), dev(w.lengths), dev(t3), dev(w.dur), None, delta, workspace=ws)
+        assert_outputs_match_oracle([o.double().cpu().numpy() for o in out], r)
