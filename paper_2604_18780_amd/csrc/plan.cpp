@@ -87,15 +87,15 @@ int auto_interval(int B, int T, int K, int C)
 // longer per position than one, and shorter intervals make more boundaries to compare, so halving pays only where the
 // positions saved outweigh that.  Whole call, D against D/2: K = 64, C = 24 (W = 96): D = 400 226 -> 212 us, 288 185 -> 187,
 // 240 162 -> 161, 208 152 -> 154, 192 146 -> 150, 160 132 -> 143, 96 108 -> 123; K = 16, C = 24 (W = 32): D = 128
-// 87.3 -> 85.8, 96 76.9 -> 80.1, 64 69.3 -> 72.0.  (The best-score scan is bound by the issue of its maxima, two waves take
-// twice the time of one, and keeps D: 245 us either way at D = 392.)
-int forward_interval(int B, int T, int K, int C, int Delta)
+// 87.3 -> 85.8, 96 76.9 -> 80.1, 64 69.3 -> 72.0.  (The best-score scan: after a warm-up of 128 245 us
+// with D = 392 or D/2, after 40 in 193 us with D/2.)
+int forward_interval(int B, int T, int K, int C, int Delta, int warm)
 {
     int per_scan = 0, per_int = 0;
     if (!spec_applies(K, C) || !wave_tasks_per_cu(K, C, &per_scan, &per_int)) return Delta;
     const int unit = Delta % 32 == 0 ? 32 : 8;
     const int half = (Delta / 2 + unit - 1) / unit * unit;
-    if (half >= Delta || Delta < 4 * sum_warmup(K)) return Delta;
+    if (half >= Delta || Delta < 4 * warm) return Delta;
     const double tasks = (double)B * (double)(((long long)T + half - 1) / half);
     return tasks <= 256.0 * per_scan ? half : Delta;
 }
@@ -121,7 +121,7 @@ int make_plan(int B, int T, int K, int C, int ckpt_interval, int want_grad, Plan
     pl->Delta = ckpt_interval > 0 ? (ckpt_interval > T ? T : ckpt_interval)
                                   : (lowmem ? low_memory_interval(T, K) : auto_interval(B, T, K, C));
     pl->N = (int)(((long long)T + pl->Delta - 1) / pl->Delta);
-    pl->Ds = kind == 0 && !lowmem && ckpt_interval == 0 ? forward_interval(B, T, K, C, pl->Delta) : pl->Delta;
+    pl->Ds = kind == 0 && !lowmem && ckpt_interval == 0 ? forward_interval(B, T, K, C, pl->Delta, sum_warmup(K)) : pl->Delta;
     pl->Ns = (int)(((long long)T + pl->Ds - 1) / pl->Ds);
     pl->NCH = T / PREP_CH + 1;
     pl->G = (NT / C) < K ? (NT / C) : K;
@@ -203,6 +203,15 @@ int make_plan(int B, int T, int K, int C, int ckpt_interval, int want_grad, Plan
     }
     pl->total = off;
     return SEMICRF_OK;
+}
+
+int make_viterbi_plan(int B, int T, int K, int C, Plan *pl)
+{
+    const int rc = make_plan(B, T, K, C, 0, 0, pl);
+    if (rc != SEMICRF_OK) return rc;
+    if (C > 64 || !spec_applies(K, C)) return SEMICRF_EUNSUPPORTED;
+    const int warm = K > 20 ? 40 : vit_warmup(K);  // (what the model mostly asks for)
+    return make_plan(B, T, K, C, forward_interval(B, T, K, C, pl->Delta, warm), 0, pl);
 }
 
 int check_flags(unsigned flags)

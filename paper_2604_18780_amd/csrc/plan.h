@@ -48,6 +48,11 @@ constexpr int sum_warmup(int K) { return 3 * K / 2 < 32 ? 32 : (3 * K + 1) / 2; 
 constexpr int long_warmup(int K) { return 8 * K < 64 ? 64 : 8 * K; }
 constexpr int WARM_LONG_LEAST = 768;
 
+// First and longest warm-up of the best-score scan where they do not come from the model.  (What is rejected after the
+// longest is scanned sequentially, 0.4 us a position.)
+constexpr int vit_warmup(int K) { return 2 * K < 32 ? 32 : 2 * K; }
+constexpr int vit_long_warmup(int K) { return 8 * K < 256 ? 256 : 8 * K; }
+
 // Single-wave tasks a compute unit holds at once for these sizes (scan kernel, interval kernel); false when
 // the one-wave kernels do not apply.
 bool wave_tasks_per_cu(int K, int C, int *scan, int *interval);
@@ -58,14 +63,17 @@ bool spec_applies(int K, int C);
 // Automatic checkpoint interval of the default plan (one task per SIMD where the sizes allow it).
 int auto_interval(int B, int T, int K, int C);
 
-// Interval of the scans of a forward-only call whose automatic interval is Delta.
-int forward_interval(int B, int T, int K, int C, int Delta);
+// Interval of the scans of a call with one scan whose automatic interval is Delta; warm: their warm-up.
+int forward_interval(int B, int T, int K, int C, int Delta, int warm);
 
 // Checkpoint interval of the low-memory plan: the spacing of Algorithm 1, ceil(sqrt(T*K)), as a multiple of 8.
 int low_memory_interval(int T, int K);
 
 // SEMICRF_OK or the status an entry point returns for these sizes; fills *pl.
 int make_plan(int B, int T, int K, int C, int ckpt_interval, int want_grad, Plan *pl);
+
+// The plan of a decode: one scan, whose intervals are chosen by forward_interval with the best-score scan's warm-ups.
+int make_viterbi_plan(int B, int T, int K, int C, Plan *pl);
 
 // Flag combinations no entry point accepts.
 int check_flags(unsigned flags);

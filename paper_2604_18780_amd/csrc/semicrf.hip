@@ -510,6 +510,15 @@ VitLayout viterbi_layout(int B, int T, int C)
     return l;
 }
 
+void launch_vit_cmp(const Params &p, hipStream_t st, int tier)
+{
+    const dim3 grid(p.N, p.B);
+    const int G = NT / p.C, per = p.warm_model ? (p.K + G - 1) / G : 0;
+    if (per == 0) hipLaunchKernelGGL(k_vit_cmp<0>, grid, dim3(NT), 0, st, p, tier, 0, 0);
+    else if (per <= 8) hipLaunchKernelGGL(k_vit_cmp<8>, grid, dim3(NT), 0, st, p, tier, G, per);
+    else hipLaunchKernelGGL(k_vit_cmp<WARM_PER>, grid, dim3(NT), 0, st, p, tier, G, per);
+}
+
 template <int CT, int NKW>
 int launch_viterbi_k(const Params &p, hipStream_t st)
 {
@@ -521,7 +530,7 @@ int launch_viterbi_k(const Params &p, hipStream_t st)
         return SEMICRF_ELAUNCH;
     if (p.spec) {
         // chunk-parallel scan with two warm-up lengths, as for the sum recurrences
-        int warm[2] = {2 * p.K < 32 ? 32 : 2 * p.K, 8 * p.K < 64 ? 64 : 8 * p.K};
+        int warm[2] = {vit_warmup(p.K), vit_long_warmup(p.K)};
         if (p.warm0 > 0) warm[0] = p.warm0, warm[1] = 4 * p.warm0;  // the caller's first warm-up length
         if (hipFuncSetAttribute((const void *)k_vit_spec<CT, NKW, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)(SW * lds)) != hipSuccess ||
@@ -530,9 +539,9 @@ int launch_viterbi_k(const Params &p, hipStream_t st)
             return SEMICRF_ELAUNCH;
         const dim3 grid((p.B * p.N + SW - 1) / SW), block(64 * SW);
         hipLaunchKernelGGL((k_vit_spec<CT, NKW, false>), grid, block, SW * lds, st, p, warm[0]);
-        hipLaunchKernelGGL(k_vit_cmp, dim3(p.N, p.B), dim3(NT), 0, st, p, 0);
+        launch_vit_cmp(p, st, 0);
         hipLaunchKernelGGL((k_vit_spec<CT, NKW, true>), grid, block, SW * lds, st, p, warm[1]);
-        hipLaunchKernelGGL(k_vit_cmp, dim3(p.N, p.B), dim3(NT), 0, st, p, 1);
+        launch_vit_cmp(p, st, 1);
     } else {
         hipLaunchKernelGGL(k_spec_clear, dim3((2 * p.B + 63) / 64), dim3(64), 0, st, p);
     }
@@ -596,9 +605,8 @@ int launch_vit_trace(const Params &p, hipStream_t st)
 int run_viterbi(Params p, void *workspace, size_t workspace_bytes, hipStream_t st)
 {
     Plan pl;
-    int rc = make_plan(p.B, p.T, p.K, p.C, 0, 0, &pl);
+    int rc = make_viterbi_plan(p.B, p.T, p.K, p.C, &pl);
     if (rc != SEMICRF_OK) return rc;
-    if (p.C > 64 || !spec_applies(p.K, p.C)) return SEMICRF_EUNSUPPORTED;
     if (((size_t)p.T + 1) * p.C >= ((size_t)1 << 31)) return SEMICRF_EUNSUPPORTED;  // node ids are 32-bit
     if (2 * (size_t)(p.K + VBP_TILE) * p.C * sizeof(double) > LDS_LIMIT) return SEMICRF_EUNSUPPORTED;  // back-pointer tiles
     const VitLayout vl = viterbi_layout(p.B, p.T, p.C);
@@ -621,6 +629,8 @@ int run_viterbi(Params p, void *workspace, size_t workspace_bytes, hipStream_t s
     p.vmark = (unsigned char *)(vw + vl.vmark);
     p.logpair = 1;
     p.spec = p.spec ? 1 : 0;
+    // (up to 20 segment lengths the default is hardly longer)
+    p.warm_model = warm_from_model(p) && p.K > 20 ? WARM_SHORTER : 0;
     rc = launch_prep(p, st);
     if (rc != SEMICRF_OK) return rc;
     const int C = p.C;
@@ -1217,9 +1227,8 @@ int semicrf_viterbi_workspace_bytes(int B, int T, int K, int C, size_t *bytes)
 {
     if (!bytes) return SEMICRF_EINVAL;
     Plan pl;
-    int rc = make_plan(B, T, K, C, 0, 0, &pl);
+    int rc = make_viterbi_plan(B, T, K, C, &pl);
     if (rc != SEMICRF_OK) return rc;
-    if (C > 64 || !spec_applies(K, C)) return SEMICRF_EUNSUPPORTED;
     if (((size_t)T + 1) * C >= ((size_t)1 << 31)) return SEMICRF_EUNSUPPORTED;
     *bytes = pl.total + viterbi_layout(B, T, C).total;
     return SEMICRF_OK;

@@ -222,21 +222,27 @@ __global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, N
         if (chunk == 0 || chunk * p.Delta >= p.hdr[b].L) return;
         if (p.spec_err[((size_t)b * 2) * (p.N + 1) + chunk] <= VIT_TOL) return;
     }
-    vit_task<CT, NKW, false>(p, lds_raw + (size_t)wave * scan_lds_doubles(CT, NKW), b, chunk, warm);
+    vit_task<CT, NKW, false>(p, lds_raw + (size_t)wave * scan_lds_doubles(CT, NKW), b, chunk, RETRY ? warm : first_warm(p, b, warm));
 }
 
 // Per chunk boundary j (position j*Delta): the state chunk j-1 reached against the warmed-up
 // state chunk j started from.  They must agree entry by entry up to ONE additive constant
 // (taken from the largest V entry); -inf entries must coincide.  The results of the first attempt and of the second lie
 // in the two halves of spec_err and spec_lr; the second compares again what its scans have rewritten.
-__global__ __launch_bounds__(NT) void k_vit_cmp(Params p, int tier)
+//
+// PER > 0: entries that can never win need not agree.  What an entry at distance d offers position j + 1 .. after the boundary is
+// dur[j+d] + r_d; a newer entry at d' < d offers dur[j+d'] + r_d', and is still there as long as the older one is.  With
+// negl[c] the most by which the duration bias of a longer duration exceeds that of a shorter one, an entry that lies negl[c] below
+// a newer one of its label (in both states) is never the best, so states that agree elsewhere do the same.
+template <int PER>
+__global__ __launch_bounds__(NT) void k_vit_cmp(Params p, int tier, int G, int per)
 {
-    __shared__ double part[NT / 64], spart[NT / 64];
+    __shared__ double part[NT / 64], newer[2 * NT];
     const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int L = p.hdr[b].L;
     const int nint = (L + p.Delta - 1) / p.Delta;
     if (j < 1 || j >= nint) return;
-    const int KC = p.K * p.C, C = p.C, N = p.N;
+    const int K = p.K, KC = p.K * p.C, C = p.C, N = p.N;
     const size_t o = ((size_t)b * 2) * (N + 1) + j, o2 = o + (tier ? N + 1 : 0);
     if (tier) {
         const double e0 = p.spec_err[o], em = j > 1 ? p.spec_err[o - 1] : 0.0;
@@ -251,6 +257,16 @@ __global__ __launch_bounds__(NT) void k_vit_cmp(Params p, int tier)
     const size_t ckstride = (size_t)KC + C;
     const double *A = p.ckA + ((size_t)b * (N + 1) + j) * ckstride;    // warm-up state
     const double *A2 = p.ckA2 + ((size_t)b * (N + 1) + j) * ckstride;  // reached state
+    // thread (range of per <= PER distances, label), G ranges: all its entries are requested before anything is waited for
+    const int g = PER > 0 ? tid / C : 0, c = tid - g * C, d0 = g * per;
+    const int nu = g < G ? min(per, K - d0) : 0;
+    double x[PER > 0 ? PER : 1], y[PER > 0 ? PER : 1];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int i = u < nu ? (d0 + u) * C + c : 0;
+        x[u] = A2[i];
+        y[u] = A[i];
+    }
     // additive constant: at the largest reached V entry (smallest label on ties); every wave finds it
     const double v = lane < C ? A2[KC + lane] : -INFINITY;
     const double va = lane < C ? A[KC + lane] : -INFINITY;
@@ -267,20 +283,55 @@ __global__ __launch_bounds__(NT) void k_vit_cmp(Params p, int tier)
         if (fabs(lp.y) < DBL_MAX) smag = fmax(smag, fabs(lp.y));
     }
     smag = wave_max(smag);
-#pragma unroll 8
-    for (int i = tid; i < KC + C; i += NT) {
-        const double x = A2[i], y = A[i];
+    auto differ = [&](const double x, const double y) {
         if (x == -INFINITY || y == -INFINITY) {
             if (x != y) err = DBL_MAX;
         } else {
             err = fmax(err, fabs(x - (y + delta)) / fmax(smag, fmax(fabs(x), fabs(y + delta))));
         }
+    };
+    auto over_waves = [&]() {  // the largest over the workgroup, in every thread
+        err = wave_max(err);
+        if (lane == 0) part[wv] = err;
+        __syncthreads();
+        for (int i = 0; i < NT / 64; ++i) err = fmax(err, part[i]);
+    };
+    if (wv == 0 && lane < C) differ(v, va);
+    const double err0 = err;
+    if (PER == 0) {
+#pragma unroll 8
+        for (int i = tid; i < KC; i += NT) differ(A2[i], A[i]);
+        over_waves();
+    } else {
+        double bx = -INFINITY, by = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            if (u >= nu) x[u] = y[u] = -INFINITY;
+            bx = fmax(bx, x[u]);
+            by = fmax(by, y[u]);
+        }
+        newer[tid] = bx;
+        newer[NT + tid] = by;
+        __syncthreads();
+        const double ng = c < C ? p.negl[(size_t)b * C + c] + VIT_TOL * smag : INFINITY;
+        bx = by = -INFINITY;
+        for (int g0 = 0; g0 < min(g, G); g0 += 8) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int q = min(g0 + i, g - 1) * C + c;
+                bx = fmax(bx, newer[q]);
+                by = fmax(by, newer[NT + q]);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            if (!(x[u] + ng <= bx && y[u] + ng <= by)) differ(x[u], y[u]);
+            bx = fmax(bx, x[u]);
+            by = fmax(by, y[u]);
+        }
+        over_waves();
     }
-    err = wave_max(err);
-    if (lane == 0) part[wv] = err;
-    __syncthreads();
     if (tid == 0) {
-        for (int i = 1; i < NT / 64; ++i) err = fmax(err, part[i]);
         p.spec_err[o2] = err;
         p.spec_lr[o2] = delta;
     }

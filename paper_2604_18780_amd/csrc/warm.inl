@@ -86,6 +86,7 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
     if (tid < b1 - b0) cnt = (double)((seq_len(p, b0 + tid) + WARM_EVERY - 1) / WARM_EVERY);
     // ---- largest log weight of a longer duration over a shorter one, per label (and source label where they have
     // matrices of their own): ranges of durations, then over the ranges in order
+    float favour = 0.f;  // lanes of the first wave: that of their label
     if (!dt) {
         float mn = INFINITY, mx = -INFINITY, best = 0.f;
 #pragma unroll
@@ -107,8 +108,10 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
                 best = fmaxf(best, fmaxf(red[2 * NT + gg * C + tid], red[NT + gg * C + tid] - mn));
                 mn = fminf(mn, red[gg * C + tid]);
             }
+            favour = best;
             // weights below exp(-700) are zero in the tables: nothing is negligible next to them
-            p.negl[(size_t)b * C + tid] = best < 600.f ? exp(-1.001 * (double)best) / (double)K : 0.0;  // (differences are rounded)
+            if (p.logpair) p.negl[(size_t)b * C + tid] = (double)best * 1.000001;
+            else p.negl[(size_t)b * C + tid] = best < 600.f ? exp(-1.001 * (double)best) / (double)K : 0.0;  // (differences are rounded)
         }
     } else {
         for (int p0 = 0; p0 < CC; p0 += NT) {
@@ -222,7 +225,18 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
             reach |= nx;
         }
     }
+    favour = (float)wave_max((double)favour);
     if (lane != 0) return;
+    if (p.logpair) {
+        // Best score: what decides is how soon all best paths into a window have met, which takes an emission that tells
+        // the labels apart and a label change or a split that pays.  In a replay of 8 x 800 and 40 x 150 .. 400 boundaries of
+        // random models (C = 3 .. 54, K = 8 .. 423, transitions N(0, s^2), s = 0.1 .. 1) all had met after 32 positions where
+        // there are eight labels or more, after 64 but for 2 where there are three or four (2 K before, 128 .. 846).
+        // Models out of that range keep that length.
+        const int deflt = vit_warmup(K), shrt = C >= 16 ? 40 : (C >= 8 ? 48 : (C >= 5 ? 64 : 96));
+        p.wlen[b].x = hops == 1 && favour < 4.f && r > 0.02f ? min(shrt, deflt) : deflt;
+        return;
+    }
     double wd = (double)sum_warmup(K);
     if (lam > 0.01 && hops < 64) {
         const double m = WARM_NATS / lam;

@@ -80,3 +80,26 @@ def test_duration_dependent_transitions(T, K, C, kind):
         ws = sb.alloc_durtrans_workspace(w.B, T, K, C, delta, True, "cuda:0").fill_(255)
         out = sb.semicrf_fwd_bwd_durtrans(dev(w.emis), dev(w.lengths), dev(t3), dev(w.dur), None, delta, workspace=ws)
         assert_outputs_match_oracle([o.double().cpu().numpy() for o in out], r)
+
+
+@pytest.mark.parametrize("T,K,C", [(900, 64, 24), (905, 65, 20), (700, 37, 9), (600, 32, 40), (1500, 130, 8), (2100, 300, 5), (1300, 90, 3),
+                                   (700, 21, 64)])
+@pytest.mark.parametrize("kind", ["plain", "band", "long", "forbidden durations", "confident", "no splits"])
+def test_best_segmentation(T, K, C, kind):
+    w = case(T, K, C, kind, B=3)
+    if kind == "no splits":  # a run of one label is one segment: an entry as old as the run decides
+        w.trans[np.arange(C), np.arange(C)] = -6.0
+        run = np.arange(T) // (K - 2) % C
+        w.emis[:, np.arange(T), run] += 4.0
+    ws = torch.full((sb.semicrf_viterbi_workspace_bytes(3, T, K, C) + 256,), 255, dtype=torch.uint8, device="cuda:0")
+    off = (-ws.data_ptr()) % 256
+    score, labels, starts, nseg = sb.semicrf_viterbi(dev(w.emis), dev(w.lengths), dev(w.trans), dev(w.dur),
+                                                     workspace=ws[off:ws.numel() - 256 + off])
+    ref = oracle.viterbi(w.emis, w.lengths, w.trans, w.dur)[0]
+    assert np.abs(score.double().cpu().numpy() - ref).max() <= 1e-6 * max(1.0, np.abs(ref).max())
+    for b in range(3):
+        L = int(w.lengths[b])
+        if L:  # the path is worth what the oracle's best one is (fp64 sums of T terms)
+            got = oracle.path_score(w.emis[b], L, w.trans, w.dur, labels[b].cpu().numpy(), starts[b].cpu().numpy())
+            assert abs(got - ref[b]) <= 1e-9 * max(1.0, abs(ref[b]))
+        assert nseg[b].item() == starts[b].sum().item()
