@@ -202,15 +202,17 @@ __global__ __launch_bounds__(NT) void k_interval(Params p)
 // MB positions per time block; wave_nk, lin_slack and wave_lds_doubles give the window's size (geometry.h).
 
 // Geometry and the window operations shared by the one-wave kernels.  SLACK: 0 lin_slack, 1 that of the one-wave
-// scan tasks, 2 that of the two-wave ones.
+// scan tasks, 2 that of the two-wave ones, 3 the best-score scan's (and its window in runs).
 template <int CT, int NKW, int SLACK = 0>
 struct WaveWin {
     static constexpr int CTP = pow2_ge8(CT);
     static constexpr int RS = CT;
     static constexpr int GW = 64 / CTP;
-    static constexpr int NK = wave_nk(CT, NKW);
-    static constexpr int KW = NK * GW;
-    static constexpr int M = SLACK ? scan_slack(CT, NKW, SLACK == 2) : lin_slack(KW);
+    static constexpr int NK = wave_nk(CT, NKW);                          // entries of a lane (one strip)
+    static constexpr int RUN = vit_run(CT), RUNS = vit_runs(NKW);        // best-score scan: runs of that many
+    static constexpr int NEAR = RUN * GW;                                // distances of the first run
+    static constexpr int KW = SLACK == 3 ? RUN * RUNS * GW : NK * GW;
+    static constexpr int M = SLACK == 3 ? vit_window_slack(CT, NKW) : (SLACK ? scan_slack(CT, NKW, SLACK == 2) : lin_slack(KW));
     static constexpr int ROWS = KW + M;
     static constexpr int RTOT = ROWS * RS + (CTP - CT);  // lanes c >= C read (and ignore) past a row's end
     static constexpr int H = CT <= 32 ? 2 : 1;
@@ -270,20 +272,20 @@ struct WaveWin {
         return BWD ? M : KW - 1;
     }
 
-    // acc[i] = f(acc[i], w[jj + i], entry at distance jj from `base`) over the lane's strip, every entry read once.
+    // acc[i] = f(acc[i], w[jj + i], entry at distance jj from `base`) over NE entries, every one read once.
     // The reads go out WRD at a time, one group ahead of the arithmetic that uses them (left to itself the compiler
     // waits for every pair of reads before its eight multiply-adds: an LDS round trip of ~100 clocks for each 32).
     static constexpr int WRD = 8;
-    template <bool BWD, int NI, class F>
+    template <bool BWD, int NE, int NI, class F>
     static __device__ __forceinline__ void window_fold(const double *base, const double *w, double (&acc)[NI], const F f)
     {
-        constexpr int NG = (NK + WRD - 1) / WRD;
+        constexpr int NG = (NE + WRD - 1) / WRD;
         double v[2][WRD];
         auto read = [&](const int grp, double (&d)[WRD]) {  // furthest entries first
 #pragma unroll
             for (int u = 0; u < WRD; ++u) {
-                const int jj = NK - 1 - (grp * WRD + u);
-                if (jj >= 0) d[u] = base[(BWD ? jj : NK - 1 - jj) * RS];
+                const int jj = NE - 1 - (grp * WRD + u);
+                if (jj >= 0) d[u] = base[(BWD ? jj : NE - 1 - jj) * RS];
             }
         };
         read(0, v[0]);
@@ -293,7 +295,7 @@ struct WaveWin {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < WRD; ++u) {
-                const int jj = NK - 1 - (grp * WRD + u);
+                const int jj = NE - 1 - (grp * WRD + u);
                 if (jj >= 0) {
 #pragma unroll
                     for (int i = 0; i < NI; ++i) acc[i] = f(acc[i], w[jj + i], v[grp & 1][u]);
@@ -303,18 +305,32 @@ struct WaveWin {
         }
     }
 
-    // sums of weight * entry
+    // sums of weight * entry over the lane's strip; maxima of weight + entry over one run (w: the lane's weights of that run)
     template <bool BWD, int NI>
     static __device__ __forceinline__ void window_sums(const double *base, const double *w, double (&acc)[NI])
     {
-        window_fold<BWD, NI>(base, w, acc, [](const double a, const double wt, const double x) { return fma(wt, x, a); });
+        window_fold<BWD, NK, NI>(base, w, acc, [](const double a, const double wt, const double x) { return fma(wt, x, a); });
     }
-
-    // maxima of weight + entry
     template <bool BWD, int NI>
     static __device__ __forceinline__ void window_maxima(const double *base, const double *w, double (&acc)[NI])
     {
-        window_fold<BWD, NI>(base, w, acc, [](const double a, const double wt, const double x) { return fmax(a, wt + x); });
+        window_fold<BWD, RUN, NI>(base, w, acc, [](const double a, const double wt, const double x) { return fmax(a, wt + x); });
+    }
+    // first distance of lane group g in run u, and offset of its lowest address from the newest row
+    static __device__ __forceinline__ constexpr int run_dist(const int u, const int g) { return (u * GW + g) * RUN; }
+    template <bool BWD>
+    static __device__ __forceinline__ int run_offset(const int u, const int g, const int c)
+    {
+        return (BWD ? run_dist(u, g) : -(run_dist(u, g) + RUN - 1)) * RS + c;
+    }
+    // the largest entry of label c at distances NEAR .. NEAR + MB - 1 from the newest row: what the last block has moved there
+    template <bool BWD>
+    static __device__ __forceinline__ double newly_old(const double *ring, const int r, const int c, double old)
+    {
+        const double *q = ring + (BWD ? r + NEAR : r - NEAR) * RS + c;
+#pragma unroll
+        for (int i = 0; i < MB; ++i) old = fmax(old, q[(BWD ? i : -i) * RS]);
+        return old;
     }
 
     // Checkpoint layout: message of position t' at slot t' mod K.  d = distance of slot sl

@@ -522,8 +522,8 @@ void launch_vit_cmp(const Params &p, hipStream_t st, int tier)
 template <int CT, int NKW>
 int launch_viterbi_k(const Params &p, hipStream_t st)
 {
-    constexpr int SW = spec_waves(CT, NKW);
-    const size_t lds = scan_lds_doubles(CT, NKW) * sizeof(double);
+    constexpr int SW = vit_waves(CT, NKW);
+    const size_t lds = vit_lds_doubles(CT, NKW) * sizeof(double);
     if (lds > LDS_LIMIT) return SEMICRF_EUNSUPPORTED;
     if (hipFuncSetAttribute((const void *)k_viterbi<CT, NKW>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds) != hipSuccess)

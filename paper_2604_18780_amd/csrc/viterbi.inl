@@ -65,9 +65,9 @@ template <int CT, int NKW, bool WHOLE>
 __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const int b, const int chunk,
                                          const int warm)
 {
-    using G = WaveWin<CT, NKW, 1>;
+    using G = WaveWin<CT, NKW, 3>;
     using R = RowMap<CT>;
-    constexpr int RS = G::RS, NK = G::NK, KW = G::KW, ROWS = G::ROWS;
+    constexpr int RS = G::RS, KW = G::KW, ROWS = G::ROWS, RUN = G::RUN, RUNS = G::RUNS;
     constexpr int RTOT = G::RTOT, HC = G::HC;
     const int lane = threadIdx.x & 63;
     const int K = p.K, C = p.C, KC = K * C;
@@ -88,12 +88,18 @@ __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const
     const size_t ts = (size_t)p.T + 1;  // positions of a label in RT
     const double NINF = -INFINITY;
 
-    double wd[NK + MB - 1];  // dur[g*NK + jj, c] (duration g*NK + jj + 1)
+    double wd[RUNS][RUN + MB - 1];  // bias of the durations of the lane's distances in each run, and of the next three
+    double wfar = NINF;             // largest bias of the durations beyond the first run
 #pragma unroll
-    for (int jj = 0; jj < NK + MB - 1; ++jj) {
-        const int k = g * NK + jj + 1;
-        wd[jj] = (cval && k <= K) ? (double)p.dur[(size_t)(k - 1) * C + c] : NINF;
+    for (int u = 0; u < RUNS; ++u) {
+#pragma unroll
+        for (int jj = 0; jj < RUN + MB - 1; ++jj) {
+            const int k = G::run_dist(u, g) + jj + 1;
+            wd[u][jj] = (cval && k <= K) ? (double)p.dur[(size_t)(k - 1) * C + c] : NINF;
+            if (u > 0) wfar = fmax(wfar, wd[u][jj]);
+        }
     }
+    wfar = group_max<G::CTP>(wfar);
     double wn[MB - 1];
 #pragma unroll
     for (int jj = 0; jj < MB - 1; ++jj) wn[jj] = (cval && jj + 1 <= K) ? (double)p.dur[(size_t)jj * C + c] : NINF;
@@ -139,7 +145,7 @@ __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const
         }
         tf += FT;
     };
-    const int rdoff = -(g * NK + NK - 1) * RS + c;
+    double old = NINF;  // no entry of the label beyond the first run is larger
     auto load_rows = [&](double2 (&e)[MB], const int tfrom) {
 #pragma unroll
         for (int i = 0; i < MB; ++i) e[i] = LPc[(size_t)min(tfrom + 1 + i, hi) * C];
@@ -156,9 +162,26 @@ __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const
         double acc[MB];
 #pragma unroll
         for (int i = 0; i < MB; ++i) acc[i] = NINF;
-        G::template window_maxima<false, MB>(ring + r * RS + rdoff, wd, acc);
+        G::template window_maxima<false, MB>(ring + r * RS + G::template run_offset<false>(0, g, c), wd[0], acc);
 #pragma unroll
         for (int i = 0; i < MB; ++i) acc[i] = group_max<G::CTP>(acc[i]);
+        if (RUNS > 1) {
+            // Older entries are looked at where one of them may win: none does while the largest of them with the largest
+            // bias stays below what the first run offers, for every label and position (a maximum over fewer candidates,
+            // the same to the last bit).  Splits that pay and label changes bring that about soon.
+            old = G::template newly_old<false>(ring, r, c, old);
+            const bool beaten = !cval || old + wfar <= fmin(fmin(acc[0], acc[1]), fmin(acc[2], acc[3]));
+            if (!__all(beaten)) {
+                double far[MB];
+#pragma unroll
+                for (int i = 0; i < MB; ++i) far[i] = NINF;
+#pragma unroll
+                for (int u = 1; u < RUNS; ++u)
+                    G::template window_maxima<false, MB>(ring + r * RS + G::template run_offset<false>(u, g, c), wd[u], far);
+#pragma unroll
+                for (int i = 0; i < MB; ++i) acc[i] = fmax(acc[i], group_max<G::CTP>(far[i]));
+            }
+        }
         double *rowp = p.sink + lane;  // where there is no row to keep (or a lane owns no label)
         int rstep = 0;
         if (keep && writer) {
@@ -207,22 +230,22 @@ __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const
 // and the prefix sums at the boundary.
 constexpr double VIT_TOL = 1e-12;
 
-// The chunk-parallel scan: spec_waves(CT, NKW) tasks per workgroup, one per wave, as k_spec.  RETRY: only the chunks
+// The chunk-parallel scan: vit_waves(CT, NKW) tasks per workgroup, one per wave, as k_spec.  RETRY: only the chunks
 // whose warmed-up start disagreed with what the chunk before reached (chunk 0 starts exactly; by induction over the
 // boundaries a chunk whose left boundary agrees is right up to its constant, so only these can be wrong).
 template <int CT, int NKW, bool RETRY>
-__global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, NKW)) void k_vit_spec(Params p, int warm)
+__global__ __launch_bounds__(64 * vit_waves(CT, NKW), spec_waves_per_simd(CT, NKW)) void k_vit_spec(Params p, int warm)
 {
     extern __shared__ double lds_raw[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int task = (int)blockIdx.x * spec_waves(CT, NKW) + wave;
+    const int task = (int)blockIdx.x * vit_waves(CT, NKW) + wave;
     const int b = task / p.N, chunk = task % p.N;
     if (b >= p.B) return;
     if (RETRY) {
         if (chunk == 0 || chunk * p.Delta >= p.hdr[b].L) return;
         if (p.spec_err[((size_t)b * 2) * (p.N + 1) + chunk] <= VIT_TOL) return;
     }
-    vit_task<CT, NKW, false>(p, lds_raw + (size_t)wave * scan_lds_doubles(CT, NKW), b, chunk, RETRY ? warm : first_warm(p, b, warm));
+    vit_task<CT, NKW, false>(p, lds_raw + (size_t)wave * vit_lds_doubles(CT, NKW), b, chunk, RETRY ? warm : first_warm(p, b, warm));
 }
 
 // Per chunk boundary j (position j*Delta): the state chunk j-1 reached against the warmed-up
