@@ -105,8 +105,8 @@ typedef enum {
 #define SEMICRF_LOW_MEMORY 256u
 /* flags bits 9 and 10: the chunk-parallel scan tasks run with two waves each (one runs the positions' dependent
  * chains, one adds up the older window entries a block ahead) / with one wave each.  By default the library takes
- * two waves where the window is deep or the label set large (more than 32 durations per lane, or C > 32), where
- * that is the faster form.  Same results up to rounding; both at once are refused. */
+ * the form that was measured to be faster: mostly two waves where the window is deep, the label set large or half of
+ * the chip without a task.  Same results up to rounding; both at once are refused. */
 #define SEMICRF_TWO_WAVE_SCAN 512u
 #define SEMICRF_ONE_WAVE_SCAN 1024u
 /* flags bit 7 (semicrf_viterbi only): trace back by pointer doubling over all nodes, at a cost that does not depend on the

@@ -343,13 +343,8 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
         const double *ck = ((p.warm_model & WARM_SHORTER) ? p.ckB2 : p.ckB) + at;
         double fi = 1.0;
         if (p.warm_model & WARM_SHORTER) {
-            double s1 = lane < C ? p.ckB[at + KC + lane] : 0.0, s2 = lane < C ? ck[KC + lane] : 0.0;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                s1 += __shfl_xor(s1, off);
-                s2 += __shfl_xor(s2, off);
-            }
-            fi = s1 / s2;
+            const double s1 = lane < C ? p.ckB[at + KC + lane] : 0.0, s2 = lane < C ? ck[KC + lane] : 0.0;
+            fi = wave_sum(s1) / wave_sum(s2);
         }
         const int tm = t1 % K;
         if (cval) {  // lane (g, c): the window rows at distances g, g + GW, ... of its label (no index divisions)

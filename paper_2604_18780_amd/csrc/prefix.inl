@@ -39,12 +39,9 @@ __device__ __forceinline__ void tables_body(const Params &p, const int blk)
             mxt = fmax(mxt, isd ? -DBL_MAX : v);
         }
     }
-    // maxima: inside each wave by shuffles, then over the waves (any order)
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        mxd = fmax(mxd, __shfl_xor(mxd, off));
-        mxt = fmax(mxt, __shfl_xor(mxt, off));
-    }
+    // maxima: inside each wave, then over the waves (any order)
+    mxd = wave_max(mxd);
+    mxt = wave_max(mxt);
     if ((tid & 63) == 0) {
         red[tid >> 6] = mxd;
         red[NT / 64 + (tid >> 6)] = mxt;
@@ -130,13 +127,10 @@ __device__ __forceinline__ void colsum_body(const Params &p, const int b, const 
     };
     float mps = absmax(p.proj_start), mpe = absmax(p.proj_end);
     // the maxima first inside each wave (a maximum does not care for order)
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        mx = fmax(mx, __shfl_xor(mx, off));
-        ex = fmax(ex, __shfl_xor(ex, off));
-        mps = fmaxf(mps, __shfl_xor(mps, off));
-        mpe = fmaxf(mpe, __shfl_xor(mpe, off));
-    }
+    mx = wave_max(mx);
+    ex = wave_max(ex);
+    if (p.proj_start) mps = (float)wave_max((double)mps);
+    if (p.proj_end) mpe = (float)wave_max((double)mpe);
     const float con = p.warm_model ? warm_sample(p, ch, L, smp) : 0.f;
     if ((tid & 63) == 0) {
         redc[tid >> 6] = con;
@@ -260,11 +254,8 @@ __global__ __launch_bounds__(PREP_NT) void k_prep_seq(Params p)
         fm = fmax(fm, (double)m.x);
         ex = fmax(ex, (double)m.y);
     }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {  // maxima: any order
-        fm = fmax(fm, __shfl_xor(fm, off));
-        ex = fmax(ex, __shfl_xor(ex, off));
-    }
+    fm = wave_max(fm);
+    ex = wave_max(ex);
     if ((tid & 63) == 0) {
         red[tid >> 6] = fm;
         redx[tid >> 6] = ex;
@@ -397,19 +388,16 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
             if (ch == 0) p.nu[(size_t)b * C + tid] = nu;
             nm = fabs(nu);
         }
-        // maxima of |f|, of the excursions, of |nu| and of the scalar boundaries: inside each wave by shuffles, then over the waves
+        // maxima of |f|, of the excursions, of |nu| and of the scalar boundaries: inside each wave, then over the waves
         double npi = 0.0;
         if (BTERMS && tid < C) {
             if (p.pi_start) npi = fabs((double)p.pi_start[tid]);
             if (p.pi_end) npi = fmax(npi, fabs((double)p.pi_end[tid]));
         }
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            fm = fmax(fm, __shfl_xor(fm, o));
-            ex = fmax(ex, __shfl_xor(ex, o));
-            nm = fmax(nm, __shfl_xor(nm, o));
-            if (BTERMS) npi = fmax(npi, __shfl_xor(npi, o));
-        }
+        fm = wave_max(fm);
+        ex = wave_max(ex);
+        nm = wave_max(nm);
+        if (BTERMS) npi = wave_max(npi);
         __syncthreads();
         if ((tid & 63) == 0) {
             redm[tid >> 6] = fm;

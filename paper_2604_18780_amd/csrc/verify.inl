@@ -48,8 +48,7 @@ __global__ __launch_bounds__(NT) void k_spec_cmp(Params p, int tier, int negl, i
         }
     }
     const double Y = (dir ? p.ckYB : p.ckYA)[at], Y2 = (dir ? p.ckYB2 : p.ckYA2)[at];
-    // sums of the two message vectors (their ratio is the common scale factor); C <= 64 here:
-    // every wave forms them, in lane order
+    // sums of the two message vectors (their ratio is the common scale factor); C <= 64 here: every wave forms them
     double s1 = lane < C ? A[KC + lane] : 0.0, s2 = lane < C ? A2[KC + lane] : 0.0;
     const double m1 = s1, m2 = s2, ng = contrib ? p.negl[(size_t)b * C + c] : 0.0;
     const int L = p.hdr[b].L;
@@ -67,11 +66,8 @@ __global__ __launch_bounds__(NT) void k_spec_cmp(Params p, int tier, int negl, i
         }
         return;
     }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        s1 += __shfl_xor(s1, off);
-        s2 += __shfl_xor(s2, off);
-    }
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
     const double f = s2 / s1;  // reached = f * 2^(Y2-Y) * warm-up, entry by entry, if they agree
     double err = 0.0;
     if (!(s1 > 0.0) || !(s2 > 0.0) || !(f > 0.0) || !(f < DBL_MAX)) err = DBL_MAX;
@@ -144,18 +140,15 @@ __device__ __forceinline__ SpecVerdict spec_verdict(const Params &p, const int b
     const double *err = p.spec_err + ((size_t)b * 2 + dir) * (p.N + 1);
     v.nint = (p.hdr[b].L + p.Delta - 1) / p.Delta;
     v.worst = 0.0;
-    v.nbad = 0;
+    int bad = 0;
 #pragma unroll 4
     for (int i = 1 + lane; i < v.nint; i += 64) {
         const double e = err[i];
         v.worst = fmax(v.worst, e);
-        v.nbad += !(e <= SPEC_TOL);
+        bad += !(e <= SPEC_TOL);
     }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        v.worst = fmax(v.worst, __shfl_xor(v.worst, off));
-        v.nbad += __shfl_xor(v.nbad, off);
-    }
+    v.worst = wave_max(v.worst);
+    v.nbad = (int)wave_sum((double)bad);
     v.ok = v.nbad == 0 && v.worst <= SPEC_TOL && (dir == 1 || v.nint == 0 || err[v.nint] == 0.0);
     return v;
 }
