@@ -91,6 +91,13 @@ constexpr size_t wave_lds_doubles(int CT, int NKW)
     return (size_t)(KW + lin_slack(KW)) * CT + (size_t)(CTP - CT) + (size_t)MB * YS;
 }
 
+// The scans' window lies in runs: a lane takes 16 consecutive distances (17 when a half-wave holds several lane groups, as
+// above) of each run, the lane groups one after the other, so that a run is the newest of the distances not yet
+// covered and the whole wave can leave the older runs alone.
+constexpr int scan_runs(int NKW) { return NKW / 16; }
+constexpr int scan_run(int CT) { return 16 + ((64 / pow2_ge8(CT)) > 2 ? 1 : 0); }
+constexpr int scan_kw(int CT, int NKW) { return scan_runs(NKW) * scan_run(CT) * (64 / pow2_ge8(CT)); }
+
 // Tasks of the scan kernel a SIMD holds by registers: one where the transition column or the duration strip is long.
 constexpr int spec_waves_per_simd(int CT, int NKW) { return (CT == 64 || (CT == 32 && NKW == 64)) ? 1 : 2; }
 
@@ -115,32 +122,14 @@ constexpr int slack_rows(int CT, int KW, size_t extra, size_t most)
 constexpr int scan_slack(int CT, int NKW, bool two)
 {
     const int CTP = pow2_ge8(CT);
-    const int KW = wave_nk(CT, NKW) * (64 / CTP);
     const size_t extra = (CTP - CT) + (two ? (size_t)2 * MB * CT + (size_t)2 * MB * CTP + 2 : 0);
-    return slack_rows(CT, KW, extra, two ? 2 * (size_t)spec2_waves_per_simd(CT, NKW) : 4 * (size_t)spec_waves_per_simd(CT, NKW));
+    return slack_rows(CT, scan_kw(CT, NKW), extra, two ? 2 * (size_t)spec2_waves_per_simd(CT, NKW) : 4 * (size_t)spec_waves_per_simd(CT, NKW));
 }
 
 // LDS of a one-wave scan task: the window.
 constexpr size_t scan_lds_doubles(int CT, int NKW)
 {
-    const int CTP = pow2_ge8(CT);
-    const int KW = wave_nk(CT, NKW) * (64 / CTP);
-    return (size_t)(KW + scan_slack(CT, NKW, false)) * CT + (size_t)(CTP - CT);
-}
-
-// The best-score scan's window lies in runs: a lane takes 16 consecutive distances (17 when a half-wave holds several lane
-// groups, as above) of each run, the lane groups one after the other, so that a run is the newest of the distances not yet
-// covered and the whole wave can leave the older runs alone.
-constexpr int vit_runs(int NKW) { return NKW / 16; }
-constexpr int vit_run(int CT) { return 16 + ((64 / pow2_ge8(CT)) > 2 ? 1 : 0); }
-constexpr int vit_kw(int CT, int NKW) { return vit_runs(NKW) * vit_run(CT) * (64 / pow2_ge8(CT)); }
-constexpr int vit_window_slack(int CT, int NKW)
-{
-    return slack_rows(CT, vit_kw(CT, NKW), pow2_ge8(CT) - CT, 4 * (size_t)spec_waves_per_simd(CT, NKW));
-}
-constexpr size_t vit_lds_doubles(int CT, int NKW)
-{
-    return (size_t)(vit_kw(CT, NKW) + vit_window_slack(CT, NKW)) * CT + (size_t)(pow2_ge8(CT) - CT);
+    return (size_t)(scan_kw(CT, NKW) + scan_slack(CT, NKW, false)) * CT + (size_t)(pow2_ge8(CT) - CT);
 }
 
 // Single-wave tasks of one workgroup of the scan kernels: one per SIMD where their LDS fits.
@@ -150,7 +139,6 @@ constexpr int waves_of_lds(size_t doubles)
     return 4 * lds <= LDS_LIMIT ? 4 : (2 * lds <= LDS_LIMIT ? 2 : 1);
 }
 constexpr int spec_waves(int CT, int NKW) { return waves_of_lds(scan_lds_doubles(CT, NKW)); }
-constexpr int vit_waves(int CT, int NKW) { return waves_of_lds(vit_lds_doubles(CT, NKW)); }
 
 // Single-wave tasks of one workgroup of the interval kernel.
 constexpr int interval_waves(int CT, int NKW) { return CT == 64 ? 4 : (NKW == 64 ? 3 : 1); }

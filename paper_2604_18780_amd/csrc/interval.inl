@@ -202,17 +202,17 @@ __global__ __launch_bounds__(NT) void k_interval(Params p)
 // MB positions per time block; wave_nk, lin_slack and wave_lds_doubles give the window's size (geometry.h).
 
 // Geometry and the window operations shared by the one-wave kernels.  SLACK: 0 lin_slack, 1 that of the one-wave
-// scan tasks, 2 that of the two-wave ones, 3 the best-score scan's (and its window in runs).
+// scan tasks, 2 that of the two-wave ones (whose windows lie in runs).
 template <int CT, int NKW, int SLACK = 0>
 struct WaveWin {
     static constexpr int CTP = pow2_ge8(CT);
     static constexpr int RS = CT;
     static constexpr int GW = 64 / CTP;
     static constexpr int NK = wave_nk(CT, NKW);                          // entries of a lane (one strip)
-    static constexpr int RUN = vit_run(CT), RUNS = vit_runs(NKW);        // best-score scan: runs of that many
+    static constexpr int RUN = scan_run(CT), RUNS = scan_runs(NKW);      // scans: runs of that many
     static constexpr int NEAR = RUN * GW;                                // distances of the first run
-    static constexpr int KW = SLACK == 3 ? RUN * RUNS * GW : NK * GW;
-    static constexpr int M = SLACK == 3 ? vit_window_slack(CT, NKW) : (SLACK ? scan_slack(CT, NKW, SLACK == 2) : lin_slack(KW));
+    static constexpr int KW = SLACK ? scan_kw(CT, NKW) : NK * GW;
+    static constexpr int M = SLACK ? scan_slack(CT, NKW, SLACK == 2) : lin_slack(KW);
     static constexpr int ROWS = KW + M;
     static constexpr int RTOT = ROWS * RS + (CTP - CT);  // lanes c >= C read (and ignore) past a row's end
     static constexpr int H = CT <= 32 ? 2 : 1;
@@ -305,11 +305,11 @@ struct WaveWin {
         }
     }
 
-    // sums of weight * entry over the lane's strip; maxima of weight + entry over one run (w: the lane's weights of that run)
+    // sums of weight * entry and maxima of weight + entry over one run (w: the lane's weights of that run)
     template <bool BWD, int NI>
     static __device__ __forceinline__ void window_sums(const double *base, const double *w, double (&acc)[NI])
     {
-        window_fold<BWD, NK, NI>(base, w, acc, [](const double a, const double wt, const double x) { return fma(wt, x, a); });
+        window_fold<BWD, RUN, NI>(base, w, acc, [](const double a, const double wt, const double x) { return fma(wt, x, a); });
     }
     template <bool BWD, int NI>
     static __device__ __forceinline__ void window_maxima(const double *base, const double *w, double (&acc)[NI])
@@ -323,14 +323,77 @@ struct WaveWin {
     {
         return (BWD ? run_dist(u, g) : -(run_dist(u, g) + RUN - 1)) * RS + c;
     }
-    // the largest entry of label c at distances NEAR .. NEAR + MB - 1 from the newest row: what the last block has moved there
-    template <bool BWD>
-    static __device__ __forceinline__ double newly_old(const double *ring, const int r, const int c, double old)
+    // f over the entries of label c at distances NEAR .. NEAR + MB - 1 from the newest row: what the last block has moved there
+    template <bool BWD, class F>
+    static __device__ __forceinline__ double newly_old(const double *ring, const int r, const int c, const F f)
     {
         const double *q = ring + (BWD ? r + NEAR : r - NEAR) * RS + c;
+        double v[MB];
 #pragma unroll
-        for (int i = 0; i < MB; ++i) old = fmax(old, q[(BWD ? i : -i) * RS]);
-        return old;
+        for (int i = 0; i < MB; ++i) v[i] = q[(BWD ? i : -i) * RS];
+        static_assert(MB == 4, "four entries");
+        return f(f(v[0], v[1]), f(v[2], v[3]));
+    }
+    // Weights of the lane for the sums below: entry (u, jj) is that of the duration run_dist(u, g) + jj + first of label c (0
+    // where there is none); returns 2^54 times the largest of them beyond the first run.
+    static __device__ __forceinline__ double load_weights(const Params &p, const int g, const int c, const int first,
+                                                          double (&w)[RUNS][RUN + MB - 1])
+    {
+        double wfar = 0.0;
+#pragma unroll
+        for (int u = 0; u < RUNS; ++u) {
+#pragma unroll
+            for (int jj = 0; jj < RUN + MB - 1; ++jj) {
+                const int k = run_dist(u, g) + jj + first;
+                w[u][jj] = (c < p.C && k <= p.K) ? p.W[(size_t)(k - 1) * p.C + c] : 0.0;
+                if (u > 0) wfar = fmax(wfar, w[u][jj]);
+            }
+        }
+        return RUNS > 1 ? 0x1p54 * group_max<CTP>(wfar) : 0.0;
+    }
+    // Sum of the entries of label c beyond the first run behind row r, for a window that is there already.
+    template <bool BWD>
+    static __device__ __forceinline__ double all_old(const double *ring, const int r, const int g, const int c)
+    {
+        double s = 0.0;
+        if (RUNS > 1) {
+            for (int d = NEAR + g; d < KW; d += GW) s += ring[(BWD ? r + d : r - d) * RS + c];
+            s = group_sum<CTP>(s);
+        }
+        return s;
+    }
+    // acc[i]: what the whole window behind row r adds to the i-th position of the next block, in every lane of the label.
+    //
+    // The messages of a label grow from position to position (in its own frame, see warm_plan), so that the older runs mostly
+    // lie far below the newest.  They are left alone while old, the sum of all entries that ever went beyond the first
+    // run (an upper bound of those still there), times the largest weight there is below 2^-54 of what the first run adds,
+    // for every label and position of the block: less than half of the last bit's rounding.  Anything that is not a
+    // finite number takes the whole window.
+    // Whole calls, all runs read against this: K = 512, C = 8, T = 400 000 754 -> 663 us (forward only 363 -> 285), 4 x 100 000 positions
+    // with K = 64, C = 24 539 -> 531 (208 -> 197).
+    template <bool BWD>
+    static __device__ __forceinline__ void whole_window(const double *ring, const int r, const int g, const int c, const bool cval,
+                                                        const double (&w)[RUNS][RUN + MB - 1], const double wfar, double &old,
+                                                        double (&acc)[MB])
+    {
+#pragma unroll
+        for (int i = 0; i < MB; ++i) acc[i] = 0.0;
+        window_sums<BWD, MB>(ring + r * RS + run_offset<BWD>(0, g, c), w[0], acc);
+#pragma unroll
+        for (int i = 0; i < MB; ++i) acc[i] = group_sum<CTP>(acc[i]);
+        if (RUNS > 1) {
+            old += newly_old<BWD>(ring, r, c, [](const double a, const double x) { return a + x; });
+            const bool little = old * wfar <= fmin(fmin(fmin(acc[0], acc[1]), fmin(acc[2], acc[3])), DBL_MAX);
+            if (!__all(!cval || little)) {
+                double far[MB];
+#pragma unroll
+                for (int i = 0; i < MB; ++i) far[i] = 0.0;
+#pragma unroll
+                for (int u = 1; u < RUNS; ++u) window_sums<BWD, MB>(ring + r * RS + run_offset<BWD>(u, g, c), w[u], far);
+#pragma unroll
+                for (int i = 0; i < MB; ++i) acc[i] += group_sum<CTP>(far[i]);
+            }
+        }
     }
 
     // Checkpoint layout: message of position t' at slot t' mod K.  d = distance of slot sl

@@ -298,21 +298,21 @@ int launch_spec_k(const Params &p, hipStream_t st, bool both, int warm, int tier
         if (rc != SEMICRF_OK) return rc;
         rest = 1;
     }
-    // Two waves per task: a first attempt that leaves half of the SIMDs without a task, or gradients with short strips; where
-    // the window or the transition product is long next to a position's dependent chain, there unless the chip is full of
-    // tasks that one wave holds in registers.  Whole calls, one wave against two (tasks of both directions):
-    //   few tasks    K = 8, C = 4, T = 512 64.9 -> 61.6 us; K = 100, C = 16, T = 3000 148 -> 125; K = 50, C = 24, T = 2000
-    //                110 -> 101; forward only 46 -> 43, 78 -> 59, 62 -> 57
-    //   16 a lane    K = 100, C = 8 404 -> 368; K = 40, C = 16 445 -> 398; K = 16, C = 24 485 -> 457, 2048 short tasks 98 -> 96;
-    //                K = 16, C = 32 339 -> 321; K = 12, C = 64 254 -> 277; forward only 165 -> 187, 160 -> 173, 119 -> 124
-    //   32 a lane    K = 64, C = 24 539 -> 534; K = 37, C = 19 141 -> 144; K = 40, C = 32 413 -> 470; K = 32, C = 64 the two level;
-    //                forward only 196 -> 212, K = 32, C = 64 115 -> 107
-    //   64 a lane    K = 512, C = 8 746 -> 751; K = 130, C = 12 610 -> 526; K = 128, C = 24 532 -> 483; K = 128, C = 32 584 -> 701;
-    //                forward only 407 -> 363, 241 -> 202, 249 -> 219, 301 -> 237
+    // Two waves per task: a first attempt that leaves half of the SIMDs without a task; gradients with short strips, or with
+    // long ones up to 24 labels (one wave spills there); scores alone with long strips or many labels.  Whole calls, one wave
+    // against two, us (trained and initial transitions alike):
+    //   few tasks    K = 8, C = 4, T = 512 63 -> 60; K = 100, C = 16, T = 3000 141 -> 132; K = 50, C = 24, T = 2000 108 -> 103;
+    //                forward only 44 -> 42, 68 -> 65, 61 -> 58
+    //   16 a lane    K = 100, C = 8 238 -> 221; K = 40, C = 16 248 -> 229; K = 30, C = 24 515 -> 496; K = 24, C = 64 679 -> 693;
+    //                forward only 101 -> 99, 104 -> 98, 176 -> 193, 202 -> 197
+    //   32 a lane    K = 64, C = 24 542 -> 547; K = 37, C = 19 137 -> 142; K = 40, C = 32 245 -> 302; K = 32, C = 64 286 -> 305;
+    //                forward only 193 -> 217, 74 -> 76, 100 -> 106, 108 -> 103
+    //   64 a lane    K = 512, C = 8 860 -> 657; K = 130, C = 12 551 -> 409; K = 128, C = 24 294 -> 237; K = 128, C = 32 275 -> 330;
+    //                K = 60, C = 57 521 -> 574; forward only 390 -> 285, 186 -> 145, 149 -> 113, 154 -> 120, 198 -> 170
     const long tasks = (long)p.B * p.N * (both ? 2 : 1);
     const bool few = tasks <= 512, deep = NKW == 64 || CT == 64;
     bool pays = deep;
-    if (tier == 0) pays = few || (deep ? !((CT == 64 && NKW == 16 && both) || (CT == 32 && NKW == 64)) : (NKW == 16 && both));
+    if (tier == 0) pays = few || (both ? NKW == 16 ? CT <= 32 : NKW == 64 && CT <= 24 : deep);
     const bool two = (p.spec2 == 1 || (p.spec2 == 0 && pays)) && spec2_lds_doubles<CT, NKW>() * sizeof(double) <= LDS_LIMIT;
     if (tier == 0) rc = launch_spec_tasks<CT, NKW, false>(p, st, both, warm, tier, rest, two);
     else rc = launch_spec_tasks<CT, NKW, true>(p, st, both, warm, tier, rest, two);
@@ -533,8 +533,8 @@ void launch_vit_cmp(const Params &p, hipStream_t st, int tier)
 template <int CT, int NKW>
 int launch_viterbi_k(const Params &p, hipStream_t st)
 {
-    constexpr int SW = vit_waves(CT, NKW);
-    const size_t lds = vit_lds_doubles(CT, NKW) * sizeof(double);
+    constexpr int SW = spec_waves(CT, NKW);
+    const size_t lds = scan_lds_doubles(CT, NKW) * sizeof(double);
     if (lds > LDS_LIMIT) return SEMICRF_EUNSUPPORTED;
     if (hipFuncSetAttribute((const void *)k_viterbi<CT, NKW>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds) != hipSuccess)

@@ -77,7 +77,7 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
 {
     using G = WaveWin<CT, NKW, 1>;
     using R = RowMap<CT>;
-    constexpr int CTP = G::CTP, RS = G::RS, NK = G::NK, KW = G::KW, M = G::M, ROWS = G::ROWS;
+    constexpr int RS = G::RS, KW = G::KW, M = G::M, ROWS = G::ROWS, RUN = G::RUN, RUNS = G::RUNS;
     constexpr int RTOT = G::RTOT, H = G::H, HC = G::HC;
     const int lane = threadIdx.x & 63;
     const int K = p.K, C = p.C, KC = K * C;
@@ -97,12 +97,8 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
     const double2 *EIc = p.EI + row0 * C + cc;
     const int *nbc = p.nbase + row0 * C + cc;
 
-    double wx[NK + MB - 1];  // W[g*NK + jj + 1, c]
-#pragma unroll
-    for (int jj = 0; jj < NK + MB - 1; ++jj) {
-        const int k = g * NK + jj + 1;
-        wx[jj] = (cval && k <= K) ? p.W[(size_t)(k - 1) * C + c] : 0.0;
-    }
+    double wx[RUNS][RUN + MB - 1];  // weights of the durations of the lane's distances in each run, and of the next three
+    const double wfar = G::load_weights(p, g, c, 1, wx);
     double wn[MB - 1];       // W[1..MB-1, c]: durations inside a block
 #pragma unroll
     for (int jj = 0; jj < MB - 1; ++jj) wn[jj] = (cval && jj + 1 <= K) ? p.W[(size_t)jj * C + c] : 0.0;
@@ -120,6 +116,7 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
     int r = BWD ? M : KW - 1;  // row of the newest message
     double ylast = 0.0;        // newest message vector, entry c (the same in every group; 0 beyond C)
     double Y = 0.0;
+    double old = 0.0;          // sum of the entries of the label that went beyond the first run
     if (repair) {
         // the reached state at the boundary: K-deep window in slot order, message vector, scale
         const int bs = BWD ? j + 1 : j;
@@ -132,6 +129,8 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
         }
         if (cval) ylast = src[KC + c];
         Y = ((BWD ? p.ckYB2 : p.ckYA2) + (size_t)b * (N + 1))[bs];
+        lds_wave_fence();
+        old = G::template all_old<BWD>(ring, r, g, c);
     } else {
         double q;
         if (!BWD) {
@@ -190,8 +189,6 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
         start_rows();
     }
 
-    // this lane's lowest window address relative to the newest row
-    const int rdoff = BWD ? g * NK * RS + c : -(g * NK + NK - 1) * RS + c;
     int t = s0;
     auto load_rows = [&](double2 (&e)[MB], const int tfrom) {  // rows of the MB positions after tfrom
 #pragma unroll
@@ -235,18 +232,14 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
             const int ex = safe_exponent(prevsum);
             Y += (double)ex;
             G::template rescale_live<BWD>(ring, g, c, cval, r, dnx - ex);
+            old = fmin(ldexp(old, dnx - ex), DBL_MAX);
             jnx += BWD ? -1 : 1;
             dnx = nbdelta(jnx);
         }
         if (__builtin_expect(BWD ? r < MB : r + MB > ROWS - 1, 0)) r = G::template move<BWD>(ring, lane, r);
         // ---- what the window contributes to the MB positions of the block
-        const double *base = ring + r * RS + rdoff;
         double acc[MB];
-#pragma unroll
-        for (int i = 0; i < MB; ++i) acc[i] = 0.0;
-        G::template window_sums<BWD, MB>(base, wx, acc);
-#pragma unroll
-        for (int i = 0; i < MB; ++i) acc[i] = group_sum<CTP>(acc[i]);
+        G::template whole_window<BWD>(ring, r, g, c, cval, wx, wfar, old, acc);
         // ---- the positions one after the other
         double qn[MB];
         // A whole block (nearly all are): nothing is decided per position.  The rows of a block that lies in the

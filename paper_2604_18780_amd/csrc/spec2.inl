@@ -23,10 +23,9 @@ template <int CT, int NKW>
 __host__ __device__ constexpr size_t spec2_lds_doubles()
 {
     const int CTP = pow2_ge8(CT);
-    const int KW = wave_nk(CT, NKW) * (64 / CTP);
     // window rows + MB spare rows at both ends (the helper's window starts MB rows behind the newest row),
     // two sets of MB far sums per label, the published exponent
-    return (size_t)(KW + scan_slack(CT, NKW, true) + 2 * MB) * CT + (size_t)(CTP - CT) + (size_t)2 * MB * CTP + 2;
+    return (size_t)(scan_kw(CT, NKW) + scan_slack(CT, NKW, true) + 2 * MB) * CT + (size_t)(CTP - CT) + (size_t)2 * MB * CTP + 2;
 }
 
 template <int CT, int NKW, bool BWD>
@@ -35,7 +34,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
 {
     using G = WaveWin<CT, NKW, 2>;
     using R = RowMap<CT>;
-    constexpr int CTP = G::CTP, RS = G::RS, NK = G::NK, KW = G::KW, M = G::M, ROWS = G::ROWS, GW = G::GW;
+    constexpr int CTP = G::CTP, RS = G::RS, KW = G::KW, M = G::M, ROWS = G::ROWS, GW = G::GW, RUN = G::RUN, RUNS = G::RUNS;
     constexpr int H = G::H, HC = G::HC;
     constexpr int RTOT2 = (ROWS + 2 * MB) * RS + (CTP - CT);
     const int lane = threadIdx.x & 63;
@@ -255,21 +254,13 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
         record(tend, ck2 + (size_t)iend * ckstride, ckY2 + iend);
     } else {
         // ================================ the helper ================================
-        double wx[NK + MB - 1];  // W[g*NK + jj + MB + 1, c]: entry at distance g*NK + jj behind the window's base
-#pragma unroll
-        for (int jj = 0; jj < NK + MB - 1; ++jj) {
-            const int k = g * NK + jj + MB + 1;
-            wx[jj] = (cval && k <= K) ? p.W[(size_t)(k - 1) * C + c] : 0.0;
-        }
+        double wx[RUNS][RUN + MB - 1];  // as in the one-wave task, for a window that begins MB positions behind a block's base
+        const double wfar = G::load_weights(p, g, c, MB + 1, wx);
+        double old = 0.0;
         // what the entries from row rb on (MB positions behind a block's base, and older) add to its MB positions
         auto far_sums = [&](const int rb, const int buf) {
-            const double *base = ring + rb * RS + (BWD ? g * NK * RS + c : -(g * NK + NK - 1) * RS + c);
             double acc[MB];
-#pragma unroll
-            for (int i = 0; i < MB; ++i) acc[i] = 0.0;
-            G::template window_sums<BWD, MB>(base, wx, acc);
-#pragma unroll
-            for (int i = 0; i < MB; ++i) acc[i] = group_sum<CTP>(acc[i]);
+            G::template whole_window<BWD>(ring, rb, g, c, cval, wx, wfar, old, acc);
             double *fb = farb + buf * MB * CTP + c;
             if (g == 0) {
 #pragma unroll
@@ -280,6 +271,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
         if (repair) {
             // a mended task starts with a whole window: the first block has older entries, too (after a warm-up's start
             // there is only the newest one)
+            old = G::template all_old<BWD>(ring, BWD ? r + MB : r - MB, g, c);
             far_sums(BWD ? r + MB : r - MB, 0);
             lds_barrier();
         }
@@ -306,6 +298,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
                     }
                 }
                 lds_wave_fence();
+                old = fmin(ldexp(old, sft), DBL_MAX);
             }
             // what the entries at least MB positions before the NEXT block's base add to its MB positions
             // (the base is the last position of this block; its newest MB predecessors are the tip's)

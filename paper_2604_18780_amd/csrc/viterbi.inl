@@ -65,7 +65,7 @@ template <int CT, int NKW, bool WHOLE>
 __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const int b, const int chunk,
                                          const int warm)
 {
-    using G = WaveWin<CT, NKW, 3>;
+    using G = WaveWin<CT, NKW, 1>;
     using R = RowMap<CT>;
     constexpr int RS = G::RS, KW = G::KW, ROWS = G::ROWS, RUN = G::RUN, RUNS = G::RUNS;
     constexpr int RTOT = G::RTOT, HC = G::HC;
@@ -169,7 +169,7 @@ __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const
             // Older entries are looked at where one of them may win: none does while the largest of them with the largest
             // bias stays below what the first run offers, for every label and position (a maximum over fewer candidates,
             // the same to the last bit).  Splits that pay and label changes bring that about soon.
-            old = G::template newly_old<false>(ring, r, c, old);
+            old = fmax(old, G::template newly_old<false>(ring, r, c, [](const double a, const double x) { return fmax(a, x); }));
             const bool beaten = !cval || old + wfar <= fmin(fmin(acc[0], acc[1]), fmin(acc[2], acc[3]));
             if (!__all(beaten)) {
                 double far[MB];
@@ -230,22 +230,22 @@ __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const
 // and the prefix sums at the boundary.
 constexpr double VIT_TOL = 1e-12;
 
-// The chunk-parallel scan: vit_waves(CT, NKW) tasks per workgroup, one per wave, as k_spec.  RETRY: only the chunks
+// The chunk-parallel scan: spec_waves(CT, NKW) tasks per workgroup, one per wave, as k_spec.  RETRY: only the chunks
 // whose warmed-up start disagreed with what the chunk before reached (chunk 0 starts exactly; by induction over the
 // boundaries a chunk whose left boundary agrees is right up to its constant, so only these can be wrong).
 template <int CT, int NKW, bool RETRY>
-__global__ __launch_bounds__(64 * vit_waves(CT, NKW), spec_waves_per_simd(CT, NKW)) void k_vit_spec(Params p, int warm)
+__global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, NKW)) void k_vit_spec(Params p, int warm)
 {
     extern __shared__ double lds_raw[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int task = (int)blockIdx.x * vit_waves(CT, NKW) + wave;
+    const int task = (int)blockIdx.x * spec_waves(CT, NKW) + wave;
     const int b = task / p.N, chunk = task % p.N;
     if (b >= p.B) return;
     if (RETRY) {
         if (chunk == 0 || chunk * p.Delta >= p.hdr[b].L) return;
         if (p.spec_err[((size_t)b * 2) * (p.N + 1) + chunk] <= VIT_TOL) return;
     }
-    vit_task<CT, NKW, false>(p, lds_raw + (size_t)wave * vit_lds_doubles(CT, NKW), b, chunk, RETRY ? warm : first_warm(p, b, warm));
+    vit_task<CT, NKW, false>(p, lds_raw + (size_t)wave * scan_lds_doubles(CT, NKW), b, chunk, RETRY ? warm : first_warm(p, b, warm));
 }
 
 // Per chunk boundary j (position j*Delta): the state chunk j-1 reached against the warmed-up
