@@ -298,21 +298,22 @@ int launch_spec_k(const Params &p, hipStream_t st, bool both, int warm, int tier
         if (rc != SEMICRF_OK) return rc;
         rest = 1;
     }
-    // Two waves per task: a first attempt that leaves half of the SIMDs without a task; gradients with short strips, or with
-    // long ones up to 24 labels (one wave spills there); scores alone with long strips or many labels.  Whole calls, one wave
+    // Two waves per task: a first attempt that leaves half of the SIMDs without a task; gradients with short strips, with
+    // long ones up to 24 labels (one wave spills there), or with 64 labels and no more tasks than SIMDs; scores alone with long strips or many labels.  Whole calls, one wave
     // against two, us (trained and initial transitions alike):
     //   few tasks    K = 8, C = 4, T = 512 63 -> 60; K = 100, C = 16, T = 3000 141 -> 132; K = 50, C = 24, T = 2000 108 -> 103;
     //                forward only 44 -> 42, 68 -> 65, 61 -> 58
     //   16 a lane    K = 100, C = 8 238 -> 221; K = 40, C = 16 248 -> 229; K = 30, C = 24 515 -> 496; K = 24, C = 64 679 -> 693;
     //                forward only 101 -> 99, 104 -> 98, 176 -> 193, 202 -> 197
     //   32 a lane    K = 64, C = 24 542 -> 547; K = 37, C = 19 137 -> 142; K = 40, C = 32 245 -> 302; K = 32, C = 64 286 -> 305;
+    //                ... with no more tasks than SIMDs K = 23, C = 54, T = 5516 132 -> 127, K = 20, C = 64, 16 x 500 124 -> 121;
     //                forward only 193 -> 217, 74 -> 76, 100 -> 106, 108 -> 103
     //   64 a lane    K = 512, C = 8 860 -> 657; K = 130, C = 12 551 -> 409; K = 128, C = 24 294 -> 237; K = 128, C = 32 275 -> 330;
     //                K = 60, C = 57 521 -> 574; forward only 390 -> 285, 186 -> 145, 149 -> 113, 154 -> 120, 198 -> 170
     const long tasks = (long)p.B * p.N * (both ? 2 : 1);
     const bool few = tasks <= 512, deep = NKW == 64 || CT == 64;
     bool pays = deep;
-    if (tier == 0) pays = few || (both ? NKW == 16 ? CT <= 32 : NKW == 64 && CT <= 24 : deep);
+    if (tier == 0) pays = few || (both ? (NKW == 16 ? CT <= 32 : (NKW == 64 ? CT <= 24 : CT == 64 && tasks <= MG_SIMDS)) : deep);
     const bool two = (p.spec2 == 1 || (p.spec2 == 0 && pays)) && spec2_lds_doubles<CT, NKW>() * sizeof(double) <= LDS_LIMIT;
     if (tier == 0) rc = launch_spec_tasks<CT, NKW, false>(p, st, both, warm, tier, rest, two);
     else rc = launch_spec_tasks<CT, NKW, true>(p, st, both, warm, tier, rest, two);
