@@ -27,6 +27,19 @@ def test_entropies_over_many_workgroups(T, C):
     np.testing.assert_allclose(h_bdy.cpu().numpy(), rb, rtol=1e-6, atol=1e-6)
 
 
+def test_entropy_terms_of_single_values():
+    """One value per sequence, so that its -x log x shows: the ends of the float's range, both sides of the powers of two and of
+    the square root of one half, 1, values that are no probabilities, and none at all."""
+    x = [1e-45, 1.2e-38, 3e-20, 0.25, 0.5, 0.70710677, 0.70710683, 0.99999994, 1.0, 1.0000001, 1.4142135, 1.4142137, 2.0, 3e38]
+    x = np.concatenate([np.array(x, dtype=np.float32), np.random.default_rng(1).random(200, dtype=np.float32)])
+    odd = np.array([0.0, -1.0, np.nan, np.inf], dtype=np.float32)
+    pm = np.concatenate([x, odd]).reshape(-1, 1, 1)
+    h = sb.semicrf_entropies(dev(pm), dev(np.ones((len(pm), 2), dtype=np.float32)), None)[0].cpu().numpy()
+    want = (-x.astype(np.float64) * np.log(x.astype(np.float64))).astype(np.float32)
+    np.testing.assert_allclose(h[: len(x)], want, rtol=1.2e-7, atol=0)  # 64-bit terms: the float's rounding, on either side
+    assert (h[len(x):-1] == 0).all() and h[-1] == -np.inf
+
+
 @pytest.mark.parametrize("T,C", [(1, 1), (7, 3), (8, 24), (255, 5), (256, 24), (257, 64), (1000, 33), (1024, 130)])
 @pytest.mark.parametrize("scale", [1.0, 30.0])
 def test_prefix_sums_at_chunk_and_segment_edges(T, C, scale):
