@@ -82,9 +82,10 @@ __global__ __launch_bounds__(NT) void k_interval(Params p)
             Yb = 0.0;
         } else {
             const int ci = t1 / Delta;
-            const double *ck = p.ckB + ((size_t)b * (N + 1) + ci) * ckstride;
-            for (int i = tid; i < KC; i += NT) l.ring[i] = ck[i];
-            if (tid < C) l.yv[tid] = ck[KC + tid];
+            const double *ck;
+            const double f = state_above(p, b, ((size_t)b * (N + 1) + ci) * ckstride, ck);
+            for (int i = tid; i < KC; i += NT) l.ring[i] = f * ck[i];
+            if (tid < C) l.yv[tid] = f * ck[KC + tid];
             Yb = p.ckYB[(size_t)b * (N + 1) + ci];
         }
         for (int i = tid; i < KC; i += NT) l.accD[i] = 0.0;
@@ -657,13 +658,14 @@ __global__ __launch_bounds__(64 * interval_waves(CT, NKW)) void k_interval_wave(
             Yb = 0.0;
         } else {
             const int ci = t1 / Delta;
-            const double *ck = p.ckB + ((size_t)b * (N + 1) + ci) * ckstride;
+            const double *ck;
+            const double f = state_above(p, b, ((size_t)b * (N + 1) + ci) * ckstride, ck);
             const int tm = t1 % K;
             for (int i = lane; i < KC; i += 64) {
                 const int sl = i / C, col = i % C;
-                ring[(r + G::template slot_dist<true>(sl, tm, K)) * RS + col] = ck[i];
+                ring[(r + G::template slot_dist<true>(sl, tm, K)) * RS + col] = f * ck[i];
             }
-            if (lane < C) yv[lane] = ck[KC + lane];
+            if (lane < C) yv[lane] = f * ck[KC + lane];
             Yb = p.ckYB[(size_t)b * (N + 1) + ci];
         }
         lds_wave_fence();

@@ -337,15 +337,8 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
     if (tb == L) {  // v_L = E_L
         if (writer) ring[r * RS + c] = EIc[(size_t)L * C].x;
     } else if (tb == t1) {  // the state the backward task started from
-        // (or, where that may be incomplete in what no longer matters to the scan, the one the task above reached there,
-        // divided by the common factor of the two)
-        const size_t at = ((size_t)b * (N + 1) + iv + 1) * ((size_t)KC + C);
-        const double *ck = ((p.warm_model & WARM_SHORTER) ? p.ckB2 : p.ckB) + at;
-        double fi = 1.0;
-        if (p.warm_model & WARM_SHORTER) {
-            const double s1 = lane < C ? p.ckB[at + KC + lane] : 0.0, s2 = lane < C ? ck[KC + lane] : 0.0;
-            fi = wave_sum(s1) / wave_sum(s2);
-        }
+        const double *ck;
+        const double fi = state_above(p, b, ((size_t)b * (N + 1) + iv + 1) * ((size_t)KC + C), ck);
         const int tm = t1 % K;
         if (cval) {  // lane (g, c): the window rows at distances g, g + GW, ... of its label (no index divisions)
 #pragma unroll 8

@@ -442,7 +442,7 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
     // (the partial-sum arrays are planned for N * pl.msplit either way; a part holds at least K positions)
     if (p.marg && p.K < 128 && pl.Delta / pl.msplit >= p.K) p.msplit = pl.msplit;
     // Windows that agree only in what they still contribute serve the scans and, where they come complete from the neighbour
-    // (intervals of at least K positions), the stored-row marginals; the interval kernels count every entry.
+    // (state_above: intervals of at least K positions), the statistics; elsewhere the warm-up fills them.
     if (warm_from_model(p)) p.warm_model = WARM_LONGER | ((mode == 1 || (p.marg && p.Delta >= p.K)) ? WARM_SHORTER : 0);
     if (p.warm_model) p.warm_long = warm[1] = warm[1] < WARM_LONG_LEAST ? WARM_LONG_LEAST : warm[1];
     T.mark();

@@ -217,6 +217,20 @@ __device__ __forceinline__ void spec_settle(const Params &p, const int b, const 
     lr[0] = (double)v.nbad;
 }
 
+// What the statistics of an interval start from: the backward state at its upper boundary (`at`: offset of that checkpoint),
+// in the frame of the warmed-up one.  After a warm-up shorter than the window the entries that no longer matter to the scan
+// may be missing there, but the expected counts of long durations are made of them: the state the task above reached there
+// has them, and the two differ by a common factor, which is returned.  Every lane of a wave calls it.
+__device__ __forceinline__ double state_above(const Params &p, const int b, const size_t at, const double *&ck)
+{
+    ck = p.ckB + at;
+    if (!(p.warm_model & WARM_SHORTER) || !p.spec_ok[b * 2 + 1]) return 1.0;  // (no mended or sequential scan leaves them out)
+    const int lane = threadIdx.x & 63, KC = p.K * p.C;
+    const double own = lane < p.C ? ck[KC + lane] : 0.0;
+    ck = p.ckB2 + at;
+    return wave_sum(own) / wave_sum(lane < p.C ? ck[KC + lane] : 0.0);
+}
+
 // Verdicts in a launch of their own, for scans whose kernels do not work them out (duration-dependent transitions).
 // grid (B, directions), one wave.  The backward scans there have used the forward rows of the same attempt, so a backward
 // scan is accepted only where the forward one is.
