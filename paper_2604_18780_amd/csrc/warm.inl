@@ -36,7 +36,8 @@ template <int ET>
 __device__ __forceinline__ double warm_load(const Params &p, const int b, const int ch, const int L)
 {
     const int lane = threadIdx.x & 63, t = ch * PREP_CH + (threadIdx.x >> 6) * WARM_EVERY;
-    const double v = emis_at<ET>(p, ((size_t)b * p.T + max(min(t, L - 1), 0)) * p.C + min(lane, p.C - 1));
+    if (t >= L) return -INFINITY;  // (the same for the whole wave; positions beyond the sequence are never read)
+    const double v = emis_at<ET>(p, ((size_t)b * p.T + t) * p.C + min(lane, p.C - 1));
     return lane < p.C ? v : -INFINITY;
 }
 __device__ __forceinline__ float warm_sample(const Params &p, const int ch, const int L, const double v)  // per wave
