@@ -24,7 +24,6 @@
 // at every later position, less than 1/K of what the newer one adds there.
 // ---------------------------------------------------------------------------
 constexpr int WARM_EVERY = 64;      // one position in so many is sampled: one per wave and chunk
-constexpr int WARM_POOL = 16;       // sequences whose samples are taken together, where they have at most as many chunks
 constexpr int WARM_TERMS = 16;      // durations that enter lambda (a growth that needs more of them is slow anyway)
 constexpr int WARM_PER = 16;        // most window entries per thread of the comparison that ignores negligible ones
 constexpr double WARM_NATS = 27.6;  // log(1e12): a hundredth of the bound of the comparison
@@ -79,12 +78,11 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
     const int G = NT / C, g = tid / C, per = (K + G - 1) / G, k0 = g * per, k1 = g < G ? min(k0 + per, K) : k0;
 #pragma unroll
     for (int u = 0; u < WARM_PER; ++u) du[u] = p.dur[(size_t)min(k0 + u, K - 1) * C + tid % C];
-    // contrast: of this sequence, of short ones over a group of WARM_POOL (a few positions say little)
-    double con = 0.0, cnt = 0.0;
-    const int b0 = p.NCH <= WARM_POOL ? b / WARM_POOL * WARM_POOL : b, b1 = p.NCH <= WARM_POOL ? min(b0 + WARM_POOL, p.B) : b + 1;
+    // contrast: of this sequence alone, so that what happens to it does not depend on the others of its batch
+    double con = 0.0;
 #pragma unroll 8
-    for (int i = tid; i < (b1 - b0) * p.NCH; i += NT) con += (double)p.contrast[(size_t)b0 * p.NCH + i];
-    if (tid < b1 - b0) cnt = (double)((seq_len(p, b0 + tid) + WARM_EVERY - 1) / WARM_EVERY);
+    for (int i = tid; i < p.NCH; i += NT) con += (double)p.contrast[(size_t)b * p.NCH + i];
+    const double cnt = (double)((seq_len(p, b) + WARM_EVERY - 1) / WARM_EVERY);
     // ---- largest log weight of a longer duration over a shorter one, per label (and source label where they have
     // matrices of their own): ranges of durations, then over the ranges in order
     float favour = 0.f;  // lanes of the first wave: that of their label
@@ -152,7 +150,6 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
         if (e < CC) tl[e / C * ts + e % C] = tr[i];
     }
     con = wave_sum(con);
-    cnt = wave_sum(cnt);  // (the wave that goes on has it)
     __syncthreads();  // (the ranges above have been read)
     if (lane == 0) cons[wv] = con;
     // ---- detours of a label and its best successor, four threads per label

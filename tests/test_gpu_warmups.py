@@ -103,3 +103,25 @@ def test_best_segmentation(T, K, C, kind):
             got = oracle.path_score(w.emis[b], L, w.trans, w.dur, labels[b].cpu().numpy(), starts[b].cpu().numpy())
             assert abs(got - ref[b]) <= 1e-9 * max(1.0, abs(ref[b]))
         assert nseg[b].item() == starts[b].sum().item()
+
+
+@pytest.mark.parametrize("T,K,C", [(400, 16, 24), (1500, 40, 12), (700, 64, 24)])
+def test_a_sequence_does_not_depend_on_its_batch(T, K, C):
+    """The same sequence next to others whose scores are certain, or tell nothing at all: the same to the last bit."""
+    w = case(T, K, C, "plain", B=4)
+    w.lengths[:] = T
+    lone = None
+    for scale in (0.0, 1.0, 30.0):
+        w.emis[1:] *= scale
+        ws = sb.alloc_workspace(4, T, K, C, 0, 1, "cuda:0")
+        out = sb.semicrf_fwd_bwd(dev(w.emis), dev(w.lengths), dev(w.trans), dev(w.dur), None, 0, workspace=ws)
+        rep = sb.semicrf_scan_report(ws, 4, T, K, C, 0, 1) + sb.semicrf_seq_report(ws, 4, T, K, C, 0, 1)
+        fws = sb.alloc_workspace(4, T, K, C, 0, 0, "cuda:0")
+        sb.semicrf_logz_fwd(dev(w.emis), dev(w.lengths), dev(w.trans), dev(w.dur), workspace=fws)
+        rep += sb.semicrf_scan_report(fws, 4, T, K, C, 0, 0) + sb.semicrf_seq_report(fws, 4, T, K, C, 0, 0)
+        got = [x[0].cpu().numpy() for x in (out[0], out[1], out[4]) + rep]
+        if lone is not None:
+            assert all(np.array_equal(a, b) for a, b in zip(got, lone))
+        lone = got
+        w = case(T, K, C, "plain", B=4)
+        w.lengths[:] = T
