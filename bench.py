@@ -172,8 +172,9 @@ def time_call(call, steps, warmup):
 
 
 def accepted_summary(acc):
-    """How the (sequence, direction) scans were verified: first attempt / after repairs / long warm-up / sequential."""
-    return {"first": int((acc == 1).sum()), "repaired": int((acc == 2).sum()),
+    """How the (sequence, direction) scans were verified: at the first attempt (after a longer warm-up than the default where
+    labels are steps apart) / after repairs / after a second scan with a long warm-up / sequentially."""
+    return {"first": int((acc == 1).sum()), "first_longer": int((acc == 4).sum()), "repaired": int((acc == 2).sum()),
             "long_warm_up": int((acc == 3).sum()), "sequential": int((acc == 0).sum())}
 
 

@@ -375,7 +375,9 @@ int semicrf_fwd_bwd_profiled(const float *emis, const int32_t *lengths, const fl
  *   accepted [B,2] int32 device, or NULL: [b,0] forward scan (Algorithm 1), [b,1] backward
  *             scan (Algorithm 3): > 0 = the chunk-parallel result was verified and used:
  *             1 at the first attempt, 2 after the intervals whose start had disagreed were
- *             rerun from the state their neighbour reached, 3 after a warm-up longer than max(1.5K, 32);
+ *             rerun from the state their neighbour reached, 3 after a second scan with a longer
+ *             warm-up, 4 at the first attempt after a warm-up longer than max(1.5K, 32), chosen
+ *             because labels reach each other only over several steps;
  *             0 = the sequential scan computed it (flag SEMICRF_SEQUENTIAL_SCAN, sizes the
  *             chunk-parallel kernels do not cover, a direction that call did not run, or
  *             a boundary that did not agree).

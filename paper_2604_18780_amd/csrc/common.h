@@ -108,7 +108,8 @@ struct Params {
                         // longer than the default, WARM_SHORTER also if it is shorter (windows are then compared by what
                         // their entries can still contribute, and may be incomplete otherwise); 0: always the default
     double *negl;       // [B][C] see warm_plan
-    int4 *wlen;         // [B] first warm-up; duration-dependent transitions: warm-ups of the second attempt (forward, backward)
+    int4 *wlen;         // [B] first warm-up; duration-dependent transitions: warm-ups of the second attempt (forward, backward);
+                        // 1 where the first is longer than the default because labels are steps apart
     float *contrast;    // [B][NCH] sum over the sampled positions of a chunk of log sum_c exp(score - largest score)
     int warm0;          // first warm-up length of the chunk-parallel scans asked for by the caller (0 = default)
     int marg_route;     // 0 automatic, 1 marginals from the stored rows of both scans, 2 per-interval recurrence

@@ -209,9 +209,10 @@ __device__ __forceinline__ void spec_settle(const Params &p, const int b, const 
         }
     }
     if (lane != 0) return;
-    // how it was verified: 1 after the default warm-up or a shorter one, 2 after repairs, 3 after a longer warm-up: chosen
-    // from the model, or by a later attempt (what those did was decided by the number of boundaries that had disagreed before)
-    const int code = tier == 0 ? (first_warm(p, b, 0) > sum_warmup(p.K) + 3 ? 3 : 1) : (lr[0] <= (double)max(2, nint / 16) ? 2 : 3);
+    // which attempt verified it: 1 the first, or 4 the first after a warm-up as long as labels that are steps apart need
+    // (warm_plan); 2 after repairs, 3 after a longer warm-up (what the later attempts did was decided by the number of
+    // boundaries that had disagreed before)
+    const int code = tier == 0 ? (p.warm_model && p.wlen[b].w ? 4 : 1) : (lr[0] <= (double)max(2, nint / 16) ? 2 : 3);
     p.spec_rep[b * 2 + dir] = v.worst;
     p.spec_ok[b * 2 + dir] = v.ok ? code : 0;
     lr[0] = (double)v.nbad;

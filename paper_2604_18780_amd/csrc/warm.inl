@@ -244,7 +244,7 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
         else wd = fmin(wd, fmax(16.0, fmax(2.0 * m, slow) + 4.0));
     }
     if (!(p.warm_model & WARM_SHORTER)) wd = fmax(wd, (double)sum_warmup(K));
-    p.wlen[b] = make_int4(((int)wd + 3) & ~3, p.warm_long, p.warm_long, 0);
+    p.wlen[b] = make_int4(((int)wd + 3) & ~3, p.warm_long, p.warm_long, hops > 2 && wd > (double)sum_warmup(K));
 }
 
 // The first warm-up of a scan task of sequence b; deflt: what it is without a model.

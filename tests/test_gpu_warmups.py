@@ -125,3 +125,31 @@ def test_a_sequence_does_not_depend_on_its_batch(T, K, C):
         lone = got
         w = case(T, K, C, "plain", B=4)
         w.lengths[:] = T
+
+
+def labelled(B, T, K, C, sd, own=True, band=None, seed=1):
+    """Scores that follow a label path (2 for its label, unit noise) and transitions N(0, sd^2), the labels' own forbidden or not,
+    those beyond a band forbidden or not."""
+    g = np.random.default_rng(seed)
+    trans = (sd * g.standard_normal((C, C))).astype(np.float32)
+    d = np.abs(np.arange(C)[:, None] - np.arange(C)[None, :])
+    trans[(d == 0) & (not own) | (np.minimum(d, C - d) > (C if band is None else band))] = -1e4
+    emis = g.standard_normal((B, T, C)).astype(np.float32)
+    label = g.integers(0, C, (B, T + 1))
+    path = np.take_along_axis(label, np.cumsum(g.random((B, T)) < 3 / K, axis=1), 1)
+    np.put_along_axis(emis, path[:, :, None], np.take_along_axis(emis, path[:, :, None], 2) + 2.0, 2)
+    return dev(emis), None, dev(trans), dev((0.1 * g.standard_normal((K, C))).astype(np.float32))
+
+
+def score(x, B, T, K, C, flags=sb.SEMICRF_CENTER):
+    """logZ in 64 bits, and how the scan was verified."""
+    ws = sb.alloc_workspace(B, T, K, C, 0, 0, "cuda:0").fill_(255)
+    sb.semicrf_logz_fwd(*x, flags=flags, workspace=ws)
+    return (sb.semicrf_seq_report(ws, B, T, K, C, 0, 0)[1].cpu().numpy(), sb.semicrf_scan_report(ws, B, T, K, C, 0, 0)[0][:, 0].cpu().numpy())
+
+
+def test_the_report_tells_a_longer_first_attempt_from_a_second():
+    B, T, K, C = 4, 3000, 37, 19
+    x = labelled(B, T, K, C, 0.3, band=2)
+    assert (score(x, B, T, K, C)[1] == 4).all()
+    assert (score(x, B, T, K, C, sb.SEMICRF_CENTER | sb.SEMICRF_WARMUP(40))[1] == 3).all()
