@@ -10,13 +10,26 @@
 // g sum_k W[k,c] lambda^-k = 1, and what was in the window n positions ago has become lambda^-n of it.  The slowest label
 // decides.  g comes from the transition matrix: Etr[c,c] for the label itself, plus r Etr[c,o] Etr[o,c] for a detour of
 // one position through o, where r is how far the other labels' scores lie below the best one (the mean over every
-// WARM_EVERY-th position of log sum_c exp(score - best), sampled by k_colsum).  Models in which a label reaches
-// another only over several steps (forbidden transitions) forget more slowly, about in proportion to the steps.
+// WARM_EVERY-th position of log sum_c exp(score - best), sampled by k_colsum).
+//
+// Growth is not all: the labels' shares must settle, too.  They settle as fast where the transitions are about alike, and ever more
+// slowly the sharper these are, most of all where the scores tell nothing (r near 1), while the detours' sum grows.  So a
+// detour counts for 1 at most, and the length grows with s, the standard deviation of the transition scores that are not
+// forbidden (or by how much a label's own is above the others', where that is more): 1.15 + (0.02 + r) s^2 + (0.04 + 0.3 r) s^4
+// times what the growth asks for.  Where that factor is above 2.4 it varies too much from model to model to be worth less than
+// half of the default length.  Models in which a label reaches another only over several steps (forbidden transitions) forget
+// more slowly, about in proportion to the steps.
 //
 // The length only decides how long the scan takes: whether it was enough is checked at every interval boundary
-// (k_spec_cmp).  Measured in a replay of the recurrences on 96 random models of C = 3 .. 64, K = 4 .. 512, transitions N(0, s^2),
-// s = 0.1 .. 1: the mismatch falls below 1e-10 after 0.6 .. 1.8 times log(1e12) / log(lambda) positions (12 at C = 64, 16 .. 20
-// at C = 24, 28 at C = 8, 40 .. 56 at C = 3; 1.5 K before), 0.3 .. 0.8 of that per step where transitions are forbidden.
+// (k_spec_cmp).  Found in a replay of the recurrences at 24 boundaries of each of 10 752 random models: C = 3 .. 64, K = 8 .. 300,
+// transitions N(0, s^2), s = 0.1 .. 3, as they are, with 40 % or all beyond a band of 2 forbidden, with the labels' own
+// forbidden or raised by 1 or 2, all lowered by 2; scores that tell much, little and nothing; durations favoured by up to
+// 0.2 a position.  Positions until the mismatch is below 1e-13, in units of log(1e15) / log(lambda), at most (means of 2 and noise of
+// 1 | noise of 0.1 alone): 1.2 | 1.0 at s = 0.1, 1.1 | 1.4 at 0.5, 1.3 | 2.3 at 1, 1.7 | 5 at 1.3, 3.9 | 11 at 2; per step where
+// a band is all that is allowed, mostly 0.5 .. 0.8 | 1.7 .. 4.  Without a band the choice sufficed at all 24 boundaries for every
+// model up to s = 1 whose scores tell anything, but for 0 .. 10 % of those with the labels' own raised by 2,
+// 0 .. 12 % by 1, 0 .. 2 % with 40 % forbidden; where they tell nothing but for 0 .. 4 %; up to s = 1.6 but for 0 .. 22 % (25 %); with means of 2 it was 47 positions
+// on average, of 179 by default.  Of a thousand boundaries one or two take longer, mostly in long runs of one label: those are mended.
 //
 // A longer warm-up than K + (that) is never needed for the windows to agree entry by entry; a shorter one leaves the older
 // entries of the window different, in places where they no longer matter.  negl[c] = 1 / (K R), with R the largest ratio of
@@ -26,7 +39,8 @@
 constexpr int WARM_EVERY = 64;      // one position in so many is sampled: one per wave and chunk
 constexpr int WARM_TERMS = 16;      // durations that enter lambda (a growth that needs more of them is slow anyway)
 constexpr int WARM_PER = 16;        // most window entries per thread of the comparison that ignores negligible ones
-constexpr double WARM_NATS = 27.6;  // log(1e12): a hundredth of the bound of the comparison
+constexpr double WARM_NATS = 34.5;  // log(1e15): a hundredth of the bound on states after a chosen warm-up
+constexpr double WARM_FACTOR = 2.4; // largest factor for sharpness with which any length below the default is chosen
 static_assert(PREP_CH == WARM_EVERY * (NT / 64), "every wave takes one sample of a chunk");
 
 // The contrast of a chunk's scores: every wave takes one position, a label per lane.  warm_load is called early, so that
@@ -52,10 +66,11 @@ __device__ __forceinline__ float warm_sample(const Params &p, const int ch, cons
 // LDS by four threads per label.  lds: (PREP_NSEG + 1) C doubles, buf: 2 NT.
 __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf)
 {
-    // buf, one after the other: ranges of durations [3 * NT]; then detours, successors and best successors, [4][64] each
-    float *red = (float *)buf, *part = (float *)buf, *best4 = (float *)(buf + 3 * NT / 2);
-    unsigned long long *succ = (unsigned long long *)(buf + NT / 2);
-    __shared__ double cons[NT / 64];
+    // buf, one after the other: ranges of durations [3 * NT]; detours (all, counted for 1 at most) and best successors, [4][64]
+    // each; successors [4][64]
+    float *red = (float *)buf, *part = (float *)buf, *part1 = part + NT, *best4 = part + 2 * NT;
+    unsigned long long *succ = (unsigned long long *)buf;
+    __shared__ double cons[NT / 64], off[3][NT / 64];
     static_assert(NT == 4 * 64, "four threads per label");
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int K = p.K, C = p.C, CC = C * C;
@@ -66,14 +81,14 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
     const int lc = min(lane, C - 1), n = min(K, WARM_TERMS);
     // ---- requests: transitions, the first durations of the lane's label, this thread's range of durations, contrast
     constexpr int NTR = (64 * 64 + NT - 1) / NT, NWR = (64 * WARM_TERMS + NT - 1) / NT;
-    float tr[NTR], wq[NWR], du[WARM_PER];
+    float tr[NTR], wq[NWR], dq[NWR], du[WARM_PER];
 #pragma unroll
     for (int i = 0; i < NTR; ++i) tr[i] = i * NT < CC ? t1[min(i * NT + tid, CC - 1)] : 0.f;
 #pragma unroll
     for (int i = 0; i < NWR; ++i) {
         const int e = min(i * NT + tid, n * C - 1);
         wq[i] = p.dur[e];
-        if (dt) wq[i] += p.trans3[(size_t)(e / C) * CC + e % C * (C + 1)];
+        dq[i] = dt ? p.trans3[(size_t)(e / C) * CC + e % C * (C + 1)] : 0.f;
     }
     const int G = NT / C, g = tid / C, per = (K + G - 1) / G, k0 = g * per, k1 = g < G ? min(k0 + per, K) : k0;
 #pragma unroll
@@ -140,6 +155,7 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
         if (tid < C) {
             double best = lds[tid];
             for (int o = 1; o < C; ++o) best = fmax(best, lds[o * C + tid]);
+            favour = (float)best;
             p.negl[(size_t)b * C + tid] = best < 600.f ? exp(-1.001 * (double)best) / (double)K : 0.0;  // (differences are rounded)
         }
         __syncthreads();
@@ -154,54 +170,63 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
     if (lane == 0) cons[wv] = con;
     // ---- detours of a label and its best successor, four threads per label
     const float stay = tl[lc * ts + lc];
-    float det = 0.f, mx = -INFINITY;
+    float det = 0.f, det1 = 0.f, mx = -INFINITY;
     const int o0 = wv * ((C + 3) / 4), o1 = min(o0 + (C + 3) / 4, C);
 #pragma unroll 4
     for (int o = o0; o < o1; ++o) {
-        const float out = tl[lc * ts + o];
-        det += o == lc ? 0.f : __expf(out + tl[o * ts + lc] - stay);
+        const float out = tl[lc * ts + o], d = o == lc ? 0.f : __expf(out + tl[o * ts + lc]);
+        det += d;
+        det1 += fminf(d, 1.f);
         mx = fmaxf(mx, out);
     }
     part[wv * 64 + lane] = det;
+    part1[wv * 64 + lane] = det1;
     best4[wv * 64 + lane] = mx;
     __syncthreads();
     mx = fmaxf(fmaxf(best4[lane], best4[64 + lane]), fmaxf(best4[128 + lane], best4[192 + lane]));
-    unsigned long long reach = 0;  // successors within eight nats of the best one
-#pragma unroll 4
-    for (int o = o0; o < o1; ++o) reach |= (unsigned long long)(tl[lc * ts + o] > mx - 8.f) << o;
-    succ[wv * 64 + lane] = reach;
+    det = ((part[lane] + part[64 + lane]) + part[128 + lane]) + part[192 + lane];
+    det1 = ((part1[lane] + part1[64 + lane]) + part1[128 + lane]) + part1[192 + lane];
     __syncthreads();
-    float *wl = tl;  // [WARM_TERMS][C], in the place of the transitions
+    unsigned long long reach = 0;        // successors within eight nats of the best one
+    double os = 0.0, oss = 0.0, on = 0.0;  // scores of the other labels (forbidden ones apart): sum, of squares, number
+#pragma unroll 4
+    for (int o = o0; o < o1; ++o) {
+        const float v = tl[lc * ts + o];
+        reach |= (unsigned long long)(v > mx - 8.f) << o;
+        const double x = lane < C && o != lc && v > mx - 50.f ? (double)v : 0.0;
+        os += x;
+        oss += x * x;
+        on += lane < C && o != lc && v > mx - 50.f ? 1.0 : 0.0;
+    }
+    succ[wv * 64 + lane] = reach;
+    os = wave_sum(os);
+    oss = wave_sum(oss);
+    on = wave_sum(on);
+    if (lane == 0) off[0][wv] = os, off[1][wv] = oss, off[2][wv] = on;
+    __syncthreads();
+    float *wl = tl;  // [2][WARM_TERMS][C], in the place of the transitions: durations, own transitions of each
 #pragma unroll
-    for (int i = 0; i < NWR; ++i)
-        if (i * NT + tid < n * C) wl[i * NT + tid] = wq[i];
+    for (int i = 0; i < NWR; ++i) {
+        if (i * NT + tid < n * C) {
+            wl[i * NT + tid] = wq[i];
+            wl[WARM_TERMS * C + i * NT + tid] = dq[i];
+        }
+    }
     __syncthreads();
     if (wv != 0) return;
     con = ((cons[0] + cons[1]) + cons[2]) + cons[3];
     const float r = cnt > 0.0 ? (__expf((float)(con / cnt)) - 1.f) / (float)(C - 1) : 0.f;
-    det = ((part[lane] + part[64 + lane]) + part[128 + lane]) + part[192 + lane];
-    // ---- growth of the label: y = 1 / lambda
-    float y1 = 1.f;
+    // ---- how sharp the transitions are: s^2
+    double sharp;
     {
-        float w[WARM_TERMS];
-#pragma unroll
-        for (int k = 0; k < WARM_TERMS; ++k) w[k] = k < n ? __expf(wl[min(k, n - 1) * C + lc] + (dt ? 0.f : stay)) : 0.f;
-        const float q = 1.f + r * det;
-        float y0 = 0.f;
-        for (int it = 0; it < 12; ++it) {
-            const float y = 0.5f * (y0 + y1);
-            float s0 = 0.f, s1 = 0.f;  // even and odd durations, two chains
-#pragma unroll
-            for (int k = WARM_TERMS - 2; k >= 0; k -= 2) {
-                s0 = fmaf(s0, y * y, w[k]);
-                s1 = fmaf(s1, y * y, w[k + 1]);
-            }
-            if (q * fmaf(s1, y, s0) * y > 1.f) y1 = y;
-            else y0 = y;
-        }
+        const bool own = lane < C && stay > mx - 50.f;
+        const double so = own ? (double)stay : 0.0, sn = wave_sum(own ? 1.0 : 0.0), st = wave_sum(so), sst = wave_sum(so * so);
+        os = ((off[0][0] + off[0][1]) + off[0][2]) + off[0][3];
+        oss = ((off[1][0] + off[1][1]) + off[1][2]) + off[1][3];
+        on = ((off[2][0] + off[2][1]) + off[2][2]) + off[2][3];
+        const double mean = (os + st) / (on + sn), raised = on > 0.0 && sn > 0.0 ? fmax(st / sn - os / on, 0.0) : 0.0;
+        sharp = fmax((oss + sst) / (on + sn) - mean * mean, raised * raised);
     }
-    double lam = lane < C ? (double)-__logf(y1) : INFINITY;  // log(lambda); 0 where there is no growth
-    lam = -wave_max(lam == lam ? -lam : 0.0);
     // ---- steps from a label to every other
     reach = (succ[lane] | succ[64 + lane]) | (succ[128 + lane] | succ[192 + lane]);
     const unsigned long long full = C >= 64 ? ~0ull : (1ull << C) - 1ull;
@@ -224,27 +249,63 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
         }
     }
     favour = (float)wave_max((double)favour);
-    if (lane != 0) return;
     if (p.logpair) {
         // Best score: what decides is how soon all best paths into a window have met, which takes an emission that tells
-        // the labels apart and a label change or a split that pays.  In a replay of 8 x 800 and 40 x 150 .. 400 boundaries of
-        // random models (C = 3 .. 54, K = 8 .. 423, transitions N(0, s^2), s = 0.1 .. 1) all had met after 32 positions where
-        // there are eight labels or more, after 64 but for 2 where there are three or four (2 K before, 128 .. 846).
-        // Models out of that range keep that length.
+        // the labels apart, but not for certain, and a label change or a split that pays.  In a replay of 12 boundaries of each of 3 504
+        // models (C = 3 .. 48, K = 24 .. 128, transitions N(0, s^2)) the share of models where not all had met after these lengths,
+        // and after 2 K: r = 0.12 .. 0.4, s up to 1.5 0.2 % (up to 98 positions), 0; s = 2 0.9 %, 0; r = 0.35 .. 0.56, s up to 1 0, 0, s = 1.5 11 %, 7 %;
+        // r = 0.58 .. 0.88 0 .. 63 %, 0 .. 44 %; r = 0.03 .. 0.05 4 .. 26 %, 0 .. 4 %; own transitions or others forbidden 0 .. 63 %, 0 .. 89 %.
+        if (lane != 0) return;
         const int deflt = vit_warmup(K), shrt = C >= 16 ? 40 : (C >= 8 ? 48 : (C >= 5 ? 64 : 96));
-        p.wlen[b].x = hops == 1 && favour < 4.f && r > 0.02f ? min(shrt, deflt) : deflt;
+        const bool plain = hops == 1 && favour < 4.f && r > 0.08f && r < 0.45f && sharp < 1.7 * 1.7;
+        p.wlen[b].x = plain ? min(shrt, deflt) : deflt;
         return;
     }
-    double wd = (double)sum_warmup(K);
-    if (lam > 0.01 && hops < 64) {
-        const double m = WARM_NATS / lam;
-        const double slow = 0.85 * m * (double)hops;
-        // longer than the default only where labels are far apart; sure scores forget faster than the growth of their runs says
-        if (hops > 2 && slow > wd) wd = fmin(slow, (double)p.warm_long);
-        else wd = fmin(wd, fmax(16.0, fmax(2.0 * m, slow) + 4.0));
+    // ---- growth of the label: y = 1 / lambda
+    float y1 = 1.f;
+    {
+        const float q = r * (hops > 2 ? det : det1);  // (steps are counted for themselves)
+        float w[WARM_TERMS];
+#pragma unroll
+        for (int k = 0; k < WARM_TERMS; ++k) {
+            const float *wk = wl + min(k, n - 1) * C + lc;
+            w[k] = k < n ? __expf(wk[0]) * (__expf(dt ? wk[WARM_TERMS * C] : stay) + q) : 0.f;
+        }
+        float y0 = 0.f;
+        for (int it = 0; it < 12; ++it) {
+            const float y = 0.5f * (y0 + y1);
+            float s0 = 0.f, s1 = 0.f;  // even and odd durations, two chains
+#pragma unroll
+            for (int k = WARM_TERMS - 2; k >= 0; k -= 2) {
+                s0 = fmaf(s0, y * y, w[k]);
+                s1 = fmaf(s1, y * y, w[k + 1]);
+            }
+            if (fmaf(s1, y, s0) * y > 1.f) y1 = y;
+            else y0 = y;
+        }
     }
-    if (!(p.warm_model & WARM_SHORTER)) wd = fmax(wd, (double)sum_warmup(K));
-    p.wlen[b] = make_int4(((int)wd + 3) & ~3, p.warm_long, p.warm_long, hops > 2 && wd > (double)sum_warmup(K));
+    double lam = lane < C ? (double)-__logf(y1) : INFINITY;  // log(lambda); 0 where there is no growth
+    lam = -wave_max(lam == lam ? -lam : 0.0);
+    if (lane != 0) return;
+    const double deflt = (double)sum_warmup(K);
+    double wd = deflt;
+    if (lam > 0.01 && hops < 64) {
+        // a few positions say little about the contrast; entries that later durations favour must have fallen further
+        const double m = (WARM_NATS + (double)favour) / lam * (1.0 + 0.25 / sqrt(fmax(cnt, 1.0)));
+        if (hops > 2) {
+            const double far = (0.55 + 1.5 * (double)r) * m * (double)hops;
+            if (far > deflt) wd = fmin(far, (double)p.warm_long);
+            else if (sharp < 1.6 * 1.6) wd = fmin(deflt, fmax(16.0, far) + 4.0);
+        } else if (sharp < 2.2 * 2.2) {
+            const double factor = 1.15 + (0.02 + (double)r) * sharp + (0.04 + 0.3 * (double)r) * sharp * sharp;
+            const double n = fmax(16.0, factor * m) + 4.0;
+            if (n < (factor <= WARM_FACTOR ? deflt : 0.5 * deflt)) wd = n;
+            // sharp transitions and windows that will hardly agree entry by entry after the default length
+            else if (factor <= WARM_FACTOR && sharp > 0.36 && (double)K + 0.5 * n > deflt) wd = fmin(n, 1.5 * deflt);
+        }
+    }
+    if (!(p.warm_model & WARM_SHORTER)) wd = hops > 2 ? fmax(wd, deflt) : deflt;
+    p.wlen[b] = make_int4(wd == deflt ? sum_warmup(K) : ((int)wd + 3) & ~3, p.warm_long, p.warm_long, hops > 2 && wd > deflt);
 }
 
 // The first warm-up of a scan task of sequence b; deflt: what it is without a model.

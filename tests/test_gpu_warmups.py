@@ -153,3 +153,14 @@ def test_the_report_tells_a_longer_first_attempt_from_a_second():
     x = labelled(B, T, K, C, 0.3, band=2)
     assert (score(x, B, T, K, C)[1] == 4).all()
     assert (score(x, B, T, K, C, sb.SEMICRF_CENTER | sb.SEMICRF_WARMUP(40))[1] == 3).all()
+
+
+@pytest.mark.parametrize("B,T,K,C", [(16, 2000, 32, 32), (8, 2000, 32, 64), (4, 4000, 20, 48), (4, 4000, 64, 24), (2, 8000, 128, 12)])
+@pytest.mark.parametrize("sd,own", [(0.3, True), (0.3, False), (1.0, True), (1.0, False), (1.5, True)])
+def test_sharper_transitions_are_not_scanned_twice(B, T, K, C, sd, own):
+    x = labelled(B, T, K, C, sd, own)
+    lz, acc = score(x, B, T, K, C)
+    print(f"[case] K={K} C={C} sd={sd} own {own} verified at {acc.tolist()}", flush=True)
+    assert ((acc == 1) | (acc == 2)).all() and (acc == 1).mean() >= 0.75  # a boundary that takes longer is mended
+    ref = score(x, B, T, K, C, sb.SEMICRF_CENTER | sb.SEMICRF_SEQUENTIAL_SCAN)[0]
+    assert np.abs(lz - ref).max() <= 1e-10 * (T / 8)  # the bound of a boundary, and at most that many of them
