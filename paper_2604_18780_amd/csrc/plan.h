@@ -48,10 +48,16 @@ constexpr int sum_warmup(int K) { return 3 * K / 2 < 32 ? 32 : (3 * K + 1) / 2; 
 constexpr int long_warmup(int K) { return 8 * K < 64 ? 64 : 8 * K; }
 constexpr int WARM_LONG_LEAST = 768;
 
-// First and longest warm-up of the best-score scan where they do not come from the model.  (What is rejected after the
-// longest is scanned sequentially, 0.4 us a position.)
+// First warm-up of the best-score scan where it does not come from the model, and the longest.  What is rejected after the
+// longest is scanned sequentially, 0.4 us a position, so it is at least 256 positions where the sequence is long next to that;
+// short ones pay for the positions (64 x 256, K = 16, C = 24 153 us a call after 128, 186 after 256), and those of 4000 do where
+// 8 K suffices (K = 20, C = 48 387 us after 160, 433), but 3600 where it does not (transitions N(0, 2^2)).
 constexpr int vit_warmup(int K) { return 2 * K < 32 ? 32 : 2 * K; }
-constexpr int vit_long_warmup(int K) { return 8 * K < 256 ? 256 : 8 * K; }
+constexpr int vit_long_warmup(int K, int T)
+{
+    const int least = T / 16 < 64 ? 64 : (T / 16 > 256 ? 256 : T / 16);
+    return 8 * K < least ? least : 8 * K;
+}
 
 // Single-wave tasks a compute unit holds at once for these sizes (scan kernel, interval kernel); false when
 // the one-wave kernels do not apply.

@@ -542,7 +542,7 @@ int launch_viterbi_k(const Params &p, hipStream_t st)
         return SEMICRF_ELAUNCH;
     if (p.spec) {
         // chunk-parallel scan with two warm-up lengths, as for the sum recurrences
-        int warm[2] = {vit_warmup(p.K), vit_long_warmup(p.K)};
+        int warm[2] = {vit_warmup(p.K), vit_long_warmup(p.K, p.T)};
         if (p.warm0 > 0) warm[0] = p.warm0, warm[1] = 4 * p.warm0;  // the caller's first warm-up length
         if (hipFuncSetAttribute((const void *)k_vit_spec<CT, NKW, false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)(SW * lds)) != hipSuccess ||

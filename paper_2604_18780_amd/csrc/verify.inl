@@ -241,9 +241,8 @@ __global__ __launch_bounds__(64) void k_spec_fix(Params p, int ndir, int tier)
     if (tier > 0 && p.spec_ok[b * 2 + dir]) return;
     SpecVerdict v = spec_verdict(p, b, dir, lane);
     if (p.warm_model && tier == 0 && lane == 0) {
-        // the next attempt's warm-up, as spec_job works it out
         const int w0 = p.wlen[b].x;
-        (&p.wlen[b].y)[dir] = v.ok ? w0 : max(w0, second_warm(p, w0, v.worst));
+        (&p.wlen[b].y)[dir] = v.ok ? w0 : last_warm(p, w0);
     }
     if (dir == 1) v.ok = v.ok && spec_verdict(p, b, 0, lane).ok;
     spec_settle(p, b, dir, ndir, tier, v, lane);

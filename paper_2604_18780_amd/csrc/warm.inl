@@ -324,10 +324,21 @@ __device__ __forceinline__ int dt_warm(const Params &p, const int b, const int d
 
 // Warm-up of the second attempt where the first, of `warm` positions, left the mismatch `worst`.  The mismatch falls
 // geometrically, so the length that brings it to 1e-12 follows; a quarter and half a segment length on top for
-// stretches that forget more slowly.  Hopeless cases take eight segment lengths, or twice what was tried.
+// stretches that forget more slowly, never less than the default.  What follows overshoots where the mismatch has hardly
+// begun to fall (K = 34, C = 12, transitions N(0, 2^2) .. N(0, 3^2): 272 positions suffice where 350 .. 480 follow, 195 -> 280 us a
+// call), so eight segment lengths, or twice what was tried, are the most, and what hopeless cases take; the third attempt goes further.
 __device__ __forceinline__ int second_warm(const Params &p, const int warm, const double worst)
 {
-    double w = (double)max(max(8 * p.K, 64), 2 * warm);
-    if (worst > 0.0 && worst < 0.1) w = 1.25 * (double)warm * (-27.7 / log(worst)) + 0.5 * (double)p.K;
-    return ((int)fmin(w, (double)p.warm_long) + 3) & ~3;
+    const double most = p.warm_model ? fmin((double)max(long_warmup(p.K), 2 * warm), (double)p.warm_long) : (double)p.warm_long;
+    double w = most;
+    if (worst > 0.0 && worst < 0.1) w = fmin(w, 1.25 * (double)warm * (-27.7 / log(worst)) + 0.5 * (double)p.K);
+    if (p.warm_model) w = fmax(w, (double)sum_warmup(p.K));
+    return ((int)w + 3) & ~3;
+}
+
+// The same for the scans with duration-dependent transitions, whose second attempt is the last before the whole sequence is
+// scanned: eight segment lengths, or twice a first warm-up that was chosen longer than the default.
+__device__ __forceinline__ int last_warm(const Params &p, const int warm)
+{
+    return warm > sum_warmup(p.K) ? min(max(long_warmup(p.K), 2 * warm), p.warm_long) : long_warmup(p.K);
 }
