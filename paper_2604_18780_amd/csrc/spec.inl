@@ -14,7 +14,7 @@
 // Nothing is taken on trust: k_spec_cmp compares, for every chunk boundary, the state
 // the previous chunk actually reached with the warm-up state the next chunk started
 // from, entry by entry or by what an entry can still contribute, after removing their common scale
-// factor.  If all boundaries of a (sequence, direction) agree to SPEC_TOL the warm-up states do what the
+// factor.  If all boundaries of a (sequence, direction) agree (spec_tol) the warm-up states do what the
 // sequential states do, to that relative accuracy (perturbations of the start do not grow: the maps
 // are non-expansive in the projective metric).  The warm-up is 1.5 K positions, or what the model asks
 // for (warm_plan): genomic shape 96 -> 40, scans 310 -> 278 us; K = 512, C = 8 768 -> 56, 684 -> 388 us;
@@ -38,6 +38,7 @@ constexpr int SPEC_RUN_MAX = 2;  // intervals one wave mends in a row in the rep
 struct SpecJob {
     bool idle, mend;
     int warm, nint;
+    double tol;
     const double *err;
 };
 __device__ __forceinline__ SpecJob spec_job(const Params &p, const int b, const int dir, const int j, const int ndir,
@@ -48,6 +49,7 @@ __device__ __forceinline__ SpecJob spec_job(const Params &p, const int b, const 
     s.idle = s.mend = false;
     s.warm = warm;
     s.nint = 0;
+    s.tol = SPEC_TOL;
     s.err = p.spec_err + ((size_t)b * 2 + dir) * (p.N + 1);
     if (tier == 0) return s;
     const int lane = threadIdx.x & 63;
@@ -55,7 +57,8 @@ __device__ __forceinline__ SpecJob spec_job(const Params &p, const int b, const 
         s.idle = true;
         return s;
     }
-    const SpecVerdict v = spec_verdict(p, b, dir, lane);
+    const SpecVerdict v = spec_verdict(p, b, dir, lane, tier - 1);
+    s.tol = spec_tol(p, b, tier - 1);
     if (j == 0 && settles) spec_settle(p, b, dir, ndir, tier - 1, v, lane);
     s.idle = v.ok;
     s.nint = v.nint;
@@ -66,7 +69,7 @@ __device__ __forceinline__ SpecJob spec_job(const Params &p, const int b, const 
     return s;
 }
 // Boundary m disagreed in the attempt before.
-__device__ __forceinline__ bool spec_bad(const SpecJob &s, const int m) { return m >= 1 && m <= s.nint - 1 && !(s.err[m] <= SPEC_TOL); }
+__device__ __forceinline__ bool spec_bad(const SpecJob &s, const int m) { return m >= 1 && m <= s.nint - 1 && !(s.err[m] <= s.tol); }
 
 // One scan task of the chunk-parallel scan, one wave (window and time blocking as above).
 // repair: the task restarts from the state its neighbour in scan order REACHED at their common boundary (no

@@ -2,7 +2,17 @@
 // (sequence, direction), and what an accepted one leaves for the later kernels.
 // Included by semicrf.hip inside its anonymous namespace (after common.h); not a translation unit of its own.
 
+// Largest disagreement at a boundary that is accepted: of two windows entry by entry after a default warm-up or a retry, which
+// leave 1e-15 nearly everywhere; and where it is the choice of the warm-up that decides how much is left, or only what entries can
+// still contribute that agrees: a length of L positions makes logZ some 3 L, whose 64 bits end at 3e-16 L or above, so that neither
+// costs a digit of it.
 constexpr double SPEC_TOL = 1e-10;
+__device__ __forceinline__ double spec_tol_chosen(const Params &p, const int b) { return fmax(1e-13, 1e-16 * (double)p.hdr[b].L); }
+// The bound of an attempt.
+__device__ __forceinline__ double spec_tol(const Params &p, const int b, const int attempt)
+{
+    return attempt == 0 && p.warm_model && p.wlen[b].x != sum_warmup(p.K) ? spec_tol_chosen(p, b) : SPEC_TOL;
+}
 constexpr int SPEC_ATTEMPTS = 3;
 
 // One workgroup per (chunk boundary j, sequence, direction): compare the state chunk j-1
@@ -10,11 +20,11 @@ constexpr int SPEC_ATTEMPTS = 3;
 // neighbouring chunk started from.  Number 0 is no boundary: its workgroup checks that the forward scan's final
 // message vector can be summed (entry nint of the mismatches).
 //
-// negl: directions (bit 0 forward, bit 1 backward) whose windows are compared by what their entries can still contribute (p.negl,
-// see warm_plan): the difference of two entries counts against the larger of the two, or against negl[c] times the largest
-// newer entry of the label, whichever is more.  At every later position an entry's difference then adds at most 1e-10 / K of
-// what the newer entry adds there, so the states agree to 2e-10 in all they do, as with the plain comparison: everything a
-// state does later is a sum of positive multiples of these direct contributions.
+// negl: directions (bit 0 forward, bit 1 backward) whose windows may be compared by what their entries can still contribute
+// (p.negl, see warm_plan): the difference of two entries counts against the larger of the two, or against negl[c] times the largest
+// newer entry of the label, whichever is more.  At every later position an entry's difference then adds at most the bound / K of
+// what the newer entry adds there, so the states agree to twice the bound in all they do: everything a state does later is a sum of
+// positive multiples of these direct contributions.  Windows that agree entry by entry are not looked at this way.
 template <int PER>
 __global__ __launch_bounds__(NT) void k_spec_cmp(Params p, int tier, int negl, int G, int per)
 {
@@ -34,7 +44,7 @@ __global__ __launch_bounds__(NT) void k_spec_cmp(Params p, int tier, int negl, i
     const bool contrib = PER > 0 && ((negl >> dir) & 1);
     bool shorter = false;
     if (PER > 0) {
-        shorter = p.wlen[b].x < sum_warmup(K);
+        shorter = tier == 0 && p.wlen[b].x < sum_warmup(K);
         const int tm = j * p.Delta % K;
         int sl = dir ? tm + d0 : tm - d0;  // slot of the position at that distance
         sl += dir ? (sl >= K ? -K : 0) : (sl < 0 ? K : 0);
@@ -101,7 +111,8 @@ __global__ __launch_bounds__(NT) void k_spec_cmp(Params p, int tier, int negl, i
             for (int u = 0; u < PER; ++u) differ(x[u], y[u], 0.0);
             over_waves();
         }
-        if (contrib && (shorter || err > SPEC_TOL)) {
+        const double whole = shorter ? DBL_MAX : err;
+        if (contrib && whole > spec_tol(p, b, tier)) {
             double big = 0.0;
 #pragma unroll
             for (int u = 0; u < PER; ++u) big = fmax(big, fmin(x[u], y[u]));
@@ -119,6 +130,7 @@ __global__ __launch_bounds__(NT) void k_spec_cmp(Params p, int tier, int negl, i
                 big = fmax(big, fmin(x[u], y[u]));
             }
             over_waves();
+            if (!shorter && err > spec_tol_chosen(p, b)) err = whole;
         }
     }
     if (tid == 0) {
@@ -134,9 +146,10 @@ struct SpecVerdict {
     int nint, nbad;  // intervals; boundaries that disagreed
     double worst;
 };
-__device__ __forceinline__ SpecVerdict spec_verdict(const Params &p, const int b, const int dir, const int lane)
+__device__ __forceinline__ SpecVerdict spec_verdict(const Params &p, const int b, const int dir, const int lane, const int attempt)
 {
     SpecVerdict v;
+    const double tol = spec_tol(p, b, attempt);
     const double *err = p.spec_err + ((size_t)b * 2 + dir) * (p.N + 1);
     v.nint = (p.hdr[b].L + p.Delta - 1) / p.Delta;
     v.worst = 0.0;
@@ -145,11 +158,11 @@ __device__ __forceinline__ SpecVerdict spec_verdict(const Params &p, const int b
     for (int i = 1 + lane; i < v.nint; i += 64) {
         const double e = err[i];
         v.worst = fmax(v.worst, e);
-        bad += !(e <= SPEC_TOL);
+        bad += !(e <= tol);
     }
     v.worst = wave_max(v.worst);
     v.nbad = (int)wave_sum((double)bad);
-    v.ok = v.nbad == 0 && v.worst <= SPEC_TOL && (dir == 1 || v.nint == 0 || err[v.nint] == 0.0);
+    v.ok = v.nbad == 0 && v.worst <= tol && (dir == 1 || v.nint == 0 || err[v.nint] == 0.0);
     return v;
 }
 
@@ -239,12 +252,12 @@ __global__ __launch_bounds__(64) void k_spec_fix(Params p, int ndir, int tier)
 {
     const int b = blockIdx.x, dir = blockIdx.y, lane = threadIdx.x;
     if (tier > 0 && p.spec_ok[b * 2 + dir]) return;
-    SpecVerdict v = spec_verdict(p, b, dir, lane);
+    SpecVerdict v = spec_verdict(p, b, dir, lane, tier);
     if (p.warm_model && tier == 0 && lane == 0) {
         const int w0 = p.wlen[b].x;
         (&p.wlen[b].y)[dir] = v.ok ? w0 : last_warm(p, w0);
     }
-    if (dir == 1) v.ok = v.ok && spec_verdict(p, b, 0, lane).ok;
+    if (dir == 1) v.ok = v.ok && spec_verdict(p, b, 0, lane, tier).ok;
     spec_settle(p, b, dir, ndir, tier, v, lane);
 }
 
@@ -255,7 +268,7 @@ __device__ __forceinline__ bool spec_settled(const Params &p, const int b, const
     if (!p.spec) return false;
     if (p.spec_ok[b * 2 + dir]) return true;
     const int lane = threadIdx.x & 63;
-    const SpecVerdict v = spec_verdict(p, b, dir, lane);
+    const SpecVerdict v = spec_verdict(p, b, dir, lane, tier);
     if (threadIdx.x < 64) spec_settle(p, b, dir, ndir, tier, v, lane);
     return v.ok;
 }

@@ -164,3 +164,16 @@ def test_sharper_transitions_are_not_scanned_twice(B, T, K, C, sd, own):
     assert ((acc == 1) | (acc == 2)).all() and (acc == 1).mean() >= 0.75  # a boundary that takes longer is mended
     ref = score(x, B, T, K, C, sb.SEMICRF_CENTER | sb.SEMICRF_SEQUENTIAL_SCAN)[0]
     assert np.abs(lz - ref).max() <= 1e-10 * (T / 8)  # the bound of a boundary, and at most that many of them
+
+
+@pytest.mark.parametrize("B,T,K,C,sd", [(2, 512, 8, 4, 1.5), (64, 256, 16, 24, 1.0), (64, 256, 16, 24, 1.5), (8, 1000, 34, 12, 1.0),
+                                        (8, 1000, 34, 12, 2.0), (4, 4000, 100, 3, 2.0)])
+def test_chosen_warm_ups_cost_no_digits(B, T, K, C, sd):
+    """logZ in 64 bits, next to the sequential scan's: a few units in the last place, as after a warm-up of 1.5 K, although windows that
+    agree in what they still contribute are accepted too."""
+    x = labelled(B, T, K, C, sd)
+    lz, acc = score(x, B, T, K, C)
+    ref = score(x, B, T, K, C, sb.SEMICRF_CENTER | sb.SEMICRF_SEQUENTIAL_SCAN)[0]
+    rel = (np.abs(lz - ref) / np.abs(ref)).max()
+    print(f"[case] K={K} C={C} sd={sd} verified at {sorted(set(acc.tolist()))}, logZ differs by {rel:.1e}", flush=True)
+    assert rel <= 1e-15
