@@ -83,8 +83,9 @@ __global__ __launch_bounds__(NT) void k_spec_cmp(Params p, int tier, int negl, i
     if (!(s1 > 0.0) || !(s2 > 0.0) || !(f > 0.0) || !(f < DBL_MAX)) err = DBL_MAX;
     auto differ = [&](const double x, const double y, const double least) {
         const double m = fmax(fabs(x), fabs(y));
-        // (an estimate of the reciprocal, good to eight digits, decides as well as a division; 1e307: no message is larger)
-        if (m > 1e-290) err = fmax(err, fabs(x - y) * __builtin_amdgcn_rcp(fmax(m, least)));
+        // (a reciprocal by the hardware's estimate and one Newton step: to the last bits; 1e307: no message is larger)
+        const double w = fmax(m, least), r = __builtin_amdgcn_rcp(w);
+        if (m > 1e-290) err = fmax(err, fabs(x - y) * fma(fma(-w, r, 1.0), r, r));
         if (!(m < 1e307)) err = DBL_MAX;
     };
     auto over_waves = [&]() {  // the largest over the workgroup, in every thread
