@@ -194,7 +194,13 @@ int make_plan(int B, int T, int K, int C, int ckpt_interval, int want_grad, Plan
     sz[PL_SUMR] = g * b * np * c * 8;
     sz[PL_CARRY] = g * b * np * c * 8;
     sz[PL_SINK] = (size_t)SINK_DOUBLES * 8;
-    sz[PL_WARM] = warm_layout(B, C, pl->NCH).total;
+    // What the choice of the warm-up leaves is read until the scans are settled, and the partial sums are written after that: in a
+    // gradient call it lies where they do, and the workspace is as small as without it.  (Where they are smaller, one interval
+    // is thousands of positions, and no choice is made.)
+    const size_t warm = warm_layout(B, C, pl->NCH).total, sums = align_up(sz[PL_PARTD]) + align_up(sz[PL_PARTTR]) +
+        align_up(sz[PL_TOT]) + align_up(sz[PL_SUMR]) + align_up(sz[PL_CARRY]);
+    sz[PL_WARM] = kind ? 0 : warm;
+    pl->warm_room = !kind || warm <= sums;
     pl->narrays = PL_COUNT;
     size_t off = 0;
     for (int j = 0; j < PL_COUNT; ++j) {

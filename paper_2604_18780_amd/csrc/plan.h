@@ -14,6 +14,7 @@ struct Plan {
     int Delta, N, NCH, nslot, G;
     int Ds, Ns;  // interval and number of intervals of the scans of a forward-only call
     int rows;  // the backward scan tasks have row storage (stored-row marginals possible)
+    bool warm_room;  // there is room for what the choice of the warm-up leaves (in a gradient call in the place of the partial sums)
     int msplit;  // parts an interval is cut into by the one-wave stored-row marginals (per-part partial sums)
     size_t lds_mg_dur, lds_mg_te;
     size_t lds_scan, lds_interval;

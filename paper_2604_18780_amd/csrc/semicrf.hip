@@ -112,9 +112,10 @@ void bind_workspace(Params &p, const Plan &pl, void *ws)
     p.blocY = (double *)(w + pl.off[29]);
     p.sink = (double *)(w + pl.off[30]);
     const WarmLayout wl = warm_layout(p.B, p.C, pl.NCH);
-    p.negl = (double *)(w + pl.off[31] + wl.negl);
-    p.wlen = (int4 *)(w + pl.off[31] + wl.len);
-    p.contrast = (float *)(w + pl.off[31] + wl.contrast);
+    char *const ww = w + (pl.size[PL_WARM] ? pl.off[PL_WARM] : pl.off[PL_PARTD]);
+    p.negl = (double *)(ww + wl.negl);
+    p.wlen = (int4 *)(ww + wl.len);
+    p.contrast = (float *)(ww + wl.contrast);
     // what the report reads comes first: its place does not depend on how many tasks the scans were cut into
     p.spec_rep = (double *)(w + pl.off[8]);
     p.spec_ok = (int *)(p.spec_rep + (size_t)p.B * 2);
@@ -401,9 +402,9 @@ int launch_mg(const Params &p, hipStream_t st)
 }
 
 // Sizes for which the first warm-up comes from the model, unless the caller has named one.
-bool warm_from_model(const Params &p)
+bool warm_from_model(const Params &p, const Plan &pl)
 {
-    return p.spec && p.warm0 == 0 && !p.mscan && p.C >= 2 && p.C <= 64 && p.K <= WARM_PER * (NT / p.C);
+    return p.spec && pl.warm_room && p.warm0 == 0 && !p.mscan && p.C >= 2 && p.C <= 64 && p.K <= WARM_PER * (NT / p.C);
 }
 
 int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hipStream_t st,
@@ -443,7 +444,7 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
     if (p.marg && p.K < 128 && pl.Delta / pl.msplit >= p.K) p.msplit = pl.msplit;
     // Windows that agree only in what they still contribute serve the scans and, where they come complete from the neighbour
     // (state_above: intervals of at least K positions), the statistics; elsewhere the warm-up fills them.
-    if (warm_from_model(p)) p.warm_model = WARM_LONGER | ((mode == 1 || (p.marg && p.Delta >= p.K)) ? WARM_SHORTER : 0);
+    if (warm_from_model(p, pl)) p.warm_model = WARM_LONGER | ((mode == 1 || (p.marg && p.Delta >= p.K)) ? WARM_SHORTER : 0);
     if (p.warm_model) p.warm_long = warm[1] = warm[1] < WARM_LONG_LEAST ? WARM_LONG_LEAST : warm[1];
     T.mark();
     rc = launch_prep(p, st);
@@ -642,7 +643,7 @@ int run_viterbi(Params p, void *workspace, size_t workspace_bytes, hipStream_t s
     p.logpair = 1;
     p.spec = p.spec ? 1 : 0;
     // (up to 20 segment lengths the default is hardly longer)
-    p.warm_model = warm_from_model(p) && p.K > 20 ? WARM_SHORTER : 0;
+    p.warm_model = warm_from_model(p, pl) && p.K > 20 ? WARM_SHORTER : 0;
     rc = launch_prep(p, st);
     if (rc != SEMICRF_OK) return rc;
     const int C = p.C;
@@ -942,7 +943,7 @@ int run_durtrans(Params p, int ckpt_interval, void *workspace, size_t workspace_
     p.dtMA = dx.ok ? (double *)(dw + dl.ma) : nullptr;
     p.dtMB = (double *)(dw + dl.mb);
     p.dtE = (int2 *)(dw + dl.eab);
-    p.warm_model = warm_from_model(p) ? WARM_LONGER | WARM_SHORTER : 0;
+    p.warm_model = warm_from_model(p, pl) ? WARM_LONGER | WARM_SHORTER : 0;
     p.warm_long = long_warmup(p.K);
     if (p.warm_model && p.warm_long < WARM_LONG_LEAST) p.warm_long = WARM_LONG_LEAST;
     rc = launch_prep(p, st);
