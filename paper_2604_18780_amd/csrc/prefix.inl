@@ -158,7 +158,8 @@ __device__ __forceinline__ void colsum_body(const Params &p, const int b, const 
     }
 }
 
-// One launch for both: the first p.ntab workgroups build the tables, workgroup p.ntab + b*NCH + ch sums a chunk.
+// One launch: the first p.ntab workgroups build the tables, workgroup p.ntab + b*NCH + ch sums a chunk, what favour_blocks adds
+// looks at the durations of pairs of labels.
 template <int ET>
 __global__ __launch_bounds__(NT) void k_colsum(Params p)
 {
@@ -167,7 +168,8 @@ __global__ __launch_bounds__(NT) void k_colsum(Params p)
         return;
     }
     const int id = blockIdx.x - p.ntab;
-    colsum_body<ET>(p, id / p.NCH, id % p.NCH);
+    if (id >= p.NCH * p.B) favour_body(p, id - p.NCH * p.B);
+    else colsum_body<ET>(p, id / p.NCH, id % p.NCH);
 }
 
 // Scaling block length J and the range flag of a sequence: fm = max |f - nu| over its positions and labels, boundary

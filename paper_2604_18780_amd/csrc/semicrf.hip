@@ -145,7 +145,7 @@ int launch_prep_et(Params &p, hipStream_t st)
 {
     p.ntab = tables_blocks(p);
     p.logKC = log((double)p.K * (double)p.C);
-    hipLaunchKernelGGL(k_colsum<ET>, dim3(p.ntab + p.NCH * p.B), dim3(NT), 0, st, p);
+    hipLaunchKernelGGL(k_colsum<ET>, dim3(p.ntab + p.NCH * p.B + favour_blocks(p)), dim3(NT), 0, st, p);
     const bool bterms = p.logpair || p.proj_start || p.proj_end || p.pi_start || p.pi_end;
     if (p.NCH <= PREP_INLINE) {
         if (bterms) launch_prefix<true, ET, true>(p, st);

@@ -61,6 +61,44 @@ __device__ __forceinline__ float warm_sample(const Params &p, const int ch, cons
     return t < L && l > 0.f && l < 100.f ? l : 0.f;  // scores that are not numbers count as certain
 }
 
+// One matrix per duration: the largest log weight of a longer duration over a shorter one for sixteen pairs of labels, left in
+// the place of the table (which is built later).  Sixteen ranges of durations a pair, then over the ranges in order.  (In warm_plan, by
+// a single workgroup, it took 20 us longer than the prefix sums it runs beside: K = 64, C = 24, T = 100 000 52 -> 72 us.)
+constexpr int WARM_PAIRS = NT / 16;
+__device__ __forceinline__ void favour_body(const Params &p, const int blk)
+{
+    __shared__ float red[3][NT / 64][WARM_PAIRS];
+    const int tid = threadIdx.x, g = tid / WARM_PAIRS, K = p.K, C = p.C, CC = C * C;
+    const int pair = blk * WARM_PAIRS + tid % WARM_PAIRS, pr = min(pair, CC - 1);
+    const int per = (K + NT / WARM_PAIRS - 1) / (NT / WARM_PAIRS), k0 = min(g * per, K), k1 = min(k0 + per, K);
+    float mn = INFINITY, mx = -INFINITY, best = 0.f;
+#pragma unroll 8
+    for (int k = k0; k < k1; ++k) {
+        const float v = p.dur[(size_t)k * C + pr % C] + p.trans3[(size_t)k * CC + pr];
+        best = fmaxf(best, v - mn);
+        mn = fminf(mn, v);
+        mx = fmaxf(mx, v);
+    }
+    auto then = [&](const float mn2, const float mx2, const float best2) {  // a later range
+        best = fmaxf(best, fmaxf(best2, mx2 - mn));
+        mn = fminf(mn, mn2);
+        mx = fmaxf(mx, mx2);
+    };
+#pragma unroll
+    for (int off = WARM_PAIRS; off < 64; off <<= 1) then(__shfl_down(mn, off), __shfl_down(mx, off), __shfl_down(best, off));
+    if ((tid & 63) < WARM_PAIRS) {
+        red[0][tid >> 6][tid & 63] = mn;
+        red[1][tid >> 6][tid & 63] = mx;
+        red[2][tid >> 6][tid & 63] = best;
+    }
+    __syncthreads();
+    if (g != 0 || pair >= CC) return;
+#pragma unroll
+    for (int i = 1; i < NT / 64; ++i) then(red[0][i][tid], red[1][i][tid], red[2][i][tid]);
+    ((float *)p.G3)[pair] = best;
+}
+inline int favour_blocks(const Params &p) { return p.warm_model && p.trans3 ? (p.C * p.C + WARM_PAIRS - 1) / WARM_PAIRS : 0; }
+
 // One workgroup per sequence, next to those of k_prefix; it must not take longer than they do (12 us at two chunks).  So
 // everything that comes from memory is requested before anything is done with it, and the transition matrix is worked on in
 // LDS by four threads per label.  lds: (PREP_NSEG + 1) C doubles, buf: 2 NT.
@@ -93,6 +131,10 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
     const int G = NT / C, g = tid / C, per = (K + G - 1) / G, k0 = g * per, k1 = g < G ? min(k0 + per, K) : k0;
 #pragma unroll
     for (int u = 0; u < WARM_PER; ++u) du[u] = p.dur[(size_t)min(k0 + u, K - 1) * C + tid % C];
+    float fv[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (dt) fv[i] = ((const float *)p.G3)[min(i * NT + tid, CC - 1)];
     // contrast: of this sequence alone, so that what happens to it does not depend on the others of its batch
     double con = 0.0;
 #pragma unroll 8
@@ -127,38 +169,17 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
             if (p.logpair) p.negl[(size_t)b * C + tid] = (double)best * 1.000001;
             else p.negl[(size_t)b * C + tid] = best < 600.f ? exp(-1.001 * (double)best) / (double)K : 0.0;  // (differences are rounded)
         }
-    } else {
-        for (int p0 = 0; p0 < CC; p0 += NT) {
-            const int np = min(CC - p0, NT), G3 = NT / np, g3 = tid / np, pr = p0 + tid % np;
-            const int per3 = (K + G3 - 1) / G3, q0 = min(g3 * per3, K), q1 = g3 < G3 ? min(q0 + per3, K) : q0;
-            float mn = INFINITY, mx = -INFINITY, best = 0.f;
-#pragma unroll 16
-            for (int k = q0; k < q1; ++k) {
-                const float v = p.dur[(size_t)k * C + pr % C] + p.trans3[(size_t)k * CC + pr];
-                best = fmaxf(best, v - mn);
-                mn = fminf(mn, v);
-                mx = fmaxf(mx, v);
-            }
-            red[tid] = mn;
-            red[NT + tid] = mx;
-            red[2 * NT + tid] = best;
-            __syncthreads();
-            if (tid < np) {
-                for (int gg = 1; gg < G3; ++gg) {
-                    best = fmaxf(best, fmaxf(red[2 * NT + gg * np + tid], red[NT + gg * np + tid] - mn));
-                    mn = fminf(mn, red[gg * np + tid]);
-                }
-                lds[pr] = (double)best;
-            }
-            __syncthreads();
-        }
+    } else {  // (by pairs of labels, from k_colsum)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) red[i * NT + tid] = fv[i];
+        __syncthreads();
         if (tid < C) {
-            double best = lds[tid];
-            for (int o = 1; o < C; ++o) best = fmax(best, lds[o * C + tid]);
-            favour = (float)best;
+            float best = red[tid];
+#pragma unroll 8
+            for (int o = 1; o < C; ++o) best = fmaxf(best, red[o * C + tid]);
+            favour = best;
             p.negl[(size_t)b * C + tid] = best < 600.f ? exp(-1.001 * (double)best) / (double)K : 0.0;  // (differences are rounded)
         }
-        __syncthreads();
     }
 #pragma unroll
     for (int i = 0; i < NTR; ++i) {
