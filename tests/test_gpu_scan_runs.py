@@ -51,6 +51,7 @@ def test_runs_that_count_are_taken(T, K, C, kind, form):
         lz = sb.semicrf_seq_report(ws, w.B, T, K, C, delta, 1)[1].cpu().numpy()
         acc = sb.semicrf_scan_report(ws, w.B, T, K, C, delta, 1)[0].cpu().numpy()
         print(f"[case] {kind} {form} T={T} K={K} C={C} warm-up {warm or 'chosen'} verified at {acc.tolist()}", flush=True)
+        assert kind != "plain" or warm or (acc >= 1).all()  # (the sequential scan's results would be right, too)
         assert_outputs_match_oracle([o.double().cpu().numpy() for o in out], r)
         # what is left alone is below 2^-54 of every sum; accepted boundaries agree to 2e-10 each; T sums in 64 bits
         bound = 2e-10 * (T / delta) + 1e-13 * T + 1e-13 * np.abs(r.logz).max()

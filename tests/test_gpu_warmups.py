@@ -67,6 +67,7 @@ def test_models_the_choice_may_misjudge(T, K, C, kind):
     for delta in (0, max(K, 40)):
         out, acc = train(w, delta)
         print(f"[case] {kind} T={T} K={K} C={C} interval {delta} verified at {acc.tolist()}", flush=True)
+        assert kind != "confident" or (acc[w.lengths > 0] >= 1).all()
         assert_outputs_match_oracle(out, r)
 
 
@@ -79,6 +80,9 @@ def test_duration_dependent_transitions(T, K, C, kind):
     for delta in (0, 64):
         ws = sb.alloc_durtrans_workspace(w.B, T, K, C, delta, True, "cuda:0").fill_(255)
         out = sb.semicrf_fwd_bwd_durtrans(dev(w.emis), dev(w.lengths), dev(t3), dev(w.dur), None, delta, workspace=ws)
+        acc = sb.semicrf_scan_report(ws, w.B, T, K, C, sb.semicrf_durtrans_ckpt_interval(w.B, T, K, C, delta), True)[0].cpu().numpy()
+        print(f"[case] {kind} T={T} K={K} C={C} interval {delta} verified at {acc.tolist()}", flush=True)
+        assert kind != "plain" or (acc[w.lengths > 0] >= 1).all()  # (not by the whole-sequence scans, whose results are the same)
         assert_outputs_match_oracle([o.double().cpu().numpy() for o in out], r)
 
 
@@ -95,6 +99,9 @@ def test_best_segmentation(T, K, C, kind):
     off = (-ws.data_ptr()) % 256
     score, labels, starts, nseg = sb.semicrf_viterbi(dev(w.emis), dev(w.lengths), dev(w.trans), dev(w.dur),
                                                      workspace=ws[off:ws.numel() - 256 + off])
+    acc = sb.semicrf_scan_report(ws[off:ws.numel() - 256 + off], 3, T, K, C, 0, 0)[0][:, 0].cpu().numpy()
+    print(f"[case] {kind} T={T} K={K} C={C} verified at {acc.tolist()}", flush=True)
+    assert kind not in ("plain", "confident") or (acc[w.lengths > 0] == 1).all()
     ref = oracle.viterbi(w.emis, w.lengths, w.trans, w.dur)[0]
     assert np.abs(score.double().cpu().numpy() - ref).max() <= 1e-6 * max(1.0, np.abs(ref).max())
     for b in range(3):
