@@ -127,8 +127,9 @@ class Problem:
     def roofline(self, ms_step, stage):
         """The dominant stage against the fp64 vector peak.  One "unit" is K*C (duration sum) + C*C
         (transition product) multiply-adds per position.  The scan stage runs the forward and the backward
-        recurrence once each (2 units; its forward tasks also leave the rows that Algorithm 3 would recompute
-        per interval); the interval stage runs the backward recurrence again inside each interval and
+        recurrence once each (2 units, of whose K window entries only the newest run is counted, which is read at every
+        position: the scans leave the older runs alone where they are below the last bit; its forward tasks also leave
+        the rows that Algorithm 3 would recompute per interval); the interval stage runs the backward recurrence again inside each interval and
         accumulates the marginals (2 units), or forms the marginals from the rows both scans stored (1 unit;
         the default wherever the plan has a row slot per interval for both scans).  Warm-up positions of the
         chunk-parallel scans are overhead, not counted."""
@@ -140,7 +141,10 @@ class Problem:
                    sb.semicrf_workspace_bytes(w.B, w.T, w.K, w.C, self.delta, 1) >
                    sb.semicrf_workspace_bytes(w.B, w.T, w.K, w.C, self.delta, 2))
         rows_route = planned and not (self.flags & sb.SEMICRF_MARGINALS_INTERVAL)
-        stage_flop = {"scans": 2 * unit, "intervals": (1 if rows_route else 2) * unit}
+        groups = 64 // max(8, 1 << (w.C - 1).bit_length()) if w.C <= 64 else 0
+        newest = min(w.K, groups * (17 if groups > 2 else 16)) if groups else w.K  # distances of the window's first run
+        scan_unit = 2.0 * (newest * w.C + w.C * w.C) * w.positions
+        stage_flop = {"scans": 2 * scan_unit, "intervals": (1 if rows_route else 2) * unit}
         kernels = {"scans": "k_spec (chunk-parallel forward + backward scans, one launch; stage time "
                             "includes its small verification kernels and the early exits of the retries)",
                    "intervals": (("k_mg_wave (marginals from the stored rows of both scans, one launch)" if w.K < 128 else

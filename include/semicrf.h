@@ -58,15 +58,19 @@ typedef enum {
 #define SEMICRF_CENTER 1u
 /* flags bit 1: run the forward scan of Algorithm 1 and the backward scan of Algorithm 3
  * strictly sequentially.  By default both are run chunk-parallel: every checkpoint interval
- * is scanned as an independent task that first warms its ring up over the max(1.5K,32)
- * positions before the interval (max(8K,64) in a second attempt for what the first did not
- * verify), starting from the state of a sequence that begins there.
- * The state each task reaches at its end is then compared, entry by entry and up to the
- * common scale factor, with the warmed-up state its neighbour started from; a (sequence,
- * direction) is accepted only if every one of its boundaries agrees to 1e-10 (relative),
- * which bounds the deviation from the sequential scan by 2e-10 per boundary crossed.  A
- * rejected (sequence, direction) is rescanned sequentially inside the same call, so the
- * results are those of the sequential scan either way; only the time differs.
+ * is scanned as an independent task that first warms its ring up over positions before the
+ * interval, starting from the state of a sequence that begins there: as many positions as the
+ * model and the scores ask for (16 and up whatever K is; more than max(1.5K,32) where labels reach
+ * each other only over several steps), max(1.5K,32) where that choice does not apply.
+ * The state each task reaches at its end is then compared, up to the common scale factor, with
+ * the warmed-up state its neighbour started from: entry by entry to 1e-10 (relative) after a default
+ * warm-up, and after a chosen one by what each entry can still contribute, to max(1e-13, 1e-16 L).  A
+ * (sequence, direction) is accepted only if every one of its boundaries agrees, which bounds
+ * the deviation from the sequential scan by twice that per boundary crossed.  What does not agree is
+ * mended where it is isolated boundaries, else scanned again after a longer warm-up (eight segment
+ * lengths at most, then the longest, at least 768 positions).  A (sequence, direction) that is still
+ * rejected is rescanned sequentially inside the same call, so the results are those of the
+ * sequential scan either way; only the time differs.
  * semicrf_scan_report tells which happened. */
 #define SEMICRF_SEQUENTIAL_SCAN 2u
 /* flags bits 2, 3: storage type of `emis`.  With one of them set the `emis` argument of every

@@ -424,8 +424,8 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
     p.nslot = pl.nslot;
     p.want_grad = mode == 2;
     bind_workspace(p, pl, workspace);
-    // warm-up lengths of the chunk-parallel scan: one and a half maximal segment lengths first,
-    // eight for the (sequence, direction) pairs that fails for, the sequential scan for the rest
+    // first and longest warm-up of the chunk-parallel scan where they do not come from the model (see below), in between what
+    // the first attempt's mismatch asks for; the sequential scan for the (sequence, direction) pairs that fails for
     int warm[2] = {sum_warmup(p.K), long_warmup(p.K)};
     if (p.warm0 > 0) warm[0] = p.warm0, warm[1] = 4 * p.warm0;  // the caller's first warm-up length (flags bits 16..31)
     p.warm_long = warm[1];
