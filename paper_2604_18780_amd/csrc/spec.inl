@@ -17,8 +17,8 @@
 // factor.  If all boundaries of a (sequence, direction) agree (spec_tol) the warm-up states do what the
 // sequential states do, to that relative accuracy (perturbations of the start do not grow: the maps
 // are non-expansive in the projective metric).  The warm-up is 1.5 K positions, or what the model asks
-// for (warm_plan): genomic shape 96 -> 40, scans 310 -> 278 us; K = 512, C = 8 768 -> 56, 684 -> 388 us;
-// band 2 in 19 labels, K = 37 56 -> 204, so that the first attempt is accepted (225 -> 120 us).  spec_settle then chains the scale
+// for (warm_plan): genomic shape 96 -> 32 (310 -> 278 us at 40); K = 512, C = 8 768 -> 44 (684 -> 388 us at 56);
+// band 2 in 19 labels, K = 37 56 -> 264, so that the first attempt is accepted (225 -> 139 us).  spec_settle then chains the scale
 // factors into the checkpoint scales and logZ.  Otherwise the flag stays 0 and the
 // sequential scan kernel, launched after the later attempts, which returns at once for
 // accepted (sequence, direction) pairs, recomputes that pair from scratch.

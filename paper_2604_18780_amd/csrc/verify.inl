@@ -25,6 +25,8 @@ constexpr int SPEC_ATTEMPTS = 3;
 // newer entry of the label, whichever is more.  At every later position an entry's difference then adds at most the bound / K of
 // what the newer entry adds there, so the states agree to twice the bound in all they do: everything a state does later is a sum of
 // positive multiples of these direct contributions.  Windows that agree entry by entry are not looked at this way.
+// Bound by the latency of two states' loads and of the reductions: the working launch takes 16.5 us at the genomic shape (13.0 entry by
+// entry alone), 16 at 32 x 2000, K = 32, C = 64 (12.5).
 template <int PER>
 __global__ __launch_bounds__(NT) void k_spec_cmp(Params p, int tier, int negl, int G, int per)
 {

@@ -99,7 +99,8 @@ __device__ __forceinline__ void favour_body(const Params &p, const int blk)
 }
 inline int favour_blocks(const Params &p) { return p.warm_model && p.trans3 ? (p.C * p.C + WARM_PAIRS - 1) / WARM_PAIRS : 0; }
 
-// One workgroup per sequence, next to those of k_prefix; it must not take longer than they do (12 us at two chunks).  So
+// One workgroup per sequence, next to those of k_prefix; it should not take longer than they do (14 us at one or two chunks of
+// 24 labels; with 4 labels and two chunks it does: the launch takes 7.5 us without, 10.0 with it).  So
 // everything that comes from memory is requested before anything is done with it, and the transition matrix is worked on in
 // LDS by four threads per label.  lds: (PREP_NSEG + 1) C doubles, buf: 2 NT.
 __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf)
