@@ -406,8 +406,11 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tie
 // the labels (b_t) and, weighted with a_t, over the source labels (mass of the segments that start at t).  A wave takes the
 // labels wave, wave + 8, ...; the waves' sums for b meet in LDS.  The window lies label by label along the positions, so
 // that the product's operand comes with immediate offsets; it slides downwards and is moved back every m positions.
-// Inside the block, one wave per task (0 .. 3) finishes the positions by row broadcasts, the other (4 .. 7) forms what
-// durations 1 .. 3 add to the mass that starts at a position, and writes the block's rows.
+// Inside the block, one wave per task (0 .. 3) finishes the positions by row broadcasts, while the other (4 .. 7) forms what
+// durations 1 .. 3 add to the mass that starts at a position; it then writes the block's rows.
+// Bound by the product (17 of 28 thousand clocks per block at the genomic shape, where its matrix instructions take 12) and by what
+// lies between two products: the tables of those sums held in registers that only the chain waves need otherwise, the sums
+// formed beside the chains, and rows stored unconditionally took the launch from 1278 to 1190 us (K = 39, C = 6: 672 -> 650).
 // ---------------------------------------------------------------------------
 template <int MT, int SF2>
 __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tier)
@@ -453,17 +456,31 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
     const int qo = q * 4 * CPB;
 
     for (int i = tid; i < DX_TASKS * TS + 4 * 16 * CPB; i += DX_NT) lds_raw[i] = 0.0;
-    // the lane's part of the tables of durations 1 .. 3 (chain waves: contraction over the label)
-    double Ek[DX_MB - 1][R::HC];
+    // the lane's part of the tables of durations 1 .. 3: chain waves the contraction over the label, the others the operands of
+    // their two tiles of sum_c' a_t(c') G[k][c'][c] (below)
+    constexpr int NSH = (DX_MB - 1) * MT;  // tiles (duration - 1, label tile)
+    double Ek[(DX_MB - 1) * R::HC];
+    if (chain) {
 #pragma unroll
-    for (int k = 0; k < DX_MB - 1; ++k)
+        for (int k = 0; k < DX_MB - 1; ++k)
 #pragma unroll
-        for (int i = 0; i < R::HC; ++i) {
-            const int o = (lane >> 5) * R::HC + i;
-            const bool ok = chain && k < K && cv && o < C;
-            const double v = p.G3[ok ? (size_t)k * CC + (size_t)c * C + o : 0];
-            Ek[k][i] = ok ? v : 0.0;
-        }
+            for (int i = 0; i < R::HC; ++i) {
+                const int o = (lane >> 5) * R::HC + i;
+                const bool ok = k < K && cv && o < C;
+                const double v = p.G3[ok ? (size_t)k * CC + (size_t)c * C + o : 0];
+                Ek[k * R::HC + i] = ok ? v : 0.0;
+            }
+    } else {
+        static_assert(4 * SF2 <= (DX_MB - 1) * R::HC && NSH <= 8, "two tiles per wave, in the chain waves' registers");
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int s = 0; s < SF2; ++s) {
+                const double2 gs = ((const double2 *)p.GS)[((size_t)min(q + 4 * u, NSH - 1) * SF2 + s) * 64 + lane];
+                Ek[(u * SF2 + s) * 2] = gs.x;
+                Ek[(u * SF2 + s) * 2 + 1] = gs.y;
+            }
+    }
     lds_barrier();
     bool done = !tk.active;
     double Yb = 0.0, Ytop = 0.0, blast = 0.0;
@@ -653,23 +670,6 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
                     }
                 }
             }
-            // sums over the source labels of a_t G[k], k = 1 .. 3, for what durations inside the block add to the mass
-            // that starts at a position: one product of the sixteen rows per (duration, label tile), waves 7, 6, ...
-            for (int tile = 7 - wave; tile < (DX_MB - 1) * MT; tile += 8) {
-                dx_d4 w = {0.0, 0.0, 0.0, 0.0};
-                const double2 *GS = (const double2 *)p.GS + (size_t)tile * (SF2 * 64) + lane;
-#pragma unroll
-                for (int s = 0; s < SF2; ++s) {
-                    const double2 gs = GS[s * 64];
-                    const double *ar = avL + (tn * 4 + pn) * CPB + 8 * s + g4;
-                    w = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[0], gs.x, w, 0, 0, 0);
-                    w = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[4], gs.y, w, 0, 0, 0);
-                }
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {  // row 4 v + g4: task g4, position v
-                    wL[(((tile / MT) * 4 + g4) * 4 + v) * CPB + (tile % MT) * 16 + j] = w[v];
-                }
-            }
 #pragma unroll
             for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -678,6 +678,7 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
                     if (r < C) bp[(wave * C + r) * 16 + j] = bacc[m][v];
                 }
         }
+        if (chain && lane < nbk && t0 - lane < hi) rowYb[t0 - lane] = Yb - Ytop;
         load_rows(t0 - nbk);  // the next block's, with the serial part to arrive
         lds_barrier();
         if ((tid >> 4) < C) {  // 512 threads: source label, column
@@ -703,7 +704,7 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
                     double b = bf[i];
 #pragma unroll
                     for (int k = 1; k <= i; ++k)  // ends at position i - k of the block, finished before
-                        b += R::product(cv ? ie[i] * v[i - k] : 0.0, Ek[k - 1]);
+                        b += R::product(cv ? ie[i] * v[i - k] : 0.0, Ek + (k - 1) * R::HC);
                     b = cv ? b : 0.0;
                     v[i] = b * es[i];
                     blast = b;
@@ -713,26 +714,45 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
                     }
                 }
             }
-        }
-        lds_barrier();
-        if (!chain && owner) {
-            double v[DX_MB];
+        } else {
+            // meanwhile, sums over the source labels of a_t G[k], k = 1 .. 3, for what durations inside the block add to the
+            // mass that starts at a position: one product of the sixteen rows per (duration, label tile)
+            double ar[2 * SF2];
 #pragma unroll
-            for (int i = 0; i < DX_MB; ++i) v[i] = Vq[c * W + r0 - i];
+            for (int s = 0; s < 2 * SF2; ++s) ar[s] = avL[((j & 3) * 4 + (j >> 2)) * CPB + 4 * s + g4];
 #pragma unroll
-            for (int i = 0; i < DX_MB; ++i) {
-                const int tt = t0 - i;
-                if (i < nbk && tt < hi) {
-                    const int o = qo + i * CPB + c;
-                    double out = (oL[o] + oL[o + 16 * CPB]) + (oL[o + 32 * CPB] + oL[o + 48 * CPB]);
+            for (int u = 0; u < 2; ++u) {
+                const int tile = q + 4 * u;
+                if (tile >= NSH) break;  // uniform
+                dx_d4 w = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                    for (int k = 1; k <= i; ++k) out = fma(wL[(k - 1) * 16 * CPB + o], v[i - k], out);
-                    rowV[(size_t)tt * C + c] = v[i];
-                    rowD[(size_t)tt * C + c] = out * ieL[o] - (tt >= 1 ? avL[o] * bL[o] : 0.0);
-                }
+                for (int s = 0; s < 2 * SF2; ++s) w = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[s], Ek[u * 2 * SF2 + s], w, 0, 0, 0);
+#pragma unroll
+                for (int v = 0; v < 4; ++v)  // row 4 v + g4: task g4, position v
+                    wL[(((tile / MT) * 4 + g4) * 4 + v) * CPB + (tile % MT) * 16 + j] = w[v];
             }
         }
-        if (chain && lane < nbk && t0 - lane < hi) rowYb[t0 - lane] = Yb - Ytop;
+        lds_barrier();
+        // ---- the block's rows.  What has no row goes to a sink: the number of stores behind the next block's loads is then known, and
+        // waiting for those is not waiting for these.  Lanes that own no label store what the owner of theirs, or of label 0, stores.
+        if (!chain) {
+            constexpr int OS = 16 * CPB;
+            const double *vr = Vq + cc0 * W + r0;
+            double v[DX_MB];
+#pragma unroll
+            for (int i = 0; i < DX_MB; ++i) v[i] = vr[-i];
+#pragma unroll
+            for (int i = 0; i < DX_MB; ++i) {
+                const int tt = t0 - i, o = qo + i * CPB + cc0;
+                double out = (oL[o] + oL[o + OS]) + (oL[o + 2 * OS] + oL[o + 3 * OS]);
+#pragma unroll
+                for (int k = 1; k <= i; ++k) out = fma(wL[(k - 1) * OS + o], v[i - k], out);
+                const bool row = i < nbk && tt < hi;  // uniform
+                const size_t at = (size_t)tt * C + cc0;
+                *(row ? rowV + at : p.sink + tid) = v[i];
+                *(row ? rowD + at : p.sink + tid) = out * ieL[o] - (tt >= 1 ? avL[o] * bL[o] : 0.0);
+            }
+        }
         const int tlast = t0 - nbk + 1, rlast = r0 - nbk + 1;
         t0 -= nbk;
         r0 -= nbk;
