@@ -5,8 +5,11 @@
 // sixteen (task, position) pairs are the rows (forward) or columns (backward) of v_mfma_f64_16x16x4 products with the
 // table G[k][c'][c], so a table entry fetched from L2 once serves sixteen positions instead of four, and one
 // instruction does 1024 multiply-adds.  Scans of the genomic shape (K = 64, C = 24, 4 x 100 000), forward and backward: 4.9
-// and 6.3 ms with vector multiply-adds, four positions per table entry and one task per workgroup (durtrans.inl), 1.27 and
-// 1.58 ms so, the matrix pipes busy 37 and 41 % of the time.
+// and 6.3 ms with vector multiply-adds, four positions per table entry and one task per workgroup (durtrans.inl), 1.00 and
+// 1.19 ms so, the matrix pipes busy 41 and 45 % of the time.  The products wait for the table, so its entries are fetched as far
+// ahead as registers allow: three tiles or groups for up to sixteen labels, else one (two, with 25 registers spilled: k_dx_fwd 1003 ->
+// 1031 us at the genomic shape).  One ahead against three: 1 x 1293, K = 380, C = 10 forward 627 -> 585, backward 447 -> 435 us;
+// 3 x 58043, K = 373, C = 6 forward 640 -> 603; 15 x 11034, K = 39, C = 4 392 -> 380, 341 -> 337.
 // fp64 matrix and vector instructions have the same peak here; what is won is table traffic, LDS operand traffic and
 // instruction count.  Everything that is not the product with the table (scaling, the durations inside a block of four
 // positions, checkpoints, stored rows) follows durtrans.inl, whose kernels still rescan what the verification rejects.
@@ -156,6 +159,7 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tie
 {
     extern __shared__ double lds_raw[];
     constexpr int CT = 8 * SF2, CS = CT + 1;
+    constexpr int AHEAD = SF2 <= 2 ? 3 : 1;  // tiles of 2 SF2 products whose table entries are fetched ahead
     using R = RowMap<CT>;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -318,20 +322,24 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tie
                 int slot = dx_wrap(rbD + k1, KR);
                 if (slot >= KR) slot = 0;                  // beyond K + 3: not used
                 const int kmax = cl < C ? K + DX_MB - 1 : 0;
-                double2 B[2][SF2];
+                constexpr int NB = AHEAD + 1;  // tiles by turns (runs are multiples of four)
+                double2 B[NB][SF2];
 #pragma unroll
-                for (int s = 0; s < SF2; ++s) B[0][s] = sgm == 0 ? B0[s] : GF[s * 64];
-                for (int kk = ka; kk < kb; kk += 2) {
+                for (int h = 0; h < AHEAD; ++h)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
+                    for (int s = 0; s < SF2; ++s) B[h][s] = sgm == 0 && h == 0 ? B0[s] : GF[(h * SF2 + s) * 64];
+                GF += (AHEAD - 1) * (SF2 * 64);
+                for (int kk = ka; kk < kb; kk += NB) {
+#pragma unroll
+                    for (int h = 0; h < NB; ++h) {
                         const bool use = k1 <= kmax;
                         double *xp = XD + slot * C + cl;
                         double xo = 0.0;
                         if (use) xo = *xp;
-                        if (h == 0 || kk + 2 < kb) {  // the next tile's entries
-                            GF += SF2 * 64;
+                        GF += SF2 * 64;
+                        if (h == 0 || kk + NB < kb) {  // the entries of the tile AHEAD
 #pragma unroll
-                            for (int s = 0; s < SF2; ++s) B[1 - h][s] = GF[s * 64];
+                            for (int s = 0; s < SF2; ++s) B[(h + AHEAD) % NB][s] = GF[s * 64];
                         }
                         dx_d4 D = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -339,7 +347,7 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tie
                             D = __builtin_amdgcn_mfma_f64_16x16x4f64(A[2 * s], B[h][s].x, D, 0, 0, 0);
                             D = __builtin_amdgcn_mfma_f64_16x16x4f64(A[2 * s + 1], B[h][s].y, D, 0, 0, 0);
                         }
-                        if (kk < DX_MB - 1) {  // uniform: targets inside the block were served above
+                        if (NB == 4 ? h < DX_MB - 1 && kk == 0 : kk < DX_MB - 1) {  // uniform: targets inside the block were served above
                             D[0] = k1 >= nbD ? D[0] : 0.0;
                             D[1] = k1 + 1 >= nbD ? D[1] : 0.0;
                             D[2] = k1 + 2 >= nbD ? D[2] : 0.0;
@@ -604,10 +612,11 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
                 }
             const double *Vn = V + tn * TS + (ctl[4 + tn] - pn + g4 + 1);
             // table entries: one double2 per lane and step (two label tiles) or pair of steps (one), four steps at a
-            // time, a group ahead (the first group of a label during the last of the label before)
+            // time, AHEAD groups ahead (across labels)
             constexpr int LG = 2 * MT;
-            double2 Gg[2][LG];
-            double bg[2][4];
+            constexpr int NBUF = MT == 1 ? 4 : 2, AHEAD = NBUF - 1;
+            double2 Gg[NBUF][LG];
+            double bg[NBUF][4];
             auto fetch = [&](const int cc, const int s, double2 (&G)[LG], double (&b)[4]) {
                 const double2 *GB = (const double2 *)p.GB + ((size_t)cc * KS + s) * (MT * 32) + lane;
                 const double *Vc = Vn + cc * W + 4 * s;
@@ -641,7 +650,7 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
                 oL[((g4 * 4 + tn) * 4 + pn) * CPB + cc] = o;
             };
             if (wave < C) {
-                // groups of all the wave's labels in one sequence, two per turn (even and odd buffers)
+                // groups of all the wave's labels in one sequence, NBUF per turn
                 const int ng = KS / 4, total = ((C - wave + 7) / 8) * ng;
                 int cc = wave, gq = 0;        // group being multiplied
                 int ccn = wave, gn = 0;       // group being fetched
@@ -651,13 +660,16 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
                         cx += 8;
                     }
                 };
-                fetch(ccn, 0, Gg[0], bg[0]);
-                next(ccn, gn);
-                for (int i = 0; i < total; i += 2) {
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
+                for (int h = 0; h < AHEAD; ++h) {
+                    if (h == 0 || h < total) fetch(ccn, 4 * gn, Gg[h], bg[h]);
+                    next(ccn, gn);
+                }
+                for (int i = 0; i < total; i += NBUF) {
+#pragma unroll
+                    for (int h = 0; h < NBUF; ++h) {
                         if (i + h < total) {  // uniform
-                            if (i + h + 1 < total) fetch(ccn, 4 * gn, Gg[1 - h], bg[1 - h]);
+                            if (i + h + AHEAD < total) fetch(ccn, 4 * gn, Gg[(h + AHEAD) % NBUF], bg[(h + AHEAD) % NBUF]);
                             next(ccn, gn);
                             if (gq == 0) {
 #pragma unroll
