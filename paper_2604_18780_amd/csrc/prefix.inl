@@ -72,6 +72,53 @@ __device__ __forceinline__ float float_above(const double x)
     return (double)q < x ? nextafterf(q, INFINITY) : q;
 }
 
+// The emissions of one item, n of them (o: offset of the first), zeros beyond: their sum, and into mx and ex the largest and the
+// largest excursion.
+template <int ET>
+__device__ __forceinline__ double col_item(const Params &p, const size_t o, const int n, double &mx, double &ex)
+{
+    const int C = p.C;
+    double f[JMAX];
+    if (n == JMAX) {
+#pragma unroll
+        for (int i = 0; i < JMAX; ++i) f[i] = emis_at<ET>(p, o + (unsigned)(i * C));
+    } else if (n > 0) {  // the sequence's last: rows beyond its end are replaced by its last one, so that nothing waits in a branch
+#pragma unroll
+        for (int i = 0; i < JMAX; ++i) {
+            const double v = emis_at<ET>(p, o + (unsigned)(min(i, n - 1) * C));
+            f[i] = i < n ? v : 0.0;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < JMAX; ++i) f[i] = 0.0;
+    }
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < JMAX; ++i) {
+        mx = fmax(mx, fabs(f[i]));
+        s += f[i];
+        if (i < JMAX - 1) ex = fmax(ex, fabs(s));
+    }
+    return s;
+}
+
+// The largest entry of rows u0 .. u1-1 of a projection (0 without one), this thread's share.
+__device__ __forceinline__ float rows_absmax(const Params &p, const float *a, const int b, const int u0, const int u1)
+{
+    float m = 0.f;
+    if (!a || u1 <= u0) return m;
+    a += ((size_t)b * p.T + u0) * p.C;  // one after the other
+    const int n = (u1 - u0) * p.C, n4 = ((uintptr_t)a & 15) == 0 ? n / 4 : 0;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < n4; i += NT) {
+        const float4 v = ((const float4 *)a)[i];
+        m = fmaxf(fmaxf(fmaxf(m, fabsf(v.x)), fmaxf(fabsf(v.y), fabsf(v.z))), fabsf(v.w));
+    }
+#pragma unroll 4
+    for (int i = 4 * n4 + threadIdx.x; i < n; i += NT) m = fmaxf(m, fabsf(a[i]));
+    return m;
+}
+
 template <int ET>
 __device__ __forceinline__ void colsum_body(const Params &p, const int b, const int ch)
 {
@@ -86,46 +133,10 @@ __device__ __forceinline__ void colsum_body(const Params &p, const int b, const 
     double mx = 0.0, ex = 0.0;
     for (int it = tid; it < COL_NG * C; it += NT) {
         const int t0 = u0 + it / C * JMAX, n = min(L - t0, JMAX);
-        const size_t o = ((size_t)b * p.T + t0) * C + it % C;
-        double f[JMAX];
-        if (n == JMAX) {
-#pragma unroll
-            for (int i = 0; i < JMAX; ++i) f[i] = emis_at<ET>(p, o + (unsigned)(i * C));
-        } else if (n > 0) {  // the sequence's last: rows beyond its end are replaced by its last one, so that nothing waits in a branch
-#pragma unroll
-            for (int i = 0; i < JMAX; ++i) {
-                const double v = emis_at<ET>(p, o + (unsigned)(min(i, n - 1) * C));
-                f[i] = i < n ? v : 0.0;
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < JMAX; ++i) f[i] = 0.0;
-        }
-        double s = 0.0;
-#pragma unroll
-        for (int i = 0; i < JMAX; ++i) {
-            mx = fmax(mx, fabs(f[i]));
-            s += f[i];
-            if (i < JMAX - 1) ex = fmax(ex, fabs(s));
-        }
-        red[it] = s;
+        red[it] = col_item<ET>(p, ((size_t)b * p.T + t0) * C + it % C, n, mx, ex);
     }
     // the boundary projections move a message like an emission does: their maxima are added
-    auto absmax = [&](const float *a) {
-        float m = 0.f;
-        if (!a || u1 <= u0) return m;
-        a += ((size_t)b * p.T + u0) * C;  // the chunk's rows, one after the other
-        const int n = (u1 - u0) * C, n4 = ((uintptr_t)a & 15) == 0 ? n / 4 : 0;
-#pragma unroll 4
-        for (int i = tid; i < n4; i += NT) {
-            const float4 v = ((const float4 *)a)[i];
-            m = fmaxf(fmaxf(fmaxf(m, fabsf(v.x)), fmaxf(fabsf(v.y), fabsf(v.z))), fabsf(v.w));
-        }
-#pragma unroll 4
-        for (int i = 4 * n4 + tid; i < n; i += NT) m = fmaxf(m, fabsf(a[i]));
-        return m;
-    };
-    float mps = absmax(p.proj_start), mpe = absmax(p.proj_end);
+    float mps = rows_absmax(p, p.proj_start, b, u0, u1), mpe = rows_absmax(p, p.proj_end, b, u0, u1);
     // the maxima first inside each wave (a maximum does not care for order)
     mx = wave_max(mx);
     ex = wave_max(ex);
@@ -175,13 +186,9 @@ __global__ __launch_bounds__(NT) void k_colsum(Params p)
 // Scaling block length J and the range flag of a sequence: fm = max |f - nu| over its positions and labels, boundary
 // terms included; ex = largest excursion of the sums of f inside JMAX aligned positions, nm = max |nu|.  tabmax: the maxima of the
 // p.ntab table workgroups.
-__device__ __forceinline__ SeqHdr seq_header(const Params &p, const int L, const double fm, const double ex, const double nm)
+__device__ __forceinline__ SeqHdr seq_header(const Params &p, const int L, const double fm, const double ex, const double nm,
+                                             const double dmax, const double tmax)
 {
-    double dmax = p.tabmax[0], tmax = p.tabmax[1];
-    for (int i = 1; i < p.ntab; ++i) {
-        dmax = fmax(dmax, p.tabmax[2 * i]);
-        tmax = fmax(tmax, p.tabmax[2 * i + 1]);
-    }
     double grow = fm + fmax(dmax, 0.0) + fmax(tmax, 0.0) + p.logKC;
     double shrink = fm + fmax(-dmax, 0.0) + fmax(-tmax, 0.0);
     double r = fmax(fmax(grow, shrink), 1e-9);
@@ -199,6 +206,16 @@ __device__ __forceinline__ SeqHdr seq_header(const Params &p, const int L, const
     SeqHdr h;
     h.L = L; h.J = J; h.flags = flags; h.pad = 0; h.logZ = 0.0; h.logZb = 0.0;
     return h;
+}
+// The same with the maxima that k_colsum has left.
+__device__ __forceinline__ SeqHdr seq_header(const Params &p, const int L, const double fm, const double ex, const double nm)
+{
+    double dmax = p.tabmax[0], tmax = p.tabmax[1];
+    for (int i = 1; i < p.ntab; ++i) {
+        dmax = fmax(dmax, p.tabmax[2 * i]);
+        tmax = fmax(tmax, p.tabmax[2 * i + 1]);
+    }
+    return seq_header(p, L, fm, ex, nm, dmax, tmax);
 }
 
 // ---------------------------------------------------------------------------
@@ -297,6 +314,17 @@ constexpr int PREP_NSEG = PREP_CH / PREP_SEG;
 constexpr int PREP_INLINE = 512;
 static_assert(PREP_CH % JMAX == 0 && JMAX % PREP_SEG == 0 && NT == 256 && PREP_NSEG == 32, "k_prefix geometry");
 
+// The largest of x over the workgroup, in every thread (red: a number per wave).
+__device__ __forceinline__ double over_workgroup(double x, double *red)
+{
+    x = wave_max(x);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+    __syncthreads();
+    for (int i = 0; i < NT / 64; ++i) x = fmax(x, red[i]);
+    return x;
+}
+
 // 1/x to the last bit or two: hardware estimate and two Newton steps (x is a finite positive exp)
 __device__ __forceinline__ double recip(const double x)
 {
@@ -338,9 +366,24 @@ __device__ __forceinline__ double exp_any(const double x)
 }
 
 // BTERMS: any boundary term of Eq. 4 present, or the log-domain pair of the max semiring; ET: emission storage type
-template <bool BTERMS, int ET, bool INLINE>
+// MODE: what has been done before.  PREP_OFFSETS: k_colsum and k_prep_seq; PREP_SUMS: k_colsum (INLINE above); PREP_NOTHING: the
+// workgroup adds up its whole sequence itself, and one of them builds the tables, see prep_alone.
+constexpr int PREP_OFFSETS = 0, PREP_SUMS = 1, PREP_NOTHING = 2;
+constexpr int PREP_ALONE = 3;        // chunks
+constexpr int PREP_ALONE_C = 44;     // labels: C (C + 1) <= TAB_ITEMS
+static_assert((PREP_ALONE_C + 1) * (PREP_ALONE_C + 2) > TAB_ITEMS, "more labels have more entries of the tables");
+// Short sequences with small tables: the launch of k_colsum and the gap behind it cost more than sums that every workgroup of a
+// sequence forms for itself.  Whole calls, two launches against one, us: gradients 2 x 512, K = 8, C = 4 60.5 -> 57.4; 64 x 256,
+// K = 16, C = 24 96.8 -> 92.7, decoding 85.4 -> 80.9; 8 x 767, K = 16, C = 24 83.9 -> 82.0 (each further chunk adds a round of loads).
+inline bool prep_alone(const Params &p)
+{
+    return p.NCH <= PREP_ALONE && p.ntab == 1 && p.dur && p.trans && !p.trans3;
+}
+
+template <bool BTERMS, int ET, int MODE>
 __global__ __launch_bounds__(NT) void k_prefix(Params p)
 {
+    constexpr bool INLINE = MODE != PREP_OFFSETS;
     extern __shared__ double lds_raw[];  // [PREP_NSEG][C] segment sums, then starts; INLINE: + [C] nu
     __shared__ double red2[2 * NT];
     __shared__ double redm[NT / 64], redx[NT / 64];
@@ -349,18 +392,66 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
     const int b = blockIdx.y, ch = (int)blockIdx.x - (p.warm_model ? 1 : 0), tid = threadIdx.x;
     const int C = p.C, NCH = p.NCH;
     if (ch < 0) {
-        warm_plan(p, b, lds_raw, red2);
+        double con = 0.0;  // first lane of each wave: its samples
+        if (MODE == PREP_NOTHING) {
+            const int len = seq_len(p, b);
+            double v[PREP_ALONE];
+#pragma unroll
+            for (int i = 0; i < PREP_ALONE; ++i) v[i] = i < NCH ? warm_load<ET>(p, b, i, len) : -INFINITY;
+#pragma unroll
+            for (int i = 0; i < PREP_ALONE; ++i)
+                if (i < NCH) con += (double)warm_sample(p, i, len, v[i]);
+            con = (tid & 63) == 0 ? con : 0.0;
+        }
+        warm_plan(p, b, lds_raw, red2, MODE != PREP_NOTHING, con);
         return;
     }
+    constexpr int NTB = MODE == PREP_NOTHING ? TAB_ITEMS / NT : 1;
+    float tab[NTB];  // this thread's entries of the tables, before exp (duration biases first)
+    const int KC = p.K * C;
     double *seg = lds_raw, *nus = lds_raw + PREP_NSEG * C;
+    const size_t f0 = (size_t)b * p.T * C;
     int L, J;
     double off = 0.0;  // threads tid < C: centred prefix sum at the chunk's first position
     if (INLINE) {
         L = seq_len(p, b);
         const int G = NT / C, g = tid / C, c = tid % C;
         const double *cs = p.chsum + (size_t)b * NCH * C + c;
-        double tot = 0.0, pre = 0.0;
-        if (g < G) {
+        double tot = 0.0, pre = 0.0, fm = 0.0, ex = 0.0, mxd = -DBL_MAX, mxt = -DBL_MAX;
+        if (MODE == PREP_NOTHING) {
+            __shared__ double csum[PREP_ALONE * COL_NG * PREP_ALONE_C];
+            const int ngr = (L + JMAX - 1) / JMAX;  // groups of positions
+#pragma unroll
+            for (int u = 0; u < NTB; ++u) {
+                const int i = min(u * NT + tid, KC + C * C - 1);
+                tab[u] = *(i < KC ? p.dur + i : p.trans + (i - KC));
+            }
+            for (int it = tid; it < ngr * C; it += NT) {
+                const int t0 = it / C * JMAX;
+                csum[it] = col_item<ET>(p, f0 + (size_t)t0 * C + it % C, min(L - t0, JMAX), fm, ex);
+            }
+            const float mps = rows_absmax(p, p.proj_start, b, 0, L), mpe = rows_absmax(p, p.proj_end, b, 0, L);
+            if (p.proj_start || p.proj_end)  // (of the whole workgroup: they are added to the largest emission)
+                fm = over_workgroup(fm, redm) + over_workgroup((double)mps, redm) + over_workgroup((double)mpe, redm);
+#pragma unroll
+            for (int u = 0; u < NTB; ++u) {
+                const int i = u * NT + tid;
+                mxd = fmax(mxd, i < KC ? (double)tab[u] : -DBL_MAX);
+                mxt = fmax(mxt, i >= KC ? (double)tab[u] : -DBL_MAX);
+            }
+            mxd = wave_max(mxd);
+            mxt = wave_max(mxt);
+            __syncthreads();
+            if (tid < C) {
+                for (int i = 0; i * COL_NG < ngr; ++i) {  // chunk by chunk
+                    double s = 0.0;
+#pragma unroll
+                    for (int q = 0; q < COL_NG; ++q) s += i * COL_NG + q < ngr ? csum[min(i * COL_NG + q, ngr - 1) * C + tid] : 0.0;
+                    tot += s;
+                    pre += i < ch ? s : 0.0;
+                }
+            }
+        } else if (g < G) {
 #pragma unroll 8
             for (int i = g; i < NCH; i += G) {
                 const double v = cs[(size_t)i * C];
@@ -368,21 +459,26 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
                 pre += i < ch ? v : 0.0;
             }
         }
-        double fm = 0.0, ex = 0.0;
-        for (int i = tid; i < NCH; i += NT) {
-            const float2 m = p.chmax[(size_t)b * NCH + i];
-            fm = fmax(fm, (double)m.x);
-            ex = fmax(ex, (double)m.y);
+        if (MODE == PREP_SUMS) {
+            for (int i = tid; i < NCH; i += NT) {
+                const float2 m = p.chmax[(size_t)b * NCH + i];
+                fm = fmax(fm, (double)m.x);
+                ex = fmax(ex, (double)m.y);
+            }
+            red2[tid] = tot;
+            red2[NT + tid] = pre;
+            __syncthreads();
         }
-        red2[tid] = tot;
-        red2[NT + tid] = pre;
-        __syncthreads();
         double nm = 0.0;
         if (tid < C) {
-            tot = 0.0;
-            for (int gg = 0; gg < G; ++gg) {
-                tot += red2[gg * C + tid];
-                off += red2[NT + gg * C + tid];
+            if (MODE == PREP_SUMS) {
+                tot = 0.0;
+                for (int gg = 0; gg < G; ++gg) {
+                    tot += red2[gg * C + tid];
+                    off += red2[NT + gg * C + tid];
+                }
+            } else {
+                off = pre;
             }
             const double nu = (p.center && L > 0) ? tot / (double)L : 0.0;
             off -= (double)min(ch * PREP_CH, L) * nu;
@@ -400,12 +496,16 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
         ex = wave_max(ex);
         nm = wave_max(nm);
         if (BTERMS) npi = wave_max(npi);
-        __syncthreads();
+        if (MODE == PREP_SUMS) __syncthreads();
         if ((tid & 63) == 0) {
             redm[tid >> 6] = fm;
             redx[tid >> 6] = ex;
             red2[tid >> 6] = nm;
             red2[NT + (tid >> 6)] = npi;
+            if (MODE == PREP_NOTHING) {
+                red2[8 + (tid >> 6)] = mxd;
+                red2[16 + (tid >> 6)] = mxt;
+            }
         }
         __syncthreads();
         if (tid == 0) {
@@ -414,8 +514,14 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
                 ex = fmax(ex, redx[i]);
                 nm = fmax(nm, red2[i]);
                 npi = fmax(npi, red2[NT + i]);
+                if (MODE == PREP_NOTHING) {
+                    mxd = fmax(mxd, red2[8 + i]);
+                    mxt = fmax(mxt, red2[16 + i]);
+                }
             }
-            hs = seq_header(p, L, fm + nm + 2.0 * npi, ex, nm);
+            // (single precision upwards, as k_colsum leaves them)
+            hs = MODE == PREP_NOTHING ? seq_header(p, L, (double)float_above(fm) + nm + 2.0 * npi, (double)float_above(ex), nm, mxd, mxt)
+                                      : seq_header(p, L, fm + nm + 2.0 * npi, ex, nm);
             if (ch == 0) p.hdr[b] = hs;
         }
     } else {
@@ -432,8 +538,14 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
     const int Jm = J - 1;
     const int tc = ch * PREP_CH;
     const size_t row0 = (size_t)b * (p.T + 1);
-    const size_t f0 = (size_t)b * p.T * C;
     const int items = PREP_NSEG * C;
+    if (MODE == PREP_NOTHING && b == 0 && ch == NCH - 1) {
+#pragma unroll
+        for (int u = 0; u < NTB; ++u) {
+            const int i = u * NT + tid;
+            if (i < KC + C * C) (i < KC ? p.W : p.Etr - KC)[i] = exp((double)tab[u]);
+        }
+    }
     auto load = [&](const int t0, const int c, double (&f)[PREP_SEG]) {
         const size_t o = f0 + (size_t)t0 * C + c;
         if (t0 + PREP_SEG <= L) {

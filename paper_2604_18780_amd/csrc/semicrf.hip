@@ -129,15 +129,15 @@ int check_launch()
 }
 
 // prefix stage shared by all entry points
-template <bool BTERMS, int ET, bool INLINE>
+template <bool BTERMS, int ET, int MODE>
 void launch_prefix(const Params &p, hipStream_t st)
 {
     // at most 66 KB (C = 256): C <= 64 stays within the default dynamic LDS
     const size_t lds = prefix_lds(p.C);
     if (lds > 64 * 1024)
-        (void)hipFuncSetAttribute((const void *)k_prefix<BTERMS, ET, INLINE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        (void)hipFuncSetAttribute((const void *)k_prefix<BTERMS, ET, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)lds);
-    hipLaunchKernelGGL((k_prefix<BTERMS, ET, INLINE>), dim3(p.NCH + (p.warm_model ? 1 : 0), p.B), dim3(NT), lds, st, p);
+    hipLaunchKernelGGL((k_prefix<BTERMS, ET, MODE>), dim3(p.NCH + (p.warm_model ? 1 : 0), p.B), dim3(NT), lds, st, p);
 }
 
 template <int ET>
@@ -145,15 +145,20 @@ int launch_prep_et(Params &p, hipStream_t st)
 {
     p.ntab = tables_blocks(p);
     p.logKC = log((double)p.K * (double)p.C);
-    hipLaunchKernelGGL(k_colsum<ET>, dim3(p.ntab + p.NCH * p.B + favour_blocks(p)), dim3(NT), 0, st, p);
     const bool bterms = p.logpair || p.proj_start || p.proj_end || p.pi_start || p.pi_end;
+    if (prep_alone(p)) {
+        if (bterms) launch_prefix<true, ET, PREP_NOTHING>(p, st);
+        else launch_prefix<false, ET, PREP_NOTHING>(p, st);
+        return check_launch();
+    }
+    hipLaunchKernelGGL(k_colsum<ET>, dim3(p.ntab + p.NCH * p.B + favour_blocks(p)), dim3(NT), 0, st, p);
     if (p.NCH <= PREP_INLINE) {
-        if (bterms) launch_prefix<true, ET, true>(p, st);
-        else launch_prefix<false, ET, true>(p, st);
+        if (bterms) launch_prefix<true, ET, PREP_SUMS>(p, st);
+        else launch_prefix<false, ET, PREP_SUMS>(p, st);
     } else {
         hipLaunchKernelGGL(k_prep_seq, dim3(p.B), dim3(PREP_NT), 0, st, p);
-        if (bterms) launch_prefix<true, ET, false>(p, st);
-        else launch_prefix<false, ET, false>(p, st);
+        if (bterms) launch_prefix<true, ET, PREP_OFFSETS>(p, st);
+        else launch_prefix<false, ET, PREP_OFFSETS>(p, st);
     }
     return check_launch();
 }

@@ -103,7 +103,8 @@ inline int favour_blocks(const Params &p) { return p.warm_model && p.trans3 ? (p
 // 24 labels; with 4 labels and two chunks it does: the launch takes 7.5 us without, 10.0 with it).  So
 // everything that comes from memory is requested before anything is done with it, and the transition matrix is worked on in
 // LDS by four threads per label.  lds: (PREP_NSEG + 1) C doubles, buf: 2 NT.
-__device__ void warm_plan(const Params &p, const int b, double *lds, double *buf)
+// sampled: p.contrast holds the samples; else con has those of the caller's wave (first lane; zero in the others).
+__device__ void warm_plan(const Params &p, const int b, double *lds, double *buf, const bool sampled, double con)
 {
     // buf, one after the other: ranges of durations [3 * NT]; detours (all, counted for 1 at most) and best successors, [4][64]
     // each; successors [4][64]
@@ -137,9 +138,10 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
     for (int i = 0; i < 4; ++i)
         if (dt) fv[i] = ((const float *)p.G3)[min(i * NT + tid, CC - 1)];
     // contrast: of this sequence alone, so that what happens to it does not depend on the others of its batch
-    double con = 0.0;
+    if (sampled) {
 #pragma unroll 8
-    for (int i = tid; i < p.NCH; i += NT) con += (double)p.contrast[(size_t)b * p.NCH + i];
+        for (int i = tid; i < p.NCH; i += NT) con += (double)p.contrast[(size_t)b * p.NCH + i];
+    }
     const double cnt = (double)((seq_len(p, b) + WARM_EVERY - 1) / WARM_EVERY);
     // ---- largest log weight of a longer duration over a shorter one, per label (and source label where they have
     // matrices of their own): ranges of durations, then over the ranges in order
