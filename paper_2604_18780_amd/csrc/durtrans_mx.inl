@@ -5,8 +5,8 @@
 // sixteen (task, position) pairs are the rows (forward) or columns (backward) of v_mfma_f64_16x16x4 products with the
 // table G[k][c'][c], so a table entry fetched from L2 once serves sixteen positions instead of four, and one
 // instruction does 1024 multiply-adds.  Scans of the genomic shape (K = 64, C = 24, 4 x 100 000), forward and backward: 4.9
-// and 6.3 ms with vector multiply-adds, four positions per table entry and one task per workgroup (durtrans.inl), 1.00 and
-// 1.19 ms so, the matrix pipes busy 41 and 45 % of the time.  The products wait for the table, so its entries are fetched as far
+// and 6.3 ms with vector multiply-adds, four positions per table entry and one task per workgroup (durtrans.inl), 0.97 and
+// 1.19 ms so, the matrix pipes busy 43 and 48 % of the time.  The products wait for the table, so its entries are fetched as far
 // ahead as registers allow: three tiles or groups for up to sixteen labels, else one (two, with 25 registers spilled: k_dx_fwd 1003 ->
 // 1031 us at the genomic shape).  One ahead against three: 1 x 1293, K = 380, C = 10 forward 627 -> 585, backward 447 -> 435 us;
 // 3 x 58043, K = 373, C = 6 forward 640 -> 603; 15 x 11034, K = 39, C = 4 392 -> 380, 341 -> 337.
@@ -282,10 +282,6 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tie
 #pragma unroll
                     for (int k = 1; i + k < DX_MB; ++k)
                         if (i + k < nbk) x[i + k] = fma(e[i].y, R::product(a, Ek[k - 1]), x[i + k]);
-                    if (tt > lo || tt == 0) {
-                        if (owner) rowA[(size_t)tt * C + c] = a;
-                        if (lane == 0) rowY[tt] = Y - Ybase;
-                    }
                     if (owner) Xq[dx_wrap(rb + i, KR) * C + c] = 0.0;  // consumed: free for a later target
                 }
                 if (owner) {
@@ -377,6 +373,20 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tie
                     const int k1 = pk[a] + i;
                     if (pk[a] > 0 && pslot[a] < C && k1 <= K + DX_MB - 1) XD[dx_wrap(rbD + k1, KR) * C + pslot[a]] += pend[a][i];
                 }
+        }
+        // The block's rows, by the waves that have nothing to do until the next long part: in the chains they delayed these, and the
+        // table entries fetched after them retired after them (launch 1005 -> 970 us at the genomic shape; C = 6, K = 373 600 -> 586);
+        // what has no row goes to a sink, lanes that own no label store what the owner of theirs, or of label 0, stores.
+        if (!chain) {
+#pragma unroll
+            for (int i = 0; i < DX_MB; ++i) {
+                const int tt = t0 + i;
+                const bool row = i < nbk && (tt > lo || tt == 0);  // uniform
+                *(row ? rowA + (size_t)tt * C + (cv ? c : 0) : p.sink + tid) = avq[i * CS + (cv ? c : 0)];
+            }
+        } else {
+            const int tt = t0 + lane;
+            *(lane < nbk && (tt > lo || tt == 0) ? rowY + tt : p.sink + tid) = Y - Ybase;
         }
         const int tlast = t0 + nbk - 1;
         t0 += nbk;
