@@ -362,7 +362,8 @@ __device__ __forceinline__ double xlogx(const float v)
     const double l = h + ((c - (h - a)) + fma(c * z, q, fma((double)e, LN2_REST, 2.0 * left)));
     return x > 0.0 ? x * (x < INFINITY ? l : x) : 0.0;
 }
-__device__ __forceinline__ double ent_block_sum(double v, double *red)  // every thread of NT; sum in thread 0
+template <int N>
+__device__ __forceinline__ double ent_block_sum(double v, double *red)  // every thread of N; sum in thread 0
 {
     for (int off = 32; off; off >>= 1) v += __shfl_down(v, off);
     __syncthreads();
@@ -370,34 +371,45 @@ __device__ __forceinline__ double ent_block_sum(double v, double *red)  // every
     __syncthreads();
     double s = 0.0;
     if (threadIdx.x == 0)
-        for (int i = 0; i < NT / 64; ++i) s += red[i];
+        for (int i = 0; i < N / 64; ++i) s += red[i];
     return s;
 }
 
-__global__ __launch_bounds__(NT) void k_ent_part(const float *pos_marg, const float *bdy_post, const int32_t *lengths,
+// Sixteen bytes per load, four loads at a time, and six waves per SIMD instead of three at the genomic shape: both launches 38.7 -> 32.5
+// us, the arithmetic of 9.6 million logarithms.
+constexpr int ENT_NT = 512;
+__global__ __launch_bounds__(ENT_NT) void k_ent_part(const float *pos_marg, const float *bdy_post, const int32_t *lengths,
                                                  int T, int C, int want_pos, int want_bdy, double *part)
 {
-    __shared__ double red[NT / 64];
+    __shared__ double red[ENT_NT / 64];
     const int b = blockIdx.y, tid = threadIdx.x;
     int L = lengths ? lengths[b] : T;
     L = L < 0 ? 0 : (L > T ? T : L);
     const int u0 = blockIdx.x * ENT_TOK, n = min(L - u0, ENT_TOK);  // n <= 0 beyond the sequence: sums are 0
     double a = 0.0, s = 0.0, e = 0.0;
-    if (want_pos) {
+    if (want_pos && n > 0) {
         const float *pm = pos_marg + ((size_t)b * T + u0) * C;
+        const int m = n * C, head = min((int)(-((uintptr_t)pm >> 2) & 3), m), body = (m - head) >> 2;  // (4-byte aligned at least)
+        const float4 *pm4 = (const float4 *)(pm + head);
 #pragma unroll 4
-        for (int i = tid; i < n * C; i += NT) a -= xlogx(pm[i]);
+        for (int i = tid; i < body; i += ENT_NT) {
+            const float4 v = pm4[i];
+            a -= (xlogx(v.x) + xlogx(v.y)) + (xlogx(v.z) + xlogx(v.w));
+        }
+        if (tid < head) a -= xlogx(pm[tid]);
+        const int tail = head + 4 * body + tid;
+        if (tail < m) a -= xlogx(pm[tail]);
     }
     if (want_bdy) {
         const float *bd = bdy_post + (size_t)b * (T + 1) + u0;
-        for (int i = tid; i < n; i += NT) {
+        for (int i = tid; i < n; i += ENT_NT) {
             s += (double)bd[i];
             e += xlogx(bd[i]);
         }
     }
-    a = ent_block_sum(a, red);
-    s = ent_block_sum(s, red);
-    e = ent_block_sum(e, red);
+    a = ent_block_sum<ENT_NT>(a, red);
+    s = ent_block_sum<ENT_NT>(s, red);
+    e = ent_block_sum<ENT_NT>(e, red);
     if (tid == 0) {
         double *o = part + ((size_t)b * gridDim.x + blockIdx.x) * 3;
         o[0] = a;
@@ -418,7 +430,7 @@ __global__ __launch_bounds__(NT) void k_ent_fin(const double *part, const int32_
 #pragma unroll
         for (int j = 0; j < 3; ++j) v[j] += part[((size_t)b * npart + i) * 3 + j];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) v[j] = ent_block_sum(v[j], red);
+    for (int j = 0; j < 3; ++j) v[j] = ent_block_sum<NT>(v[j], red);
     if (threadIdx.x != 0) return;
     if (h_pos) h_pos[b] = L > 0 ? (float)(v[0] / (double)L) : 0.f;
     // (no mass: no distribution, entropy 0, as k_entropies gives it)
