@@ -10,7 +10,7 @@
 // g sum_k W[k,c] lambda^-k = 1, and what was in the window n positions ago has become lambda^-n of it.  The slowest label
 // decides.  g comes from the transition matrix: Etr[c,c] for the label itself, plus r Etr[c,o] Etr[o,c] for a detour of
 // one position through o, where r is how far the other labels' scores lie below the best one (the mean over every
-// WARM_EVERY-th position of log sum_c exp(score - best), sampled by k_colsum).
+// WARM_EVERY-th position of log sum_c exp(score - best), sampled by k_colsum, or by k_prefix itself).
 //
 // Growth is not all: the labels' shares must settle, too.  They settle as fast where the transitions are about alike, and ever more
 // slowly the sharper these are, most of all where the scores tell nothing (r near 1), while the detours' sum grows.  So a
