@@ -314,17 +314,6 @@ constexpr int PREP_NSEG = PREP_CH / PREP_SEG;
 constexpr int PREP_INLINE = 512;
 static_assert(PREP_CH % JMAX == 0 && JMAX % PREP_SEG == 0 && NT == 256 && PREP_NSEG == 32, "k_prefix geometry");
 
-// The largest of x over the workgroup, in every thread (red: a number per wave).
-__device__ __forceinline__ double over_workgroup(double x, double *red)
-{
-    x = wave_max(x);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
-    __syncthreads();
-    for (int i = 0; i < NT / 64; ++i) x = fmax(x, red[i]);
-    return x;
-}
-
 // 1/x to the last bit or two: hardware estimate and two Newton steps (x is a finite positive exp)
 __device__ __forceinline__ double recip(const double x)
 {
@@ -426,13 +415,42 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
                 const int i = min(u * NT + tid, KC + C * C - 1);
                 tab[u] = *(i < KC ? p.dur + i : p.trans + (i - KC));
             }
+            double mc[PREP_ALONE] = {};  // boundary terms: the largest emission of each chunk
             for (int it = tid; it < ngr * C; it += NT) {
-                const int t0 = it / C * JMAX;
-                csum[it] = col_item<ET>(p, f0 + (size_t)t0 * C + it % C, min(L - t0, JMAX), fm, ex);
+                const int g32 = it / C;
+                double m = 0.0;
+                csum[it] = col_item<ET>(p, f0 + (size_t)g32 * JMAX * C + it % C, min(L - g32 * JMAX, JMAX), m, ex);
+                if (BTERMS) {
+#pragma unroll
+                    for (int i = 0; i < PREP_ALONE; ++i) mc[i] = fmax(mc[i], g32 / COL_NG == i ? m : 0.0);
+                } else {
+                    fm = fmax(fm, m);
+                }
             }
-            const float mps = rows_absmax(p, p.proj_start, b, 0, L), mpe = rows_absmax(p, p.proj_end, b, 0, L);
-            if (p.proj_start || p.proj_end)  // (of the whole workgroup: they are added to the largest emission)
-                fm = over_workgroup(fm, redm) + over_workgroup((double)mps, redm) + over_workgroup((double)mpe, redm);
+            if (BTERMS) {  // the largest sum of a chunk's three maxima, not the sum of the sequence's: see colsum_body
+                constexpr int NW = NT / 64;
+#pragma unroll
+                for (int i = 0; i < PREP_ALONE; ++i) {
+                    const int u0 = i * PREP_CH, u1 = min(u0 + PREP_CH, L);
+                    const double m[3] = {wave_max(mc[i]), wave_max((double)rows_absmax(p, p.proj_start, b, u0, u1)),
+                                         wave_max((double)rows_absmax(p, p.proj_end, b, u0, u1))};
+                    if ((tid & 63) == 0) {
+#pragma unroll
+                        for (int j = 0; j < 3; ++j) red2[(i * 3 + j) * NW + (tid >> 6)] = m[j];
+                    }
+                }
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < PREP_ALONE; ++i) {
+                    double sum = 0.0;
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) {
+                        const double *r = red2 + (i * 3 + j) * NW;
+                        sum += fmax(fmax(r[0], r[1]), fmax(r[2], r[3]));
+                    }
+                    fm = fmax(fm, sum);
+                }
+            }
 #pragma unroll
             for (int u = 0; u < NTB; ++u) {
                 const int i = u * NT + tid;

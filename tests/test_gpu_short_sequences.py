@@ -42,3 +42,64 @@ def test_sums_and_tables_in_one_launch(T, K, C, terms):
     best = sb.semicrf_viterbi(emis, dev(w.lengths, np.int32), dev(w.trans), dev(w.dur))[0].double().cpu().numpy()
     want = oracle.viterbi(emis.float().cpu().numpy(), w.lengths, w.trans, w.dur)[0]
     assert (np.abs(best - want) <= 1e-5 * np.maximum(np.abs(want), 1.0)).all()
+
+
+@pytest.mark.parametrize("T", [600, 767, 768, 900])
+def test_bounds_add_up_the_maxima_of_a_chunk(T):
+    """How far a message can move in a position is bounded by the largest emission, start and end term of the same 256 positions, with
+    sums in one launch (T < 768) or in two: 200 + 150 in different chunks is within the 300 nats of the range report, in one chunk not."""
+    w = synth.small_random(T, 2, T, 6, 5, ragged=False)
+    w.lengths[:] = T
+    ps, pe = np.zeros((2, 2, T, 5), dtype=np.float32)
+    w.emis[:, 100, 2] = 200.0
+    ps[0, 300, 1], pe[0, 520, 3] = 150.0, -120.0  # a chunk each
+    ps[1, 90, 1] = 150.0                          # the emission's
+    ws = sb.alloc_workspace(2, T, 6, 5, 0, 1, "cuda:0")
+    out = sb.semicrf_fwd_bwd_boundary(dev(w.emis), dev(w.lengths, np.int32), dev(w.trans), dev(w.dur), None, dev(ps), dev(pe), workspace=ws)
+    exceeded, logz = [x.cpu().numpy() for x in sb.semicrf_seq_report(ws, 2, T, 6, 5, 0, 1)]
+    assert exceeded.tolist() == [0, 1]
+    r = oracle.fwd_bwd(w.emis, w.lengths, w.trans, w.dur, proj_start=ps, proj_end=pe)
+    assert abs(logz[0] - r.logz[0]) <= 1e-9 * abs(r.logz[0])
+    assert np.abs(out["grad_emis"][0].double().cpu().numpy() - r.grad_emis[0]).max() <= 1e-4
+
+
+def outputs(x, T, K, C, terms):
+    """Everything that scores, gradients and decoding leave, with intervals of 96 positions where a caller can say so."""
+    B = x[0].shape[0]
+    flat = []
+    for kind in (0, 1):
+        ws = sb.alloc_workspace(B, T, K, C, 96, kind, "cuda:0")
+        if kind:
+            flat += list(sb.semicrf_fwd_bwd_boundary(*x, None, *terms, ckpt_interval=96, workspace=ws).values())
+        else:
+            flat.append(sb.semicrf_logz_fwd_boundary(*x, *terms, ckpt_interval=96, workspace=ws))
+        flat += sb.semicrf_seq_report(ws, B, T, K, C, 96, kind) + sb.semicrf_scan_report(ws, B, T, K, C, 96, kind)
+    flat += sb.semicrf_viterbi(*x, *terms)
+    return [a.cpu().numpy() for a in flat]
+
+
+@pytest.mark.parametrize("K,C", [(8, 4), (16, 24), (5, 7), (2, 44)])
+@pytest.mark.parametrize("terms", [False, True])
+@pytest.mark.parametrize("scale", [1.0, 30.0])
+def test_the_same_bits_as_with_sums_from_a_launch_of_their_own(K, C, terms, scale):
+    """The same sequences, one of them empty, in rows of 767 positions (one launch) and of 768 (two): the same scaling blocks, warm-ups
+    and sums, so everything is the same to the last bit.  Block lengths between 1 and 32: scores up to `scale`, whose largest values lie
+    in other chunks than those of the projections.  Positions beyond a sequence hold NaN."""
+    rng = np.random.default_rng(K + C)
+    got = []
+    lengths = np.array([0, 767, 512, 300, 700, 1], dtype=np.int32)
+    w = synth.small_random(C, 6, 768, K, C, ragged=False)
+    w.emis[:, :256] *= scale
+    ps, pe = rng.standard_normal((2, 6, 768, C)).astype(np.float32)
+    ps[:, 256:512] *= 0.7 * scale
+    pe[:, 512:] *= 0.5 * scale
+    pis, pie = rng.standard_normal((2, C)).astype(np.float32)
+    for a in (w.emis, ps, pe):
+        for b, n in enumerate(lengths):
+            a[b, n:] = np.nan
+    for T in (767, 768):
+        t = [dev(ps[:, :T]), dev(pe[:, :T]), dev(pis), dev(pie)] if terms else [None] * 4
+        got.append(outputs((dev(w.emis[:, :T]), dev(lengths, np.int32), dev(w.trans), dev(w.dur)), T, K, C, t))
+    for i, (a, b) in enumerate(zip(*got)):
+        cut = tuple(slice(0, min(m, n)) for m, n in zip(a.shape, b.shape))
+        assert np.array_equal(a[cut], b[cut]), (i, a.shape)
