@@ -381,18 +381,19 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
     const int b = blockIdx.y, ch = (int)blockIdx.x - (p.warm_model ? 1 : 0), tid = threadIdx.x;
     const int C = p.C, NCH = p.NCH;
     if (ch < 0) {
-        double con = 0.0;  // first lane of each wave: its samples
+        __shared__ float smp[PREP_ALONE * (NT / 64)];
         if (MODE == PREP_NOTHING) {
             const int len = seq_len(p, b);
             double v[PREP_ALONE];
 #pragma unroll
             for (int i = 0; i < PREP_ALONE; ++i) v[i] = i < NCH ? warm_load<ET>(p, b, i, len) : -INFINITY;
 #pragma unroll
-            for (int i = 0; i < PREP_ALONE; ++i)
-                if (i < NCH) con += (double)warm_sample(p, i, len, v[i]);
-            con = (tid & 63) == 0 ? con : 0.0;
+            for (int i = 0; i < PREP_ALONE; ++i) {
+                const float s = i < NCH ? warm_sample(p, i, len, v[i]) : 0.f;
+                if ((tid & 63) == 0) smp[i * (NT / 64) + (tid >> 6)] = s;
+            }
         }
-        warm_plan(p, b, lds_raw, red2, MODE != PREP_NOTHING, con);
+        warm_plan(p, b, lds_raw, red2, MODE == PREP_NOTHING ? smp : nullptr);
         return;
     }
     constexpr int NTB = MODE == PREP_NOTHING ? TAB_ITEMS / NT : 1;

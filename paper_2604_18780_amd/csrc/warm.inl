@@ -103,8 +103,8 @@ inline int favour_blocks(const Params &p) { return p.warm_model && p.trans3 ? (p
 // 24 labels; with 4 labels and two chunks it does: the launch takes 7.5 us without, 10.0 with it).  So
 // everything that comes from memory is requested before anything is done with it, and the transition matrix is worked on in
 // LDS by four threads per label.  lds: (PREP_NSEG + 1) C doubles, buf: 2 NT.
-// sampled: p.contrast holds the samples; else con has those of the caller's wave (first lane; zero in the others).
-__device__ void warm_plan(const Params &p, const int b, double *lds, double *buf, const bool sampled, double con)
+// smp: the samples of the sequence's chunks, NT / 64 each, written by the caller in LDS; else p.contrast holds their sums.
+__device__ void warm_plan(const Params &p, const int b, double *lds, double *buf, const float *smp)
 {
     // buf, one after the other: ranges of durations [3 * NT]; detours (all, counted for 1 at most) and best successors, [4][64]
     // each; successors [4][64]
@@ -138,7 +138,8 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
     for (int i = 0; i < 4; ++i)
         if (dt) fv[i] = ((const float *)p.G3)[min(i * NT + tid, CC - 1)];
     // contrast: of this sequence alone, so that what happens to it does not depend on the others of its batch
-    if (sampled) {
+    double con = 0.0;
+    if (!smp) {
 #pragma unroll 8
         for (int i = tid; i < p.NCH; i += NT) con += (double)p.contrast[(size_t)b * p.NCH + i];
     }
@@ -189,6 +190,8 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
         const int e = i * NT + tid;
         if (e < CC) tl[e / C * ts + e % C] = tr[i];
     }
+    // (added up as k_colsum does it, so that both prefix stages choose the same length)
+    if (smp && tid < p.NCH) con = (double)(((smp[4 * tid] + smp[4 * tid + 1]) + smp[4 * tid + 2]) + smp[4 * tid + 3]);
     con = wave_sum(con);
     __syncthreads();  // (the ranges above have been read)
     if (lane == 0) cons[wv] = con;
