@@ -358,15 +358,29 @@ __device__ __forceinline__ double exp_any(const double x)
 // MODE: what has been done before.  PREP_OFFSETS: k_colsum and k_prep_seq; PREP_SUMS: k_colsum (INLINE above); PREP_NOTHING: the
 // workgroup adds up its whole sequence itself, and one of them builds the tables, see prep_alone.
 constexpr int PREP_OFFSETS = 0, PREP_SUMS = 1, PREP_NOTHING = 2;
-constexpr int PREP_ALONE = 3;        // chunks
-constexpr int PREP_ALONE_C = 44;     // labels: C (C + 1) <= TAB_ITEMS
-static_assert((PREP_ALONE_C + 1) * (PREP_ALONE_C + 2) > TAB_ITEMS, "more labels have more entries of the tables");
+constexpr int PREP_ALONE = 3;   // chunks
+constexpr int PREP_ROUNDS = 2;  // items of 32 positions per thread
 // Short sequences with small tables: the launch of k_colsum and the gap behind it cost more than sums that every workgroup of a
-// sequence forms for itself.  Whole calls, two launches against one, us: gradients 2 x 512, K = 8, C = 4 60.5 -> 57.4; 64 x 256,
-// K = 16, C = 24 96.8 -> 92.7, decoding 85.4 -> 80.9; 8 x 767, K = 16, C = 24 83.9 -> 82.0 (each further chunk adds a round of loads).
+// sequence forms for itself, as long as these are few.  Time of a whole call with two launches over that with one, least .. most of
+// training, scores and best segmentations with 4 .. 44 labels, T = 250 .. 760 (calls of 45 .. 1800 us):
+//   sequences                     1             4             16            64            256          1024
+//   one chunk                1.01 .. 1.08  1.01 .. 1.09  1.02 .. 1.09  1.03 .. 1.10  1.01 .. 1.06  1.00 .. 1.05
+//   more, an item a thread   1.01 .. 1.07  1.03 .. 1.07  1.02 .. 1.06  1.02 .. 1.06  1.01 .. 1.04  1.00 .. 1.03
+//   ... two items             .99 .. 1.05  1.01 .. 1.09  1.01 .. 1.04  1.02 .. 1.06  1.00 .. 1.03   .95 .. 1.03
+//   ... three items and more  .98 .. 1.05   .99 .. 1.06  1.00 .. 1.04  1.00 .. 1.05   .99 .. 1.02   .98 .. 1.03
+// With two items and three chunks it turns between 256 and 340 sequences (1.00 .. 1.03, .98 .. 1.01).  Start and end projections are
+// read by every workgroup of the sequence, too; with those (replayed from a graph: host work is longer than the smallest of these calls)
+//   one chunk                1.00 .. 1.02  1.01 .. 1.02  1.02 .. 1.13  1.02 .. 1.06  1.00 .. 1.03
+//   two chunks                .98 .. 1.01   .99 .. 1.01  1.01 .. 1.09  1.00 .. 1.03   .99 .. 1.00
+//   three chunks              .96 .. 1.01   .98 .. 1.05   .99 .. 1.07   .98 .. 1.02   .99 .. 1.01
 inline bool prep_alone(const Params &p)
 {
-    return p.NCH <= PREP_ALONE && p.ntab == 1 && p.dur && p.trans && !p.trans3;
+    if (p.NCH > PREP_ALONE || p.ntab != 1 || !p.dur || !p.trans || p.trans3) return false;
+    const int items = (p.T + JMAX - 1) / JMAX * p.C, chunks = p.B * p.NCH;  // (no overflow: C <= 44 with one share of tables)
+    if (items > PREP_ROUNDS * NT) return false;
+    if (p.NCH == 1) return true;
+    if (p.proj_start || p.proj_end) return p.NCH == 2 && chunks >= 32 && chunks <= 128;
+    return items <= NT || chunks <= 768;
 }
 
 template <bool BTERMS, int ET, int MODE>
@@ -409,26 +423,27 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
         const double *cs = p.chsum + (size_t)b * NCH * C + c;
         double tot = 0.0, pre = 0.0, fm = 0.0, ex = 0.0, mxd = -DBL_MAX, mxt = -DBL_MAX;
         if (MODE == PREP_NOTHING) {
-            __shared__ double csum[PREP_ALONE * COL_NG * PREP_ALONE_C];
+            __shared__ double csum[PREP_ROUNDS * NT];
             const int ngr = (L + JMAX - 1) / JMAX;  // groups of positions
 #pragma unroll
             for (int u = 0; u < NTB; ++u) {
                 const int i = min(u * NT + tid, KC + C * C - 1);
                 tab[u] = *(i < KC ? p.dur + i : p.trans + (i - KC));
             }
-            double mc[PREP_ALONE] = {};  // boundary terms: the largest emission of each chunk
+            const bool proj = BTERMS && (p.proj_start || p.proj_end);
+            double mc[PREP_ALONE] = {};  // with projections: the largest emission of each chunk
             for (int it = tid; it < ngr * C; it += NT) {
                 const int g32 = it / C;
                 double m = 0.0;
                 csum[it] = col_item<ET>(p, f0 + (size_t)g32 * JMAX * C + it % C, min(L - g32 * JMAX, JMAX), m, ex);
-                if (BTERMS) {
+                if (proj) {
 #pragma unroll
                     for (int i = 0; i < PREP_ALONE; ++i) mc[i] = fmax(mc[i], g32 / COL_NG == i ? m : 0.0);
                 } else {
                     fm = fmax(fm, m);
                 }
             }
-            if (BTERMS) {  // the largest sum of a chunk's three maxima, not the sum of the sequence's: see colsum_body
+            if (proj) {  // the largest sum of a chunk's three maxima, not the sum of the sequence's: see colsum_body
                 constexpr int NW = NT / 64;
 #pragma unroll
                 for (int i = 0; i < PREP_ALONE; ++i) {

@@ -1,6 +1,8 @@
 """GPU parity of the prefix stage that needs no launch before it (up to three chunks of 256 positions, tables of at most 2048
-entries), at its edges and on the other side of them: groups of 32 positions, chunks, the largest tables, sequences that are empty or
-end at a chunk's edge, half-precision emissions.  Tolerances as elsewhere: 1e-5 of logZ, 1e-4 of a gradient's largest entry."""
+entries, at most two sums of 32 positions per thread), at its edges and on the other side of them: groups of 32 positions, chunks, the
+largest tables, sequences that are empty or end at a chunk's edge, half-precision emissions.  Tolerances as elsewhere: 1e-5 of logZ,
+1e-4 of a gradient's largest entry where that is above 1.  What the stage leaves beside the sums (bounds, warm-ups) is compared to the
+last bit with what two launches leave for the same sequences."""
 import numpy as np
 import pytest
 import torch
@@ -44,62 +46,63 @@ def test_sums_and_tables_in_one_launch(T, K, C, terms):
     assert (np.abs(best - want) <= 1e-5 * np.maximum(np.abs(want), 1.0)).all()
 
 
-@pytest.mark.parametrize("T", [600, 767, 768, 900])
+@pytest.mark.parametrize("T", [400, 511, 512, 900])
 def test_bounds_add_up_the_maxima_of_a_chunk(T):
     """How far a message can move in a position is bounded by the largest emission, start and end term of the same 256 positions, with
-    sums in one launch (T < 768) or in two: 200 + 150 in different chunks is within the 300 nats of the range report, in one chunk not."""
-    w = synth.small_random(T, 2, T, 6, 5, ragged=False)
-    w.lengths[:] = T
-    ps, pe = np.zeros((2, 2, T, 5), dtype=np.float32)
-    w.emis[:, 100, 2] = 200.0
-    ps[0, 300, 1], pe[0, 520, 3] = 150.0, -120.0  # a chunk each
-    ps[1, 90, 1] = 150.0                          # the emission's
-    ws = sb.alloc_workspace(2, T, 6, 5, 0, 1, "cuda:0")
+    sums in one launch (T < 512) or in two: 200 and 150 + 120 in different chunks are within the 300 nats of the range report, 200 + 150
+    in one chunk are not."""
+    w = synth.small_random(T, 16, T, 6, 5, ragged=False)
+    ps, pe = np.zeros((2, 16, T, 5), dtype=np.float32)
+    w.emis[:2, 100, 2] = 200.0
+    ps[0, 300, 1], pe[0, 320, 3] = 150.0, -120.0
+    ps[1, 90, 1] = 150.0
+    ws = sb.alloc_workspace(16, T, 6, 5, 0, 1, "cuda:0")
     out = sb.semicrf_fwd_bwd_boundary(dev(w.emis), dev(w.lengths, np.int32), dev(w.trans), dev(w.dur), None, dev(ps), dev(pe), workspace=ws)
-    exceeded, logz = [x.cpu().numpy() for x in sb.semicrf_seq_report(ws, 2, T, 6, 5, 0, 1)]
-    assert exceeded.tolist() == [0, 1]
+    exceeded, logz = [x.cpu().numpy() for x in sb.semicrf_seq_report(ws, 16, T, 6, 5, 0, 1)]
+    assert exceeded.tolist() == [0, 1] + [0] * 14
     r = oracle.fwd_bwd(w.emis, w.lengths, w.trans, w.dur, proj_start=ps, proj_end=pe)
     assert abs(logz[0] - r.logz[0]) <= 1e-9 * abs(r.logz[0])
     assert np.abs(out["grad_emis"][0].double().cpu().numpy() - r.grad_emis[0]).max() <= 1e-4
 
 
-def outputs(x, T, K, C, terms):
-    """Everything that scores, gradients and decoding leave, with intervals of 96 positions where a caller can say so."""
+def outputs(x, T, K, C, terms, delta):
+    """Everything that scores, gradients and decoding leave, with intervals of delta positions where a caller can say so."""
     B = x[0].shape[0]
     flat = []
     for kind in (0, 1):
-        ws = sb.alloc_workspace(B, T, K, C, 96, kind, "cuda:0")
+        ws = sb.alloc_workspace(B, T, K, C, delta, kind, "cuda:0")
         if kind:
-            flat += list(sb.semicrf_fwd_bwd_boundary(*x, None, *terms, ckpt_interval=96, workspace=ws).values())
+            flat += list(sb.semicrf_fwd_bwd_boundary(*x, None, *terms, ckpt_interval=delta, workspace=ws).values())
         else:
-            flat.append(sb.semicrf_logz_fwd_boundary(*x, *terms, ckpt_interval=96, workspace=ws))
-        flat += sb.semicrf_seq_report(ws, B, T, K, C, 96, kind) + sb.semicrf_scan_report(ws, B, T, K, C, 96, kind)
+            flat.append(sb.semicrf_logz_fwd_boundary(*x, *terms, ckpt_interval=delta, workspace=ws))
+        flat += sb.semicrf_seq_report(ws, B, T, K, C, delta, kind) + sb.semicrf_scan_report(ws, B, T, K, C, delta, kind)
     flat += sb.semicrf_viterbi(*x, *terms)
     return [a.cpu().numpy() for a in flat]
 
 
-@pytest.mark.parametrize("K,C", [(8, 4), (16, 24), (5, 7), (2, 44)])
-@pytest.mark.parametrize("terms", [False, True])
+@pytest.mark.parametrize("T,K,C,terms", [(767, 8, 4, False), (767, 20, 16, False), (767, 5, 7, False), (767, 2, 21, False), (352, 2, 44, False),
+                                         (512, 16, 32, False), (511, 8, 4, True), (511, 16, 24, True), (511, 30, 32, True), (352, 2, 44, True)])
 @pytest.mark.parametrize("scale", [1.0, 30.0])
-def test_the_same_bits_as_with_sums_from_a_launch_of_their_own(K, C, terms, scale):
-    """The same sequences, one of them empty, in rows of 767 positions (one launch) and of 768 (two): the same scaling blocks, warm-ups
-    and sums, so everything is the same to the last bit.  Block lengths between 1 and 32: scores up to `scale`, whose largest values lie
-    in other chunks than those of the projections.  Positions beyond a sequence hold NaN."""
+def test_the_same_bits_as_with_sums_from_a_launch_of_their_own(T, K, C, terms, scale):
+    """The same sequences, the first of them empty, in rows of T positions (one launch) and of T + 1 (two launches: a chunk or a
+    sum per thread more than one launch is for): the same scaling blocks, warm-ups and sums, so everything is the same to the last bit.  Block
+    lengths between 1 and 32: scores up to `scale`, whose largest values lie in other chunks than those of the projections.  Positions
+    beyond a sequence hold NaN."""
     rng = np.random.default_rng(K + C)
     got = []
-    lengths = np.array([0, 767, 512, 300, 700, 1], dtype=np.int32)
-    w = synth.small_random(C, 6, 768, K, C, ragged=False)
+    lengths = np.array([0, T, T * 2 // 3, T // 256 * 256, T - 67, 1] + [T] * 10, dtype=np.int32)
+    w = synth.small_random(C, 16, T + 1, K, C, ragged=False)
     w.emis[:, :256] *= scale
-    ps, pe = rng.standard_normal((2, 6, 768, C)).astype(np.float32)
-    ps[:, 256:512] *= 0.7 * scale
-    pe[:, 512:] *= 0.5 * scale
+    ps, pe = rng.standard_normal((2, 16, T + 1, C)).astype(np.float32)
+    ps[:, 256:] *= 0.7 * scale
+    pe[:, 384:] *= 0.5 * scale
     pis, pie = rng.standard_normal((2, C)).astype(np.float32)
     for a in (w.emis, ps, pe):
         for b, n in enumerate(lengths):
             a[b, n:] = np.nan
-    for T in (767, 768):
-        t = [dev(ps[:, :T]), dev(pe[:, :T]), dev(pis), dev(pie)] if terms else [None] * 4
-        got.append(outputs((dev(w.emis[:, :T]), dev(lengths, np.int32), dev(w.trans), dev(w.dur)), T, K, C, t))
+    for n in (T, T + 1):
+        t = [dev(ps[:, :n]), dev(pe[:, :n]), dev(pis), dev(pie)] if terms else [None] * 4
+        got.append(outputs((dev(w.emis[:, :n]), dev(lengths, np.int32), dev(w.trans), dev(w.dur)), n, K, C, t, (T + 8) // 8))
     for i, (a, b) in enumerate(zip(*got)):
         cut = tuple(slice(0, min(m, n)) for m, n in zip(a.shape, b.shape))
         assert np.array_equal(a[cut], b[cut]), (i, a.shape)
