@@ -396,18 +396,17 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
     const int C = p.C, NCH = p.NCH;
     if (ch < 0) {
         __shared__ float smp[PREP_ALONE * (NT / 64)];
-        if (MODE == PREP_NOTHING) {
-            const int len = seq_len(p, b);
-            double v[PREP_ALONE];
+        const int len = seq_len(p, b);
+        double v[PREP_ALONE];
 #pragma unroll
-            for (int i = 0; i < PREP_ALONE; ++i) v[i] = i < NCH ? warm_load<ET>(p, b, i, len) : -INFINITY;
+        for (int i = 0; i < PREP_ALONE; ++i) v[i] = MODE == PREP_NOTHING && i < NCH ? warm_load<ET>(p, b, i, len) : -INFINITY;
+        warm_plan(p, b, lds_raw, red2, MODE == PREP_NOTHING ? smp : nullptr, [&]() {
 #pragma unroll
             for (int i = 0; i < PREP_ALONE; ++i) {
                 const float s = i < NCH ? warm_sample(p, i, len, v[i]) : 0.f;
                 if ((tid & 63) == 0) smp[i * (NT / 64) + (tid >> 6)] = s;
             }
-        }
-        warm_plan(p, b, lds_raw, red2, MODE == PREP_NOTHING ? smp : nullptr);
+        });
         return;
     }
     constexpr int NTB = MODE == PREP_NOTHING ? TAB_ITEMS / NT : 1;

@@ -103,8 +103,9 @@ inline int favour_blocks(const Params &p) { return p.warm_model && p.trans3 ? (p
 // 24 labels; with 4 labels and two chunks it does: the launch takes 7.5 us without, 10.0 with it).  So
 // everything that comes from memory is requested before anything is done with it, and the transition matrix is worked on in
 // LDS by four threads per label.  lds: (PREP_NSEG + 1) C doubles, buf: 2 NT.
-// smp: the samples of the sequence's chunks, NT / 64 each, written by the caller in LDS; else p.contrast holds their sums.
-__device__ void warm_plan(const Params &p, const int b, double *lds, double *buf, const float *smp)
+// smp: place in LDS for the samples of the sequence's chunks, NT / 64 each, which sample() takes; without, p.contrast holds their sums.
+template <class Sample>
+__device__ __forceinline__ void warm_plan(const Params &p, const int b, double *lds, double *buf, const float *smp, Sample sample)
 {
     // buf, one after the other: ranges of durations [3 * NT]; detours (all, counted for 1 at most) and best successors, [4][64]
     // each; successors [4][64]
@@ -139,7 +140,9 @@ __device__ void warm_plan(const Params &p, const int b, double *lds, double *buf
         if (dt) fv[i] = ((const float *)p.G3)[min(i * NT + tid, CC - 1)];
     // contrast: of this sequence alone, so that what happens to it does not depend on the others of its batch
     double con = 0.0;
-    if (!smp) {
+    if (smp) {
+        sample();
+    } else {
 #pragma unroll 8
         for (int i = tid; i < p.NCH; i += NT) con += (double)p.contrast[(size_t)b * p.NCH + i];
     }
