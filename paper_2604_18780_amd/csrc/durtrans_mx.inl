@@ -375,18 +375,21 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tie
                 }
         }
         // The block's rows, by the waves that have nothing to do until the next long part: in the chains they delayed these, and the
-        // table entries fetched after them retired after them (launch 1005 -> 970 us at the genomic shape; C = 6, K = 373 600 -> 586);
-        // what has no row goes to a sink, lanes that own no label store what the owner of theirs, or of label 0, stores.
-        if (!chain) {
+        // table entries fetched after them retired after them (launch 1005 -> 970 us at the genomic shape; C = 6, K = 373 600 -> 586).
+        // In a block that has rows, a position without one goes to a sink; lanes that own no label store what the owner of theirs, or
+        // of label 0, stores.  A block of the warm-up has none and stores nothing: see k_dx_bwd.
+        if (nbk > 0 && (t0 + nbk - 1 > lo || t0 == 0)) {  // uniform
+            if (!chain) {
 #pragma unroll
-            for (int i = 0; i < DX_MB; ++i) {
-                const int tt = t0 + i;
-                const bool row = i < nbk && (tt > lo || tt == 0);  // uniform
-                *(row ? rowA + (size_t)tt * C + (cv ? c : 0) : p.sink + tid) = avq[i * CS + (cv ? c : 0)];
+                for (int i = 0; i < DX_MB; ++i) {
+                    const int tt = t0 + i;
+                    const bool row = i < nbk && (tt > lo || tt == 0);  // uniform
+                    *(row ? rowA + (size_t)tt * C + (cv ? c : 0) : p.sink + tid) = avq[i * CS + (cv ? c : 0)];
+                }
+            } else {
+                const int tt = t0 + lane;
+                *(lane < nbk && (tt > lo || tt == 0) ? rowY + tt : p.sink + tid) = Y - Ybase;
             }
-        } else {
-            const int tt = t0 + lane;
-            *(lane < nbk && (tt > lo || tt == 0) ? rowY + tt : p.sink + tid) = Y - Ybase;
         }
         const int tlast = t0 + nbk - 1;
         t0 += nbk;
@@ -755,9 +758,13 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
             }
         }
         lds_barrier();
-        // ---- the block's rows.  What has no row goes to a sink: the number of stores behind the next block's loads is then known, and
-        // waiting for those is not waiting for these.  Lanes that own no label store what the owner of theirs, or of label 0, stores.
-        if (!chain) {
+        // ---- the block's rows.  A position without one goes to a sink: the number of stores behind the next block's loads is then
+        // known, and waiting for those is not waiting for these.  Lanes that own no label store what the owner of theirs, or of label 0,
+        // stores.  A block of the warm-up has no rows and forms none: with sums and stores to the sink there too, long warm-ups (few labels,
+        // short segments) took longer than without any of this; a call, before | with them | so, us: 16 x 2000, K = 8, C = 4
+        // 618 | 632 | 597; C = 1 586 | 609 | 572; K = 16, C = 5 841 | 861 | 802; K = 16, C = 16 242 | 225 | 221; 2 x 1704, K = 77, C = 4
+        // 258 | 260 | 251; 4 x 100 000, K = 64, C = 24 3307 | 3161 | 3164.
+        if (!chain && nbk > 0 && t0 - nbk + 1 < hi) {  // uniform
             constexpr int OS = 16 * CPB;
             const double *vr = Vq + cc0 * W + r0;
             double v[DX_MB];
