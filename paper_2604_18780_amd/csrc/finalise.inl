@@ -376,12 +376,18 @@ __device__ __forceinline__ double ent_block_sum(double v, double *red)  // every
 }
 
 // Sixteen bytes per load, four loads at a time, and six waves per SIMD instead of three at the genomic shape: both launches 38.7 -> 32.5
-// us, the arithmetic of 9.6 million logarithms.
-constexpr int ENT_NT = 512;
-__global__ __launch_bounds__(ENT_NT) void k_ent_part(const float *pos_marg, const float *bdy_post, const int32_t *lengths,
-                                                 int T, int C, int want_pos, int want_bdy, double *part)
+// us, the arithmetic of 9.6 million logarithms.  A workgroup has as many threads as its ENT_TOK tokens of C marginals keep busy, and no more:
+// both launches, us, one number per load and 256 threads | 128 | 256 | 512 threads (launches alone take 15.5):
+//   64 x 100 000   C = 1 36 | 33 | 40 | 58; C = 2 46 | 43 | 46 | 62; C = 4 67 | 65 | 66 | 79; C = 6 88 | 86 | 86 | 95
+//   1024 x 2000    C = 1 17 | 16 | 18 | 24; C = 4 28 | 34 | 28 | 31; C = 8 43 | 49 | 46 | 43; C = 24 101 | 108 | 96 | 96
+//   64 x 20 000    C = 2 16 | 20 | 16 | 17; C = 6 26 | 27 | 24 | 25; C = 8 30 | 32 | 28 | 29; C = 24 69 | 76 | 63 | 63
+//   4 x 100 000    C = 8 16 | 16 | 16 | 16; C = 12 20 | 20 | 19 | 19; C = 24 35 | 36 | 31 | 30; C = 64 81 | 81 | 70 | 65
+inline int ent_threads(const int C) { return C < 2 ? 128 : (C < 8 ? 256 : 512); }
+template <int N>
+__global__ __launch_bounds__(N) void k_ent_part(const float *pos_marg, const float *bdy_post, const int32_t *lengths,
+                                                int T, int C, int want_pos, int want_bdy, double *part)
 {
-    __shared__ double red[ENT_NT / 64];
+    __shared__ double red[N / 64];
     const int b = blockIdx.y, tid = threadIdx.x;
     int L = lengths ? lengths[b] : T;
     L = L < 0 ? 0 : (L > T ? T : L);
@@ -392,7 +398,7 @@ __global__ __launch_bounds__(ENT_NT) void k_ent_part(const float *pos_marg, cons
         const int m = n * C, head = min((int)(-((uintptr_t)pm >> 2) & 3), m), body = (m - head) >> 2;  // (4-byte aligned at least)
         const float4 *pm4 = (const float4 *)(pm + head);
 #pragma unroll 4
-        for (int i = tid; i < body; i += ENT_NT) {
+        for (int i = tid; i < body; i += N) {
             const float4 v = pm4[i];
             a -= (xlogx(v.x) + xlogx(v.y)) + (xlogx(v.z) + xlogx(v.w));
         }
@@ -402,14 +408,14 @@ __global__ __launch_bounds__(ENT_NT) void k_ent_part(const float *pos_marg, cons
     }
     if (want_bdy) {
         const float *bd = bdy_post + (size_t)b * (T + 1) + u0;
-        for (int i = tid; i < n; i += ENT_NT) {
+        for (int i = tid; i < n; i += N) {
             s += (double)bd[i];
             e += xlogx(bd[i]);
         }
     }
-    a = ent_block_sum<ENT_NT>(a, red);
-    s = ent_block_sum<ENT_NT>(s, red);
-    e = ent_block_sum<ENT_NT>(e, red);
+    a = ent_block_sum<N>(a, red);
+    s = ent_block_sum<N>(s, red);
+    e = ent_block_sum<N>(e, red);
     if (tid == 0) {
         double *o = part + ((size_t)b * gridDim.x + blockIdx.x) * 3;
         o[0] = a;

@@ -1234,7 +1234,9 @@ int semicrf_entropies_ws(const float *pos_marg, const float *bdy_post, const int
     (void)semicrf_entropies_workspace_bytes(B, T, &need);
     if (!workspace || ((uintptr_t)workspace & 255) != 0 || workspace_bytes < need) return SEMICRF_EWORKSPACE;
     const int npart = (int)(((long long)T + ENT_TOK - 1) / ENT_TOK);
-    hipLaunchKernelGGL(k_ent_part, dim3(npart, B), dim3(ENT_NT), 0, (hipStream_t)stream, pos_marg, bdy_post, lengths, T, C,
+    const int threads = ent_threads(C);
+    const auto part = threads == 128 ? k_ent_part<128> : (threads == 256 ? k_ent_part<256> : k_ent_part<512>);
+    hipLaunchKernelGGL(part, dim3(npart, B), dim3(threads), 0, (hipStream_t)stream, pos_marg, bdy_post, lengths, T, C,
                        h_pos ? 1 : 0, h_bdy ? 1 : 0, (double *)workspace);
     hipLaunchKernelGGL(k_ent_fin, dim3(B), dim3(NT), 0, (hipStream_t)stream, (const double *)workspace, lengths, T, npart,
                        h_pos, h_bdy);

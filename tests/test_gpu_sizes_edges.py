@@ -27,6 +27,20 @@ def test_entropies_over_many_workgroups(T, C):
     np.testing.assert_allclose(h_bdy.cpu().numpy(), rb, rtol=1e-6, atol=1e-6)
 
 
+@pytest.mark.parametrize("C", [1, 2, 7, 8])
+@pytest.mark.parametrize("offset", [0, 1, 2, 3])
+def test_entropies_of_few_labels(C, offset):
+    """Every number of threads a workgroup can have, marginals at every place relative to the 16 bytes of a load."""
+    rng = np.random.default_rng(C)
+    pm, bd = rng.random((3, 1030, C), dtype=np.float32), rng.random((3, 1031), dtype=np.float32)
+    lengths = np.array([1030, 513, 0], dtype=np.int32)
+    flat = dev(np.concatenate([np.full(offset, np.nan, dtype=np.float32), pm.ravel()]))
+    h_pos, h_bdy = sb.semicrf_entropies(flat[offset:].view(3, 1030, C), dev(bd), dev(lengths))
+    rp, rb = oracle.entropies(pm, bd, lengths)
+    np.testing.assert_allclose(h_pos.cpu().numpy(), rp, rtol=1e-6, atol=1e-7)
+    np.testing.assert_allclose(h_bdy.cpu().numpy(), rb, rtol=1e-6, atol=1e-6)
+
+
 def test_entropy_terms_of_single_values():
     """One value per sequence, so that its -x log x shows: the ends of the float's range, both sides of the powers of two and of
     the square root of one half, 1, values that are no probabilities, and none at all."""
