@@ -47,13 +47,14 @@ CASES = [(2, 12, 1), (2, 14, 1), (2, 15, 1), (2, 30, 1), (2, 60, 0), (2, 140, 1)
          (4, 120, 0), (5, 60, 1), (8, 12, 0), (8, 100, 0), (8, 250, 0)]
 
 
+# Lengths with sums and headers from one launch (up to three chunks of 256 positions; with projections of two sequences: one), and from two.
 @pytest.mark.parametrize("C,s,center", CASES)
 def test_training_and_scoring(C, s, center):
-    for K, extra in ((8, 0), (8, sb.SEMICRF_SEQUENTIAL_SCAN), (8, sb.SEMICRF_MARGINALS_INTERVAL), (8, sb.SEMICRF_TWO_WAVE_SCAN),
-                     (150, 0)):
-        w = confident(10 * C + s, 2, 700, K, C, s)
+    for T, K, extra in ((700, 8, 0), (700, 8, sb.SEMICRF_SEQUENTIAL_SCAN), (700, 8, sb.SEMICRF_MARGINALS_INTERVAL),
+                        (700, 8, sb.SEMICRF_TWO_WAVE_SCAN), (700, 150, 0), (1100, 8, 0), (1100, 150, 0)):
+        w = confident(10 * C + s, 2, T, K, C, s)
         flags = (sb.SEMICRF_CENTER if center else 0) | extra
-        print(f"[case] C={C} s={s} center={center} K={K} flags={flags}", flush=True)
+        print(f"[case] C={C} s={s} center={center} T={T} K={K} flags={flags}", flush=True)
         x = (dev(w.emis), dev(w.lengths, np.int32), dev(w.trans), dev(w.dur))
         ws = sb.alloc_workspace(w.B, w.T, K, C, 0, sb.grad_workspace_kind(flags), DEV)
         out = sb.semicrf_fwd_bwd(*x, flags=flags, workspace=ws)
@@ -69,15 +70,15 @@ def test_training_and_scoring(C, s, center):
 
 @pytest.mark.parametrize("C,s,center", CASES)
 def test_boundary_terms(C, s, center):
-    K, B, T = 8, 2, 700
-    w = confident(10 * C + s, B, T, K, C, s)
-    rng = np.random.default_rng(s)
-    q = min(s, 60) / 8
-    ps, pe = (q * rng.uniform(-1, 1, (2, B, T, C))).astype(np.float32)
-    pis, pie = (q * rng.uniform(-1, 1, (2, C))).astype(np.float32)
-    r = oracle.fwd_bwd(w.emis, w.lengths, w.trans, w.dur, proj_start=ps, proj_end=pe, pi_start=pis, pi_end=pie,
-                       center=bool(center))
-    for extra in (0, sb.SEMICRF_MARGINALS_INTERVAL):
+    K, B = 8, 2
+    for T, extra in ((700, 0), (700, sb.SEMICRF_MARGINALS_INTERVAL), (250, 0)):
+        w = confident(10 * C + s, B, T, K, C, s)
+        rng = np.random.default_rng(s)
+        q = min(s, 60) / 8
+        ps, pe = (q * rng.uniform(-1, 1, (2, B, T, C))).astype(np.float32)
+        pis, pie = (q * rng.uniform(-1, 1, (2, C))).astype(np.float32)
+        r = oracle.fwd_bwd(w.emis, w.lengths, w.trans, w.dur, proj_start=ps, proj_end=pe, pi_start=pis, pi_end=pie,
+                           center=bool(center))
         out = sb.semicrf_fwd_bwd_boundary(dev(w.emis), dev(w.lengths, np.int32), dev(w.trans), dev(w.dur), None, dev(ps),
                                           dev(pe), dev(pis), dev(pie), flags=(sb.SEMICRF_CENTER if center else 0) | extra)
         assert np.abs(out["logz"].double().cpu().numpy() - r.logz).max() <= 1e-5 * np.abs(r.logz).max()

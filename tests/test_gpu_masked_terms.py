@@ -18,7 +18,8 @@ def dev(a, dtype=np.float32):
 
 @pytest.mark.parametrize("mask", [-np.inf, -1.0e4, np.finfo(np.float32).min])
 @pytest.mark.parametrize("T,K,C,extra", [(300, 12, 5, 0), (300, 12, 5, sb.SEMICRF_SEQUENTIAL_SCAN), (700, 20, 24, 0),
-                                         (500, 140, 6, 0), (200, 30, 64, 0), (300, 12, 5, sb.SEMICRF_MARGINALS_INTERVAL)])
+                                         (500, 140, 6, 0), (200, 30, 64, 0), (300, 12, 5, sb.SEMICRF_MARGINALS_INTERVAL),
+                                         (250, 12, 5, 0), (1000, 12, 5, 0)])
 def test_forbidden_starts_and_ends(T, K, C, extra, mask):
     rng = np.random.default_rng(T + C)
     w = synth.small_random(T + K, 2, T, K, C, ragged=False)

@@ -521,28 +521,30 @@ def test_low_memory_plan_more_tasks_than_row_buffers_genomic_shape():
 
 def test_sequence_report_range_flag_and_double_logz():
     """semicrf_seq_report: logZ in fp64 as the forward scan computed it, and the flag of sequences whose scores
-    exceed the range the scaled recurrences are built for (300 nats per position)."""
-    B, T, K, C = 3, 400, 6, 5
-    w = synth.small_random(91, B, T, K, C, ragged=False)
-    w.emis[1, 100, 2] = 5000.0            # one position that no scaling block can hold
-    emis, lengths, trans, dur = to_dev(w)
-    ws = sb.alloc_workspace(B, T, K, C, 0, 1, DEV)
-    out = sb.semicrf_fwd_bwd(emis, lengths, trans, dur, workspace=ws)
-    rng, lz64 = sb.semicrf_seq_report(ws, B, T, K, C, 0, 1)
-    torch.cuda.synchronize()
-    assert rng.cpu().numpy().tolist() == [0, 1, 0]
-    r = oracle.fwd_bwd(w.emis, w.lengths, w.trans, w.dur)
-    lz = lz64.cpu().numpy()
-    for b in (0, 2):
-        assert abs(lz[b] - r.logz[b]) <= 1e-9 * max(1.0, abs(r.logz[b]))
-        assert np.float32(lz[b]) == out[0].cpu().numpy()[b]
-    # forward-only calls leave the same fields
-    fws = sb.alloc_workspace(B, T, K, C, 0, 0, DEV)
-    sb.semicrf_logz_fwd(emis, lengths, trans, dur, workspace=fws)
-    rng2, lz2 = sb.semicrf_seq_report(fws, B, T, K, C, 0, 0)
-    torch.cuda.synchronize()
-    assert rng2.cpu().numpy().tolist() == [0, 1, 0]
-    assert np.array_equal(lz2.cpu().numpy()[[0, 2]], lz[[0, 2]])
+    exceed the range the scaled recurrences are built for (300 nats per position); short sequences, whose prefix stage is one
+    launch, and longer ones."""
+    for T in (400, 1100):
+        B, K, C = 3, 6, 5
+        w = synth.small_random(91, B, T, K, C, ragged=False)
+        w.emis[1, 100, 2] = 5000.0            # one position that no scaling block can hold
+        emis, lengths, trans, dur = to_dev(w)
+        ws = sb.alloc_workspace(B, T, K, C, 0, 1, DEV)
+        out = sb.semicrf_fwd_bwd(emis, lengths, trans, dur, workspace=ws)
+        rng, lz64 = sb.semicrf_seq_report(ws, B, T, K, C, 0, 1)
+        torch.cuda.synchronize()
+        assert rng.cpu().numpy().tolist() == [0, 1, 0]
+        r = oracle.fwd_bwd(w.emis, w.lengths, w.trans, w.dur)
+        lz = lz64.cpu().numpy()
+        for b in (0, 2):
+            assert abs(lz[b] - r.logz[b]) <= 1e-9 * max(1.0, abs(r.logz[b]))
+            assert np.float32(lz[b]) == out[0].cpu().numpy()[b]
+        # forward-only calls leave the same fields
+        fws = sb.alloc_workspace(B, T, K, C, 0, 0, DEV)
+        sb.semicrf_logz_fwd(emis, lengths, trans, dur, workspace=fws)
+        rng2, lz2 = sb.semicrf_seq_report(fws, B, T, K, C, 0, 0)
+        torch.cuda.synchronize()
+        assert rng2.cpu().numpy().tolist() == [0, 1, 0]
+        assert np.array_equal(lz2.cpu().numpy()[[0, 2]], lz[[0, 2]])
 
 
 @pytest.mark.parametrize("waves", ["one", "two"])

@@ -65,6 +65,23 @@ def test_bounds_add_up_the_maxima_of_a_chunk(T):
     assert np.abs(out["grad_emis"][0].double().cpu().numpy() - r.grad_emis[0]).max() <= 1e-4
 
 
+@pytest.mark.parametrize("T", [256, 511, 767, 768])
+def test_bounds_count_the_largest_table_entries(T):
+    """The largest duration bias and the largest transition are part of that bound, with tables from the same launch (T < 768) or from one
+    of their own: with 90 and 80 of them, an emission of 120 stays within the 300 nats (log K C = 3.4 more) and one of 130 does not."""
+    w = synth.small_random(T, 3, T, 6, 5, ragged=False)
+    w.dur[4, 1], w.trans[2, 3] = 90.0, 80.0
+    w.emis[0, T // 2, 2], w.emis[1, T // 2, 2] = 120.0, 130.0
+    for kind in (0, 1):
+        ws = sb.alloc_workspace(3, T, 6, 5, 0, kind, "cuda:0")
+        call = sb.semicrf_fwd_bwd if kind else sb.semicrf_logz_fwd
+        call(dev(w.emis), dev(w.lengths, np.int32), dev(w.trans), dev(w.dur), flags=0, workspace=ws)
+        exceeded, logz = [x.cpu().numpy() for x in sb.semicrf_seq_report(ws, 3, T, 6, 5, 0, kind)]
+        assert exceeded.tolist() == [0, 1, 0]
+        ref = oracle.logz(w.emis, w.lengths, w.trans, w.dur, center=False)
+        assert (np.abs(logz - ref)[[0, 2]] <= 1e-9 * np.abs(ref)[[0, 2]]).all()
+
+
 def outputs(x, T, K, C, terms, delta):
     """Everything that scores, gradients and decoding leave, with intervals of delta positions where a caller can say so."""
     B = x[0].shape[0]
