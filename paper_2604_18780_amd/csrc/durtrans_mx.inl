@@ -5,8 +5,8 @@
 // sixteen (task, position) pairs are the rows (forward) or columns (backward) of v_mfma_f64_16x16x4 products with the
 // table G[k][c'][c], so a table entry fetched from L2 once serves sixteen positions instead of four, and one
 // instruction does 1024 multiply-adds.  Scans of the genomic shape (K = 64, C = 24, 4 x 100 000), forward and backward: 4.9
-// and 6.3 ms with vector multiply-adds, four positions per table entry and one task per workgroup (durtrans.inl), 0.97 and
-// 1.19 ms so, the matrix pipes busy 43 and 48 % of the time.  The products wait for the table, so its entries are fetched as far
+// and 6.3 ms with vector multiply-adds, four positions per table entry and one task per workgroup (durtrans.inl), 1.00 and
+// 1.21 ms so, the matrix pipes busy 43 and 48 % of the clocks.  The products wait for the table, so its entries are fetched as far
 // ahead as registers allow: three tiles or groups for up to sixteen labels, else one (two, with 25 registers spilled: k_dx_fwd 1003 ->
 // 1031 us at the genomic shape).  One ahead against three: 1 x 1293, K = 380, C = 10 forward 627 -> 585, backward 447 -> 435 us;
 // 3 x 58043, K = 373, C = 6 forward 640 -> 603; 15 x 11034, K = 39, C = 4 392 -> 380, 341 -> 337.
@@ -429,8 +429,8 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tie
 // that the product's operand comes with immediate offsets; it slides downwards and is moved back every m positions.
 // Inside the block, one wave per task (0 .. 3) finishes the positions by row broadcasts, while the other (4 .. 7) forms what
 // durations 1 .. 3 add to the mass that starts at a position; it then writes the block's rows.
-// Bound by the product (17 of 28 thousand clocks per block at the genomic shape, where its matrix instructions take 12) and by what
-// lies between two products: the tables of those sums held in registers that only the chain waves need otherwise, the sums
+// Bound by the products (of 26 thousand clocks per block at the genomic shape their matrix instructions alone take 13) and by what
+// lies between two of them: the tables of those sums held in registers that only the chain waves need otherwise, the sums
 // formed beside the chains, and rows stored unconditionally took the launch from 1278 to 1190 us (K = 39, C = 6: 672 -> 650).
 // ---------------------------------------------------------------------------
 template <int MT, int SF2>

@@ -99,8 +99,8 @@ __device__ __forceinline__ void favour_body(const Params &p, const int blk)
 }
 inline int favour_blocks(const Params &p) { return p.warm_model && p.trans3 ? (p.C * p.C + WARM_PAIRS - 1) / WARM_PAIRS : 0; }
 
-// One workgroup per sequence, next to those of k_prefix; it should not take longer than they do (14 us at one or two chunks of
-// 24 labels; with 4 labels and two chunks it does: the launch takes 7.5 us without, 10.0 with it).  So
+// One workgroup per sequence, next to those of k_prefix; it should not take longer than they do (64 sequences of a
+// chunk of 24 labels: the launch takes 15.2 us without, 15.8 with it; with 4 labels and two chunks it does: 6.9 without, 10.8).  So
 // everything that comes from memory is requested before anything is done with it, and the transition matrix is worked on in
 // LDS by four threads per label.  lds: (PREP_NSEG + 1) C doubles, buf: 2 NT.
 // smp: place in LDS for the samples of the sequence's chunks, NT / 64 each, which sample() takes; without, p.contrast holds their sums.
