@@ -29,33 +29,30 @@ __device__ __forceinline__ double mg_yb(const Params &p, const int b, const int 
     return top + p.blocY[((size_t)b * p.N + j) * p.Delta + i];
 }
 
-// Duration-bias statistics.  Thread (ks, c): label c, durations ks*MG_KS + 1 .. ks*MG_KS + MG_KS, one
-// accumulator each.  Positions are taken in groups inside one scaling block: the group's q rows
-// and the v rows it can reach are staged in LDS, the latter converted to the group's frame with
+// Duration-bias statistics by vector multiply-adds: short intervals next to the durations, and scaling blocks shorter than a
+// tile of the matrix-core form below (J < 16, confident scores).  Thread (ks, c): label c, durations ks*MG_KS + 1 ..
+// ks*MG_KS + MG_KS, one accumulator each: labels c0 .. c0 + CL - 1, strips s0 .. s1 - 1.  Positions are taken in groups inside one
+// scaling block: the group's q rows and the v rows it can reach are staged in LDS, the latter converted to the group's frame with
 // all exponents combined before anything is formed; four positions share every LDS read.  The
 // absolute scales of all rows the interval can touch are fetched into LDS once, at the start.
-__global__ __launch_bounds__(1024) void k_mg_dur(Params p)
+__device__ __forceinline__ void mg_dur_vector(const Params &p, double *lds_raw, const int b, const int iv,
+                                              const int c0, const int CL, const int s0, const int s1)
 {
-    extern __shared__ double lds_raw[];
     const int tid = threadIdx.x, nth = blockDim.x;
     const int K = p.K, C = p.C, N = p.N, Delta = p.Delta;
-    const int b = blockIdx.x / N, iv = blockIdx.x % N;
     const SeqHdr h = p.hdr[b];
     const int L = h.L, J = h.J;
     const int lo = iv * Delta;
-    if (lo >= L) return;
-    if (!(p.spec_ok[b * 2] && p.spec_ok[b * 2 + 1])) return;  // the interval kernel takes this sequence
     const int hi = min(lo + Delta, L);
-    const int nsl = (K + MG_KS - 1) / MG_KS;
-    const bool active = tid < C * nsl;
-    const int c = tid % C, kA = (tid / C) * MG_KS;
-    const int VR = MG_TG + MG_KS * nsl + 3;
-    double *Qrow = lds_raw;            // [MG_TG][C]
-    // rows of CP = C|3 doubles: the threads of a wave read rows MG_KS apart (one per duration strip),
-    // and MG_KS*C is a multiple of the 32 banks (of 8 bytes) for every C that is a multiple of 4;
+    const bool active = tid < CL * (s1 - s0);
+    const int c = tid % CL, kA = (tid / CL) * MG_KS, kS = s0 * MG_KS;
+    const int VR = MG_TG + MG_KS * (s1 - s0) + 3;
+    double *Qrow = lds_raw;            // [MG_TG][CL]
+    // rows of CP = CL|3 doubles: the threads of a wave read rows MG_KS apart (one per duration strip),
+    // and MG_KS*CL is a multiple of the 32 banks (of 8 bytes) for every CL that is a multiple of 4;
     // with CP = 3 mod 4 the strips of a half-wave fall 24 banks apart instead of on top of each other
-    const int CP = C | 3;
-    double *Vp = Qrow + MG_TG * C;     // [VR][CP]
+    const int CP = CL | 3;
+    double *Vp = Qrow + MG_TG * CL;    // [VR][CP]
     double *qf = Vp + VR * CP;         // [MG_TG] per-row factors of the group
     double *vf = qf + MG_TG;           // [VR]
     int *ve = (int *)(vf + VR);        // [VR]
@@ -63,16 +60,16 @@ __global__ __launch_bounds__(1024) void k_mg_dur(Params p)
     double *yAs = vf + 2 * VR;         // [Delta]      absolute scale of the forward row lo + i
     double *yBs = yAs + Delta;         // [Delta + K]  absolute scale of the backward row lo + 1 + i
     const size_t row0 = (size_t)b * (p.T + 1);
-    const double2 *EI = p.EI + row0 * C;
-    const int *nb = p.nbase + row0 * C;
-    const double2 *frow = (const double2 *)p.aloc + ((size_t)b * N) * Delta * C;  // row of position t at t*C
-    const double2 *brow = (const double2 *)p.bloc + ((size_t)b * N) * Delta * C;  // (slots are consecutive)
+    const double2 *EI = p.EI + row0 * C + c0;
+    const int *nb = p.nbase + row0 * C + c0;
+    const double2 *frow = (const double2 *)p.aloc + ((size_t)b * N) * Delta * C + c0;  // row of position t at t*C
+    const double2 *brow = (const double2 *)p.bloc + ((size_t)b * N) * Delta * C + c0;  // (slots are consecutive)
     const double logZ = h.logZ;
     double acc[MG_KS];
 #pragma unroll
     for (int kk = 0; kk < MG_KS; ++kk) acc[kk] = 0.0;
-    for (int i = tid; i < hi - lo; i += blockDim.x) yAs[i] = mg_ya(p, b, iv, i);
-    for (int i = tid; i < hi - lo + K; i += blockDim.x) {
+    for (int i = tid; i < hi - lo; i += nth) yAs[i] = mg_ya(p, b, iv, i);
+    for (int i = kS + tid; i < min(hi - lo + K, hi - lo + kS + VR); i += nth) {
         const int s = lo + 1 + i;
         yBs[i] = s < L ? mg_yb(p, b, s / Delta, s % Delta, L) : 0.0;  // b_L = 1: scale 0
     }
@@ -84,14 +81,14 @@ __global__ __launch_bounds__(1024) void k_mg_dur(Params p)
         const double yA0 = yAs[tg0 - lo];
         // per row first (uniform over the labels): the scale factor of a q row; for a v row the
         // fractional factor, the integer exponent and the scaling block it was stored in
-        for (int r = tid; r < MG_TG + VR; r += blockDim.x) {
+        for (int r = tid; r < MG_TG + VR; r += nth) {
             if (r < MG_TG) {
                 qf[r] = r < ng ? exp2(yAs[tg0 + r - lo] - yA0) : 0.0;
             } else {
-                const int rr = r - MG_TG, s = tg0 + 1 + rr;
+                const int rr = r - MG_TG, s = tg0 + 1 + kS + rr;
                 double f = 0.0;
                 int e = 0, js = jt;
-                if (s <= L && rr < ng + K) {
+                if (s <= L && kS + rr < ng + K) {
                     const double lf = (yA0 + yBs[s - lo - 1]) - logZ * LOG2E;
                     const double fl = floor(lf);
                     f = exp2(lf - fl);
@@ -109,8 +106,8 @@ __global__ __launch_bounds__(1024) void k_mg_dur(Params p)
         // the loops; the loads of several rows per thread are issued together (rows beyond the
         // sequence are clamped, their factor is zero).
         {
-            const int rstep = nth / C;               // rows per sweep of the workgroup
-            const int o = tid % C, r0 = tid / C;     // threads with r0 >= rstep idle here
+            const int rstep = nth / CL;              // rows per sweep of the workgroup
+            const int o = tid % CL, r0 = tid / CL;     // threads with r0 >= rstep idle here
             if (r0 < rstep) {
                 {
                     constexpr int UQ = 4;  // the q rows of a thread are fetched together
@@ -122,7 +119,7 @@ __global__ __launch_bounds__(1024) void k_mg_dur(Params p)
 #pragma unroll
                         for (int u = 0; u < UQ; ++u) {
                             const int r = rb + u * rstep;
-                            if (r < MG_TG) Qrow[r * C + o] = qv[u] * qf[r];  // qf is zero beyond the group
+                            if (r < MG_TG) Qrow[r * CL + o] = qv[u] * qf[r];  // qf is zero beyond the group
                         }
                     }
                 }
@@ -134,7 +131,7 @@ __global__ __launch_bounds__(1024) void k_mg_dur(Params p)
 #pragma unroll
                     for (int u = 0; u < UV; ++u) {
                         const int r = min(rb + u * rstep, VR - 1);
-                        const int s = min(tg0 + 1 + r, L);
+                        const int s = min(tg0 + 1 + kS + r, L);
                         vs[u] = s == L ? EI[(size_t)L * C + o].x : brow[(size_t)s * C + o].y;
                         n1[u] = nb[(size_t)vj[r] * C + o];
                     }
@@ -154,7 +151,7 @@ __global__ __launch_bounds__(1024) void k_mg_dur(Params p)
             for (int i0 = 0; i0 < ng; i0 += 4) {
                 double ca[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) ca[i] = i0 + i < ng ? Qrow[(i0 + i) * C + c] : 0.0;
+                for (int i = 0; i < 4; ++i) ca[i] = i0 + i < ng ? Qrow[(i0 + i) * CL + c] : 0.0;
                 double w[MG_KS + 3];
 #pragma unroll
                 for (int q = 0; q < MG_KS + 3; ++q) w[q] = Vp[(i0 + kA + q) * CP + c];
@@ -171,9 +168,229 @@ __global__ __launch_bounds__(1024) void k_mg_dur(Params p)
         double *pD = p.partD + ((size_t)b * p.NP + iv) * K * C;
 #pragma unroll
         for (int kk = 0; kk < MG_KS; ++kk) {
-            const int k = kA + kk + 1;
-            if (k <= K) pD[(size_t)(k - 1) * C + c] = acc[kk] * p.W[(size_t)(k - 1) * C + c];
+            const int k = kS + kA + kk + 1;
+            if (k <= K) pD[(size_t)(k - 1) * C + c0 + c] = acc[kk] * p.W[(size_t)(k - 1) * C + c0 + c];
         }
+    }
+}
+
+// One workgroup per (sequence, interval).
+__global__ __launch_bounds__(1024) void k_mg_dur(Params p)
+{
+    extern __shared__ double lds_raw[];
+    const int b = blockIdx.x / p.N, iv = blockIdx.x % p.N;
+    if (iv * p.Delta >= p.hdr[b].L) return;
+    if (!(p.spec_ok[b * 2] && p.spec_ok[b * 2 + 1])) return;  // the interval kernel takes this sequence
+    mg_dur_vector(p, lds_raw, b, iv, 0, p.C, 0, (p.K + MG_KS - 1) / MG_KS);
+}
+
+// Duration-bias statistics on the matrix cores.  For one label,
+//   D[k] = sum_t q_t v_{t+k}      (each v brought into the frame of its t)
+// is a correlation.  With positions in groups of sixteen, t = 16 g + s, let
+//   P[s][x] = sum_g q_{16g+s} v_{16g+1+x},   so that   D[k' + 1] = sum_s P[s][s + k'].
+// P is a product with the groups as the inner dimension: v_mfma_f64_16x16x4 takes four groups (64 positions) of the
+// sixteen s against sixteen x, and K + 16 columns x replace K durations.  What is a frame's business happens on the way into
+// the instruction: a row v lies in LDS once, in a frame of its group w of sixteen rows (16 w + 1 .. 16 w + 16), and is brought
+// into the frame of group g by one power of two, 2^(E[w] - F[g]), per label and pair of groups, with all exponents
+// combined in whole numbers before anything is formed.  (A group lies in one scaling block, J >= 16; its row v may be the first of
+// the next block, brought down by the step the scan itself makes there.)
+// Wave (label of LW, range of kb * 16 durations, kb <= KB): kb + 1 tiles of P in its accumulators for the whole interval, one
+// workgroup of eight waves per (interval, group of labels, part of the durations), two of them on a compute unit.  Rows go
+// through LDS in a ring of RG groups, fetched a step of 64 positions ahead.  A product and the conversion of its operand element
+// take 84 clocks of a SIMD (64 the product alone; a power of two by integer adds or by a multiplication is no cheaper), which
+// makes 65 us of the 139 at K = 512, C = 8, T = 400 000 (vector form: 220); the rest is a workgroup's tables and first
+// rows, the steps' barriers, and the sums over s at the end.  KB = 16, one workgroup per compute unit: 151.
+// Sequences with J < 16 take the vector form in shares of the same labels and durations, 1.06 times as long a call as when
+// one workgroup did an interval (scores N(0, 20^2), 50 000 positions, K = 512, C = 8: 1802 -> 1919 us).
+constexpr int MGD_NT = 512;
+constexpr int MGD_J = 16;  // shortest scaling block of this form: a tile's positions
+constexpr int mgd_fill(int KB, int LW) { return ((8 / LW) * KB + 4 + 3) / 4 * 4; }  // groups of rows a step of 64 positions reads, whole steps
+constexpr int mgd_ring(int KB, int LW) { return mgd_fill(KB, LW) + 4 <= 16 ? 16 : (mgd_fill(KB, LW) + 4 <= 32 ? 32 : 64); }
+constexpr int MGD_QS = 72;                                                            // doubles of a label's positions of a step
+constexpr int mgd_steps(int Delta) { return (Delta + 15 + 15) / 64 + 1; }             // most steps of an interval
+constexpr size_t mgd_lds(int KB, int LW, int K, int Delta)
+{
+    return ((size_t)LW * mgd_ring(KB, LW) * 16 + 2 * LW * MGD_QS + Delta + K + 2 * ((size_t)K / Delta + 4)) * sizeof(double) +
+           ((size_t)LW * (4 * mgd_steps(Delta) + mgd_fill(KB, LW)) + (size_t)LW * 4 * mgd_steps(Delta) + Delta + K +
+            (size_t)LW * ((Delta + K) / MGD_J + 2)) * sizeof(int);
+}
+
+template <int KB, int LW>
+__global__ __launch_bounds__(MGD_NT, 4) void k_mg_dur_mx(Params p, int nlg, int parts, int kb)
+{
+    typedef double double4_t __attribute__((ext_vector_type(4)));
+    constexpr int RANGES = 8 / LW, RG = mgd_ring(KB, LW), FILL = mgd_fill(KB, LW), NST = FILL / 4, ROWS = 64;
+    extern __shared__ double lds_raw[];
+    const int tid = threadIdx.x;
+    const int K = p.K, C = p.C, N = p.N, Delta = p.Delta;
+    const int part = blockIdx.x % parts, lg = blockIdx.x / parts % nlg, task = blockIdx.x / (parts * nlg);
+    const int b = task / N, iv = task % N;
+    const SeqHdr h = p.hdr[b];
+    const int L = h.L, J = h.J;
+    const int lo = iv * Delta;
+    if (lo >= L) return;
+    if (!(p.spec_ok[b * 2] && p.spec_ok[b * 2 + 1])) return;  // the interval kernel takes this sequence
+    if (J < MGD_J) {
+        const int strips = (K + MG_KS - 1) / MG_KS;  // the same labels and about the same durations, by vector multiply-adds
+        mg_dur_vector(p, lds_raw, b, iv, lg * LW, min(LW, C - lg * LW), strips * part / parts, strips * (part + 1) / parts);
+        return;
+    }
+    const int hi = min(lo + Delta, L), smax = min(hi - 1 + K, L);  // rows v_s, lo < s <= smax
+    const int ljb = __builtin_ctz(J), blk0 = lo >> ljb, nblk = (smax >> ljb) - blk0 + 1;
+    const int g0 = lo >> 4, w0 = g0 + part * RANGES * kb;  // first group of positions, of rows
+    const int steps = (((hi + 15) >> 4) - g0 + 3) / 4, NG = 4 * (steps - 1) + FILL;
+    double *const V = lds_raw;                     // [LW][RG * 16]  rows, by group modulo RG
+    double *const Q = V + LW * RG * 16;            // [2][LW][MGD_QS] q of the step's positions
+    double *const rowF = Q + 2 * LW * MGD_QS;      // [Delta + K]    per row lo + 1 + i: factor in [1, 2) ...
+    double *const tabF = rowF + Delta + K;         // per interval the rows reach into, and one for row L: the same at its upper end
+    double *const tabE = tabF + K / Delta + 4;
+    int *const rowE = (int *)(tabE + K / Delta + 4);  // [Delta + K] ... and exponent of its scale
+    int *const Es = rowE + Delta + K;              // [NG][LW]       exponent of a group of rows w0 + i
+    int *const Fs = Es + LW * NG;                  // [4 steps][LW]  exponent of a group of positions g0 + i
+    int *const nbl = Fs + LW * 4 * steps;          // [nblk][LW]     block exponents
+    const size_t row0 = (size_t)b * (p.T + 1);
+    const int *nb = p.nbase + row0 * C;
+    const char *const frow = (const char *)((const double2 *)p.aloc + ((size_t)b * N + iv) * Delta * C);  // row of position lo + i at i*C
+    const char *const brow = (const char *)((const double2 *)p.bloc + ((size_t)b * N + iv) * Delta * C);  // (slots are consecutive)
+    const double *frowY = p.alocY + ((size_t)b * N + iv) * Delta, *browY = p.blocY + ((size_t)b * N + iv) * Delta;
+
+    // ---- staging: thread (row of 64, label of LW)
+    const int sl = tid % LW, sr = tid / LW;
+    const int sc = min(lg * LW + sl, C - 1);
+    const double vL = p.EI[(row0 + L) * C + sc].x;  // v_L = ES_L, scale 0
+    const int slast = min(smax, L - 1) - lo;         // last stored row (relative to the interval, as all that follow)
+    auto row_of = [&](const int q) { return 16 * (w0 + 4 * q) + 1 + sr - lo; };
+    // (every thread, whatever it does with them: loads under a condition are waited for where the condition ends)
+    auto fetch = [&](const int q) {  // four groups of rows
+        const unsigned s = (unsigned)max(min(row_of(q), slast), 0);
+        return *(const double *)(brow + (s * (unsigned)C + (unsigned)sc) * 16u + 8u);
+    };
+    auto place = [&](const int q, const double v) {
+        if (sr >= ROWS) return;
+        const int s = row_of(q), i = max(min(s, smax - lo), 1), g = 4 * q + (sr >> 4);
+        const int e = rowE[i - 1] + nbl[(((i + lo) >> ljb) - blk0) * LW + sl] - Es[g * LW + sl];
+        const double x = fmin(ldexp((i + lo == L ? vL : v) * rowF[i - 1], e), DBL_MAX);
+        V[(sl * RG + (g & (RG - 1))) * 16 + (sr & 15)] = s == i ? x : 0.0;  // (rows before lo + 1 and after smax: none)
+    };
+    auto fetch_q = [&](const int k) {
+        const unsigned t = (unsigned)max(min(16 * (g0 + 4 * k) + sr, hi - 1) - lo, 0);
+        return *(const double *)(frow + (t * (unsigned)C + (unsigned)sc) * 16u + 8u);
+    };
+    auto place_q = [&](const int k, const double q) {
+        const int t = 16 * (g0 + 4 * k) + sr;
+        if (sr < ROWS) Q[((k & 1) * LW + sl) * MGD_QS + sr] = t >= lo && t < hi ? q : 0.0;
+    };
+    double first[NST];
+#pragma unroll
+    for (int q = 0; q < NST; ++q) first[q] = fetch(q);
+    const double fq = fetch_q(0);
+
+    // What 2^(Y_alpha(lo) + Y_beta(s)) / Z takes apart into: stored scales are whole numbers relative to their interval's upper
+    // end.  All that the tables are made of is requested before the first of it is waited for.
+    constexpr int RB = 3;  // rows per thread and sweep
+    double rowY[RB];
+    auto fetch_scales = [&](const int i0) {
+#pragma unroll
+        for (int u = 0; u < RB; ++u) rowY[u] = browY[min(i0 + u * MGD_NT + tid + 1, slast)];
+    };
+    fetch_scales(0);
+    auto block_exponent = [&](const int i) { return nb[(size_t)(blk0 + min(i / LW, nblk - 1)) * C + min(lg * LW + i % LW, C - 1)]; };
+    const int nb_first = block_exponent(tid);
+    auto first_position = [&](const int i) { return max(16 * (g0 + i / LW), lo); };  // of a group of positions
+    const double fy_first = frowY[min(first_position(tid), hi - 1) - lo];
+    const int nj = slast / Delta + 1;
+    for (int i = tid; i <= nj; i += MGD_NT) {
+        const double top = i == nj || iv + i == (L - 1) / Delta ? 0.0 : p.ckYB[(size_t)b * (N + 1) + iv + i + 1];
+        const double lf = (p.ckYA[(size_t)b * (N + 1) + iv] + top) - h.logZ * LOG2E, fl = floor(lf);
+        tabF[i] = exp2(lf - fl);
+        tabE[i] = fmin(fmax(fl, -100000.0), 100000.0);
+    }
+    for (int i = tid; i < nblk * LW; i += MGD_NT) nbl[i] = i == tid ? nb_first : block_exponent(i);
+    __syncthreads();
+    for (int i0 = 0; i0 < smax - lo; i0 += RB * MGD_NT) {
+        if (i0 > 0) fetch_scales(i0);
+#pragma unroll
+        for (int u = 0; u < RB; ++u) {
+            const int i = i0 + u * MGD_NT + tid, s = i + 1;  // row lo + s
+            if (i < smax - lo) {
+                const bool last = lo + s == L;
+                const int jj = last ? nj : (int)((unsigned)s / (unsigned)Delta);
+                rowF[i] = tabF[jj];
+                rowE[i] = (int)tabE[jj] + (last ? 0 : (int)rowY[u]);
+            }
+        }
+    }
+    for (int i = tid; i < LW * 4 * steps; i += MGD_NT) {
+        const int t = first_position(i);
+        if (t < hi) Fs[i] = nbl[((t >> ljb) - blk0) * LW + i % LW] - (int)(i == tid ? fy_first : frowY[t - lo]);
+        else Fs[i] = 0;
+    }
+    __syncthreads();
+    for (int i = tid; i < LW * NG; i += MGD_NT) {  // the frame of a group of rows: that of its first
+        const int f = max(16 * (w0 + i / LW) + 1, lo + 1);
+        Es[i] = f <= smax ? rowE[f - lo - 1] + nbl[((f >> ljb) - blk0) * LW + i % LW] : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NST; ++q) place(q, first[q]);
+    place_q(0, fq);
+    __syncthreads();
+
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, m = lane >> 4, n = lane & 15;
+    const int wl = wave % LW, wr = wave / LW, c = lg * LW + wl, kb0 = (part * RANGES + wr) * kb;
+    const bool mine = c < C && kb0 * 16 < K;
+    double4_t P[KB + 1];
+#pragma unroll
+    for (int j = 0; j <= KB; ++j) P[j] = double4_t{0.0, 0.0, 0.0, 0.0};
+    const char *const vbase = (const char *)(V + wl * RG * 16 + n);
+    const int *const ebase = Es + (m + wr * kb) * LW + wl, *const fbase = Fs + m * LW + wl;
+    for (int k = 0; k < steps; ++k) {
+        const double nv = fetch(k + NST), nq = fetch_q(k + 1);
+        const bool more = k + 1 < steps;
+        if (mine) {
+            const double a = Q[((k & 1) * LW + wl) * MGD_QS + lane];
+            const int F = fbase[4 * k * LW], rel = 4 * k + m + wr * kb;
+            // all operand elements are requested first; each is converted while the product before it runs
+            double raw[KB + 1];
+            int e[KB + 1];
+#pragma unroll
+            for (int j = 0; j <= KB; ++j) {
+                raw[j] = *(const double *)(vbase + ((rel * 128 + j * 128) & (RG * 128 - 1)));
+                e[j] = ebase[(4 * k + j) * LW];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            double x = fmin(ldexp(raw[0], e[0] - F), DBL_MAX);
+#pragma unroll
+            for (int j = 0; j <= KB; ++j) {
+                const double xn = j < KB ? fmin(ldexp(raw[j + 1], e[j + 1] - F), DBL_MAX) : 0.0;
+                __builtin_amdgcn_sched_barrier(0);
+                if (j <= kb) P[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, x, P[j], 0, 0, 0);
+                x = xn;
+            }
+        }
+        if (more) {
+            place(k + NST, nv);
+            place_q(k + 1, nq);
+            __syncthreads();
+        }
+    }
+    if (!mine) return;
+    // ---- D[k' + 1] = sum_s P[s][s + k']: tile element (s = 4 v + m, n) belongs to k' = 16 j + n - s
+    double *pD = p.partD + ((size_t)b * p.NP + iv) * K * C;
+    double w[KB];
+#pragma unroll
+    for (int j = 0; j < KB; ++j) w[j] = p.W[(size_t)min((kb0 + j) * 16 + n, K - 1) * C + c];
+#pragma unroll
+    for (int j = 0; j < KB; ++j) {
+        double sum = 0.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int s = 4 * v + m;
+            sum += __shfl(n >= s ? P[j][v] : P[j + 1][v], (lane & 48) | ((n + s) & 15));
+        }
+        sum = add_across_32(add_across_16(sum));
+        const int kk = (kb0 + j) * 16 + n;
+        if (m == 0 && j < kb && kk < K) pD[(size_t)kk * C + c] = sum * w[j];
     }
 }
 

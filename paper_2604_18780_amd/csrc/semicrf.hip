@@ -406,6 +406,42 @@ int launch_mg(const Params &p, hipStream_t st)
     return SEMICRF_EUNSUPPORTED;
 }
 
+// Duration statistics of K >= 128.  On the matrix cores: groups of eight labels, or of four where there are no more, and as many
+// parts of the durations as it takes.  A workgroup of that form has tables to fill (some 10 us) before its products, which
+// take 1 us per 64 positions: where intervals are short next to the durations and there are more workgroups than the chip
+// holds, the vector form is faster up to 191 durations.  Whole calls, vector against matrix form, us:
+//   64 x 500 positions, K = 128, C = 20 188 -> 197; 16 x 1000, K = 128, C = 28 180 -> 184, C = 32 184 -> 188; 4 x 20000, K = 128, C = 32
+//   286 -> 290; 32 x 700, K = 160, C = 9 177 -> 179; 64 x 500, K = 192, C = 12 214 -> 210; 32 x 700, K = 256, C = 16 248 -> 240;
+//   2 x 3000, K = 128, C = 32 (376 workgroups) 163 -> 159; 4 x 50000, K = 150, C = 8 (intervals of 392) 315 -> 286
+bool mg_dur_vector_pays(const Params &p, int workgroups) { return p.K < 192 && p.Delta < 2 * p.K && workgroups > 512; }
+
+template <int KB, int LW>
+int launch_mg_dur_k(const Params &p, const Plan &pl, hipStream_t st)
+{
+    const int nlg = (p.C + LW - 1) / LW, blocks = (p.K + 15) / 16, each = KB * (8 / LW), parts = (blocks + each - 1) / each;
+    const int waves = parts * (8 / LW), kb = (blocks + waves - 1) / waves;  // blocks of sixteen durations per wave
+    const size_t mx = mgd_lds(KB, LW, p.K, p.Delta), lds = mx > pl.lds_mg_dur ? mx : pl.lds_mg_dur;
+    if (lds > LDS_LIMIT || mg_dur_vector_pays(p, p.B * p.N * nlg * parts)) {
+        const int mg_nsl = (p.K + MG_KS - 1) / MG_KS;
+        int ntd = (p.C * mg_nsl + 63) / 64 * 64;
+        if (ntd < NT) ntd = NT;  // the extra threads help staging the rows
+        if (hipFuncSetAttribute((const void *)k_mg_dur, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds_mg_dur) !=
+            hipSuccess)
+            return SEMICRF_ELAUNCH;
+        hipLaunchKernelGGL(k_mg_dur, dim3(p.B * p.N), dim3(ntd), pl.lds_mg_dur, st, p);
+        return SEMICRF_OK;
+    }
+    if (hipFuncSetAttribute((const void *)k_mg_dur_mx<KB, LW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return SEMICRF_ELAUNCH;
+    hipLaunchKernelGGL((k_mg_dur_mx<KB, LW>), dim3(p.B * p.N * nlg * parts), dim3(MGD_NT), lds, st, p, nlg, parts, kb);
+    return SEMICRF_OK;
+}
+
+int launch_mg_dur(const Params &p, const Plan &pl, hipStream_t st)
+{
+    return p.C <= 4 ? launch_mg_dur_k<8, 4>(p, pl, st) : launch_mg_dur_k<8, 8>(p, pl, st);
+}
+
 // Sizes for which the first warm-up comes from the model, unless the caller has named one.
 bool warm_from_model(const Params &p, const Plan &pl)
 {
@@ -480,16 +516,11 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
         rc = launch_mg(p, st);
         if (rc != SEMICRF_OK) return rc;
     } else if (p.marg) {
-        const int mg_nsl = (p.K + MG_KS - 1) / MG_KS;
-        if (hipFuncSetAttribute((const void *)k_mg_dur, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)pl.lds_mg_dur) != hipSuccess)
-            return SEMICRF_ELAUNCH;
-        int ntd = (p.C * mg_nsl + 63) / 64 * 64;
-        if (ntd < NT) ntd = NT;  // the extra threads help staging the rows
+        rc = launch_mg_dur(p, pl, st);
+        if (rc != SEMICRF_OK) return rc;
         if (hipFuncSetAttribute((const void *)k_mg_te, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)pl.lds_mg_te) != hipSuccess)
             return SEMICRF_ELAUNCH;
-        hipLaunchKernelGGL(k_mg_dur, dim3(p.B * p.N), dim3(ntd), pl.lds_mg_dur, st, p);
         hipLaunchKernelGGL(k_mg_te, dim3(p.B * p.N), dim3(NT), pl.lds_mg_te, st, p);
     }
     // the interval kernels: everything without the stored rows, else only what those kernels left
