@@ -171,12 +171,12 @@ int make_plan(int B, int T, int K, int C, int ckpt_interval, int want_grad, Plan
     const int mg_nsl = (K + MG_KS - 1) / MG_KS;
     const size_t mg_vr = (size_t)MG_TG + (size_t)MG_KS * mg_nsl + 3;
     pl->lds_mg_dur = (MG_TG * c + mg_vr * (c | 3) + MG_TG + 2 * mg_vr + 2 * (size_t)pl->Delta + k) * sizeof(double);
-    pl->lds_mg_te = ((size_t)3 * MG_TE * c + pl->Delta) * sizeof(double);
+    const size_t longest = ((size_t)3 * 64 * c + pl->Delta) * sizeof(double);  // (an interval's scales next to 64 rows: bounds its length)
     const int mg_gw = 64 / pow2_ge8(C > 64 ? 64 : C);
     const int mg_per_simd = mg_waves_per_simd(C, (K + mg_gw - 1) / mg_gw);  // of the one-wave kernel (K < 128)
     const bool rows = !lowmem && (kind == 3 || kind == 1);
     pl->rows = rows && spec_applies(K, C) && ntask <= (size_t)pl->nslot && c * mg_nsl <= 1024 &&
-               pl->lds_mg_dur <= LDS_LIMIT && pl->lds_mg_te <= LDS_LIMIT;
+               pl->lds_mg_dur <= LDS_LIMIT && longest <= LDS_LIMIT;
     const size_t gr = pl->rows ? 1 : 0;
     sz[PL_BLOC] = gr * (size_t)pl->nslot * pl->Delta * 2 * c * 8;
     sz[PL_BLOCY] = gr * (size_t)pl->nslot * pl->Delta * 8;

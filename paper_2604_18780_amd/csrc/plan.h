@@ -16,7 +16,7 @@ struct Plan {
     int rows;  // the backward scan tasks have row storage (stored-row marginals possible)
     bool warm_room;  // there is room for what the choice of the warm-up leaves (in a gradient call in the place of the partial sums)
     int msplit;  // parts an interval is cut into by the one-wave stored-row marginals (per-part partial sums)
-    size_t lds_mg_dur, lds_mg_te;
+    size_t lds_mg_dur;
     size_t lds_scan, lds_interval;
     size_t total;
     size_t off[32];

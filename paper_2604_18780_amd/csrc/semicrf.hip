@@ -518,10 +518,10 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
     } else if (p.marg) {
         rc = launch_mg_dur(p, pl, st);
         if (rc != SEMICRF_OK) return rc;
-        if (hipFuncSetAttribute((const void *)k_mg_te, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)pl.lds_mg_te) != hipSuccess)
-            return SEMICRF_ELAUNCH;
-        hipLaunchKernelGGL(k_mg_te, dim3(p.B * p.N), dim3(NT), pl.lds_mg_te, st, p);
+        const size_t lds = mgt_lds(p.C);
+        if (p.C <= 8) hipLaunchKernelGGL((k_mg_te<8, 1>), dim3(p.B * p.N), dim3(64 * MGT_W), lds, st, p);
+        else if (p.C <= 16) hipLaunchKernelGGL((k_mg_te<16, 1>), dim3(p.B * p.N), dim3(64 * MGT_W), lds, st, p);
+        else hipLaunchKernelGGL((k_mg_te<16, 2>), dim3(p.B * p.N), dim3(64 * MGT_W), lds, st, p);
     }
     // the interval kernels: everything without the stored rows, else only what those kernels left
     rc = launch_interval(p, pl, st);
