@@ -634,6 +634,30 @@ __global__ __launch_bounds__(NT) void k_prefix(Params p)
             }
             continue;
         }
+        if (BTERMS && J >= PREP_SEG && t0 + PREP_SEG <= L && !p.cum) {
+            // The same for a segment inside the sequence: all projections are requested at once and nothing is decided per
+            // position (genomic analysis 670 -> 655 us with the rows below stored as they are now).
+            if ((t0 & Jm) == 0) p.nbase[(row0 + (size_t)(t0 >> logJ)) * C + c] = (int)n;
+            const size_t o = f0 + (size_t)t0 * C + c;
+            float fs[PREP_SEG], fe[PREP_SEG];
+#pragma unroll
+            for (int i = 0; i < PREP_SEG; ++i) {
+                fs[i] = p.proj_start ? p.proj_start[o + (unsigned)(i * C)] : 0.f;
+                fe[i] = p.proj_end ? p.proj_end[t0 + i >= 1 ? o + (unsigned)(i * C) - C : o] : 0.f;
+            }
+#pragma unroll
+            for (int i = 0; i < PREP_SEG; ++i) {
+                double ps = (double)fs[i], pe = (double)fe[i];
+                if (i == 0 && t0 == 0) {
+                    pe = 0.0;
+                    if (p.pi_start) ps += (double)p.pi_start[c];
+                }
+                E[(unsigned)(i * C)] = p.logpair ? make_double2(S + pe, ps - S)
+                                                 : make_double2(exp_any((S - base) + pe), exp_any(ps - (S - base)));
+                S += f[i] - nu;
+            }
+            continue;
+        }
         // boundary terms: start score of token t, end score of token t-1
         double xs[PREP_SEG], xe[PREP_SEG];
         if (BTERMS) {
