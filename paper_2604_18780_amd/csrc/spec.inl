@@ -180,6 +180,7 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
     const bool writer = cval && g == 0;
     double2 *aloc = (double2 *)(BWD ? p.bloc : p.aloc) + ((size_t)b * N + j) * Delta * C;
     double *alocY = (BWD ? p.blocY : p.alocY) + ((size_t)b * N + j) * Delta;
+    const unsigned lane_row = writer ? (unsigned)c * 16u : ROW_NOWHERE;
     double Yrec = 0.0;  // scale at the chunk's first position (forward) / upper end (backward)
     auto start_rows = [&]() {
         Yrec = Y;
@@ -246,18 +247,13 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
         // ---- the positions one after the other
         double qn[MB];
         // A whole block (nearly all are): nothing is decided per position.  The rows of a block that lies in the
-        // chunk go out through one pointer per lane (the lanes that own no label store to a sink), its scale once
+        // chunk go out through a buffer (the lanes that own no label store nothing), its scale once
         // for the MB positions.  A forward block that reaches the chunk's end takes the general path (the end
         // position itself has no row).
         if (__builtin_expect(nb == MB && (BWD || !inchunk || t + MB < hi), 1)) {
-            double2 *rowp = (double2 *)p.sink + lane;
-            int rstep = 0;
+            const int p0 = BWD ? t - 1 - lo : t + 1 - lo;  // slot row of the block's first position
+            const RowStore rows(aloc + (ptrdiff_t)(inchunk ? (BWD ? p0 - (MB - 1) : p0) : 0) * C, inchunk ? MB * C * 16 : 0);
             if (inchunk) {
-                const int p0 = BWD ? t - 1 - lo : t + 1 - lo;  // slot row of the block's first position
-                if (writer) {
-                    rowp = aloc + (size_t)p0 * C + c;
-                    rstep = BWD ? -C : C;
-                }
                 alocY[BWD ? p0 - (lane & (MB - 1)) : p0 + (lane & (MB - 1))] = Y - Yrec;  // every lane, the same value
             }
 #pragma unroll
@@ -272,7 +268,7 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
                 qn[i] = q;
                 r += BWD ? -1 : 1;
                 if (writer) ring[r * RS + c] = q;
-                if (keep) store_row(rowp + i * rstep, y, q);
+                if (keep) rows.pair(lane_row, (BWD ? MB - 1 - i : i) * C * 16, y, q);
             }
         } else {
     #pragma unroll

@@ -155,6 +155,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
         const bool writer = cval && g == 0;
         double2 *aloc = (double2 *)(BWD ? p.bloc : p.aloc) + ((size_t)b * N + j) * Delta * C;
         double *alocY = (BWD ? p.blocY : p.alocY) + ((size_t)b * N + j) * Delta;
+        const unsigned lane_row = writer ? (unsigned)c * 16u : ROW_NOWHERE;
         double Yrec = 0.0;  // scale at the chunk's first position (forward) / upper end (backward)
         auto start_rows = [&]() {
             Yrec = Y;
@@ -214,30 +215,43 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
                 lds_barrier();   // the exponent is published (and the window entries above were read before it is rescaled)
             }
             double qn[MB];
+            auto position = [&](const int i) {
+                double x = far[i];
 #pragma unroll
-            for (int i = 0; i < MB; ++i) {
-                if (i < nb) {
-                    double x = far[i];
+                for (int m = 0; m < MB; ++m) x = fma(wn[i + m], qp[m], x);        // duration i + 1 + m
 #pragma unroll
-                    for (int m = 0; m < MB; ++m) x = fma(wn[i + m], qp[m], x);        // duration i + 1 + m
+                for (int jn = 0; jn < i; ++jn) x = fma(wn[i - 1 - jn], qn[jn], x);  // inside the block
+                const double y = x * (BWD ? e[i].y : e[i].x);
+                ylast = y;
+                const double z = R::product(y, Ereg);
+                qn[i] = z * (BWD ? e[i].x : e[i].y);
+                if (writer) ring[(BWD ? r - 1 - i : r + 1 + i) * RS + c] = qn[i];
+            };
+            const int p0 = BWD ? t - 1 - lo : t + 1 - lo;  // slot row of the block's first position
+            // Whole blocks on a path of their own, as in the one-wave task, where tasks are long next to the code (deep windows; K = 512,
+            // C = 8 scans 295 -> 264 us): for short ones it is only more to load (64 x 256, K = 16, C = 24 91.3 -> 92.7 us a call).
+            constexpr bool WHOLE = NKW == 64;
+            if (WHOLE && __builtin_expect(nb == MB && (BWD || !inchunk || t + MB < hi), 1)) {
+                const RowStore rows(aloc + (ptrdiff_t)(inchunk ? (BWD ? p0 - (MB - 1) : p0) : 0) * C, inchunk ? MB * C * 16 : 0);
+                if (inchunk) alocY[BWD ? p0 - (lane & (MB - 1)) : p0 + (lane & (MB - 1))] = Y - Yrec;
 #pragma unroll
-                    for (int jn = 0; jn < i; ++jn) x = fma(wn[i - 1 - jn], qn[jn], x);  // inside the block
-                    const double y = x * (BWD ? e[i].y : e[i].x);
-                    ylast = y;
-                    const double z = R::product(y, Ereg);
-                    const double q = z * (BWD ? e[i].x : e[i].y);
-                    qn[i] = q;
-                    if (writer) ring[(BWD ? r - 1 - i : r + 1 + i) * RS + c] = q;
-                    if (!BWD && inchunk && t + 1 + i < hi) {
-                        if (writer) store_row(aloc + (size_t)(t + 1 + i - lo) * C + c, y, q);
-                        if (lane == 0) alocY[t + 1 + i - lo] = Y - Yrec;
+                for (int i = 0; i < MB; ++i) {
+                    position(i);
+                    if (keep) rows.pair(lane_row, (BWD ? MB - 1 - i : i) * C * 16, ylast, qn[i]);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < MB; ++i) {
+                    if (i < nb) {
+                        position(i);
+                        if (inchunk && (BWD || t + 1 + i < hi)) {
+                            const int at = BWD ? p0 - i : p0 + i;
+                            if (writer) store_row(aloc + (size_t)at * C + c, ylast, qn[i]);
+                            if (lane == 0) alocY[at] = Y - Yrec;
+                        }
+                    } else {
+                        qn[i] = 0.0;
                     }
-                    if (BWD && inchunk) {  // position t - 1 - i of [lo, hi)
-                        if (writer) store_row(aloc + (size_t)(t - 1 - i - lo) * C + c, y, q);
-                        if (lane == 0) alocY[t - 1 - i - lo] = Y - Yrec;
-                    }
-                } else {
-                    qn[i] = 0.0;
                 }
             }
             lds_barrier();   // end of the block: the new window rows and the helper's sums for the next block are there

@@ -77,6 +77,7 @@ __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const
     const bool cval = c < C;
     const int cc = cval ? c : 0;
     const bool writer = cval && g == 0;
+    const unsigned lane_row = writer ? (unsigned)c * 8u : ROW_NOWHERE;
     const int L = p.hdr[b].L;
     const int lo = WHOLE ? 0 : chunk * p.Delta;
     if (!WHOLE && lo >= L && !(lo == 0 && L == 0)) return;
@@ -182,12 +183,7 @@ __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const
                 for (int i = 0; i < MB; ++i) acc[i] = fmax(acc[i], group_max<G::CTP>(far[i]));
             }
         }
-        double *rowp = p.sink + lane;  // where there is no row to keep (or a lane owns no label)
-        int rstep = 0;
-        if (keep && writer) {
-            rowp = VV + (size_t)(t + 1) * C + c;
-            rstep = C;
-        }
+        const RowStore rows(VV + (size_t)(t + 1) * C, keep ? MB * C * 8 : 0);
         double qn[MB];
         auto position = [&](const int i) {
             double x = acc[i];
@@ -199,7 +195,7 @@ __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const
             qn[i] = q;
             ++r;
             if (writer) ring[r * RS + c] = q;
-            __builtin_nontemporal_store(y, rowp + i * rstep);
+            rows.one(lane_row, i * C * 8, y);
         };
         if (__builtin_expect(nb == MB, 1)) {  // a whole block: nothing is decided per position
 #pragma unroll
