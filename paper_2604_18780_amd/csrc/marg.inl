@@ -394,8 +394,9 @@ __global__ __launch_bounds__(MGD_NT, 4) void k_mg_dur_mx(Params p, int nlg, int 
     }
 }
 
-// Transition statistics and the running emission sums (K >= 128, so C <= 32).  A workgroup of eight waves takes an interval from
-// its upper end downwards (the emission sums are suffix sums), 8 * S positions at a time, S of them to a wave.  A wave takes
+// Transition statistics and the running emission sums (K >= 128, so C <= 32).  A workgroup of W waves (eight; four with more than 16
+// labels, whose rows take more registers) takes an interval from its upper end downwards (the emission sums are suffix sums), W * S
+// positions at a time, S of them to a wave.  A wave takes
 // 64 / LB positions by LB labels at once (LB = 8 up to eight labels, else 16, twice with more than 16), the rows of the next ones
 // requested a step ahead; every lane forms a_t kappa, p_t and (out - in) kappa of its position and label, which are
 // the operands of the transition product as they stand (v_mfma_f64_16x16x4, inner index the position; with eight
@@ -404,13 +405,12 @@ __global__ __launch_bounds__(MGD_NT, 4) void k_mg_dur_mx(Params p, int nlg, int 
 // They go through LDS, where the waves above add theirs, and out in rows.  Bound by memory: 48 bytes read and 4 written per
 // position and label.  K = 512, C = 8, T = 400 000:
 // 33 us (4.9 TB/s), against 69 with the rows staged in LDS for a thread per pair of labels and one per label for the sums.
-constexpr int MGT_W = 8;  // waves
 constexpr int mgt_seg(int C) { return C <= 8 ? 64 : (C <= 16 ? 32 : 16); }  // S
 // (at most 46 KB: within the default dynamic LDS)
-constexpr size_t mgt_lds(int C) { return ((size_t)MGT_W * mgt_seg(C) * C + (2 * MGT_W + 2) * (size_t)C + (size_t)C * C) * sizeof(double); }
+constexpr size_t mgt_lds(int W, int C) { return ((size_t)W * mgt_seg(C) * C + (2 * W + 2) * (size_t)C + (size_t)C * C) * sizeof(double); }
 
-template <int LB, int TL>
-__global__ __launch_bounds__(64 * MGT_W, TL == 2 ? 2 : 4) void k_mg_te(Params p)
+template <int LB, int TL, int W>
+__global__ __launch_bounds__(64 * W, TL == 2 ? 3 : 4) void k_mg_te(Params p)
 {
     typedef double double4_t __attribute__((ext_vector_type(4)));
     constexpr int PP = 64 / LB;  // positions of a step
@@ -424,11 +424,11 @@ __global__ __launch_bounds__(64 * MGT_W, TL == 2 ? 2 : 4) void k_mg_te(Params p)
     if (lo >= L) return;
     if (!(p.spec_ok[b * 2] && p.spec_ok[b * 2 + 1])) return;
     const int hi = min(lo + Delta, L);
-    const int S = mgt_seg(C), CH = MGT_W * S;
+    const int S = mgt_seg(C), CH = W * S;
     double *const Rl = lds_raw;              // [CH][C]  running sums of a chunk, each wave's from its own upper end
     double *const seg = Rl + (size_t)CH * C;  // [W][C]   what a wave's positions add up to
-    double *const ssum = seg + MGT_W * C;    // [W][C]   sum of its running sums
-    double *const top = ssum + MGT_W * C;    // [C]      what the chunks above add up to
+    double *const ssum = seg + W * C;    // [W][C]   sum of its running sums
+    double *const top = ssum + W * C;    // [C]      what the chunks above add up to
     double *const tsum = top + C;            // [C]      sum of the running sums so far
     double *const trs = tsum + C;            // [C][C]
     const size_t row0 = (size_t)b * (p.T + 1), slot = (size_t)b * N + iv;
@@ -447,7 +447,7 @@ __global__ __launch_bounds__(64 * MGT_W, TL == 2 ? 2 : 4) void k_mg_te(Params p)
 #pragma unroll
     for (int u = 0; u < TL; ++u)
 #pragma unroll
-        for (int w = 0; w < TL; ++w) acc[u][w] = double4_t{0.0, 0.0, 0.0, 0.0};
+        for (int x = 0; x < TL; ++x) acc[u][x] = double4_t{0.0, 0.0, 0.0, 0.0};
     if (tid < 2 * C) top[tid] = 0.0;  // and tsum
     struct Rows {
         double2 a[TL], v[TL], e[TL];
@@ -498,8 +498,8 @@ __global__ __launch_bounds__(64 * MGT_W, TL == 2 ? 2 : 4) void k_mg_te(Params p)
 #pragma unroll
             for (int u = 0; u < TL; ++u)
 #pragma unroll
-                for (int w = 0; w < TL; ++w)
-                    acc[u][w] = __builtin_amdgcn_mfma_f64_16x16x4f64(ak[u], r.v[w].x, acc[u][w], 0, 0, 0);
+                for (int x = 0; x < TL; ++x)
+                    acc[u][x] = __builtin_amdgcn_mfma_f64_16x16x4f64(ak[u], r.v[x].x, acc[u][x], 0, 0, 0);
             r = rn;
         }
 #pragma unroll
@@ -515,7 +515,7 @@ __global__ __launch_bounds__(64 * MGT_W, TL == 2 ? 2 : 4) void k_mg_te(Params p)
         const int m = min(tg1, CH);  // positions of the chunk
         if (tid < C) {
             double above = top[tid], sum = tsum[tid];
-            for (int w = 0; w < MGT_W; ++w) {
+            for (int w = 0; w < W; ++w) {
                 const double own = seg[w * C + tid];
                 sum += ssum[w * C + tid] + above * (double)max(min(m - w * S, S), 0);
                 seg[w * C + tid] = above;
@@ -527,14 +527,14 @@ __global__ __launch_bounds__(64 * MGT_W, TL == 2 ? 2 : 4) void k_mg_te(Params p)
         __syncthreads();
         // rows in ascending order of addresses: row x of the chunk is position tg1 - 1 - x
         float *const out = p.grad_emis + ((size_t)b * p.T + lo + tg1 - m) * C;
-        for (int i = tid; i < m * C; i += 64 * MGT_W) {
+        for (int i = tid; i < m * C; i += 64 * W) {
             const int x = m - 1 - i / C, c = i % C;
             out[i] = (float)(Rl[(size_t)x * C + c] + seg[x / S * C + c]);
         }
         __syncthreads();
     }
-    for (int i = tid; i < CC; i += 64 * MGT_W) trs[i] = 0.0;
-    for (int w = 0; w < MGT_W; ++w) {  // the waves' products, one after the other
+    for (int i = tid; i < CC; i += 64 * W) trs[i] = 0.0;
+    for (int w = 0; w < W; ++w) {  // the waves' products, one after the other
         __syncthreads();
         if (wave == w) {
 #pragma unroll
@@ -555,7 +555,7 @@ __global__ __launch_bounds__(64 * MGT_W, TL == 2 ? 2 : 4) void k_mg_te(Params p)
     }
     __syncthreads();
     double *pT = p.partTr + slot * CC;
-    for (int i = tid; i < CC; i += 64 * MGT_W) pT[i] = trs[i];
+    for (int i = tid; i < CC; i += 64 * W) pT[i] = trs[i];
     if (tid < C) {
         p.tot[slot * C + tid] = top[tid];
         p.sumR[slot * C + tid] = tsum[tid];
@@ -694,7 +694,7 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
     double2 aq[NPL], pv[NPL], e[NPL];  // this lane's label, positions pofs .. pofs+NPL-1 below tfrom
     double aA[TRN], bB[TRN];        // operand elements: position pj of the block, label pl of tile tr
     double ya, yb;                  // stored scales of the position just below tfrom (forward, backward)
-    int nd;                         // exponent step of this lane's label at the scaling-block boundary tfrom
+    int nhi, nlo;                   // exponents of this lane's label on both sides of the scaling-block boundary tfrom
     // Byte offsets from the (wave-uniform) starts of the interval's rows fit 32 bits: a slot has Delta*C < 2^27
     // pairs (the plan's limits), a sequence fewer than 2^31 position-label pairs (checked by the caller).
     const char *const arb = (const char *)arow, *const brb = (const char *)brow;
@@ -726,8 +726,11 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
         ya = arowY[i0];
         yb = browY[i0];
         const int jb = max(tfrom / J, 1);
-        const int hiE = nbc[(size_t)min(jb, L / J) * C], loE = nbc[(size_t)(jb - 1) * C];
-        nd = (tfrom / J >= 1 && (long)jb * J <= (long)L) ? hiE - loE : 0;
+        // (taken apart where it is used: a choice here puts the loads under a condition, and the wave waits for everything
+        // it has just requested, block after block; genomic shape: call 506 -> 484 us with the
+        // product above the stores)
+        nhi = nbc[(size_t)min(jb, L / J) * C];
+        nlo = nbc[(size_t)(jb - 1) * C];
     };
     // kappa(t,t) = exp((Y_alpha + Y_beta) ln2 - logZ) of the positions of a scaling block (they share both scales):
     // the stored scales are whole numbers, so it is one fixed factor in [1, 2) times a power of two
@@ -770,6 +773,7 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
         const int nb = min(min(t - ta, MB), ((t - 1) & Jm) + 1);
         if (__builtin_expect((t & Jm) == 0, 0)) {
             // the scan stepped into a new scaling block here: same shift of the live window, read off its scales
+            const int nd = t >= J ? nhi - nlo : 0;  // (t <= L: the block of position t is there)
             G::template rescale_live<true>(ring, g, c, cval, r, nd - (int)(yb - ybPrev));
             ybPrev = yb;
             kappa = kappa_of();
@@ -779,6 +783,19 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
         // newest are not among those the block reads)
         double coef[MB];
         const bool whole = nb == MB && t - MB >= 1;
+        {
+            // transition statistics on the matrix cores (before the block's stores, whose number differs: a wait for these
+            // operands behind them would be one for the stores); label rows beyond C are never stored, positions beyond a
+            // short block's end must count nothing
+            const bool on = whole || pj < nb;
+#pragma unroll
+            for (int tr = 0; tr < TRN; ++tr) {
+                const double a = on ? aA[tr] * kappa : 0.0;
+#pragma unroll
+                for (int tc = 0; tc < TRN; ++tc)
+                    accT[tr][tc] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bB[tc], accT[tr][tc], 0, 0, 0);
+            }
+        }
         if (SPLIT && whole) {
             // This lane's positions of the block: pofs + l, rows t-1-pofs-l.  A whole block (nearly all are) decides
             // nothing per position: every lane works on its label cc (the lanes of one label and half hold the same
@@ -891,18 +908,6 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
                 *dst = (float)R;
                 sR += on ? R : 0.0;
                 R += d;
-            }
-        }
-        {
-            // transition statistics on the matrix cores; label rows beyond C are never stored, positions beyond a
-            // short block's end must count nothing
-            const bool on = whole || pj < nb;
-#pragma unroll
-            for (int tr = 0; tr < TRN; ++tr) {
-                const double a = on ? aA[tr] * kappa : 0.0;
-#pragma unroll
-                for (int tc = 0; tc < TRN; ++tc)
-                    accT[tr][tc] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bB[tc], accT[tr][tc], 0, 0, 0);
             }
         }
         // ---- the next block's rows

@@ -518,10 +518,9 @@ int run(Params p, int ckpt_interval, void *workspace, size_t workspace_bytes, hi
     } else if (p.marg) {
         rc = launch_mg_dur(p, pl, st);
         if (rc != SEMICRF_OK) return rc;
-        const size_t lds = mgt_lds(p.C);
-        if (p.C <= 8) hipLaunchKernelGGL((k_mg_te<8, 1>), dim3(p.B * p.N), dim3(64 * MGT_W), lds, st, p);
-        else if (p.C <= 16) hipLaunchKernelGGL((k_mg_te<16, 1>), dim3(p.B * p.N), dim3(64 * MGT_W), lds, st, p);
-        else hipLaunchKernelGGL((k_mg_te<16, 2>), dim3(p.B * p.N), dim3(64 * MGT_W), lds, st, p);
+        if (p.C <= 8) hipLaunchKernelGGL((k_mg_te<8, 1, 8>), dim3(p.B * p.N), dim3(512), mgt_lds(8, p.C), st, p);
+        else if (p.C <= 16) hipLaunchKernelGGL((k_mg_te<16, 1, 8>), dim3(p.B * p.N), dim3(512), mgt_lds(8, p.C), st, p);
+        else hipLaunchKernelGGL((k_mg_te<16, 2, 4>), dim3(p.B * p.N), dim3(256), mgt_lds(4, p.C), st, p);
     }
     // the interval kernels: everything without the stored rows, else only what those kernels left
     rc = launch_interval(p, pl, st);

@@ -74,7 +74,8 @@ __device__ __forceinline__ bool spec_bad(const SpecJob &s, const int m) { return
 // One scan task of the chunk-parallel scan, one wave (window and time blocking as above).
 // repair: the task restarts from the state its neighbour in scan order REACHED at their common boundary (no
 // warm-up: exact if the neighbour's own start was).
-template <int CT, int NKW, bool BWD>
+// KEEP: a call with gradients, whose tasks store their rows (a forward-only one must not even issue the stores: 196 -> 207 us).
+template <int CT, int NKW, bool BWD, bool KEEP>
 __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, const int b, const int j,
                                           const int warm, const bool repair)
 {
@@ -176,7 +177,7 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
     // stage then skips its forward recompute for accepted sequences).
     // Backward tasks do the same with (p_t, v_t) and the scale relative to the chunk's upper end,
     // for t = hi-1 .. lo, when the marginals are formed from the stored rows of both scans.
-    const bool keep = BWD ? p.marg != 0 : p.fuse != 0;
+    const bool keep = KEEP && (BWD ? p.marg != 0 : p.fuse != 0);
     const bool writer = cval && g == 0;
     double2 *aloc = (double2 *)(BWD ? p.bloc : p.aloc) + ((size_t)b * N + j) * Delta * C;
     double *alocY = (BWD ? p.blocY : p.alocY) + ((size_t)b * N + j) * Delta;
@@ -248,14 +249,16 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
         double qn[MB];
         // A whole block (nearly all are): nothing is decided per position.  The rows of a block that lies in the
         // chunk go out through a buffer (the lanes that own no label store nothing), its scale once
-        // for the MB positions.  A forward block that reaches the chunk's end takes the general path (the end
+        // for the MB positions; a block that has none issues the same stores, of nothing, and either kind of block takes over the next
+        // block's rows itself: the compiler then knows how many stores lie behind those loads.  (Where it does not it waits for
+        // all stores of the block before the next one begins: genomic training 522 -> 506 us, 456 with no rows stored at all.)
+        // A forward block that reaches the chunk's end takes the general path (the end
         // position itself has no row).
         if (__builtin_expect(nb == MB && (BWD || !inchunk || t + MB < hi), 1)) {
             const int p0 = BWD ? t - 1 - lo : t + 1 - lo;  // slot row of the block's first position
             const RowStore rows(aloc + (ptrdiff_t)(inchunk ? (BWD ? p0 - (MB - 1) : p0) : 0) * C, inchunk ? MB * C * 16 : 0);
-            if (inchunk) {
-                alocY[BWD ? p0 - (lane & (MB - 1)) : p0 + (lane & (MB - 1))] = Y - Yrec;  // every lane, the same value
-            }
+            const RowStore scales(alocY + (inchunk ? (BWD ? p0 - (MB - 1) : p0) : 0), inchunk ? MB * 8 : 0);
+            if (KEEP) scales.one((unsigned)(lane & (MB - 1)) * 8u, 0, Y - Yrec);
 #pragma unroll
             for (int i = 0; i < MB; ++i) {
                 double x = acc[i];
@@ -268,8 +271,10 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
                 qn[i] = q;
                 r += BWD ? -1 : 1;
                 if (writer) ring[r * RS + c] = q;
-                if (keep) rows.pair(lane_row, (BWD ? MB - 1 - i : i) * C * 16, y, q);
+                if (KEEP) rows.pair(lane_row, (BWD ? MB - 1 - i : i) * C * 16, y, q);
             }
+#pragma unroll
+            for (int i = 0; i < MB; ++i) e[i] = en[i];
         } else {
     #pragma unroll
             for (int i = 0; i < MB; ++i) {
@@ -296,12 +301,11 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
                     qn[i] = 0.0;
                 }
             }
-
+#pragma unroll
+            for (int i = 0; i < MB; ++i) e[i] = en[i];
         }
         lds_wave_fence();  // the block's new rows are read by other lanes from here on
         t = tn;
-#pragma unroll
-        for (int i = 0; i < MB; ++i) e[i] = en[i];
         if (__builtin_expect(t == tstart, 0)) {
             record(t, ck1 + (size_t)istart * ckstride, ckY1 + istart);
             start_rows();
@@ -339,8 +343,9 @@ __global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, N
     }
     if (!RETRY || !job.mend) {
         const int w = RETRY ? job.warm : first_warm(p, b, warm);
-        if (dir == 0) spec_task<CT, NKW, false>(p, lds, b, j, w, false);
-        else spec_task<CT, NKW, true>(p, lds, b, j, w, false);
+        if (!both) spec_task<CT, NKW, false, false>(p, lds, b, j, w, false);
+        else if (dir == 0) spec_task<CT, NKW, false, true>(p, lds, b, j, w, false);
+        else spec_task<CT, NKW, true, true>(p, lds, b, j, w, false);
         return;
     }
     // A run of adjacent boundaries that disagreed is taken by ONE wave, the task that starts at the first of them
@@ -351,8 +356,8 @@ __global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, N
     if (!spec_bad(job, dir ? j + 1 : j) || spec_bad(job, dir ? j + 2 : j - 1)) return;
     int jj = j;
     for (int n = 0; n < SPEC_RUN_MAX; ++n) {
-        if (dir == 0) spec_task<CT, NKW, false>(p, lds, b, jj, 0, true);
-        else spec_task<CT, NKW, true>(p, lds, b, jj, 0, true);
+        if (dir == 0) spec_task<CT, NKW, false, true>(p, lds, b, jj, 0, true);
+        else spec_task<CT, NKW, true, true>(p, lds, b, jj, 0, true);
         const int nx = dir ? jj - 1 : jj + 1;              // the next task in scan order ...
         if (nx < 0 || nx >= job.nint || !spec_bad(job, dir ? nx + 1 : nx)) break;  // ... starts where this one ended
         __threadfence();  // the reached state this wave has just written is what it restarts from

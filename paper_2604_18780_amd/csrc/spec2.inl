@@ -28,7 +28,7 @@ __host__ __device__ constexpr size_t spec2_lds_doubles()
     return (size_t)(scan_kw(CT, NKW) + scan_slack(CT, NKW, true) + 2 * MB) * CT + (size_t)(CTP - CT) + (size_t)2 * MB * CTP + 2;
 }
 
-template <int CT, int NKW, bool BWD>
+template <int CT, int NKW, bool BWD, bool KEEP>
 __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, const int b, const int j,
                                            const int warm, const bool repair)
 {
@@ -151,7 +151,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
         double *ckY2 = (BWD ? p.ckYB2 : p.ckYA2) + (size_t)b * (N + 1);
         const int istart = BWD ? j + 1 : j, iend = BWD ? j : j + 1;
         // rows for the interval stage / the stored-row marginals, as in the one-wave task
-        const bool keep = BWD ? p.marg != 0 : p.fuse != 0;
+        const bool keep = KEEP && (BWD ? p.marg != 0 : p.fuse != 0);
         const bool writer = cval && g == 0;
         double2 *aloc = (double2 *)(BWD ? p.bloc : p.aloc) + ((size_t)b * N + j) * Delta * C;
         double *alocY = (BWD ? p.blocY : p.alocY) + ((size_t)b * N + j) * Delta;
@@ -228,17 +228,18 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
                 if (writer) ring[(BWD ? r - 1 - i : r + 1 + i) * RS + c] = qn[i];
             };
             const int p0 = BWD ? t - 1 - lo : t + 1 - lo;  // slot row of the block's first position
-            // Whole blocks on a path of their own, as in the one-wave task, where tasks are long next to the code (deep windows; K = 512,
-            // C = 8 scans 295 -> 264 us): for short ones it is only more to load (64 x 256, K = 16, C = 24 91.3 -> 92.7 us a call).
-            constexpr bool WHOLE = NKW == 64;
-            if (WHOLE && __builtin_expect(nb == MB && (BWD || !inchunk || t + MB < hi), 1)) {
+            if (__builtin_expect(nb == MB && (BWD || !inchunk || t + MB < hi), 1)) {
+                // a whole block: nothing is decided per position, and it always issues the same stores (as in the one-wave task)
                 const RowStore rows(aloc + (ptrdiff_t)(inchunk ? (BWD ? p0 - (MB - 1) : p0) : 0) * C, inchunk ? MB * C * 16 : 0);
-                if (inchunk) alocY[BWD ? p0 - (lane & (MB - 1)) : p0 + (lane & (MB - 1))] = Y - Yrec;
+                const RowStore scales(alocY + (inchunk ? (BWD ? p0 - (MB - 1) : p0) : 0), inchunk ? MB * 8 : 0);
+                if (KEEP) scales.one((unsigned)(lane & (MB - 1)) * 8u, 0, Y - Yrec);
 #pragma unroll
                 for (int i = 0; i < MB; ++i) {
                     position(i);
-                    if (keep) rows.pair(lane_row, (BWD ? MB - 1 - i : i) * C * 16, ylast, qn[i]);
+                    if (KEEP) rows.pair(lane_row, (BWD ? MB - 1 - i : i) * C * 16, ylast, qn[i]);
                 }
+#pragma unroll
+                for (int i = 0; i < MB; ++i) e[i] = en[i];
             } else {
 #pragma unroll
                 for (int i = 0; i < MB; ++i) {
@@ -253,13 +254,13 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
                         qn[i] = 0.0;
                     }
                 }
+#pragma unroll
+                for (int i = 0; i < MB; ++i) e[i] = en[i];
             }
             lds_barrier();   // end of the block: the new window rows and the helper's sums for the next block are there
             r += BWD ? -nb : nb;
             t = tn;
             ++nblk;
-#pragma unroll
-            for (int i = 0; i < MB; ++i) e[i] = en[i];
             if (__builtin_expect(t == tstart, 0)) {
                 record(t, ck1 + (size_t)istart * ckstride, ckY1 + istart);
                 start_rows();
@@ -342,15 +343,16 @@ __global__ __launch_bounds__(128, spec2_waves_per_simd(CT, NKW)) void k_spec2(Pa
     }
     if (!RETRY || !job.mend) {
         const int w = RETRY ? job.warm : first_warm(p, b, warm);
-        if (dir == 0) spec2_task<CT, NKW, false>(p, lds_raw, b, j, w, false);
-        else spec2_task<CT, NKW, true>(p, lds_raw, b, j, w, false);
+        if (!both) spec2_task<CT, NKW, false, false>(p, lds_raw, b, j, w, false);
+        else if (dir == 0) spec2_task<CT, NKW, false, true>(p, lds_raw, b, j, w, false);
+        else spec2_task<CT, NKW, true, true>(p, lds_raw, b, j, w, false);
         return;
     }
     if (!spec_bad(job, dir ? j + 1 : j) || spec_bad(job, dir ? j + 2 : j - 1)) return;
     int jj = j;
     for (int n = 0; n < SPEC_RUN_MAX; ++n) {  // a run of boundaries is mended as in k_spec
-        if (dir == 0) spec2_task<CT, NKW, false>(p, lds_raw, b, jj, 0, true);
-        else spec2_task<CT, NKW, true>(p, lds_raw, b, jj, 0, true);
+        if (dir == 0) spec2_task<CT, NKW, false, true>(p, lds_raw, b, jj, 0, true);
+        else spec2_task<CT, NKW, true, true>(p, lds_raw, b, jj, 0, true);
         const int nx = dir ? jj - 1 : jj + 1;
         if (nx < 0 || nx >= job.nint || !spec_bad(job, dir ? nx + 1 : nx)) break;
         __threadfence();

@@ -200,18 +200,21 @@ __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const
         if (__builtin_expect(nb == MB, 1)) {  // a whole block: nothing is decided per position
 #pragma unroll
             for (int i = 0; i < MB; ++i) position(i);
+            // (either kind of block takes over the next rows itself, before stores whose number differs: see spec_task)
+#pragma unroll
+            for (int i = 0; i < MB; ++i) e[i] = en[i];
         } else {
 #pragma unroll
             for (int i = 0; i < MB; ++i) {
                 if (i < nb) position(i);
                 else qn[i] = NINF;
             }
+#pragma unroll
+            for (int i = 0; i < MB; ++i) e[i] = en[i];
         }
         lds_wave_fence();
         t += nb;
         if (t - tf >= FT - 1) flush();
-#pragma unroll
-        for (int i = 0; i < MB; ++i) e[i] = en[i];
         if (!WHOLE && __builtin_expect(t == lo, 0)) record(p.ckA + ((size_t)b * (p.N + 1) + chunk) * ckstride);
     }
     if (tf <= t) flush();
