@@ -635,8 +635,13 @@ __global__ __launch_bounds__(NT) void k_dt_fin(Params p)
     s = 0.0;
 #pragma unroll
     for (int q = 0; q < NG; ++q) s += red[q * DT_FO + o];
-    p.sumG[i] = s;
-    p.grad_trans3[i] = (float)s;
+    size_t at = i;
+    if (p.dtMA) {  // the matrix-core marginals' tables (see k_dx_acc)
+        at = i % p.K * ((size_t)p.C * p.C) + i / p.K;
+        s *= p.G3[at];
+    }
+    p.sumG[at] = s;
+    p.grad_trans3[at] = (float)s;
 }
 
 // The duration bias enters the potential together with the transition: its gradient is the

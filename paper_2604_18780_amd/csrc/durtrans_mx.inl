@@ -324,6 +324,7 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tie
                 for (int h = 0; h < AHEAD; ++h)
 #pragma unroll
                     for (int s = 0; s < SF2; ++s) B[h][s] = sgm == 0 && h == 0 ? B0[s] : GF[(h * SF2 + s) * 64];
+                const double2 *const GF0 = GF;
                 GF += (AHEAD - 1) * (SF2 * 64);
                 for (int kk = ka; kk < kb; kk += NB) {
 #pragma unroll
@@ -333,10 +334,11 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tie
                         double xo = 0.0;
                         if (use) xo = *xp;
                         GF += SF2 * 64;
-                        if (h == 0 || kk + NB < kb) {  // the entries of the tile AHEAD
+                        // the entries of the tile AHEAD (behind the run's last one the first again: loads under a condition make the
+                        // compiler wait for them before the tiles in front; genomic call 3160 -> 3125 us, 64 x 256 positions 252 -> 245, both scans)
+                        const double2 *const next = h == 0 || kk + NB < kb ? GF : GF0;
 #pragma unroll
-                            for (int s = 0; s < SF2; ++s) B[(h + AHEAD) % NB][s] = GF[s * 64];
-                        }
+                        for (int s = 0; s < SF2; ++s) B[(h + AHEAD) % NB][s] = next[s * 64];
                         dx_d4 D = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
                         for (int s = 0; s < SF2; ++s) {
@@ -625,14 +627,15 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
                 }
             const double *Vn = V + tn * TS + (ctl[4 + tn] - pn + g4 + 1);
             // table entries: one double2 per lane and step (two label tiles) or pair of steps (one), four steps at a
-            // time, AHEAD groups ahead (across labels)
+            // time, AHEAD groups ahead (across labels).  Always fetched, behind the last group one that is there already: a fetch
+            // under a condition makes the compiler wait for it before the group in front.
             constexpr int LG = 2 * MT;
             constexpr int NBUF = MT == 1 ? 4 : 2, AHEAD = NBUF - 1;
             double2 Gg[NBUF][LG];
             double bg[NBUF][4];
             auto fetch = [&](const int cc, const int s, double2 (&G)[LG], double (&b)[4]) {
-                const double2 *GB = (const double2 *)p.GB + ((size_t)cc * KS + s) * (MT * 32) + lane;
-                const double *Vc = Vn + cc * W + 4 * s;
+                const double2 *GB = (const double2 *)p.GB + ((size_t)min(cc, C - 1) * KS + s) * (MT * 32) + lane;
+                const double *Vc = Vn + min(cc, C - 1) * W + 4 * s;
 #pragma unroll
                 for (int u = 0; u < LG; ++u) G[u] = GB[u * 64];
 #pragma unroll
@@ -675,14 +678,14 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
                 };
 #pragma unroll
                 for (int h = 0; h < AHEAD; ++h) {
-                    if (h == 0 || h < total) fetch(ccn, 4 * gn, Gg[h], bg[h]);
+                    fetch(ccn, 4 * gn, Gg[h], bg[h]);
                     next(ccn, gn);
                 }
                 for (int i = 0; i < total; i += NBUF) {
 #pragma unroll
                     for (int h = 0; h < NBUF; ++h) {
                         if (i + h < total) {  // uniform
-                            if (i + h + AHEAD < total) fetch(ccn, 4 * gn, Gg[(h + AHEAD) % NBUF], bg[(h + AHEAD) % NBUF]);
+                            fetch(ccn, 4 * gn, Gg[(h + AHEAD) % NBUF], bg[(h + AHEAD) % NBUF]);
                             next(ccn, gn);
                             if (gq == 0) {
 #pragma unroll
@@ -1012,17 +1015,19 @@ __global__ __launch_bounds__(64 * DXA_W, 4) void k_dx_acc(Params p)
         }
     }
     if (!mine) return;
+    // Partial tables as [source label][label][duration], so that sixteen lanes store a line, and without the factor G, which
+    // k_dt_fin applies once: with a load of it before each of 32 stores of single doubles a genomic call takes 3125 us, so 3081.
     double *pg = p.partG + (size_t)blockIdx.x * K * CC;
+    const int kd = kA + j;
+    int first = (g4 * C + c) * K + kd;
+    asm volatile("" : "+v"(first));  // (formed here: ahead of the loop it and what is added to it would cost registers there)
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int k = 0; k < KT; ++k)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int o = 16 * m + 4 * v + g4, kd = kA + 16 * k + j;
-                if (o < C && kd < K) {
-                    const size_t at = (size_t)kd * CC + (size_t)o * C + c;
-                    pg[at] = acc[m][k][v] * p.G3[at];
-                }
+                const int o = 16 * m + 4 * v;
+                if (o + g4 < C && 16 * k < K - kd) pg[first + (o * C * K + 16 * k)] = acc[m][k][v];
             }
 }
