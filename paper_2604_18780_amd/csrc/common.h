@@ -185,6 +185,12 @@ __device__ __forceinline__ int safe_exponent(double m)
     return e;
 }
 
+// A whole number of a stored scale, or of a sum of them, as an integer.  Scales are relative to an end of their interval or of the
+// sequence: each is as large as what all the positions to there gain (up to 433 bits a position), and only what they add up to lies
+// near a double's range.  So the limit is the integers' (met by scores outside the supported range alone), and no part of an exponent
+// is cut off before the others are added.
+__device__ __forceinline__ int whole_exponent(const double e) { return (int)fmin(fmax(e, -0x1p30), 0x1p30); }
+
 __device__ __forceinline__ void lds_barrier()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");

@@ -243,8 +243,8 @@ __global__ __launch_bounds__(MGD_NT, 4) void k_mg_dur_mx(Params p, int nlg, int 
     double *const Q = V + LW * RG * 16;            // [2][LW][MGD_QS] q of the step's positions
     double *const rowF = Q + 2 * LW * MGD_QS;      // [Delta + K]    per row lo + 1 + i: factor in [1, 2) ...
     double *const tabF = rowF + Delta + K;         // per interval the rows reach into, and one for row L: the same at its upper end
-    double *const tabE = tabF + K / Delta + 4;
-    int *const rowE = (int *)(tabE + K / Delta + 4);  // [Delta + K] ... and exponent of its scale
+    int *const tabE = (int *)(tabF + K / Delta + 4);
+    int *const rowE = (int *)(tabF + 2 * (K / Delta + 4));  // [Delta + K] ... and exponent of its scale
     int *const Es = rowE + Delta + K;              // [NG][LW]       exponent of a group of rows w0 + i
     int *const Fs = Es + LW * NG;                  // [4 steps][LW]  exponent of a group of positions g0 + i
     int *const nbl = Fs + LW * 4 * steps;          // [nblk][LW]     block exponents
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(MGD_NT, 4) void k_mg_dur_mx(Params p, int nlg, int 
         const double top = i == nj || iv + i == (L - 1) / Delta ? 0.0 : p.ckYB[(size_t)b * (N + 1) + iv + i + 1];
         const double lf = (p.ckYA[(size_t)b * (N + 1) + iv] + top) - h.logZ * LOG2E, fl = floor(lf);
         tabF[i] = exp2(lf - fl);
-        tabE[i] = fmin(fmax(fl, -100000.0), 100000.0);
+        tabE[i] = whole_exponent(fl);
     }
     for (int i = tid; i < nblk * LW; i += MGD_NT) nbl[i] = i == tid ? nb_first : block_exponent(i);
     __syncthreads();
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(MGD_NT, 4) void k_mg_dur_mx(Params p, int nlg, int 
                 const bool last = lo + s == L;
                 const int jj = last ? nj : (int)((unsigned)s / (unsigned)Delta);
                 rowF[i] = tabF[jj];
-                rowE[i] = (int)tabE[jj] + (last ? 0 : (int)rowY[u]);
+                rowE[i] = tabE[jj] + (last ? 0 : (int)rowY[u]);
             }
         }
     }
@@ -438,7 +438,7 @@ __global__ __launch_bounds__(64 * W, TL == 2 ? 3 : 4) void k_mg_te(Params p)
     // kappa(t,t) = exp((Y_alpha + Y_beta) ln2 - logZ): the stored scales are whole numbers relative to the interval's ends
     const double kx = (p.ckYA[(size_t)b * (N + 1) + iv] + (hi == L ? 0.0 : p.ckYB[(size_t)b * (N + 1) + iv + 1])) - h.logZ * LOG2E;
     const double kxi = floor(kx), kfrac = exp2(kx - kxi);
-    const int kint = (int)fmin(fmax(kxi, -100000.0), 100000.0);
+    const int kint = whole_exponent(kxi);
     const int pi = lane / LB, pl = lane % LB;  // position (from the upper end) and label of the lane
     int cc[TL];
 #pragma unroll
@@ -660,7 +660,7 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
 #pragma unroll
         for (int u = 0; u < NK; ++u) {
             const int d = g * NK + u, sp = tb + d;
-            const int e = (int)fmin(fmax((sp == L ? 0.0 : ys[u]) - ybt, -100000.0), 100000.0) + (sp == L ? nsL : ns[u]) - nbt;
+            const int e = whole_exponent((sp == L ? 0.0 : ys[u]) - ybt) + (sp == L ? nsL : ns[u]) - nbt;
             const double val = fmin(ldexp(sp == L ? vL : vr[u], e), DBL_MAX);
             if (cval && d < K && sp <= L) ring[(r + d) * RS + c] = val;
         }
@@ -736,7 +736,7 @@ __global__ __launch_bounds__(64, mg_waves_per_simd(CT, NKW)) void k_mg_wave(Para
     // the stored scales are whole numbers, so it is one fixed factor in [1, 2) times a power of two
     const double kx = (Y0 + Ytop) - logZ * LOG2E, kxi = floor(kx);
     const double kfrac = exp2(kx - kxi);
-    const int kint = (int)fmin(fmax(kxi, -100000.0), 100000.0);
+    const int kint = whole_exponent(kxi);
     auto kappa_of = [&]() { return ldexp(kfrac, kint + (int)(ya + yb)); };
 
     int t = tb;

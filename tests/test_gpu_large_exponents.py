@@ -1,0 +1,89 @@
+"""GPU parity where an interval gains more than 100 000 bits: the statistics of stored rows put together powers of two
+that cancel, and none of them may be cut off before the others are added.
+
+Scores are large or the interval is long, all within the 300 nats per position that the entry points promise.  Tolerances as in
+test_gpu_parity: 1e-5 relative on logZ, 1e-4 on what belongs to a position, 1e-4 of the largest entry on the accumulated gradients; against
+the per-interval recurrence 2e-6 (the same sums in another order, rounded once to float; scales of 2^18 bits in doubles move a term by
+2^18 ln 2 * 2^-53 = 2e-11).
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2604_18780_amd import binding as sb
+from paper_2604_18780_amd import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+NAMES = ("grad_emis", "grad_trans", "grad_dur", "pos_marg")
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def scores(B, T, K, C, sd, trans=None):
+    w = synth.small_random(T + K + C, B, T, K, C, ragged=False, scale=sd)
+    if trans is not None:
+        w.trans[:] = trans
+    return w
+
+
+def close(got, r, scale=1.0):
+    assert np.abs(got[0] - r.logz).max() <= 1e-5 * np.abs(r.logz).max()
+    for g, n in zip(got[1:], NAMES):
+        ref = getattr(r, n)
+        top = scale if n in ("grad_emis", "pos_marg") else max(1.0, np.abs(ref).max())
+        assert np.all(np.isfinite(g)), n
+        print(f"       {n}: {np.abs(g - ref).max() / top:.1e}", flush=True)
+        assert np.abs(g - ref).max() <= 1e-4 * top, n
+
+
+def check(w, delta, least_bits):
+    B, T, K, C = w.B, w.T, w.K, w.C
+    r = oracle.fwd_bwd(w.emis, w.lengths, w.trans, w.dur)
+    x = (dev(w.emis), dev(w.lengths), dev(w.trans), dev(w.dur))
+    ws = sb.alloc_workspace(B, T, K, C, delta, 1, DEV)
+    # (what the sequence gains above the path that stays with the mean scores, which the centring takes out)
+    bits = (r.logz - T * w.emis.astype(np.float64).mean(axis=(1, 2))) / np.log(2) / T * delta
+    print(f"[case] B={B} T={T} K={K} C={C} delta={delta}: about {bits.min():.0f} bits an interval", flush=True)
+    assert bits.min() > least_bits
+    out = sb.semicrf_fwd_bwd(*x, None, delta, workspace=ws)
+    assert sb.semicrf_scan_report(ws, B, T, K, C, delta, 1)[0].min().item() > 0  # the stored rows are used
+    assert sb.semicrf_seq_report(ws, B, T, K, C, delta, 1)[0].sum().item() == 0
+    close([o.double().cpu().numpy() for o in out], r)
+    recur = sb.semicrf_fwd_bwd(*x, None, delta, sb.SEMICRF_CENTER | sb.SEMICRF_MARGINALS_INTERVAL)
+    for a, b in zip(out[1:], recur[1:]):
+        assert (a - b).abs().max().item() <= 2e-6 * max(1.0, b.abs().max().item())
+
+
+@pytest.mark.parametrize("T,K,C,delta,sd", [
+    (4096, 128, 8, 4096, 20.0),
+    (3000, 128, 13, 3000, 20.0),   # nine to sixteen labels
+    (3000, 128, 20, 3000, 20.0),   # more
+    (3000, 130, 3, 1500, 60.0),    # two intervals
+])
+def test_transition_and_emission_sums_of_long_durations(T, K, C, delta, sd):
+    check(scores(1, T, K, C, sd), delta, 100_000)
+
+
+# Scaling blocks of sixteen positions: the durations' matrix-core form.  Transitions are not centred.
+@pytest.mark.parametrize("T,K,C,delta,bits", [
+    (8192, 128, 8, 8192, 100_000),
+    (8192, 300, 8, 4096, 50_000),  # two intervals: rows above the next one's lower end are two intervals away from their scale's
+    (8192, 130, 4, 4096, 50_000),
+    (8000, 128, 20, 5000, 100_000),
+])
+def test_duration_sums_of_long_durations(T, K, C, delta, bits):
+    check(scores(1, T, K, C, 0.05, 14.0), delta, bits)
+
+
+@pytest.mark.parametrize("T,K,C,delta,sd", [
+    (4096, 16, 8, 4096, 20.0),  # (an interval in parts)
+    (3000, 60, 24, 3000, 20.0),
+    (2000, 8, 64, 2000, 30.0),
+])
+def test_statistics_of_short_durations(T, K, C, delta, sd):
+    check(scores(1, T, K, C, sd), delta, 100_000)
+
