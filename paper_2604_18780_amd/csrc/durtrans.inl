@@ -574,8 +574,7 @@ __global__ __launch_bounds__(1024) void k_dt_acc(Params p)
                     const double lf = (yA0 + yB) - logZ * LOG2E;
                     const double fl = floor(lf);
                     const int sh = nb[(size_t)js * C + o] - nb[(size_t)jt * C + o];
-                    const double ef = fmin(fmax(fl, -100000.0), 100000.0);
-                    v = fmin(ldexp(rowV[(size_t)s * C + o] * exp2(lf - fl), sh + (int)ef), DBL_MAX);
+                    v = fmin(ldexp(rowV[(size_t)s * C + o] * exp2(lf - fl), sh + whole_exponent(fl)), DBL_MAX);
                 }
                 Vp[i] = v;
             }

@@ -843,7 +843,7 @@ __global__ __launch_bounds__(NT) void k_dx_emis(Params p)
             const double fa = floor(ya), fb = floor(yb);
             p.dtMA[row0 + tt] = exp2(ya - fa);
             p.dtMB[row0 + tt] = exp2(yb - fb);
-            p.dtE[row0 + tt] = make_int2((int)fmin(fmax(fa, -1.0e8), 1.0e8), (int)fmin(fmax(fb, -1.0e8), 1.0e8));
+            p.dtE[row0 + tt] = make_int2(whole_exponent(fa), whole_exponent(fb));
         }
     }
     const int per = (hi - lo + 7) / 8;

@@ -92,7 +92,7 @@ __device__ __forceinline__ void mg_dur_vector(const Params &p, double *lds_raw, 
                     const double lf = (yA0 + yBs[s - lo - 1]) - logZ * LOG2E;
                     const double fl = floor(lf);
                     f = exp2(lf - fl);
-                    e = (int)fmin(fmax(fl, -100000.0), 100000.0);
+                    e = whole_exponent(fl);
                     js = s / J;
                 }
                 vf[rr] = f;

@@ -1,4 +1,4 @@
-"""GPU parity where an interval gains more than 100 000 bits: the statistics of stored rows put together powers of two
+"""GPU parity where an interval, or a segment, gains more than 100 000 bits: the statistics of stored rows put together powers of two
 that cancel, and none of them may be cut off before the others are added.
 
 Scores are large or the interval is long, all within the 300 nats per position that the entry points promise.  Tolerances as in
@@ -27,6 +27,15 @@ def scores(B, T, K, C, sd, trans=None):
     w = synth.small_random(T + K + C, B, T, K, C, ragged=False, scale=sd)
     if trans is not None:
         w.trans[:] = trans
+    return w
+
+
+def segments(T, K, C, s, segment):
+    """One label at +s and the others at -s, plus unit noise, in segments of that many positions."""
+    w = scores(1, T, K, C, 1.0)
+    label = np.repeat(np.arange(T // segment + 1) % C, segment)[:T]
+    w.emis -= np.float32(s)
+    w.emis[0, np.arange(T), label] += np.float32(2 * s)
     return w
 
 
@@ -87,3 +96,27 @@ def test_duration_sums_of_long_durations(T, K, C, delta, bits):
 def test_statistics_of_short_durations(T, K, C, delta, sd):
     check(scores(1, T, K, C, sd), delta, 100_000)
 
+
+# A segment of several hundred positions of one label far above the mean: the scale's power of two and the label's cancel.
+@pytest.mark.parametrize("K,C,delta", [(512, 3, 0), (512, 8, 1600)])
+def test_segments_of_long_durations(K, C, delta):
+    w = segments(3000, K, C, 250.0, 1000)
+    r = oracle.fwd_bwd(w.emis, w.lengths, w.trans, w.dur)
+    x = (dev(w.emis), dev(w.lengths), dev(w.trans), dev(w.dur))
+    print(f"[case] K={K} C={C} delta={delta}", flush=True)
+    out = sb.semicrf_fwd_bwd(*x, None, delta)
+    close([o.double().cpu().numpy() for o in out], r)
+
+
+@pytest.mark.parametrize("T,K,C", [
+    (2000, 3000, 2),    # sizes without a matrix-core form
+    (3000, 512, 3),
+    (330_000, 4, 2),    # scales of more than 100 000 000 bits
+])
+def test_duration_dependent_transitions(T, K, C):
+    w = segments(T, K, C, 250.0, 1000)
+    trans3 = synth.duration_transitions(w, C, 0.3)
+    r = oracle.fwd_bwd_durtrans(w.emis, w.lengths, trans3, w.dur)
+    print(f"[case] T={T} K={K} C={C}: logZ {r.logz}", flush=True)
+    out = sb.semicrf_fwd_bwd_durtrans(dev(w.emis), dev(w.lengths), dev(trans3), dev(w.dur))
+    close([o.double().cpu().numpy() for o in out], r)
