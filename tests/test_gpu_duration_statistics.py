@@ -21,17 +21,17 @@ DEV = "cuda:0"
 
 @pytest.mark.parametrize("B,T,K,C,delta,scale", [
     (1, 700, 128, 3, 0, 1.0),       # four labels a workgroup, two ranges of durations
-    (2, 900, 257, 4, 0, 1.0),       # ... of twelve tiles
-    (1, 1500, 512, 4, 0, 1.0),      # ... of sixteen
-    (3, 500, 129, 8, 0, 1.0),       # one group of labels, one part
+    (2, 900, 257, 4, 0, 1.0),       # ... of five tiles of sixteen, in two parts
+    (1, 1500, 512, 4, 0, 1.0),      # ... of eight
+    (3, 500, 129, 8, 0, 1.0),       # one group of labels, two parts of the durations
     (1, 800, 192, 7, 104, 1.0),     # intervals that begin inside a tile of sixteen positions
     (2, 1100, 256, 8, 0, 1.0),
-    (1, 1300, 300, 8, 0, 1.0),      # two parts of the durations
+    (1, 1300, 300, 8, 0, 1.0),      # three parts of the durations
     (1, 2000, 512, 8, 0, 1.0),
     (2, 600, 128, 24, 0, 1.0),      # three groups of labels
     (1, 700, 200, 13, 0, 1.0),      # two, the second not full
     (1, 400, 160, 8, 8, 1.0),       # intervals shorter than a tile and than the durations
-    (1, 333, 140, 5, 1, 1.0),       # ... of one position
+    (1, 333, 140, 5, 1, 1.0),       # ... of one position: 666 workgroups, so the vector form
     (2, 400, 128, 6, 0, 12.0),      # scaling blocks shorter than a tile
     (2, 300, 300, 8, 0, 30.0),
     (2, 260, 128, 20, 0, 12.0),
