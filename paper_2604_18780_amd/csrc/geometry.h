@@ -25,6 +25,14 @@ constexpr int MG_KS = 8;   // stored-row marginals: durations per thread of the 
 constexpr int FIN_SLICES = 4;    // workgroups per sequence of the carry / mean reduction (sums behind the mean per slice)
 constexpr int MG_SIMDS = 1024;  // SIMDs of the chip (256 compute units of four)
 
+// LDS bytes of the vector form of the duration statistics for that many labels and strips of MG_KS durations at once: rows of a group,
+// their factors, exponents and scaling blocks, and the absolute scales of the rows that the interval can touch.
+constexpr size_t mg_dur_lds(int labels, int strips, int K, int Delta)
+{
+    const size_t vr = (size_t)MG_TG + (size_t)MG_KS * strips + 3;
+    return ((size_t)MG_TG * labels + vr * (labels | 3) + MG_TG + 2 * vr + 2 * (size_t)Delta + (size_t)K) * 8;
+}
+
 // Tasks of the one-wave stored-row marginals a SIMD holds: two where the duration strip of a lane (NKW) and the
 // transition tiles (CT) leave the kernel within half the register file, else one.
 constexpr int mg_waves_per_simd(int CT, int NKW) { return (CT <= 32 && NKW <= 32) ? 2 : 1; }

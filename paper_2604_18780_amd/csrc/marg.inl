@@ -200,8 +200,11 @@ __global__ __launch_bounds__(1024) void k_mg_dur(Params p)
 // take 84 clocks of a SIMD (64 the product alone; a power of two by integer adds or by a multiplication is no cheaper), which
 // makes 65 us of the 139 at K = 512, C = 8, T = 400 000 (vector form: 220); the rest is a workgroup's tables and first
 // rows, the steps' barriers, and the sums over s at the end.  KB = 16, one workgroup per compute unit: 151.
-// Sequences with J < 16 take the vector form in shares of the same labels and durations, 1.06 times as long a call as when
-// one workgroup did an interval (scores N(0, 20^2), 50 000 positions, K = 512, C = 8: 1802 -> 1919 us).
+// Sequences with J < 16 take the vector form: a share is a group of labels with all durations, or with one of vparts ranges of them
+// where a workgroup's LDS or threads do not hold that, and a sequence's first workgroups take its shares one after the other, all
+// sequences side by side: every parts-th workgroup alone would meet in a quarter of the compute units.  Calls with scores N(0, 20^2), in
+// shares of the parts' own durations, which each fetch scales and positions again / by every parts-th workgroup / so: K = 512, C = 8,
+// 50 000 positions 1900 / 2430 / 1790 us, eight such sequences 8440 / 7000 / 4715; K = 256, C = 16, two 1566 / 1890 / 1285.
 constexpr int MGD_NT = 512;
 constexpr int MGD_J = 16;  // shortest scaling block of this form: a tile's positions
 constexpr int mgd_fill(int KB, int LW) { return ((8 / LW) * KB + 4 + 3) / 4 * 4; }  // groups of rows a step of 64 positions reads, whole steps
@@ -216,25 +219,26 @@ constexpr size_t mgd_lds(int KB, int LW, int K, int Delta)
 }
 
 template <int KB, int LW>
-__global__ __launch_bounds__(MGD_NT, 4) void k_mg_dur_mx(Params p, int nlg, int parts, int kb)
+__global__ __launch_bounds__(MGD_NT, 4) void k_mg_dur_mx(Params p, int nlg, int parts, int kb, int vparts)
 {
     typedef double double4_t __attribute__((ext_vector_type(4)));
     constexpr int RANGES = 8 / LW, RG = mgd_ring(KB, LW), FILL = mgd_fill(KB, LW), NST = FILL / 4, ROWS = 64;
     extern __shared__ double lds_raw[];
     const int tid = threadIdx.x;
     const int K = p.K, C = p.C, N = p.N, Delta = p.Delta;
-    const int part = blockIdx.x % parts, lg = blockIdx.x / parts % nlg, task = blockIdx.x / (parts * nlg);
-    const int b = task / N, iv = task % N;
+    const int b = blockIdx.x, x = blockIdx.y;
     const SeqHdr h = p.hdr[b];
     const int L = h.L, J = h.J;
-    const int lo = iv * Delta;
-    if (lo >= L) return;
     if (!(p.spec_ok[b * 2] && p.spec_ok[b * 2 + 1])) return;  // the interval kernel takes this sequence
     if (J < MGD_J) {
-        const int strips = (K + MG_KS - 1) / MG_KS;  // the same labels and about the same durations, by vector multiply-adds
-        mg_dur_vector(p, lds_raw, b, iv, lg * LW, min(LW, C - lg * LW), strips * part / parts, strips * (part + 1) / parts);
+        const int vpart = x % vparts, l0 = x / vparts % nlg * LW, viv = x / (vparts * nlg), strips = (K + MG_KS - 1) / MG_KS;
+        if (viv < N && viv * Delta < L)
+            mg_dur_vector(p, lds_raw, b, viv, l0, min(LW, C - l0), strips * vpart / vparts, strips * (vpart + 1) / vparts);
         return;
     }
+    const int part = x % parts, lg = x / parts % nlg, iv = x / (parts * nlg);
+    const int lo = iv * Delta;
+    if (lo >= L) return;
     const int hi = min(lo + Delta, L), smax = min(hi - 1 + K, L);  // rows v_s, lo < s <= smax
     const int ljb = __builtin_ctz(J), blk0 = lo >> ljb, nblk = (smax >> ljb) - blk0 + 1;
     const int g0 = lo >> 4, w0 = g0 + part * RANGES * kb;  // first group of positions, of rows

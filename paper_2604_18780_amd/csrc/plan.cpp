@@ -169,8 +169,7 @@ int make_plan(int B, int T, int K, int C, int ckpt_interval, int want_grad, Plan
     // 0.18 against 0.33 ms; K = 32, C = 64: 0.09 against 0.19 ms; K = 16, C = 24, short sequences: level.  The
     // route is planned whenever every task has its slot and the sizes fit its kernels.
     const int mg_nsl = (K + MG_KS - 1) / MG_KS;
-    const size_t mg_vr = (size_t)MG_TG + (size_t)MG_KS * mg_nsl + 3;
-    pl->lds_mg_dur = (MG_TG * c + mg_vr * (c | 3) + MG_TG + 2 * mg_vr + 2 * (size_t)pl->Delta + k) * sizeof(double);
+    pl->lds_mg_dur = mg_dur_lds(C, mg_nsl, K, pl->Delta);
     const size_t longest = ((size_t)3 * 64 * c + pl->Delta) * sizeof(double);  // (an interval's scales next to 64 rows: bounds its length)
     const int mg_gw = 64 / pow2_ge8(C > 64 ? 64 : C);
     const int mg_per_simd = mg_waves_per_simd(C, (K + mg_gw - 1) / mg_gw);  // of the one-wave kernel (K < 128)

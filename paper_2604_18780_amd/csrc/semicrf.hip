@@ -420,9 +420,20 @@ int launch_mg_dur_k(const Params &p, const Plan &pl, hipStream_t st)
 {
     const int nlg = (p.C + LW - 1) / LW, blocks = (p.K + 15) / 16, each = KB * (8 / LW), parts = (blocks + each - 1) / each;
     const int waves = parts * (8 / LW), kb = (blocks + waves - 1) / waves;  // blocks of sixteen durations per wave
-    const size_t mx = mgd_lds(KB, LW, p.K, p.Delta), lds = mx > pl.lds_mg_dur ? mx : pl.lds_mg_dur;
-    if (lds > LDS_LIMIT || mg_dur_vector_pays(p, p.B * p.N * nlg * parts)) {
-        const int mg_nsl = (p.K + MG_KS - 1) / MG_KS;
+    const int mg_nsl = (p.K + MG_KS - 1) / MG_KS;
+    // Sequences with short scaling blocks take the vector form, in the fewest ranges of the durations that fit a workgroup's threads and
+    // leave the compute unit two workgroups, if the matrix-core form does (which sequences those are is known on the device only).
+    const size_t mx = mgd_lds(KB, LW, p.K, p.Delta), room = mx > LDS_LIMIT / 2 ? mx : LDS_LIMIT / 2;
+    const int labels = p.C < LW ? p.C : LW;
+    int vparts = 0, share = 0;
+    size_t vec = 0;
+    do {
+        share = (mg_nsl + vparts) / (vparts + 1);  // strips of a range
+        ++vparts;
+        vec = mg_dur_lds(labels, share, p.K, p.Delta);
+    } while (vparts < parts && (vec > room || labels * share > MGD_NT));
+    const size_t lds = mx > vec ? mx : vec;
+    if (lds > LDS_LIMIT || labels * share > MGD_NT || mg_dur_vector_pays(p, p.B * p.N * nlg * parts)) {
         int ntd = (p.C * mg_nsl + 63) / 64 * 64;
         if (ntd < NT) ntd = NT;  // the extra threads help staging the rows
         if (hipFuncSetAttribute((const void *)k_mg_dur, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pl.lds_mg_dur) !=
@@ -433,7 +444,7 @@ int launch_mg_dur_k(const Params &p, const Plan &pl, hipStream_t st)
     }
     if (hipFuncSetAttribute((const void *)k_mg_dur_mx<KB, LW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return SEMICRF_ELAUNCH;
-    hipLaunchKernelGGL((k_mg_dur_mx<KB, LW>), dim3(p.B * p.N * nlg * parts), dim3(MGD_NT), lds, st, p, nlg, parts, kb);
+    hipLaunchKernelGGL((k_mg_dur_mx<KB, LW>), dim3(p.B, p.N * nlg * parts), dim3(MGD_NT), lds, st, p, nlg, parts, kb, vparts);
     return SEMICRF_OK;
 }
 

@@ -1,5 +1,6 @@
 """GPU parity of the duration, transition and emission statistics of long maximal durations (K >= 128), by the form that a call's
-sizes lead to: tiles on the matrix cores, or vector multiply-adds where there are many workgroups with short intervals.
+sizes lead to: tiles on the matrix cores, or vector multiply-adds where there are many workgroups with short intervals; and
+inside the matrix-core launch vector multiply-adds for sequences with scaling blocks of fewer than sixteen positions.
 
 Every case states its form, and the host's rule is worked out again from the sizes.  Tolerances as in test_gpu_duration_statistics:
 1e-4 of the largest entry on the accumulated gradients and 1e-4 on what belongs to a position, against the oracle; 2e-6 of the largest entry
@@ -89,3 +90,27 @@ def test_vector_form_where_there_are_many_workgroups(B, T, K, C, delta):
 ])
 def test_intervals_of_several_chunks(T, K, C, delta):
     check(2, T, K, C, delta)
+
+
+# Scaling blocks of fewer than sixteen positions (scores of N(0, 12^2)) in the matrix-core launch.
+@pytest.mark.parametrize("B,T,K,C,delta", [
+    (1, 2000, 512, 8, 1568),  # ranges of half of the durations: an interval's scales and all of them do not fit
+    (1, 1700, 505, 6, 1600),  # ... which are not equal
+    (1, 900, 512, 8, 392),    # one range, in the first of four parts
+    (2, 400, 200, 13, 160),   # two groups of labels, the second not full
+    (1, 600, 512, 3, 150),
+])
+def test_short_scaling_blocks_in_the_matrix_launch(B, T, K, C, delta):
+    assert form(B, T, K, C, delta) == "matrix"
+    check(B, T, K, C, delta, scale=12.0)
+
+
+# Sequences of both kinds in one call: the first workgroups form other sequences' sums before their own.
+@pytest.mark.parametrize("T,K,C,delta,scale", [
+    (700, 300, 8, 100, (1.0, 12.0, 1.0, 12.0)),
+    (600, 200, 13, 60, (12.0, 1.0, 1.0)),
+    (500, 512, 4, 120, (1.0, 1.0, 12.0)),
+])
+def test_short_scaling_blocks_in_some_sequences(T, K, C, delta, scale):
+    assert form(len(scale), T, K, C, delta) == "matrix"
+    check(len(scale), T, K, C, delta, scale)
