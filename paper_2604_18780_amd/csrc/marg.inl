@@ -194,7 +194,7 @@ __global__ __launch_bounds__(1024) void k_mg_dur(Params p)
 // into the frame of group g by one power of two, 2^(E[w] - F[g]), per label and pair of groups, with all exponents
 // combined in whole numbers before anything is formed.  (A group lies in one scaling block, J >= 16; its row v may be the first of
 // the next block, brought down by the step the scan itself makes there.)
-// Wave (label of LW, range of kb * 16 durations, kb <= KB): kb + 1 tiles of P in its accumulators for the whole interval, one
+// Wave (label of LW, range of kb * 16 durations, kb <= KB = 8): kb + 1 tiles of P in its accumulators for the whole interval, one
 // workgroup of eight waves per (interval, group of labels, part of the durations), two of them on a compute unit.  Rows go
 // through LDS in a ring of RG groups, fetched a step of 64 positions ahead.  A product and the conversion of its operand element
 // take 84 clocks of a SIMD (64 the product alone; a power of two by integer adds or by a multiplication is no cheaper), which
@@ -207,22 +207,24 @@ __global__ __launch_bounds__(1024) void k_mg_dur(Params p)
 // 50 000 positions 1900 / 2430 / 1790 us, eight such sequences 8440 / 7000 / 4715; K = 256, C = 16, two 1566 / 1890 / 1285.
 constexpr int MGD_NT = 512;
 constexpr int MGD_J = 16;  // shortest scaling block of this form: a tile's positions
-constexpr int mgd_fill(int KB, int LW) { return ((8 / LW) * KB + 4 + 3) / 4 * 4; }  // groups of rows a step of 64 positions reads, whole steps
-constexpr int mgd_ring(int KB, int LW) { return mgd_fill(KB, LW) + 4 <= 16 ? 16 : (mgd_fill(KB, LW) + 4 <= 32 ? 32 : 64); }
+constexpr int MGD_KB = 8;
+constexpr int mgd_fill(int LW) { return ((8 / LW) * MGD_KB + 4 + 3) / 4 * 4; }  // groups of rows a step of 64 positions reads, whole steps
+constexpr int mgd_ring(int LW) { return mgd_fill(LW) + 4 <= 16 ? 16 : 32; }
+static_assert(mgd_fill(8) + 4 <= mgd_ring(8) && mgd_fill(4) + 4 <= mgd_ring(4), "a step's rows next to those of the one before");
 constexpr int MGD_QS = 72;                                                            // doubles of a label's positions of a step
 constexpr int mgd_steps(int Delta) { return (Delta + 15 + 15) / 64 + 1; }             // most steps of an interval
-constexpr size_t mgd_lds(int KB, int LW, int K, int Delta)
+constexpr size_t mgd_lds(int LW, int K, int Delta)
 {
-    return ((size_t)LW * mgd_ring(KB, LW) * 16 + 2 * LW * MGD_QS + Delta + K + 2 * ((size_t)K / Delta + 4)) * sizeof(double) +
-           ((size_t)LW * (4 * mgd_steps(Delta) + mgd_fill(KB, LW)) + (size_t)LW * 4 * mgd_steps(Delta) + Delta + K +
+    return ((size_t)LW * mgd_ring(LW) * 16 + 2 * LW * MGD_QS + Delta + K + 2 * ((size_t)K / Delta + 4)) * sizeof(double) +
+           ((size_t)LW * (4 * mgd_steps(Delta) + mgd_fill(LW)) + (size_t)LW * 4 * mgd_steps(Delta) + Delta + K +
             (size_t)LW * ((Delta + K) / MGD_J + 2)) * sizeof(int);
 }
 
-template <int KB, int LW>
+template <int LW>
 __global__ __launch_bounds__(MGD_NT, 4) void k_mg_dur_mx(Params p, int nlg, int parts, int kb, int vparts)
 {
     typedef double double4_t __attribute__((ext_vector_type(4)));
-    constexpr int RANGES = 8 / LW, RG = mgd_ring(KB, LW), FILL = mgd_fill(KB, LW), NST = FILL / 4, ROWS = 64;
+    constexpr int KB = MGD_KB, RANGES = 8 / LW, RG = mgd_ring(LW), FILL = mgd_fill(LW), NST = FILL / 4, ROWS = 64;
     extern __shared__ double lds_raw[];
     const int tid = threadIdx.x;
     const int K = p.K, C = p.C, N = p.N, Delta = p.Delta;
@@ -410,8 +412,8 @@ __global__ __launch_bounds__(MGD_NT, 4) void k_mg_dur_mx(Params p, int nlg, int 
 // position and label.  K = 512, C = 8, T = 400 000:
 // 33 us (4.9 TB/s), against 69 with the rows staged in LDS for a thread per pair of labels and one per label for the sums.
 constexpr int mgt_seg(int C) { return C <= 8 ? 64 : (C <= 16 ? 32 : 16); }  // S
-// (at most 46 KB: within the default dynamic LDS)
 constexpr size_t mgt_lds(int W, int C) { return ((size_t)W * mgt_seg(C) * C + (2 * W + 2) * (size_t)C + (size_t)C * C) * sizeof(double); }
+static_assert(mgt_lds(8, 8) <= 65536 && mgt_lds(8, 16) <= 65536 && mgt_lds(4, 32) <= 65536, "what a kernel may have without asking");
 
 template <int LB, int TL, int W>
 __global__ __launch_bounds__(64 * W, TL == 2 ? 3 : 4) void k_mg_te(Params p)

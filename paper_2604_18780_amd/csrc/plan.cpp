@@ -170,12 +170,11 @@ int make_plan(int B, int T, int K, int C, int ckpt_interval, int want_grad, Plan
     // route is planned whenever every task has its slot and the sizes fit its kernels.
     const int mg_nsl = (K + MG_KS - 1) / MG_KS;
     pl->lds_mg_dur = mg_dur_lds(C, mg_nsl, K, pl->Delta);
-    const size_t longest = ((size_t)3 * 64 * c + pl->Delta) * sizeof(double);  // (an interval's scales next to 64 rows: bounds its length)
     const int mg_gw = 64 / pow2_ge8(C > 64 ? 64 : C);
     const int mg_per_simd = mg_waves_per_simd(C, (K + mg_gw - 1) / mg_gw);  // of the one-wave kernel (K < 128)
     const bool rows = !lowmem && (kind == 3 || kind == 1);
     pl->rows = rows && spec_applies(K, C) && ntask <= (size_t)pl->nslot && c * mg_nsl <= 1024 &&
-               pl->lds_mg_dur <= LDS_LIMIT && longest <= LDS_LIMIT;
+               pl->lds_mg_dur <= LDS_LIMIT;
     const size_t gr = pl->rows ? 1 : 0;
     sz[PL_BLOC] = gr * (size_t)pl->nslot * pl->Delta * 2 * c * 8;
     sz[PL_BLOCY] = gr * (size_t)pl->nslot * pl->Delta * 8;

@@ -415,15 +415,15 @@ int launch_mg(const Params &p, hipStream_t st)
 //   2 x 3000, K = 128, C = 32 (376 workgroups) 163 -> 159; 4 x 50000, K = 150, C = 8 (intervals of 392) 315 -> 286
 bool mg_dur_vector_pays(const Params &p, int workgroups) { return p.K < 192 && p.Delta < 2 * p.K && workgroups > 512; }
 
-template <int KB, int LW>
+template <int LW>
 int launch_mg_dur_k(const Params &p, const Plan &pl, hipStream_t st)
 {
-    const int nlg = (p.C + LW - 1) / LW, blocks = (p.K + 15) / 16, each = KB * (8 / LW), parts = (blocks + each - 1) / each;
+    const int nlg = (p.C + LW - 1) / LW, blocks = (p.K + 15) / 16, each = MGD_KB * (8 / LW), parts = (blocks + each - 1) / each;
     const int waves = parts * (8 / LW), kb = (blocks + waves - 1) / waves;  // blocks of sixteen durations per wave
     const int mg_nsl = (p.K + MG_KS - 1) / MG_KS;
     // Sequences with short scaling blocks take the vector form, in the fewest ranges of the durations that fit a workgroup's threads and
     // leave the compute unit two workgroups, if the matrix-core form does (which sequences those are is known on the device only).
-    const size_t mx = mgd_lds(KB, LW, p.K, p.Delta), room = mx > LDS_LIMIT / 2 ? mx : LDS_LIMIT / 2;
+    const size_t mx = mgd_lds(LW, p.K, p.Delta), room = mx > LDS_LIMIT / 2 ? mx : LDS_LIMIT / 2;
     const int labels = p.C < LW ? p.C : LW;
     int vparts = 0, share = 0;
     size_t vec = 0;
@@ -442,15 +442,15 @@ int launch_mg_dur_k(const Params &p, const Plan &pl, hipStream_t st)
         hipLaunchKernelGGL(k_mg_dur, dim3(p.B * p.N), dim3(ntd), pl.lds_mg_dur, st, p);
         return SEMICRF_OK;
     }
-    if (hipFuncSetAttribute((const void *)k_mg_dur_mx<KB, LW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    if (hipFuncSetAttribute((const void *)k_mg_dur_mx<LW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
         return SEMICRF_ELAUNCH;
-    hipLaunchKernelGGL((k_mg_dur_mx<KB, LW>), dim3(p.B, p.N * nlg * parts), dim3(MGD_NT), lds, st, p, nlg, parts, kb, vparts);
+    hipLaunchKernelGGL((k_mg_dur_mx<LW>), dim3(p.B, p.N * nlg * parts), dim3(MGD_NT), lds, st, p, nlg, parts, kb, vparts);
     return SEMICRF_OK;
 }
 
 int launch_mg_dur(const Params &p, const Plan &pl, hipStream_t st)
 {
-    return p.C <= 4 ? launch_mg_dur_k<8, 4>(p, pl, st) : launch_mg_dur_k<8, 8>(p, pl, st);
+    return p.C <= 4 ? launch_mg_dur_k<4>(p, pl, st) : launch_mg_dur_k<8>(p, pl, st);
 }
 
 // Sizes for which the first warm-up comes from the model, unless the caller has named one.
