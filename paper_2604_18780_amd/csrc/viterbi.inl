@@ -77,7 +77,6 @@ __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const
     const bool cval = c < C;
     const int cc = cval ? c : 0;
     const bool writer = cval && g == 0;
-    const unsigned lane_row = writer ? (unsigned)c * 8u : ROW_NOWHERE;
     const int L = p.hdr[b].L;
     const int lo = WHOLE ? 0 : chunk * p.Delta;
     if (!WHOLE && lo >= L && !(lo == 0 && L == 0)) return;
@@ -183,49 +182,56 @@ __device__ __forceinline__ void vit_task(const Params &p, double *lds_raw, const
                 for (int i = 0; i < MB; ++i) acc[i] = fmax(acc[i], group_max<G::CTP>(far[i]));
             }
         }
-        // (With more than 32 labels through one pointer per lane, to a sink where there is nothing to store: 3222 us for four sequences of
-        // 4000 positions, K = 20, C = 48, in one piece, through the buffer 3350; with 20 labels, K = 30, 1408 against 1287.)
-        const RowStore rows(VV + (size_t)(t + 1) * C, keep ? MB * C * 8 : 0);
-        double *rowp = p.sink + lane;
-        int rstep = 0;
-        if (CT == 64 && keep && writer) {
-            rowp = VV + (size_t)(t + 1) * C + c;
-            rstep = C;
-        }
-        double qn[MB];
-        auto position = [&](const int i) {
-            double x = acc[i];
+        auto block = [&](auto store) {  // store(i, y): V of the block's position i
+            double qn[MB];
+            auto position = [&](const int i) {
+                double x = acc[i];
 #pragma unroll
-            for (int jn = 0; jn < i; ++jn) x = fmax(x, wn[i - 1 - jn] + qn[jn]);
-            const double y = x + e[i].x;  // V_t(c)
-            ylast = y;
-            const double q = R::max_product(y, Treg) + e[i].y;
-            qn[i] = q;
-            ++r;
-            if (writer) ring[r * RS + c] = q;
-            if (CT == 64) __builtin_nontemporal_store(y, rowp + i * rstep);
-            else rows.one(lane_row, i * C * 8, y);
-        };
-        if (__builtin_expect(nb == MB, 1)) {  // a whole block: nothing is decided per position
+                for (int jn = 0; jn < i; ++jn) x = fmax(x, wn[i - 1 - jn] + qn[jn]);
+                const double y = x + e[i].x;  // V_t(c)
+                ylast = y;
+                const double q = R::max_product(y, Treg) + e[i].y;
+                qn[i] = q;
+                ++r;
+                if (writer) ring[r * RS + c] = q;
+                store(i, y);
+            };
+            if (__builtin_expect(nb == MB, 1)) {  // a whole block: nothing is decided per position
 #pragma unroll
-            for (int i = 0; i < MB; ++i) position(i);
-            // (either kind of block takes over the next rows itself, before stores whose number differs: see spec_task)
+                for (int i = 0; i < MB; ++i) position(i);
+                // (either kind of block takes over the next rows itself, before stores whose number differs: see spec_task)
 #pragma unroll
-            for (int i = 0; i < MB && CT < 64; ++i) e[i] = en[i];
-        } else {
+                for (int i = 0; i < MB; ++i) e[i] = en[i];
+            } else {
 #pragma unroll
-            for (int i = 0; i < MB; ++i) {
-                if (i < nb) position(i);
-                else qn[i] = NINF;
+                for (int i = 0; i < MB; ++i) {
+                    if (i < nb) position(i);
+                    else qn[i] = NINF;
+                }
+#pragma unroll
+                for (int i = 0; i < MB; ++i) e[i] = en[i];
             }
-#pragma unroll
-            for (int i = 0; i < MB && CT < 64; ++i) e[i] = en[i];
+        };
+        // The rows of V go out through a buffer that holds just the block's; with 64 label lanes through one pointer per lane, to a sink where
+        // there is nothing to store: the transitions alone take half of a wave's registers there, and a position moves 48 values
+        // between the two halves of the register file, through the buffer 66 (K <= 32).  4 x 4000 positions, K = 20, C = 48: 403 us, through the
+        // buffer 421, in one piece 434 and 454; 20 labels, K = 30, in one piece 1408 and 1287.
+        if constexpr (CT == 64) {
+            double *rowp = p.sink + lane;
+            int rstep = 0;
+            if (keep && writer) {
+                rowp = VV + (size_t)(t + 1) * C + c;
+                rstep = C;
+            }
+            block([&](const int i, const double y) { __builtin_nontemporal_store(y, rowp + i * rstep); });
+        } else {
+            const RowStore rows(VV + (size_t)(t + 1) * C, keep ? MB * C * 8 : 0);
+            const unsigned lane_row = writer ? (unsigned)c * 8u : ROW_NOWHERE;
+            block([&](const int i, const double y) { rows.one(lane_row, i * C * 8, y); });
         }
         lds_wave_fence();
         t += nb;
         if (t - tf >= FT - 1) flush();
-#pragma unroll
-        for (int i = 0; i < MB && CT == 64; ++i) e[i] = en[i];
         if (!WHOLE && __builtin_expect(t == lo, 0)) record(p.ckA + ((size_t)b * (p.N + 1) + chunk) * ckstride);
     }
     if (tf <= t) flush();
