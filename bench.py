@@ -148,7 +148,7 @@ class Problem:
         kernels = {"scans": "k_spec (chunk-parallel forward + backward scans, one launch; stage time "
                             "includes its small verification kernels and the early exits of the retries)",
                    "intervals": (("k_mg_wave (marginals from the stored rows of both scans, one launch)" if w.K < 128 else
-                                  "k_mg_dur + k_mg_te (marginals from the stored rows of both scans, two launches)")
+                                  "k_mg_dur_mx (or k_mg_dur) + k_mg_te (marginals from the stored rows of both scans, two launches)")
                                  if rows_route else
                                  "k_interval_wave / k_interval (per-interval recompute + marginals, one launch)")}
         dom = "scans" if stage[1] >= stage[2] else "intervals"

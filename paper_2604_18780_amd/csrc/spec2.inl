@@ -228,8 +228,9 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
                 if (writer) ring[(BWD ? r - 1 - i : r + 1 + i) * RS + c] = qn[i];
             };
             const int p0 = BWD ? t - 1 - lo : t + 1 - lo;  // slot row of the block's first position
-            // (With 64 labels a position is long next to its store, and a second copy of it only more to load: 8 x 3000 positions, K = 20,
-            // C = 60, band 2, scans repeated 1370 -> 1386 us.)
+            // (Not with 64 labels, whose positions are long next to their stores: a second copy of four positions takes the kernel from 54 to
+            // 67 KB, past the 64 KB of instructions that two compute units hold, that of repeated scans from 107 to 130.  8 x 3000
+            // positions, K = 20, C = 60, band 2, scans repeated 1370 -> 1386 us.)
             if (CT < 64 && __builtin_expect(nb == MB && (BWD || !inchunk || t + MB < hi), 1)) {
                 // a whole block: nothing is decided per position, and it always issues the same stores (as in the one-wave task)
                 const RowStore rows(aloc + (ptrdiff_t)(inchunk ? (BWD ? p0 - (MB - 1) : p0) : 0) * C, inchunk ? MB * C * 16 : 0);
