@@ -435,7 +435,7 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_fwd(Params p, int warm, int tie
 // lies between two of them: the tables of those sums held in registers that only the chain waves need otherwise, the sums
 // formed beside the chains, and rows stored unconditionally took the launch from 1278 to 1190 us (K = 39, C = 6: 672 -> 650).
 // ---------------------------------------------------------------------------
-template <int MT, int SF2>
+template <int MT, int SF2, bool BEHIND>
 __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tier)
 {
     extern __shared__ double lds_raw[];
@@ -627,8 +627,8 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
                 }
             const double *Vn = V + tn * TS + (ctl[4 + tn] - pn + g4 + 1);
             // table entries: one double2 per lane and step (two label tiles) or pair of steps (one), four steps at a
-            // time, AHEAD groups ahead (across labels).  Always fetched, behind the last group one that is there already: a fetch
-            // under a condition makes the compiler wait for it before the group in front.
+            // time, AHEAD groups ahead (across labels).  BEHIND: always fetched, behind the last group one that is there already, as a
+            // fetch under a condition makes the compiler wait for it before the group in front.
             constexpr int LG = 2 * MT;
             constexpr int NBUF = MT == 1 ? 4 : 2, AHEAD = NBUF - 1;
             double2 Gg[NBUF][LG];
@@ -678,14 +678,14 @@ __global__ __launch_bounds__(DX_NT, 2) void k_dx_bwd(Params p, int warm, int tie
                 };
 #pragma unroll
                 for (int h = 0; h < AHEAD; ++h) {
-                    fetch(ccn, 4 * gn, Gg[h], bg[h]);
+                    if (BEHIND || h == 0 || h < total) fetch(ccn, 4 * gn, Gg[h], bg[h]);
                     next(ccn, gn);
                 }
                 for (int i = 0; i < total; i += NBUF) {
 #pragma unroll
                     for (int h = 0; h < NBUF; ++h) {
                         if (i + h < total) {  // uniform
-                            fetch(ccn, 4 * gn, Gg[(h + AHEAD) % NBUF], bg[(h + AHEAD) % NBUF]);
+                            if (BEHIND || i + h + AHEAD < total) fetch(ccn, 4 * gn, Gg[(h + AHEAD) % NBUF], bg[(h + AHEAD) % NBUF]);
                             next(ccn, gn);
                             if (gq == 0) {
 #pragma unroll

@@ -878,22 +878,28 @@ int launch_dx_fwd_any(const Params &p, const DxGeom &g, hipStream_t st, int warm
     }
 }
 
-template <int MT, int SF2>
+template <int MT, int SF2, bool BEHIND>
 int launch_dx_bwd(const Params &p, const DxGeom &g, hipStream_t st, int warm, int tier)
 {
-    if (hipFuncSetAttribute((const void *)k_dx_bwd<MT, SF2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g.lds_b) != hipSuccess)
+    if (hipFuncSetAttribute((const void *)k_dx_bwd<MT, SF2, BEHIND>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g.lds_b) != hipSuccess)
         return SEMICRF_ELAUNCH;
-    hipLaunchKernelGGL((k_dx_bwd<MT, SF2>), dim3((p.B * p.N + DX_TASKS - 1) / DX_TASKS), dim3(DX_NT), g.lds_b, st, p, warm, tier);
+    hipLaunchKernelGGL((k_dx_bwd<MT, SF2, BEHIND>), dim3((p.B * p.N + DX_TASKS - 1) / DX_TASKS), dim3(DX_NT), g.lds_b, st, p, warm, tier);
     return SEMICRF_OK;
 }
+
+// Up to eight labels a wave of the backward scan has one label, K / 16 groups of table entries a block: where these are few, the fetches
+// behind the last of them (up to four groups) cost more than the waits they save.  Calls without them / with them, us: K = 8, C = 4, 16 x 2000
+// 393 / 397; K = 24, C = 8, 16 x 3000 337 / 344; K = 64, C = 8, 8 x 20 000 549 / 553; K = 144, C = 8, 2 x 20 000 412.3 / 413.7; K = 200,
+// C = 8, 4 x 20 000 684.8 / 683.8; K = 512, C = 6, 2 x 20 000 952 / 944.
+constexpr int DX_FEW = 160;
 
 int launch_dx_bwd_any(const Params &p, const DxGeom &g, hipStream_t st, int warm, int tier)
 {
     switch (g.ncg) {
-    case 1: return launch_dx_bwd<1, 1>(p, g, st, warm, tier);
-    case 2: return launch_dx_bwd<1, 2>(p, g, st, warm, tier);
-    case 3: return launch_dx_bwd<2, 3>(p, g, st, warm, tier);
-    default: return launch_dx_bwd<2, 4>(p, g, st, warm, tier);
+    case 1: return p.K <= DX_FEW ? launch_dx_bwd<1, 1, false>(p, g, st, warm, tier) : launch_dx_bwd<1, 1, true>(p, g, st, warm, tier);
+    case 2: return launch_dx_bwd<1, 2, true>(p, g, st, warm, tier);
+    case 3: return launch_dx_bwd<2, 3, true>(p, g, st, warm, tier);
+    default: return launch_dx_bwd<2, 4, true>(p, g, st, warm, tier);
     }
 }
 
