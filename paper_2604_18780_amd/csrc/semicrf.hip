@@ -271,25 +271,25 @@ void launch_spec_cmp(const Params &p, hipStream_t st, int ndir, int tier, int ne
 
 // Chunk-parallel scan: returns 1 when it does not apply to these sizes.
 // two: the form with two waves per task.
-template <int CT, int NKW, bool RETRY>
+template <int CT, int NKW, bool RETRY, bool ROWS>
 int launch_spec_tasks(const Params &p, hipStream_t st, bool both, int warm, int tier, int rest, bool two)
 {
     const int ndir = both ? 2 : 1;
     if (two) {
         const size_t lds = spec2_lds_doubles<CT, NKW>() * sizeof(double);
-        if (hipFuncSetAttribute((const void *)k_spec2<CT, NKW, RETRY>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        if (hipFuncSetAttribute((const void *)k_spec2<CT, NKW, RETRY, ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds) != hipSuccess)
             return SEMICRF_ELAUNCH;
-        hipLaunchKernelGGL((k_spec2<CT, NKW, RETRY>), dim3(p.B * p.N * ndir), dim3(128), lds, st, p, both ? 1 : 0,
+        hipLaunchKernelGGL((k_spec2<CT, NKW, RETRY, ROWS>), dim3(p.B * p.N * ndir), dim3(128), lds, st, p, both ? 1 : 0,
                            warm, tier, rest);
         return SEMICRF_OK;
     }
     constexpr int SW = spec_waves(CT, NKW);
     const size_t lds = SW * scan_lds_doubles(CT, NKW) * sizeof(double);
-    if (hipFuncSetAttribute((const void *)k_spec<CT, NKW, RETRY>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    if (hipFuncSetAttribute((const void *)k_spec<CT, NKW, RETRY, ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds) != hipSuccess)
         return SEMICRF_ELAUNCH;
-    hipLaunchKernelGGL((k_spec<CT, NKW, RETRY>), dim3((p.B * p.N + SW - 1) / SW * ndir), dim3(64 * SW), lds, st, p,
+    hipLaunchKernelGGL((k_spec<CT, NKW, RETRY, ROWS>), dim3((p.B * p.N + SW - 1) / SW * ndir), dim3(64 * SW), lds, st, p,
                        both ? 1 : 0, warm, tier, rest);
     return SEMICRF_OK;
 }
@@ -321,8 +321,13 @@ int launch_spec_k(const Params &p, hipStream_t st, bool both, int warm, int tier
     bool pays = deep;
     if (tier == 0) pays = few || (both ? (NKW == 16 ? CT <= 32 : (NKW == 64 ? CT <= 24 : CT == 64 && tasks <= MG_SIMDS)) : deep);
     const bool two = (p.spec2 == 1 || (p.spec2 == 0 && pays)) && spec2_lds_doubles<CT, NKW>() * sizeof(double) <= LDS_LIMIT;
-    if (tier == 0) rc = launch_spec_tasks<CT, NKW, false>(p, st, both, warm, tier, rest, two);
-    else rc = launch_spec_tasks<CT, NKW, true>(p, st, both, warm, tier, rest, two);
+    if (p.fuse) {  // rows are kept
+        if (tier == 0) rc = launch_spec_tasks<CT, NKW, false, true>(p, st, both, warm, tier, rest, two);
+        else rc = launch_spec_tasks<CT, NKW, true, true>(p, st, both, warm, tier, rest, two);
+    } else {
+        if (tier == 0) rc = launch_spec_tasks<CT, NKW, false, false>(p, st, both, warm, tier, rest, two);
+        else rc = launch_spec_tasks<CT, NKW, true, false>(p, st, both, warm, tier, rest, two);
+    }
     if (rc != SEMICRF_OK) return rc;
     launch_spec_cmp(p, st, both ? 2 : 1, tier, 3);
     return check_launch();

@@ -74,9 +74,9 @@ __device__ __forceinline__ bool spec_bad(const SpecJob &s, const int m) { return
 // One scan task of the chunk-parallel scan, one wave (window and time blocking as above).
 // repair: the task restarts from the state its neighbour in scan order REACHED at their common boundary (no
 // warm-up: exact if the neighbour's own start was).
-// KEEP: a call with gradients, whose tasks store their rows.  The tasks of a forward-only one do not even issue the stores (196 -> 207 us), but
-// for the mended intervals of a repair, which have no copy of the code of their own: with one, 11 x 3001 positions, K = 37,
-// C = 19, band 2 take 119.5 us instead of 120.4, and gradients 537 instead of 535 (8 x 3000, K = 20, C = 60, band 2).
+// KEEP: a call that keeps rows, whose tasks store theirs.  The others, scores and gradients of more tasks than there are row slots, do not even
+// issue the stores (which would store nothing: scores at the genomic shape 196 -> 207 us; gradients of 55 x 6836 positions, K = 8,
+// C = 25, 774 -> 752).
 template <int CT, int NKW, bool BWD, bool KEEP>
 __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, const int b, const int j,
                                           const int warm, const bool repair)
@@ -322,9 +322,10 @@ __device__ __forceinline__ void spec_task(const Params &p, double *lds_raw, cons
 // 227 or 264 us depending on the shape of the kernel before).  The directions fill one half of the grid each, so that
 // a SIMD with two tasks has one of each.
 // rest: only the sequences the lock-step kernel (k_mscan, launched before) leaves out
+// ROWS: KEEP of its tasks; kernels of their own for the same reason (all four kinds of tasks in one: speech 263 -> 268 us).
 // RETRY: the later attempts; a kernel of its own, so that the first attempt is not compiled around their cases
 // (one kernel for both: 304 -> 338 us at the genomic shape).
-template <int CT, int NKW, bool RETRY>
+template <int CT, int NKW, bool RETRY, bool ROWS>
 __global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, NKW)) void k_spec(Params p, int both, int warm, int tier, int rest)
 {
     constexpr int SW = spec_waves(CT, NKW);
@@ -345,9 +346,8 @@ __global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, N
     }
     if (!RETRY || !job.mend) {
         const int w = RETRY ? job.warm : first_warm(p, b, warm);
-        if (!both) spec_task<CT, NKW, false, false>(p, lds, b, j, w, false);
-        else if (dir == 0) spec_task<CT, NKW, false, true>(p, lds, b, j, w, false);
-        else spec_task<CT, NKW, true, true>(p, lds, b, j, w, false);
+        if (dir == 0) spec_task<CT, NKW, false, ROWS>(p, lds, b, j, w, false);
+        else spec_task<CT, NKW, true, ROWS>(p, lds, b, j, w, false);
         return;
     }
     // A run of adjacent boundaries that disagreed is taken by ONE wave, the task that starts at the first of them
@@ -358,8 +358,8 @@ __global__ __launch_bounds__(64 * spec_waves(CT, NKW), spec_waves_per_simd(CT, N
     if (!spec_bad(job, dir ? j + 1 : j) || spec_bad(job, dir ? j + 2 : j - 1)) return;
     int jj = j;
     for (int n = 0; n < SPEC_RUN_MAX; ++n) {
-        if (dir == 0) spec_task<CT, NKW, false, true>(p, lds, b, jj, 0, true);
-        else spec_task<CT, NKW, true, true>(p, lds, b, jj, 0, true);
+        if (dir == 0) spec_task<CT, NKW, false, ROWS>(p, lds, b, jj, 0, true);
+        else spec_task<CT, NKW, true, ROWS>(p, lds, b, jj, 0, true);
         const int nx = dir ? jj - 1 : jj + 1;              // the next task in scan order ...
         if (nx < 0 || nx >= job.nint || !spec_bad(job, dir ? nx + 1 : nx)) break;  // ... starts where this one ended
         __threadfence();  // the reached state this wave has just written is what it restarts from

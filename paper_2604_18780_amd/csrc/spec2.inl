@@ -329,7 +329,7 @@ __device__ __forceinline__ void spec2_task(const Params &p, double *lds_raw, con
     }
 }
 
-template <int CT, int NKW, bool RETRY>
+template <int CT, int NKW, bool RETRY, bool ROWS>
 __global__ __launch_bounds__(128, spec2_waves_per_simd(CT, NKW)) void k_spec2(Params p, int both, int warm, int tier, int rest)
 {
     extern __shared__ double lds_raw[];
@@ -346,16 +346,15 @@ __global__ __launch_bounds__(128, spec2_waves_per_simd(CT, NKW)) void k_spec2(Pa
     }
     if (!RETRY || !job.mend) {
         const int w = RETRY ? job.warm : first_warm(p, b, warm);
-        if (!both) spec2_task<CT, NKW, false, false>(p, lds_raw, b, j, w, false);
-        else if (dir == 0) spec2_task<CT, NKW, false, true>(p, lds_raw, b, j, w, false);
-        else spec2_task<CT, NKW, true, true>(p, lds_raw, b, j, w, false);
+        if (dir == 0) spec2_task<CT, NKW, false, ROWS>(p, lds_raw, b, j, w, false);
+        else spec2_task<CT, NKW, true, ROWS>(p, lds_raw, b, j, w, false);
         return;
     }
     if (!spec_bad(job, dir ? j + 1 : j) || spec_bad(job, dir ? j + 2 : j - 1)) return;
     int jj = j;
     for (int n = 0; n < SPEC_RUN_MAX; ++n) {  // a run of boundaries is mended as in k_spec
-        if (dir == 0) spec2_task<CT, NKW, false, true>(p, lds_raw, b, jj, 0, true);
-        else spec2_task<CT, NKW, true, true>(p, lds_raw, b, jj, 0, true);
+        if (dir == 0) spec2_task<CT, NKW, false, ROWS>(p, lds_raw, b, jj, 0, true);
+        else spec2_task<CT, NKW, true, ROWS>(p, lds_raw, b, jj, 0, true);
         const int nx = dir ? jj - 1 : jj + 1;
         if (nx < 0 || nx >= job.nint || !spec_bad(job, dir ? nx + 1 : nx)) break;
         __threadfence();
